@@ -1,9 +1,10 @@
 // Sparse multi-head attention of SPT (section 4.1: Eq. 6, Algorithm 1; section 5.1: Algorithms 2
 // and 3, CSR with a fixed row length) for gfx950.
 //
-// None of this is a dense contraction: every query gathers its own 128/256-byte rows through an
-// index list, so the kernels are organised around coalesced rows, LDS residency and the 64-lane
-// wavefront, not around MFMA.
+// Codes and index lists are integer work; the attention products over the kept keys run as dense
+// tiles on the matrix cores (mha_dense.hip) unless very few of many keys are kept.  For those shapes
+// every query gathers its own 128/256-byte rows through its index list here: coalesced rows, LDS
+// residency and the 64-lane wavefront.
 //
 //   pq_assign_kernel        one thread per (vector, codebook): fused distance + argmin, codebooks in LDS
 //   topl_lane_kernel        Algorithm 3 bit-sliced, one LANE per query: inverted code table in LDS,
@@ -20,10 +21,9 @@
 //                           wavefront per query / per key), for sequences too large for LDS
 #include <math.h>
 
-#include "../../include/spt_mha.h"
+#include "mha_host.hpp"
 #include "profile.hpp"
 #include "spt_device.hpp"
-#include "spt_host.hpp"
 
 namespace spt {
 namespace {
@@ -1136,8 +1136,18 @@ __global__ __launch_bounds__(kSeqThreads) void seq_accum_kernel(const uint16_t* 
 }
 
 // ---------------------------------------------------------------- host side
+// Dense tiles on the matrix cores (mha_dense.hip) cost n multiply-adds per query and channel where
+// the gathering kernels here cost L.  Measured, forward + backward without the codes and lists, us:
+//   S 512, n 512, dh 64    L 8: 373 gathering, 293 dense   L 32: 462, 316   L 64: 637, 262
+//   S 512, n 512, dh 128   L 8: 528, 567                   L 32: 759, 578
+//   S 128, n 2048, dh 64   L 32: 2382, 1436                L 64: 4411, 1469
+// (the lists regrouped by key are what the long sequences pay for).  Dense tiles load list entries
+// four at a time, so they want L >= 4.
+bool use_dense(const spt_mha_shape_t& s) { return s.L >= 4 && s.n <= 32 * s.L; }
+
 struct MhaWorkspace {
   float* dS;          // [S][n][L]
+  float2* maxes;      // dense tiles: [S][ceil(n/4)] largest |A|, |dS| of four queries
   int32_t* toff;      // [S][n + 1]
   uint32_t* tlist;    // [S][n * L]
   uint32_t* gbits;    // [S][n][ceil(n/32)] when the transposition does not fit LDS, else null
@@ -1159,9 +1169,14 @@ MhaWorkspace plan_mha(const spt_mha_shape_t& s, void* ws) {
   size_t off = 0;
   const size_t rows = (size_t)s.S * s.n;
   w.dS = reinterpret_cast<float*>(p + off);        off += align256(rows * s.L * sizeof(float));
+  w.maxes = nullptr; w.toff = nullptr; w.tlist = nullptr; w.gbits = nullptr;
+  if (use_dense(s)) {
+    w.maxes = reinterpret_cast<float2*>(p + off);  off += align256((size_t)s.S * ((s.n + 3) / 4) * sizeof(float2));
+    w.bytes = off;
+    return w;
+  }
   w.toff = reinterpret_cast<int32_t*>(p + off);    off += align256((size_t)s.S * (s.n + 1) * sizeof(int32_t));
   w.tlist = reinterpret_cast<uint32_t*>(p + off);  off += align256(rows * s.L * sizeof(uint32_t));
-  w.gbits = nullptr;
   if (!transpose_fits_lds(s.n, s.L)) {
     w.gbits = reinterpret_cast<uint32_t*>(p + off);
     off += align256(rows * ((s.n + 31) / 32) * sizeof(uint32_t));
@@ -1312,6 +1327,7 @@ int spt_mha_attn_fwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
   {
     ScopedKernelTimer tm(kSlotMhaFwd, st);
     uint16_t* y = static_cast<uint16_t*>(Y);
+    if (use_dense(*shape)) return mha_dense_fwd(*shape, Q, K, V, idx, A, Y, st) == hipSuccess ? SPT_OK : SPT_ERR_HIP;
     if (seq_resident(shape->n, shape->dh)) {
       if (shape->dh == 64) {
         launch_seq_dots<64, false>(*shape, q, k, idx, nullptr, A, st);
@@ -1344,6 +1360,17 @@ int spt_mha_attn_bwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
   const uint16_t* k = static_cast<const uint16_t*>(K);
   const uint16_t* v = static_cast<const uint16_t*>(V);
   const uint16_t* dy = static_cast<const uint16_t*>(dY);
+  if (w.maxes) {
+    hipError_t e;
+    {
+      ScopedKernelTimer tm(kSlotMhaBwdQ, st);
+      e = mha_dense_bwd_q(*shape, K, V, dY, idx, A, w.dS, w.maxes, dQ, st);
+    }
+    if (e != hipSuccess) return SPT_ERR_HIP;
+    ScopedKernelTimer tm(kSlotMhaBwdKV, st);
+    e = mha_dense_bwd_kv(*shape, Q, dY, idx, A, w.dS, w.maxes, dK, dV, st);
+    return e == hipSuccess ? SPT_OK : SPT_ERR_HIP;
+  }
   float* Amut = const_cast<float*>(A);   // read-only in the backward instantiation
   const bool resident = seq_resident(shape->n, shape->dh);
   {

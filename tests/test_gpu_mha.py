@@ -122,6 +122,19 @@ def test_whole_path_matches_oracle(sh):
     torch.cuda.synchronize()
 
 
+# Dense-tile kernels: edges of the 32-key tiles, 256- and 512-key chunks and 32-query blocks, list
+# lengths around the four-entry vectors and the 64-entry steps; and, where few keys of many are
+# kept, the gathering kernels (resident, and too large for LDS).
+EDGES = [(n, dh, L) for dh in (64, 128) for n, L in
+         ((31, 4), (33, 5), (96, 33), (255, 63), (256, 64), (257, 65), (511, 67), (512, 129), (513, 130), (770, 255),
+          (1025, 256), (600, 9), (1030, 3))]
+
+
+@pytest.mark.parametrize("n,dh,L", EDGES)
+def test_attention_tile_edges(n, dh, L):
+    test_whole_path_matches_oracle(custom_mha_shape(1, 2, n, dh, L, seed=n + L))
+
+
 def test_backward_is_deterministic_and_workspace_reusable():
     sh = custom_mha_shape(2, 2, 200, 64, 40, seed=21)
     inp = make_mha_inputs(sh)
