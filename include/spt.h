@@ -84,8 +84,8 @@ size_t spt_workspace_bytes(const spt_shape_t* shape, int which);
  *   b_r    in   fp32 [N] or NULL (no bias)
  *   idx    out  int32 [T,k]
  *   logits out  fp32 [T,N] or NULL (diagnostic copy of the fp32 logits)
- *   ws: spt_workspace_bytes(shape, SPT_WS_ROUTER) bytes (holds the logits between the two
- *       kernels; not touched when `logits` is given).                               */
+ *   ws: spt_workspace_bytes(shape, SPT_WS_ROUTER) bytes (holds the logits or parts of their
+ *       sums between the two kernels; not touched when `logits` is given).                               */
 int spt_router_topk(const spt_shape_t* shape, const void* X, const float* W_r,
                     const float* b_r, int32_t* idx, float* logits, void* ws, size_t ws_bytes,
                     void* stream);

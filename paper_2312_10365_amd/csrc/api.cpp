@@ -34,7 +34,7 @@ size_t spt_workspace_bytes(const spt_shape_t* shape, int which) {
     case SPT_WS_BUCKET: return bucket_ws_bytes(*shape);
     case SPT_WS_FWD: return plan_fwd(*shape, nullptr).bytes;
     case SPT_WS_BWD: return plan_bwd(*shape, nullptr).bytes;
-    case SPT_WS_ROUTER: return align256((size_t)shape->T * shape->N * sizeof(float));
+    case SPT_WS_ROUTER: return router_ws_bytes(*shape);
     case SPT_WS_LORA_FWD: return plan_lora(*shape, nullptr, false).bytes;
     case SPT_WS_LORA_BWD: return plan_lora(*shape, nullptr, true).bytes;
     case SPT_WS_BALANCE: return plan_balance(*shape, nullptr).bytes;
@@ -51,10 +51,9 @@ int spt_router_topk(const spt_shape_t* shape, const void* X, const float* W_r, c
   if ((b_r && !aligned(b_r, 4)) || (logits && !aligned(logits, 4))) return SPT_ERR_ARG;
   if (!logits) {
     if (!aligned(ws, 256)) return SPT_ERR_ARG;
-    if (ws_bytes < align256((size_t)shape->T * shape->N * sizeof(float))) return SPT_ERR_WORKSPACE;
-    logits = static_cast<float*>(ws);
+    if (ws_bytes < router_ws_bytes(*shape)) return SPT_ERR_WORKSPACE;
   }
-  const hipError_t e = run_router_topk(*shape, X, W_r, b_r, idx, logits, static_cast<hipStream_t>(stream));
+  const hipError_t e = run_router_topk(*shape, X, W_r, b_r, idx, logits, static_cast<float*>(ws), static_cast<hipStream_t>(stream));
   return e == hipSuccess ? SPT_OK : SPT_ERR_HIP;
 }
 

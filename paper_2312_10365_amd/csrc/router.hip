@@ -5,8 +5,8 @@
 // additions can move the fp64 sum, by parts in 1e-16 -- far below the fp32 rounding step.
 // The k largest keys win; equal keys go to the lower block id; ids are emitted ascending.
 //
-// Kernel 1 (logits): fp64 matrix cores, v_mfma_f64_16x16x4_f64.  A workgroup of 4 wavefronts
-// owns 64 tokens x 32 blocks, each wavefront a 32 x 16 part (2 MFMA tiles) over the whole of d.
+// Kernel 1 (logits): fp64 matrix cores, v_mfma_f64_16x16x4_f64.  A workgroup owns 16 MT tokens x 16 NT
+// blocks and its KS wavefronts split d; their sums are added through LDS in wavefront order.
 // Operands go straight from global memory to registers: a lane reads 8
 // consecutive bf16 of one token row and the matching 8 rows of one W_r column, widens them to
 // fp64, and feeds 8 MFMAs; which real k sits in which MFMA k-slot is the same for both
@@ -14,7 +14,8 @@
 // Kernel 2 (top-k): one wavefront per token; the k-th largest key is found by a 32-step radix
 // search on the order-preserving integer image of the fp32 keys, the keys above it are selected,
 // ties at it go to the lowest block ids: block b is selected iff fewer than k blocks b' have
-// key[b'] > key[b] or (key[b'] == key[b] and b' < b).
+// key[b'] > key[b] or (key[b'] == key[b] and b' < b).  With at most 32 blocks one workgroup holds all
+// logits of its tokens and selects in the same launch.
 #include "spt_device.hpp"
 #include "spt_host.hpp"
 #include "profile.hpp"
@@ -23,150 +24,24 @@ namespace spt {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// NT = MFMA tiles per wavefront along the block axis: a wavefront owns 32 tokens x 16*NT
-// blocks, a workgroup (2 x 2 wavefronts) 64 tokens x 32*NT blocks.  NT = 1 doubles the number
-// of wavefronts per SIMD over NT = 2, which is what hides the global-load latency here: the
-// operands are loaded two 32-wide k-chunks ahead of the MFMAs that consume them.
-template <int NT, int KSPLIT>
-__global__ __launch_bounds__(256 * KSPLIT) void router_logits_kernel(
-    const uint16_t* __restrict__ X, const float* __restrict__ Wr, const float* __restrict__ br,
-    int T, int d, int N, float* __restrict__ logits) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3, kpart = tid >> 8;
-  const int r16 = lane & 15, slot = lane >> 4;
-  const int tok0 = blockIdx.x * 64 + (wave >> 1) * 32;
-  const int blk0 = blockIdx.y * (32 * NT) + (wave & 1) * (16 * NT);
-  const int kbeg = kpart * (d / KSPLIT);  // d is a multiple of 64: each part a multiple of 32
-
-  const uint16_t* xrow[2];
-  const float* wcol[NT];
-  bool bok[NT];
-#pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    const int t = min(tok0 + 16 * m + r16, T - 1);  // clamped rows are computed but never stored
-    xrow[m] = X + (size_t)t * d + kbeg + 8 * slot;
-  }
-#pragma unroll
-  for (int n = 0; n < NT; ++n) {
-    const int b = blk0 + 16 * n + r16;
-    bok[n] = b < N;
-    wcol[n] = Wr + (size_t)(kbeg + 8 * slot) * N + (bok[n] ? b : 0);
-  }
-  f64x4 acc[2][NT];
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int n = 0; n < NT; ++n) acc[m][n] = f64x4{0.0, 0.0, 0.0, 0.0};
-
-  // Register ring of three k-chunks: chunk c is consumed while c+1 and c+2 are in flight.
-  uint4 xq[3][2];
-  float wq[3][NT][8];
-  auto fetch = [&](int st, int k0) {
-#pragma unroll
-    for (int m = 0; m < 2; ++m) xq[st][m] = *reinterpret_cast<const uint4*>(xrow[m] + k0);
-#pragma unroll
-    for (int n = 0; n < NT; ++n)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) wq[st][n][e] = wcol[n][(size_t)(k0 + e) * N];
-  };
-  auto consume = [&](int st) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      double a[2], b[NT];
-#pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        const uint32_t w32 = reinterpret_cast<const uint32_t*>(&xq[st][m])[e >> 1];
-        a[m] = (double)((e & 1) ? hi_bf16(w32) : lo_bf16(w32));
-      }
-#pragma unroll
-      for (int n = 0; n < NT; ++n) b[n] = bok[n] ? (double)wq[st][n][e] : 0.0;
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-          acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b[n], acc[m][n], 0, 0, 0);
-    }
-  };
-  const int chunks = d / (32 * KSPLIT);
-  fetch(0, 0);
-  if (chunks > 1) fetch(1, 32);
-  int c = 0;
-  for (; c + 3 <= chunks; c += 3) {  // three chunks per trip keeps the ring slots static
-    if (c + 2 < chunks) fetch(2, (c + 2) * 32);
-    consume(0);
-    if (c + 3 < chunks) fetch(0, (c + 3) * 32);
-    consume(1);
-    if (c + 4 < chunks) fetch(1, (c + 4) * 32);
-    consume(2);
-  }
-  // chunks % 3 leftovers: ring slots 0 and 1 already hold them
-  if (c < chunks) consume(0);
-  if (c + 1 < chunks) consume(1);
-
-  if (KSPLIT > 1) {  // sum the k-parts through LDS, in part order, into part 0
-    __shared__ double red[(KSPLIT - 1) * 4 * 2 * NT * 4 * 64];
-    if (kpart > 0) {
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            red[((((kpart - 1) * 4 + wave) * 2 + m) * NT + n) * 256 + v * 64 + lane] = acc[m][n][v];
-    }
-    __syncthreads();
-    if (kpart > 0) return;
-#pragma unroll
-    for (int p = 1; p < KSPLIT; ++p)
-#pragma unroll
-      for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            acc[m][n][v] += red[((((p - 1) * 4 + wave) * 2 + m) * NT + n) * 256 + v * 64 + lane];
-  }
-
-  // D layout of the 16x16 fp64 tile: lane holds column (lane & 15), rows 4*v + (lane >> 4).
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-      const int b = blk0 + 16 * n + r16;
-      if (b >= N) continue;
-      const double bias = br ? (double)br[b] : 0.0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int t = tok0 + 16 * m + 4 * v + slot;
-        if (t < T) logits[(size_t)t * N + b] = (float)(acc[m][n][v] + bias);
-      }
-    }
+// Top-k of one token by one wavefront, NPL keys per lane (block b = lane + 64 n, logit[n]; lanes past N
+// ignored).  The k-th largest key is found by a radix search on the order-preserving integer image of
+// the fp32 keys (32 steps of compare + ballot + popcount: the largest T with at least k keys >= T);
+// every key above it is selected, and of the keys equal to it the lowest block ids, as many as are
+// still missing.  Ids are emitted ascending.
+__device__ __forceinline__ uint32_t key_image(float logit, int flags) {   // larger key <=> larger image, never 0
+  const float key = ((flags & 1) ? fabsf(logit) : logit) + 0.0f;           // -0 -> +0: equal keys, equal images
+  const uint32_t bits = __float_as_uint(key);
+  const uint32_t u = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
+  return u ? u : 1u;                       // (only a NaN with all mantissa bits set maps to 0)
 }
-
-// One wavefront per token, NPL keys per lane (block b = lane + 64 n).  The k-th largest key is
-// found by a radix search on the order-preserving integer image of the fp32 keys (32 steps of
-// compare + ballot + popcount: the largest T with at least k keys >= T); every key above it is
-// selected, and of the keys equal to it the lowest block ids, as many as are still missing.  Ids
-// are emitted ascending.  (Rank-by-counting, the first version, compared every key with every
-// other: 1400 instructions per token at N = 128 against about 250.)
 template <int NPL>
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ logits, int T, int N,
-                                                   int k, int flags, int32_t* __restrict__ idx) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = blockIdx.x * 4 + wave;
-  if (t >= T) return;                      // whole wavefront; the kernel has no barrier
-  uint32_t u[NPL];                         // larger key <=> larger u; 0 for lanes past N (below every real key)
+__device__ __forceinline__ void select_topk(const float (&logit)[NPL], int lane, int N, int k, int flags,
+                                            int32_t* __restrict__ out) {
+  uint32_t u[NPL];                         // 0 for lanes past N: below every real key
 #pragma unroll
-  for (int n = 0; n < NPL; ++n) {
-    const int b = lane + 64 * n;
-    u[n] = 0u;
-    if (b < N) {
-      const float l = logits[(size_t)t * N + b];
-      const float key = ((flags & 1) ? fabsf(l) : l) + 0.0f;       // -0 -> +0: equal keys, equal images
-      const uint32_t bits = __float_as_uint(key);
-      u[n] = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
-      if (u[n] == 0u) u[n] = 1u;           // (only a NaN with all mantissa bits set maps to 0)
-    }
-  }
+  for (int n = 0; n < NPL; ++n)
+    u[n] = lane + 64 * n < N ? key_image(logit[n], flags) : 0u;
   uint32_t thr = 0u;
 #pragma unroll 1
   for (int bit = 31; bit >= 0; --bit) {
@@ -183,50 +58,260 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ log
   int base = 0;
 #pragma unroll
   for (int n = 0; n < NPL; ++n) {
-    const int b = lane + 64 * n;
     const unsigned long long below = (1ull << lane) - 1ull;
     const unsigned long long eq = __ballot(u[n] == thr);
     const bool sel = (u[n] > thr) || (u[n] == thr && __popcll(eq & below) < need);
     need -= min(need, __popcll(eq));
     const unsigned long long m = __ballot(sel);
     const int pos = base + __popcll(m & below);
-    if (sel) idx[(size_t)t * k + pos] = b;
+    if (sel) out[pos] = lane + 64 * n;
     base += __popcll(m);
   }
 }
 
+// One wavefront holds 16 MT tokens x 16 NT blocks of fp64 accumulators; the wavefronts share
+// the 32-wide chunks of d evenly, with those of other workgroups (gridDim.z) when `partial` is given: then
+// the fp64 sums go there and the top-k kernel adds them.  Operands are loaded DEPTH - 1 chunks ahead of the
+// MFMAs that consume them.  `TOPK`: the workgroup's tile covers all blocks (N <= 16 NT) and the block
+// ids are selected here too.
+template <int MT, int NT, int KS, int DEPTH, bool TOPK>
+__global__ __launch_bounds__(64 * KS) void router_logits_kernel(
+    const uint16_t* __restrict__ X, const float* __restrict__ Wr, const float* __restrict__ br, int T, int d, int N,
+    float* __restrict__ logits, double* __restrict__ partial, int k, int flags, int32_t* __restrict__ idx) {
+  constexpr int TOK = 16 * MT, BLK = 16 * NT;
+  __shared__ double red[KS > 1 ? KS / 2 : 1][MT * NT * 4][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, slot = lane >> 4;
+  const int tok0 = blockIdx.x * TOK, blk0 = blockIdx.y * BLK;
+
+  const uint16_t* xrow[MT];
+  const float* wcol[NT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+    xrow[m] = X + (size_t)min(tok0 + 16 * m + r16, T - 1) * d + 8 * slot;  // clamped rows are computed but never stored
+#pragma unroll
+  for (int n = 0; n < NT; ++n)
+    wcol[n] = Wr + (size_t)(8 * slot) * N + min(blk0 + 16 * n + r16, N - 1);  // ... columns likewise
+  f64x4 acc[MT][NT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[m][n] = f64x4{0.0, 0.0, 0.0, 0.0};
+
+  uint4 xq[DEPTH][MT];
+  float wq[DEPTH][NT][8];
+  auto fetch = [&](int st, int c) {
+    const int k0 = c * 32;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) xq[st][m] = *reinterpret_cast<const uint4*>(xrow[m] + k0);
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) wq[st][n][e] = wcol[n][(size_t)(k0 + e) * N];
+  };
+  auto consume = [&](int st) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      double a[MT], b[NT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        const uint32_t w32 = reinterpret_cast<const uint32_t*>(&xq[st][m])[e >> 1];
+        a[m] = (double)((e & 1) ? hi_bf16(w32) : lo_bf16(w32));
+      }
+#pragma unroll
+      for (int n = 0; n < NT; ++n) b[n] = (double)wq[st][n][e];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+          acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b[n], acc[m][n], 0, 0, 0);
+    }
+  };
+  const int chunks = d / 32, parts = KS * gridDim.z, pw = blockIdx.z * KS + wave;
+  const int cbeg = pw * chunks / parts, cend = (pw + 1) * chunks / parts;
+  if (cbeg < cend) {
+    const int clast = cend - 1;  // (requests past the last chunk repeat it: no branch around a load)
+#pragma unroll
+    for (int s = 0; s < DEPTH - 1; ++s) fetch(s, min(cbeg + s, clast));
+    int c = cbeg;
+    for (; c + DEPTH <= cend; c += DEPTH) {  // DEPTH chunks per trip keep the ring slots static
+#pragma unroll
+      for (int s = 0; s < DEPTH; ++s) {
+        fetch((s + DEPTH - 1) % DEPTH, min(c + s + DEPTH - 1, clast));
+        consume(s);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < DEPTH - 1; ++s)
+      if (c + s < cend) consume(s);
+  }
+
+  // The upper half of the wavefronts hands its sums to the lower half, and so on: a fixed order.
+#pragma unroll
+  for (int half = KS / 2; half >= 1; half >>= 1) {
+    if (wave >= half && wave < 2 * half) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) red[wave - half][(m * NT + n) * 4 + v][lane] = acc[m][n][v];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[m][n][v] += red[wave][(m * NT + n) * 4 + v][lane];
+    }
+    __syncthreads();
+  }
+
+  // D layout of the 16x16 fp64 tile: lane holds column (lane & 15), rows 4*v + (lane >> 4).
+  uint32_t* keys = reinterpret_cast<uint32_t*>(&red[0][0][0]);  // [TOK][BLK] key images
+  if (wave == 0) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        const int b = blk0 + 16 * n + r16;
+        const double bias = (br && b < N) ? (double)br[b] : 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = 16 * m + 4 * v + slot;
+          const double sum = acc[m][n][v] + bias;
+          if (TOPK) keys[row * BLK + 16 * n + r16] = b < N ? key_image((float)sum, flags) : 0u;
+          if (b < N && tok0 + row < T) {
+            const size_t at = (size_t)(tok0 + row) * N + b;
+            if (partial) partial[(size_t)blockIdx.z * T * N + at] = acc[m][n][v];
+            else if (logits) logits[at] = (float)sum;
+          }
+        }
+      }
+  }
+  if (TOPK) {
+    // A block's rank = blocks with a larger key, or an equal one and a lower id.  BLK lanes per token,
+    // 64 / BLK tokens per wavefront at a time.
+    __syncthreads();
+    const int b = lane % BLK;
+    for (int row0 = wave * (64 / BLK); row0 < TOK; row0 += KS * (64 / BLK)) {
+      const int row = row0 + lane / BLK, t = tok0 + row;
+      const uint32_t mine = keys[row * BLK + b];
+      int rank = 0;
+#pragma unroll
+      for (int o = 0; o < BLK; o += 4) {
+        const uint4 q = *reinterpret_cast<const uint4*>(keys + row * BLK + o);
+        rank += (q.x > mine) || (q.x == mine && o < b);
+        rank += (q.y > mine) || (q.y == mine && o + 1 < b);
+        rank += (q.z > mine) || (q.z == mine && o + 2 < b);
+        rank += (q.w > mine) || (q.w == mine && o + 3 < b);
+      }
+      const bool sel = rank < k;
+      const unsigned long long m = __ballot(sel);
+      const uint32_t group = (uint32_t)(m >> (lane - b)) & (BLK == 32 ? 0xFFFFFFFFu : (1u << (BLK & 31)) - 1u);
+      if (sel && t < T) idx[(size_t)t * k + __popc(group & ((1u << b) - 1u))] = b;
+    }
+  }
+}
+
+// (Rank-by-counting, the first version, compared every key with every other: 1400 instructions per token
+// at N = 128 against about 250.)
 template <int NPL>
-static void launch_topk(const spt_shape_t& s, const float* logits, int32_t* idx, hipStream_t st) {
-  topk_kernel<NPL><<<(s.T + 3) / 4, 256, 0, st>>>(logits, s.T, s.N, s.k, s.flags, idx);
+__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ logits,
+                                                   const double* __restrict__ partial, const float* __restrict__ br,
+                                                   int splits, int T, int N, int k, int flags,
+                                                   int32_t* __restrict__ idx) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t = blockIdx.x * 4 + wave;
+  if (t >= T) return;                      // whole wavefront; the kernel has no barrier
+  float l[NPL];
+#pragma unroll
+  for (int n = 0; n < NPL; ++n) {
+    const int b = lane + 64 * n;
+    l[n] = 0.f;
+    if (b < N) {
+      if (partial) {   // the parts of d, in order
+        double sum = 0.0;
+        for (int z0 = 0; z0 < splits; z0 += 8) {   // eight loads in flight
+          double p[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) p[u] = z0 + u < splits ? partial[((size_t)(z0 + u) * T + t) * N + b] : 0.0;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) sum += p[u];
+        }
+        l[n] = (float)(sum + (br ? (double)br[b] : 0.0));
+      } else {
+        l[n] = logits[(size_t)t * N + b];
+      }
+    }
+  }
+  select_topk<NPL>(l, lane, N, k, flags, idx + (size_t)t * k);
+}
+
+template <int NPL>
+static void launch_topk(const spt_shape_t& s, const float* logits, const double* partial, const float* br, int splits,
+                        int32_t* idx, hipStream_t st) {
+  topk_kernel<NPL><<<(s.T + 3) / 4, 256, 0, st>>>(logits, partial, br, splits, s.T, s.N, s.k, s.flags, idx);
+}
+
+// Parts d is split into over workgroups: a tile of 16 tokens x 16 blocks keeps one CU's fp64 units busy
+// for 4 d cycles (8 us at d = 4096), so a batch with few tiles hands every tile to several CUs.
+static int router_splits(const spt_shape_t& s) {
+  const int64_t tiles = (int64_t)((s.T + 15) / 16) * ((s.N + 15) / 16);
+  if (tiles > 64 || s.d < 1024) return 1;
+  const int fill = (int)(256 / tiles), most = s.d / 256;
+  const int p = fill < most ? fill : most;
+  return p < 16 ? p : 16;
+}
+
+size_t router_ws_bytes(const spt_shape_t& s) {
+  const size_t n = (size_t)s.T * s.N;
+  const int splits = router_splits(s);
+  return align256(splits > 1 ? n * splits * sizeof(double) : n * sizeof(float));
+}
+
+template <int MT, int NT, int KS, int DEPTH, bool TOPK>
+static void launch_logits(const spt_shape_t& s, const uint16_t* X, const float* Wr, const float* br, int32_t* idx,
+                          float* logits, double* partial, int splits, hipStream_t st) {
+  const dim3 grid((s.T + 16 * MT - 1) / (16 * MT), (s.N + 16 * NT - 1) / (16 * NT), splits);
+  router_logits_kernel<MT, NT, KS, DEPTH, TOPK><<<grid, 64 * KS, 0, st>>>(X, Wr, br, s.T, s.d, s.N, logits, partial,
+                                                                         s.k, s.flags, idx);
 }
 
 hipError_t run_router_topk(const spt_shape_t& s, const void* X, const float* Wr, const float* br,
-                           int32_t* idx, float* logits, hipStream_t st) {
+                           int32_t* idx, float* logits, float* ws, hipStream_t st) {
+  const uint16_t* x = static_cast<const uint16_t*>(X);
+  // (the caller's logits leave no workspace to split over)
+  const int splits = logits ? 1 : router_splits(s);
+  const bool fused = s.N <= 32 && splits == 1;
+  double* partial = splits > 1 ? reinterpret_cast<double*>(ws) : nullptr;
+  float* l = logits ? logits : (fused || partial) ? nullptr : ws;
   {
     ScopedKernelTimer tm(kSlotRouter, st);
-    // Two 16-block MFMA tiles per wavefront when there are blocks to fill them: the fp64
-    // conversions of a token's values are then shared by both (they cost as much VALU time as the
-    // MFMAs take), 0.159 against 0.168 ms at N = 128.
-    if (s.N > 32) {
-      const dim3 grid((s.T + 63) / 64, (s.N + 63) / 64);
-      router_logits_kernel<2, 2><<<grid, 512, 0, st>>>(static_cast<const uint16_t*>(X), Wr, br, s.T, s.d, s.N,
-                                                       logits);
-    } else {
-      const dim3 grid((s.T + 63) / 64, (s.N + 31) / 32);
-      router_logits_kernel<1, 2><<<grid, 512, 0, st>>>(static_cast<const uint16_t*>(X), Wr, br, s.T, s.d, s.N,
-                                                       logits);
-    }
+    auto tiles = [&](int mt, int nt) {
+      return (int64_t)((s.T + 16 * mt - 1) / (16 * mt)) * ((s.N + 16 * nt - 1) / (16 * nt));
+    };
+    // The largest tile of which there are two for every CU (a wider one shares the conversions of a
+    // token's values between its blocks; measured at N = 128, d = 4096, us: T 8192 164 with 32 x 32 against
+    // 186 with 16 x 16, T 3001 87 against 75 with 16 x 32, T 24 46 against 21 with 16 x 16).
+    if (fused && s.N <= 16) launch_logits<1, 1, 8, 3, true>(s, x, Wr, br, idx, l, partial, splits, st);
+    else if (fused) launch_logits<1, 2, 8, 3, true>(s, x, Wr, br, idx, l, partial, splits, st);
+    else if (tiles(2, 2) >= 512) launch_logits<2, 2, 8, 3, false>(s, x, Wr, br, idx, l, partial, splits, st);
+    else if (tiles(1, 2) >= 512) launch_logits<1, 2, 8, 3, false>(s, x, Wr, br, idx, l, partial, splits, st);
+    else launch_logits<1, 1, 8, 3, false>(s, x, Wr, br, idx, l, partial, splits, st);
   }
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || fused) return e;
   {
     ScopedKernelTimer tm(kSlotTopk, st);
     const int npl = (s.N + 63) / 64;
-    if (npl <= 1) launch_topk<1>(s, logits, idx, st);
-    else if (npl <= 2) launch_topk<2>(s, logits, idx, st);
-    else if (npl <= 4) launch_topk<4>(s, logits, idx, st);
-    else if (npl <= 8) launch_topk<8>(s, logits, idx, st);
-    else launch_topk<16>(s, logits, idx, st);
+    if (npl <= 1) launch_topk<1>(s, l, partial, br, splits, idx, st);
+    else if (npl <= 2) launch_topk<2>(s, l, partial, br, splits, idx, st);
+    else if (npl <= 4) launch_topk<4>(s, l, partial, br, splits, idx, st);
+    else if (npl <= 8) launch_topk<8>(s, l, partial, br, splits, idx, st);
+    else launch_topk<16>(s, l, partial, br, splits, idx, st);
   }
   return hipGetLastError();
 }

@@ -12,8 +12,11 @@ constexpr int kBucketChunkTokens = 128;  // tokens per workgroup in the bucketin
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// logits may be null: then ws (router_ws_bytes) holds them, or the parts of their sums, between the two
+// kernels (or nothing does, with few blocks).
+size_t router_ws_bytes(const spt_shape_t& s);
 hipError_t run_router_topk(const spt_shape_t& s, const void* X, const float* Wr, const float* br,
-                           int32_t* idx, float* logits, hipStream_t st);
+                           int32_t* idx, float* logits, float* ws, hipStream_t st);
 hipError_t run_bucket(const spt_shape_t& s, const int32_t* idx, int32_t* offsets, int32_t* perm,
                       int32_t* inv, int32_t* chunk_hist, hipStream_t st);
 // Device address, on the current device, of the library's fixed bucketing scratch
@@ -51,6 +54,7 @@ struct BwdWorkspace {
   uint16_t* dHpre;  // dHpre per pair        wide blocks: row-major [P,Bs])
   uint16_t* part;   // [P,d] per-pair partial dX rows (wide blocks only)
   float* dw_stage;  // [dw_cap - N][Bs][d] products of the pieces after a bucket's first (narrow blocks)
+  float* dw_stage2; // ... of the second gradient, when both are formed in one launch; else null
   size_t bytes;
 };
 FwdWorkspace plan_fwd(const spt_shape_t& s, void* ws);
@@ -69,6 +73,9 @@ struct ScatterPlan {
 ScatterPlan plan_scatter(const spt_shape_t& s);
 // The dense table starts[r][b] (written by the schedule kernel) inside the run-table buffer.
 int32_t* scatter_starts(const ScatterPlan& p, int32_t* table);
+struct RunRec;   // the ranges' run records [nr][cap] and their counts [nr] in the same buffer
+RunRec* scatter_runs(const ScatterPlan& p, int32_t* table);
+int32_t* scatter_counts(const ScatterPlan& p, int32_t* table);
 // Turns the dense table into the per-range lists of non-empty runs.
 hipError_t run_scatter_ranges(const spt_shape_t& s, const ScatterPlan& p, int32_t* table, hipStream_t st);
 // out[t][:] = sum_{b in S(t), ascending} Hin[pos(t,b)][:] W[b]  (+ Z[t][:] when Z is given)
@@ -122,11 +129,6 @@ hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const vo
 hipError_t launch_dw(const uint16_t* Act, const uint16_t* Hin, bool hin_frag, const int32_t* offsets,
                      const int32_t* tok, const int32_t* border, const uint16_t* zero_row, int N,
                      int Bs, int d, float* dW, int slot, hipStream_t st);
-// The same GEMM over a piece table (Schedule::dw_pieces) instead of whole buckets, followed by
-// the fixed-order sum of the staged pieces into their blocks.
-hipError_t launch_dw_pieces(const uint16_t* Act, const uint16_t* Hin, bool hin_frag, const Schedule& sc, int N,
-                            int Bs, int d, float* dW, float* stage, int slot, hipStream_t st);
-
 // Load-balancing loss of the route network and its gradient.
 struct BalanceWorkspace {
   uint16_t* dl;        // [T][Npad] bf16 d loss / d logit

@@ -411,3 +411,21 @@ def test_step_replays_identically_from_a_hip_graph():
             assert torch.equal(got, ref)
         step()                      # eager work between the replays
         torch.cuda.synchronize()
+
+
+# Route network and bucketing at the edges of their launch rules: 16 / 32 blocks (selection fused into the
+# logits kernel) and one more, few tokens with d split over workgroups (logits left to the workspace),
+# 8192 pairs and one more token, a histogram table of more than 16384 counts, many blocks.
+@pytest.mark.parametrize("T,d,N,k", [(1, 64, 1, 1), (17, 128, 16, 5), (130, 192, 17, 16), (65, 2048, 32, 9),
+                                     (33, 64, 33, 2), (1, 4096, 128, 32), (50, 1024, 300, 7), (24, 4160, 64, 64),
+                                     (1024, 64, 16, 8), (1025, 64, 16, 8), (2100, 64, 1024, 9), (3000, 128, 70, 3),
+                                     (9000, 64, 40, 4)])
+@pytest.mark.parametrize("flags", [0, spt.FLAG_ABS_LOGIT])
+def test_routing_and_bucketing_launch_edges(T, d, N, k, flags):
+    s = gen.custom_shape(T, d, N, 32, k, seed=T + N, flags=flags, zipf_bias=True, wr_std=0.2)
+    dv = Dev(gen.make_inputs(s))
+    tag = f"edges T{T} d{d} N{N} k{k} flags{flags}"
+    idx, g_idx, _ = check_routing(dv, tag)
+    idx2 = spt.router_topk(dv.shape, dv.X, dv.W_r, dv.b_r)      # logits in the workspace: other kernels, same ids
+    assert torch.equal(idx, idx2), tag
+    check_bucket(dv, idx, g_idx, tag)
