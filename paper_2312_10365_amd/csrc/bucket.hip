@@ -1,12 +1,11 @@
 // Token batching by activated block: Algorithm 4's per-block token selection, done once
 // for all blocks as a stable counting sort of the (token, slot) pairs by block id.
 //
-// Three small integer kernels, exact and deterministic:
-//   1. per chunk of 128 tokens, a (block x token) membership bitmask in LDS gives the
-//      chunk's histogram;
-//   2. one workgroup turns the chunk histograms into bucket offsets and per-chunk bases;
-//   3. each chunk rebuilds its bitmask; the rank of a pair inside its bucket is the chunk
-//      base plus the number of lower tokens of the chunk in the same bucket (popcount).
+// Small integer kernels, exact and deterministic.  Per chunk of 128 tokens a (block x token) membership
+// bitmask in LDS gives the chunk's histogram; then each chunk rebuilds its bitmask, adds up the
+// histograms of the chunks before it, and the rank of a pair inside its bucket is that base plus the
+// number of lower tokens of the chunk in the same bucket (popcount).  Few pairs are sorted whole by one
+// workgroup in one launch; very many blocks times chunks get their bases from a launch of their own.
 // A token lists each block at most once, so one bit per (block, token) is enough, and the
 // order inside a bucket is by token id, i.e. stable.
 #include "spt_device.hpp"
@@ -89,25 +88,52 @@ __global__ __launch_bounds__(1024) void bucket_scan_kernel(int32_t* __restrict__
   if (b == N - 1) offsets[N] = before + total;
 }
 
-__global__ __launch_bounds__(256) void bucket_scatter_kernel(
-    const int32_t* __restrict__ idx, int T, int N, int k, const int32_t* __restrict__ chunk_hist,
-    const int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv) {
-  extern __shared__ uint32_t mask[];
-  build_chunk_mask(idx, T, N, k, blockIdx.x, mask);
-  const int t0 = blockIdx.x * kBucketChunkTokens;
+// kScan: chunk_hist holds the chunks' histograms as they are and this kernel adds up those before its own
+// chunk (and all of them, for the offsets, which workgroup 0 writes); otherwise it holds the bases and
+// `offsets` is complete.
+template <bool kScan>
+__global__ __launch_bounds__(1024) void bucket_scatter_kernel(
+    const int32_t* __restrict__ idx, int T, int N, int k, const int32_t* __restrict__ chunk_hist, int nchunks,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv) {
+  extern __shared__ uint32_t mask[];                       // [N][4] bits, then [N] first position per bucket
+  int32_t* first = reinterpret_cast<int32_t*>(mask + N * kWordsPerChunk);
+  __shared__ int32_t wtot[16];
+  const int chunk = blockIdx.x;
+  if (kScan) {
+    const int b = threadIdx.x;
+    int before = 0, all = 0;
+    if (b < N) {
+      for (int c0 = 0; c0 < nchunks; c0 += 16) {           // sixteen loads in flight
+        int v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = (c0 + u < nchunks) ? chunk_hist[(size_t)(c0 + u) * N + b] : 0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          before += c0 + u < chunk ? v[u] : 0;
+          all += v[u];
+        }
+      }
+    }
+    int total;
+    const int off = block_inclusive_sum(all, wtot, total) - all;
+    if (b < N) first[b] = off + before;
+    if (chunk == 0) {
+      if (b < N) offsets[b] = off;
+      if (b == 0) offsets[N] = total;
+    }
+  } else {
+    for (int b = threadIdx.x; b < N; b += blockDim.x) first[b] = offsets[b] + chunk_hist[(size_t)chunk * N + b];
+  }
+  build_chunk_mask(idx, T, N, k, chunk, mask);
+  const int t0 = chunk * kBucketChunkTokens;
   const int nt = min(kBucketChunkTokens, T - t0);
   const int64_t p0 = (int64_t)t0 * k;
   for (int e0 = threadIdx.x; e0 < nt * k; e0 += 4 * blockDim.x) {   // four pairs at a time per thread
-    int bv[4], base[4];
+    int bv[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int e = e0 + u * blockDim.x;
       bv[u] = (e < nt * k) ? idx[p0 + e] : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const bool ok = bv[u] >= 0 && bv[u] < N;
-      base[u] = ok ? offsets[bv[u]] + chunk_hist[(size_t)blockIdx.x * N + bv[u]] : 0;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -117,9 +143,72 @@ __global__ __launch_bounds__(256) void bucket_scatter_kernel(
       const uint32_t* m = mask + b * kWordsPerChunk;
       int r = __popc(m[tl >> 5] & ((1u << (tl & 31)) - 1u));
       for (int w = 0; w < (tl >> 5); ++w) r += __popc(m[w]);
-      const int q = base[u] + r;
+      const int q = first[b] + r;
       perm[q] = (int32_t)(p0 + e);
       inv[p0 + e] = q;
+    }
+  }
+}
+
+// All pairs by one workgroup: the (block x token) bitmask of the whole batch, bits before each of its words, and
+// the block totals' prefix all sit in LDS.
+__global__ __launch_bounds__(1024) void bucket_small_kernel(const int32_t* __restrict__ idx, int T, int N, int k,
+                                                            int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+                                                            int32_t* __restrict__ inv) {
+  extern __shared__ uint32_t mask[];                       // [N][nwp] bits, [N][nwp] set bits in earlier words, [N] totals
+  __shared__ int32_t wtot[16];
+  const int nw = (T + 31) >> 5, nwp = nw | 1, P = T * k;   // odd row stride: rows start on different banks
+  uint16_t* pre = reinterpret_cast<uint16_t*>(mask + N * nwp);
+  int32_t* tot = reinterpret_cast<int32_t*>(pre + ((N * nwp + 1) & ~1));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int e = tid; e < N * nwp; e += 1024) mask[e] = 0u;
+  __syncthreads();
+  for (int p0 = tid; p0 < P; p0 += 8 * 1024) {
+    int bv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) bv[u] = p0 + u * 1024 < P ? idx[p0 + u * 1024] : -1;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int t = (p0 + u * 1024) / k;
+      if (bv[u] >= 0 && bv[u] < N) atomicOr(&mask[bv[u] * nwp + (t >> 5)], 1u << (t & 31));
+    }
+  }
+  __syncthreads();
+  for (int b = wave; b < N; b += 16) {                     // a wavefront per block, lanes over words
+    int sum = 0;
+    for (int w0 = 0; w0 < nw; w0 += 64) {
+      const int w = w0 + lane;
+      const int c = w < nw ? __popc(mask[b * nwp + w]) : 0;
+      int incl = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl, o);
+        if (lane >= o) incl += up;
+      }
+      if (w < nw) pre[b * nwp + w] = (uint16_t)(sum + incl - c);
+      sum += __shfl(incl, 63);
+    }
+    if (lane == 0) tot[b] = sum;
+  }
+  __syncthreads();
+  const int mine = tid < N ? tot[tid] : 0;
+  int total;
+  const int off = block_inclusive_sum(mine, wtot, total) - mine;
+  if (tid < N) { tot[tid] = off; offsets[tid] = off; }
+  if (tid == 0) offsets[N] = total;
+  __syncthreads();
+  for (int p0 = tid; p0 < P; p0 += 4 * 1024) {
+    int bv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) bv[u] = p0 + u * 1024 < P ? idx[p0 + u * 1024] : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int p = p0 + u * 1024, b = bv[u];
+      if (b < 0 || b >= N) continue;
+      const int t = p / k, w = b * nwp + (t >> 5);
+      const int q = tot[b] + pre[w] + __popc(mask[w] & ((1u << (t & 31)) - 1u));
+      perm[q] = p;
+      inv[p] = q;
     }
   }
 }
@@ -149,6 +238,14 @@ hipError_t bucket_static_scratch(int32_t** out) {
 
 hipError_t run_bucket(const spt_shape_t& s, const int32_t* idx, int32_t* offsets, int32_t* perm,
                       int32_t* inv, int32_t* chunk_hist, hipStream_t st) {
+  // One workgroup sorts 8 thousand pairs in 5-7 us, two launches over many CUs take 9 (16 thousand: 14 us).
+  const size_t nwp = ((s.T + 31) / 32) | 1;
+  const size_t small = (size_t)s.N * nwp * 4 + ((size_t)s.N * nwp + 1) / 2 * 4 + (size_t)s.N * 4;
+  if ((int64_t)s.T * s.k <= 8192 && small <= 60 * 1024) {
+    ScopedKernelTimer tm(kSlotBucketScatter, st);
+    bucket_small_kernel<<<1, 1024, small, st>>>(idx, s.T, s.N, s.k, offsets, perm, inv);
+    return hipGetLastError();
+  }
   const int nchunks = (s.T + kBucketChunkTokens - 1) / kBucketChunkTokens;
   const size_t smem = (size_t)s.N * kWordsPerChunk * sizeof(uint32_t);
   {
@@ -157,17 +254,21 @@ hipError_t run_bucket(const spt_shape_t& s, const int32_t* idx, int32_t* offsets
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  {
+  // Every chunk's workgroup reads the whole histogram table (N x chunks counts) unless that is more than
+  // 64 KiB of them: then one workgroup turns it into bases first.
+  const bool scan = (int64_t)nchunks * s.N > 16384;
+  if (scan) {
     ScopedKernelTimer tm(kSlotBucketScan, st);
     bucket_scan_kernel<<<1, 1024, 0, st>>>(chunk_hist, nchunks, s.N, offsets);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  {
-    ScopedKernelTimer tm(kSlotBucketScatter, st);
-    bucket_scatter_kernel<<<nchunks, 256, smem, st>>>(idx, s.T, s.N, s.k, chunk_hist, offsets, perm,
-                                                      inv);
-  }
+  ScopedKernelTimer tm(kSlotBucketScatter, st);
+  const int threads = s.N <= 256 ? 256 : 1024;
+  const size_t sm = smem + (size_t)s.N * sizeof(int32_t);
+  if (scan)
+    bucket_scatter_kernel<false><<<nchunks, threads, sm, st>>>(idx, s.T, s.N, s.k, chunk_hist, nchunks, offsets, perm, inv);
+  else
+    bucket_scatter_kernel<true><<<nchunks, threads, sm, st>>>(idx, s.T, s.N, s.k, chunk_hist, nchunks, offsets, perm, inv);
   return hipGetLastError();
 }
 

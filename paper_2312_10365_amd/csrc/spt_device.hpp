@@ -13,6 +13,29 @@ constexpr int kWave = 64;
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
+// Inclusive sum over a workgroup of whole wavefronts (at most 16): wavefront prefix by shuffles, wavefront
+// totals through `wtot` (16 words of LDS).  Two barriers; `total` is the sum over the workgroup.
+__device__ __forceinline__ int block_inclusive_sum(int v, int32_t* wtot, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (int)(blockDim.x >> 6);
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o);
+    if (lane >= o) incl += up;
+  }
+  __syncthreads();   // (wtot may still be read from the call before)
+  if (lane == 63) wtot[wave] = incl;
+  __syncthreads();
+  int before = 0;
+  total = 0;
+  for (int w = 0; w < nw; ++w) {
+    const int x = wtot[w];
+    before += w < wave ? x : 0;
+    total += x;
+  }
+  return before + incl;
+}
+
 // Round-to-nearest-even float -> bf16 bit pattern (finite inputs).
 __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
   const uint32_t u = __float_as_uint(f);
