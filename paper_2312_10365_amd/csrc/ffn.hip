@@ -37,67 +37,72 @@ namespace spt {
 //                     weight blocks.  With fewer buckets the bucket-major tile sequence is
 //                     cut into 8 contiguous runs (weight reuse only).
 
-__global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ offsets, int N,
-                                                    int QT, int cap,
-                                                    int32_t* __restrict__ border,
-                                                    int32_t* __restrict__ kd_count,
-                                                    KdTile* __restrict__ kd_list,
-                                                    uint32_t* __restrict__ zero_row,
-                                                    const int32_t* __restrict__ perm, int P, int k,
-                                                    int32_t* __restrict__ tok, int R, int nr,
-                                                    int32_t* __restrict__ starts, int dw_rows, int dw_cap,
-                                                    DwPiece* __restrict__ dw_pieces,
-                                                    int32_t* __restrict__ dw_xlist) {
-  // Workgroups past the first fill tok[q] = token of sorted position q (one launch instead of
-  // two) and, for narrow blocks (R > 0), the table starts[r][b] = first sorted position of bucket
-  // b whose token is >= r R (r = 0 .. nr): position q is that first position for every range
-  // after its predecessor's and up to its own, and the bucket's end for the ranges behind its
-  // last row -- every entry is written exactly once, no search, no atomics.
-  if (blockIdx.x > 0) {
-    __shared__ int32_t off_sh[1025];
-    if (R > 0) {
-      for (int e = threadIdx.x; e <= N; e += 1024) off_sh[e] = offsets[e];
-      __syncthreads();
-    }
+struct PlanArgs {
+  const int32_t* offsets;
+  const int32_t* perm;
+  int N, QT, cap, P, k;
+  int32_t *border, *kd_count;
+  KdTile* kd_list;
+  uint32_t* zero_row;
+  int32_t* tok;
+  int R, nr;               // narrow blocks: token ranges of the K = Bs kernel (R = 0: none)
+  int32_t* starts;
+  RunRec* runs;
+  int32_t* nruns;
+  int run_cap;
+  int dw_rows, dw_cap;
+  DwPiece* dw_pieces;
+  int32_t* dw_xlist;
+};
+
+// Sorted position q: tok[q] = its token and, for narrow blocks (R > 0), its entries of the table
+// starts[r][b] = first sorted position of bucket b whose token is >= r R (r = 0 .. nr): position q is
+// that first position for every range after its predecessor's and up to its own, and the bucket's
+// end for the ranges behind its last row -- every entry is written exactly once, no search, no atomics.
+__device__ __forceinline__ void plan_position(const PlanArgs& p, const int32_t* off_sh, int q) {
+  const int t = p.perm[q] / p.k;
+  p.tok[q] = t;
+  if (p.R <= 0) return;
+  int lo = 0, hi = p.N;   // bucket of q: the largest b with offsets[b] <= q
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (off_sh[mid] <= q) lo = mid; else hi = mid;
+  }
+  const int b = lo;
+  const int rq = t / p.R;
+  const int rprev = (q > off_sh[b]) ? (p.perm[q - 1] / p.k) / p.R : -1;
+  for (int r = rprev + 1; r <= rq; ++r) p.starts[(size_t)r * p.N + b] = q;
+  if (q + 1 == off_sh[b + 1])
+    for (int r = rq + 1; r <= p.nr; ++r) p.starts[(size_t)r * p.N + b] = q + 1;
+}
+
+// Workgroup 0 builds the tables over buckets, the others take 1024 sorted positions each; kAll: one
+// workgroup does everything, the run lists of the K = Bs kernel included (few pairs: a launch of the
+// path then costs more than the work in it).
+template <bool kAll>
+__global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
+  __shared__ int32_t off_sh[1025];
+  const int N = p.N;
+  for (int e = threadIdx.x; e <= N; e += 1024) off_sh[e] = p.offsets[e];
+  __syncthreads();
+  if (!kAll && blockIdx.x > 0) {
     const int q = (blockIdx.x - 1) * 1024 + threadIdx.x;
-    if (q >= P) return;
-    const int t = perm[q] / k;
-    tok[q] = t;
-    if (R <= 0) return;
-    int lo = 0, hi = N;   // bucket of q: the largest b with offsets[b] <= q
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (off_sh[mid] <= q) lo = mid; else hi = mid;
-    }
-    const int b = lo;
-    const int rq = t / R;
-    const int rprev = (q > off_sh[b]) ? (perm[q - 1] / k) / R : -1;
-    for (int r = rprev + 1; r <= rq; ++r) starts[(size_t)r * N + b] = q;
-    if (q + 1 == off_sh[b + 1])
-      for (int r = rq + 1; r <= nr; ++r) starts[(size_t)r * N + b] = q + 1;
+    if (q < p.P) plan_position(p, off_sh, q);
     return;
   }
-  __shared__ int32_t scan[1024];
-  if (threadIdx.x < 64) zero_row[threadIdx.x] = 0u;  // 256 bytes of zeros for padded K rows
+  __shared__ int32_t wtot[16];
+  if (threadIdx.x < 64) p.zero_row[threadIdx.x] = 0u;  // 256 bytes of zeros for padded K rows
   __shared__ int32_t sm_m[1024];
   __shared__ int32_t sm_ntq_by_rank[1024];
   const int b = threadIdx.x;
-  const int off = (b < N) ? offsets[b] : 0;
-  const int m = (b < N) ? offsets[b + 1] - off : 0;
-  if (R > 0 && b < N && m == 0)   // an empty bucket has no row to write its table column
-    for (int r = 0; r <= nr; ++r) starts[(size_t)r * N + b] = off;
+  const int off = (b < N) ? off_sh[b] : 0;
+  const int m = (b < N) ? off_sh[b + 1] - off : 0;
+  if (p.R > 0 && b < N && m == 0)   // an empty bucket has no row to write its table column
+    for (int r = 0; r <= p.nr; ++r) p.starts[(size_t)r * N + b] = off;
 
   auto inclusive_scan = [&](int v) {
-    __syncthreads();
-    scan[b] = v;
-    __syncthreads();
-    for (int s = 1; s < 1024; s <<= 1) {
-      const int t = (b >= s) ? scan[b - s] : 0;
-      __syncthreads();
-      scan[b] += t;
-      __syncthreads();
-    }
-    return scan[b];
+    int total;
+    return block_inclusive_sum(v, wtot, total);
   };
 
   sm_m[b] = m;
@@ -105,29 +110,29 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
   int rank = 0;
   if (b < N)
     for (int o = 0; o < N; ++o) rank += (sm_m[o] > m) || (sm_m[o] == m && o < b);
-  const int ntq = (m + QT - 1) / QT;
+  const int ntq = (m + p.QT - 1) / p.QT;
   if (b < N) {
-    border[rank] = b;
+    p.border[rank] = b;
     sm_ntq_by_rank[rank] = ntq;
   }
   __syncthreads();
 
   // Weight-gradient work items (backward, narrow blocks): a bucket of m rows becomes
-  // ceil(m / dw_rows) pieces of equal size (an empty bucket one empty piece: its gradient block
+  // ceil(m / p.dw_rows) pieces of equal size (an empty bucket one empty piece: its gradient block
   // is written as zeros), listed largest bucket first.  A bucket's first piece goes straight
   // into its gradient block, the others into staging slots that are added afterwards in order.
-  if (dw_pieces) {
+  if (p.dw_pieces) {
     __shared__ int32_t sm_np_rank[1024];
     __shared__ int32_t sm_wstart[1024];
-    const int np = (b < N) ? (m > dw_rows ? (m + dw_rows - 1) / dw_rows : 1) : 0;
+    const int np = (b < N) ? (m > p.dw_rows ? (m + p.dw_rows - 1) / p.dw_rows : 1) : 0;
     const int x_end = inclusive_scan(np > 1 ? np - 1 : 0);     // staging slots, in bucket order
     const int l_end = inclusive_scan(np > 1 ? 1 : 0);          // buckets with staged pieces
     if (b < N && np > 1) {
-      dw_xlist[1 + 3 * (l_end - 1)] = b;
-      dw_xlist[2 + 3 * (l_end - 1)] = x_end - (np - 1);
-      dw_xlist[3 + 3 * (l_end - 1)] = x_end;
+      p.dw_xlist[1 + 3 * (l_end - 1)] = b;
+      p.dw_xlist[2 + 3 * (l_end - 1)] = x_end - (np - 1);
+      p.dw_xlist[3 + 3 * (l_end - 1)] = x_end;
     }
-    if (b == N - 1) dw_xlist[0] = l_end;
+    if (b == N - 1) p.dw_xlist[0] = l_end;
     sm_np_rank[b] = 0;
     __syncthreads();
     if (b < N) sm_np_rank[rank] = np;
@@ -142,10 +147,10 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
       const int at = sm_wstart[rank], base = m / np, rem = m % np;
       for (int pc = 0; pc < np; ++pc) {
         const int lo = off + pc * base + (pc < rem ? pc : rem);
-        dw_pieces[at + pc] = DwPiece{lo, lo + base + (pc < rem ? 1 : 0), pc == 0 ? b : N + x_end - (np - 1) + pc - 1, 0};
+        p.dw_pieces[at + pc] = DwPiece{lo, lo + base + (pc < rem ? 1 : 0), pc == 0 ? b : N + x_end - (np - 1) + pc - 1, 0};
       }
     }
-    for (int e = total_pieces + b; e < dw_cap; e += 1024) dw_pieces[e] = DwPiece{0, 0, -1, 0};
+    for (int e = total_pieces + b; e < p.dw_cap; e += 1024) p.dw_pieces[e] = DwPiece{0, 0, -1, 0};
   }
 
   if (N >= 16) {
@@ -153,8 +158,8 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
     // member at position p of group g has rank 8p + (p even ? g : 7 - g); sizes fall with p.
     const int pg = rank >> 3;
     const int g = (pg & 1) ? 7 - (rank & 7) : (rank & 7);
-    auto member_ntq = [&](int grp, int p) {
-      const int r = 8 * p + ((p & 1) ? 7 - grp : grp);
+    auto member_ntq = [&](int grp, int pos) {
+      const int r = 8 * pos + ((pos & 1) ? 7 - grp : grp);
       return (r < N) ? sm_ntq_by_rank[r] : 0;
     };
     if (b < N) {
@@ -162,14 +167,14 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
       int alive = (N + 7) / 8;    // members that still have a tile at this level: a prefix
       for (int lvl = 0; lvl < ntq; ++lvl) {
         while (alive > 0 && member_ntq(g, alive - 1) <= lvl) --alive;
-        kd_list[(size_t)g * cap + before + pg] = KdTile{b, off + lvl * QT};
+        p.kd_list[(size_t)g * p.cap + before + pg] = KdTile{b, off + lvl * p.QT};
         before += alive;
       }
     }
     if (b < 8) {
       int total = 0;
-      for (int p = 0; 8 * p < N; ++p) total += member_ntq(b, p);
-      kd_count[b] = total;
+      for (int pos = 0; 8 * pos < N; ++pos) total += member_ntq(b, pos);
+      p.kd_count[b] = total;
     }
   } else {
     const int inc = inclusive_scan(ntq);
@@ -181,11 +186,19 @@ __global__ __launch_bounds__(1024) void plan_kernel(const int32_t* __restrict__ 
     if (b < N)
       for (int lvl = 0; lvl < ntq; ++lvl) {
         const int t = inc - ntq + lvl;
-        kd_list[(size_t)(t / per) * cap + (t % per)] = KdTile{b, off + lvl * QT};
+        p.kd_list[(size_t)(t / per) * p.cap + (t % per)] = KdTile{b, off + lvl * p.QT};
       }
     if (b < 8) {
       const int left = total - b * per;
-      kd_count[b] = left < 0 ? 0 : (left < per ? left : per);
+      p.kd_count[b] = left < 0 ? 0 : (left < per ? left : per);
+    }
+  }
+  if (kAll) {
+    for (int q = threadIdx.x; q < p.P; q += 1024) plan_position(p, off_sh, q);
+    if (p.R > 0) {
+      __syncthreads();   // (the table is this workgroup's own)
+      for (int r = threadIdx.x >> 6; r < p.nr; r += 16)
+        compact_runs(p.starts, N, p.run_cap, p.runs, p.nruns, r, threadIdx.x & 63);
     }
   }
 }
@@ -405,13 +418,24 @@ constexpr int DW_KT = 16;                          // tokens per stage
 constexpr int DW_HALF_BYTES = DW_KT * 256 * 2;     // 8 KiB: 16 token rows x 256 columns
 constexpr int DW_SLOTS = 6;   // 72 KiB per workgroup with 256 x 128 tiles, 120 with 512 x 128 (a 7th slot gained nothing)
 
+// One product of the weight-gradient GEMM: its operands, the gradient, and the staging slots of pieces.
+struct DwOperands {
+  const uint16_t *Act, *Hin;
+  float *dW, *stage;
+};
+
 template <bool FRAG, int UT, int CT>  // FRAG: Hin in fragment order (hfrag_off) instead of row-major [rows, Bs]
 __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
-    const uint16_t* __restrict__ Act, const uint16_t* __restrict__ Hin,
+    DwOperands ops0, DwOperands ops1,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ tok,
     const int32_t* __restrict__ border, const uint16_t* __restrict__ zero_row, int N, int Bs,
-    int d, float* __restrict__ dW, const DwPiece* __restrict__ pieces, int nblocks,
-    float* __restrict__ stage) {
+    int d, const DwPiece* __restrict__ pieces, int nblocks) {
+  // (blockIdx.z picks the product: both weight gradients of a step can go out in one launch)
+  const DwOperands ops = blockIdx.z ? ops1 : ops0;
+  const uint16_t* __restrict__ Act = ops.Act;
+  const uint16_t* __restrict__ Hin = ops.Hin;
+  float* __restrict__ dW = ops.dW;
+  float* __restrict__ stage = ops.stage;
   constexpr int MI = UT == 128 ? 4 : 2;               // 32-column tiles per wavefront
   constexpr int DW_CT = CT;
   constexpr int DW_A_BYTES = (CT / 256) * DW_HALF_BYTES;   // 8 or 16 KiB
@@ -633,8 +657,10 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
 
 // dW[b] += stage[first] + ... + stage[end - 1] (in that order) for every bucket b that was cut
 // into more than one piece; xlist = (count, then (bucket, first slot, end slot) triples).
-__global__ __launch_bounds__(256) void dw_reduce_kernel(float* __restrict__ dW, const float* __restrict__ stage,
+__global__ __launch_bounds__(256) void dw_reduce_kernel(DwOperands ops0, DwOperands ops1,
                                                         const int32_t* __restrict__ xlist, int Bs, int d) {
+  float* __restrict__ dW = blockIdx.y ? ops1.dW : ops0.dW;
+  const float* __restrict__ stage = blockIdx.y ? ops1.stage : ops0.stage;
   const int count = xlist[0];
   const size_t e4 = (size_t)Bs * d / 4;   // 16-byte groups per block
   for (size_t it = (size_t)blockIdx.x * 256 + threadIdx.x; it < (size_t)count * e4;
@@ -770,10 +796,17 @@ BwdWorkspace plan_bwd(const spt_shape_t& s, void* ws, bool weight_grads) {
   w.Hact = reinterpret_cast<uint16_t*>(p + o);       o += align256(hrows(P) * s.Bs * 2);
   w.dHpre = reinterpret_cast<uint16_t*>(p + o);      o += align256(hrows(P) * s.Bs * 2);
   o += carve_part(s, p, o, w.part);
-  w.dw_stage = nullptr;
+  w.dw_stage = w.dw_stage2 = nullptr;
   if (w.sched.dw_cap > 0) {
+    // Both gradients go out in one launch, with staging slots of their own, unless those are large:
+    // where a launch has thousands of work items there is no half-empty last round to share.
+    const size_t bytes = align256((size_t)(w.sched.dw_cap - s.N) * s.Bs * s.d * 4);
     w.dw_stage = reinterpret_cast<float*>(p + o);
-    o += align256((size_t)(w.sched.dw_cap - s.N) * s.Bs * s.d * 4);
+    o += bytes;
+    if (bytes <= ((size_t)64 << 20)) {
+      w.dw_stage2 = reinterpret_cast<float*>(p + o);
+      o += bytes;
+    }
   }
   w.bytes = o;
   return w;
@@ -800,17 +833,25 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
                            const Schedule& sc, hipStream_t st) {
   const int P = s.T * s.k;
   const ScatterPlan sp = sc.rstart ? plan_scatter(s) : ScatterPlan{};
+  PlanArgs a = {};
+  a.offsets = offsets; a.perm = perm;
+  a.N = s.N; a.QT = FU_ROWS; a.cap = sc.kd_cap; a.P = P; a.k = s.k;
+  a.border = sc.border; a.kd_count = sc.kd_count; a.kd_list = static_cast<KdTile*>(sc.kd_list);
+  a.zero_row = reinterpret_cast<uint32_t*>(sc.zero_row);
+  a.tok = sc.tok;
+  if (sc.rstart) {
+    a.R = sp.R; a.nr = sp.nr; a.starts = scatter_starts(sp, sc.rstart);
+    a.runs = scatter_runs(sp, sc.rstart); a.nruns = scatter_counts(sp, sc.rstart); a.run_cap = sp.cap;
+  }
+  a.dw_rows = sc.dw_rows; a.dw_cap = sc.dw_cap; a.dw_pieces = sc.dw_pieces; a.dw_xlist = sc.dw_xlist;
+  const bool all = P <= 8192;   // eight positions per thread: less than the two launches it saves
   {
     ScopedKernelTimer tm(kSlotPlan, st);
-    plan_kernel<<<1 + (P + 1023) / 1024, 1024, 0, st>>>(offsets, s.N, FU_ROWS, sc.kd_cap, sc.border, sc.kd_count,
-                                                        static_cast<KdTile*>(sc.kd_list),
-                                                        reinterpret_cast<uint32_t*>(sc.zero_row), perm, P, s.k,
-                                                        sc.tok, sc.rstart ? sp.R : 0, sp.nr,
-                                                        sc.rstart ? scatter_starts(sp, sc.rstart) : nullptr,
-                                                        sc.dw_rows, sc.dw_cap, sc.dw_pieces, sc.dw_xlist);
+    if (all) plan_kernel<true><<<1, 1024, 0, st>>>(a);
+    else plan_kernel<false><<<1 + (P + 1023) / 1024, 1024, 0, st>>>(a);
   }
   SPT_LAUNCH_CHECK();
-  if (sc.rstart) {
+  if (sc.rstart && !all) {
     ScopedKernelTimer tm(kSlotPlan, st);
     return run_scatter_ranges(s, sp, sc.rstart, st);
   }
@@ -875,16 +916,15 @@ static hipError_t launch_up(const spt_shape_t& s, const uint16_t* Wa, const uint
 
 // One instantiation of the weight-gradient GEMM (UT = hidden units per workgroup tile).
 template <bool FRAG, int UT, int CT>
-static hipError_t launch_dw_ttt(const uint16_t* Act, const uint16_t* Hin, const int32_t* offsets,
-                               const int32_t* tok, const int32_t* border, const uint16_t* zero_row, int N,
-                               int Bs, int d, float* dW, int slot, hipStream_t st, const DwPiece* pieces,
-                               int nblocks, float* stage) {
+static hipError_t launch_dw_ttt(const DwOperands* ops, int nops, const int32_t* offsets, const int32_t* tok,
+                                const int32_t* border, const uint16_t* zero_row, int N, int Bs, int d, int slot,
+                                hipStream_t st, const DwPiece* pieces, int nblocks) {
   const int nct = (d + CT - 1) / CT;
   int gx;
   if (nct % 8 == 0) gx = nct * N;
   else if (8 % nct == 0) gx = 8 * ((N + 8 / nct - 1) / (8 / nct));
   else gx = nct * N;
-  const dim3 grid(gx, (Bs + UT - 1) / UT);
+  const dim3 grid(gx, (Bs + UT - 1) / UT, nops);
   const int dw_smem = DW_SLOTS * ((CT / 256) * DW_HALF_BYTES + DW_KT * UT * 2);
   static bool attr_set = false;
   if (!attr_set) {
@@ -895,8 +935,8 @@ static hipError_t launch_dw_ttt(const uint16_t* Act, const uint16_t* Hin, const 
   }
   {
     ScopedKernelTimer tm(slot, st);
-    kq_gemm_kernel<FRAG, UT, CT><<<grid, CT, dw_smem, st>>>(Act, Hin, offsets, tok, border, zero_row, N, Bs, d, dW,
-                                                         pieces, nblocks, stage);
+    kq_gemm_kernel<FRAG, UT, CT><<<grid, CT, dw_smem, st>>>(ops[0], ops[nops - 1], offsets, tok, border, zero_row, N, Bs,
+                                                         d, pieces, nblocks);
   }
   return hipGetLastError();
 }
@@ -905,48 +945,45 @@ static hipError_t launch_dw_ttt(const uint16_t* Act, const uint16_t* Hin, const 
 // fewer, the uneven last round costs more than the shared hidden-unit copies save: measured on the
 // skewed OPT-1.3B-like shape), 256-column ones otherwise.
 template <bool FRAG, int UT>
-static hipError_t launch_dw_tt(const uint16_t* Act, const uint16_t* Hin, const int32_t* offsets,
-                               const int32_t* tok, const int32_t* border, const uint16_t* zero_row, int N,
-                               int Bs, int d, float* dW, int slot, hipStream_t st, const DwPiece* pieces,
-                               int nblocks, float* stage) {
+static hipError_t launch_dw_tt(const DwOperands* ops, int nops, const int32_t* offsets, const int32_t* tok,
+                               const int32_t* border, const uint16_t* zero_row, int N, int Bs, int d, int slot,
+                               hipStream_t st, const DwPiece* pieces, int nblocks) {
   if (d % 512 == 0 && (int64_t)(d / 512) * N >= 1024)
-    return launch_dw_ttt<FRAG, UT, 512>(Act, Hin, offsets, tok, border, zero_row, N, Bs, d, dW, slot, st, pieces,
-                                        nblocks, stage);
-  return launch_dw_ttt<FRAG, UT, 256>(Act, Hin, offsets, tok, border, zero_row, N, Bs, d, dW, slot, st, pieces,
-                                      nblocks, stage);
+    return launch_dw_ttt<FRAG, UT, 512>(ops, nops, offsets, tok, border, zero_row, N, Bs, d, slot, st, pieces, nblocks);
+  return launch_dw_ttt<FRAG, UT, 256>(ops, nops, offsets, tok, border, zero_row, N, Bs, d, slot, st, pieces, nblocks);
 }
 
 // dW[b][u][c] = sum_{q in bucket b} Hin[q][u] * Act[tok[q]][c] for N buckets of Bs units and d
 // columns (the narrow-block weight-gradient GEMM; also run with a 32-wide side for the adapter
 // gradients of the low-rank variant).
 template <bool FRAG>
-static hipError_t launch_dw_t(const uint16_t* Act, const uint16_t* Hin, const int32_t* offsets,
-                              const int32_t* tok, const int32_t* border, const uint16_t* zero_row, int N,
-                              int Bs, int d, float* dW, int slot, hipStream_t st,
-                              const DwPiece* pieces = nullptr, int nblocks = 0, float* stage = nullptr) {
-  return Bs <= 64 ? launch_dw_tt<FRAG, 64>(Act, Hin, offsets, tok, border, zero_row, N, Bs, d, dW, slot, st, pieces,
-                                           nblocks, stage)
-                  : launch_dw_tt<FRAG, 128>(Act, Hin, offsets, tok, border, zero_row, N, Bs, d, dW, slot, st,
-                                            pieces, nblocks, stage);
+static hipError_t launch_dw_t(const DwOperands* ops, int nops, const int32_t* offsets, const int32_t* tok,
+                              const int32_t* border, const uint16_t* zero_row, int N, int Bs, int d, int slot,
+                              hipStream_t st, const DwPiece* pieces = nullptr, int nblocks = 0) {
+  return Bs <= 64 ? launch_dw_tt<FRAG, 64>(ops, nops, offsets, tok, border, zero_row, N, Bs, d, slot, st, pieces, nblocks)
+                  : launch_dw_tt<FRAG, 128>(ops, nops, offsets, tok, border, zero_row, N, Bs, d, slot, st, pieces, nblocks);
 }
 
 hipError_t launch_dw(const uint16_t* Act, const uint16_t* Hin, bool hin_frag, const int32_t* offsets,
                      const int32_t* tok, const int32_t* border, const uint16_t* zero_row, int N, int Bs, int d,
                      float* dW, int slot, hipStream_t st) {
-  return hin_frag ? launch_dw_t<true>(Act, Hin, offsets, tok, border, zero_row, N, Bs, d, dW, slot, st)
-                  : launch_dw_t<false>(Act, Hin, offsets, tok, border, zero_row, N, Bs, d, dW, slot, st);
+  const DwOperands ops = {Act, Hin, dW, nullptr};
+  return hin_frag ? launch_dw_t<true>(&ops, 1, offsets, tok, border, zero_row, N, Bs, d, slot, st)
+                  : launch_dw_t<false>(&ops, 1, offsets, tok, border, zero_row, N, Bs, d, slot, st);
 }
 
-hipError_t launch_dw_pieces(const uint16_t* Act, const uint16_t* Hin, bool hin_frag, const Schedule& sc, int N,
-                            int Bs, int d, float* dW, float* stage, int slot, hipStream_t st) {
+// The same GEMM over the piece table (Schedule::dw_pieces) of hidden values in fragment order, for one
+// product or two at once, followed by the fixed-order sum of the staged pieces into their blocks (no
+// launch where a routing cannot need any).
+static hipError_t launch_dw_pieces(const DwOperands* ops, int nops, const Schedule& sc, int N, int Bs, int d, int slot,
+                                   hipStream_t st) {
   ScopedKernelTimer tm(slot, st);   // (covers the GEMM and the sum of the staged pieces)
-  const hipError_t e =
-      hin_frag ? launch_dw_t<true>(Act, Hin, nullptr, sc.tok, nullptr, sc.zero_row, sc.dw_cap, Bs, d, dW, -1, st,
-                                   sc.dw_pieces, N, stage)
-               : launch_dw_t<false>(Act, Hin, nullptr, sc.tok, nullptr, sc.zero_row, sc.dw_cap, Bs, d, dW, -1, st,
-                                    sc.dw_pieces, N, stage);
-  if (e != hipSuccess) return e;
-  dw_reduce_kernel<<<1024, 256, 0, st>>>(dW, stage, sc.dw_xlist, Bs, d);
+  const hipError_t e = launch_dw_t<true>(ops, nops, nullptr, sc.tok, nullptr, sc.zero_row, sc.dw_cap, Bs, d, -1, st,
+                                         sc.dw_pieces, N);
+  if (e != hipSuccess || sc.dw_cap == N) return e;
+  const size_t groups = (size_t)(sc.dw_cap - N) * Bs * d / 4;   // 16-byte groups of the most blocks that can have pieces
+  const unsigned gx = (unsigned)(groups / 256 < 1 ? 1 : groups / 256 > 1024 ? 1024 : groups / 256);
+  dw_reduce_kernel<<<dim3(gx, nops), 256, 0, st>>>(ops[0], ops[nops - 1], sc.dw_xlist, Bs, d);
   return hipGetLastError();
 }
 
@@ -1050,9 +1087,11 @@ hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const vo
                        nullptr, st);
   }
   if (e != hipSuccess) return e;
-  e = launch_dw_pieces(dy, w.Hact, true, sc, s.N, s.Bs, s.d, dW2, w.dw_stage, kSlotDW2, st);
-  if (e != hipSuccess) return e;
-  return launch_dw_pieces(x, w.dHpre, true, sc, s.N, s.Bs, s.d, dW1, w.dw_stage, kSlotDW1, st);
+  const DwOperands ops[2] = {{dy, w.Hact, dW2, w.dw_stage}, {x, w.dHpre, dW1, w.dw_stage2}};
+  if (w.dw_stage2) return launch_dw_pieces(ops, 2, sc, s.N, s.Bs, s.d, kSlotDW2, st);   // (both under one slot)
+  const DwOperands second = {x, w.dHpre, dW1, w.dw_stage};
+  e = launch_dw_pieces(ops, 1, sc, s.N, s.Bs, s.d, kSlotDW2, st);
+  return e != hipSuccess ? e : launch_dw_pieces(&second, 1, sc, s.N, s.Bs, s.d, kSlotDW1, st);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -29,6 +29,40 @@ __device__ __forceinline__ size_t hval_off(int q, int u, int Bs) {
 // One row tile of a bucket in an XCD's run order: bucket id and first sorted position.
 struct KdTile { int32_t bucket, q0; };
 
+// Run table.  For token range r (tokens r R .. r R + R - 1) and bucket b the rows of the bucket
+// that belong to the range are one contiguous run of sorted positions (inside a bucket the token
+// ids ascend): [starts[r][b], starts[r+1][b]), a dense table the schedule kernel fills.  One
+// wavefront per range turns its two table rows into the list of the range's NON-EMPTY runs, in
+// ascending block order and cut into pieces of at most SC_RUN rows (one pass of the GEMM
+// kernel's four row tiles), as (block, first, end, 0) records, and their count.  A range has at
+// most N + R k / SC_RUN records.
+constexpr int SC_RUN = 128;
+struct RunRec { int32_t b, lo, hi, pad; };
+
+__device__ __forceinline__ void compact_runs(const int32_t* starts, int N, int cap, RunRec* runs, int32_t* nruns, int r,
+                                             int lane) {
+  const int32_t* s0 = starts + (size_t)r * N;
+  const int32_t* s1 = s0 + N;
+  RunRec* list = runs + (size_t)r * cap;
+  int count = 0;
+  for (int b0 = 0; b0 < N; b0 += 64) {
+    const int b = b0 + lane;
+    const int first = (b < N) ? s0[b] : 0, end = (b < N) ? s1[b] : 0;
+    const int pieces = (end - first + SC_RUN - 1) / SC_RUN;
+    int incl = pieces;  // inclusive scan over the wavefront
+#pragma unroll
+    for (int sft = 1; sft < 64; sft <<= 1) {
+      const int up = __shfl_up(incl, sft);
+      if (lane >= sft) incl += up;
+    }
+    int at = count + incl - pieces;
+    for (int p = 0; p < pieces; ++p, ++at)
+      if (at < cap) list[at] = RunRec{b, first + p * SC_RUN, min(first + (p + 1) * SC_RUN, end), 0};
+    count += __shfl(incl, 63);
+  }
+  if (lane == 0) nruns[r] = count < cap ? count : cap;
+}
+
 // 16-byte slot of (row, chunk) in a stage region with 4 chunks (64 bytes, 32 K-values) per row.
 __device__ __forceinline__ int kd_slot(int row, int chunk) { return row * 4 + (chunk ^ ((row >> 2) & 3)); }
 

@@ -51,40 +51,11 @@ __device__ __forceinline__ void sc_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// Run table.  For token range r (tokens r R .. r R + R - 1) and bucket b the rows of the bucket
-// that belong to the range are one contiguous run of sorted positions (inside a bucket the token
-// ids ascend): [starts[r][b], starts[r+1][b]), a dense table the schedule kernel fills.  One
-// wavefront per range turns its two table rows into the list of the range's NON-EMPTY runs, in
-// ascending block order and cut into pieces of at most SC_RUN rows (one pass of the GEMM
-// kernel's four row tiles), as (block, first, end, 0) records, and their count.  A range has at
-// most N + R k / SC_RUN records.
-constexpr int SC_RUN = 128;
-struct RunRec { int32_t b, lo, hi, pad; };
-
+// One wavefront per token range: see compact_runs.
 __global__ __launch_bounds__(64) void scatter_runs_kernel(const int32_t* __restrict__ starts, int N, int cap,
                                                           RunRec* __restrict__ runs,
                                                           int32_t* __restrict__ nruns) {
-  const int r = blockIdx.x, lane = threadIdx.x;
-  const int32_t* s0 = starts + (size_t)r * N;
-  const int32_t* s1 = s0 + N;
-  RunRec* list = runs + (size_t)r * cap;
-  int count = 0;
-  for (int b0 = 0; b0 < N; b0 += 64) {
-    const int b = b0 + lane;
-    const int first = (b < N) ? s0[b] : 0, end = (b < N) ? s1[b] : 0;
-    const int pieces = (end - first + SC_RUN - 1) / SC_RUN;
-    int incl = pieces;  // inclusive scan over the wavefront
-#pragma unroll
-    for (int sft = 1; sft < 64; sft <<= 1) {
-      const int up = __shfl_up(incl, sft);
-      if (lane >= sft) incl += up;
-    }
-    int at = count + incl - pieces;
-    for (int p = 0; p < pieces; ++p, ++at)
-      if (at < cap) list[at] = RunRec{b, first + p * SC_RUN, min(first + (p + 1) * SC_RUN, end), 0};
-    count += __shfl(incl, 63);
-  }
-  if (lane == 0) nruns[r] = count < cap ? count : cap;
+  compact_runs(starts, N, cap, runs, nruns, blockIdx.x, threadIdx.x);
 }
 
 // KS = Bs / 16 K-steps per block.  A workgroup owns R tokens x 64 output columns; a run (at most
@@ -418,10 +389,14 @@ int32_t* scatter_starts(const ScatterPlan& p, int32_t* table) {
   return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + p.runs_bytes + p.counts_bytes);
 }
 
+RunRec* scatter_runs(const ScatterPlan&, int32_t* table) { return reinterpret_cast<RunRec*>(table); }
+int32_t* scatter_counts(const ScatterPlan& p, int32_t* table) {
+  return reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + p.runs_bytes);
+}
+
 hipError_t run_scatter_ranges(const spt_shape_t& s, const ScatterPlan& p, int32_t* table, hipStream_t st) {
-  RunRec* runs = reinterpret_cast<RunRec*>(table);
-  int32_t* nruns = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(table) + p.runs_bytes);
-  scatter_runs_kernel<<<p.nr, 64, 0, st>>>(scatter_starts(p, table), s.N, p.cap, runs, nruns);
+  scatter_runs_kernel<<<p.nr, 64, 0, st>>>(scatter_starts(p, table), s.N, p.cap, scatter_runs(p, table),
+                                           scatter_counts(p, table));
   return hipGetLastError();
 }
 
