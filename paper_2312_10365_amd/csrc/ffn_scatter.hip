@@ -32,6 +32,7 @@
 // the banks by token id (measured 65 % of the LDS peak with random rows, against 100 % for
 // consecutive rows and 30 % for 4-byte accesses with the lanes on the column axis; the LDS
 // float atomic add runs at a hundredth of that rate).
+#include <math.h>
 #include <stdlib.h>
 #include <type_traits>
 
@@ -364,25 +365,49 @@ __global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
 
 // ------------------------------------------------------------------------------------------
 // host side
-ScatterPlan plan_scatter(const spt_shape_t& s) {
+static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   ScatterPlan p;
   const int budget = 160 * 1024 - SC_STAGES * s.Bs * 128 - SC_STRIDE;  // (one slab row is the dummy)
   int rmax = budget / SC_STRIDE;
   if (rmax > 448) rmax = 448;
   p.nslab = s.d / SC_C;
-  // ranges: as few as the LDS slab allows, but enough workgroups to occupy the chip when the
-  // shape is small (never below 64 tokens per range)
-  p.nr = (s.T + rmax - 1) / rmax;
-  const int fill = (256 + p.nslab - 1) / p.nslab, cap = (s.T + 63) / 64;
-  if (p.nr < fill) p.nr = fill < cap ? fill : (cap > p.nr ? cap : p.nr);
-  p.R = (s.T + p.nr - 1) / p.nr;
-  p.nr = (s.T + p.R - 1) / p.R;
+  // Tokens per range.  A workgroup's time is that of its run records (two thirds of it whatever a record holds, a third
+  // with its rows: slab accesses) plus a prologue and epilogue worth about six of them, and the chip runs
+  // 256 workgroups at a time: of the range counts the LDS slab allows, down to 64 tokens per range, take
+  // the one with the least record time in a row.  Rows of a range in a block are about Binomial(R, k / N), so a
+  // record count per block of 1 + P(rows > 128) + ...: at k / N = 1/4 432 tokens (108 rows) are near the best
+  // ratio, at 2/5 300 are (448 would need two records for almost every block).
+  const double share = (double)s.k / s.N;
+  const int nr_min = (s.T + rmax - 1) / rmax, nr_max = (s.T + 63) / 64 > nr_min ? (s.T + 63) / 64 : nr_min;
+  double best = -1.0;
+  for (int nr = nr_min; nr <= nr_max && nr <= nr_min + 512; ++nr) {
+    const int R = (s.T + nr - 1) / nr, real_nr = (s.T + R - 1) / R;
+    const double mean = R * share, sd = sqrt(mean * (1.0 - share) + 1e-9);
+    double records = 1.0 - exp(-mean);                       // (blocks none of the range's tokens activates have none)
+    for (int c = 1; c * SC_RUN < mean + 6.0 * sd; ++c) records += 0.5 * erfc((c * SC_RUN + 0.5 - mean) / (sd * 1.41421356));
+    const int64_t rounds = ((int64_t)real_nr * p.nslab + 255) / 256;
+    const double cost = (double)rounds * (s.N * records * (0.7 + 0.3 * (mean < SC_RUN ? mean / SC_RUN : 1.0)) + 4.0 + R * 0.005);
+    if (best < 0.0 || cost < best * 0.999) { best = cost; p.R = R; p.nr = real_nr; }
+  }
   p.smem = (p.R + 1) * SC_STRIDE + SC_STAGES * s.Bs * 128;
   p.cap = s.N + (int)(((int64_t)p.R * s.k + SC_RUN - 1) / SC_RUN);
   p.runs_bytes = align256((size_t)p.nr * p.cap * sizeof(RunRec));
   p.counts_bytes = align256((size_t)p.nr * 4);
   p.table_bytes = p.runs_bytes + p.counts_bytes + align256((size_t)(p.nr + 1) * s.N * 4);
   return p;
+}
+
+// (The search over range counts takes tens of microseconds and every call of the path asks several times:
+// each thread keeps the plans of the last few shapes, which are functions of the shape alone.)
+ScatterPlan plan_scatter(const spt_shape_t& s) {
+  struct Kept { int32_t T, d, N, Bs, k; ScatterPlan plan; };
+  static thread_local Kept kept[8] = {};
+  static thread_local int next = 0;
+  for (const Kept& e : kept)
+    if (e.T == s.T && e.d == s.d && e.N == s.N && e.Bs == s.Bs && e.k == s.k) return e.plan;
+  Kept& e = kept[next++ & 7];
+  e = Kept{s.T, s.d, s.N, s.Bs, s.k, plan_scatter_once(s)};
+  return e.plan;
 }
 
 int32_t* scatter_starts(const ScatterPlan& p, int32_t* table) {
