@@ -383,6 +383,92 @@ __global__ __launch_bounds__(256, 2) void ffn_up_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
+// The same forward GEMM where a bucket holds a handful of rows (decoding batches): every weight is read
+// for few multiply-adds, so the launch is bound by streaming W1 and wants bytes in flight on all CUs, not
+// tiles.  A workgroup owns 32 hidden units of one block and 32 RT bucket rows at a time; its four
+// wavefronts split d in chunks of 32 and load both operands straight into registers, chunks ahead
+// (a lane reads 32 contiguous bytes of a row; which K-values share an MFMA slot is the same for both
+// operands, which is all a contraction needs).  The wavefronts' sums are added through LDS in order.
+// 7B-like layer, 24 tokens (6 rows a bucket): 41 us, with 256-row tiles 69 (128 of 256 CUs, one K-stage per
+// memory latency).
+template <int ACT, int RT>
+__global__ __launch_bounds__(256) void ffn_up_few_rows_kernel(
+    const uint16_t* __restrict__ W1, const uint16_t* __restrict__ X, const int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ tok, int Bs, int d, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact) {
+  constexpr int DEPTH = 4;                       // chunks in registers, DEPTH - 1 of them in flight (8: no faster)
+  __shared__ float red[4][RT][16][64];
+  const int b = blockIdx.x, u0 = blockIdx.y * 32;
+  const int qb = offsets[b], qe = offsets[b + 1];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = lane & 31, h = lane >> 5;
+  const int chunks = d / 32, cbeg = wave * chunks / 4, cend = (wave + 1) * chunks / 4, clast = cend - 1;
+  const uint16_t* wrow = W1 + ((size_t)b * Bs + u0 + rho32(i)) * d + 16 * h;
+  for (int q0 = qb; q0 < qe; q0 += 32 * RT) {
+    const uint16_t* xrow[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) xrow[rt] = X + (size_t)tok[min(q0 + rt * 32 + i, qe - 1)] * d + 16 * h;
+    f32x16 acc[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
+    uint4 wq[DEPTH][2], xq[DEPTH][RT][2];
+    auto fetch = [&](int st, int c) {
+      const int k0 = min(c, clast) * 32;       // (requests past the last chunk repeat it: no branch around a load)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        wq[st][s] = *reinterpret_cast<const uint4*>(wrow + k0 + 8 * s);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) xq[st][rt][s] = *reinterpret_cast<const uint4*>(xrow[rt] + k0 + 8 * s);
+      }
+    };
+    auto consume = [&](int st) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wq[st][s]), as_bf16x8(xq[st][rt][s]), acc[rt], 0, 0, 0);
+    };
+    if (cbeg < cend) {
+#pragma unroll
+      for (int s = 0; s < DEPTH - 1; ++s) fetch(s, cbeg + s);
+      int c = cbeg;
+      for (; c + DEPTH <= cend; c += DEPTH) {
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) {
+          fetch((s + DEPTH - 1) % DEPTH, c + s + DEPTH - 1);
+          consume(s);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < DEPTH - 1; ++s)
+        if (c + s < cend) consume(s);
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[wave][rt][v][lane] = acc[rt][v];
+    __syncthreads();
+    // wavefront w finishes accumulators 4 w .. 4 w + 3: hidden units u0 + 16 h + 4 w .. + 3 of the lane's row
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const int q = q0 + rt * 32 + i, u = u0 + 16 * h + 4 * wave;
+      float z[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        z[e] = ((red[0][rt][4 * wave + e][lane] + red[1][rt][4 * wave + e][lane]) + red[2][rt][4 * wave + e][lane]) +
+               red[3][rt][4 * wave + e][lane];
+      if (q < qe) {
+        if (Hsave) *reinterpret_cast<uint2*>(Hsave + (size_t)q * Bs + u) = make_uint2(pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3]));
+        *reinterpret_cast<uint2*>(Hact + hfrag_off(q, u, Bs)) =
+            make_uint2(pack_bf16x2(act_fn<ACT>(z[0]), act_fn<ACT>(z[1])), pack_bf16x2(act_fn<ACT>(z[2]), act_fn<ACT>(z[3])));
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // K = bucket rows GEMMs for Bs <= 128: dW1 (Act = X, Hin = dHpre) and dW2 (Act = dY, Hin = act(H)).
 //   dW[b][u][c] = sum_{q in bucket b} Hin[q][u] * Act[tok[q]][c]    MFMA rows c, columns u
 // K runs over the bucket's rows in sorted order, so the sum order is fixed (no split-K, no
@@ -739,6 +825,14 @@ static int max_row_tiles(const spt_shape_t& s, int rows) {
 
 static bool use_narrow(const spt_shape_t& s) { return s.Bs <= TILE; }
 
+// Few rows per bucket on average: a decoding batch.  Measured up-projection, us, 256-row tiles against this: 7B-like
+// layer, 16 rows 70, 47; 32 rows 75, 66; 64 rows 76, 112; layers with no more than one workgroup per CU gain up
+// to 64 rows (d 2048, N 64: 40, 30; 128 rows: 40, 46).
+static bool few_rows(const spt_shape_t& s) {
+  const int64_t P = (int64_t)s.T * s.k;
+  return P <= 40 * (int64_t)s.N || (P <= 64 * (int64_t)s.N && s.N * (s.Bs / 32) <= 256);
+}
+
 static size_t carve_schedule(const spt_shape_t& s, char* p, size_t o0, Schedule& sc, bool weight_grads = false) {
   const size_t P = (size_t)s.T * s.k;
   size_t o = o0;
@@ -783,6 +877,8 @@ FwdWorkspace plan_fwd(const spt_shape_t& s, void* ws) {
   o += carve_schedule(s, p, o, w.sched);
   w.Hact = reinterpret_cast<uint16_t*>(p + o);       o += align256(hrows(P) * s.Bs * 2);
   o += carve_part(s, p, o, w.part);
+  w.split = use_narrow(s) ? reinterpret_cast<float*>(p + o) : nullptr;
+  o += use_narrow(s) ? plan_scatter(s).split_bytes : 0;
   w.bytes = o;
   return w;
 }
@@ -796,6 +892,8 @@ BwdWorkspace plan_bwd(const spt_shape_t& s, void* ws, bool weight_grads) {
   w.Hact = reinterpret_cast<uint16_t*>(p + o);       o += align256(hrows(P) * s.Bs * 2);
   w.dHpre = reinterpret_cast<uint16_t*>(p + o);      o += align256(hrows(P) * s.Bs * 2);
   o += carve_part(s, p, o, w.part);
+  w.split = use_narrow(s) ? reinterpret_cast<float*>(p + o) : nullptr;
+  o += use_narrow(s) ? plan_scatter(s).split_bytes : 0;
   w.dw_stage = w.dw_stage2 = nullptr;
   if (w.sched.dw_cap > 0) {
     // Both gradients go out in one launch, with staging slots of their own, unless those are large:
@@ -891,6 +989,18 @@ static hipError_t launch_up_t(const spt_shape_t& s, const uint16_t* Wa, const ui
   ffn_up_kernel<MODE, ACT, KS><<<dim3(8 * wg_per_xcd), 256, FU_SMEM_BYTES, st>>>(
       Wa, Act, offsets, sc.kd_count, static_cast<const KdTile*>(sc.kd_list), sc.kd_cap, sc.tok, s.Bs, s.d,
       Hsave, Hact, dHpre, Xe, We);
+  return hipGetLastError();
+}
+
+// The forward GEMM of a batch with few rows per bucket (see ffn_up_few_rows_kernel).
+static hipError_t launch_up_few_rows(const spt_shape_t& s, const uint16_t* W1, const uint16_t* X, const int32_t* offsets,
+                                     const Schedule& sc, uint16_t* Hsave, uint16_t* Hact, hipStream_t st) {
+  const dim3 grid(s.N, s.Bs / 32);
+  const bool one = (int64_t)s.T * s.k <= (int64_t)24 * s.N;
+#define SPT_FEW(ACT, RT) ffn_up_few_rows_kernel<ACT, RT><<<grid, 256, 0, st>>>(W1, X, offsets, sc.tok, s.Bs, s.d, Hsave, Hact)
+  if (s.act == SPT_ACT_GELU) { if (one) SPT_FEW(0, 1); else SPT_FEW(0, 2); }
+  else                       { if (one) SPT_FEW(1, 1); else SPT_FEW(1, 2); }
+#undef SPT_FEW
   return hipGetLastError();
 }
 
@@ -1013,12 +1123,13 @@ hipError_t run_fwd(const spt_shape_t& s, const void* X, const void* W1, const vo
   if (use_narrow(s)) {
     {
       ScopedKernelTimer tm(kSlotUp, st);
-      e = launch_up<0>(s, w1, x, offsets, sc, hs, w.Hact, nullptr, st);
+      e = few_rows(s) ? launch_up_few_rows(s, w1, x, offsets, sc, hs, w.Hact, st)
+                      : launch_up<0>(s, w1, x, offsets, sc, hs, w.Hact, nullptr, st);
     }
     if (e != hipSuccess) return e;
     ScopedKernelTimer tm(kSlotDown, st);
     return launch_scatter(s, plan_scatter(s), w.Hact, w2, sc.rstart, sc.tok,
-                          static_cast<uint16_t*>(Y), nullptr, st);
+                          static_cast<uint16_t*>(Y), nullptr, w.split, st);
   }
   WideArgs a = wide_args(s, offsets, sc);
   a.A = w1; a.B = x; a.Hsave = hs; a.Hact = w.Hact;
@@ -1084,7 +1195,7 @@ hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const vo
   {
     ScopedKernelTimer tm(kSlotDXPart, st);
     e = launch_scatter(s, plan_scatter(s), w.dHpre, w1, sc.rstart, sc.tok, static_cast<uint16_t*>(dX),
-                       nullptr, st);
+                       nullptr, w.split, st);
   }
   if (e != hipSuccess) return e;
   const DwOperands ops[2] = {{dy, w.Hact, dW2, w.dw_stage}, {x, w.dHpre, dW1, w.dw_stage2}};
@@ -1200,7 +1311,7 @@ hipError_t run_lora_fwd(const spt_shape_t& s, int r, const void* X, const void* 
   if (!narrow) return run_combine(s, w.fwd.part, inv, Y, 0, s.d, (size_t)s.d, (size_t)TILE, kSlotCombineY, st, w.Z);
   ScopedKernelTimer tm(kSlotDown, st);
   return launch_scatter(s, plan_scatter(s), w.fwd.Hact, static_cast<const uint16_t*>(W2), w.fwd.sched.rstart,
-                        w.fwd.sched.tok, static_cast<uint16_t*>(Y), w.Z, st);
+                        w.fwd.sched.tok, static_cast<uint16_t*>(Y), w.Z, w.fwd.split, st);
 }
 
 hipError_t run_lora_bwd(const spt_shape_t& s, int r, const void* X, const void* W1, const void* W2,
@@ -1267,7 +1378,7 @@ hipError_t run_lora_bwd(const spt_shape_t& s, int r, const void* X, const void* 
   if (narrow) {
     ScopedKernelTimer tm(kSlotDXPart, st);
     e = launch_scatter(s, plan_scatter(s), w.bwd.dHpre, static_cast<const uint16_t*>(W1), sc.rstart, sc.tok,
-                       static_cast<uint16_t*>(dX), w.Z, st);
+                       static_cast<uint16_t*>(dX), w.Z, w.bwd.split, st);
   } else {
     e = run_combine(s, w.bwd.part, inv, dX, 0, s.d, (size_t)s.d, (size_t)TILE, kSlotCombineDX, st, w.Z);
   }

@@ -92,7 +92,8 @@ template <int KS>
 __global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
     const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
     const int32_t* __restrict__ nruns, const int32_t* __restrict__ tok, int N, int d, int T, int R,
-    int nr, int nslab, int cap, uint16_t* __restrict__ out, const uint16_t* __restrict__ Z) {
+    int nr, int nslab, int cap, uint16_t* __restrict__ out, const uint16_t* __restrict__ Z,
+    float* __restrict__ split) {
   constexpr int Bs = KS * 16;
   constexpr int THREADS = SC_THREADS;
   constexpr int NWAVES = THREADS / 64;
@@ -130,8 +131,11 @@ __global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
   char* ring = slab_lds + ring_off;
 
   typedef const __attribute__((address_space(4))) RunRec* const_run_ptr;
-  const const_run_ptr rl = (const_run_ptr)(uintptr_t)(runs + (size_t)r * cap);
-  const int M = __builtin_amdgcn_readfirstlane(nruns[r]);
+  // (few tokens: blockIdx.y takes its part of the range's records and leaves fp32 sums to be added)
+  const int Mall = __builtin_amdgcn_readfirstlane(nruns[r]);
+  const int jfirst = (int)((int64_t)Mall * blockIdx.y / gridDim.y);
+  const int M = (int)((int64_t)Mall * (blockIdx.y + 1) / gridDim.y) - jfirst;
+  const const_run_ptr rl = (const_run_ptr)(uintptr_t)(runs + (size_t)r * cap + jfirst);
   struct Run { int b, lo, hi; bool real; };
   auto run_at = [&](int j) {  // wave-uniform scalar load; past the end: the last run again, marked unreal
     const int jj = j < M ? j : (M > 0 ? M - 1 : 0);
@@ -209,6 +213,12 @@ __global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
   // ---- prologue: request the first operands, clear the slab while they fly, stage slices 0 and
   // 1 and read run 0's fragments.  (Every token activates k >= 1 blocks, so a range always has
   // runs; M = 0 means a caller's table that lists nothing for these tokens: zeros.)
+  if (M == 0 && split) {
+    for (int it = tid; it < rows * (SC_C / 4); it += THREADS)
+      *reinterpret_cast<uint4*>(split + ((size_t)blockIdx.y * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
+          make_uint4(0u, 0u, 0u, 0u);
+    return;
+  }
   if (M == 0) {
     for (int it = tid; it < rows * (SC_C / 8); it += THREADS) {
       const size_t o = (size_t)(t0 + it / (SC_C / 8)) * d + c0 + (it % (SC_C / 8)) * 8;
@@ -325,6 +335,12 @@ __global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
   } while (j < M);
   sc_barrier();
 
+  if (split) {
+    for (int it = tid; it < rows * (SC_C / 4); it += THREADS)
+      *reinterpret_cast<uint4*>(split + ((size_t)blockIdx.y * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
+          *reinterpret_cast<const uint4*>(slab_lds + (it / (SC_C / 4)) * SC_STRIDE + (it % (SC_C / 4)) * 16);
+    return;
+  }
   // write the slab out: one rounding to bf16 (+ the low-rank row of the token, if any)
   constexpr int CG = SC_C / 8;  // 16-byte output pieces per row
   if (!Z) {
@@ -363,6 +379,21 @@ __global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
   }
 }
 
+// out = the parts' sums added in order (+ the low-rank row), rounded once.
+__global__ __launch_bounds__(256) void scatter_sum_kernel(const float* __restrict__ split, int splits, int64_t total,
+                                                          uint16_t* __restrict__ out, const uint16_t* __restrict__ Z) {
+  const int64_t at = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (at >= total) return;
+  f32x4 s = *reinterpret_cast<const f32x4*>(split + at);
+#pragma unroll 4
+  for (int z = 1; z < splits; ++z) s += *reinterpret_cast<const f32x4*>(split + (size_t)z * total + at);
+  if (Z) {
+    const uint2 z = *reinterpret_cast<const uint2*>(Z + at);
+    s += f32x4{lo_bf16(z.x), hi_bf16(z.x), lo_bf16(z.y), hi_bf16(z.y)};
+  }
+  *reinterpret_cast<uint2*>(out + at) = make_uint2(pack_bf16x2(s[0], s[1]), pack_bf16x2(s[2], s[3]));
+}
+
 // ------------------------------------------------------------------------------------------
 // host side
 static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
@@ -385,10 +416,16 @@ static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
     const double mean = R * share, sd = sqrt(mean * (1.0 - share) + 1e-9);
     double records = 1.0 - exp(-mean);                       // (blocks none of the range's tokens activates have none)
     for (int c = 1; c * SC_RUN < mean + 6.0 * sd; ++c) records += 0.5 * erfc((c * SC_RUN + 0.5 - mean) / (sd * 1.41421356));
-    const int64_t rounds = ((int64_t)real_nr * p.nslab + 255) / 256;
-    const double cost = (double)rounds * (s.N * records * (0.7 + 0.3 * (mean < SC_RUN ? mean / SC_RUN : 1.0)) + 4.0 + R * 0.005);
-    if (best < 0.0 || cost < best * 0.999) { best = cost; p.R = R; p.nr = real_nr; }
+    // With few tokens the block list is cut into parts too (16 records or more each), whose fp32 sums are
+    // added by another launch: fewer weight slices per workgroup, for 8 bytes per part, token and column.
+    for (int sp = 1; sp == 1 || (sp <= 16 && sp * 16 <= s.N); sp += sp < 4 ? 1 : 2) {
+      const int64_t rounds = ((int64_t)real_nr * p.nslab * sp + 255) / 256;
+      double cost = (double)rounds * (s.N * records * (0.7 + 0.3 * (mean < SC_RUN ? mean / SC_RUN : 1.0)) / sp + 4.0 + R * 0.005);
+      if (sp > 1) cost += 5.0 + (double)sp * s.T * s.d * 8.0 / 2.5e6;   // (in records of 0.7 us)
+      if (best < 0.0 || cost < best * 0.999) { best = cost; p.R = R; p.nr = real_nr; p.splits = sp; }
+    }
   }
+  p.split_bytes = p.splits > 1 ? align256((size_t)p.splits * s.T * s.d * 4) : 0;
   p.smem = (p.R + 1) * SC_STRIDE + SC_STAGES * s.Bs * 128;
   p.cap = s.N + (int)(((int64_t)p.R * s.k + SC_RUN - 1) / SC_RUN);
   p.runs_bytes = align256((size_t)p.nr * p.cap * sizeof(RunRec));
@@ -428,7 +465,7 @@ hipError_t run_scatter_ranges(const spt_shape_t& s, const ScatterPlan& p, int32_
 template <int KS>
 static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin,
                                    const uint16_t* W, const int32_t* table, const int32_t* tok,
-                                   uint16_t* out, const uint16_t* Z, hipStream_t st) {
+                                   uint16_t* out, const uint16_t* Z, float* split, hipStream_t st) {
   static bool attr_set = false;
   if (!attr_set) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_scatter_kernel<KS>),
@@ -445,15 +482,21 @@ static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, c
   }
   const RunRec* runs = reinterpret_cast<const RunRec*>(table);
   const int32_t* nruns = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + p.runs_bytes);
-  ffn_scatter_kernel<KS><<<grid, SC_THREADS, p.smem, st>>>(Hin, W, runs, nruns, tok, s.N, s.d, s.T, p.R, p.nr,
-                                                            p.nslab, p.cap, out, Z);
+  const bool parts = p.splits > 1;
+  ffn_scatter_kernel<KS><<<dim3(grid, p.splits), SC_THREADS, p.smem, st>>>(Hin, W, runs, nruns, tok, s.N, s.d, s.T, p.R,
+                                                                         p.nr, p.nslab, p.cap, out, Z, parts ? split : nullptr);
+  if (!parts) return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t total = (int64_t)s.T * s.d;
+  scatter_sum_kernel<<<(unsigned)((total / 4 + 255) / 256), 256, 0, st>>>(split, p.splits, total, out, Z);
   return hipGetLastError();
 }
 
 hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W,
                           const int32_t* table, const int32_t* tok, uint16_t* out, const uint16_t* Z,
-                          hipStream_t st) {
-#define SPT_SC(KS) launch_scatter_t<KS>(s, p, Hin, W, table, tok, out, Z, st)
+                          float* split, hipStream_t st) {
+#define SPT_SC(KS) launch_scatter_t<KS>(s, p, Hin, W, table, tok, out, Z, split, st)
   switch (s.Bs / 16) {
     case 2: return SPT_SC(2);
     case 4: return SPT_SC(4);

@@ -46,6 +46,7 @@ struct FwdWorkspace {
   Schedule sched;
   uint16_t* Hact;        // bf16 activated hidden values per pair (narrow blocks: fragment order)
   uint16_t* part;        // [P,d] bf16 per-pair partial output rows (wide blocks only)
+  float* split;          // ScatterPlan::split_bytes (narrow blocks)
   size_t bytes;
 };
 struct BwdWorkspace {
@@ -53,6 +54,7 @@ struct BwdWorkspace {
   uint16_t* Hact;   // act(Hsave) per pair  (narrow blocks: fragment order, ffn_common.hpp;
   uint16_t* dHpre;  // dHpre per pair        wide blocks: row-major [P,Bs])
   uint16_t* part;   // [P,d] per-pair partial dX rows (wide blocks only)
+  float* split;     // ScatterPlan::split_bytes (narrow blocks)
   float* dw_stage;  // [dw_cap - N][Bs][d] products of the pieces after a bucket's first (narrow blocks)
   float* dw_stage2; // ... of the second gradient, when both are formed in one launch; else null
   size_t bytes;
@@ -66,6 +68,8 @@ BwdWorkspace plan_bwd(const spt_shape_t& s, void* ws, bool weight_grads = true);
 struct ScatterPlan {
   int R, nr, nslab, smem;
   int cap;               // run records per range
+  int splits;            // parts of the block list given to workgroups of their own (few tokens; else 1)
+  size_t split_bytes;    // [splits][T][d] fp32 sums of the parts, added afterwards
   size_t runs_bytes;     // bytes of the [nr][cap] run records
   size_t counts_bytes;   // bytes of the per-range record counts
   size_t table_bytes;    // run records + counts + the dense [nr+1][N] table of run starts
@@ -81,7 +85,7 @@ hipError_t run_scatter_ranges(const spt_shape_t& s, const ScatterPlan& p, int32_
 // out[t][:] = sum_{b in S(t), ascending} Hin[pos(t,b)][:] W[b]  (+ Z[t][:] when Z is given)
 hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W,
                           const int32_t* rstart, const int32_t* tok, uint16_t* out, const uint16_t* Z,
-                          hipStream_t st);
+                          float* split, hipStream_t st);
 
 // Arguments of the wide-block GEMM kernels (blocks of more than 128 hidden units).
 struct WideArgs {
