@@ -215,18 +215,30 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
 // bound by bytes entering the CU; two workgroups per CU.  The K = Bs contraction that follows
 // (down-projection, dX) is the token-range-stationary kernel of ffn_scatter.hip.
 constexpr int KD_KT = 32;  // K values per stage
-constexpr int FU_ROWS = 256;
-constexpr int FU_STAGE1_SLOTS = (TILE + FU_ROWS) * 4;     // one stage: 24 KiB
-constexpr int FU_SMEM_BYTES = 3 * FU_STAGE1_SLOTS * 16;   // 72 KiB
+constexpr int FU_ROWS = 256;      // rows of a tile
+constexpr int FU_ROWS_FEW = 64;   // ... where 256-row tiles would leave CUs without one
 
-template <int MODE, int ACT, int KS>
-__global__ __launch_bounds__(256, 2) void ffn_up_kernel(
+// WV wavefronts own 32 NI rows each: (4, 2) = 256-row tiles with a 3-slot ring, two workgroups per CU;
+// (2, 1) = 64-row tiles with a 4-slot ring, three per CU.
+template <int KS, int WV>
+struct UpTile {
+  static constexpr int NI = WV == 4 ? 2 : 1, ROWS = 32 * NI * WV, SLOTS = WV == 4 ? 3 : 4;
+  static constexpr int UNITS = KS * 16;                      // weight rows of a stage
+  static constexpr int STAGE_SLOTS = (UNITS + ROWS) * 4;     // 16-byte slots of a stage (24 KiB at 256 rows x 128 units)
+  static constexpr int SMEM = SLOTS * STAGE_SLOTS * 16;
+};
+
+template <int MODE, int ACT, int KS, int WV>
+__global__ __launch_bounds__(64 * WV, 2) void ffn_up_kernel(
     const uint16_t* __restrict__ Wa, const uint16_t* __restrict__ Act,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ kd_count,
     const KdTile* __restrict__ kd_list, int cap, const int32_t* __restrict__ tok, int Bs, int d,
     uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact, uint16_t* __restrict__ dHpre,
     const uint16_t* __restrict__ Xe, const uint16_t* __restrict__ We) {
   constexpr int MI = KS / 2;   // 32-unit tiles of the block
+  typedef UpTile<KS, WV> Tile;
+  constexpr int NI = Tile::NI, SLOTS = Tile::SLOTS, STAGE = Tile::STAGE_SLOTS;
+  constexpr int PA = 2 * MI, NA = (PA + WV - 1) / WV, NB = 2 * NI, NP = NA + NB;   // copies per stage: weights, of a wavefront, rows, all
   extern __shared__ uint4 fu_smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint32_t lds0 = (uint32_t)(uintptr_t)fu_smem;
@@ -243,81 +255,81 @@ __global__ __launch_bounds__(256, 2) void ffn_up_kernel(
     const int qend = offsets[b + 1];
     __builtin_amdgcn_s_barrier();  // LDS of the previous tile is free
 
-    // DMA: a stage is 128 weight rows + 256 gathered rows of 64 bytes (32 K-values);
-    // an instruction moves 16 rows; this wavefront issues 2 + 4 of the 8 + 16 per stage.
+    // DMA: a stage is the block's weight rows + the tile's gathered rows of 64 bytes (32 K-values);
+    // an instruction moves 16 rows; this wavefront issues NA + NB of them per stage.
     // Lane L of instruction j fills row 16 j + L / 4, physical chunk L % 4 = logical ^ swizzle.
     // (the swizzle term (row >> 2) & 3 is (lane >> 4) & 3 for every instruction: the rows an
     // instruction covers start at a multiple of 16)
     const int ch8 = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;
-    int urow[2], tq[4];  // hidden unit / token id of this lane's row in each instruction
+    int urow[NA], apiece[NA], tq[NB];  // hidden unit / token id of this lane's row in each instruction
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int row = (wave * 2 + j) * 16 + (lane >> 2);
-      urow[j] = b * Bs + (row < Bs ? row : 0);
+    for (int j = 0; j < NA; ++j) {
+      apiece[j] = (wave * NA + j) % PA;  // (surplus instructions repeat one: same bytes to the same place)
+      urow[j] = b * Bs + apiece[j] * 16 + (lane >> 2);
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = (wave * 4 + j) * 16 + (lane >> 2);
+    for (int j = 0; j < NB; ++j) {
+      const int row = (wave * NB + j) * 16 + (lane >> 2);
       tq[j] = tok[(q0 + row < qend) ? q0 + row : q0];
     }
     // (row addresses are formed once per tile: a 64-bit multiply per copy in the K loop sits on
     // the path between the barrier and the fragment reads)
-    const uint16_t* arow[2];
-    const uint16_t* brow[4];
+    const uint16_t* arow[NA];
+    const uint16_t* brow[NB];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) arow[j] = Wa + (size_t)urow[j] * d + ch8;
+    for (int j = 0; j < NA; ++j) arow[j] = Wa + (size_t)urow[j] * d + ch8;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) brow[j] = Act + (size_t)tq[j] * d + ch8;
-    // copy `piece` (0, 1: weight rows; 2 .. 5: gathered rows) of K-stage kt into ring slot `stage`
+    for (int j = 0; j < NB; ++j) brow[j] = Act + (size_t)tq[j] * d + ch8;
+    // copy `piece` (0 .. NA-1: weight rows; then gathered rows) of K-stage kt into ring slot `stage`
     auto issue_piece = [&](int stage, int kt, int piece) {
-      const uint32_t base = lds0 + (uint32_t)(stage * FU_STAGE1_SLOTS) * 16u;
+      const uint32_t base = lds0 + (uint32_t)(stage * STAGE) * 16u;
       const bool ext = kt >= nkd;  // wave-uniform
-      if (piece < 2) {
+      if (piece < NA) {
         const int j = piece;
         dma16(ext ? We + (size_t)urow[j] * (2 * KD_KT) + ch8 + (kt - nkd) * KD_KT : arow[j] + kt * KD_KT,
-              __builtin_amdgcn_readfirstlane(base + (uint32_t)((wave * 2 + j) * 64) * 16u));
+              __builtin_amdgcn_readfirstlane(base + (uint32_t)(apiece[j] * 64) * 16u));
       } else {
-        const int j = piece - 2;
+        const int j = piece - NA;
         dma16(ext ? Xe + (size_t)tq[j] * (2 * KD_KT) + ch8 + (kt - nkd) * KD_KT : brow[j] + kt * KD_KT,
-              __builtin_amdgcn_readfirstlane(base + (uint32_t)(TILE * 4 + (wave * 4 + j) * 64) * 16u));
+              __builtin_amdgcn_readfirstlane(base + (uint32_t)(Tile::UNITS * 4 + (wave * NB + j) * 64) * 16u));
       }
     };
 
-    f32x16 acc[MI][2];
+    f32x16 acc[MI][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
+      for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
-    // Ring schedule: "issue j" copies K-stage min(j, nk-1) into slot j % 3; past the last stage it
+    // Ring schedule: "issue j" copies K-stage min(j, nk-1) into slot j % SLOTS; past the last stage it
     // repeats it into a slot nobody reads any more, so the loop body has no branch and every
-    // vmcnt wait is a constant.  Issues 0 and 1 go out up front, iteration kt sends issue kt+2
+    // vmcnt wait is a constant.  Issues 0 .. SLOTS-2 go out up front, iteration kt sends issue kt+SLOTS-1
     // piece by piece behind its first MFMAs (the slot stage kt-1 left at the barrier).
     const int klast = nk - 1;
 #pragma unroll
-    for (int p6 = 0; p6 < 6; ++p6) issue_piece(0, 0, p6);
+    for (int st = 0; st < SLOTS - 1; ++st)
 #pragma unroll
-    for (int p6 = 0; p6 < 6; ++p6) issue_piece(1, klast < 1 ? klast : 1, p6);
+      for (int p = 0; p < NP; ++p) issue_piece(st, klast < st ? klast : st, p);
     int stage = 0;
     for (int kt = 0; kt < nk; ++kt) {
-      // own copies of stage kt have landed (stage kt+1's six may still be in flight) ...
-      wait_vmcnt<6>();
+      // own copies of stage kt have landed (those of the SLOTS-2 stages after it may still be in flight) ...
+      wait_vmcnt<NP * (SLOTS - 2)>();
       __builtin_amdgcn_s_barrier();  // ... and everyone's; all are done reading stage kt-1
-      const int fill = stage >= 1 ? stage - 1 : 2;
-      const int kfill = kt + 2 < klast ? kt + 2 : klast;
-      const uint4* As = fu_smem + stage * FU_STAGE1_SLOTS;
-      const uint4* Bt = As + TILE * 4;
+      const int fill = stage >= 1 ? stage - 1 : SLOTS - 1;
+      const int kfill = kt + SLOTS - 1 < klast ? kt + SLOTS - 1 : klast;
+      const uint4* As = fu_smem + stage * STAGE;
+      const uint4* Bt = As + Tile::UNITS * 4;
       // all fragment reads of the stage go out first, so the MFMAs of the first K-step run
       // while the second K-step's fragments are still arriving (the compiler left to itself
       // sinks each read next to its use and exposes the LDS latency every few MFMAs)
-      bf16x8 a[KD_KT / 16][MI], bb[KD_KT / 16][2];
+      bf16x8 a[KD_KT / 16][MI], bb[KD_KT / 16][NI];
 #pragma unroll
       for (int s = 0; s < KD_KT / 16; ++s) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) a[s][mi] = as_bf16x8(As[kd_slot(mi * 32 + i, 2 * s + h)]);
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni) bb[s][ni] = as_bf16x8(Bt[kd_slot(wave * 64 + ni * 32 + i, 2 * s + h)]);
+        for (int ni = 0; ni < NI; ++ni) bb[s][ni] = as_bf16x8(Bt[kd_slot(wave * 32 * NI + ni * 32 + i, 2 * s + h)]);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -325,24 +337,24 @@ __global__ __launch_bounds__(256, 2) void ffn_up_kernel(
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-          for (int ni = 0; ni < 2; ++ni) {
+          for (int ni = 0; ni < NI; ++ni) {
             acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][mi], bb[s][ni], acc[mi][ni], 0, 0, 0);
-            const int m = (s * MI + mi) * 2 + ni;
-            if (m < 6) {
+            const int m = (s * MI + mi) * NI + ni;
+            if (m < NP) {
               issue_piece(fill, kfill, m);
               __builtin_amdgcn_sched_barrier(0);
             }
           }
 #pragma unroll
-      for (int m = (KD_KT / 16) * MI * 2; m < 6; ++m) issue_piece(fill, kfill, m);  // 32-unit blocks: 4 MFMAs only
+      for (int m = (KD_KT / 16) * MI * NI; m < NP; ++m) issue_piece(fill, kfill, m);  // (small blocks: fewer MFMAs than copies)
       __builtin_amdgcn_sched_barrier(0);
-      stage = (stage == 2) ? 0 : stage + 1;
+      stage = (stage == SLOTS - 1) ? 0 : stage + 1;
     }
     wait_vmcnt<0>();  // the trailing copies (repeats of the last stage) are done too
     // epilogue: lane (i, h) holds, for row q, units 32 mi + 8 g + 4 h + e  (v = 4 g + e)
 #pragma unroll
-    for (int ni = 0; ni < 2; ++ni) {
-      const int q = q0 + wave * 64 + ni * 32 + i;
+    for (int ni = 0; ni < NI; ++ni) {
+      const int q = q0 + wave * 32 * NI + ni * 32 + i;
       const bool live = q < qend;
       const size_t orow = (size_t)(live ? q : q0) * Bs;
 #pragma unroll
@@ -825,6 +837,14 @@ static int max_row_tiles(const spt_shape_t& s, int rows) {
 
 static bool use_narrow(const spt_shape_t& s) { return s.Bs <= TILE; }
 
+// Rows of a K = d tile: 256, or 64 (narrow blocks) where 256-row tiles of mean buckets would occupy fewer than half
+// the CUs.  us, 256 against 64 rows: 64 tiles (T 3053, d 1088, N 16) 30, 21; 128 tiles 55, 54 (T 2000, d 2048,
+// N 64) and 85, 95 (T 1000, d 4096, N 128); 213 tiles 26, 32.
+static int kd_rows(const spt_shape_t& s) {
+  const int64_t mean = ((int64_t)s.T * s.k + s.N - 1) / s.N;
+  return use_narrow(s) && (mean + FU_ROWS - 1) / FU_ROWS * s.N < 128 ? FU_ROWS_FEW : FU_ROWS;
+}
+
 // Few rows per bucket on average: a decoding batch.  Measured up-projection, us, 256-row tiles against this: 7B-like
 // layer, 16 rows 70, 47; 32 rows 75, 66; 64 rows 76, 112; layers with no more than one workgroup per CU gain up
 // to 64 rows (d 2048, N 64: 40, 30; 128 rows: 40, 46).
@@ -836,7 +856,7 @@ static bool few_rows(const spt_shape_t& s) {
 static size_t carve_schedule(const spt_shape_t& s, char* p, size_t o0, Schedule& sc, bool weight_grads = false) {
   const size_t P = (size_t)s.T * s.k;
   size_t o = o0;
-  sc.kd_cap = max_row_tiles(s, FU_ROWS);  // the narrow- and wide-block kernels both walk 256-row tiles
+  sc.kd_cap = max_row_tiles(s, kd_rows(s));
   sc.border = reinterpret_cast<int32_t*>(p + o);      o += align256((size_t)s.N * 4);
   sc.kd_count = reinterpret_cast<int32_t*>(p + o);    o += align256(8 * 4);
   sc.kd_list = p + o;                                 o += align256((size_t)8 * sc.kd_cap * sizeof(KdTile));
@@ -933,7 +953,7 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
   const ScatterPlan sp = sc.rstart ? plan_scatter(s) : ScatterPlan{};
   PlanArgs a = {};
   a.offsets = offsets; a.perm = perm;
-  a.N = s.N; a.QT = FU_ROWS; a.cap = sc.kd_cap; a.P = P; a.k = s.k;
+  a.N = s.N; a.QT = kd_rows(s); a.cap = sc.kd_cap; a.P = P; a.k = s.k;
   a.border = sc.border; a.kd_count = sc.kd_count; a.kd_list = static_cast<KdTile*>(sc.kd_list);
   a.zero_row = reinterpret_cast<uint32_t*>(sc.zero_row);
   a.tok = sc.tok;
@@ -974,19 +994,20 @@ static hipError_t run_combine(const spt_shape_t& s, const uint16_t* part, const 
   return hipSuccess;
 }
 
-template <int MODE, int ACT, int KS>
+template <int MODE, int ACT, int KS, int WV>
 static hipError_t launch_up_t(const spt_shape_t& s, const uint16_t* Wa, const uint16_t* Act,
                               const int32_t* offsets, const Schedule& sc, uint16_t* Hsave, uint16_t* Hact,
                               uint16_t* dHpre, hipStream_t st, const uint16_t* Xe, const uint16_t* We) {
   static bool attr_set = false;
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_kernel<MODE, ACT, KS>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, FU_SMEM_BYTES);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_kernel<MODE, ACT, KS, WV>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, UpTile<KS, WV>::SMEM);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  const int wg_per_xcd = sc.kd_cap < 64 ? sc.kd_cap : 64;  // two workgroups per CU
-  ffn_up_kernel<MODE, ACT, KS><<<dim3(8 * wg_per_xcd), 256, FU_SMEM_BYTES, st>>>(
+  const int most = WV == 4 ? 64 : 96;     // two (three) workgroups per CU
+  const int wg_per_xcd = sc.kd_cap < most ? sc.kd_cap : most;
+  ffn_up_kernel<MODE, ACT, KS, WV><<<dim3(8 * wg_per_xcd), 64 * WV, UpTile<KS, WV>::SMEM, st>>>(
       Wa, Act, offsets, sc.kd_count, static_cast<const KdTile*>(sc.kd_list), sc.kd_cap, sc.tok, s.Bs, s.d,
       Hsave, Hact, dHpre, Xe, We);
   return hipGetLastError();
@@ -1011,7 +1032,9 @@ static hipError_t launch_up(const spt_shape_t& s, const uint16_t* Wa, const uint
                             const int32_t* offsets, const Schedule& sc, uint16_t* Hsave, uint16_t* Hact,
                             uint16_t* dHpre, hipStream_t st, const uint16_t* Xe = nullptr,
                             const uint16_t* We = nullptr) {
-#define SPT_UP(ACT, KS) return launch_up_t<MODE, ACT, KS>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We)
+#define SPT_UP(ACT, KS)                                                                                                \
+  return kd_rows(s) == FU_ROWS ? launch_up_t<MODE, ACT, KS, 4>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We) \
+                               : launch_up_t<MODE, ACT, KS, 2>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We)
 #define SPT_UP_KS(ACT)                    \
   switch (s.Bs / 16) {                    \
     case 2: SPT_UP(ACT, 2);               \
