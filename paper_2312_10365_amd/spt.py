@@ -105,13 +105,15 @@ def workspace_bytes(shape: SptShape, which: int) -> int:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle of torch.cuda.current_stream() without building a Stream object around it (0.3 against 2.6 us, five
+    # times in a step whose kernels take 50 us)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: Optional[torch.Tensor], dtype, numel: int, name: str):
     if t is None:
         return None
-    if not t.is_cuda or t.dtype != dtype or not t.is_contiguous() or t.numel() != numel:
+    if t.dtype is not dtype or t.numel() != numel or not t.is_contiguous() or not t.is_cuda:
         raise ValueError(f"{name}: need a contiguous cuda tensor of {dtype} with {numel} elements, "
                          f"got {t.dtype} {tuple(t.shape)} on {t.device}")
     return t.data_ptr()
