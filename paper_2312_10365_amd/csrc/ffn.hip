@@ -36,11 +36,13 @@ namespace spt {
 //                     token sits in k of the N buckets) and, level after level, the same few
 //                     weight blocks.  With fewer buckets the bucket-major tile sequence is
 //                     cut into 8 contiguous runs (weight reuse only).
+//                     Wide blocks have one list, bucket-major, and its length in kd_count[0]: there
+//                     the kernel itself cuts the (row tile, A-side tile) items into 8 equal slices.
 
 struct PlanArgs {
   const int32_t* offsets;
   const int32_t* perm;
-  int N, QT, cap, P, k;
+  int N, QT, cap, P, k, wide;
   int32_t *border, *kd_count;
   KdTile* kd_list;
   uint32_t* zero_row;
@@ -153,7 +155,12 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     for (int e = total_pieces + b; e < p.dw_cap; e += 1024) p.dw_pieces[e] = DwPiece{0, 0, -1, 0};
   }
 
-  if (N >= 16) {
+  if (p.wide) {
+    const int inc = inclusive_scan(ntq);
+    if (b < N)
+      for (int lvl = 0; lvl < ntq; ++lvl) p.kd_list[inc - ntq + lvl] = KdTile{b, off + lvl * p.QT};
+    if (b == N - 1) p.kd_count[0] = inc;
+  } else if (N >= 16) {
     // rank r goes to group r%16 (<8) or 15 - r%16: position pg = r/8 inside the group; the
     // member at position p of group g has rank 8p + (p even ? g : 7 - g); sizes fall with p.
     const int pg = rank >> 3;
@@ -953,6 +960,7 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
   const ScatterPlan sp = sc.rstart ? plan_scatter(s) : ScatterPlan{};
   PlanArgs a = {};
   a.offsets = offsets; a.perm = perm;
+  a.wide = !use_narrow(s);
   a.N = s.N; a.QT = kd_rows(s); a.cap = sc.kd_cap; a.P = P; a.k = s.k;
   a.border = sc.border; a.kd_count = sc.kd_count; a.kd_list = static_cast<KdTile*>(sc.kd_list);
   a.zero_row = reinterpret_cast<uint32_t*>(sc.zero_row);
@@ -1125,7 +1133,6 @@ static WideArgs wide_args(const spt_shape_t& s, const int32_t* offsets, const Sc
   a.offsets = offsets;
   a.kd_count = sc.kd_count;
   a.kd_list = sc.kd_list;
-  a.cap = sc.kd_cap;
   a.tok = sc.tok;
   a.border = sc.border;
   a.zero_row = sc.zero_row;

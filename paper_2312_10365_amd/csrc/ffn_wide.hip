@@ -31,11 +31,19 @@ namespace spt {
 
 constexpr int WD = 256;                      // tile edge, both sides
 constexpr int WK = 32;                       // K values per stage
-constexpr int W_REGION = WD * WK * 2;        // bytes of one operand in a stage (16 KiB)
-constexpr int W_STAGE = 2 * W_REGION;        // 32 KiB
-constexpr int W_STAGES = 5;
-constexpr int W_SMEM = W_STAGES * W_STAGE;   // 160 KiB, the whole LDS of a CU
 constexpr int W_RT = 4;                      // row tiles per scheduling group
+
+// A tile of MA x NB MFMA tiles per wavefront: 4 x 4 is the 256 x 256 one, 4 x 2 has half the B-side rows, 2 x 2 is
+// a quarter (both for what is left after the last full round of the CUs).  Fewer products per stage hide less of a
+// copy's latency, so the smaller ones keep more stages in flight, in rings of the same 160 KiB or less.
+template <int MA, int NB>
+struct WideTile {
+  static constexpr int A_EDGE = 64 * MA, B_EDGE = 64 * NB;
+  static constexpr int A_REGION = A_EDGE * WK * 2, B_REGION = B_EDGE * WK * 2;  // bytes of an operand in a stage
+  static constexpr int STAGE = A_REGION + B_REGION;                            // 32, 24, 16 KiB
+  static constexpr int STAGES = 160 * 1024 / STAGE;                            // 5, 6, 10
+};
+constexpr int W_SMEM = WideTile<4, 4>::STAGES * WideTile<4, 4>::STAGE;   // 160 KiB, the whole LDS of a CU
 
 enum { OP_UP = 0, OP_DH = 1, OP_PART = 2, OP_DW = 3 };
 
@@ -47,13 +55,18 @@ __device__ __forceinline__ float pin_vgpr(float x) {
   return x;
 }
 
-// One 256 x 256 output tile.  b: block; a0 / n0: first A-side / B-side index; [qb, qe): the K
+// One A_EDGE x B_EDGE output tile.  b: block; a0 / n0: first A-side / B-side index; [qb, qe): the K
 // range (OP_DW: the bucket's rows) -- for the other GEMMs qe bounds the B-side rows.
-template <int OP, int ACT>
+template <int OP, int ACT, int MA, int NB>
 __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b, int a0, int n0,
                                           int qb, int qe) {
   constexpr bool A_TR = (OP == OP_PART || OP == OP_DW);
   constexpr bool B_TR = (OP == OP_DW);
+  static_assert((MA == 4 && NB == 4) || OP != OP_DW, "the weight gradients have full tiles only");
+  using Tile = WideTile<MA, NB>;
+  constexpr int W_STAGE = Tile::STAGE, W_STAGES = Tile::STAGES;
+  constexpr int A_CH = 8 * MA, B_CH = 8 * NB;      // 16-byte chunks of a K-row of a K-major operand
+  constexpr int A_HALF = 32 * MA, B_HALF = 32 * NB;  // A-side / B-side indices of a wavefront
   const int Bs = p.Bs, d = p.d;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -70,20 +83,21 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   const int nkd = d / WK;
   const int nk = (OP == OP_DW) ? (qe - qb + WK - 1) / WK : ((OP == OP_PART) ? Bs / WK : nkd + (EXT ? 2 : 0));
 
-  // ---- DMA lane roles.  A wavefront issues 4 instructions per operand and stage; instruction
-  // (wave, j) fills 1 KiB: for a K-contiguous operand rows 16 (4 wave + j) + lane / 4, physical
-  // chunk lane % 4 (logical chunk = physical ^ swizzle(row)); for a K-major operand K-rows
-  // 2 (4 wave + j) + lane / 32, physical chunk lane % 32 (logical = physical ^ ((krow & 3) << 2)).
-  const uint16_t* a_ptr[4];
-  const uint16_t* b_ptr[4];
-  int a_coloff[4], b_coloff[4];
-  int a_unit[4], b_tok[4];  // K = d GEMMs: hidden unit / token id of this lane's row (for the extension)
+  // ---- DMA lane roles.  A wavefront issues MA (NB) instructions for the A (B) operand of a stage;
+  // instruction (wave, j) fills 1 KiB: for a K-contiguous operand rows 16 (MA wave + j) + lane / 4, physical
+  // chunk lane % 4 (logical chunk = physical ^ swizzle(row)); for a K-major operand (MA = 4) K-rows
+  // 2 (4 wave + j) + lane / 32, physical chunk lane % 32 (logical = physical ^ ((krow & 3) << 2)); MA = 2: K-rows
+  // 4 (2 wave + j) + lane / 16, chunk lane % 16.
+  const uint16_t* a_ptr[MA];
+  const uint16_t* b_ptr[NB];
+  int a_coloff[MA], b_coloff[NB];
+  int a_unit[MA], b_tok[NB];  // K = d GEMMs: hidden unit / token id of this lane's row (for the extension)
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = (wave * 4 + j) * 16 + (lane >> 2);
+  for (int j = 0; j < MA; ++j) {
+    const int row = (wave * MA + j) * 16 + (lane >> 2);
     const int ch = (lane & 3) ^ ((row >> 2) & 3);
-    const int krow = 2 * (wave * 4 + j) + (lane >> 5);
-    const int kcol = ((lane & 31) ^ ((krow & 3) << 2)) << 3;
+    const int krow = (64 / A_CH) * (wave * MA + j) + lane / A_CH;
+    const int kcol = ((lane & (A_CH - 1)) ^ ((krow & 3) << 2)) << 3;
     if (!A_TR) {
       const int u = (a0 + row < Bs) ? a0 + row : a0;
       a_ptr[j] = Aop + ((size_t)b * Bs + u) * d + ch * 8;
@@ -95,6 +109,13 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
       a_ptr[j] = (OP == OP_PART) ? Aop + ((size_t)b * Bs + krow) * d + col : Aop;
       a_unit[j] = 0;
     }
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int row = (wave * NB + j) * 16 + (lane >> 2);
+    const int ch = (lane & 3) ^ ((row >> 2) & 3);
+    const int krow = (64 / B_CH) * (wave * NB + j) + lane / B_CH;
+    const int kcol = ((lane & (B_CH - 1)) ^ ((krow & 3) << 2)) << 3;
     if (!B_TR) {
       const int q = (n0 + row < qe) ? n0 + row : n0;
       b_tok[j] = (OP == OP_PART) ? 0 : p.tok[q];
@@ -125,7 +146,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   // K-stage kt into ring slot `stage`.
   auto issue_one = [&](int which, int j, int stage, int kt, const int (&ids)[8]) {
     const uint32_t dst = __builtin_amdgcn_readfirstlane(
-        lds0 + (uint32_t)(stage * W_STAGE + which * W_REGION + (wave * 4 + j) * 1024));
+        lds0 + (uint32_t)(stage * W_STAGE + (which ? Tile::A_REGION : 0) + (wave * (which ? NB : MA) + j) * 1024));
     if (which == 0) {
       if (!A_TR) {
         // (selects, not a branch: the loop body stays one basic block)
@@ -162,29 +183,29 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   const int ag = sl & 3;
   const int acol = 4 * (4 * (ag & 1) + 2 * (g & 1) + (ag >> 1));
   const int bcol = 16 * (g & 1) + 4 * (sl & 3);
-  const uint32_t tr_row0 = (uint32_t)((8 * (g >> 1) + (sl >> 2)) * 512);
+  const uint32_t tr_row0 = (uint32_t)((8 * (g >> 1) + (sl >> 2)) * 16);   // (times the chunks of a K-row)
   const int arow = rho32(i);
 
-  // Fragment f of K-step s of the stage at st: f < 4 is A-side tile f, else B-side tile f - 4.
+  // Fragment f of K-step s of the stage at st: f < MA is A-side tile f, else B-side tile f - MA.
   auto load_frag = [&](const char* st, int s, int f) -> bf16x8 {
-    if (f < 4) {
-      if (!A_TR) return as_bf16x8(reinterpret_cast<const uint4*>(st)[kd_slot(wm * 128 + f * 32 + arow, 2 * s + h)]);
-      const uint32_t ch = (uint32_t)((((wm * 4 + f) * 4 + (acol >> 3)) ^ sw) * 16 + (acol & 4) * 2);
-      const char* base = st + s * 16 * 512 + tr_row0 + ch;
-      return tr_read_frag(base, base + 4 * 512);
+    if (f < MA) {
+      if (!A_TR) return as_bf16x8(reinterpret_cast<const uint4*>(st)[kd_slot(wm * A_HALF + f * 32 + arow, 2 * s + h)]);
+      const uint32_t ch = (uint32_t)((((wm * MA + f) * 4 + (acol >> 3)) ^ sw) * 16 + (acol & 4) * 2);
+      const char* base = st + s * 16 * A_CH * 16 + tr_row0 * A_CH + ch;
+      return tr_read_frag(base, base + 4 * A_CH * 16);
     }
-    const char* stB = st + W_REGION;
-    if (!B_TR) return as_bf16x8(reinterpret_cast<const uint4*>(stB)[kd_slot(wn * 128 + (f - 4) * 32 + i, 2 * s + h)]);
-    const uint32_t ch = (uint32_t)((((wn * 4 + (f - 4)) * 4 + (bcol >> 3)) ^ sw) * 16 + (bcol & 4) * 2);
-    const char* base = stB + s * 16 * 512 + tr_row0 + ch;
-    return tr_read_frag(base, base + 4 * 512);
+    const char* stB = st + Tile::A_REGION;
+    if (!B_TR) return as_bf16x8(reinterpret_cast<const uint4*>(stB)[kd_slot(wn * B_HALF + (f - MA) * 32 + i, 2 * s + h)]);
+    const uint32_t ch = (uint32_t)((((wn * NB + (f - MA)) * 4 + (bcol >> 3)) ^ sw) * 16 + (bcol & 4) * 2);
+    const char* base = stB + s * 16 * B_CH * 16 + tr_row0 * B_CH + ch;
+    return tr_read_frag(base, base + 4 * B_CH * 16);
   };
 
-  f32x16 acc[4][4];
+  f32x16 acc[MA][NB];
 #pragma unroll
-  for (int mi = 0; mi < 4; ++mi)
+  for (int mi = 0; mi < MA; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni)
+    for (int ni = 0; ni < NB; ++ni)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
 
@@ -192,11 +213,11 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   // before the ring is refilled.
   wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
-  // Ring schedule (5 slots).  "Issue j" copies K-stage min(j, nk-1) into slot j % 5: past the
+  // Ring schedule (W_STAGES = S slots).  "Issue j" copies K-stage min(j, nk-1) into slot j % S: past the
   // last stage it copies the last one again into a slot nobody reads, which keeps the number of
   // copies per iteration -- and with it every vmcnt wait -- the same from the first to the last
-  // iteration, and the loop body free of branches.  Issues 0..3 go out up front; iteration kt
-  // sends issue kt+4 (into the slot stage kt-1 left).  At the top of iteration kt the stages kt
+  // iteration, and the loop body free of branches.  Issues 0..S-2 go out up front; iteration kt
+  // sends issue kt+S-1 (into the slot stage kt-1 left).  At the top of iteration kt the stages kt
   // and kt+1 have landed and are visible to every wavefront, and the fragments of (stage kt,
   // K-step 0) are in registers.
   //
@@ -205,68 +226,71 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   // matrix pipe busy for 32 cycles): after MFMA 0..7 of a K-step one fragment read for the next
   // K-step (issued half an iteration before its data are used), after MFMA 8..11 one DMA
   // instruction, after MFMA 12 the scalar loads of the token ids for the next iteration's DMA.
+  // (The smaller tiles: a fragment read behind each of the first MFMAs, the copies behind the last ones.)
   const int klast = nk - 1;
   auto kclamp = [&](int j) { return j < klast ? j : klast; };
   int ids[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ids_next[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  bf16x8 fa[2][4], fb[2][4];
+  bf16x8 fa[2][MA], fb[2][NB];
   const char* ring = reinterpret_cast<const char*>(smem);
   if (nk > 0) {
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
+    for (int st = 0; st < W_STAGES - 1; ++st) {
       if (OP == OP_DW) load_ids(kclamp(st), ids);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) issue_one(0, j, st, kclamp(st), ids);
+      for (int j = 0; j < MA; ++j) issue_one(0, j, st, kclamp(st), ids);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) issue_one(1, j, st, kclamp(st), ids);
+      for (int j = 0; j < NB; ++j) issue_one(1, j, st, kclamp(st), ids);
     }
-    if (OP == OP_DW) load_ids(kclamp(4), ids);
-    wait_vmcnt<16>();  // issues 0 and 1 have landed (2 and 3 may be out)
+    if (OP == OP_DW) load_ids(kclamp(W_STAGES - 1), ids);
+    wait_vmcnt<(W_STAGES - 3) * (MA + NB)>();  // issues 0 and 1 have landed (2 .. S-2 may be out)
     __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-      fa[0][f] = load_frag(ring, 0, f);
-      fb[0][f] = load_frag(ring, 0, f + 4);
-    }
+    for (int f = 0; f < MA; ++f) fa[0][f] = load_frag(ring, 0, f);
+#pragma unroll
+    for (int f = 0; f < NB; ++f) fb[0][f] = load_frag(ring, 0, f + MA);
   }
   int stage = 0;
   for (int kt = 0; kt < nk; ++kt) {
     const int next = (stage + 1 == W_STAGES) ? 0 : stage + 1;
-    const int fill = (stage == 0) ? W_STAGES - 1 : stage - 1;  // slot of stage kt-1 = (kt+4) % 5
+    const int fill = (stage == 0) ? W_STAGES - 1 : stage - 1;  // slot of stage kt-1 = (kt+S-1) % S
     const char* st0 = ring + stage * W_STAGE;
     // after the last stage the look-ahead reads the current one again: harmless
     const char* st1 = ring + ((kt + 1 < nk) ? next : stage) * W_STAGE;
-    const int kfill = kclamp(kt + 4);
+    const int kfill = kclamp(kt + W_STAGES - 1);
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
-      // half 0: multiply K-step 0, read (stage kt, K-step 1), copy the A part of issue kt+4;
+      // half 0: multiply K-step 0, read (stage kt, K-step 1), copy the A part of issue kt+S-1;
       // half 1: multiply K-step 1, read (stage kt+1, K-step 0), copy the B part.
+      constexpr int M = MA * NB;
+      const int copies = half ? NB : MA, c0 = M == 16 ? 8 : M - copies;   // c0: first MFMA with a copy behind it
 #pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        const int mi = m >> 2, ni = m & 3;
+      for (int m = 0; m < M; ++m) {
+        const int mi = m / NB, ni = m % NB;
         acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[half][mi], fb[half][ni], acc[mi][ni], 0, 0, 0);
-        if (m < 8) {
+        if (m < MA + NB) {
           const bf16x8 fr = load_frag(half ? st1 : st0, half ? 0 : 1, m);
-          if (m < 4) fa[half ^ 1][m] = fr; else fb[half ^ 1][m - 4] = fr;
-        } else if (m < 12) {
-          issue_one(half, m - 8, fill, kfill, ids);
+          if (m < MA) fa[half ^ 1][m] = fr; else fb[half ^ 1][m - MA] = fr;
+        }
+        if (m >= c0 && m < c0 + copies) {
+          issue_one(half, m - c0, fill, kfill, ids);
         } else if (m == 12 && half == 1 && OP == OP_DW) {
-          load_ids(kclamp(kt + 5), ids_next);
+          load_ids(kclamp(kt + W_STAGES), ids_next);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) ids[e] = ids_next[e];
-    // own copies of stage kt+2 have landed: only issues kt+3 and kt+4 (8 instructions each) may
+    // own copies of stage kt+2 have landed: only issues kt+3 .. kt+S-1 (MA + NB instructions each) may
     // be outstanding; the barrier makes everyone's visible and ends all reads of stage kt
-    wait_vmcnt<16>();
+    wait_vmcnt<(W_STAGES - 3) * (MA + NB)>();
     __builtin_amdgcn_s_barrier();
     stage = next;
   }
   wait_vmcnt<0>();  // the trailing copies (repeats of the last stage) are done too
 
-  // ---- epilogue: lane (i, h) holds, for B-side index n0 + 128 wn + 32 ni + i, the A-side
-  // indices a0 + 128 wm + 32 mi + 16 h + (0..15).
+  // ---- epilogue: lane (i, h) holds, for B-side index n0 + B_HALF wn + 32 ni + i, the A-side
+  // indices a0 + A_HALF wm + 32 mi + 16 h + (0..15).
   // dH reads the saved pre-activations of its whole tile first (32 loads of 16 bytes per lane, all
   // in flight together; the fragment registers of the main loop are free by now), so the epilogue
   // waits for memory once instead of once per fragment.
@@ -280,35 +304,35 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
     float* tbuf = reinterpret_cast<float*>(smem) + wave * (32 * 36);
     const int cc = lane & 7, r0 = lane >> 3;
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni)
+    for (int ni = 0; ni < NB; ++ni)
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi) {
+      for (int mi = 0; mi < MA; ++mi) {
         const f32x16& c = acc[mi][ni];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           *reinterpret_cast<f32x4*>(tbuf + i * 36 + 16 * h + 4 * e) = f32x4{c[4 * e], c[4 * e + 1], c[4 * e + 2], c[4 * e + 3]};
         wave_lds_fence();
-        const int aidx = a0 + wm * 128 + mi * 32 + 4 * cc;
+        const int aidx = a0 + wm * A_HALF + mi * 32 + 4 * cc;
         f32x4 o[4];  // (all four reads go out before the first store waits for its data)
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = *reinterpret_cast<const f32x4*>(tbuf + (r0 + 8 * e) * 36 + 4 * cc);
         wave_lds_fence();
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int nidx = n0 + wn * 128 + ni * 32 + r0 + 8 * e;
+          const int nidx = n0 + wn * B_HALF + ni * 32 + r0 + 8 * e;
           if (nidx < Bs && aidx < a_lim) *reinterpret_cast<f32x4*>(p.dW + ((size_t)b * Bs + nidx) * d + aidx) = o[e];
         }
       }
     return;
   }
-  uint4 zsave[(OP == OP_DH) ? 4 : 1][(OP == OP_DH) ? 4 : 1][2];
+  uint4 zsave[(OP == OP_DH) ? NB : 1][(OP == OP_DH) ? MA : 1][2];
   if (OP == OP_DH) {
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) {
-      const int nidx = n0 + wn * 128 + ni * 32 + i;
+    for (int ni = 0; ni < NB; ++ni) {
+      const int nidx = n0 + wn * B_HALF + ni * 32 + i;
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi) {
-        const int aidx = a0 + wm * 128 + mi * 32 + 16 * h;
+      for (int mi = 0; mi < MA; ++mi) {
+        const int aidx = a0 + wm * A_HALF + mi * 32 + 16 * h;
         if (nidx < qe && aidx < a_lim) {
           const uint4* src = reinterpret_cast<const uint4*>(p.Hsave + (size_t)nidx * Bs + aidx);
           zsave[ni][mi][0] = src[0];
@@ -318,12 +342,12 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
     }
   }
 #pragma unroll
-  for (int ni = 0; ni < 4; ++ni) {
-    const int nidx = n0 + wn * 128 + ni * 32 + i;
+  for (int ni = 0; ni < NB; ++ni) {
+    const int nidx = n0 + wn * B_HALF + ni * 32 + i;
     const bool n_ok = (OP == OP_DW) ? nidx < Bs : nidx < qe;
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi) {
-      const int aidx = a0 + wm * 128 + mi * 32 + 16 * h;
+    for (int mi = 0; mi < MA; ++mi) {
+      const int aidx = a0 + wm * A_HALF + mi * 32 + 16 * h;
       const f32x16& c = acc[mi][ni];
       if (n_ok && aidx < a_lim) {
         if (OP == OP_UP) {
@@ -376,26 +400,48 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   }
 }
 
-// Up / dH / partial-row GEMMs: persistent workgroups, one per CU.  Workgroup id modulo 8 is
-// the XCD it runs on; it walks that XCD's work items -- (row tile of the XCD's list, A-side
-// tile), in groups of W_RT row tiles x all A-side tiles, A-side tile major -- with a stride of
-// the workgroups per XCD.  The 32 workgroups of an XCD are then on about 4 row tiles x 8
-// A-side tiles at a time, in step, so each operand slice pulled into that XCD's L2 serves
-// several of them.
+// Up / dH / partial-row GEMMs: persistent workgroups, one per CU.  The work items -- (row tile of the
+// bucket-major list, A-side tile), in groups of W_RT row tiles x all A-side tiles, A-side tile major --
+// are cut into 8 equal slices, one per XCD (workgroup id modulo 8), and an XCD's 32 workgroups walk its
+// slice in step.  They are then on about 4 row tiles x 8 A-side tiles at a time, so each operand slice
+// pulled into that XCD's L2 serves several of them.
+// What is left of a slice after its full rounds of 32 would cost another round whatever its size.  So up to
+// 8 items are worked off as quarters, at 0.35 of a round, up to 16 as halves, at 0.6 (smaller pieces read more
+// operand bytes per product; a second and third round of quarters gains nothing over a full one).
+// Whole row tiles dealt to the XCDs before: 9 of 66 to some, 4 rounds of 11 A-side tiles each, where 2.84
+// rounds' worth of items is there.  us, before and now: T 8192, d 4096, 4 blocks of 2752, k 2: up-projection 450,
+// 373, its backward 499, 403, partial rows 376, 345; 3001 tokens of that 215, 168; 24 tokens 85, 46.
 template <int OP, int ACT>
 __global__ __launch_bounds__(256, 1) void wide_rows_kernel(WideArgs p) {
   extern __shared__ uint4 w_smem[];
-  const int xcd = blockIdx.x & 7, wg_per_xcd = gridDim.x >> 3;
-  const int count = p.kd_count[xcd];
+  const int xcd = blockIdx.x & 7, wg = blockIdx.x >> 3, wgs = gridDim.x >> 3;
+  const int count = p.kd_count[0];
   const int a_lim = (OP == OP_PART) ? p.d : p.Bs;
   const int n_at = (a_lim + WD - 1) / WD;
-  const KdTile* list = static_cast<const KdTile*>(p.kd_list) + (size_t)xcd * p.cap;
-  for (int item = blockIdx.x >> 3; item < count * n_at; item += wg_per_xcd) {
+  const KdTile* list = static_cast<const KdTile*>(p.kd_list);
+  const int64_t items = (int64_t)count * n_at;
+  const int lo = (int)(items * xcd / 8), n = (int)(items * (xcd + 1) / 8) - lo;
+  const int left = n % wgs, split = left > wgs / 2 ? 1 : (left > wgs / 4 ? 2 : 4), full = split > 1 ? n - left : n;
+  auto locate = [&](int item, KdTile& t, int& a0) {
     const int grp = item / (W_RT * n_at), rem = item - grp * W_RT * n_at;
     const int rtg = (count - grp * W_RT < W_RT) ? count - grp * W_RT : W_RT;
-    const KdTile t = list[grp * W_RT + rem % rtg];
-    wide_tile<OP, ACT>(p, w_smem, t.bucket, (rem / rtg) * WD, t.q0, 0, p.offsets[t.bucket + 1]);
+    t = list[grp * W_RT + rem % rtg];
+    a0 = (rem / rtg) * WD;
+  };
+  KdTile t;
+  int a0;
+  for (int e = wg; e < full; e += wgs) {
+    locate(lo + e, t, a0);
+    wide_tile<OP, ACT, 4, 4>(p, w_smem, t.bucket, a0, t.q0, 0, p.offsets[t.bucket + 1]);
   }
+  // (at most one piece per workgroup)
+  if (wg >= split * (n - full)) return;
+  locate(lo + full + wg / split, t, a0);
+  const int part = wg % split, n0 = t.q0 + (part & 1) * (WD / 2), qe = p.offsets[t.bucket + 1];
+  a0 += (part >> 1) * (WD / 2);
+  if (n0 >= qe || a0 >= a_lim) return;
+  if (split == 2) wide_tile<OP, ACT, 4, 2>(p, w_smem, t.bucket, a0, n0, 0, qe);
+  else            wide_tile<OP, ACT, 2, 2>(p, w_smem, t.bucket, a0, n0, 0, qe);
 }
 
 // dW GEMMs: one work item (column tile, unit tile, bucket) per workgroup.  With a multiple of
@@ -420,13 +466,14 @@ __global__ __launch_bounds__(256, 1) void wide_dw_kernel(WideArgs p) {
   }
   if (br >= p.N) return;
   const int b = p.border[br];
-  wide_tile<OP_DW, 0>(p, w_smem, b, ct * WD, ut * WD, p.offsets[b], p.offsets[b + 1]);
+  wide_tile<OP_DW, 0, 4, 4>(p, w_smem, b, ct * WD, ut * WD, p.offsets[b], p.offsets[b + 1]);
 }
 
 template <int OP, int ACT>
 static void launch_rows(const WideArgs& a, hipStream_t st) {
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(wide_rows_kernel<OP, ACT>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, W_SMEM);
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wide_rows_kernel<OP, ACT>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, W_SMEM);
+  (void)attr;
   wide_rows_kernel<OP, ACT><<<8 * 32, 256, W_SMEM, st>>>(a);
 }
 
@@ -448,8 +495,9 @@ hipError_t launch_wide(int op, const spt_shape_t& s, const WideArgs& a, hipStrea
       break;
     default: {
       const int n_ct = (s.d + WD - 1) / WD, n_ut = (s.Bs + WD - 1) / WD;
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(wide_dw_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, W_SMEM);
+      static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wide_dw_kernel),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, W_SMEM);
+      (void)attr;
       wide_dw_kernel<<<n_ct * n_ut * s.N, 256, W_SMEM, st>>>(a);
     }
   }

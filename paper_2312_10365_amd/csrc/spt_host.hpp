@@ -92,9 +92,8 @@ struct WideArgs {
   const void* A;             // A-side operand (MFMA rows): W block, or the gathered activations
   const void* B;             // B-side operand: gathered activation rows, or H / dHpre
   const int32_t* offsets;
-  const int32_t* kd_count;   // row tiles per XCD
-  const void* kd_list;       // [8][cap] row tiles in per-XCD run order
-  int cap;
+  const int32_t* kd_count;   // number of row tiles
+  const void* kd_list;       // row tiles, bucket-major
   const int32_t* tok;
   const int32_t* border;
   const uint16_t* zero_row;
