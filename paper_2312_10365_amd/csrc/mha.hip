@@ -1169,15 +1169,12 @@ MhaWorkspace plan_mha(const spt_mha_shape_t& s, void* ws) {
   size_t off = 0;
   const size_t rows = (size_t)s.S * s.n;
   w.dS = reinterpret_cast<float*>(p + off);        off += align256(rows * s.L * sizeof(float));
-  w.maxes = nullptr; w.toff = nullptr; w.tlist = nullptr; w.gbits = nullptr;
-  if (use_dense(s)) {
-    w.maxes = reinterpret_cast<float2*>(p + off);  off += align256((size_t)s.S * ((s.n + 3) / 4) * sizeof(float2));
-    w.bytes = off;
-    return w;
-  }
+  w.gbits = nullptr;
   w.toff = reinterpret_cast<int32_t*>(p + off);    off += align256((size_t)s.S * (s.n + 1) * sizeof(int32_t));
   w.tlist = reinterpret_cast<uint32_t*>(p + off);  off += align256(rows * s.L * sizeof(uint32_t));
-  if (!transpose_fits_lds(s.n, s.L)) {
+  // (the dense tiles need no transposition; their maxima take its place)
+  w.maxes = use_dense(s) ? reinterpret_cast<float2*>(w.tlist) : nullptr;
+  if (!w.maxes && !transpose_fits_lds(s.n, s.L)) {
     w.gbits = reinterpret_cast<uint32_t*>(p + off);
     off += align256(rows * ((s.n + 31) / 32) * sizeof(uint32_t));
   }
