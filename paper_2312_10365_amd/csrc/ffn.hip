@@ -529,11 +529,10 @@ struct DwOperands {
   float *dW, *stage;
 };
 
-template <bool FRAG, int UT, int CT>  // FRAG: Hin in fragment order (hfrag_off) instead of row-major [rows, Bs]
+template <int UT, int CT>
 __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
     DwOperands ops0, DwOperands ops1,
-    const int32_t* __restrict__ offsets, const int32_t* __restrict__ tok,
-    const int32_t* __restrict__ border, const uint16_t* __restrict__ zero_row, int N, int Bs,
+    const int32_t* __restrict__ tok, const uint16_t* __restrict__ zero_row, int npieces, int Bs,
     int d, const DwPiece* __restrict__ pieces, int nblocks) {
   // (blockIdx.z picks the product: both weight gradients of a step can go out in one launch)
   const DwOperands ops = blockIdx.z ? ops1 : ops0;
@@ -568,19 +567,11 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
     ct = blockIdx.x % nct;
     br = blockIdx.x / nct;
   }
-  if (br >= N) return;   // N: work items (buckets, or entries of the piece table)
-  int qb, qe;
-  float* dst;
-  if (pieces) {
-    const DwPiece pc = pieces[br];
-    if (pc.dst < 0) return;
-    qb = pc.lo; qe = pc.hi;
-    dst = pc.dst < nblocks ? dW + (size_t)pc.dst * Bs * d : stage + (size_t)(pc.dst - nblocks) * Bs * d;
-  } else {
-    const int b = border[br];
-    qb = offsets[b]; qe = offsets[b + 1];
-    dst = dW + (size_t)b * Bs * d;
-  }
+  if (br >= npieces) return;
+  const DwPiece pc = pieces[br];
+  if (pc.dst < 0) return;
+  const int qb = pc.lo, qe = pc.hi;
+  float* const dst = pc.dst < nblocks ? dW + (size_t)pc.dst * Bs * d : stage + (size_t)(pc.dst - nblocks) * Bs * d;
   const int c0 = ct * DW_CT, u0 = blockIdx.y * UT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -630,7 +621,7 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
   auto issue_b = [&](int slot, int kt) {
     if (CT == 512 && !copies_b) return;  // (wave-uniform)
     const int q = qb + kt * DW_KT + b_row;
-    const uint16_t* src = (q < qe) ? Hin + hval_off<FRAG>(q, b_coloff, Bs) : zero_row + ((lane & 15) << 3);
+    const uint16_t* src = (q < qe) ? Hin + hfrag_off(q, b_coloff, Bs) : zero_row + ((lane & 15) << 3);
     dma16(src, __builtin_amdgcn_readfirstlane(
                    lds0 + (uint32_t)(slot * DW_STAGE_BYTES + DW_A_BYTES + (UT == 128 ? wq : wave & 1) * 1024)));
   };
@@ -783,17 +774,10 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(DwOperands ops0, DwOpera
 // ------------------------------------------------------------------------------------------
 // Combine: out[t][:] = sum_{j<k} part[inv[t*k+j]][:], j ascending, fp32, one rounding to bf16.
 // This is Alg. 4's write-back with block outputs added (k > 1 blocks per token).
-// `part` holds dc columns per row: column c of row r sits at r*row_stride + (c/128)*chunk_stride
-// + c%128 (row-major: row_stride = dc, chunk_stride = 128; chunk-major, the layout the
-// row-walking GEMM writes as whole contiguous 32 KiB blocks: row_stride = 128, chunk_stride =
-// P*128).  `out` points at the first of those columns inside the [T, out_ld] result.
 __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict__ part,
-                                                      const int32_t* __restrict__ inv, int T, int dc,
-                                                      size_t row_stride, size_t chunk_stride,
-                                                      int out_ld, int k,
-                                                      uint16_t* __restrict__ out,
-                                                      const uint16_t* __restrict__ Z) {
-  const int cpr = dc >> 3;  // 16-byte groups per row
+                                                      const int32_t* __restrict__ inv, int T, int d, int k,
+                                                      uint16_t* __restrict__ out) {
+  const int cpr = d >> 3;  // 16-byte groups per row
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= (int64_t)T * cpr) return;
   const int t = (int)(gid / cpr), cg = (int)(gid % cpr);
@@ -801,13 +785,13 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
 #pragma unroll
   for (int e = 0; e < 8; ++e) a[e] = 0.f;
   const int32_t* iv = inv + (size_t)t * k;
-  part += (size_t)(cg >> 4) * chunk_stride + (cg & 15) * 8;
+  part += cg * 8;
   int j = 0;
   for (; j + 8 <= k; j += 8) {
     u32x4 v[8];
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj)
-      v[jj] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(part + (size_t)iv[j + jj] * row_stride));
+      v[jj] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(part + (size_t)iv[j + jj] * d));
 #pragma unroll
     for (int jj = 0; jj < 8; ++jj) {
       a[0] += lo_bf16(v[jj].x); a[1] += hi_bf16(v[jj].x);
@@ -817,20 +801,13 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint16_t* __restrict
     }
   }
   for (; j < k; ++j) {
-    const uint4 v = *reinterpret_cast<const uint4*>(part + (size_t)iv[j] * row_stride);
+    const uint4 v = *reinterpret_cast<const uint4*>(part + (size_t)iv[j] * d);
     a[0] += lo_bf16(v.x); a[1] += hi_bf16(v.x);
     a[2] += lo_bf16(v.y); a[3] += hi_bf16(v.y);
     a[4] += lo_bf16(v.z); a[5] += hi_bf16(v.z);
     a[6] += lo_bf16(v.w); a[7] += hi_bf16(v.w);
   }
-  if (Z) {  // one more row per token: the low-rank term of the outer projection (section 2.2)
-    const uint4 v = *reinterpret_cast<const uint4*>(Z + (size_t)t * out_ld + cg * 8);
-    a[0] += lo_bf16(v.x); a[1] += hi_bf16(v.x);
-    a[2] += lo_bf16(v.y); a[3] += hi_bf16(v.y);
-    a[4] += lo_bf16(v.z); a[5] += hi_bf16(v.z);
-    a[6] += lo_bf16(v.w); a[7] += hi_bf16(v.w);
-  }
-  *reinterpret_cast<uint4*>(out + (size_t)t * out_ld + cg * 8) =
+  *reinterpret_cast<uint4*>(out + (size_t)t * d + cg * 8) =
       make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]),
                  pack_bf16x2(a[6], a[7]));
 }
@@ -989,15 +966,11 @@ hipError_t run_schedule(const spt_shape_t& s, const int32_t* offsets, const int3
   return run_plan(s, offsets, perm, sc, st);
 }
 
-static hipError_t run_combine(const spt_shape_t& s, const uint16_t* part, const int32_t* inv,
-                              void* out, int c_begin, int dc, size_t row_stride,
-                              size_t chunk_stride, int slot, hipStream_t st,
-                              const uint16_t* Z = nullptr) {
-  const int64_t items = (int64_t)s.T * (dc / 8);
+static hipError_t run_combine(const spt_shape_t& s, const uint16_t* part, const int32_t* inv, void* out, int slot,
+                              hipStream_t st) {
+  const int64_t items = (int64_t)s.T * (s.d / 8);
   ScopedKernelTimer tm(slot, st);
-  combine_kernel<<<(unsigned)((items + 255) / 256), 256, 0, st>>>(
-      part, inv, s.T, dc, row_stride, chunk_stride, s.d, s.k, static_cast<uint16_t*>(out) + c_begin,
-      Z ? Z + c_begin : nullptr);
+  combine_kernel<<<(unsigned)((items + 255) / 256), 256, 0, st>>>(part, inv, s.T, s.d, s.k, static_cast<uint16_t*>(out));
   SPT_LAUNCH_CHECK();
   return hipSuccess;
 }
@@ -1056,71 +1029,39 @@ static hipError_t launch_up(const spt_shape_t& s, const uint16_t* Wa, const uint
 }
 
 // One instantiation of the weight-gradient GEMM (UT = hidden units per workgroup tile).
-template <bool FRAG, int UT, int CT>
-static hipError_t launch_dw_ttt(const DwOperands* ops, int nops, const int32_t* offsets, const int32_t* tok,
-                                const int32_t* border, const uint16_t* zero_row, int N, int Bs, int d, int slot,
-                                hipStream_t st, const DwPiece* pieces, int nblocks) {
-  const int nct = (d + CT - 1) / CT;
-  int gx;
-  if (nct % 8 == 0) gx = nct * N;
-  else if (8 % nct == 0) gx = 8 * ((N + 8 / nct - 1) / (8 / nct));
-  else gx = nct * N;
-  const dim3 grid(gx, (Bs + UT - 1) / UT, nops);
+template <int UT, int CT>
+static hipError_t launch_dw_ct(const DwOperands* ops, int nops, const Schedule& sc, int N, int Bs, int d, hipStream_t st) {
+  const int nct = (d + CT - 1) / CT, np = sc.dw_cap;
+  const int gx = nct % 8 != 0 && 8 % nct == 0 ? 8 * ((np + 8 / nct - 1) / (8 / nct)) : nct * np;
   const int dw_smem = DW_SLOTS * ((CT / 256) * DW_HALF_BYTES + DW_KT * UT * 2);
   static bool attr_set = false;
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kq_gemm_kernel<FRAG, UT, CT>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kq_gemm_kernel<UT, CT>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, dw_smem);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  {
-    ScopedKernelTimer tm(slot, st);
-    kq_gemm_kernel<FRAG, UT, CT><<<grid, CT, dw_smem, st>>>(ops[0], ops[nops - 1], offsets, tok, border, zero_row, N, Bs,
-                                                         d, pieces, nblocks);
-  }
+  kq_gemm_kernel<UT, CT><<<dim3(gx, (Bs + UT - 1) / UT, nops), CT, dw_smem, st>>>(
+      ops[0], ops[nops - 1], sc.tok, sc.zero_row, np, Bs, d, sc.dw_pieces, N);
   return hipGetLastError();
 }
 
 // 512-column workgroups where each CU still gets at least four of them one after the other (with
 // fewer, the uneven last round costs more than the shared hidden-unit copies save: measured on the
 // skewed OPT-1.3B-like shape), 256-column ones otherwise.
-template <bool FRAG, int UT>
-static hipError_t launch_dw_tt(const DwOperands* ops, int nops, const int32_t* offsets, const int32_t* tok,
-                               const int32_t* border, const uint16_t* zero_row, int N, int Bs, int d, int slot,
-                               hipStream_t st, const DwPiece* pieces, int nblocks) {
-  if (d % 512 == 0 && (int64_t)(d / 512) * N >= 1024)
-    return launch_dw_ttt<FRAG, UT, 512>(ops, nops, offsets, tok, border, zero_row, N, Bs, d, slot, st, pieces, nblocks);
-  return launch_dw_ttt<FRAG, UT, 256>(ops, nops, offsets, tok, border, zero_row, N, Bs, d, slot, st, pieces, nblocks);
+template <int UT>
+static hipError_t launch_dw_ut(const DwOperands* ops, int nops, const Schedule& sc, int N, int Bs, int d, hipStream_t st) {
+  if (d % 512 == 0 && (int64_t)(d / 512) * sc.dw_cap >= 1024) return launch_dw_ct<UT, 512>(ops, nops, sc, N, Bs, d, st);
+  return launch_dw_ct<UT, 256>(ops, nops, sc, N, Bs, d, st);
 }
 
-// dW[b][u][c] = sum_{q in bucket b} Hin[q][u] * Act[tok[q]][c] for N buckets of Bs units and d
-// columns (the narrow-block weight-gradient GEMM; also run with a 32-wide side for the adapter
-// gradients of the low-rank variant).
-template <bool FRAG>
-static hipError_t launch_dw_t(const DwOperands* ops, int nops, const int32_t* offsets, const int32_t* tok,
-                              const int32_t* border, const uint16_t* zero_row, int N, int Bs, int d, int slot,
-                              hipStream_t st, const DwPiece* pieces = nullptr, int nblocks = 0) {
-  return Bs <= 64 ? launch_dw_tt<FRAG, 64>(ops, nops, offsets, tok, border, zero_row, N, Bs, d, slot, st, pieces, nblocks)
-                  : launch_dw_tt<FRAG, 128>(ops, nops, offsets, tok, border, zero_row, N, Bs, d, slot, st, pieces, nblocks);
-}
-
-hipError_t launch_dw(const uint16_t* Act, const uint16_t* Hin, bool hin_frag, const int32_t* offsets,
-                     const int32_t* tok, const int32_t* border, const uint16_t* zero_row, int N, int Bs, int d,
-                     float* dW, int slot, hipStream_t st) {
-  const DwOperands ops = {Act, Hin, dW, nullptr};
-  return hin_frag ? launch_dw_t<true>(&ops, 1, offsets, tok, border, zero_row, N, Bs, d, slot, st)
-                  : launch_dw_t<false>(&ops, 1, offsets, tok, border, zero_row, N, Bs, d, slot, st);
-}
-
-// The same GEMM over the piece table (Schedule::dw_pieces) of hidden values in fragment order, for one
-// product or two at once, followed by the fixed-order sum of the staged pieces into their blocks (no
+// dW[b][u][c] = sum_{q in bucket b} Hin[q][u] * Act[tok[q]][c], the narrow-block weight-gradient GEMM over the
+// piece table (Schedule::dw_pieces), for one product or two at once, followed by the fixed-order sum of the staged pieces into their blocks (no
 // launch where a routing cannot need any).
 static hipError_t launch_dw_pieces(const DwOperands* ops, int nops, const Schedule& sc, int N, int Bs, int d, int slot,
                                    hipStream_t st) {
   ScopedKernelTimer tm(slot, st);   // (covers the GEMM and the sum of the staged pieces)
-  const hipError_t e = launch_dw_t<true>(ops, nops, nullptr, sc.tok, nullptr, sc.zero_row, sc.dw_cap, Bs, d, -1, st,
-                                         sc.dw_pieces, N);
+  const hipError_t e = Bs <= 64 ? launch_dw_ut<64>(ops, nops, sc, N, Bs, d, st) : launch_dw_ut<128>(ops, nops, sc, N, Bs, d, st);
   if (e != hipSuccess || sc.dw_cap == N) return e;
   const size_t groups = (size_t)(sc.dw_cap - N) * Bs * d / 4;   // 16-byte groups of the most blocks that can have pieces
   const unsigned gx = (unsigned)(groups / 256 < 1 ? 1 : groups / 256 > 1024 ? 1024 : groups / 256);
@@ -1174,7 +1115,7 @@ hipError_t run_fwd(const spt_shape_t& s, const void* X, const void* W1, const vo
     e = launch_wide(kWidePart, s, a, st);
   }
   if (e != hipSuccess) return e;
-  return run_combine(s, w.part, inv, Y, 0, s.d, (size_t)s.d, (size_t)TILE, kSlotCombineY, st);
+  return run_combine(s, w.part, inv, Y, kSlotCombineY, st);
 }
 
 hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const void* W2,
@@ -1215,7 +1156,7 @@ hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const vo
       e = launch_wide(kWidePart, s, a, st);
     }
     if (e != hipSuccess) return e;
-    return run_combine(s, w.part, inv, dX, 0, s.d, (size_t)s.d, (size_t)TILE, kSlotCombineDX, st);
+    return run_combine(s, w.part, inv, dX, kSlotCombineDX, st);
   }
   {
     ScopedKernelTimer tm(kSlotDH, st);
@@ -1237,19 +1178,6 @@ hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const vo
 
 // ------------------------------------------------------------------------------------------
 // Low-rank adapted path (section 2.2 on top of section 4.2).
-constexpr size_t kLoraPiece = 512;
-static size_t lora_piece_rows(const spt_shape_t& s) {
-  size_t piece = kLoraPiece;
-  while ((size_t)s.T * s.k / piece + s.N > 1024) piece *= 2;
-  return piece;
-}
-static size_t lora_chunk_tokens(const spt_shape_t& s) {
-  // chunks of the token axis for the K = T adapter gradients: at least 512 tokens, at most 1024 chunks
-  size_t c = 512;
-  while (((size_t)s.T + c - 1) / c > 1024) c *= 2;
-  return c;
-}
-
 LoraWorkspace plan_lora(const spt_shape_t& s, void* ws, bool backward) {
   const size_t P = (size_t)s.T * s.k, D = (size_t)s.N * s.Bs, T = s.T, d = s.d;
   char* p = static_cast<char*>(ws);
@@ -1266,24 +1194,26 @@ LoraWorkspace plan_lora(const spt_shape_t& s, void* ws, bool backward) {
   w.C2P = static_cast<uint16_t*>(take(32 * d * 2));
   w.A1P = static_cast<uint16_t*>(take(d * 32 * 2));
   w.C2T = static_cast<uint16_t*>(take(d * 32 * 2));
-  w.Z = static_cast<uint16_t*>(take(T * d * 2));
+  w.Z = use_narrow(s) ? static_cast<uint16_t*>(take(T * d * 2)) : nullptr;
   w.Upad = static_cast<uint16_t*>(take(T * 64 * 2));
-  w.Gpad = static_cast<uint16_t*>(take(T * 64 * 2));
-  w.Sb = static_cast<uint16_t*>(take(T * 32 * 2));
   w.Sp = static_cast<float*>(take(P * 32 * 4));
-  w.Sf = static_cast<float*>(take(T * 32 * 4));
   if (backward) {
-    const size_t chunk = lora_chunk_tokens(s), nc = (T + chunk - 1) / chunk;
-    // pieces of at most kLoraPiece rows; at most 1024 of them (the dW kernel's bucket limit)
-    w.max_pieces = (int)(P / lora_piece_rows(s) + s.N);
-    w.gpad = static_cast<float*>(take((size_t)w.max_pieces * s.Bs * 64 * 4));
+    w.Gpad = static_cast<uint16_t*>(take(T * 64 * 2));
+    w.Upair = static_cast<uint16_t*>(take(P * 64 * 2));
+    w.Gpair = static_cast<uint16_t*>(take(P * 64 * 2));
+    w.Rb = static_cast<uint16_t*>(take(T * 32 * 2));
+    w.Vb = static_cast<uint16_t*>(take(T * 32 * 2));
+    w.Sp2 = static_cast<float*>(take(P * 32 * 4));
+    w.piece = grad_piece_rows((int64_t)P, s.N, s.Bs);
+    w.max_pieces = (int)(P / w.piece) + s.N;
+    w.chunk = grad_piece_rows((int64_t)T, 1, s.d);
+    w.nchunks = (int)((T + w.chunk - 1) / w.chunk);
+    w.stage[0] = static_cast<float*>(take((size_t)w.max_pieces * s.Bs * 32 * 4));
+    w.stage[1] = static_cast<float*>(take((size_t)w.max_pieces * s.Bs * 32 * 4));
+    w.stage[2] = static_cast<float*>(take((size_t)w.nchunks * d * 32 * 4));
+    w.stage[3] = static_cast<float*>(take((size_t)w.nchunks * d * 32 * 4));
     w.p_first = static_cast<int32_t*>(take((size_t)(s.N + 1) * 4));
     w.p_off = static_cast<int32_t*>(take((size_t)(w.max_pieces + 1) * 4));
-    w.p_id = static_cast<int32_t*>(take((size_t)w.max_pieces * 4));
-    w.gchunks = static_cast<float*>(take(nc * 32 * d * 4));
-    w.c_off = static_cast<int32_t*>(take((nc + 1) * 4));
-    w.c_tok = static_cast<int32_t*>(take(T * 4));
-    w.c_border = static_cast<int32_t*>(take(nc * 4));
   }
   w.bytes = o;
   return w;
@@ -1303,12 +1233,13 @@ hipError_t run_lora_fwd(const spt_shape_t& s, int r, const void* X, const void* 
     const uint16_t *a1 = static_cast<const uint16_t*>(A1), *c1 = static_cast<const uint16_t*>(C1);
     const uint16_t *b2 = static_cast<const uint16_t*>(B2), *c2 = static_cast<const uint16_t*>(C2);
     PadJobs jobs = {};
-    jobs.job[0] = PadJob{a1, s.d, r, 1, 0, w.A1T, 32, s.d};   // A1^T      [32][d]
-    jobs.job[1] = PadJob{c1, r, D, 1, 1, w.C1T, D, 64};       // C1^T twice [D][64]
-    jobs.job[2] = PadJob{b2, D, r, 1, 0, w.B2T, 32, D};       // B2^T      [32][D]
-    jobs.job[3] = PadJob{c2, r, s.d, 1, 0, w.C2T, s.d, 32};   // C2^T      [d][32]
-    if ((e = lora_pad(jobs, 4, st)) != hipSuccess) return e;
-    if ((e = lora_proj(x, w.A1T, s.T, s.d, w.Upad, st)) != hipSuccess) return e;
+    jobs.job[0] = PadJob{a1, s.d, r, 1, 0, 1, w.A1T, 32, s.d};   // A1^T      [32][d]
+    jobs.job[1] = PadJob{c1, r, D, 1, 1, 0, w.C1T, D, 64};       // C1^T twice [D][64]
+    jobs.job[2] = PadJob{b2, D, r, 1, 0, 1, w.B2T, 32, D};       // B2^T      [32][D]
+    jobs.job[3] = PadJob{c2, r, s.d, 1, 0, 0, w.C2T, s.d, 32};   // C2^T      [d][32]
+    if ((e = lora_setup(jobs, 4, nullptr, st)) != hipSuccess) return e;
+    const ProjJob proj = {x, w.A1T, w.Upad, nullptr};             // U = X A1
+    if ((e = lora_proj(&proj, 1, inv, s.T, s.d, s.k, st)) != hipSuccess) return e;
   }
   const bool narrow = use_narrow(s);
   if (narrow) {
@@ -1331,14 +1262,18 @@ hipError_t run_lora_fwd(const spt_shape_t& s, int r, const void* X, const void* 
     }
     if (e != hipSuccess) return e;
   }
+  // V[t] = sum_b B2_b^T h_b(t); the write-back adds V C2 per token
   {
-    // V[t] = sum_b B2_b^T h_b(t);  Z = V C2, the low-rank row the write-back adds per token
     ScopedKernelTimer tm(kSlotLoraSmall, st);
-    if ((e = lora_pair_gemm(w.fwd.Hact, narrow, w.B2T, offsets, s.N, s.Bs, P, 2, w.Sp, st)) != hipSuccess) return e;
-    if ((e = lora_token_sum(w.Sp, inv, s.T, s.k, w.Sf, nullptr, st)) != hipSuccess) return e;
-    if ((e = lora_expand(w.Sf, w.C2T, s.T, s.d, w.Z, st)) != hipSuccess) return e;
+    const PairJob pair = {w.fwd.Hact, w.B2T, w.Sp};
+    if ((e = lora_pair_gemm(&pair, 1, narrow, offsets, s.N, s.Bs, P, st)) != hipSuccess) return e;
+    if (narrow) e = lora_expand(w.Sp, w.C2T, inv, s.T, s.d, s.k, nullptr, w.Z, nullptr, nullptr, nullptr, st);
+    if (e != hipSuccess) return e;
   }
-  if (!narrow) return run_combine(s, w.fwd.part, inv, Y, 0, s.d, (size_t)s.d, (size_t)TILE, kSlotCombineY, st, w.Z);
+  if (!narrow) {
+    ScopedKernelTimer tm(kSlotCombineY, st);
+    return lora_expand(w.Sp, w.C2T, inv, s.T, s.d, s.k, w.fwd.part, static_cast<uint16_t*>(Y), nullptr, nullptr, nullptr, st);
+  }
   ScopedKernelTimer tm(kSlotDown, st);
   return launch_scatter(s, plan_scatter(s), w.fwd.Hact, static_cast<const uint16_t*>(W2), w.fwd.sched.rstart,
                         w.fwd.sched.tok, static_cast<uint16_t*>(Y), w.Z, w.fwd.split, st);
@@ -1356,24 +1291,22 @@ hipError_t run_lora_bwd(const spt_shape_t& s, int r, const void* X, const void* 
   const Schedule& sc = w.bwd.sched;
   hipError_t e = run_plan(s, offsets, perm, sc, st);
   if (e != hipSuccess) return e;
-  const int chunk = (int)lora_chunk_tokens(s), nc = (s.T + chunk - 1) / chunk;
   {
     ScopedKernelTimer tm(kSlotLoraSmall, st);
     const uint16_t *a1 = static_cast<const uint16_t*>(A1), *c1 = static_cast<const uint16_t*>(C1);
     const uint16_t *b2 = static_cast<const uint16_t*>(B2), *c2 = static_cast<const uint16_t*>(C2);
     PadJobs jobs = {};
-    jobs.job[0] = PadJob{a1, s.d, r, 1, 0, w.A1T, 32, s.d};   // A1^T       [32][d]
-    jobs.job[1] = PadJob{a1, s.d, r, 0, 0, w.A1P, s.d, 32};   // A1         [d][32]
-    jobs.job[2] = PadJob{c1, r, D, 0, 0, w.C1P, 32, D};       // C1         [32][D]
-    jobs.job[3] = PadJob{b2, D, r, 1, 0, w.B2T, 32, D};       // B2^T       [32][D]
-    jobs.job[4] = PadJob{b2, D, r, 0, 1, w.B2P, D, 64};       // B2 twice   [D][64]
-    jobs.job[5] = PadJob{c2, r, s.d, 0, 0, w.C2P, 32, s.d};   // C2         [32][d]
-    if ((e = lora_pad(jobs, 6, st)) != hipSuccess) return e;
-    if ((e = lora_proj(x, w.A1T, s.T, s.d, w.Upad, st)) != hipSuccess) return e;   // U = X A1
-    if ((e = lora_proj(dy, w.C2P, s.T, s.d, w.Gpad, st)) != hipSuccess) return e;  // G = dY C2^T
-    if ((e = lora_chunks(s.T, chunk, nc, w.c_off, w.c_tok, w.c_border, st)) != hipSuccess) return e;
-    if ((e = lora_pieces(offsets, s.N, (int)lora_piece_rows(s), w.max_pieces, w.p_first, w.p_off, w.p_id,
-                         st)) != hipSuccess) return e;
+    jobs.job[0] = PadJob{a1, s.d, r, 1, 0, 1, w.A1T, 32, s.d};   // A1^T       [32][d]
+    jobs.job[1] = PadJob{a1, s.d, r, 0, 0, 0, w.A1P, s.d, 32};   // A1         [d][32]
+    jobs.job[2] = PadJob{c1, r, D, 0, 0, 1, w.C1P, 32, D};       // C1         [32][D]
+    jobs.job[3] = PadJob{b2, D, r, 1, 0, 1, w.B2T, 32, D};       // B2^T       [32][D]
+    jobs.job[4] = PadJob{b2, D, r, 0, 1, 0, w.B2P, D, 64};       // B2 twice   [D][64]
+    jobs.job[5] = PadJob{c2, r, s.d, 0, 0, 1, w.C2P, 32, s.d};   // C2         [32][d]
+    const PieceTable pieces = {offsets, s.N, w.piece, w.max_pieces, w.p_first, w.p_off};
+    if ((e = lora_setup(jobs, 6, &pieces, st)) != hipSuccess) return e;
+    const ProjJob proj[2] = {{x, w.A1T, nullptr, w.Upair},        // U = X A1
+                             {dy, w.C2P, w.Gpad, w.Gpair}};       // G = dY C2^T
+    if ((e = lora_proj(proj, 2, inv, s.T, s.d, s.k, st)) != hipSuccess) return e;
   }
   const bool narrow = use_narrow(s);
   if (narrow) {
@@ -1397,47 +1330,34 @@ hipError_t run_lora_bwd(const spt_shape_t& s, int r, const void* X, const void* 
     }
     if (e != hipSuccess) return e;
   }
+  // R[t] = sum_b C1_b dhpre_b(t), V[t] = sum_b B2_b^T h_b(t);  dX = sum_b dhpre_b W1_b + R A1^T
   {
-    // R[t] = sum_b C1_b dhpre_b(t)
     ScopedKernelTimer tm(kSlotLoraSmall, st);
-    if ((e = lora_pair_gemm(w.bwd.dHpre, narrow, w.C1P, offsets, s.N, s.Bs, P, 2, w.Sp, st)) != hipSuccess) return e;
-    if ((e = lora_token_sum(w.Sp, inv, s.T, s.k, w.Sf, w.Sb, st)) != hipSuccess) return e;
-    if ((e = lora_expand(w.Sf, w.A1P, s.T, s.d, w.Z, st)) != hipSuccess) return e;  // Z = R A1^T
+    const PairJob pair[2] = {{w.bwd.dHpre, w.C1P, w.Sp}, {w.bwd.Hact, w.B2T, w.Sp2}};
+    if ((e = lora_pair_gemm(pair, 2, narrow, offsets, s.N, s.Bs, P, st)) != hipSuccess) return e;
+    if (narrow) e = lora_expand(w.Sp, w.A1P, inv, s.T, s.d, s.k, nullptr, w.Z, w.Rb, w.Sp2, w.Vb, st);
+    if (e != hipSuccess) return e;
   }
-  // dX = sum_b dhpre_b W1_b + R A1^T
   if (narrow) {
     ScopedKernelTimer tm(kSlotDXPart, st);
     e = launch_scatter(s, plan_scatter(s), w.bwd.dHpre, static_cast<const uint16_t*>(W1), sc.rstart, sc.tok,
                        static_cast<uint16_t*>(dX), w.Z, w.bwd.split, st);
   } else {
-    e = run_combine(s, w.bwd.part, inv, dX, 0, s.d, (size_t)s.d, (size_t)TILE, kSlotCombineDX, st, w.Z);
+    ScopedKernelTimer tm(kSlotCombineDX, st);
+    e = lora_expand(w.Sp, w.A1P, inv, s.T, s.d, s.k, w.bwd.part, static_cast<uint16_t*>(dX), w.Rb, w.Sp2, w.Vb, st);
   }
   if (e != hipSuccess) return e;
-  // dA1[i][rho] = sum_t X[t][i] R[t][rho]: the dW GEMM over token chunks, then a sum over chunks
-  e = launch_dw(x, w.Sb, false, w.c_off, w.c_tok, w.c_border, sc.zero_row, nc, 32, s.d, w.gchunks, kSlotLoraGrad, st);
-  if (e != hipSuccess) return e;
-  if ((e = lora_reduce(w.gchunks, nc, 32, s.d, true, false, dA1, s.d, r, st)) != hipSuccess) return e;
-  // dC1[rho][unit] = sum_{q in b} U[tok q][rho] dHpre[q][u]
-  // (U as its two bf16 parts, 64 columns: the two products are added when the result is unpacked)
-  // per piece of a bucket, then summed over the bucket's pieces in order
-  e = launch_dw(w.Upad, w.bwd.dHpre, narrow, w.p_off, sc.tok, w.p_id, sc.zero_row, w.max_pieces, s.Bs, 64, w.gpad,
-                kSlotLoraGrad, st);
-  if (e != hipSuccess) return e;
-  if ((e = lora_reduce_pieces(w.gpad, w.p_first, s.N, s.Bs, r, true, dC1, st)) != hipSuccess) return e;
-  // dB2[unit][rho] = sum_{q in b} Hact[q][u] G[tok q][rho]
-  e = launch_dw(w.Gpad, w.bwd.Hact, narrow, w.p_off, sc.tok, w.p_id, sc.zero_row, w.max_pieces, s.Bs, 64, w.gpad,
-                kSlotLoraGrad, st);
-  if (e != hipSuccess) return e;
-  if ((e = lora_reduce_pieces(w.gpad, w.p_first, s.N, s.Bs, r, false, dB2, st)) != hipSuccess) return e;
-  // V[t] = sum_b B2_b^T h_b(t);  dC2[rho][c] = sum_t V[t][rho] dY[t][c]
-  {
-    ScopedKernelTimer tm(kSlotLoraSmall, st);
-    if ((e = lora_pair_gemm(w.bwd.Hact, narrow, w.B2T, offsets, s.N, s.Bs, P, 2, w.Sp, st)) != hipSuccess) return e;
-    if ((e = lora_token_sum(w.Sp, inv, s.T, s.k, nullptr, w.Sb, st)) != hipSuccess) return e;
-  }
-  e = launch_dw(dy, w.Sb, false, w.c_off, w.c_tok, w.c_border, sc.zero_row, nc, 32, s.d, w.gchunks, kSlotLoraGrad, st);
-  if (e != hipSuccess) return e;
-  return lora_reduce(w.gchunks, nc, 32, s.d, false, false, dC2, r, s.d, st);
+  // dC1[rho][unit] = sum_{q in b} U[tok q][rho] dHpre[q][u],  dB2[unit][rho] = sum_{q in b} Hact[q][u] G[tok q][rho]
+  // (U and G as their two bf16 parts, the two products added),  dA1[i][rho] = sum_t X[t][i] R[t][rho],
+  // dC2[rho][c] = sum_t V[t][rho] dY[t][c]: per piece of the rows, then the pieces in order
+  const int ut = (s.Bs + 127) / 128, dt = (s.d + 127) / 128;
+  const GradJobs jobs = {{
+      {w.bwd.dHpre, w.Upair, w.stage[0], w.p_off, w.p_first, dC1, s.Bs, 64, 32, w.max_pieces, ut, w.piece, P, s.N, 1},
+      {w.bwd.Hact, w.Gpair, w.stage[1], w.p_off, w.p_first, dB2, s.Bs, 64, 32, w.max_pieces, ut, w.piece, P, s.N, 0},
+      {x, w.Rb, w.stage[2], nullptr, nullptr, dA1, s.d, 32, 32, w.nchunks, dt, w.chunk, s.T, 1, 0},
+      {dy, w.Vb, w.stage[3], nullptr, nullptr, dC2, s.d, 32, 32, w.nchunks, dt, w.chunk, s.T, 1, 1}}};
+  ScopedKernelTimer tm(kSlotLoraGrad, st);
+  return lora_grads(jobs, narrow, r, sc.zero_row, st);
 }
 
 }  // namespace spt

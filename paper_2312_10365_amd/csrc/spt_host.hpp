@@ -125,19 +125,11 @@ hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const vo
                    const int32_t* inv, const void* Hsave, void* dX, float* dW1, float* dW2,
                    const BwdWorkspace& w, hipStream_t st, const Schedule* prebuilt = nullptr);
 
-// dW[b][u][c] = sum_{q in bucket b} Hin[q][u] * Act[tok[q]][c] (N buckets, Bs units, d columns):
-// the narrow-block weight-gradient GEMM, also used with a 32/64-wide side by the adapter and
-// router gradients.
-// hin_frag: Hin is in the fragment order of the narrow-block hidden values (ffn_common.hpp).
-hipError_t launch_dw(const uint16_t* Act, const uint16_t* Hin, bool hin_frag, const int32_t* offsets,
-                     const int32_t* tok, const int32_t* border, const uint16_t* zero_row, int N,
-                     int Bs, int d, float* dW, int slot, hipStream_t st);
 // Load-balancing loss of the route network and its gradient.
 struct BalanceWorkspace {
   uint16_t* dl;        // [T][Npad] bf16 d loss / d logit
   float* part;         // [groups][2][N] partial sums of p and of dlogit
-  float* gchunks;      // [chunks][Npad][d] gradient staging
-  int32_t *c_off, *c_tok, *c_border;
+  float* gchunks;      // [chunks][d][Npad] gradient staging
   uint16_t* zero_row;
   int npad, groups, chunk, nchunks;
   size_t bytes;
@@ -154,13 +146,14 @@ struct LoraWorkspace {
   BwdWorkspace bwd;
   uint16_t *A1T, *C1T, *C1P, *B2T, *B2P, *C2P;  // [32][d] [D][64] [32][D] [32][D] [D][64] [32][d]
   uint16_t *A1P, *C2T;                          // [d][32] [d][32]: K-contiguous forms for lora_expand
-  uint16_t* Z;                                  // [T][d] bf16: the low-rank term of an outer projection
+  uint16_t* Z;                                  // [T][d] bf16, narrow blocks: the low-rank term of an outer projection
   uint16_t *Upad, *Gpad;                        // [T][64] bf16 value | remainder: X A1, dY C2^T
-  uint16_t* Sb;                                 // [T][32] bf16 rounded token sums
-  float *Sp, *Sf;                               // [P][32] per pair, [T][32] per token
-  float *gpad, *gchunks;                        // [pieces][Bs][64] and [chunks][32][d] gradient staging
-  int32_t *c_off, *c_tok, *c_border;            // identity schedule over token chunks
-  int32_t *p_first, *p_off, *p_id;              // buckets cut into pieces (see lora_pieces)
+  uint16_t *Upair, *Gpair;                      // [P][64] the same rows in sorted order (backward)
+  uint16_t *Rb, *Vb;                            // [T][32] bf16 rounded token sums (backward)
+  float *Sp, *Sp2;                              // [P][32] per pair
+  float* stage[4];                              // gradient staging: [pieces][Bs][32] twice, [chunks][d][32] twice
+  int32_t *p_first, *p_off;                     // buckets cut into pieces (PieceTable)
+  int piece, chunk, nchunks;                    // rows of a piece / of a chunk of the tokens
   int max_pieces;
   size_t bytes;
 };
@@ -178,26 +171,44 @@ hipError_t run_lora_bwd(const spt_shape_t& s, int r, const void* X, const void* 
 // b' = dup ? b % 32 : b, zero outside src (srows x scols).
 struct PadJob {
   const uint16_t* src;
-  int srows, scols, transpose, dup;
+  int srows, scols, transpose, dup, frag;   // frag: in operand order, see lora_setup_kernel
   uint16_t* dst;
   int drows, dcols;
 };
 constexpr int kMaxPadJobs = 6;
 struct PadJobs { PadJob job[kMaxPadJobs]; };
-hipError_t lora_pad(const PadJobs& jobs, int njobs, hipStream_t st);
-hipError_t lora_expand(const float* S, const uint16_t* MT, int T, int d, uint16_t* Z, hipStream_t st);
-hipError_t lora_proj(const uint16_t* Act, const uint16_t* MT, int T, int d, uint16_t* S, hipStream_t st);
-hipError_t lora_pair_gemm(const uint16_t* Hin, bool hin_frag, const uint16_t* WT, const int32_t* offsets, int N, int Bs,
-                          int P, int act, float* Sp, hipStream_t st);
-hipError_t lora_token_sum(const float* Sp, const int32_t* inv, int T, int k, float* Sf, uint16_t* Sb,
+// Buckets cut into pieces of at most `piece` rows (see lora_setup_kernel).
+struct PieceTable {
+  const int32_t* offsets;
+  int N, piece, max_pieces;
+  int32_t *first, *off;
+};
+struct ProjJob {              // X A or dY C^T: [T][d] x panel [32][d]
+  const uint16_t *act, *panel;
+  uint16_t *by_token, *by_pair;   // [T][64], [P][64]; either may be null
+};
+struct PairJob {              // per pair: Hin [P][Bs] x panel [32][N*Bs]
+  const uint16_t *hin, *panel;
+  float* out;                 // [P][32]
+};
+// out[piece][u][rho] = sum over the piece's rows q of H[q][u] R[q][rho].
+struct GradJob {
+  const uint16_t *H, *R;      // [rows][units], [rows][ldr]
+  float* out;                 // staging [npieces][units][ldo]
+  const int32_t* off;         // piece boundaries; null: `piece` rows each, up to `rows`
+  const int32_t* first;       // first piece of each block; null: all pieces belong to the one block
+  float* result;
+  int units, ldr, ldo, npieces, tiles, piece, rows, nblocks, transpose;   // tiles: ceil(units / 128)
+};
+struct GradJobs { GradJob job[4]; };
+hipError_t lora_setup(const PadJobs& jobs, int njobs, const PieceTable* pieces, hipStream_t st);
+hipError_t lora_proj(const ProjJob* jobs, int njobs, const int32_t* inv, int T, int d, int k, hipStream_t st);
+hipError_t lora_pair_gemm(const PairJob* jobs, int njobs, bool narrow, const int32_t* offsets, int N, int Bs, int P,
                           hipStream_t st);
-hipError_t lora_chunks(int T, int chunk, int nchunks, int32_t* offsets, int32_t* tok, int32_t* border,
-                       hipStream_t st);
-hipError_t lora_pieces(const int32_t* offsets, int N, int piece, int max_pieces, int32_t* first,
-                       int32_t* p_off, int32_t* p_id, hipStream_t st);
-hipError_t lora_reduce_pieces(const float* src, const int32_t* first, int N, int Bs, int r, bool transpose,
-                              float* out, hipStream_t st);
-hipError_t lora_reduce(const float* src, int nchunks, int srows, int scols, bool transpose, bool fold,
-                       float* out, int orows, int ocols, hipStream_t st);
+hipError_t lora_expand(const float* Sp, const uint16_t* panel, const int32_t* inv, int T, int d, int k,
+                       const uint16_t* part, uint16_t* out, uint16_t* Sb, const float* Sp2, uint16_t* Sb2, hipStream_t st);
+hipError_t lora_grads(const GradJobs& jobs, bool frag, int r, const uint16_t* zero_row, hipStream_t st);
+hipError_t row_contraction(const GradJob& jb, const uint16_t* zero_row, hipStream_t st);
+int grad_piece_rows(int64_t rows, int blocks, int units);
 
 }  // namespace spt
