@@ -211,41 +211,131 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
 }
 
 // ------------------------------------------------------------------------------------------
-// K = d GEMM of one 256-row tile of one bucket for Bs <= 128, activation in the epilogue.
+// K = d GEMM of one row tile of one bucket for Bs <= 128, activation in the epilogue.
 //   MODE 0 (forward, Alg. 4 line 4):  Hsave = Xg W1_b^T,  Hact = act(Hsave)
 //   MODE 1 (backward):  dHpre = (dYg W2_b^T) * act'(Hsave),  Hact = act(Hsave)
 // Hsave is row-major [P, Bs] (it crosses the ABI); Hact and dHpre are in fragment order (hfrag_off).
-// C[u][q] is computed with hidden units as MFMA rows, so a lane holds, for ITS bucket row q,
-// hidden units 8g + 4h + e of every 32-unit tile.  Four wavefronts own 64 bucket rows each
-// (all hidden units) and share the LDS DMA: gathered rows + weight block through a 3-stage
-// ring (global_load_lds_dwordx4, the gather folded into the DMA addresses).  The kernel is
-// bound by bytes entering the CU; two workgroups per CU.  The K = Bs contraction that follows
+// C[u][q] is computed with hidden units as MFMA rows, so a lane holds hidden units of ITS bucket row q.  The
+// gathered rows and the weight block go through an LDS ring (global_load_lds_dwordx4, the gather folded into the copy
+// addresses).  The kernel is bound by bytes entering the CU.  The K = Bs contraction that follows
 // (down-projection, dX) is the token-range-stationary kernel of ffn_scatter.hip.
-constexpr int KD_KT = 32;  // K values per stage
+// Two tilings: 256 rows, eight wavefronts, one workgroup per CU (ffn_up_pair_kernel); and, where that would leave CUs
+// without a tile, 64 rows, two wavefronts of 32 rows each, three workgroups per CU (ffn_up_kernel).
+constexpr int KD_KT = 32;         // K values per stage of the 64-row tiles
 constexpr int FU_ROWS = 256;      // rows of a tile
 constexpr int FU_ROWS_FEW = 64;   // ... where 256-row tiles would leave CUs without one
 
-// WV wavefronts own 32 NI rows each: (4, 2) = 256-row tiles with a 3-slot ring, two workgroups per CU;
-// (2, 1) = 64-row tiles with a 4-slot ring, three per CU.
-template <int KS, int WV>
+template <int KS>
 struct UpTile {
-  static constexpr int NI = WV == 4 ? 2 : 1, ROWS = 32 * NI * WV, SLOTS = WV == 4 ? 3 : 4;
-  static constexpr int UNITS = KS * 16;                      // weight rows of a stage
-  static constexpr int STAGE_SLOTS = (UNITS + ROWS) * 4;     // 16-byte slots of a stage (24 KiB at 256 rows x 128 units)
+  static constexpr int SLOTS = 4;
+  static constexpr int UNITS = KS * 16;                           // weight rows of a stage
+  static constexpr int STAGE_SLOTS = (UNITS + FU_ROWS_FEW) * 4;   // 16-byte slots of a stage (12 KiB at 128 units)
   static constexpr int SMEM = SLOTS * STAGE_SLOTS * 16;
 };
 
-template <int MODE, int ACT, int KS, int WV>
-__global__ __launch_bounds__(64 * WV, 2) void ffn_up_kernel(
+// Epilogue of a 32-row tile: lane (i, h) holds, for row q, units 32 mi + 8 g + 4 h + e in c[mi][4 g + e].
+template <int MODE, int ACT, int MI>
+__device__ __forceinline__ void up_store(const f32x16 (&c)[MI], int q, int q0, int qend, int h, int Bs,
+                                         uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact,
+                                         uint16_t* __restrict__ dHpre) {
+  const bool live = q < qend;
+  const int ql = live ? q : q0;
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int u = mi * 32 + 8 * g + 4 * h;
+      const size_t off = (size_t)ql * Bs + u;           // Hsave: row-major
+      const size_t foff = hfrag_off(ql, u, Bs);         // Hact, dHpre
+      const float c0 = c[mi][4 * g], c1 = c[mi][4 * g + 1], c2 = c[mi][4 * g + 2], c3 = c[mi][4 * g + 3];
+      if (MODE == 0) {
+        if (live) {
+          if (Hsave) *reinterpret_cast<uint2*>(Hsave + off) = make_uint2(pack_bf16x2(c0, c1), pack_bf16x2(c2, c3));
+          *reinterpret_cast<uint2*>(Hact + foff) =
+              make_uint2(pack_bf16x2(act_fn<ACT>(c0), act_fn<ACT>(c1)), pack_bf16x2(act_fn<ACT>(c2), act_fn<ACT>(c3)));
+        }
+      } else {
+        const uint2 hp = *reinterpret_cast<const uint2*>(Hsave + off);
+        const float z0 = lo_bf16(hp.x), z1 = hi_bf16(hp.x), z2 = lo_bf16(hp.y), z3 = hi_bf16(hp.y);
+        if (live) {
+          *reinterpret_cast<uint2*>(dHpre + foff) =
+              make_uint2(pack_bf16x2(c0 * act_grad<ACT>(z0), c1 * act_grad<ACT>(z1)),
+                         pack_bf16x2(c2 * act_grad<ACT>(z2), c3 * act_grad<ACT>(z3)));
+          *reinterpret_cast<uint2*>(Hact + foff) =
+              make_uint2(pack_bf16x2(act_fn<ACT>(z0), act_fn<ACT>(z1)), pack_bf16x2(act_fn<ACT>(z2), act_fn<ACT>(z3)));
+        }
+      }
+    }
+    // keep the scheduler from interleaving the 16-value groups: their erf evaluations
+    // would otherwise all be in flight at once and spill
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The same where the hidden units went through rho32: units 32 mi + 16 h + (0..15) in c[mi], stored as 32-byte runs.
+template <int MODE, int ACT, int MI>
+__device__ __forceinline__ void up_store_runs(const f32x16 (&c)[MI], int q, int q0, int qend, int h, int Bs,
+                                              uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact,
+                                              uint16_t* __restrict__ dHpre) {
+  const bool live = q < qend;
+  const int ql = live ? q : q0;
+  uint4* hs = reinterpret_cast<uint4*>(Hsave + (size_t)ql * Bs + 16 * h);   // 32 units further: 4 words
+  const size_t f0 = hfrag_off(ql, 16 * h, Bs);                              // 32 units further: 1024 values
+  uint4 z[MODE ? MI : 1][2];
+  if (MODE)
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+      z[mi][0] = hs[4 * mi];
+      z[mi][1] = hs[4 * mi + 1];
+    }
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      if (MODE == 0) {
+        uint32_t hw[4], aw[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          hw[e] = pack_bf16x2(c[mi][8 * hf + 2 * e], c[mi][8 * hf + 2 * e + 1]);
+          aw[e] = pack_bf16x2(act_fn<ACT>(c[mi][8 * hf + 2 * e]), act_fn<ACT>(c[mi][8 * hf + 2 * e + 1]));
+        }
+        if (live) {
+          if (Hsave) hs[4 * mi + hf] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+          reinterpret_cast<uint4*>(Hact + f0 + 1024 * mi)[hf] = make_uint4(aw[0], aw[1], aw[2], aw[3]);
+        }
+      } else {
+        const uint4 zq = z[MODE ? mi : 0][hf];
+        const uint32_t zw[4] = {zq.x, zq.y, zq.z, zq.w};
+        uint32_t gw[4], aw[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float zl = lo_bf16(zw[e]), zh = hi_bf16(zw[e]);
+          gw[e] = pack_bf16x2(c[mi][8 * hf + 2 * e] * act_grad<ACT>(zl), c[mi][8 * hf + 2 * e + 1] * act_grad<ACT>(zh));
+          aw[e] = pack_bf16x2(act_fn<ACT>(zl), act_fn<ACT>(zh));
+        }
+        if (live) {
+          reinterpret_cast<uint4*>(dHpre + f0 + 1024 * mi)[hf] = make_uint4(gw[0], gw[1], gw[2], gw[3]);
+          reinterpret_cast<uint4*>(Hact + f0 + 1024 * mi)[hf] = make_uint4(aw[0], aw[1], aw[2], aw[3]);
+        }
+      }
+      // keep the scheduler from interleaving the groups: their erf evaluations would otherwise all be in
+      // flight at once and spill
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+template <int MODE, int ACT, int KS>
+__global__ __launch_bounds__(128, 2) void ffn_up_kernel(
     const uint16_t* __restrict__ Wa, const uint16_t* __restrict__ Act,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ kd_count,
     const KdTile* __restrict__ kd_list, int cap, const int32_t* __restrict__ tok, int Bs, int d,
     uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact, uint16_t* __restrict__ dHpre,
     const uint16_t* __restrict__ Xe, const uint16_t* __restrict__ We) {
   constexpr int MI = KS / 2;   // 32-unit tiles of the block
-  typedef UpTile<KS, WV> Tile;
-  constexpr int NI = Tile::NI, SLOTS = Tile::SLOTS, STAGE = Tile::STAGE_SLOTS;
-  constexpr int PA = 2 * MI, NA = (PA + WV - 1) / WV, NB = 2 * NI, NP = NA + NB;   // copies per stage: weights, of a wavefront, rows, all
+  typedef UpTile<KS> Tile;
+  constexpr int SLOTS = Tile::SLOTS, STAGE = Tile::STAGE_SLOTS;
+  constexpr int NA = MI, NB = 2, NP = NA + NB;   // a wavefront's copies per stage: weights, rows, all
   extern __shared__ uint4 fu_smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint32_t lds0 = (uint32_t)(uintptr_t)fu_smem;
@@ -271,7 +361,7 @@ __global__ __launch_bounds__(64 * WV, 2) void ffn_up_kernel(
     int urow[NA], apiece[NA], tq[NB];  // hidden unit / token id of this lane's row in each instruction
 #pragma unroll
     for (int j = 0; j < NA; ++j) {
-      apiece[j] = (wave * NA + j) % PA;  // (surplus instructions repeat one: same bytes to the same place)
+      apiece[j] = wave * NA + j;
       urow[j] = b * Bs + apiece[j] * 16 + (lane >> 2);
     }
 #pragma unroll
@@ -302,13 +392,11 @@ __global__ __launch_bounds__(64 * WV, 2) void ffn_up_kernel(
       }
     };
 
-    f32x16 acc[MI][NI];
+    f32x16 acc[MI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+      for (int v = 0; v < 16; ++v) acc[mi][v] = 0.f;
     // Ring schedule: "issue j" copies K-stage min(j, nk-1) into slot j % SLOTS; past the last stage it
     // repeats it into a slot nobody reads any more, so the loop body has no branch and every
     // vmcnt wait is a constant.  Issues 0 .. SLOTS-2 go out up front, iteration kt sends issue kt+SLOTS-1
@@ -330,74 +418,235 @@ __global__ __launch_bounds__(64 * WV, 2) void ffn_up_kernel(
       // all fragment reads of the stage go out first, so the MFMAs of the first K-step run
       // while the second K-step's fragments are still arriving (the compiler left to itself
       // sinks each read next to its use and exposes the LDS latency every few MFMAs)
-      bf16x8 a[KD_KT / 16][MI], bb[KD_KT / 16][NI];
+      bf16x8 a[KD_KT / 16][MI], bb[KD_KT / 16];
 #pragma unroll
       for (int s = 0; s < KD_KT / 16; ++s) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) a[s][mi] = as_bf16x8(As[kd_slot(mi * 32 + i, 2 * s + h)]);
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni) bb[s][ni] = as_bf16x8(Bt[kd_slot(wave * 32 * NI + ni * 32 + i, 2 * s + h)]);
+        bb[s] = as_bf16x8(Bt[kd_slot(wave * 32 + i, 2 * s + h)]);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int s = 0; s < KD_KT / 16; ++s)
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-          for (int ni = 0; ni < NI; ++ni) {
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][mi], bb[s][ni], acc[mi][ni], 0, 0, 0);
-            const int m = (s * MI + mi) * NI + ni;
-            if (m < NP) {
-              issue_piece(fill, kfill, m);
-              __builtin_amdgcn_sched_barrier(0);
-            }
+        for (int mi = 0; mi < MI; ++mi) {
+          acc[mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][mi], bb[s], acc[mi], 0, 0, 0);
+          const int m = s * MI + mi;
+          if (m < NP) {
+            issue_piece(fill, kfill, m);
+            __builtin_amdgcn_sched_barrier(0);
           }
+        }
 #pragma unroll
-      for (int m = (KD_KT / 16) * MI * NI; m < NP; ++m) issue_piece(fill, kfill, m);  // (small blocks: fewer MFMAs than copies)
+      for (int m = (KD_KT / 16) * MI; m < NP; ++m) issue_piece(fill, kfill, m);  // (small blocks: fewer MFMAs than copies)
       __builtin_amdgcn_sched_barrier(0);
       stage = (stage == SLOTS - 1) ? 0 : stage + 1;
     }
     wait_vmcnt<0>();  // the trailing copies (repeats of the last stage) are done too
-    // epilogue: lane (i, h) holds, for row q, units 32 mi + 8 g + 4 h + e  (v = 4 g + e)
+    up_store<MODE, ACT, MI>(acc, q0 + wave * 32 + i, q0, qend, h, Bs, Hsave, Hact, dHpre);
+  }
+}
+
+// The K = d GEMM of a 256-row tile with eight wavefronts, one workgroup per CU, in stages of 64 K-values.
+// A row then contributes 128 contiguous bytes to a stage, a whole line: an LDS copy of 64-byte pieces reaches
+// 64-80 bytes per ns and CU out of L2, one of 128-byte pieces 125, and the tile wants 48 KiB per 1024 matrix-core
+// cycles.  (With 64-byte pieces, two workgroups of four wavefronts: 364 us on the 7B-like shape, 326 with every
+// operand in L2.)  Wavefronts w and w + 4 share a SIMD and 64 bucket rows; each takes half of every stage's K-steps
+// (the two sums are added through LDS at the end), and they work in opposite phases: while one reads its fragments
+// of a stage the other multiplies, a barrier between the phases, so neither the matrix cores nor LDS wait for the
+// other.  Ring of three stages: the slot of stage kt - 1 is filled again (stage kt + 2) as soon as both have
+// read it.
+template <int KS>
+struct UpPair {
+  static constexpr int UNITS = KS * 16, ROWS = UNITS + FU_ROWS;
+  static constexpr int STAGE = ROWS * 128;        // bytes: 48 KiB at 128 units
+  static constexpr int SLOTS = KS <= 4 ? 4 : 3;
+  static constexpr int SMEM = SLOTS * STAGE;
+};
+// 16-byte chunk c of a 128-byte row lies at physical chunk c ^ up_swz(row): one chunk of the 16 rows that are read together
+// -- consecutive bucket rows, hidden units in rho32 order -- then covers all banks.
+__device__ __forceinline__ int up_swz_row(int row) { return (row >> 1) & 7; }
+__device__ __forceinline__ int up_swz_unit(int row) { return ((row >> 1) & 3) | ((row >> 2) & 4); }
+
+template <int MODE, int ACT, int KS, bool EXT>
+__global__ __launch_bounds__(512, 2) void ffn_up_pair_kernel(
+    const uint16_t* __restrict__ Wa, const uint16_t* __restrict__ Act, const int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ kd_count, const KdTile* __restrict__ kd_list, int cap, const int32_t* __restrict__ tok,
+    int Bs, int d, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact, uint16_t* __restrict__ dHpre,
+    const uint16_t* __restrict__ Xe, const uint16_t* __restrict__ We) {
+  typedef UpPair<KS> Tile;
+  constexpr int MI = KS / 2, SLOTS = Tile::SLOTS, STAGE = Tile::STAGE;
+  constexpr int PA = 2 * KS;                           // copies of the weight rows of a stage (8 rows each)
+  constexpr int NA = (PA + 7) / 8, NB = 4, NP = NA + NB;   // copies of a wavefront per stage
+  extern __shared__ uint4 fu_smem[];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int grp = wave >> 2, rw = wave & 3;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)fu_smem;
+  const char* ring = reinterpret_cast<const char*>(fu_smem);
+  const int nkd = d / 64, nk = nkd + (EXT ? 1 : 0), klast = nk - 1;   // (EXT, low-rank adapters: one stage more)
+  const int xcd = blockIdx.x & 7, wg_per_xcd = gridDim.x >> 3;
+  const int count = kd_count[xcd];
+
+  for (int slot_id = blockIdx.x >> 3; slot_id < count; slot_id += wg_per_xcd) {
+    const KdTile tile = kd_list[(size_t)xcd * cap + slot_id];
+    const int b = tile.bucket, q0 = tile.q0;
+    const int qend = offsets[b + 1];
+    // (lane roles from an opaque thread id: as loop invariants they would be kept, spilled, across the tiles)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, i = lane & 31, h = lane >> 5;
+    // fragment addresses: chunk 2 s + h of the lane's hidden unit / bucket row (and 32, 64, ... further); this
+    // wavefront's K-steps are s = 2 grp, 2 grp + 1
+    uint32_t foff_a[2], foff_b[2];
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      const int q = q0 + wave * 32 * NI + ni * 32 + i;
-      const bool live = q < qend;
-      const size_t orow = (size_t)(live ? q : q0) * Bs;
+    for (int s = 0; s < 2; ++s) {
+      const int ch = 2 * (2 * grp + s) + h;
+      foff_a[s] = (uint32_t)(rho32(i) * 128 + ((ch ^ up_swz_unit(rho32(i))) << 4));
+      foff_b[s] = (uint32_t)(i * 128 + ((ch ^ up_swz_row(i)) << 4));
+    }
+    // DMA: instruction p of a stage fills rows 8 p .. 8 p + 7; lane L row L / 8, physical chunk L % 8.
+    const uint16_t* arow[NA];
+    const uint16_t* brow[NB];
+    int urow[NA], apiece[NA], tq[NB];
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
+    for (int j = 0; j < NA; ++j) {
+      apiece[j] = (wave * NA + j) % PA;   // (surplus instructions repeat one: same bytes to the same place)
+      const int row = apiece[j] * 8 + (lane >> 3);
+      urow[j] = b * Bs + row;
+      arow[j] = Wa + (size_t)urow[j] * d + (((lane & 7) ^ up_swz_unit(row)) << 3);
+    }
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const size_t off = orow + mi * 32 + 8 * g + 4 * h;                        // Hsave: row-major
-          const size_t foff = hfrag_off(live ? q : q0, mi * 32 + 8 * g + 4 * h, Bs);  // Hact, dHpre
-          const float c0 = acc[mi][ni][4 * g], c1 = acc[mi][ni][4 * g + 1];
-          const float c2 = acc[mi][ni][4 * g + 2], c3 = acc[mi][ni][4 * g + 3];
-          if (MODE == 0) {
-            if (live) {
-              if (Hsave)
-                *reinterpret_cast<uint2*>(Hsave + off) = make_uint2(pack_bf16x2(c0, c1), pack_bf16x2(c2, c3));
-              *reinterpret_cast<uint2*>(Hact + foff) =
-                  make_uint2(pack_bf16x2(act_fn<ACT>(c0), act_fn<ACT>(c1)),
-                             pack_bf16x2(act_fn<ACT>(c2), act_fn<ACT>(c3)));
-            }
-          } else {
-            const uint2 hp = *reinterpret_cast<const uint2*>(Hsave + off);
-            const float z0 = lo_bf16(hp.x), z1 = hi_bf16(hp.x), z2 = lo_bf16(hp.y), z3 = hi_bf16(hp.y);
-            if (live) {
-              *reinterpret_cast<uint2*>(dHpre + foff) =
-                  make_uint2(pack_bf16x2(c0 * act_grad<ACT>(z0), c1 * act_grad<ACT>(z1)),
-                             pack_bf16x2(c2 * act_grad<ACT>(z2), c3 * act_grad<ACT>(z3)));
-              *reinterpret_cast<uint2*>(Hact + foff) =
-                  make_uint2(pack_bf16x2(act_fn<ACT>(z0), act_fn<ACT>(z1)),
-                             pack_bf16x2(act_fn<ACT>(z2), act_fn<ACT>(z3)));
+    for (int j = 0; j < NB; ++j) {
+      const int row = (wave * NB + j) * 8 + (lane >> 3);
+      tq[j] = tok[(q0 + row < qend) ? q0 + row : q0];
+      brow[j] = Act + (size_t)tq[j] * d + (((lane & 7) ^ up_swz_row(row)) << 3);
+    }
+    auto issue_piece = [&](int slot, int kt, int piece) {
+      const uint32_t base = lds0 + (uint32_t)(slot * STAGE);
+      const bool ext = EXT && kt >= nkd;
+      if (piece < NA) {
+        const int j = piece;
+        const int ch8 = ((lane & 7) ^ up_swz_unit(apiece[j] * 8 + (lane >> 3))) << 3;
+        dma16(ext ? We + (size_t)urow[j] * 64 + ch8 : arow[j] + kt * 64,
+              __builtin_amdgcn_readfirstlane(base + (uint32_t)(apiece[j] * 1024)));
+      } else {
+        const int j = piece - NA;
+        const int ch8 = ((lane & 7) ^ up_swz_row(j * 8 + (lane >> 3))) << 3;
+        dma16(ext ? Xe + (size_t)tq[j] * 64 + ch8 : brow[j] + kt * 64,
+              __builtin_amdgcn_readfirstlane(base + (uint32_t)(Tile::UNITS * 128 + (wave * NB + j) * 1024)));
+      }
+    };
+    bf16x8 a[2][MI], bb[2][2];
+    auto read_frags = [&](int slot) {
+      const char* st = ring + slot * STAGE;
+      const char* bt = st + Tile::UNITS * 128 + rw * 64 * 128;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) a[s][mi] = *reinterpret_cast<const bf16x8*>(st + foff_a[s] + mi * 4096);
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) bb[s][ni] = *reinterpret_cast<const bf16x8*>(bt + foff_b[s] + ni * 4096);
+      }
+    };
+    f32x16 acc[MI][2];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+    // the products of the fragments in registers, with stage min(kf, klast) copied into `slot` behind them
+    auto multiply = [&](bool fill, int slot, int kf) {
+      constexpr int C0 = 4 * MI >= NP + 4 ? 4 : 0;   // first MFMA with a copy behind it
+      const int kfill = kf < klast ? kf : klast;
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < 2; ++ni) {
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][mi], bb[s][ni], acc[mi][ni], 0, 0, 0);
+            const int m = (s * MI + mi) * 2 + ni;
+            if (fill && m >= C0 && m < C0 + NP) {
+              issue_piece(slot, kfill, m - C0);
+              __builtin_amdgcn_sched_barrier(0);
             }
           }
-        }
-        // keep the scheduler from interleaving the 16-value groups: their erf evaluations
-        // would otherwise all be in flight at once and spill
+      if (fill)
+#pragma unroll
+        for (int p = 4 * MI - C0; p < NP; ++p) issue_piece(slot, kfill, p);   // (small blocks: fewer MFMAs than copies)
+      __builtin_amdgcn_sched_barrier(0);
+    };
+
+    __builtin_amdgcn_s_barrier();  // LDS of the previous tile is free
+#pragma unroll
+    for (int st = 0; st < SLOTS - 1; ++st)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) issue_piece(st, klast < st ? klast : st, p);
+    wait_vmcnt<(SLOTS - 2) * NP>();
+    // Phase A of stage kt (after the first barrier): wavefronts 0-3 read it, 4-7 multiply stage kt - 1; phase B: the
+    // other way round.  Each sends its copies of stage kt + SLOTS - 1 behind its own products; at the end of
+    // phase B its copies of stage kt + 1 have landed.
+    int slot = 0, fill = SLOTS - 1;
+    auto step = [&] {
+      slot = slot + 1 == SLOTS ? 0 : slot + 1;
+      fill = fill + 1 == SLOTS ? 0 : fill + 1;
+    };
+    if (grp == 0) {
+      for (int kt = 0; kt < nk; ++kt) {
+        __builtin_amdgcn_s_barrier();
+        read_frags(slot);
         __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        multiply(true, fill, kt + SLOTS - 1);
+        wait_vmcnt<(SLOTS - 2) * NP>();
+        step();
       }
+    } else {
+      for (int kt = 0; kt < nk; ++kt) {
+        __builtin_amdgcn_s_barrier();
+        if (kt > 0) {
+          multiply(true, fill, kt + SLOTS - 1);
+        } else {
+#pragma unroll
+          for (int p = 0; p < NP; ++p) issue_piece(fill, klast < SLOTS - 1 ? klast : SLOTS - 1, p);
+        }
+        __builtin_amdgcn_s_barrier();
+        read_frags(slot);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        wait_vmcnt<(SLOTS - 2) * NP>();
+        step();
+      }
+      multiply(false, 0, 0);
     }
+    wait_vmcnt<0>();               // the trailing copies (repeats of the last stage) are done too
+    __builtin_amdgcn_s_barrier();  // ... everyone's: the ring is free
+    // Wavefront w keeps rows 0-31 of the pair's 64, w + 4 rows 32-63; each hands the other its sums of the other half.
+    f32x4* xch = reinterpret_cast<f32x4*>(fu_smem) + lane;
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = grp ? acc[mi][0][4 * g + e] : acc[mi][1][4 * g + e];
+        xch[((rw * 2 + (grp ^ 1)) * MI * 4 + mi * 4 + g) * 64] = o;
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    f32x16 c[MI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 o = xch[((rw * 2 + grp) * MI * 4 + mi * 4 + g) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[mi][4 * g + e] = (grp ? acc[mi][1][4 * g + e] : acc[mi][0][4 * g + e]) + o[e];
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    up_store_runs<MODE, ACT, MI>(c, q0 + rw * 64 + grp * 32 + i, q0, qend, h, Bs, Hsave, Hact, dHpre);
   }
 }
 
@@ -975,22 +1224,28 @@ static hipError_t run_combine(const spt_shape_t& s, const uint16_t* part, const 
   return hipSuccess;
 }
 
-template <int MODE, int ACT, int KS, int WV>
+template <int MODE, int ACT, int KS>
 static hipError_t launch_up_t(const spt_shape_t& s, const uint16_t* Wa, const uint16_t* Act,
                               const int32_t* offsets, const Schedule& sc, uint16_t* Hsave, uint16_t* Hact,
                               uint16_t* dHpre, hipStream_t st, const uint16_t* Xe, const uint16_t* We) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_kernel<MODE, ACT, KS, WV>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, UpTile<KS, WV>::SMEM);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  const int most = WV == 4 ? 64 : 96;     // two (three) workgroups per CU
-  const int wg_per_xcd = sc.kd_cap < most ? sc.kd_cap : most;
-  ffn_up_kernel<MODE, ACT, KS, WV><<<dim3(8 * wg_per_xcd), 64 * WV, UpTile<KS, WV>::SMEM, st>>>(
-      Wa, Act, offsets, sc.kd_count, static_cast<const KdTile*>(sc.kd_list), sc.kd_cap, sc.tok, s.Bs, s.d,
-      Hsave, Hact, dHpre, Xe, We);
+  static const hipError_t attr[3] = {
+      hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_kernel<MODE, ACT, KS>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, UpTile<KS>::SMEM),
+      hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_pair_kernel<MODE, ACT, KS, false>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, UpPair<KS>::SMEM),
+      hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_pair_kernel<MODE, ACT, KS, true>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, UpPair<KS>::SMEM)};
+  const bool few = kd_rows(s) == FU_ROWS_FEW;
+  const hipError_t e = attr[few ? 0 : Xe ? 2 : 1];
+  if (e != hipSuccess) return e;
+  const int most = few ? 96 : 32;     // three workgroups per CU, or one
+  const int grid = 8 * (sc.kd_cap < most ? sc.kd_cap : most);
+  const KdTile* list = static_cast<const KdTile*>(sc.kd_list);
+#define SPT_UP_ARGS Wa, Act, offsets, sc.kd_count, list, sc.kd_cap, sc.tok, s.Bs, s.d, Hsave, Hact, dHpre, Xe, We
+  if (few) ffn_up_kernel<MODE, ACT, KS><<<grid, 128, UpTile<KS>::SMEM, st>>>(SPT_UP_ARGS);
+  else if (Xe) ffn_up_pair_kernel<MODE, ACT, KS, true><<<grid, 512, UpPair<KS>::SMEM, st>>>(SPT_UP_ARGS);
+  else ffn_up_pair_kernel<MODE, ACT, KS, false><<<grid, 512, UpPair<KS>::SMEM, st>>>(SPT_UP_ARGS);
+#undef SPT_UP_ARGS
   return hipGetLastError();
 }
 
@@ -1014,8 +1269,7 @@ static hipError_t launch_up(const spt_shape_t& s, const uint16_t* Wa, const uint
                             uint16_t* dHpre, hipStream_t st, const uint16_t* Xe = nullptr,
                             const uint16_t* We = nullptr) {
 #define SPT_UP(ACT, KS)                                                                                                \
-  return kd_rows(s) == FU_ROWS ? launch_up_t<MODE, ACT, KS, 4>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We) \
-                               : launch_up_t<MODE, ACT, KS, 2>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We)
+  return launch_up_t<MODE, ACT, KS>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We)
 #define SPT_UP_KS(ACT)                    \
   switch (s.Bs / 16) {                    \
     case 2: SPT_UP(ACT, 2);               \
