@@ -18,7 +18,8 @@
 //   transpose_lists_kernel  one workgroup per sequence: the index lists regrouped by key, each
 //                           key's entries in ascending query order (bit matrix in LDS, popcount ranks)
 //   attn_row_kernel, attn_kv_kernel   the dots + accumulate pair with rows read from L2 (one
-//                           wavefront per query / per key), for sequences too large for LDS
+//                           wavefront per query / per key), for sequences too large for LDS; the query
+//                           one also in front of the dense key side where few of more than 512 keys are kept
 #include <math.h>
 
 #include "mha_host.hpp"
@@ -390,7 +391,8 @@ __device__ __forceinline__ void fma8(float (&acc)[8], float w, const u32x4& row)
 //   w_l = softmax_l(scale * R[v] . G1[idx_l]),  Out[v] = sum_l w_l G2[idx_l],  A <- w.
 // With (R, G1, G2) = (dY, V, K) it is the query side of the backward pass:
 //   dA_l = R[v] . G1[idx_l],  w_l = A_l (dA_l - sum_m A_m dA_m) scale,  Out[v] = sum_l w_l G2[idx_l],
-// and w is kept (dS) for the key side.  Entry l lives on lane l % 64 for the softmax; for the row
+// and w is kept (dS) for the key side, with (maxes given) the largest |A| and |dS| of the workgroup's four queries,
+// which the dense key side scales by.  Entry l lives on lane l % 64 for the softmax; for the row
 // work lane = (g, c): group g handles entry step * G + g, c is the 16-byte piece of the row.
 template <int DH, int LPL, bool BWD>
 __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restrict__ R,
@@ -398,14 +400,15 @@ __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restric
                                                        const uint16_t* __restrict__ G2,
                                                        const int32_t* __restrict__ idx,
                                                        float* __restrict__ A, float* __restrict__ dS,
+                                                       float2* __restrict__ maxes,
                                                        uint16_t* __restrict__ Out, int S, int n, int L,
                                                        float scale) {
   constexpr int LPR = RowMap<DH>::LPR, G = RowMap<DH>::G;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int s, blk;
   if (!seq_block((n + 3) >> 2, S, s, blk)) return;
-  const int i = blk * 4 + wave;
-  if (i >= n) return;                  // whole wavefront; no barrier follows
+  __shared__ float2 wmax[4];
+  const int i = min(blk * 4 + wave, n - 1);   // (past the end: the last query again, same values to the same place)
   const size_t v = (size_t)s * n + i;
   const int g = lane / LPR, c = lane % LPR;
   const uint16_t* g1 = G1 + (size_t)s * n * DH + c * 8;
@@ -480,6 +483,17 @@ __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restric
       w[cc] = a[cc] * (w[cc] - dotsum) * scale;
       if (l < L) dS[v * L + l] = w[cc];
     }
+    if (maxes) {   // (uniform)
+      float ma = 0.f, mw = 0.f;
+#pragma unroll
+      for (int cc = 0; cc < LPL; ++cc) {
+        ma = fmaxf(ma, fabsf(a[cc]));
+        mw = fmaxf(mw, cc * 64 + lane < L ? fabsf(w[cc]) : 0.f);
+      }
+      ma = wave_max(ma);
+      mw = wave_max(mw);
+      if (lane == 0) wmax[wave] = make_float2(ma, mw);
+    }
   }
   // Weighted sum of the gathered rows.
 #pragma unroll
@@ -515,6 +529,13 @@ __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restric
 #pragma unroll
     for (int e = 0; e < 4; ++e) o4[e] = pack_bf16x2(acc[2 * e], acc[2 * e + 1]);
     *reinterpret_cast<u32x4*>(Out + v * DH + c * 8) = o4;
+  }
+  if (BWD && maxes) {
+    __syncthreads();
+    if (threadIdx.x == 0)
+      maxes[(size_t)s * ((n + 3) >> 2) + blk] =
+          make_float2(fmaxf(fmaxf(wmax[0].x, wmax[1].x), fmaxf(wmax[2].x, wmax[3].x)),
+                      fmaxf(fmaxf(wmax[0].y, wmax[1].y), fmaxf(wmax[2].y, wmax[3].y)));
   }
 }
 
@@ -1145,6 +1166,18 @@ __global__ __launch_bounds__(kSeqThreads) void seq_accum_kernel(const uint16_t* 
 // four at a time, so they want L >= 4.
 bool use_dense(const spt_mha_shape_t& s) { return s.L >= 4 && s.n <= 32 * s.L; }
 
+// The query side of dense shapes (forward, dQ).  Up to 512 keys are one pass of the tile kernel.  Longer sequences go
+// through it in chunks, and where few keys are kept gathering the rows from L2 is faster; the line is where the two
+// met, L about (dh 64) 80, 100, 115, 192, 256 and (dh 128) 80, 87, 103, 130, 170 at n 520, 768, 1024, 1536, 2048.
+// us, forward, dense and gathering: n 2048, dh 64, L 64: 309, 152; n 1024, dh 128, L 64: 221, 138; L 128: 220, 273.
+constexpr int kDenseRowsKeys = 512;
+bool use_dense_rows(const spt_mha_shape_t& s) {
+  if (!use_dense(s)) return false;
+  return s.n <= kDenseRowsKeys || (s.dh == 64 ? s.L > 64 + s.n * s.n / 22000 : s.L > 50 + s.n / 17);
+}
+// Gathering query side: out of LDS up to the same length, from L2 beyond.
+bool rows_in_lds(const spt_mha_shape_t& s) { return s.n <= kDenseRowsKeys; }
+
 struct MhaWorkspace {
   float* dS;          // [S][n][L]
   float2* maxes;      // dense tiles: [S][ceil(n/4)] largest |A|, |dS| of four queries
@@ -1187,11 +1220,11 @@ bool aligned4(const void* p) { return p && (reinterpret_cast<uintptr_t>(p) & 3) 
 
 template <int DH, bool BWD>
 void launch_row(const spt_mha_shape_t& s, const uint16_t* R, const uint16_t* G1, const uint16_t* G2,
-                const int32_t* idx, float* A, float* dS, uint16_t* Out, hipStream_t st) {
+                const int32_t* idx, float* A, float* dS, float2* maxes, uint16_t* Out, hipStream_t st) {
   const dim3 grid(seq_block_grid((s.n + 3) / 4, s.S));
   const int lpl = (s.L + 63) / 64;
 #define SPT_ROW(LPL_) \
-  hipLaunchKernelGGL((attn_row_kernel<DH, LPL_, BWD>), grid, dim3(256), 0, st, R, G1, G2, idx, A, dS, Out, s.S, \
+  hipLaunchKernelGGL((attn_row_kernel<DH, LPL_, BWD>), grid, dim3(256), 0, st, R, G1, G2, idx, A, dS, maxes, Out, s.S, \
                      s.n, s.L, s.scale)
   switch (lpl) {
     case 1: SPT_ROW(1); break;
@@ -1206,21 +1239,11 @@ template <int DH, bool BWD>
 void launch_seq_dots(const spt_mha_shape_t& s, const uint16_t* R, const uint16_t* G1, const int32_t* idx,
                      const float* Ain, float* Wout, hipStream_t st) {
   const size_t lds = seq_lds_bytes(s.n, DH);
-  const int lpl = (s.L + 63) / 64;
-#define SPT_DOTS(LPL_)                                                                                      \
-  do {                                                                                                      \
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(seq_dots_kernel<DH, LPL_, BWD>),                \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                        \
-    hipLaunchKernelGGL((seq_dots_kernel<DH, LPL_, BWD>), dim3(s.S), dim3(kSeqThreads), lds, st, R, G1, idx, \
-                       Ain, Wout, s.n, s.L, s.scale);                                                       \
-  } while (0)
-  switch (lpl) {
-    case 1: SPT_DOTS(1); break;
-    case 2: SPT_DOTS(2); break;
-    case 3: SPT_DOTS(3); break;
-    default: SPT_DOTS(4); break;
-  }
-#undef SPT_DOTS
+  static_assert(kDenseRowsKeys <= 32 * 64, "lists longer than 64 entries take the dense tiles");
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(seq_dots_kernel<DH, 1, BWD>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((seq_dots_kernel<DH, 1, BWD>), dim3(s.S), dim3(kSeqThreads), lds, st, R, G1, idx, Ain, Wout, s.n,
+                     s.L, s.scale);
 }
 
 template <int DH, bool kKeys>
@@ -1277,17 +1300,24 @@ int spt_mha_topl(const spt_mha_shape_t* shape, const uint8_t* cq, const uint8_t*
     return SPT_ERR_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
   ScopedKernelTimer tm(kSlotMhaTopl, st);
-  // One lane per query when the inverted table and the row staging fit LDS (up to 8 wavefronts per
-  // workgroup share a table; as many as still let two workgroups share a CU); otherwise one
-  // wavefront per query.
+  // One lane per query when the inverted table and the row staging fit LDS, otherwise one wavefront per query.  The
+  // wavefronts of a workgroup (up to 8) share a table; LDS is what limits how many run on a CU, and the kernel is bound
+  // by the latency of its table reads, so the count is the one that gives the most of them with work (the last
+  // workgroup of a sequence may be half empty) -- two workgroups rather than one of twice the size.  (us, when workgroups that do not fit twice had one wavefront: n 2048, 64 sequences,
+  // 16 codebooks, L 128: 500; 8 codebooks, L 250: 495.)
   const size_t table_bytes = (size_t)shape->M * 16 * ((shape->n + 31) / 32 + 1) * sizeof(uint32_t);
   const size_t stage_bytes = (size_t)64 * (shape->L + 2) * sizeof(uint16_t);
   int waves = 0;
-  for (int cand = 8; cand >= 1 && !waves; cand >>= 1)
-    if (2 * (table_bytes + cand * stage_bytes) <= kLdsLimit || cand == 1)
-      if (table_bytes + cand * stage_bytes <= kLdsLimit) waves = cand;
+  double most = 0.0;
+  for (int cand = 8; cand >= 1; --cand) {
+    if (cand > 1 && (cand - 1) * 64 >= shape->n) continue;   // short sequences: no idle wavefronts
+    const int groups = (int)(kLdsLimit / (table_bytes + cand * stage_bytes));
+    const int running = cand * groups < 16 ? cand * groups : 16;
+    const int slots = (shape->n + cand * 64 - 1) / (cand * 64) * cand;   // wavefronts started for a sequence's queries
+    const double busy = (double)running * shape->n / (64.0 * slots);
+    if (busy > most || (busy == most && groups > 1 && waves == running)) { most = busy; waves = cand; }
+  }
   if (waves) {
-    while (waves > 1 && (waves / 2) * 64 >= shape->n) waves >>= 1;   // short sequences: no idle wavefronts
     const size_t lds = table_bytes + waves * stage_bytes;
     const dim3 grid((shape->n + waves * 64 - 1) / (waves * 64), shape->S);
     if (shape->M == 8) {
@@ -1324,8 +1354,8 @@ int spt_mha_attn_fwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
   {
     ScopedKernelTimer tm(kSlotMhaFwd, st);
     uint16_t* y = static_cast<uint16_t*>(Y);
-    if (use_dense(*shape)) return mha_dense_fwd(*shape, Q, K, V, idx, A, Y, st) == hipSuccess ? SPT_OK : SPT_ERR_HIP;
-    if (seq_resident(shape->n, shape->dh)) {
+    if (use_dense_rows(*shape)) return mha_dense_fwd(*shape, Q, K, V, idx, A, Y, st) == hipSuccess ? SPT_OK : SPT_ERR_HIP;
+    if (rows_in_lds(*shape)) {
       if (shape->dh == 64) {
         launch_seq_dots<64, false>(*shape, q, k, idx, nullptr, A, st);
         launch_seq_accum<64, false>(*shape, v, idx, nullptr, nullptr, A, y, st);
@@ -1334,9 +1364,9 @@ int spt_mha_attn_fwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
         launch_seq_accum<128, false>(*shape, v, idx, nullptr, nullptr, A, y, st);
       }
     } else if (shape->dh == 64) {
-      launch_row<64, false>(*shape, q, k, v, idx, A, nullptr, y, st);
+      launch_row<64, false>(*shape, q, k, v, idx, A, nullptr, nullptr, y, st);
     } else {
-      launch_row<128, false>(*shape, q, k, v, idx, A, nullptr, y, st);
+      launch_row<128, false>(*shape, q, k, v, idx, A, nullptr, nullptr, y, st);
     }
   }
   return hipGetLastError() == hipSuccess ? SPT_OK : SPT_ERR_HIP;
@@ -1357,23 +1387,15 @@ int spt_mha_attn_bwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
   const uint16_t* k = static_cast<const uint16_t*>(K);
   const uint16_t* v = static_cast<const uint16_t*>(V);
   const uint16_t* dy = static_cast<const uint16_t*>(dY);
-  if (w.maxes) {
-    hipError_t e;
-    {
-      ScopedKernelTimer tm(kSlotMhaBwdQ, st);
-      e = mha_dense_bwd_q(*shape, K, V, dY, idx, A, w.dS, w.maxes, dQ, st);
-    }
-    if (e != hipSuccess) return SPT_ERR_HIP;
-    ScopedKernelTimer tm(kSlotMhaBwdKV, st);
-    e = mha_dense_bwd_kv(*shape, Q, dY, idx, A, w.dS, w.maxes, dK, dV, st);
-    return e == hipSuccess ? SPT_OK : SPT_ERR_HIP;
-  }
   float* Amut = const_cast<float*>(A);   // read-only in the backward instantiation
   const bool resident = seq_resident(shape->n, shape->dh);
-  {
+  if (use_dense_rows(*shape)) {
+    ScopedKernelTimer tm(kSlotMhaBwdQ, st);
+    if (mha_dense_bwd_q(*shape, K, V, dY, idx, A, w.dS, w.maxes, dQ, st) != hipSuccess) return SPT_ERR_HIP;
+  } else {
     ScopedKernelTimer tm(kSlotMhaBwdQ, st);
     uint16_t* dq = static_cast<uint16_t*>(dQ);
-    if (resident) {
+    if (rows_in_lds(*shape)) {
       if (shape->dh == 64) {
         launch_seq_dots<64, true>(*shape, dy, v, idx, A, w.dS, st);
         launch_seq_accum<64, false>(*shape, k, idx, nullptr, nullptr, w.dS, dq, st);
@@ -1382,10 +1404,14 @@ int spt_mha_attn_bwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
         launch_seq_accum<128, false>(*shape, k, idx, nullptr, nullptr, w.dS, dq, st);
       }
     } else if (shape->dh == 64) {
-      launch_row<64, true>(*shape, dy, v, k, idx, Amut, w.dS, dq, st);
+      launch_row<64, true>(*shape, dy, v, k, idx, Amut, w.dS, w.maxes, dq, st);
     } else {
-      launch_row<128, true>(*shape, dy, v, k, idx, Amut, w.dS, dq, st);
+      launch_row<128, true>(*shape, dy, v, k, idx, Amut, w.dS, w.maxes, dq, st);
     }
+  }
+  if (w.maxes) {
+    ScopedKernelTimer tm(kSlotMhaBwdKV, st);
+    return mha_dense_bwd_kv(*shape, Q, dY, idx, A, w.dS, w.maxes, dK, dV, st) == hipSuccess ? SPT_OK : SPT_ERR_HIP;
   }
   {
     ScopedKernelTimer tm(kSlotMhaTranspose, st);

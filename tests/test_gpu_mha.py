@@ -124,10 +124,10 @@ def test_whole_path_matches_oracle(sh):
 
 # Dense-tile kernels: edges of the 32-key tiles, 256- and 512-key chunks and 32-query blocks, list
 # lengths around the four-entry vectors and the 64-entry steps; and, where few keys of many are
-# kept, the gathering kernels (resident, and too large for LDS).
+# kept, the gathering kernels (resident, and too large for LDS); beyond 512 keys either kind on the query side.
 EDGES = [(n, dh, L) for dh in (64, 128) for n, L in
          ((31, 4), (33, 5), (96, 33), (255, 63), (256, 64), (257, 65), (511, 67), (512, 129), (513, 130), (770, 255),
-          (1025, 256), (600, 9), (1030, 3))]
+          (1025, 256), (600, 9), (1030, 3), (513, 17), (770, 65), (1023, 110), (1023, 134))]
 
 
 @pytest.mark.parametrize("n,dh,L", EDGES)
