@@ -151,3 +151,12 @@ def test_lora_full_size_7b_like_parity():
     """The benchmark configuration, rank 16 (the paper's default adapter rank): every output of
     the forward and backward compared in full (the oracle takes about a minute on 16 cores)."""
     check_full(gen.PRESETS["ffn_7b"], 16, std=0.02)
+
+
+# Pieces and chunks of the gradient contractions (128 rows and more, an empty bucket), the split block list with a
+# low-rank row to add, the extra stage of the 256-row tiles, halves and quarters of the wide ones.
+@pytest.mark.parametrize("dims", [(129, 192, 12, 64, 1, 3), (24, 256, 64, 64, 16, 4), (900, 192, 128, 96, 16, 7),
+                                  (5000, 320, 2, 288, 2, 8)], ids=str)
+def test_lora_launch_edges(dims):
+    T, d, N, Bs, k, r = dims
+    check_full(gen.custom_shape(T, d, N, Bs, k, seed=T + N + r, w_std=0.05, wr_std=0.05), r, std=0.1)

@@ -429,3 +429,21 @@ def test_routing_and_bucketing_launch_edges(T, d, N, k, flags):
     idx2 = spt.router_topk(dv.shape, dv.X, dv.W_r, dv.b_r)      # logits in the workspace: other kernels, same ids
     assert torch.equal(idx, idx2), tag
     check_bucket(dv, idx, g_idx, tag)
+
+
+# Feed-forward kernels at the edges of their launch rules.
+@pytest.mark.parametrize("dims", [
+    # (T, d, N, Bs, k).  Up-projection of decoding batches: one row tile up to 24 rows a bucket, two beyond, 40 and 64
+    # rows as the last ones, 64-row tiles after that; block list of the K = Bs kernel split over workgroups
+    (1, 256, 40, 128, 3), (64, 192, 8, 64, 3), (65, 192, 8, 64, 3), (256, 64, 8, 96, 2), (257, 64, 8, 96, 2),
+    (24, 1024, 64, 128, 16), (33, 320, 128, 32, 40),
+    # 64-row tiles at 127 buckets, 256-row ones from 128; one, two, three stages of 64 values in rings of three and four
+    (700, 64, 127, 32, 16), (700, 64, 128, 32, 16), (700, 128, 128, 96, 16), (700, 192, 130, 64, 16), (1100, 320, 64, 128, 24),
+    # schedule by one workgroup up to 8192 pairs
+    (1024, 64, 40, 32, 8), (2731, 64, 40, 32, 3),
+    # wide blocks, items left over per XCD: as quarters, as halves, as whole tiles, after a full round
+    (1300, 192, 2, 288, 2), (5000, 320, 2, 288, 2), (5000, 64, 2, 1056, 2), (5000, 64, 2, 1696, 2),
+], ids=str)
+def test_ffn_launch_edges(dims):
+    T, d, N, Bs, k = dims
+    full_parity(gen.custom_shape(T, d, N, Bs, k, seed=T + N, w_std=0.05, wr_std=0.05), f"edges {dims}")
