@@ -495,10 +495,11 @@ __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restric
       if (lane == 0) wmax[wave] = make_float2(ma, mw);
     }
   }
-  // Weighted sum of the gathered rows.
+  // Weighted sum of the gathered rows.  (Entries without a key add zeros: the row read in their place may hold
+  // infinities or NaN, which a weight of zero would not take away.)
 #pragma unroll
   for (int cc = 0; cc < LPL; ++cc) {
-    if (jj[cc] < 0) { jj[cc] = 0; w[cc] = 0.f; }
+    if (jj[cc] < 0) w[cc] = 0.f;
   }
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -512,7 +513,8 @@ __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restric
         for (int u = 0; u < 4; ++u) {
           we[u] = __shfl(w[cc], (i0 + u) * G + g);
           const int je = __shfl(jj[cc], (i0 + u) * G + g);
-          row[u] = *reinterpret_cast<const u32x4*>(g2 + (size_t)je * DH);
+          row[u] = *reinterpret_cast<const u32x4*>(g2 + (size_t)max(je, 0) * DH);
+          if (je < 0) row[u] = u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) fma8(acc, we[u], row[u]);
@@ -739,7 +741,7 @@ __global__ __launch_bounds__(256) void attn_kv_kernel(const uint16_t* __restrict
     }
 #pragma unroll
     for (int i0 = 0; i0 < LPR; i0 += 4) {
-      if (i0 * G < cnt) {                // uniform; lanes past cnt carry zero weights and query 0
+      if (i0 * G < cnt) {                // uniform; past cnt: zero weights and rows of zeros
         u32x4 yr[4], qr[4];
         float wa[4], wd[4];
 #pragma unroll
@@ -750,6 +752,7 @@ __global__ __launch_bounds__(256) void attn_kv_kernel(const uint16_t* __restrict
           wd[u] = __shfl(ds, src);
           yr[u] = *reinterpret_cast<const u32x4*>(ys + (size_t)qe * DH);
           qr[u] = *reinterpret_cast<const u32x4*>(qs + (size_t)qe * DH);
+          if (src >= cnt) yr[u] = qr[u] = u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
