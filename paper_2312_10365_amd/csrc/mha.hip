@@ -391,24 +391,21 @@ __device__ __forceinline__ void fma8(float (&acc)[8], float w, const u32x4& row)
 //   w_l = softmax_l(scale * R[v] . G1[idx_l]),  Out[v] = sum_l w_l G2[idx_l],  A <- w.
 // With (R, G1, G2) = (dY, V, K) it is the query side of the backward pass:
 //   dA_l = R[v] . G1[idx_l],  w_l = A_l (dA_l - sum_m A_m dA_m) scale,  Out[v] = sum_l w_l G2[idx_l],
-// and w is kept (dS) for the key side, with (maxes given) the largest |A| and |dS| of the workgroup's four queries,
-// which the dense key side scales by.  Entry l lives on lane l % 64 for the softmax; for the row
-// work lane = (g, c): group g handles entry step * G + g, c is the 16-byte piece of the row.
+// and w is kept (dS) for the key side.  Entry l lives on lane l % 64 for the softmax; for the row work lane = (g, c): group g handles entry step * G + g, c is the 16-byte piece of the row.
 template <int DH, int LPL, bool BWD>
 __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restrict__ R,
                                                        const uint16_t* __restrict__ G1,
                                                        const uint16_t* __restrict__ G2,
                                                        const int32_t* __restrict__ idx,
                                                        float* __restrict__ A, float* __restrict__ dS,
-                                                       float2* __restrict__ maxes,
                                                        uint16_t* __restrict__ Out, int S, int n, int L,
                                                        float scale) {
   constexpr int LPR = RowMap<DH>::LPR, G = RowMap<DH>::G;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int s, blk;
   if (!seq_block((n + 3) >> 2, S, s, blk)) return;
-  __shared__ float2 wmax[4];
-  const int i = min(blk * 4 + wave, n - 1);   // (past the end: the last query again, same values to the same place)
+  const int i = blk * 4 + wave;
+  if (i >= n) return;
   const size_t v = (size_t)s * n + i;
   const int g = lane / LPR, c = lane % LPR;
   const uint16_t* g1 = G1 + (size_t)s * n * DH + c * 8;
@@ -483,17 +480,6 @@ __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restric
       w[cc] = a[cc] * (w[cc] - dotsum) * scale;
       if (l < L) dS[v * L + l] = w[cc];
     }
-    if (maxes) {   // (uniform)
-      float ma = 0.f, mw = 0.f;
-#pragma unroll
-      for (int cc = 0; cc < LPL; ++cc) {
-        ma = fmaxf(ma, fabsf(a[cc]));
-        mw = fmaxf(mw, cc * 64 + lane < L ? fabsf(w[cc]) : 0.f);
-      }
-      ma = wave_max(ma);
-      mw = wave_max(mw);
-      if (lane == 0) wmax[wave] = make_float2(ma, mw);
-    }
   }
   // Weighted sum of the gathered rows.  (Entries without a key add zeros: the row read in their place may hold
   // infinities or NaN, which a weight of zero would not take away.)
@@ -531,13 +517,6 @@ __global__ __launch_bounds__(256) void attn_row_kernel(const uint16_t* __restric
 #pragma unroll
     for (int e = 0; e < 4; ++e) o4[e] = pack_bf16x2(acc[2 * e], acc[2 * e + 1]);
     *reinterpret_cast<u32x4*>(Out + v * DH + c * 8) = o4;
-  }
-  if (BWD && maxes) {
-    __syncthreads();
-    if (threadIdx.x == 0)
-      maxes[(size_t)s * ((n + 3) >> 2) + blk] =
-          make_float2(fmaxf(fmaxf(wmax[0].x, wmax[1].x), fmaxf(wmax[2].x, wmax[3].x)),
-                      fmaxf(fmaxf(wmax[0].y, wmax[1].y), fmaxf(wmax[2].y, wmax[3].y)));
   }
 }
 
@@ -1183,7 +1162,6 @@ bool rows_in_lds(const spt_mha_shape_t& s) { return s.n <= kDenseRowsKeys; }
 
 struct MhaWorkspace {
   float* dS;          // [S][n][L]
-  float2* maxes;      // dense tiles: [S][ceil(n/4)] largest |A|, |dS| of four queries
   int32_t* toff;      // [S][n + 1]
   uint32_t* tlist;    // [S][n * L]
   uint32_t* gbits;    // [S][n][ceil(n/32)] when the transposition does not fit LDS, else null
@@ -1208,9 +1186,8 @@ MhaWorkspace plan_mha(const spt_mha_shape_t& s, void* ws) {
   w.gbits = nullptr;
   w.toff = reinterpret_cast<int32_t*>(p + off);    off += align256((size_t)s.S * (s.n + 1) * sizeof(int32_t));
   w.tlist = reinterpret_cast<uint32_t*>(p + off);  off += align256(rows * s.L * sizeof(uint32_t));
-  // (the dense tiles need no transposition; their maxima take its place)
-  w.maxes = use_dense(s) ? reinterpret_cast<float2*>(w.tlist) : nullptr;
-  if (!w.maxes && !transpose_fits_lds(s.n, s.L)) {
+  // (the dense tiles need no transposition and leave its lists unused)
+  if (!use_dense(s) && !transpose_fits_lds(s.n, s.L)) {
     w.gbits = reinterpret_cast<uint32_t*>(p + off);
     off += align256(rows * ((s.n + 31) / 32) * sizeof(uint32_t));
   }
@@ -1223,12 +1200,12 @@ bool aligned4(const void* p) { return p && (reinterpret_cast<uintptr_t>(p) & 3) 
 
 template <int DH, bool BWD>
 void launch_row(const spt_mha_shape_t& s, const uint16_t* R, const uint16_t* G1, const uint16_t* G2,
-                const int32_t* idx, float* A, float* dS, float2* maxes, uint16_t* Out, hipStream_t st) {
+                const int32_t* idx, float* A, float* dS, uint16_t* Out, hipStream_t st) {
   const dim3 grid(seq_block_grid((s.n + 3) / 4, s.S));
   const int lpl = (s.L + 63) / 64;
 #define SPT_ROW(LPL_) \
-  hipLaunchKernelGGL((attn_row_kernel<DH, LPL_, BWD>), grid, dim3(256), 0, st, R, G1, G2, idx, A, dS, maxes, Out, s.S, \
-                     s.n, s.L, s.scale)
+  hipLaunchKernelGGL((attn_row_kernel<DH, LPL_, BWD>), grid, dim3(256), 0, st, R, G1, G2, idx, A, dS, Out, s.S, s.n, \
+                     s.L, s.scale)
   switch (lpl) {
     case 1: SPT_ROW(1); break;
     case 2: SPT_ROW(2); break;
@@ -1367,9 +1344,9 @@ int spt_mha_attn_fwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
         launch_seq_accum<128, false>(*shape, v, idx, nullptr, nullptr, A, y, st);
       }
     } else if (shape->dh == 64) {
-      launch_row<64, false>(*shape, q, k, v, idx, A, nullptr, nullptr, y, st);
+      launch_row<64, false>(*shape, q, k, v, idx, A, nullptr, y, st);
     } else {
-      launch_row<128, false>(*shape, q, k, v, idx, A, nullptr, nullptr, y, st);
+      launch_row<128, false>(*shape, q, k, v, idx, A, nullptr, y, st);
     }
   }
   return hipGetLastError() == hipSuccess ? SPT_OK : SPT_ERR_HIP;
@@ -1394,7 +1371,7 @@ int spt_mha_attn_bwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
   const bool resident = seq_resident(shape->n, shape->dh);
   if (use_dense_rows(*shape)) {
     ScopedKernelTimer tm(kSlotMhaBwdQ, st);
-    if (mha_dense_bwd_q(*shape, K, V, dY, idx, A, w.dS, w.maxes, dQ, st) != hipSuccess) return SPT_ERR_HIP;
+    if (mha_dense_bwd_q(*shape, K, V, dY, idx, A, w.dS, dQ, st) != hipSuccess) return SPT_ERR_HIP;
   } else {
     ScopedKernelTimer tm(kSlotMhaBwdQ, st);
     uint16_t* dq = static_cast<uint16_t*>(dQ);
@@ -1407,14 +1384,14 @@ int spt_mha_attn_bwd(const spt_mha_shape_t* shape, const void* Q, const void* K,
         launch_seq_accum<128, false>(*shape, k, idx, nullptr, nullptr, w.dS, dq, st);
       }
     } else if (shape->dh == 64) {
-      launch_row<64, true>(*shape, dy, v, k, idx, Amut, w.dS, w.maxes, dq, st);
+      launch_row<64, true>(*shape, dy, v, k, idx, Amut, w.dS, dq, st);
     } else {
-      launch_row<128, true>(*shape, dy, v, k, idx, Amut, w.dS, w.maxes, dq, st);
+      launch_row<128, true>(*shape, dy, v, k, idx, Amut, w.dS, dq, st);
     }
   }
-  if (w.maxes) {
+  if (use_dense(*shape)) {
     ScopedKernelTimer tm(kSlotMhaBwdKV, st);
-    return mha_dense_bwd_kv(*shape, Q, dY, idx, A, w.dS, w.maxes, dK, dV, st) == hipSuccess ? SPT_OK : SPT_ERR_HIP;
+    return mha_dense_bwd_kv(*shape, Q, dY, idx, A, w.dS, dK, dV, st) == hipSuccess ? SPT_OK : SPT_ERR_HIP;
   }
   {
     ScopedKernelTimer tm(kSlotMhaTranspose, st);

@@ -1,4 +1,5 @@
-"""Attention where the values leave the ordinary range: outliers, infinities and NaN.  Against the fp64 oracle, given the A that the kernel stored, row by row: a row of a result may
+"""Attention where the values leave the ordinary range: a saturated softmax, magnitudes far apart inside a sequence,
+infinities and NaN.  Against the fp64 oracle, given the A that the kernel stored, row by row: a row of a result may
 depend on what it is summed from and on nothing else of its sequence.  The oracle walks kept entries only, so its
 infinities and NaN are where IEEE arithmetic puts them.  Tolerance: outputs are bf16 (2^-9 per value), sums fp32."""
 import numpy as np
@@ -11,8 +12,9 @@ from paper_2312_10365_amd.inputs import bf16_bits_to_f32, f32_to_bf16_bits
 pytestmark = pytest.mark.gpu
 ROW_TOL = 1e-2
 
-# (n, dh, L): the gathering kernels that read their rows from L2
-SHAPES = [(700, 128, 20), (1100, 64, 30)]
+# (n, dh, L): one chunk of up to 256 and up to 512 keys, several, and (L = 40) rows gathered in front of dense keys
+SHAPES = [(70, 64, 20), (70, 128, 20), (300, 64, 70), (300, 128, 70), (700, 64, 140), (700, 128, 140), (700, 64, 40),
+          (700, 128, 40)]
 
 
 def bf16(x):
@@ -70,6 +72,39 @@ def check_rows(name, got, ref):
 def check_all(A, A_ref, got, ref):
     for name in got:
         check_rows(name, got[name], ref[name])
+
+
+@pytest.mark.parametrize("n,dh,L", SHAPES)
+def test_saturated_softmax(n, dh, L):
+    """The top key leads the second by 70 to 90 nats: A = 1 and dS = 0 for it, 1e-30 to 1e-38 for the others.  (The
+    unscaled softmax; the oracle's own A would differ below fp32's range, so Y alone is checked with it.)"""
+    rng, t, idx = make(n, dh, L, 41)
+    S = idx.shape[0]
+    for s in range(S):
+        k = t["K"][s]
+        top = idx[s][np.arange(n), rng.integers(0, L, n)]
+        dots = np.take_along_axis(k[top] @ k.T, idx[s], axis=1)
+        own = (k[top] ** 2).sum(-1)
+        second = np.where(idx[s] == top[:, None], -np.inf, dots).max(-1)
+        t["Q"][s] = bf16((rng.uniform(70, 90, n) / (own - second))[:, None] * k[top])
+    A, A_ref, got, ref = run(t, idx, 1.0)
+    assert (A.max(-1) == 1.0).all() and np.isfinite(got["dQ"]).all()
+    check_all(A, A_ref, got, ref)
+
+
+@pytest.mark.parametrize("n,dh,L", SHAPES)
+def test_magnitudes_far_apart(n, dh, L):
+    """The first half of the queries keeps the first half of the keys, and the second half the second, with everything
+    that the second half is summed from 2^-35 (V, K, Q) and 2^-40 (dY) times as large."""
+    rng, t, idx = make(n, dh, L, 43)
+    half = n // 2
+    for s in range(idx.shape[0]):
+        for i in range(n):
+            pool = np.arange(half) if i < half else np.arange(half, n)
+            idx[s, i] = np.sort(rng.permutation(pool)[:L]) if L <= len(pool) else -1
+    for x, e in (("Q", -35), ("K", -35), ("V", -35), ("dY", -40)):
+        t[x][:, half:] = bf16(t[x][:, half:] * np.float32(2.0) ** e)
+    check_all(*run(t, idx, dh ** -0.5))
 
 
 @pytest.mark.parametrize("n,dh,L", SHAPES)
