@@ -653,86 +653,95 @@ __global__ __launch_bounds__(512, 2) void ffn_up_pair_kernel(
 // ------------------------------------------------------------------------------------------
 // The same forward GEMM where a bucket holds a handful of rows (decoding batches): every weight is read
 // for few multiply-adds, so the launch is bound by streaming W1 and wants bytes in flight on all CUs, not
-// tiles.  A workgroup owns 32 hidden units of one block and 32 RT bucket rows at a time; its four
+// tiles.  A workgroup owns 32 hidden units of one block and one row tile of its bucket, 32 RT rows at a time; its four
 // wavefronts split d in chunks of 32 and load both operands straight into registers, chunks ahead
 // (a lane reads 32 contiguous bytes of a row; which K-values share an MFMA slot is the same for both
 // operands, which is all a contraction needs).  The wavefronts' sums are added through LDS in order.
-// 7B-like layer, 24 tokens (6 rows a bucket): 41 us, with 256-row tiles 69 (128 of 256 CUs, one K-stage per
+// 7B-like layer, 24 tokens (6 rows a bucket): 32 us, with 256-row tiles 69 (128 of 256 CUs, one K-stage per
 // memory latency).
+// The row tiles come from the schedule's lists, as those of the tile kernels do: the mean says little about a single
+// bucket.  8192 tokens, 256 blocks of 128 units, d 2048, k 1, half of the tokens in one block: 220 us, with a
+// workgroup per bucket and 32 units 2834.
 template <int ACT, int RT>
 __global__ __launch_bounds__(256) void ffn_up_few_rows_kernel(
     const uint16_t* __restrict__ W1, const uint16_t* __restrict__ X, const int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ kd_count, const KdTile* __restrict__ kd_list, int cap, int tile_rows,
     const int32_t* __restrict__ tok, int Bs, int d, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact) {
   constexpr int DEPTH = 4;                       // chunks in registers, DEPTH - 1 of them in flight (8: no faster)
   __shared__ float red[4][RT][16][64];
-  const int b = blockIdx.x, u0 = blockIdx.y * 32;
-  const int qb = offsets[b], qe = offsets[b + 1];
+  // (the unit slices of a tile side by side; workgroups that find the list at its end are the last ones handed out)
+  const int slices = Bs / 32, xcd = blockIdx.x & 7, per_xcd = (int)(gridDim.x >> 3) / slices, count = kd_count[xcd];
+  const int u0 = (int)(blockIdx.x >> 3) % slices * 32;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = lane & 31, h = lane >> 5;
   const int chunks = d / 32, cbeg = wave * chunks / 4, cend = (wave + 1) * chunks / 4, clast = cend - 1;
-  const uint16_t* wrow = W1 + ((size_t)b * Bs + u0 + rho32(i)) * d + 16 * h;
-  for (int q0 = qb; q0 < qe; q0 += 32 * RT) {
-    const uint16_t* xrow[RT];
+  for (int slot = (int)(blockIdx.x >> 3) / slices; slot < count; slot += per_xcd) {
+    const KdTile tile = kd_list[(size_t)xcd * cap + slot];
+    const int qe = min(tile.q0 + tile_rows, offsets[tile.bucket + 1]);
+    const uint16_t* wrow = W1 + ((size_t)tile.bucket * Bs + u0 + rho32(i)) * d + 16 * h;
+    for (int q0 = tile.q0; q0 < qe; q0 += 32 * RT) {
+      const uint16_t* xrow[RT];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) xrow[rt] = X + (size_t)tok[min(q0 + rt * 32 + i, qe - 1)] * d + 16 * h;
-    f32x16 acc[RT];
+      for (int rt = 0; rt < RT; ++rt) xrow[rt] = X + (size_t)tok[min(q0 + rt * 32 + i, qe - 1)] * d + 16 * h;
+      f32x16 acc[RT];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
-    uint4 wq[DEPTH][2], xq[DEPTH][RT][2];
-    auto fetch = [&](int st, int c) {
-      const int k0 = min(c, clast) * 32;       // (requests past the last chunk repeat it: no branch around a load)
+        for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
+      uint4 wq[DEPTH][2], xq[DEPTH][RT][2];
+      auto fetch = [&](int st, int c) {
+        const int k0 = min(c, clast) * 32;       // (requests past the last chunk repeat it: no branch around a load)
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        wq[st][s] = *reinterpret_cast<const uint4*>(wrow + k0 + 8 * s);
+        for (int s = 0; s < 2; ++s) {
+          wq[st][s] = *reinterpret_cast<const uint4*>(wrow + k0 + 8 * s);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) xq[st][rt][s] = *reinterpret_cast<const uint4*>(xrow[rt] + k0 + 8 * s);
+          for (int rt = 0; rt < RT; ++rt) xq[st][rt][s] = *reinterpret_cast<const uint4*>(xrow[rt] + k0 + 8 * s);
+        }
+      };
+      auto consume = [&](int st) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+            acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wq[st][s]), as_bf16x8(xq[st][rt][s]), acc[rt], 0, 0, 0);
+      };
+      if (cbeg < cend) {
+#pragma unroll
+        for (int s = 0; s < DEPTH - 1; ++s) fetch(s, cbeg + s);
+        int c = cbeg;
+        for (; c + DEPTH <= cend; c += DEPTH) {
+#pragma unroll
+          for (int s = 0; s < DEPTH; ++s) {
+            fetch((s + DEPTH - 1) % DEPTH, c + s + DEPTH - 1);
+            consume(s);
+          }
+        }
+#pragma unroll
+        for (int s = 0; s < DEPTH - 1; ++s)
+          if (c + s < cend) consume(s);
       }
-    };
-    auto consume = [&](int st) {
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
+      for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wq[st][s]), as_bf16x8(xq[st][rt][s]), acc[rt], 0, 0, 0);
-    };
-    if (cbeg < cend) {
+        for (int v = 0; v < 16; ++v) red[wave][rt][v][lane] = acc[rt][v];
+      __syncthreads();
+      // wavefront w finishes accumulators 4 w .. 4 w + 3: hidden units u0 + 16 h + 4 w .. + 3 of the lane's row
 #pragma unroll
-      for (int s = 0; s < DEPTH - 1; ++s) fetch(s, cbeg + s);
-      int c = cbeg;
-      for (; c + DEPTH <= cend; c += DEPTH) {
+      for (int rt = 0; rt < RT; ++rt) {
+        const int q = q0 + rt * 32 + i, u = u0 + 16 * h + 4 * wave;
+        float z[4];
 #pragma unroll
-        for (int s = 0; s < DEPTH; ++s) {
-          fetch((s + DEPTH - 1) % DEPTH, c + s + DEPTH - 1);
-          consume(s);
+        for (int e = 0; e < 4; ++e)
+          z[e] = ((red[0][rt][4 * wave + e][lane] + red[1][rt][4 * wave + e][lane]) + red[2][rt][4 * wave + e][lane]) +
+                 red[3][rt][4 * wave + e][lane];
+        if (q < qe) {
+          if (Hsave) *reinterpret_cast<uint2*>(Hsave + (size_t)q * Bs + u) = make_uint2(pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3]));
+          *reinterpret_cast<uint2*>(Hact + hfrag_off(q, u, Bs)) =
+              make_uint2(pack_bf16x2(act_fn<ACT>(z[0]), act_fn<ACT>(z[1])), pack_bf16x2(act_fn<ACT>(z[2]), act_fn<ACT>(z[3])));
         }
       }
-#pragma unroll
-      for (int s = 0; s < DEPTH - 1; ++s)
-        if (c + s < cend) consume(s);
+      __syncthreads();
     }
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) red[wave][rt][v][lane] = acc[rt][v];
-    __syncthreads();
-    // wavefront w finishes accumulators 4 w .. 4 w + 3: hidden units u0 + 16 h + 4 w .. + 3 of the lane's row
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const int q = q0 + rt * 32 + i, u = u0 + 16 * h + 4 * wave;
-      float z[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        z[e] = ((red[0][rt][4 * wave + e][lane] + red[1][rt][4 * wave + e][lane]) + red[2][rt][4 * wave + e][lane]) +
-               red[3][rt][4 * wave + e][lane];
-      if (q < qe) {
-        if (Hsave) *reinterpret_cast<uint2*>(Hsave + (size_t)q * Bs + u) = make_uint2(pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3]));
-        *reinterpret_cast<uint2*>(Hact + hfrag_off(q, u, Bs)) =
-            make_uint2(pack_bf16x2(act_fn<ACT>(z[0]), act_fn<ACT>(z[1])), pack_bf16x2(act_fn<ACT>(z[2]), act_fn<ACT>(z[3])));
-      }
-    }
-    __syncthreads();
   }
 }
 
@@ -1252,9 +1261,10 @@ static hipError_t launch_up_t(const spt_shape_t& s, const uint16_t* Wa, const ui
 // The forward GEMM of a batch with few rows per bucket (see ffn_up_few_rows_kernel).
 static hipError_t launch_up_few_rows(const spt_shape_t& s, const uint16_t* W1, const uint16_t* X, const int32_t* offsets,
                                      const Schedule& sc, uint16_t* Hsave, uint16_t* Hact, hipStream_t st) {
-  const dim3 grid(s.N, s.Bs / 32);
+  const int rows = kd_rows(s);
+  const int grid = (max_row_tiles(s, rows) + 7) / 8 * 8 * (s.Bs / 32);   // (an XCD with more tiles than its share takes more rounds)
   const bool one = (int64_t)s.T * s.k <= (int64_t)24 * s.N;
-#define SPT_FEW(ACT, RT) ffn_up_few_rows_kernel<ACT, RT><<<grid, 256, 0, st>>>(W1, X, offsets, sc.tok, s.Bs, s.d, Hsave, Hact)
+#define SPT_FEW(ACT, RT) ffn_up_few_rows_kernel<ACT, RT><<<grid, 256, 0, st>>>(W1, X, offsets, sc.kd_count, static_cast<const KdTile*>(sc.kd_list), sc.kd_cap, rows, sc.tok, s.Bs, s.d, Hsave, Hact)
   if (s.act == SPT_ACT_GELU) { if (one) SPT_FEW(0, 1); else SPT_FEW(0, 2); }
   else                       { if (one) SPT_FEW(1, 1); else SPT_FEW(1, 2); }
 #undef SPT_FEW

@@ -447,3 +447,15 @@ def test_routing_and_bucketing_launch_edges(T, d, N, k, flags):
 def test_ffn_launch_edges(dims):
     T, d, N, Bs, k = dims
     full_parity(gen.custom_shape(T, d, N, Bs, k, seed=T + N, w_std=0.05, wr_std=0.05), f"edges {dims}")
+
+
+@pytest.mark.parametrize("dims", [
+    # (T, d, N, Bs, k, rows of a tile): few rows a bucket on average, most of them in one bucket of several row tiles; one
+    # and two 32-row tiles at a time
+    (700, 64, 64, 96, 1, 64), (3000, 64, 100, 32, 1, 64), (2400, 64, 130, 32, 1, 256), (4500, 64, 130, 64, 1, 256),
+], ids=str)
+def test_few_rows_a_bucket_but_for_one(dims):
+    T, d, N, Bs, k, rows = dims
+    s = gen.custom_shape(T, d, N, Bs, k, seed=T + N, zipf_bias=True, w_std=0.05, wr_std=0.05)
+    _, (offsets, _, _), _ = full_parity(s, f"one large bucket {dims}")
+    assert np.diff(offsets.cpu().numpy()).max() > 2 * rows, "the case is meant to have a bucket of more than two row tiles"
