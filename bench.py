@@ -21,8 +21,8 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 
 
-def kernel_models(s):
-    """Per launch of each kernel slot: algorithmic FLOP; `bytes` = every tensor the kernel must
+def kernel_models(s, kernels=()):
+    """Per launch of each kernel slot (`kernels`: the slots that were timed): algorithmic FLOP; `bytes` = every tensor the kernel must
     read or write, once (bf16 = 2 B; the k-fold gathered re-reads of X / dY and the re-reads of
     weight slices are cache traffic by design and are NOT counted); `design_bytes` = `bytes`
     plus HBM traffic this design adds on top (the per-pair partial rows of the wide-block path)."""
@@ -43,6 +43,10 @@ def kernel_models(s):
         "combine_y": dict(bound="hbm", flops=0.0, bytes=act + P * 4, extra=part),
         "combine_dx": dict(bound="hbm", flops=0.0, bytes=act + P * 4, extra=part),
     }
+    if "dw2_gemm" in kernels and "dw1_gemm" not in kernels:
+        # narrow blocks, all but the largest layers: one launch makes both weight gradients, in this slot
+        for x in ("flops", "bytes"):
+            m["dw2_gemm"][x] += m["dw1_gemm"][x]
     for v in m.values():
         v["design_bytes"] = v["bytes"] + v.pop("extra", 0)
     return m
@@ -157,25 +161,17 @@ def bench_mha(args):
 
     row = rows * sh.dh * 2           # one [S, n, dh] bf16 tensor
     ent = rows * sh.L * 4            # one [S, n, L] 4-byte array
-    # Algorithmic HBM bytes per launch: every tensor a kernel must read or write, once.  The
-    # gathers themselves are served by the L2 (one sequence's K, V, Q, dY are 64-128 KiB each).
+    # Algorithmic HBM bytes per launch: every tensor a kernel must read or write, once.
     models = {
         "mha_pq_assign": row + rows * sh.M,
         "mha_topl": 2 * rows * sh.M + ent,
-        "mha_attn_fwd": 3 * row + ent + ent + row,
-        "mha_attn_bwd_q": 3 * row + 2 * ent + ent + row + rows * sh.L + rows * ((sh.n + 31) // 32) * 4,
-        "mha_attn_bwd_kv": 2 * row + 2 * ent + rows * sh.n + rows * ((sh.n + 31) // 32) * 4 + 2 * row,
-    }
-    gathered = {   # bytes the lanes actually pull through the cache hierarchy, per launch
-        "mha_attn_fwd": 2 * rows * sh.L * sh.dh * 2,
-        "mha_attn_bwd_q": 2 * rows * sh.L * sh.dh * 2,
-        "mha_attn_bwd_kv": 2 * rows * sh.L * sh.dh * 2,
+        "mha_attn_fwd": 3 * row + ent + ent + row,            # Q, K, V, idx -> A, Y
+        "mha_attn_bwd_q": 3 * row + 2 * ent + ent + row,      # dY, V, K, idx, A -> dS, dQ
+        "mha_attn_bwd_kv": 2 * row + 3 * ent + 2 * row,       # Q, dY, idx, A, dS -> dK, dV
     }
     for n, kd in kernels.items():
         if n in models:
             kd["algorithmic_gbs"] = models[n] / (kd["ms"] * 1e-3) / 1e9
-        if n in gathered:
-            kd["gathered_gbs"] = gathered[n] / (kd["ms"] * 1e-3) / 1e9
     traffic = None
     if os.path.exists(args.traffic_json):
         try:
@@ -186,7 +182,7 @@ def bench_mha(args):
     ach = models.get(dom, 0) / dur / 1e9
     roofline = {"kernel": dom, "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": ach / PEAK_HBM_GBS, "traffic": traffic, "avg_launch_ms": kernels[dom]["ms"],
-                "algorithmic_bytes": models.get(dom, 0), "gathered_bytes": gathered.get(dom)}
+                "algorithmic_bytes": models.get(dom, 0)}
     out = {
         "metric": "sparse multi-head attention fwd+bwd tokens/s (PQ assignment of Q and K, top-L selection, "
                   "sparse attention forward, backward; all heads) at 1 MI355X",
@@ -439,7 +435,7 @@ def main():
         kernels[dom] = dict(timed[dom], timed_region=True)
 
     tflops = run.flop / sec / 1e12
-    models = kernel_models(s)
+    models = kernel_models(s, kernels)
     m = models.get(dom)
     traffic = None
     if os.path.exists(args.traffic_json):

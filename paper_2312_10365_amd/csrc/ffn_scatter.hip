@@ -406,8 +406,9 @@ static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   // with its rows: slab accesses) plus a prologue and epilogue worth about six of them, and the chip runs
   // 256 workgroups at a time: of the range counts the LDS slab allows, down to 64 tokens per range, take
   // the one with the least record time in a row.  Rows of a range in a block are about Binomial(R, k / N), so a
-  // record count per block of 1 + P(rows > 128) + ...: at k / N = 1/4 432 tokens (108 rows) are near the best
-  // ratio, at 2/5 300 are (448 would need two records for almost every block).
+  // record count per block of 1 + P(rows > 128) + ...: at k / N = 1/4 about 430 tokens (108 rows) are the most that
+  // rarely need a second record, at 2/5 300 are (448 would need two for almost every block).  Both sides at the
+  // 7B-like layer, us a launch: 20 ranges of 410 tokens (five full rounds of workgroups) 592, 19 of 432 (4.75) 598.
   const double share = (double)s.k / s.N;
   const int nr_min = (s.T + rmax - 1) / rmax, nr_max = (s.T + 63) / 64 > nr_min ? (s.T + 63) / 64 : nr_min;
   double best = -1.0;
@@ -434,7 +435,7 @@ static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   return p;
 }
 
-// (The search over range counts takes tens of microseconds and every call of the path asks several times:
+// (The search over range counts takes 0.1 to 16 microseconds and every call of the path asks several times:
 // each thread keeps the plans of the last few shapes, which are functions of the shape alone.)
 ScatterPlan plan_scatter(const spt_shape_t& s) {
   struct Kept { int32_t T, d, N, Bs, k; ScatterPlan plan; };
