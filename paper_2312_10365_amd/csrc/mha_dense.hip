@@ -70,8 +70,12 @@ __device__ __forceinline__ u16x2 max_mag(u16x2 m, const u32x4& v) {
   return m;
 }
 __device__ __forceinline__ bool not_finite(u16x2 m) { return max((uint32_t)m[0], (uint32_t)m[1]) >= kInf; }
-__device__ __forceinline__ uint32_t max_mag(uint32_t m, float x) { return max(m, __float_as_uint(x) & 0x7FFFFFFFu); }
-__device__ __forceinline__ bool not_finite(uint32_t m) { return m >= 0x7F800000u; }
+__device__ __forceinline__ bool not_finite(float x) { return (__float_as_uint(x) & 0x7FFFFFFFu) >= 0x7F800000u; }
+// Largest of m, |x| and |y|, NaN left out.
+__device__ __forceinline__ float max_mag(float m, float x, float y) {
+  asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(x), "v"(y));
+  return m;
+}
 
 // Halves of eight words -> an MFMA fragment.
 __device__ __forceinline__ bf16x8 pick_halves(const u32x4& a, const u32x4& b, uint32_t which) {
@@ -429,7 +433,7 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
         for (int e = 0; e < 4; ++e) w[v][e] *= inv;
     } else {
       float sum = 0.f;
-      uint32_t wmag = 0u;
+      float wmag = 0.f;
 #pragma unroll
       for (int v = 0; v < LPL; ++v)
 #pragma unroll
@@ -443,7 +447,7 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           w[v][e] = ok[v][e] ? aa[v][e] * (w[v][e] - sum) * scale : 0.f;
-          wmag = max_mag(wmag, w[v][e]);
+          if (e % 2 == 1) wmag = max_mag(wmag, w[v][e - 1], w[v][e]);
         }
       w_bad = not_finite(wmag);
     }
@@ -577,7 +581,7 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
 constexpr int KV_KEYS = 256, KV_Q = 32;
 constexpr int KV_TILE = KV_KEYS * KV_Q;                    // words
 constexpr int KV_TS = KV_TILE + 64;                        // ... and the 64 dummy words behind them
-constexpr int KV_FLAGS = 32;                               // bytes
+constexpr int KV_FLAGS = 16;                               // bytes
 template <int DH, int LPL>
 __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ dY, const int32_t* __restrict__ idx,
@@ -589,8 +593,7 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
   extern __shared__ uint4 kv_smem[];
   char* smem = reinterpret_cast<char*>(kv_smem);           // A tile, dS tile, dY rows, Q rows
   char* rows = smem + 2 * KV_TS * 4;
-  int* bad = reinterpret_cast<int*>(rows + 2 * ROWS);      // the last step with an infinity or a NaN among its operands
-  uint32_t* steps = reinterpret_cast<uint32_t*>(bad + 4);  // [4] all of them, a bit each (n <= 4096: at most 128 steps)
+  uint32_t* steps = reinterpret_cast<uint32_t*>(rows + 2 * ROWS);   // [4] a bit for every step (n <= 4096: at most 128) that meets an infinity or a NaN
   float* words = reinterpret_cast<float*>(smem);
   // (lane roles are formed again for every step from a value the compiler cannot follow, see the rows kernel)
   uint32_t tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
@@ -610,7 +613,7 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
   dS += base * L;
 
   for (uint32_t e = tid; e < 2 * KV_TS / 4; e += NT) reinterpret_cast<uint4*>(smem)[e] = make_uint4(0u, 0u, 0u, 0u);
-  if (tid < 4) { bad[tid] = -1; steps[tid] = 0u; }
+  if (tid < 4) steps[tid] = 0u;
   __syncthreads();
   const uint32_t last = min(KV_KEYS, n - key0);
 
@@ -676,17 +679,33 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
         old[v][e / 2] = e % 2 ? old[v][e / 2] | to << 16 : to;
       }
   };
-  // An infinite weight, or an infinity or a NaN in the rows, of the step whose lists and rows have arrived.
-  auto not_finite_step = [&]() -> bool {
-    uint32_t m = 0u;
+  // What is infinite or NaN in the rows of a step, or infinite among its weights, in the registers it has arrived in: zeros
+  // are multiplied in its place, and the step is marked.  (A NaN weight reaches its own key only.)
+  auto drop_not_finite = [&](int b) {
+    float m = 0.f;
 #pragma unroll
     for (int v = 0; v < LPL; ++v)
 #pragma unroll
-      for (int e = 0; e < EL; ++e) m = max_mag(max_mag(m, an[v][e]), dn[v][e]);
+      for (int e = 0; e < EL; ++e) m = max_mag(m, an[v][e], dn[v][e]);
     u16x2 r = {0, 0};
 #pragma unroll
     for (int u = 0; u < RP; ++u) r = max_mag(r, rnext[u]);
-    return __any(not_finite(m) || not_finite(r));
+    if (!__any(not_finite(m) || not_finite(r))) return;
+    if (lane == 0) atomicOr(steps + b / 32, 1u << (b % 32));
+#pragma unroll
+    for (int v = 0; v < LPL; ++v)
+#pragma unroll
+      for (int e = 0; e < EL; ++e) {
+        an[v][e] = not_finite(an[v][e]) ? 0.f : an[v][e];
+        dn[v][e] = not_finite(dn[v][e]) ? 0.f : dn[v][e];
+      }
+#pragma unroll
+    for (int u = 0; u < RP; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if ((rnext[u][e] & kInf) == kInf) rnext[u][e] &= 0xFFFF0000u;
+        if ((rnext[u][e] >> 16 & kInf) == kInf) rnext[u][e] &= 0xFFFFu;
+      }
   };
 
   f32x16 acc[2][CT];                                       // [32-key tile][32-column tile]
@@ -697,30 +716,6 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[kt][ct][v] = 0.f;
 
-  // This thread's part of the step's operands, with zeros for what is infinite or NaN.
-  auto drop_not_finite = [&]() {
-#pragma unroll
-    for (int u = 0; u < RP; ++u) {
-      u32x4* at = reinterpret_cast<u32x4*>(rows + row_dst() + u * RQ * DH * 2);
-      u32x4 x = *at;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if ((x[e] & kInf) == kInf) x[e] &= 0xFFFF0000u;
-        if ((x[e] >> 16 & kInf) == kInf) x[e] &= 0xFFFFu;
-      }
-      *at = x;
-    }
-#pragma unroll
-    for (int v = 0; v < LPL; ++v)
-#pragma unroll
-      for (int e = 0; e < EL; ++e)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-          float* at = words + set(v, e) + y * KV_TS;
-          if (not_finite(max_mag(0u, *at))) *at = 0.f;
-        }
-  };
-
   const int nblk = (n + KV_Q - 1) / KV_Q;
   // vectors requested ahead of the products; the others, where registers for them are lacking, behind
   const std::integral_constant<int, 0> zero;
@@ -730,18 +725,13 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
   request_lists(0, zero, all);
   for (int b = 0; b < nblk; ++b) {
     fresh_roles();
+    drop_not_finite(b);
     scatter(b);
 #pragma unroll
     for (int u = 0; u < RP; ++u) *reinterpret_cast<u32x4*>(rows + row_dst() + u * RQ * DH * 2) = rnext[u];
-    if (not_finite_step() && lane == 0) *bad = b;
     request_rows(b + 1);
     request_lists(b + 1, zero, early);
     __syncthreads();
-    if (*bad == b) {                                        // uniform
-      drop_not_finite();
-      if (tid == 0) steps[b / 32] |= 1u << (b % 32);
-      __syncthreads();
-    }
     if (kg * 64 < last) {                                   // uniform
       fresh_roles();
       uint32_t vtr[CT], wrow[2];                           // fragments of the rows; this lane's key rows in its tensor's tile
@@ -803,12 +793,12 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
         for (int y = 0; y < 2; ++y) {
           const float wt = load_at<float>(y ? dS : A, at);
           const u32x4 x = load_at<u32x4>(src[y], (uint32_t)q * (DH * 2) + (tid % NC) * 16);
-          if (!not_finite(max_mag(0u, wt)) && !not_finite(max_mag(u16x2{0, 0}, x))) continue;
+          const bool all = not_finite(wt);
+          if (!all && !not_finite(max_mag(u16x2{0, 0}, x))) continue;
           u32x4* out = reinterpret_cast<u32x4*>((y ? dK : dV) + (base + key0 + j) * DH) + tid % NC;
           u32x4 o = *out;
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const bool all = not_finite(max_mag(0u, wt));
             const float lo = all || (x[e] & kInf) == kInf ? lo_bf16(o[e]) + wt * lo_bf16(x[e]) : lo_bf16(o[e]);
             const float hi = all || (x[e] >> 16 & kInf) == kInf ? hi_bf16(o[e]) + wt * hi_bf16(x[e]) : hi_bf16(o[e]);
             o[e] = pack_bf16x2(lo, hi);
