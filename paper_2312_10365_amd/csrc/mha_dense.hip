@@ -24,9 +24,10 @@
 // where these take 127 / 122 / 129 -- but lose what is small beside the largest weight or value.)
 //
 // Infinities and NaN.  A dense tile multiplies every key of the sequence with a weight, zero where the query
-// does not keep it, and 0 x inf is NaN.  So both kernels look for such values while they stage their operands,
-// and what they touch (a wavefront's four queries in the rows kernel, 32 queries in the keys kernel) is summed
-// over the kept entries alone, by multiply-adds: a query or key that nothing of the kind is kept with never sees it.
+// does not keep it, and 0 x inf is NaN.  So both kernels look for such values while they stage their operands.  A
+// wavefront's four queries that meet any are summed over their kept entries alone (rows kernel); a step multiplies
+// zeros in their place, and the terms that hold one are added to the rounded results at the end (keys kernel).  A query
+// or key that nothing of the kind is kept with never sees it.
 #include <math.h>
 #include <type_traits>
 
