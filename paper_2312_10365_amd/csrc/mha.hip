@@ -1141,10 +1141,12 @@ __global__ __launch_bounds__(kSeqThreads) void seq_accum_kernel(const uint16_t* 
 // ---------------------------------------------------------------- host side
 // Dense tiles on the matrix cores (mha_dense.hip) cost n multiply-adds per query and channel where
 // the gathering kernels here cost L.  Measured, forward + backward without the codes and lists, us:
-//   S 512, n 512, dh 64    L 8: 373 gathering, 293 dense   L 32: 462, 316   L 64: 637, 262
-//   S 512, n 512, dh 128   L 8: 528, 567                   L 32: 759, 578
-//   S 128, n 2048, dh 64   L 32: 2382, 1436                L 64: 4411, 1469
-// (the lists regrouped by key are what the long sequences pay for).  Dense tiles load list entries
+//   S 512, n 512, dh 64    L 8: 345 gathering, 316 dense   L 32: 405, 318   L 64: 642, 343
+//   S 512, n 512, dh 128   L 8: 512, 560                   L 32: 720, 569
+//   S 128, n 2048, dh 64   L 32: 2348, 701                 L 64: 4385, 923
+// (the lists regrouped by key are what the long sequences pay for; at n 2048 only the key side is
+// dense on the right).  128-wide heads need the line between L 8 and L 32 at 512 keys; for 64-wide
+// heads and for long sequences dense tiles win below the line too.  Dense tiles load list entries
 // four at a time, so they want L >= 4.
 bool use_dense(const spt_mha_shape_t& s) { return s.L >= 4 && s.n <= 32 * s.L; }
 
