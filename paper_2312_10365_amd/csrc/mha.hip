@@ -7,10 +7,8 @@
 // residency and the 64-lane wavefront.
 //
 //   pq_assign_kernel        one thread per (vector, codebook): fused distance + argmin, codebooks in LDS
-//   topl_lane_kernel        Algorithm 3 bit-sliced, one LANE per query: inverted code table in LDS,
+//   topl_lane_kernel        Algorithm 3 bit-sliced, two or four LANES per query: inverted code table in LDS,
 //                           carry-save score planes for 32 keys at a time, rows staged in LDS
-//   topl_kernel             the same selection with one WAVEFRONT per query (ballot ranks), for
-//                           shapes whose table and staging do not fit LDS
 //   seq_dots_kernel         one workgroup per sequence, gathered tensor resident in LDS: logits +
 //                           softmax (forward) or dA + softmax Jacobian (backward)
 //   seq_accum_kernel        same residency: weighted sums of gathered rows (Y, dQ through the index
@@ -92,125 +90,18 @@ __global__ __launch_bounds__(256) void pq_assign_kernel(const uint16_t* __restri
 }
 
 // ---------------------------------------------------------------- Algorithm 3 with Eq. 6
-// Codes are below 16 (E <= 16), so the M codes of a vector pack into M/8 words of 4-bit fields.
-__device__ __forceinline__ uint32_t pack_nibbles(uint32_t lo4, uint32_t hi4) {
-  auto squeeze = [](uint32_t b) {   // bytes b0 b1 b2 b3 -> 16 bits of nibbles
-    return (b & 0xFu) | ((b >> 4) & 0xF0u) | ((b >> 8) & 0xF00u) | ((b >> 12) & 0xF000u);
-  };
-  return squeeze(lo4) | (squeeze(hi4) << 16);
-}
-// Number of equal 4-bit fields of a query and a key (Eq. 6).  After the XOR a field is zero
-// exactly where the codes agree; the add cannot carry between fields because bit 3 of each is
-// masked off first, so the test is exact.
-template <int W>
-__device__ __forceinline__ int pq_score(const uint32_t (&kc)[W], const uint32_t (&qc)[W]) {
-  int sc = 0;
-#pragma unroll
-  for (int w = 0; w < W; ++w) {
-    const uint32_t x = kc[w] ^ qc[w];
-    const uint32_t y = ~(((x & 0x77777777u) + 0x77777777u) | x | 0x77777777u);
-    sc += __popc(y);
-  }
-  return sc;
-}
-// Number of set bits of a wavefront mask below the calling lane.
-__device__ __forceinline__ int lanes_below(uint64_t mask) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
-// The bucket sort, restated for a wavefront: keys arrive in index order, so bucket s holds the
-// keys of score s in index order and only its first L-1 are ever read; the output is those
-// prefixes concatenated from score M down, cut at L, padded with -1.  Pass 1 counts each score
-// (ballots), pass 2 places every key by its rank inside its score; buckets that are empty or lie
-// past the cut are skipped as a whole (a uniform test), and inside the pass nothing branches.
-template <int M>
-__global__ __launch_bounds__(256) void topl_kernel(const uint8_t* __restrict__ cq,
-                                                   const uint8_t* __restrict__ ck,
-                                                   int32_t* __restrict__ idx, int n, int L, int qpb) {
-  constexpr int W = M / 8;
-  extern __shared__ uint32_t kcodes[];   // [n][W] packed key codes
-  const int s = blockIdx.y;
-  {
-    const u32x2* src = reinterpret_cast<const u32x2*>(ck + (size_t)s * n * M);
-    for (int t = threadIdx.x; t < n * W; t += 256) {
-      const u32x2 b = src[t];
-      kcodes[t] = pack_nibbles(b[0], b[1]);
-    }
-  }
-  __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int q0 = blockIdx.x * qpb;
-  const int q1 = min(q0 + qpb, n);
-  for (int qi = q0 + wave; qi < q1; qi += 4) {
-    uint32_t qc[W];
-    {
-      const u32x2* qsrc = reinterpret_cast<const u32x2*>(cq + ((size_t)s * n + qi) * M);
-#pragma unroll
-      for (int w = 0; w < W; ++w) {
-        const u32x2 b = qsrc[w];
-        qc[w] = __builtin_amdgcn_readfirstlane(pack_nibbles(b[0], b[1]));
-      }
-    }
-    int cnt[M + 1];
-#pragma unroll
-    for (int b = 0; b <= M; ++b) cnt[b] = 0;
-    for (int j0 = 0; j0 < n; j0 += 64) {
-      const int j = j0 + lane;
-      int sc = -1;
-      if (j < n) {
-        uint32_t kc[W];
-#pragma unroll
-        for (int w = 0; w < W; ++w) kc[w] = kcodes[j * W + w];
-        sc = pq_score<W>(kc, qc);
-      }
-#pragma unroll
-      for (int b = 0; b <= M; ++b) cnt[b] += __popcll(__ballot(sc == b));
-    }
-    int base[M + 1];
-    int acc = 0;
-#pragma unroll
-    for (int b = M; b >= 0; --b) { base[b] = acc; acc += min(cnt[b], L - 1); }
-    const int total = min(acc, L);
-    int32_t* out = idx + ((size_t)s * n + qi) * L;
-    int run[M + 1];
-#pragma unroll
-    for (int b = 0; b <= M; ++b) run[b] = 0;
-    for (int j0 = 0; j0 < n; j0 += 64) {
-      const int j = j0 + lane;
-      int sc = -1;
-      if (j < n) {
-        uint32_t kc[W];
-#pragma unroll
-        for (int w = 0; w < W; ++w) kc[w] = kcodes[j * W + w];
-        sc = pq_score<W>(kc, qc);
-      }
-      int r = 0, first = L;              // rank inside the bucket, first output slot of the bucket
-#pragma unroll
-      for (int b = 0; b <= M; ++b) {
-        if (base[b] < L && cnt[b] > 0) {   // uniform
-          const uint64_t mask = __ballot(sc == b);
-          const int rb = run[b] + lanes_below(mask);
-          r = (sc == b) ? rb : r;
-          first = (sc == b) ? base[b] : first;
-          run[b] += __popcll(mask);
-        }
-      }
-      const int pos = first + r;
-      if (r < L - 1 && pos < L) out[pos] = j;
-    }
-    for (int pos = total + lane; pos < L; pos += 64) out[pos] = -1;
-  }
-}
-
-// Algorithm 3 again, bit-sliced: one LANE per query.  Per sequence an inverted table is built in
+// Algorithm 3, bit-sliced: a few LANES per query.  Keys arrive in index order, so bucket s holds the keys of score s in
+// index order and only its first L - 1 are ever read; the output is those prefixes concatenated from score M
+// down, cut at L, padded with -1.  Per sequence an inverted table is built in
 // LDS, table[m][e] = the set of keys (a bit mask over key indices) whose code in codebook m is e.
 // A query with codes e_1..e_M reads its M masks and adds them bit-plane-wise (a carry-save adder
 // tree on 32 keys at a time), which gives the Eq. 6 score of 32 keys in a few dozen bitwise
 // operations; "keys of score s" is then an AND of planes.  Pass A counts every score, pass B emits,
 // for each score from M down, the set bits in index order at base[s] + rank, stopping at the
 // bucket's readable length L-1 and at the row length L.  Rows are staged in LDS as 16-bit key
-// indices and written out whole.  Per query this is roughly a sixth of the wavefront-per-query kernel's
-// instructions; that kernel remains for shapes whose table and staging do not fit LDS.
+// indices and written out whole.  Bound by instructions of the vector units (16 codebooks, n 512: issuing in 79 % of
+// the cycles), half of them in pass B's loops over set bits, which go as often as the fullest of the 64 lanes (n 1100, L 137:
+// 403 turns of two keys where 69 would do were every lane equally full).
 __device__ __forceinline__ void full_add(uint32_t a, uint32_t b, uint32_t c, uint32_t& sum, uint32_t& carry) {
   const uint32_t t = a ^ b;
   sum = t ^ c;
@@ -255,19 +146,41 @@ struct ScorePlanes {
   __device__ __forceinline__ uint32_t level(int sc) const {   // sc is a compile-time constant at every use
     return sc == 16 ? top : (hi[sc >> 2] & lo[sc & 3]);
   }
+  __device__ __forceinline__ uint32_t upper() const { return hi[2] | hi[3] | top; }   // scores of 8 and more
 };
 
-template <int M>
-__global__ __launch_bounds__(512) void topl_lane_kernel(const uint8_t* __restrict__ cq,
+// Index of the lowest set bit, ~0 without one (one instruction, where __ffs checks for zero).
+__device__ __forceinline__ uint32_t lowest_bit(uint32_t x) {
+  uint32_t r;
+  asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+
+// A query's keys are split over P = 2 or 4 neighbouring lanes: each takes a contiguous part of the words, and the lanes
+// before it tell it where its keys of a score begin.  A wavefront then holds 64 / P queries and is done in a P-th of
+// the time, and stages fewer rows: more of them run on a CU (one per SIMD waits twice as long for its own instructions
+// as it issues), and a last round costs less.
+// Pairs of 32-bit mask words of a part, and words per mask of the inverted table (an odd number of pairs, so that
+// the 16 masks of a codebook start on different banks).
+__host__ __device__ inline int topl_part_pairs(int n, int P) { return (((n + 63) >> 6) + P - 1) / P; }
+__host__ __device__ inline int topl_mask_words(int n, int P) { return ((topl_part_pairs(n, P) * P) | 1) * 2; }
+// Words of a staged row: L 16-bit key indices and a slot that is written and never read, to an odd number of words (the rows
+// of neighbouring lanes start on different banks).
+__host__ __device__ inline int topl_row_words(int L) { return ((L + 2) >> 1) | 1; }
+
+template <int M, int P>
+__global__ __launch_bounds__(1024) void topl_lane_kernel(const uint8_t* __restrict__ cq,
                                                         const uint8_t* __restrict__ ck,
                                                         int32_t* __restrict__ idx, int n, int L) {
+  constexpr int QW = 64 / P;                        // queries of a wavefront
   extern __shared__ uint32_t lsm[];
   const int s = blockIdx.y;
-  const int nw = (n + 31) >> 5, nwp = nw + 1;       // padded: the 16 masks of a codebook start on different banks
+  const int pairs = topl_part_pairs(n, P), nwp = topl_mask_words(n, P);
   uint32_t* table = lsm;                            // [M][16][nwp]
-  uint16_t* stage = reinterpret_cast<uint16_t*>(lsm + M * 16 * nwp);   // [waves][64][L + 2] key indices, 0xFFFF = none
+  const int lw = topl_row_words(L);
+  uint32_t* stage = lsm + M * 16 * nwp;             // [waves][QW][lw], 0xFFFF = none
   const int tid = threadIdx.x, nthreads = blockDim.x;
-  for (int t = tid; t < M * 16 * nwp; t += nthreads) table[t] = 0u;
+  for (int t = tid; t < M * 8 * nwp; t += nthreads) reinterpret_cast<uint2*>(table)[t] = make_uint2(0u, 0u);
   __syncthreads();
   for (int j = tid; j < n; j += nthreads) {          // one key per thread: its M codes in one load
     uint32_t cw[M / 4];
@@ -280,83 +193,132 @@ __global__ __launch_bounds__(512) void topl_lane_kernel(const uint8_t* __restric
       atomicOr(table + (m * 16 + e) * nwp + (j >> 5), 1u << (j & 31));
     }
   }
-  const int wave = tid >> 6, lane = tid & 63;
-  const int ls = L + 2;                               // row stride in 16-bit units: an odd number of words
-  uint16_t* mystage = stage + (size_t)wave * 64 * ls;
-  for (int t = lane; t < 64 * ls; t += 64) mystage[t] = 0xFFFFu;
+  const int wave = tid >> 6, lane = tid & 63, part = lane % P;
+  uint32_t* mystage = stage + (size_t)wave * QW * lw;
+  for (int t = lane; t < QW * lw; t += 64) mystage[t] = 0xFFFFFFFFu;
+
+  const int q0 = (blockIdx.x * (nthreads >> 6) + wave) * QW;   // first query of this wavefront
+  const int qi = q0 + lane / P;
+  const bool live = qi < n;
+  int off[M];                                         // word offset of this lane's part of its query's mask in every codebook
+  {
+    uint32_t cw[M / 4];
+    const uint32_t* qsrc = reinterpret_cast<const uint32_t*>(cq + ((size_t)s * n + (live ? qi : 0)) * M);
+#pragma unroll
+    for (int w = 0; w < M / 4; ++w) cw[w] = qsrc[w];
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      off[m] = (m * 16 + (int)(cw[m >> 2] >> (8 * (m & 3)) & 15u)) * nwp + part * (2 * pairs);
+  }
   __syncthreads();
 
-  const int q0 = blockIdx.x * nthreads + wave * 64;   // first query of this wavefront
-  const int qi = q0 + lane;
-  const bool live = qi < n;
-  int off[M];                                         // word offset of this query's mask in every codebook
-  {
-    const uint8_t* qsrc = cq + ((size_t)s * n + (live ? qi : 0)) * M;
+  // Both passes walk the masks a pair of words at a time, the next pair requested before this one is worked on.  `each`
+  // gets the score planes of a word and its number in the part.  (Behind the last key a mask has zeros: score 0.)
+  auto walk = [&](auto each) {
+    u32x2 x[M];
 #pragma unroll
-    for (int m = 0; m < M; ++m) off[m] = (m * 16 + (qsrc[m] & 15)) * nwp;
-  }
-  const uint32_t tail = (n & 31) ? ((1u << (n & 31)) - 1u) : 0xFFFFFFFFu;   // real keys of the last word
+    for (int m = 0; m < M; ++m) x[m] = *reinterpret_cast<const u32x2*>(table + off[m]);
+    for (int p = 0; p < pairs; ++p) {
+      u32x2 next[M];
+      const uint32_t* from = table + 2 * (p + 1 < pairs ? p + 1 : p);
+#pragma unroll
+      for (int m = 0; m < M; ++m) next[m] = *reinterpret_cast<const u32x2*>(from + off[m]);
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        uint32_t xw[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) xw[m] = x[m][hf];
+        ScorePlanes<M> sp;
+        sp.build(xw);
+        each(sp, 2 * p + hf);
+      }
+#pragma unroll
+      for (int m = 0; m < M; ++m) x[m] = next[m];
+    }
+  };
 
   int cnt[M + 1];
 #pragma unroll
   for (int b = 0; b <= M; ++b) cnt[b] = 0;
-  for (int w = 0; w < nw; ++w) {
-    uint32_t x[M];
+  walk([&](const ScorePlanes<M>& sp, int) {
 #pragma unroll
-    for (int m = 0; m < M; ++m) x[m] = table[off[m] + w];
-    ScorePlanes<M> sp;
-    sp.build(x);
-    const uint32_t valid = (w == nw - 1) ? tail : 0xFFFFFFFFu;
+    for (int b = 1; b < 8; ++b) cnt[b] += __popc(sp.level(b));
+    if (__ballot(sp.upper() != 0u)) {                  // scores of 8 and more are rare
 #pragma unroll
-    for (int b = 0; b <= M; ++b) cnt[b] += __popc(sp.level(b) & valid);
-  }
-  int base[M + 1], quota[M + 1];
+      for (int b = 8; b <= M; ++b) cnt[b] += __popc(sp.level(b));
+    }
+  });
+  const int first = part * pairs * 64;                 // this part's first key
+  cnt[0] = max(0, min(n - first, pairs * 64));
+#pragma unroll
+  for (int b = 1; b <= M; ++b) cnt[0] -= cnt[b];
+  // the next slot of every bucket in this lane's row, and how many keys it still takes from this lane
+  uint16_t* row = reinterpret_cast<uint16_t*>(mystage + lane / P * lw);
+  int slot[M + 1], quota[M + 1];
   int acc = 0;
 #pragma unroll
   for (int b = M; b >= 0; --b) {
-    base[b] = acc;
-    quota[b] = live ? max(0, min(min(cnt[b], L - 1), L - acc)) : 0;   // keys this bucket contributes
-    acc += min(cnt[b], L - 1);
-  }
-  int run[M + 1];
+    int before = 0, total = cnt[b];                    // keys of score b in the parts before, in all parts
 #pragma unroll
-  for (int b = 0; b <= M; ++b) run[b] = 0;
-  uint16_t* row = mystage + lane * ls;
+    for (int o = 1; o < P; o <<= 1) {
+      const int other = __shfl_xor(total, o);
+      before += part & o ? other : 0;
+      total += other;
+    }
+    const int take = max(0, min(min(total, L - 1), L - acc));   // keys this bucket contributes
+    slot[b] = min(acc + before, L);
+    quota[b] = live ? max(0, min(cnt[b], take - before)) : 0;
+    acc += min(total, L - 1);
+  }
   bool need[M + 1];                                   // does any query of this wavefront draw on bucket b
 #pragma unroll
   for (int b = 0; b <= M; ++b) need[b] = __ballot(quota[b] > 0) != 0ull;
-  for (int w = 0; w < nw; ++w) {
-    uint32_t x[M];
-#pragma unroll
-    for (int m = 0; m < M; ++m) x[m] = table[off[m] + w];
-    ScorePlanes<M> sp;
-    sp.build(x);
-    const uint32_t valid = (w == nw - 1) ? tail : 0xFFFFFFFFu;
-#pragma unroll
-    for (int b = M; b >= 0; --b) {
-      if (need[b]) {                                   // uniform
-        uint32_t bits = (run[b] < quota[b]) ? (sp.level(b) & valid) : 0u;
-        while (bits) {
-          const int bit = __ffs(bits) - 1;
-          bits &= bits - 1;
-          row[base[b] + run[b]] = (uint16_t)(w * 32 + bit);
-          ++run[b];
-          if (run[b] >= quota[b]) bits = 0u;
-        }
+  walk([&](const ScorePlanes<M>& sp, int w) {
+    const int key0 = first + w * 32;
+    auto emit = [&](int b) {
+      if (!need[b]) return;                            // uniform
+      uint32_t bits = sp.level(b);
+      if (b == 0) bits &= n - key0 >= 32 ? 0xFFFFFFFFu : n > key0 ? (1u << (n - key0)) - 1u : 0u;
+      int c = min((int)__popc(bits), quota[b]);
+      uint16_t* to = row + slot[b];
+      quota[b] -= c;
+      slot[b] += c;
+      while (c > 0) {                                  // two keys a turn: the lanes go as often as the fullest of them
+        const uint32_t k0 = lowest_bit(bits);
+        bits &= bits - 1;
+        const uint32_t k1 = lowest_bit(bits);
+        bits &= bits - 1;
+        to[0] = (uint16_t)(key0 + k0);
+        *(c > 1 ? to + 1 : row + L) = (uint16_t)(key0 + k1);
+        to += 2;
+        c -= 2;
       }
+    };
+    if (__ballot(sp.upper() != 0u)) {
+#pragma unroll
+      for (int b = M; b >= 8; --b) emit(b);
     }
-  }
-  __syncthreads();
-  // stage -> idx, whole rows (lanes over positions)
-  for (int r = 0; r < 64; ++r) {
-    const int q = q0 + r;
-    if (q >= n) break;                                 // uniform
-    const uint16_t* src = mystage + r * ls;
-    int32_t* dst = idx + ((size_t)s * n + q) * L;
-    for (int pos = lane; pos < L; pos += 64) {
-      const uint32_t key = src[pos];
-      dst[pos] = key == 0xFFFFu ? -1 : (int32_t)key;
+#pragma unroll
+    for (int b = 7; b >= 0; --b) emit(b);
+  });
+  wave_lds_fence();
+  // stage -> idx: the wavefront's rows are one contiguous run of the output, written 64 neighbouring words at a time
+  const int rows = min(QW, n - q0);
+  if (rows <= 0) return;
+  const uint32_t items = rows * L;
+  const uint32_t magic = 0xFFFFFFFFu / (uint32_t)L + 1u;   // it / L = mulhi(it, magic): it < 2^14, L <= 2^8 (L = 1: it)
+  const uint16_t* from = reinterpret_cast<const uint16_t*>(mystage);
+  int32_t* dst = idx + ((size_t)s * n + q0) * L;
+  for (uint32_t it0 = lane; it0 < items; it0 += 64 * 8) {
+    uint32_t key[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t it = min(it0 + u * 64, items - 1), r = L == 1 ? it : __umulhi(it, magic);
+      key[u] = from[r * (2 * lw) + (it - r * L)];
     }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (it0 + u * 64 < items) dst[it0 + u * 64] = key[u] == 0xFFFFu ? -1 : (int32_t)key[u];
   }
 }
 
@@ -1217,6 +1179,47 @@ void launch_row(const spt_mha_shape_t& s, const uint16_t* R, const uint16_t* G1,
 #undef SPT_ROW
 }
 
+// Lanes per query and wavefronts per workgroup of topl_lane_kernel (at least (4, 1) fits LDS for every shape the library takes).
+// The wavefronts of a workgroup share a table.  Time of the launch, in pairs of mask words walked by a
+// wavefront that has a SIMD for itself: rounds of workgroups x (the pairs of a part, two more for what a wavefront does
+// once, times the wavefronts that share a SIMD; and 8 for every key a lane puts into the table).  us, one box, the kernel
+// with a query per lane before -> now: S 512, n 512, 8 codebooks, L 64: 56 -> 51; 16 codebooks 98 -> 80; S 96, n 1100,
+// L 137: 189 -> 94; S 32, n 2048, L 128: 145 -> 66; S 8, n 130: 17.6 -> 7.3.  Over nine shapes and every count that fits the
+// rule's choice is at most 8 % behind the best.
+struct TopLPlan { int parts, waves; size_t lds; };
+TopLPlan plan_topl(const spt_mha_shape_t& s) {
+  TopLPlan best = {0, 0, 0};
+  double least = 0.0;
+  for (int P = 2; P <= 4; P *= 2) {
+    const int rows = 64 / P;
+    const size_t table = (size_t)s.M * 16 * topl_mask_words(s.n, P) * 4, stage = (size_t)rows * topl_row_words(s.L) * 4;
+    for (int w = 16; w >= 1; --w) {
+      if (table + w * stage > kLdsLimit || (w > 1 && (w - 1) * rows >= s.n)) continue;   // (no idle wavefronts)
+      const int by_lds = (int)(kLdsLimit / (table + w * stage)), by_regs = (s.M == 16 ? 16 : 24) / w;
+      const int64_t per_cu = by_lds < by_regs ? by_lds : by_regs;                        // workgroups
+      const int64_t groups = (int64_t)s.S * ((s.n + w * rows - 1) / (w * rows));
+      auto round = [&](int64_t g) {
+        return (topl_part_pairs(s.n, P) + 2.0) * (double)((g * w + 3) / 4) + 8.0 * s.n / (64.0 * w);
+      };
+      const int64_t full = groups / (256 * per_cu), rest = groups % (256 * per_cu);
+      const double cost = (double)full * round(per_cu) + (rest ? round((rest + 255) / 256) : 0.0);
+      if (best.waves == 0 || cost < least) { least = cost; best = {P, w, table + w * stage}; }
+    }
+  }
+  return best;
+}
+
+template <int M, int P>
+hipError_t launch_topl(const spt_mha_shape_t& s, const TopLPlan& plan, const uint8_t* cq, const uint8_t* ck, int32_t* idx,
+                       hipStream_t st) {
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(topl_lane_kernel<M, P>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
+  if (e != hipSuccess) return e;
+  const int rows = plan.waves * (64 / P);
+  topl_lane_kernel<M, P><<<dim3((s.n + rows - 1) / rows, s.S), plan.waves * 64, plan.lds, st>>>(cq, ck, idx, s.n, s.L);
+  return hipGetLastError();
+}
+
 template <int DH, bool BWD>
 void launch_seq_dots(const spt_mha_shape_t& s, const uint16_t* R, const uint16_t* G1, const int32_t* idx,
                      const float* Ain, float* Wout, hipStream_t st) {
@@ -1282,45 +1285,12 @@ int spt_mha_topl(const spt_mha_shape_t* shape, const uint8_t* cq, const uint8_t*
     return SPT_ERR_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
   ScopedKernelTimer tm(kSlotMhaTopl, st);
-  // One lane per query when the inverted table and the row staging fit LDS, otherwise one wavefront per query.  The
-  // wavefronts of a workgroup (up to 8) share a table; LDS is what limits how many run on a CU, and the kernel is bound
-  // by the latency of its table reads, so the count is the one that gives the most of them with work (the last
-  // workgroup of a sequence may be half empty) -- two workgroups rather than one of twice the size.  (us, when workgroups that do not fit twice had one wavefront: n 2048, 64 sequences,
-  // 16 codebooks, L 128: 500; 8 codebooks, L 250: 495.)
-  const size_t table_bytes = (size_t)shape->M * 16 * ((shape->n + 31) / 32 + 1) * sizeof(uint32_t);
-  const size_t stage_bytes = (size_t)64 * (shape->L + 2) * sizeof(uint16_t);
-  int waves = 0;
-  double most = 0.0;
-  for (int cand = 8; cand >= 1; --cand) {
-    if (cand > 1 && (cand - 1) * 64 >= shape->n) continue;   // short sequences: no idle wavefronts
-    const int groups = (int)(kLdsLimit / (table_bytes + cand * stage_bytes));
-    const int running = cand * groups < 16 ? cand * groups : 16;
-    const int slots = (shape->n + cand * 64 - 1) / (cand * 64) * cand;   // wavefronts started for a sequence's queries
-    const double busy = (double)running * shape->n / (64.0 * slots);
-    if (busy > most || (busy == most && groups > 1 && waves == running)) { most = busy; waves = cand; }
-  }
-  if (waves) {
-    const size_t lds = table_bytes + waves * stage_bytes;
-    const dim3 grid((shape->n + waves * 64 - 1) / (waves * 64), shape->S);
-    if (shape->M == 8) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(topl_lane_kernel<8>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      hipLaunchKernelGGL(topl_lane_kernel<8>, grid, dim3(waves * 64), lds, st, cq, ck, idx, shape->n, shape->L);
-    } else {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(topl_lane_kernel<16>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      hipLaunchKernelGGL(topl_lane_kernel<16>, grid, dim3(waves * 64), lds, st, cq, ck, idx, shape->n, shape->L);
-    }
-  } else {
-    const int qpb = 16;
-    const dim3 grid((shape->n + qpb - 1) / qpb, shape->S);
-    const size_t lds = (size_t)shape->n * (shape->M / 8) * sizeof(uint32_t);
-    if (shape->M == 8)
-      hipLaunchKernelGGL(topl_kernel<8>, grid, dim3(256), lds, st, cq, ck, idx, shape->n, shape->L, qpb);
-    else
-      hipLaunchKernelGGL(topl_kernel<16>, grid, dim3(256), lds, st, cq, ck, idx, shape->n, shape->L, qpb);
-  }
-  return hipGetLastError() == hipSuccess ? SPT_OK : SPT_ERR_HIP;
+  const TopLPlan plan = plan_topl(*shape);
+#define SPT_TOPL(M, P) launch_topl<M, P>(*shape, plan, cq, ck, idx, st)
+  const hipError_t e = shape->M == 8 ? (plan.parts == 2 ? SPT_TOPL(8, 2) : SPT_TOPL(8, 4))
+                                     : (plan.parts == 2 ? SPT_TOPL(16, 2) : SPT_TOPL(16, 4));
+#undef SPT_TOPL
+  return e == hipSuccess ? SPT_OK : SPT_ERR_HIP;
 }
 
 int spt_mha_attn_fwd(const spt_mha_shape_t* shape, const void* Q, const void* K, const void* V,

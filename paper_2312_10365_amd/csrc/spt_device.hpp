@@ -36,6 +36,15 @@ __device__ __forceinline__ int block_inclusive_sum(int v, int32_t* wtot, int& to
   return before + incl;
 }
 
+// Between a wavefront's LDS writes and its own reads of what OTHER lanes wrote (and before it
+// overwrites what they read): LDS executes one wavefront's accesses in order, so no wait is
+// needed; this keeps the compiler from moving the accesses across each other.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Round-to-nearest-even float -> bf16 bit pattern (finite inputs).
 __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
   const uint32_t u = __float_as_uint(f);

@@ -135,6 +135,31 @@ def test_attention_tile_edges(n, dh, L):
     test_whole_path_matches_oracle(custom_mha_shape(1, 2, n, dh, L, seed=n + L))
 
 
+# Selection: key counts around the 64-key pairs of mask words and the parts a query's keys are split into, row lengths
+# from 1 to n, one and all codes alike (every key in the top bucket), sequences of one to many workgroups.
+@pytest.mark.parametrize("E", (1, 3, 16))
+@pytest.mark.parametrize("dh", (64, 128))
+@pytest.mark.parametrize("S,n,L", ((1, 1, 1), (3, 2, 2), (2, 63, 9), (2, 64, 64), (1, 65, 33), (3, 127, 12), (2, 129, 128),
+                                   (40, 130, 20), (1, 256, 255), (2, 257, 1), (2, 321, 40), (1, 513, 256), (1, 1089, 77)))
+def test_selection_edges(S, n, L, dh, E):
+    rng = np.random.default_rng(1000 * n + 10 * L + E)
+    M = dh // 8
+    cq, ck = (rng.integers(0, E, (S, n, M), dtype=np.uint8) for _ in range(2))
+    if n > 4:
+        ck[:, n // 2] = cq[:, n - 1]      # a key that shares all codes with a query
+    s = mha.make_shape(S, 1, n, dh, L)
+    idx = torch.full((S, n, L), -7, dtype=torch.int32, device="cuda")
+    mha.topl(s, torch.from_numpy(cq).cuda(), torch.from_numpy(ck).cuda(), idx)
+    np.testing.assert_array_equal(idx.cpu().numpy(), oracle().topl(cq, ck, L))
+
+
+def test_selection_longest():
+    rng = np.random.default_rng(5)
+    cq, ck = (rng.integers(0, 16, (1, 4096, 16), dtype=np.uint8) for _ in range(2))
+    idx = mha.topl(mha.make_shape(1, 1, 4096, 128, 256), torch.from_numpy(cq).cuda(), torch.from_numpy(ck).cuda())
+    np.testing.assert_array_equal(idx.cpu().numpy(), oracle().topl(cq, ck, 256))
+
+
 def test_backward_is_deterministic_and_workspace_reusable():
     sh = custom_mha_shape(2, 2, 200, 64, 40, seed=21)
     inp = make_mha_inputs(sh)
