@@ -39,6 +39,15 @@ namespace spt {
 //                     Wide blocks have one list, bucket-major, and its length in kd_count[0]: there
 //                     the kernel itself cuts the (row tile, A-side tile) items into 8 equal slices.
 
+constexpr int FU_ROWS = 256;      // rows of a K = d tile of narrow blocks
+// A round of K = d tiles of 256, 128 or 64 rows, one per CU of an XCD, takes as long as a tile that has the memory path for itself,
+// or as all of them together by the rows and weight rows they fetch (the kernel is bound by those): kPartAlone, and
+// kPartShare per tile; 640 = a full round of 256-row tiles.  us a launch, up / dH, whole tiles on their bucket's XCD -> this:
+// the OPT-1.3B-like layer with the skewed router (63 to 83 tiles an XCD) 102 / 114 -> 86 / 95; 7B-like (nine tiles for most
+// buckets of 2048 + 39 rows) 305 / 314 -> 287 / 296; BERT-large-like 76 / 84 -> 72 / 80; with rounds counted alone
+// (a half tile 0.6 of a whole one) 3000 tokens of the 7B-like layer were cut into halves for nothing (121, 121).
+constexpr int kPartAlone[3] = {12 * 32, 7 * 32, 5 * 32}, kPartShare[3] = {20, 13, 10};
+
 struct PlanArgs {
   const int32_t* offsets;
   const int32_t* perm;
@@ -112,10 +121,17 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
   int rank = 0;
   if (b < N)
     for (int o = 0; o < N; ++o) rank += (sm_m[o] > m) || (sm_m[o] == m && o < b);
-  const int ntq = (m + p.QT - 1) / p.QT;
+  // Tiles of p.QT rows; with 256 a bucket's last rows, if they are at most 128, are listed apart (1: up to 64, 2: up to 128).
+  __shared__ uint8_t sm_short_by_rank[1024];
+  __shared__ int16_t sm_rank[1024];
+  const bool parts = p.QT == FU_ROWS && N >= 16 && !p.wide;
+  const int end_rows = m & (p.QT - 1), mine_short = !parts || end_rows == 0 || end_rows > 128 ? 0 : end_rows > 64 ? 2 : 1;
+  const int ntq = (m >> (31 - __clz(p.QT))) + (end_rows > 0 && !mine_short);   // (64 or 256: a power of two)
   if (b < N) {
     p.border[rank] = b;
+    sm_rank[b] = (int16_t)rank;
     sm_ntq_by_rank[rank] = ntq;
+    sm_short_by_rank[rank] = (uint8_t)mine_short;
   }
   __syncthreads();
 
@@ -127,19 +143,19 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     __shared__ int32_t sm_np_rank[1024];
     __shared__ int32_t sm_wstart[1024];
     const int np = (b < N) ? (m > p.dw_rows ? (m + p.dw_rows - 1) / p.dw_rows : 1) : 0;
-    const int x_end = inclusive_scan(np > 1 ? np - 1 : 0);     // staging slots, in bucket order
-    const int l_end = inclusive_scan(np > 1 ? 1 : 0);          // buckets with staged pieces
+    if (b < N) sm_np_rank[rank] = np;
+    else sm_np_rank[b] = 0;
+    // one sum for both: staging slots, in bucket order (there are fewer than N of them: a piece holds 1.5 times the mean bucket),
+    // and, above, buckets with staged pieces
+    const int both = inclusive_scan(np > 1 ? (np - 1) | 1 << 16 : 0);
+    const int x_end = both & 0xFFFF, l_end = both >> 16;
     if (b < N && np > 1) {
       p.dw_xlist[1 + 3 * (l_end - 1)] = b;
       p.dw_xlist[2 + 3 * (l_end - 1)] = x_end - (np - 1);
       p.dw_xlist[3 + 3 * (l_end - 1)] = x_end;
     }
     if (b == N - 1) p.dw_xlist[0] = l_end;
-    sm_np_rank[b] = 0;
-    __syncthreads();
-    if (b < N) sm_np_rank[rank] = np;
-    __syncthreads();
-    const int mine = sm_np_rank[b];
+    const int mine = sm_np_rank[b];                            // (the sum's barriers lie between)
     const int w_end = inclusive_scan(mine);                    // work order: by rank
     sm_wstart[b] = w_end - mine;
     __shared__ int32_t total_pieces;
@@ -158,30 +174,111 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
   if (p.wide) {
     const int inc = inclusive_scan(ntq);
     if (b < N)
-      for (int lvl = 0; lvl < ntq; ++lvl) p.kd_list[inc - ntq + lvl] = KdTile{b, off + lvl * p.QT};
+      for (int lvl = 0; lvl < ntq; ++lvl) p.kd_list[inc - ntq + lvl] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + lvl * p.QT};
     if (b == N - 1) p.kd_count[0] = inc;
   } else if (N >= 16) {
     // rank r goes to group r%16 (<8) or 15 - r%16: position pg = r/8 inside the group; the
     // member at position p of group g has rank 8p + (p even ? g : 7 - g); sizes fall with p.
-    const int pg = rank >> 3;
-    const int g = (pg & 1) ? 7 - (rank & 7) : (rank & 7);
-    auto member_ntq = [&](int grp, int pos) {
-      const int r = 8 * pos + ((pos & 1) ? 7 - grp : grp);
-      return (r < N) ? sm_ntq_by_rank[r] : 0;
-    };
-    if (b < N) {
-      int before = 0;             // tiles of lower levels in this group
-      int alive = (N + 7) / 8;    // members that still have a tile at this level: a prefix
-      for (int lvl = 0; lvl < ntq; ++lvl) {
-        while (alive > 0 && member_ntq(g, alive - 1) <= lvl) --alive;
-        p.kd_list[(size_t)g * p.cap + before + pg] = KdTile{b, off + lvl * p.QT};
-        before += alive;
+    auto group_of = [&](int r) { return (r >> 3 & 1) ? 7 - (r & 7) : (r & 7); };
+    auto member_rank = [&](int grp, int pos) { return 8 * pos + ((pos & 1) ? 7 - grp : grp); };
+    // Per XCD: its group's tiles and the bucket ends listed apart; then, for lists that one workgroup per CU walks in rounds
+    // (parts), the same number of tiles for every XCD, and how those of a last, unfilled round are cut.
+    __shared__ int32_t own[8], surplus0[8], gap0[9], have[8], cut[8], shorts[8][2];
+    int most = 0;                 // tiles of an XCD
+    if (!parts) {
+      if (b < 8) {
+        int total = 0;
+        for (int pos = 0; 8 * pos < N; ++pos) {
+          const int r = member_rank(b, pos);
+          total += r < N ? sm_ntq_by_rank[r] : 0;
+        }
+        p.kd_count[b] = total;
+      }
+    } else {
+      if (b < 8) { own[b] = 0; shorts[b][0] = 0; shorts[b][1] = 0; }
+      __syncthreads();
+      if (b < N) {
+        atomicAdd(&own[group_of(rank)], ntq);
+        if (mine_short) atomicAdd(&shorts[group_of(rank)][mine_short - 1], 1);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int x = 0; x < 8; ++x) most += own[x];
+      most = (most + 7) / 8;
+      if (b < 8) {
+        int sur = 0, gap = 0, all = 0;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const int o = own[x];
+          all += max(o - most, 0);
+          if (x < b) { sur += max(o - most, 0); gap += max(most - o, 0); }
+        }
+        const int mine = own[b];
+        surplus0[b] = sur; gap0[b] = gap;
+        if (b == 7) gap0[8] = 0x7FFFFFFF;
+        const int hv = mine >= most ? most : mine + max(0, min(all - gap, most - mine));
+        int best = 0, least = 0;
+        const int left = hv % 32, s1 = shorts[b][0], s2 = shorts[b][1];
+        for (int c = 0; (left || s2) && c < 3; ++c) {
+          const int big = left << c, mid = c == 2 ? 0 : s2, n = big + (c == 2 ? 2 * s2 : s2) + s1;
+          int cost = 0;
+          for (int at = 0; at < n; at += 32) {
+            const int cls = at < big ? c : at < big + mid ? 1 : 2;
+            cost += max(kPartAlone[cls], kPartShare[cls] * min(32, n - at));
+          }
+          if (c == 0 || cost < least) { least = cost; best = c; }
+        }
+        have[b] = hv;
+        cut[b] = best;
+        p.kd_count[b] = hv - left + (left << best) + (best == 2 ? 2 * s2 : s2) + s1;
+      }
+      __syncthreads();
+    }
+    // the tiles: as many threads per bucket as there are, a level each
+    const int tlog = 10 - (32 - __clz(N - 1)), tpb = 1 << tlog, tb = b >> tlog;
+    if (tb < N) {
+      const int trank = sm_rank[tb], g = group_of(trank), pg = trank >> 3, tm = sm_m[tb], toff = off_sh[tb];
+      const int members = (N + 7) / 8, tn = sm_ntq_by_rank[trank];
+      for (int lvl = b & (tpb - 1); lvl < tn; lvl += tpb) {
+        int at = pg;                // members with a tile at this level are a prefix; before them: all tiles of lower levels
+#pragma unroll 4
+        for (int pos = 0; pos < members; ++pos) {
+          const int r = member_rank(g, pos);
+          at += min(r < N ? (int)sm_ntq_by_rank[r] : 0, lvl);
+        }
+        int x = g;
+        const int q = toff + lvl * p.QT;
+        if (!parts) {
+          p.kd_list[(size_t)x * p.cap + at] = KdTile{(uint16_t)tb, (uint16_t)p.QT, q};
+          continue;
+        }
+        if (at >= most) {         // more than its share: the next free place of the XCDs that have less
+          const int e = surplus0[g] + at - most;
+          for (x = 0; gap0[x + 1] <= e; ++x) {}
+          at = own[x] + e - gap0[x];
+        }
+        KdTile* list = p.kd_list + (size_t)x * p.cap;
+        const int full = have[x] / 32 * 32, c = cut[x], rows = p.QT >> c;
+        if (at < full) {
+          list[at] = KdTile{(uint16_t)tb, (uint16_t)p.QT, q};
+        } else {
+          for (int e = 0; e < 1 << c; ++e)
+            list[full + ((at - full) << c) + e] = KdTile{(uint16_t)tb, (uint16_t)(q + e * rows < toff + tm ? rows : 0), q + e * rows};
+        }
       }
     }
-    if (b < 8) {
-      int total = 0;
-      for (int pos = 0; 8 * pos < N; ++pos) total += member_ntq(b, pos);
-      p.kd_count[b] = total;
+    if (b < N && mine_short) {      // a bucket's end, behind the tiles: those of up to 128 rows, then of up to 64
+      const int g = group_of(rank), pg = rank >> 3;
+      int same = 0;
+#pragma unroll 4
+      for (int pos = 0; pos < pg; ++pos) same += sm_short_by_rank[member_rank(g, pos)] == mine_short;
+      const int left = have[g] % 32, c = cut[g], q = off + ntq * p.QT;
+      KdTile* list = p.kd_list + (size_t)g * p.cap + (have[g] - left) + (left << c);
+      const int s2_entries = c == 2 ? 2 * shorts[g][1] : shorts[g][1];
+      if (mine_short == 1) list[s2_entries + same] = KdTile{(uint16_t)b, 64, q};
+      else if (c < 2) list[same] = KdTile{(uint16_t)b, 128, q};
+      else
+        for (int e = 0; e < 2; ++e) list[2 * same + e] = KdTile{(uint16_t)b, 64, q + 64 * e};
     }
   } else {
     const int inc = inclusive_scan(ntq);
@@ -193,7 +290,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     if (b < N)
       for (int lvl = 0; lvl < ntq; ++lvl) {
         const int t = inc - ntq + lvl;
-        p.kd_list[(size_t)(t / per) * p.cap + (t % per)] = KdTile{b, off + lvl * p.QT};
+        p.kd_list[(size_t)(t / per) * p.cap + (t % per)] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + lvl * p.QT};
       }
     if (b < 8) {
       const int left = total - b * per;
@@ -222,7 +319,6 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
 // Two tilings: 256 rows, eight wavefronts, one workgroup per CU (ffn_up_pair_kernel); and, where that would leave CUs
 // without a tile, 64 rows, two wavefronts of 32 rows each, three workgroups per CU (ffn_up_kernel).
 constexpr int KD_KT = 32;         // K values per stage of the 64-row tiles
-constexpr int FU_ROWS = 256;      // rows of a tile
 constexpr int FU_ROWS_FEW = 64;   // ... where 256-row tiles would leave CUs without one
 
 template <int KS>
@@ -272,24 +368,27 @@ __device__ __forceinline__ void up_store(const f32x16 (&c)[MI], int q, int q0, i
   }
 }
 
-// The same where the hidden units went through rho32: units 32 mi + 16 h + (0..15) in c[mi], stored as 32-byte runs.
+// The same where the hidden units went through rho32: units 32 (first + mi) + 16 h + (0..15) in c[mi], stored as 32-byte
+// runs; only the first `many` of the tiles are (all of them where that is a constant, which costs nothing).
 template <int MODE, int ACT, int MI>
-__device__ __forceinline__ void up_store_runs(const f32x16 (&c)[MI], int q, int q0, int qend, int h, int Bs,
-                                              uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact,
+__device__ __forceinline__ void up_store_runs(const f32x16 (&c)[MI], int q, int q0, int qend, int first, int many, int h,
+                                              int Bs, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact,
                                               uint16_t* __restrict__ dHpre) {
   const bool live = q < qend;
   const int ql = live ? q : q0;
-  uint4* hs = reinterpret_cast<uint4*>(Hsave + (size_t)ql * Bs + 16 * h);   // 32 units further: 4 words
-  const size_t f0 = hfrag_off(ql, 16 * h, Bs);                              // 32 units further: 1024 values
+  uint4* hs = reinterpret_cast<uint4*>(Hsave + (size_t)ql * Bs + 32 * first + 16 * h);   // 32 units further: 4 words
+  const size_t f0 = hfrag_off(ql, 32 * first + 16 * h, Bs);                              // 32 units further: 1024 values
   uint4 z[MODE ? MI : 1][2];
   if (MODE)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
+      if (mi >= many) break;
       z[mi][0] = hs[4 * mi];
       z[mi][1] = hs[4 * mi + 1];
     }
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
+    if (mi >= many) break;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
       if (MODE == 0) {
@@ -468,6 +567,214 @@ struct UpPair {
 __device__ __forceinline__ int up_swz_row(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int up_swz_unit(int row) { return ((row >> 1) & 3) | ((row >> 2) & 4); }
 
+// A tile of R rows: 256 (the rule), 128 or 64 (what is left over, see plan_kernel).  A pair of wavefronts then shares R / 4 rows
+// of all units; at 64 rows 32 rows of half the 32-unit tiles.
+template <int KS, int R>
+struct UpPart {
+  static constexpr int MI = KS / 2;                                 // 32-unit tiles of the block
+  static constexpr int NI = R == 256 ? 2 : 1;                       // 32-row tiles of a wavefront
+  static constexpr int MW = R == 64 ? (MI + 1) / 2 : MI;            // ... and its 32-unit tiles
+  static constexpr int STAGE = (KS * 16 + R) * 128;                 // bytes
+  static constexpr int FIT = UpPair<KS>::SMEM / STAGE;
+  static constexpr int SLOTS = FIT < 8 ? FIT : 8;                   // (what a small stage leaves free: copies further ahead)
+};
+
+// One tile of R rows, from q0, of bucket b.
+template <int MODE, int ACT, int KS, bool EXT, int R>
+__device__ __forceinline__ void up_pair_tile(
+    const uint16_t* __restrict__ Wa, const uint16_t* __restrict__ Act, int b, int q0, int qend,
+    const int32_t* __restrict__ tok, int Bs, int d, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact,
+    uint16_t* __restrict__ dHpre, const uint16_t* __restrict__ Xe, const uint16_t* __restrict__ We) {
+  typedef UpPart<KS, R> Part;
+  constexpr int UNITS = KS * 16, MI = Part::MI, NI = Part::NI, MW = Part::MW, SLOTS = Part::SLOTS, STAGE = Part::STAGE;
+  constexpr int PA = 2 * KS;                           // copies of the weight rows of a stage (8 rows each)
+  constexpr int NA = (PA + 7) / 8, NB = R / 64, NP = NA + NB;   // copies of a wavefront per stage
+  extern __shared__ uint4 fu_smem[];
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int grp = wave >> 2, rw = wave & 3;
+  const int row0 = R == 64 ? (rw & 1) * 32 : rw * (R / 4);      // first row of the pair
+  const int mi0 = R == 64 ? (rw >> 1) * MW : 0;                 // its first unit tile
+  const uint32_t lds0 = (uint32_t)(uintptr_t)fu_smem;
+  const char* ring = reinterpret_cast<const char*>(fu_smem);
+  const int nkd = d / 64, nk = nkd + (EXT ? 1 : 0), klast = nk - 1;   // (EXT, low-rank adapters: one stage more)
+  // (lane roles from an opaque thread id: as loop invariants they would be kept, spilled, across the tiles)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, i = lane & 31, h = lane >> 5;
+  // fragment addresses: chunk 2 s + h of the lane's hidden unit / bucket row (and 32, 64, ... further); this
+  // wavefront's K-steps are s = 2 grp, 2 grp + 1
+  uint32_t foff_a[2], foff_b[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int ch = 2 * (2 * grp + s) + h;
+    foff_a[s] = (uint32_t)(rho32(i) * 128 + ((ch ^ up_swz_unit(rho32(i))) << 4));
+    foff_b[s] = (uint32_t)(i * 128 + ((ch ^ up_swz_row(i)) << 4));
+  }
+  // DMA: instruction p of a stage fills rows 8 p .. 8 p + 7; lane L row L / 8, physical chunk L % 8.
+  const uint16_t* arow[NA];
+  const uint16_t* brow[NB];
+  int urow[NA], apiece[NA], tq[NB];
+#pragma unroll
+  for (int j = 0; j < NA; ++j) {
+    apiece[j] = (wave * NA + j) % PA;   // (surplus instructions repeat one: same bytes to the same place)
+    const int row = apiece[j] * 8 + (lane >> 3);
+    urow[j] = b * Bs + row;
+    arow[j] = Wa + (size_t)urow[j] * d + (((lane & 7) ^ up_swz_unit(row)) << 3);
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int row = (wave * NB + j) * 8 + (lane >> 3);
+    tq[j] = tok[(q0 + row < qend) ? q0 + row : q0];
+    brow[j] = Act + (size_t)tq[j] * d + (((lane & 7) ^ up_swz_row(row)) << 3);
+  }
+  auto issue_piece = [&](int slot, int kt, int piece) {
+    const uint32_t base = lds0 + (uint32_t)(slot * STAGE);
+    const bool ext = EXT && kt >= nkd;
+    if (piece < NA) {
+      const int j = piece;
+      const int ch8 = ((lane & 7) ^ up_swz_unit(apiece[j] * 8 + (lane >> 3))) << 3;
+      dma16(ext ? We + (size_t)urow[j] * 64 + ch8 : arow[j] + kt * 64,
+            __builtin_amdgcn_readfirstlane(base + (uint32_t)(apiece[j] * 1024)));
+    } else {
+      const int j = piece - NA;
+      const int ch8 = ((lane & 7) ^ up_swz_row((wave * NB + j) * 8 + (lane >> 3))) << 3;
+      dma16(ext ? Xe + (size_t)tq[j] * 64 + ch8 : brow[j] + kt * 64,
+            __builtin_amdgcn_readfirstlane(base + (uint32_t)(UNITS * 128 + (wave * NB + j) * 1024)));
+    }
+  };
+  bf16x8 a[2][MW], bb[2][NI];
+  auto read_frags = [&](int slot) {
+    const char* st = ring + slot * STAGE;
+    const char* bt = st + UNITS * 128 + row0 * 128;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int mi = 0; mi < MW; ++mi) {
+        const int at = R == 64 ? min(mi0 + mi, MI - 1) : mi;   // (odd count of unit tiles: the second half repeats the last)
+        a[s][mi] = *reinterpret_cast<const bf16x8*>(st + foff_a[s] + at * 4096);
+      }
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni) bb[s][ni] = *reinterpret_cast<const bf16x8*>(bt + foff_b[s] + ni * 4096);
+    }
+  };
+  f32x16 acc[MW][NI];
+#pragma unroll
+  for (int mi = 0; mi < MW; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+  // the products of the fragments in registers, with stage min(kf, klast) copied into `slot` behind them
+  auto multiply = [&](bool fill, int slot, int kf) {
+    constexpr int M = 2 * MW * NI;                  // MFMAs
+    constexpr int C0 = M >= NP + 4 ? 4 : 0;         // first one with a copy behind it
+    const int kfill = kf < klast ? kf : klast;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int mi = 0; mi < MW; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][mi], bb[s][ni], acc[mi][ni], 0, 0, 0);
+          const int m = (s * MW + mi) * NI + ni;
+          if (fill && m >= C0 && m < C0 + NP) {
+            issue_piece(slot, kfill, m - C0);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+    if (fill)
+#pragma unroll
+      for (int p = M - C0; p < NP; ++p) issue_piece(slot, kfill, p);   // (small tiles: fewer MFMAs than copies)
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  __builtin_amdgcn_s_barrier();  // LDS of the previous tile is free
+#pragma unroll
+  for (int st = 0; st < SLOTS - 1; ++st)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) issue_piece(st, klast < st ? klast : st, p);
+  wait_vmcnt<(SLOTS - 2) * NP>();
+  // Phase A of stage kt (after the first barrier): wavefronts 0-3 read it, 4-7 multiply stage kt - 1; phase B: the
+  // other way round.  Each sends its copies of stage kt + SLOTS - 1 behind its own products; at the end of
+  // phase B its copies of stage kt + 1 have landed.
+  int slot = 0, fill = SLOTS - 1;
+  auto step = [&] {
+    slot = slot + 1 == SLOTS ? 0 : slot + 1;
+    fill = fill + 1 == SLOTS ? 0 : fill + 1;
+  };
+  if (grp == 0) {
+    for (int kt = 0; kt < nk; ++kt) {
+      __builtin_amdgcn_s_barrier();
+      read_frags(slot);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      multiply(true, fill, kt + SLOTS - 1);
+      wait_vmcnt<(SLOTS - 2) * NP>();
+      step();
+    }
+  } else {
+    for (int kt = 0; kt < nk; ++kt) {
+      __builtin_amdgcn_s_barrier();
+      if (kt > 0) {
+        multiply(true, fill, kt + SLOTS - 1);
+      } else {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) issue_piece(fill, klast < SLOTS - 1 ? klast : SLOTS - 1, p);
+      }
+      __builtin_amdgcn_s_barrier();
+      read_frags(slot);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      wait_vmcnt<(SLOTS - 2) * NP>();
+      step();
+    }
+    multiply(false, 0, 0);
+  }
+  wait_vmcnt<0>();               // the trailing copies (repeats of the last stage) are done too
+  __builtin_amdgcn_s_barrier();  // ... everyone's: the ring is free
+  // The two sums of a pair are added: wavefront w finishes the first KEEP of its 32 x 32 tiles (R = 256: all units of rows
+  // 0-31; else the first half of the unit tiles), w + 4 the rest; each hands the other its sums of the other's.
+  f32x4* xch = reinterpret_cast<f32x4*>(fu_smem) + lane;
+  constexpr int TILES = MW * NI, KEEP = (TILES + 1) / 2;
+  // tile t: R = 256 unit tile t % MW of rows 32 (t / MW); else unit tile t
+#pragma unroll
+  for (int t = 0; t < KEEP; ++t) {
+    constexpr int last = TILES - 1;
+    const int give0 = KEEP + t < TILES ? KEEP + t : last, give1 = t;   // what wavefronts w / w + 4 hand over
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = grp ? acc[give1 % MW][give1 / MW][4 * g + e] : acc[give0 % MW][give0 / MW][4 * g + e];
+      xch[((rw * 2 + (grp ^ 1)) * KEEP * 4 + t * 4 + g) * 64] = o;
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  f32x16 c[KEEP];
+#pragma unroll
+  for (int t = 0; t < KEEP; ++t) {
+    constexpr int last = TILES - 1;
+    const int mine0 = t, mine1 = KEEP + t < TILES ? KEEP + t : last;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 o = xch[((rw * 2 + grp) * KEEP * 4 + t * 4 + g) * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        c[t][4 * g + e] = (grp ? acc[mine1 % MW][mine1 / MW][4 * g + e] : acc[mine0 % MW][mine0 / MW][4 * g + e]) + o[e];
+    }
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  if (R == 256) {
+    up_store_runs<MODE, ACT, KEEP>(c, q0 + row0 + grp * 32 + i, q0, qend, 0, MI, h, Bs, Hsave, Hact, dHpre);
+  } else {
+    // (an odd count of tiles: what is listed behind the last one is not stored)
+    const int mine = mi0 + (grp ? KEEP : 0), many = min((grp ? TILES - KEEP : KEEP), MI - mine);
+    up_store_runs<MODE, ACT, KEEP>(c, q0 + row0 + i, q0, min(qend, q0 + R), mine, many, h, Bs, Hsave, Hact, dHpre);
+  }
+}
+
 // Registers: 254 of 256 at 128 units.  With the adapters' stage (EXT) 17 more are wanted there and spilled, all of them once
 // per tile around the K loops, none inside; handing the stage over once per tile instead of choosing per copy spilled 13 to
 // 340.
@@ -477,179 +784,16 @@ __global__ __launch_bounds__(512, 2) void ffn_up_pair_kernel(
     const int32_t* __restrict__ kd_count, const KdTile* __restrict__ kd_list, int cap, const int32_t* __restrict__ tok,
     int Bs, int d, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact, uint16_t* __restrict__ dHpre,
     const uint16_t* __restrict__ Xe, const uint16_t* __restrict__ We) {
-  typedef UpPair<KS> Tile;
-  constexpr int MI = KS / 2, SLOTS = Tile::SLOTS, STAGE = Tile::STAGE;
-  constexpr int PA = 2 * KS;                           // copies of the weight rows of a stage (8 rows each)
-  constexpr int NA = (PA + 7) / 8, NB = 4, NP = NA + NB;   // copies of a wavefront per stage
-  extern __shared__ uint4 fu_smem[];
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int grp = wave >> 2, rw = wave & 3;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)fu_smem;
-  const char* ring = reinterpret_cast<const char*>(fu_smem);
-  const int nkd = d / 64, nk = nkd + (EXT ? 1 : 0), klast = nk - 1;   // (EXT, low-rank adapters: one stage more)
   const int xcd = blockIdx.x & 7, wg_per_xcd = gridDim.x >> 3;
   const int count = kd_count[xcd];
-
   for (int slot_id = blockIdx.x >> 3; slot_id < count; slot_id += wg_per_xcd) {
     const KdTile tile = kd_list[(size_t)xcd * cap + slot_id];
-    const int b = tile.bucket, q0 = tile.q0;
-    const int qend = offsets[b + 1];
-    // (lane roles from an opaque thread id: as loop invariants they would be kept, spilled, across the tiles)
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    const int lane = tid & 63, i = lane & 31, h = lane >> 5;
-    // fragment addresses: chunk 2 s + h of the lane's hidden unit / bucket row (and 32, 64, ... further); this
-    // wavefront's K-steps are s = 2 grp, 2 grp + 1
-    uint32_t foff_a[2], foff_b[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int ch = 2 * (2 * grp + s) + h;
-      foff_a[s] = (uint32_t)(rho32(i) * 128 + ((ch ^ up_swz_unit(rho32(i))) << 4));
-      foff_b[s] = (uint32_t)(i * 128 + ((ch ^ up_swz_row(i)) << 4));
-    }
-    // DMA: instruction p of a stage fills rows 8 p .. 8 p + 7; lane L row L / 8, physical chunk L % 8.
-    const uint16_t* arow[NA];
-    const uint16_t* brow[NB];
-    int urow[NA], apiece[NA], tq[NB];
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      apiece[j] = (wave * NA + j) % PA;   // (surplus instructions repeat one: same bytes to the same place)
-      const int row = apiece[j] * 8 + (lane >> 3);
-      urow[j] = b * Bs + row;
-      arow[j] = Wa + (size_t)urow[j] * d + (((lane & 7) ^ up_swz_unit(row)) << 3);
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int row = (wave * NB + j) * 8 + (lane >> 3);
-      tq[j] = tok[(q0 + row < qend) ? q0 + row : q0];
-      brow[j] = Act + (size_t)tq[j] * d + (((lane & 7) ^ up_swz_row(row)) << 3);
-    }
-    auto issue_piece = [&](int slot, int kt, int piece) {
-      const uint32_t base = lds0 + (uint32_t)(slot * STAGE);
-      const bool ext = EXT && kt >= nkd;
-      if (piece < NA) {
-        const int j = piece;
-        const int ch8 = ((lane & 7) ^ up_swz_unit(apiece[j] * 8 + (lane >> 3))) << 3;
-        dma16(ext ? We + (size_t)urow[j] * 64 + ch8 : arow[j] + kt * 64,
-              __builtin_amdgcn_readfirstlane(base + (uint32_t)(apiece[j] * 1024)));
-      } else {
-        const int j = piece - NA;
-        const int ch8 = ((lane & 7) ^ up_swz_row(j * 8 + (lane >> 3))) << 3;
-        dma16(ext ? Xe + (size_t)tq[j] * 64 + ch8 : brow[j] + kt * 64,
-              __builtin_amdgcn_readfirstlane(base + (uint32_t)(Tile::UNITS * 128 + (wave * NB + j) * 1024)));
-      }
-    };
-    bf16x8 a[2][MI], bb[2][2];
-    auto read_frags = [&](int slot) {
-      const char* st = ring + slot * STAGE;
-      const char* bt = st + Tile::UNITS * 128 + rw * 64 * 128;
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) a[s][mi] = *reinterpret_cast<const bf16x8*>(st + foff_a[s] + mi * 4096);
-#pragma unroll
-        for (int ni = 0; ni < 2; ++ni) bb[s][ni] = *reinterpret_cast<const bf16x8*>(bt + foff_b[s] + ni * 4096);
-      }
-    };
-    f32x16 acc[MI][2];
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
-    // the products of the fragments in registers, with stage min(kf, klast) copied into `slot` behind them
-    auto multiply = [&](bool fill, int slot, int kf) {
-      constexpr int C0 = 4 * MI >= NP + 4 ? 4 : 0;   // first MFMA with a copy behind it
-      const int kfill = kf < klast ? kf : klast;
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-          for (int ni = 0; ni < 2; ++ni) {
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][mi], bb[s][ni], acc[mi][ni], 0, 0, 0);
-            const int m = (s * MI + mi) * 2 + ni;
-            if (fill && m >= C0 && m < C0 + NP) {
-              issue_piece(slot, kfill, m - C0);
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-      if (fill)
-#pragma unroll
-        for (int p = 4 * MI - C0; p < NP; ++p) issue_piece(slot, kfill, p);   // (small blocks: fewer MFMAs than copies)
-      __builtin_amdgcn_sched_barrier(0);
-    };
-
-    __builtin_amdgcn_s_barrier();  // LDS of the previous tile is free
-#pragma unroll
-    for (int st = 0; st < SLOTS - 1; ++st)
-#pragma unroll
-      for (int p = 0; p < NP; ++p) issue_piece(st, klast < st ? klast : st, p);
-    wait_vmcnt<(SLOTS - 2) * NP>();
-    // Phase A of stage kt (after the first barrier): wavefronts 0-3 read it, 4-7 multiply stage kt - 1; phase B: the
-    // other way round.  Each sends its copies of stage kt + SLOTS - 1 behind its own products; at the end of
-    // phase B its copies of stage kt + 1 have landed.
-    int slot = 0, fill = SLOTS - 1;
-    auto step = [&] {
-      slot = slot + 1 == SLOTS ? 0 : slot + 1;
-      fill = fill + 1 == SLOTS ? 0 : fill + 1;
-    };
-    if (grp == 0) {
-      for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_barrier();
-        read_frags(slot);
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        multiply(true, fill, kt + SLOTS - 1);
-        wait_vmcnt<(SLOTS - 2) * NP>();
-        step();
-      }
-    } else {
-      for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_barrier();
-        if (kt > 0) {
-          multiply(true, fill, kt + SLOTS - 1);
-        } else {
-#pragma unroll
-          for (int p = 0; p < NP; ++p) issue_piece(fill, klast < SLOTS - 1 ? klast : SLOTS - 1, p);
-        }
-        __builtin_amdgcn_s_barrier();
-        read_frags(slot);
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        wait_vmcnt<(SLOTS - 2) * NP>();
-        step();
-      }
-      multiply(false, 0, 0);
-    }
-    wait_vmcnt<0>();               // the trailing copies (repeats of the last stage) are done too
-    __builtin_amdgcn_s_barrier();  // ... everyone's: the ring is free
-    // Wavefront w keeps rows 0-31 of the pair's 64, w + 4 rows 32-63; each hands the other its sums of the other half.
-    f32x4* xch = reinterpret_cast<f32x4*>(fu_smem) + lane;
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = grp ? acc[mi][0][4 * g + e] : acc[mi][1][4 * g + e];
-        xch[((rw * 2 + (grp ^ 1)) * MI * 4 + mi * 4 + g) * 64] = o;
-      }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    f32x16 c[MI];
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 o = xch[((rw * 2 + grp) * MI * 4 + mi * 4 + g) * 64];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) c[mi][4 * g + e] = (grp ? acc[mi][1][4 * g + e] : acc[mi][0][4 * g + e]) + o[e];
-      }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    up_store_runs<MODE, ACT, MI>(c, q0 + rw * 64 + grp * 32 + i, q0, qend, h, Bs, Hsave, Hact, dHpre);
+    const int b = tile.bucket, q0 = tile.q0, qend = offsets[b + 1];
+#define SPT_TILE(R) up_pair_tile<MODE, ACT, KS, EXT, R>(Wa, Act, b, q0, qend, tok, Bs, d, Hsave, Hact, dHpre, Xe, We)
+    if (tile.rows == FU_ROWS) SPT_TILE(256);
+    else if (tile.rows == 128) SPT_TILE(128);
+    else if (tile.rows == 64) SPT_TILE(64);        // (0: an entry without rows)
+#undef SPT_TILE
   }
 }
 
@@ -668,7 +812,7 @@ __global__ __launch_bounds__(512, 2) void ffn_up_pair_kernel(
 template <int ACT, int RT>
 __global__ __launch_bounds__(256) void ffn_up_few_rows_kernel(
     const uint16_t* __restrict__ W1, const uint16_t* __restrict__ X, const int32_t* __restrict__ offsets,
-    const int32_t* __restrict__ kd_count, const KdTile* __restrict__ kd_list, int cap, int tile_rows,
+    const int32_t* __restrict__ kd_count, const KdTile* __restrict__ kd_list, int cap,
     const int32_t* __restrict__ tok, int Bs, int d, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact) {
   constexpr int DEPTH = 4;                       // chunks in registers, DEPTH - 1 of them in flight (8: no faster)
   __shared__ float red[4][RT][16][64];
@@ -680,7 +824,7 @@ __global__ __launch_bounds__(256) void ffn_up_few_rows_kernel(
   const int chunks = d / 32, cbeg = wave * chunks / 4, cend = (wave + 1) * chunks / 4, clast = cend - 1;
   for (int slot = (int)(blockIdx.x >> 3) / slices; slot < count; slot += per_xcd) {
     const KdTile tile = kd_list[(size_t)xcd * cap + slot];
-    const int qe = min(tile.q0 + tile_rows, offsets[tile.bucket + 1]);
+    const int qe = min(tile.q0 + tile.rows, offsets[tile.bucket + 1]);
     const uint16_t* wrow = W1 + ((size_t)tile.bucket * Bs + u0 + rho32(i)) * d + 16 * h;
     for (int q0 = tile.q0; q0 < qe; q0 += 32 * RT) {
       const uint16_t* xrow[RT];
@@ -1102,6 +1246,7 @@ static size_t carve_schedule(const spt_shape_t& s, char* p, size_t o0, Schedule&
   const size_t P = (size_t)s.T * s.k;
   size_t o = o0;
   sc.kd_cap = max_row_tiles(s, kd_rows(s));
+  if (kd_rows(s) == FU_ROWS && use_narrow(s)) sc.kd_cap += 4 * 32 + (s.N + 7) / 8 * 2;   // (a last round cut into quarters, two entries per bucket's end)
   sc.border = reinterpret_cast<int32_t*>(p + o);      o += align256((size_t)s.N * 4);
   sc.kd_count = reinterpret_cast<int32_t*>(p + o);    o += align256(8 * 4);
   sc.kd_list = p + o;                                 o += align256((size_t)8 * sc.kd_cap * sizeof(KdTile));
@@ -1264,10 +1409,9 @@ static hipError_t launch_up_t(const spt_shape_t& s, const uint16_t* Wa, const ui
 // The forward GEMM of a batch with few rows per bucket (see ffn_up_few_rows_kernel).
 static hipError_t launch_up_few_rows(const spt_shape_t& s, const uint16_t* W1, const uint16_t* X, const int32_t* offsets,
                                      const Schedule& sc, uint16_t* Hsave, uint16_t* Hact, hipStream_t st) {
-  const int rows = kd_rows(s);
-  const int grid = (max_row_tiles(s, rows) + 7) / 8 * 8 * (s.Bs / 32);   // (an XCD with more tiles than its share takes more rounds)
+  const int grid = (max_row_tiles(s, kd_rows(s)) + 7) / 8 * 8 * (s.Bs / 32);   // (an XCD with more tiles than its share takes more rounds)
   const bool one = (int64_t)s.T * s.k <= (int64_t)24 * s.N;
-#define SPT_FEW(ACT, RT) ffn_up_few_rows_kernel<ACT, RT><<<grid, 256, 0, st>>>(W1, X, offsets, sc.kd_count, static_cast<const KdTile*>(sc.kd_list), sc.kd_cap, rows, sc.tok, s.Bs, s.d, Hsave, Hact)
+#define SPT_FEW(ACT, RT) ffn_up_few_rows_kernel<ACT, RT><<<grid, 256, 0, st>>>(W1, X, offsets, sc.kd_count, static_cast<const KdTile*>(sc.kd_list), sc.kd_cap, sc.tok, s.Bs, s.d, Hsave, Hact)
   if (s.act == SPT_ACT_GELU) { if (one) SPT_FEW(0, 1); else SPT_FEW(0, 2); }
   else                       { if (one) SPT_FEW(1, 1); else SPT_FEW(1, 2); }
 #undef SPT_FEW

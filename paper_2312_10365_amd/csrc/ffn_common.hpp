@@ -26,8 +26,9 @@ __device__ __forceinline__ size_t hval_off(int q, int u, int Bs) {
   return FRAG ? hfrag_off(q, u, Bs) : (size_t)q * Bs + u;
 }
 
-// One row tile of a bucket in an XCD's run order: bucket id and first sorted position.
-struct KdTile { int32_t bucket, q0; };
+// One row tile of a bucket in an XCD's run order: bucket id (below 1024), rows (at most: the bucket may end before) and first
+// sorted position.
+struct KdTile { uint16_t bucket, rows; int32_t q0; };
 
 // Run table.  For token range r (tokens r R .. r R + R - 1) and bucket b the rows of the bucket
 // that belong to the range are one contiguous run of sorted positions (inside a bucket the token

@@ -459,3 +459,43 @@ def test_few_rows_a_bucket_but_for_one(dims):
     s = gen.custom_shape(T, d, N, Bs, k, seed=T + N, zipf_bias=True, w_std=0.05, wr_std=0.05)
     _, (offsets, _, _), _ = full_parity(s, f"one large bucket {dims}")
     assert np.diff(offsets.cpu().numpy()).max() > 2 * rows, "the case is meant to have a bucket of more than two row tiles"
+
+
+def routing_with_bucket_sizes(sizes, T, k):
+    """idx[T, k] whose buckets have exactly these sizes (sum T k, none above T): every token takes the k fullest."""
+    left = np.array(sizes)
+    idx = np.empty((T, k), dtype=np.int32)
+    for t in range(T):
+        idx[t] = np.sort(np.argsort(-left, kind="stable")[:k])
+        left[idx[t]] -= 1
+    assert not left.any()
+    return idx
+
+
+# Row tiles of 256 rows and what is left of a round of them: whole buckets several XCDs share, bucket ends of up to 64 and 128
+# rows, a last round cut into halves (10 tiles an XCD) and quarters (4), buckets without rows.
+TILE_EDGES = [2048, 1700, 1500, 1025, 1024, 900, 769, 768, 640, 513, 512, 511, 400, 385, 384, 383, 330, 321, 320, 319, 300,
+              257, 256, 255, 200, 193, 192, 191, 150, 129, 128, 127, 100, 65, 64, 63, 33, 32, 31, 1]
+
+
+@pytest.mark.parametrize("Bs", [32, 64, 96, 128])
+@pytest.mark.parametrize("sizes", [TILE_EDGES + [0] * 80 + [25] * 8, [300] * 128, [256] * 80 + [90] * 48, [256] * 32 + [40] * 96],
+                         ids=["edges", "ends", "halves", "quarters"])
+def test_row_tiles_of_a_last_round(sizes, Bs):
+    k, N = 8, len(sizes)
+    sizes = list(sizes)
+    sizes[-1] += -sum(sizes) % k
+    T = sum(sizes) // k
+    s = gen.custom_shape(T, 64, N, Bs, k, seed=N + Bs, act=spt.ACT_RELU if Bs == 64 else spt.ACT_GELU, w_std=0.1)
+    inp = gen.make_inputs(s)
+    dv = Dev(inp)
+    g_idx = routing_with_bucket_sizes(sizes, T, k)
+    offsets, perm, inv, (o_off, o_perm, o_inv) = check_bucket(dv, torch.from_numpy(g_idx).cuda(), g_idx, s.name)
+    Y, Hsave, dX, dW1, dW2 = run_gpu_ffn(dv, offsets, perm, inv)
+    a = (inp.f32("X"), inp.f32("W1"), inp.f32("W2"))
+    oY, oH = oracle.ffn_fwd(*a, g_idx, s.act)
+    odX, _ = oracle.ffn_bwd_dx(*a, inp.f32("dY"), g_idx, s.act)
+    odW1, odW2 = oracle.ffn_bwd_dw(*a, inp.f32("dY"), g_idx, s.act)
+    for name, got, ref in (("Hsave", Hsave, oracle.to_bucket_order(oH, o_perm)), ("Y", Y, oY), ("dX", dX, odX),
+                           ("dW1", dW1, odW1), ("dW2", dW2, odW2)):
+        check(s.name, name, got.float().cpu().numpy(), ref)
