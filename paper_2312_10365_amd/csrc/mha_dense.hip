@@ -155,31 +155,42 @@ __device__ __forceinline__ u32x4 tr_frag(const char* p) {
 //            G2 fragments in registers; the key groups' partial products are added through LDS in
 //            group order.
 // STAT: the sequence is one chunk, G1 and G2 fragments stay in registers for all of the
-// workgroup's query blocks.  Otherwise a workgroup does one block and walks the chunks.
+// workgroup's query blocks.  Otherwise a workgroup does one block and walks the keys twice: in chunks of kc for the
+// scores, the next chunk's G1 fragments requested a gather ahead, and in chunks of PC for the second product, whose
+// rows of G2 are copied into LDS behind the tile of weights while the chunk before is multiplied.  Two of these workgroups share a
+// CU, so LDS (80 KiB each) sets PC, and 128 registers per lane kc.
 // PLANES: an entry is split on its way into the tile, a word with the first two parts and a plane of halves with
 // the third (6 bytes per key and query).  Else the tile holds the weights and what the products read is split, n / L
 // times as many: cheaper only where the larger tile would cost the second workgroup of the CU (64-wide heads, 512 keys).
 // 128-wide heads, 512 keys: 219 / 214 us splitting behind the tile, 211 / 205 in front of it.
 // No unit is saturated: at 64-wide heads, 512 keys, the vector units issue in 60 % of the cycles, LDS is active in as many,
 // the matrix cores in 24 %; what remains are the waits between the phases of a block.
-// us, forward / backward, S 512, n 512, L 64: 127 / 122 (64-wide heads), 211 / 205 (128); S 96, n 1100, L 137, 128-wide,
-// three chunks: 398 / 402.
+// us, forward / backward, S 512, n 512, L 64: 127 / 122 (64-wide heads), 211 / 205 (128).  Several chunks, with one workgroup per CU
+// and G2 fetched between barriers -> this: S 96, n 1100, L 137, 128-wide 398 / 396 -> 242 / 244; S 160, n 600, L 90
+// 223 / 218 -> 131 / 131; S 32, n 2048, L 256 374 / 388 -> 341 / 268; 64-wide, S 256, n 600, L 90 159 / 161 -> 148 / 148; S 64,
+// n 1024, L 200 92 / 132 -> 92 / 91; S 32, n 2048, L 256 174 / 234 -> 149 / 147.  (128-wide with 512 keys per chunk of scores and
+// the fragments of one tile fetched behind the other's products: 262 / 265 where 242 / 244 is; a barrier more, to start the
+// copies before the scatter: 266 / 266; 64-wide with 256 keys per chunk of scores 184 / 182 where 149 / 147 is.)
 constexpr int NW = 8, BQ = 32, NT = NW * 64;
 template <int DH, int KT>
 constexpr bool rows_planes() { return DH == 128 || KT == 1; }
 // Registers: 128 per lane (two workgroups on a CU) where that holds the fragments and the lists, 256 otherwise.  Two
 // variants of 65 to 128 entries (64-wide heads beyond 256 keys and 128-wide up to 256, backward) keep one K fragment in
 // scratch, reloaded once per block; no other variant spills.
-template <int DH, int KT, int LPL>
-constexpr int rows_waves_per_simd() { return KT * DH <= 128 && LPL <= 2 ? 4 : 2; }
+template <int DH, int KT, int LPL, bool STAT>
+constexpr int rows_waves_per_simd() { return !STAT || (KT * DH <= 128 && LPL <= 2) ? 4 : 2; }
+// Keys of a chunk of the second product where a sequence takes several: what two workgroups of a CU have LDS for.
+template <int DH>
+constexpr int rows_pv_keys() { return DH == 128 ? 160 : 256; }
 
 template <int DH, int KT, int KG, int LPL, bool BWD, bool STAT>
-__global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_rows_kernel(
+__global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL, STAT>())) void mha_rows_kernel(
     const uint16_t* __restrict__ R, const uint16_t* __restrict__ G1, const uint16_t* __restrict__ G2,
     const int32_t* __restrict__ idx, const float* __restrict__ Ain, float* __restrict__ Wout,
     uint16_t* __restrict__ Out, int S, int n, int L, float scale, int parts, int kc) {
   constexpr int KS = DH / 16, CG = NW / KG, CT = DH / 32 / CG;
-  constexpr int VS = NW * KT * 2 / KG;                     // K-steps of 16 keys of a wavefront: kg, kg + KG, ...
+  constexpr int PC = rows_pv_keys<DH>();                   // keys of a chunk of the second product (!STAT)
+  constexpr int VS = (STAT ? NW * KT * 32 : PC) / 16 / KG; // K-steps of 16 keys of a wavefront: kg, kg + KG, ...
   constexpr int RSTRIDE = DH * 2 + 16;
   constexpr bool PLANES = rows_planes<DH, KT>();
   static_assert(BQ == 4 * NW && CT >= 1, "shape of the workgroup");
@@ -197,9 +208,12 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
   };
   int s, part;
   if (!seq_part(parts, S, s, part)) return;
-  const int ts = (PLANES ? kc + kc / 2 : kc) + 4;          // words per tile row
+  const int ts = STAT && PLANES ? kc + kc / 2 + 4 : kc + 4;   // words per tile row
+  const int pk = STAT ? kc : PC, ps = PLANES ? pk + pk / 2 + 4 : pk + 4;   // keys and words per row of the tile of weights
   float* tile = reinterpret_cast<float*>(smem);
-  const int tile_bytes = max(BQ * ts * 4, max(KG * BQ * DH * 4, kc * DH * 2));
+  const uint32_t vlds = BQ * ps * 4;                       // !STAT: a chunk of G2 behind the tile of weights
+  const int tile_bytes = STAT ? max(BQ * ts * 4, max(KG * BQ * DH * 4, kc * DH * 2))
+                              : max(max(BQ * ts * 4, KG * BQ * DH * 4), (int)vlds + PC * DH * 2);
   char* rlds = smem + tile_bytes;                          // [BQ] rows of R
   uint32_t* bad = reinterpret_cast<uint32_t*>(rlds + BQ * RSTRIDE);   // [NW] a wavefront has staged an infinity or a NaN
   uint32_t* done = bad + NW;                               // [NW] the wavefront's four queries are written already
@@ -264,8 +278,22 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
         vf[k][ct] = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
-        if (row0 < (uint32_t)kc) vf[k][ct] = as_bf16x8(tr_frag<DH>(smem + row0 * (DH * 2) + vtr[ct]));
+        if (!STAT) vf[k][ct] = as_bf16x8(tr_frag<DH>(smem + vlds + row0 * (DH * 2) + vtr[ct]));
+        else if (row0 < (uint32_t)kc) vf[k][ct] = as_bf16x8(tr_frag<DH>(smem + row0 * (DH * 2) + vtr[ct]));
       }
+    }
+  };
+
+  // !STAT: rows c0 .. c0 + PC of G2 on their way into LDS (rows past the end: the last one); they are looked at for
+  // infinities and NaN as fragments.
+  auto fetch_v = [&](int c0) {
+    constexpr int RI = 1024 / (DH * 2);                     // rows of a copy instruction
+#pragma unroll
+    for (int j = 0; j < PC / RI / NW; ++j) {
+      const uint32_t row0 = (wave * (PC / RI / NW) + j) * RI, r = row0 + lane / (DH / 8);
+      const uint32_t row = min((uint32_t)c0 + r, (uint32_t)n - 1);
+      dma16(reinterpret_cast<const char*>(g2) + row * (DH * 2) + ((lane % (DH / 8)) ^ chunk_swizzle<DH>(r)) * 16,
+            __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem + vlds + row0 * (DH * 2)));
     }
   };
 
@@ -317,8 +345,10 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
   auto sum_kept = [&](int b) {
     constexpr int C = DH / 16;                              // columns per lane
     float o[C] = {};
+    const uint32_t list = row_bytes(b);
 #pragma unroll
-    for (int v = 0; v < LPL; ++v)
+    for (int v = 0; v < LPL; ++v) {
+      const f32x4 wv = load_at<f32x4u>(Wout, list + at(v) * 4);   // (this lane's own stores)
 #pragma unroll 1
       for (uint32_t l = 0; l < 16; ++l) {
 #pragma unroll
@@ -326,16 +356,17 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
           const int src = (int)((lane & 48) + l);
           const uint32_t j = (uint32_t)__shfl(jj[v][e], src), first = 64u * v + 4 * l;
           const bool kept = j < (uint32_t)n && min(first, (uint32_t)L - 4) + e >= first;
-          const float got = __shfl(w[v][e], src), we = kept ? got : 0.f;
-          const uint32_t at = (kept ? j : 0u) * (DH * 2) + (lane & 15) * (C * 2);
+          const float got = __shfl(wv[e], src), we = kept ? got : 0.f;
+          const uint32_t from = (kept ? j : 0u) * (DH * 2) + (lane & 15) * (C * 2);
 #pragma unroll
           for (int x = 0; x < C; x += 2) {
-            const uint32_t y = kept ? load_at<uint32_t>(g2, at + x * 2) : 0u;
+            const uint32_t y = kept ? load_at<uint32_t>(g2, from + x * 2) : 0u;
             o[x] = fmaf(we, lo_bf16(y), o[x]);
             o[x + 1] = fmaf(we, hi_bf16(y), o[x + 1]);
           }
         }
       }
+    }
     const uint32_t q = b * BQ + ql;
     if (q < (uint32_t)n)
 #pragma unroll
@@ -354,16 +385,12 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
     __syncthreads();
   }
   int b = part;
-  // The workgroups of a sequence walk the same chunks of G2 at the same time: each fetches its 32 rows into their L2
-  // ahead (n 1100, 128-wide: 489 / 446 us without, 409 / 412 with).
-  u32x4 ahead = {0u, 0u, 0u, 0u};
-  if (!STAT) ahead = load_at<u32x4>(g2, min(b * BQ + tid / (DH / 8) % BQ, (uint32_t)n - 1) * (DH * 2) + tid % (DH / 8) * 16);
   if (b < nblk) { request_r(b); request_lists(b); load_k(0); store_r(); }
   __syncthreads();
 
   for (; b < nblk; b += parts) {
     fresh_roles();
-    if (BWD) request_a(b);
+    if (BWD && STAT) request_a(b);
     for (int c = 0; c < (STAT ? 1 : nch); ++c) {
       const int c0 = c * kc;
 #pragma unroll
@@ -376,6 +403,7 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
         for (int k = 0; k < KS; ++k) {
           const bf16x8 rf = as_bf16x8(*reinterpret_cast<const u32x4*>(rlds + i * RSTRIDE + h * DH + k * 16));
           acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t][k], rf, acc, 0, 0, 0);
+          if (!STAT && DH == 128 && LPL > 2 && k == KS / 2 - 1) __builtin_amdgcn_sched_barrier(0);   // (half of R's fragments at a time: registers)
         }
         f32x4* dst = reinterpret_cast<f32x4*>(tile + i * ts + (wave * KT + t) * 32 + 16 * h);
 #pragma unroll
@@ -386,18 +414,27 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
       __syncthreads();
       const float* trow = tile + ql * ts;
 #pragma unroll
-      for (int v = 0; v < LPL; ++v)
+      for (int v = 0; v < LPL; ++v) {
+        bool in[4];
+        float got[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t jl = (uint32_t)(jj[v][e] - c0);
-          const bool in = jl < (uint32_t)min(kc, n - c0);
-          const float got = trow[in ? jl : 0u];
-          if (STAT) w[v][e] = got;
-          else w[v][e] = in ? got : (c == 0 ? 0.f : w[v][e]);
+          in[e] = jl < (uint32_t)min(kc, n - c0);
+          got[e] = trow[in[e] ? jl : 0u];
         }
+        // (opaque: left to itself the compiler reads each word of a later chunk behind a branch, one LDS latency per entry)
+        if (!STAT) asm volatile("" : "+v"(got[0]), "+v"(got[1]), "+v"(got[2]), "+v"(got[3]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (STAT) w[v][e] = got[e];
+          else w[v][e] = in[e] ? got[e] : (c == 0 ? 0.f : w[v][e]);
+        }
+      }
       if (!STAT) __syncthreads();
     }
-    if (!STAT) mag = max_mag(mag, ahead);
+    if (BWD && !STAT) request_a(b);
+    if (!STAT) fetch_v(0);
     // ---- softmax / Jacobian over the list, in registers
     bool ok[LPL][4], own[LPL][4];
 #pragma unroll
@@ -458,6 +495,18 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
       for (int v = 0; v < LPL; ++v)
         store_at<f32x4u>(Wout, row + at(v) * 4, f32x4{w[v][0], w[v][1], w[v][2], w[v][3]});
     }
+    uint32_t third[LPL][2];                                 // PLANES: w holds the first two parts of a weight from here on
+    if (PLANES) {
+#pragma unroll
+      for (int v = 0; v < LPL; ++v)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          uint16_t t0, t1;
+          w[v][e] = split_bf16x3(w[v][e], t0);
+          w[v][e + 1] = split_bf16x3(w[v][e + 1], t1);
+          third[v][e / 2] = t0 | (uint32_t)t1 << 16;
+        }
+    }
 
     // ---- Out = tile x G2
     f32x16 acc[CT];
@@ -468,61 +517,66 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
         for (int v = 0; v < 16; ++v) acc[ct][v] = 0.f;
     };
     if (!STAT) clear_acc();
-    for (int c = 0; c < (STAT ? 1 : nch); ++c) {
-      const int c0 = c * kc;
+    for (int c = 0; c < (STAT ? 1 : (n + PC - 1) / PC); ++c) {
+      const int c0 = c * PC;
+      const bool last_chunk = STAT || c0 + PC >= n;
       if (!STAT) {
-        __syncthreads();
-        stage_v(c0);
-        const bool mine = __any(not_finite(mag));
-        if (lane == 0) bad[wave] = mine;
-        __syncthreads();
+        wait_vmcnt<0>();
+        __syncthreads();                                    // the chunk of G2 is there, the tile of weights has been read
         read_v();
-        if (c == nch - 1) g2_bad = any_bad();
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < VS; ++k)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) mag = max_mag(mag, __builtin_bit_cast(u32x4, vf[k][ct]));
+        if (last_chunk) {
+          const bool mine = __any(not_finite(mag));
+          if (lane == 0) bad[wave] = mine;
+        }
       }
       // this wavefront's four rows: cleared, then the list entries
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        uint4* dst = reinterpret_cast<uint4*>(tile + (4 * wave + r) * ts);
-        for (uint32_t e = lane; e < (uint32_t)(ts - 4) / 4; e += 64) dst[e] = make_uint4(0u, 0u, 0u, 0u);
+        uint4* dst = reinterpret_cast<uint4*>(tile + (4 * wave + r) * ps);
+        for (uint32_t e = lane; e < (uint32_t)(ps - 4) / 4; e += 64) dst[e] = make_uint4(0u, 0u, 0u, 0u);
       }
       wave_lds_fence();
-      float* trow = tile + ql * ts;
+      float* trow = tile + ql * ps;
 #pragma unroll
       for (int v = 0; v < LPL; ++v)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t jl = (uint32_t)(jj[v][e] - c0);
-          if (jl < (uint32_t)min(kc, n - c0)) {
-            if (PLANES) {
-              uint16_t third;
-              trow[jl] = split_bf16x3(w[v][e], third);
-              reinterpret_cast<uint16_t*>(trow + kc)[jl] = third;
-            } else {
-              trow[jl] = w[v][e];
-            }
+          if (jl < (uint32_t)min(pk, n - c0)) {
+            trow[jl] = w[v][e];
+            if (PLANES) reinterpret_cast<uint16_t*>(trow + pk)[jl] = (uint16_t)(third[v][e / 2] >> (e % 2 * 16));
           }
         }
-      if (STAT || c == nch - 1) {
+      auto finish_slow = [&]() {
         const bool slow = g2_bad || (BWD && __any(w_bad));   // uniform over the wavefront
         if (slow) sum_kept(b);
         if (lane == 0) done[wave] = slow;
-      }
+      };
+      if (STAT) finish_slow();
       if (STAT && b + parts < nblk) request_r(b + parts);
       __syncthreads();
       fresh_roles();
+      if (!STAT && !last_chunk) fetch_v(c0 + PC);
+      if (!STAT && last_chunk) {
+        g2_bad = any_bad();
+        finish_slow();
+      }
       if (STAT) clear_acc();
 #pragma unroll
       for (int k = 0; k < VS; ++k) {
         const uint32_t k0 = 16 * (kg + KG * k);
-        if (k0 >= (uint32_t)kc) continue;                   // uniform
-        const float* row = tile + i * ts + k0 + 8 * h;
+        if (STAT && k0 >= (uint32_t)kc) continue;           // uniform
+        const float* row = tile + i * ps + k0 + 8 * h;
         const u32x4* src = reinterpret_cast<const u32x4*>(row);
         bf16x8 hi, mid, lo;
         if (PLANES) {
           hi = upper_halves(src[0], src[1]);
           mid = lower_halves(src[0], src[1]);
-          lo = as_bf16x8(*reinterpret_cast<const u32x4*>(row + kc - (k0 + 8 * h) / 2));
+          lo = as_bf16x8(*reinterpret_cast<const u32x4*>(row + pk - (k0 + 8 * h) / 2));
         } else {
           split_bf16x3(src[0], src[1], hi, mid, lo);
         }
@@ -537,7 +591,7 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL>())) void mha_
     __syncthreads();
     // ---- partial products [group][query][DH], 16-byte chunks permuted by query
     fresh_roles();
-    const uint32_t groups = min(KG, kc / 16);
+    const uint32_t groups = STAT ? min(KG, kc / 16) : KG;
     float* partial = reinterpret_cast<float*>(smem);
     constexpr int PC = DH / 4;                              // 16-byte chunks per row
     if (kg < groups) {
@@ -821,7 +875,9 @@ hipError_t launch_rows(const spt_mha_shape_t& s, const uint16_t* R, const uint16
   // one chunk: the keys rounded up to a K-step of 16 per half wavefront tile; several: equal chunks
   const int nch = (s.n + KC - 1) / KC;
   const int kc = ((s.n + nch - 1) / nch + 31) / 32 * 32;
-  const size_t tile = (size_t)BQ * (kc + (rows_planes<DH, KT>() ? kc / 2 : 0) + 4) * 4, part = (size_t)KG * BQ * DH * 4, vrows = (size_t)kc * DH * 2;
+  constexpr int PC = rows_pv_keys<DH>();
+  const size_t tile = (size_t)BQ * (kc + (STAT && rows_planes<DH, KT>() ? kc / 2 : 0) + 4) * 4, part = (size_t)KG * BQ * DH * 4;
+  const size_t vrows = STAT ? (size_t)kc * DH * 2 : (size_t)BQ * (PC + (rows_planes<DH, KT>() ? PC / 2 : 0) + 4) * 4 + PC * DH * 2;
   size_t lds = tile > part ? tile : part;
   if (vrows > lds) lds = vrows;
   lds += (size_t)BQ * (DH * 2 + 16) + 2 * NW * 4;
@@ -830,7 +886,7 @@ hipError_t launch_rows(const spt_mha_shape_t& s, const uint16_t* R, const uint16
   if (STAT) {
     // workgroups per sequence: as many rounds as the chip needs times blocks per workgroup, plus
     // about one block's time for fetching the fragments
-    const int slots = 256 * (rows_waves_per_simd<DH, KT, LPL>() * 4 / NW);
+    const int slots = 256 * (rows_waves_per_simd<DH, KT, LPL, STAT>() * 4 / NW);
     int64_t best = -1;
     for (int p = 1; p <= nblk; ++p) {
       const int64_t rounds = ((int64_t)s.S * p + slots - 1) / slots, cost = rounds * ((nblk + p - 1) / p + 1);
@@ -860,7 +916,7 @@ hipError_t rows_by_shape(const spt_mha_shape_t& s, const uint16_t* R, const uint
   }
   if (s.n <= 256) SPT_ROWS(128, 1, 2, true);
   if (s.n <= 512) SPT_ROWS(128, 2, 4, true);
-  SPT_ROWS(128, 2, 4, false);
+  SPT_ROWS(128, 1, 2, false);
 #undef SPT_ROWS
 }
 

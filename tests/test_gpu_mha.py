@@ -160,6 +160,13 @@ def test_selection_longest():
     np.testing.assert_array_equal(idx.cpu().numpy(), oracle().topl(cq, ck, 256))
 
 
+# Sequences of several chunks: the second product's chunks (160 keys of 128-wide heads, 256 of 64-wide) full, one key over, one short.
+@pytest.mark.parametrize("n,dh,L", [(640, 128, 40), (641, 128, 65), (799, 128, 129), (961, 128, 200), (768, 64, 48), (769, 64, 66),
+                                    (1023, 64, 131), (1281, 64, 250)])
+def test_attention_several_chunks(n, dh, L):
+    test_whole_path_matches_oracle(custom_mha_shape(1, 1, n, dh, L, seed=n + L))
+
+
 def test_backward_is_deterministic_and_workspace_reusable():
     sh = custom_mha_shape(2, 2, 200, 64, 40, seed=21)
     inp = make_mha_inputs(sh)
