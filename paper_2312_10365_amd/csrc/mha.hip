@@ -6,7 +6,7 @@
 // every query gathers its own 128/256-byte rows through its index list here: coalesced rows, LDS
 // residency and the 64-lane wavefront.
 //
-//   pq_assign_kernel        one thread per (vector, codebook): fused distance + argmin, codebooks in LDS
+//   pq_assign_kernel        a matrix-core product per 16 vectors and codebook, fused argmin; near ties measured exactly
 //   topl_lane_kernel        Algorithm 3 bit-sliced, two or four LANES per query: inverted code table in LDS,
 //                           carry-save score planes for 32 keys at a time, rows staged in LDS
 //   seq_dots_kernel         one workgroup per sequence, gathered tensor resident in LDS: logits +
@@ -20,6 +20,9 @@
 //                           one also in front of the dense key side where few of more than 512 keys are kept
 #include <math.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "mha_host.hpp"
 #include "profile.hpp"
 #include "spt_device.hpp"
@@ -29,7 +32,6 @@ namespace {
 
 constexpr int kDp = 8;          // dimensions per codeword (section 5.1)
 constexpr int kMaxE = 16;       // codewords per codebook
-constexpr int kCbPad = 4;       // floats of padding between codebooks in LDS (bank spread)
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -49,43 +51,197 @@ __device__ __forceinline__ float wave_sum(float v) {
 }
 
 // ---------------------------------------------------------------- Algorithm 2, lines 2-3
+// The nearest codeword is the one with the largest x . c - |c|^2 / 2.  For 16 vectors and the 16 codewords of a codebook that
+// is three MFMAs, one per bf16 part of the fp32 codeword (x is bf16 as it comes, so every product is exact), with
+// codewords as rows, vectors as columns and the accumulator starting at -|c|^2 / 2.  K holds the sub-vectors of four codebooks, as
+// the lane groups load them; the codeword's part stands in its own codebook's quarter and zeros in the others.
+// A score's last four bits give way to the codeword's index, so a maximum carries it along.  What is lost with them, the
+// rounding of the scores and that of the distances they stand for are below kPqTie (|x|^2 + max |c|^2): 32 additions of
+// 2^-23 of at most (|x|^2 + 2 |c|^2) / 2 on either side, 2^-19 of that for the index, 10 of 2^-24 of a distance of at most
+// 2 (|x|^2 + |c|^2): together 2^-16.3 of |x|^2 + |c|^2.  A vector whose second best is nearer than that -- or with anything
+// infinite or NaN about it, which makes the test fail -- is measured again as Algorithm 2 has it: the distances in fp32, the
+// lower index on a tie.  So the codes are those of the distances, bit for bit.
+// us, distances measured one by one (256 instructions of the vector units per wavefront of them) -> this: S 512, n 512, E 16:
+// 20.1 -> 15.9 (8 codebooks), 37.5 -> 28.4 (16); S 96, n 1100 25.0 -> 17.6; S 8, n 130 7.6 -> 5.6; S 64, n 777, E 8 7.7 -> 7.9.  What
+// is left is reading X (15 us of the 28), preparing the codebooks, and the wait for both.  (One MFMA per codebook, its sub-vector in
+// all lane groups: 71, bound by 20 loads of 16 lines each per 16 vectors.)
+constexpr float kPqTie = 1.52587890625e-5f;   // 2^-16
+constexpr int kPqWaves = 8, kPqVectors = 16 * kPqWaves;   // vectors of a workgroup at a time
+
+__device__ __forceinline__ float hw_max(float a, float b) {   // (fmaxf would quiet its operands first)
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float hw_min(float a, float b) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float hw_max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+struct Top2 { float best, second; };
+__device__ __forceinline__ Top2 merge(const Top2& a, const Top2& b) {
+  return Top2{hw_max(a.best, b.best), hw_max3(hw_min(a.best, b.best), a.second, b.second)};
+}
+// Of two values per lane the first reduced over lanes l, l + 32 (l + 16) in the lower half (the even rows of 16 lanes), the
+// second in the upper half (the odd rows).
+template <bool HALVES>
+__device__ __forceinline__ Top2 fold(const Top2& a, const Top2& b) {
+  auto swap = [](float x, float y) {
+    const uint32_t u = __float_as_uint(x), v = __float_as_uint(y);
+    return HALVES ? __builtin_amdgcn_permlane32_swap(u, v, false, false) : __builtin_amdgcn_permlane16_swap(u, v, false, false);
+  };
+  const auto p = swap(a.best, b.best), q = swap(a.second, b.second);
+  return merge(Top2{__uint_as_float(p[0]), __uint_as_float(q[0])}, Top2{__uint_as_float(p[1]), __uint_as_float(q[1])});
+}
+__device__ __forceinline__ float upper_half(float x) { return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
+
 template <int M>
-__global__ __launch_bounds__(256) void pq_assign_kernel(const uint16_t* __restrict__ X,
-                                                        const float* __restrict__ C,
-                                                        uint8_t* __restrict__ codes,
-                                                        float* __restrict__ err, int n, int H, int E) {
-  constexpr int kStride = kMaxE * kDp + kCbPad;
-  __shared__ float cb[M * kStride];
-  const int s = blockIdx.y;
-  const int head = s % H;
-  for (int t = threadIdx.x; t < M * E * kDp; t += 256) {
-    const int m = t / (E * kDp), r = t - m * E * kDp;
-    cb[m * kStride + r] = C[(size_t)head * M * E * kDp + t];
+__global__ __launch_bounds__(kPqWaves * 64) void pq_assign_kernel(const uint16_t* __restrict__ X,
+                                                                  const float* __restrict__ C,
+                                                                  uint8_t* __restrict__ codes,
+                                                                  float* __restrict__ err, int n, int H, int E, int per) {
+  constexpr int Q = M / 4;                       // codebooks of a lane group: Q g .. Q g + Q - 1
+  __shared__ uint16_t parts[M][3][kMaxE][kDp];   // upper, next and last 8 bits of the codewords
+  __shared__ uint16_t none[kDp];                 // zeros
+  __shared__ float cb[M][kMaxE][kDp];
+  __shared__ float norm[M][kMaxE];               // -|c|^2 / 2
+  __shared__ float tie[M];                       // kPqTie max |c|^2
+  const int s = blockIdx.y, head = s % H, tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
+  const int first = blockIdx.x * per, end = min(n, first + per);
+  const size_t base = (size_t)s * n;
+  int v0 = first + (tid >> 6) * 16;
+  auto row = [&](int v) { return reinterpret_cast<const u32x4*>(X + (base + min(v + i, end - 1)) * (M * kDp)); };
+  u32x4 x[Q];                                    // (requested before the codebooks are prepared)
+#pragma unroll
+  for (int p = 0; p < Q; ++p) x[p] = row(v0)[Q * g + p];
+  for (int t = tid; t < M * kMaxE * kDp; t += kPqWaves * 64) {
+    const int m = t / (kMaxE * kDp), e = t / kDp % kMaxE, j = t % kDp;
+    const float c = e < E ? C[((size_t)head * M + m) * E * kDp + e * kDp + j] : 0.f;
+    const float r = c - upper_half(c);
+    cb[m][e][j] = c;
+    parts[m][0][e][j] = (uint16_t)(__float_as_uint(c) >> 16);
+    parts[m][1][e][j] = (uint16_t)(__float_as_uint(r) >> 16);
+    parts[m][2][e][j] = (uint16_t)(__float_as_uint(r - upper_half(r)) >> 16);
+  }
+  if (tid < kDp) none[tid] = 0;
+  if (tid < M) tie[tid] = 0.f;
+  __syncthreads();
+  if (tid < M * kMaxE) {
+    const int m = tid / kMaxE, e = tid % kMaxE;
+    float sq = 0.f;
+#pragma unroll
+    for (int j = 0; j < kDp; ++j) sq = fmaf(cb[m][e][j], cb[m][e][j], sq);
+    // The same codeword once more can go: the lower index has it on every tie.  (A row of 16 lanes is a codebook: hashes
+    // first.)
+    bool again = false;
+    uint32_t hash = 0u;
+#pragma unroll
+    for (int j = 0; j < kDp; ++j) hash = (hash ^ __float_as_uint(cb[m][e][j])) * 0x9E3779B1u;
+    auto compare = [&](auto shift) {
+      constexpr int o = decltype(shift)::value;
+      const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp((int)~hash, (int)hash, 0x110 + o, 0xF, 0xF, false);   // lane - o
+      if (other == hash) {
+        bool same = true;
+#pragma unroll
+        for (int j = 0; j < kDp; ++j) same &= cb[m][e - o][j] == cb[m][e][j];
+        again |= same;
+      }
+    };
+    [&]<int... O>(std::integer_sequence<int, O...>) {
+      (compare(std::integral_constant<int, O + 1>{}), ...);
+    }(std::make_integer_sequence<int, kMaxE - 1>{});
+    norm[m][e] = e < E && !again ? -0.5f * sq : -3e38f;   // (no codeword: never near the best)
+    // (non-negative: their order is that of the bits; infinite, NaN, or too large to tell: everything is near)
+    atomicMax(reinterpret_cast<uint32_t*>(&tie[m]), __float_as_uint(sq < 1e38f ? kPqTie * sq : INFINITY));
   }
   __syncthreads();
-  const int v0 = blockIdx.x * 256;
-  const int nv = min(256, n - v0);
-  const size_t base = (size_t)s * n + v0;
-  for (int t = threadIdx.x; t < nv * M; t += 256) {
-    const int m = t % M;
-    const u32x4 raw = *reinterpret_cast<const u32x4*>(X + base * (M * kDp) + (size_t)t * kDp);
-    float x[kDp];
+
+  float my_tie[Q];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) { x[2 * w] = lo_bf16(raw[w]); x[2 * w + 1] = hi_bf16(raw[w]); }
-    const float* c = cb + m * kStride;
-    float best = INFINITY;
-    int arg = 0;
-    for (int e = 0; e < E; ++e) {
-      float dist = 0.f;
+  for (int p = 0; p < Q; ++p) my_tie[p] = tie[Q * g + p];
+  for (; v0 < end; v0 += kPqVectors) {
+    const u32x4* next = row(min(v0 + kPqVectors, end - 1));
+    const bool real = v0 + i < end;
+    const size_t at = (base + (real ? v0 + i : v0)) * M + Q * g;
+    uint32_t word = 0u, again = 0u;              // this group's Q codes; a bit for each that is not decided
 #pragma unroll
-      for (int j = 0; j < kDp; ++j) {
-        const float df = x[j] - c[e * kDp + j];
-        dist = fmaf(df, df, dist);
+    for (int p = 0; p < Q; ++p) {
+      const bf16x8 xb = __builtin_bit_cast(bf16x8, x[p]);
+      Top2 t[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {              // codebook of group k
+        const int m = Q * k + p;
+        f32x4 score = *reinterpret_cast<const f32x4*>(&norm[m][4 * g]);
+#pragma unroll
+        for (int w = 0; w < 3; ++w) {
+          const bf16x8 c = *reinterpret_cast<const bf16x8*>(g == k ? &parts[m][w][i][0] : none);
+          score = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c, xb, score, 0, 0, 0);
+        }
+        float y[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[r] = __uint_as_float((__float_as_uint(score[r]) & ~15u) | (uint32_t)(4 * g + r));
+        t[k] = merge(Top2{hw_max(y[0], y[1]), hw_min(y[0], y[1])}, Top2{hw_max(y[2], y[3]), hw_min(y[2], y[3])});
       }
-      if (dist < best) { best = dist; arg = e; }   // strict: ties stay with the lower index
+      const Top2 f = fold<false>(fold<true>(t[0], t[2]), fold<true>(t[1], t[3]));   // group k: codebook Q k + p
+      float xx = my_tie[p] * (1.f / kPqTie);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) xx = dot2(x[p][w], x[p][w], xx);
+      x[p] = next[Q * g + p];
+      again |= f.best - f.second > kPqTie * xx ? 0u : 1u << p;
+      word |= (__float_as_uint(f.best) & 15u) << (8 * p);
     }
-    codes[base * M + t] = (uint8_t)arg;
-    if (err) err[base * M + t] = sqrtf(best);   // Algorithm 2, lines 4-5: the quantisation error
+    if (__any(again != 0u)) {
+#pragma unroll 1
+      for (int m = 0; m < M; ++m) {
+        const int p = m % Q, owner = m / Q;
+        if (!__any(g == owner && (again >> p & 1u))) continue;
+        const u32x4 xm = row(v0)[m];
+        float d = INFINITY;
+        int arg = 4 * g;
+#pragma unroll 1
+        for (int e = 4 * g; e < 4 * g + 4; ++e) {
+          float dist = 0.f;
+#pragma unroll
+          for (int j = 0; j < kDp; ++j) {
+            const float df = (j % 2 ? hi_bf16(xm[j / 2]) : lo_bf16(xm[j / 2])) - cb[m][e][j];
+            dist = fmaf(df, df, dist);
+          }
+          if (e < E && dist < d) { d = dist; arg = e; }   // strict: ties stay with the lower index
+        }
+#pragma unroll
+        for (int o = 16; o < 64; o <<= 1) {
+          const float od = __shfl_xor(d, o);
+          const int oa = __shfl_xor(arg, o);
+          if (od < d || (od == d && oa < arg)) { d = od; arg = oa; }
+        }
+        if (g == owner && (again >> p & 1u)) word = (word & ~(255u << (8 * p))) | (uint32_t)arg << (8 * p);
+      }
+    }
+    if (err && real) {                           // Algorithm 2, lines 4-5: the quantisation error
+#pragma unroll 1
+      for (int p = 0; p < Q; ++p) {
+        const u32x4 xm = row(v0)[Q * g + p];
+        const float* c = cb[Q * g + p][word >> (8 * p) & 15u];
+        float dist = 0.f;
+#pragma unroll
+        for (int j = 0; j < kDp; ++j) {
+          const float df = (j % 2 ? hi_bf16(xm[j / 2]) : lo_bf16(xm[j / 2])) - c[j];
+          dist = fmaf(df, df, dist);
+        }
+        err[at + p] = sqrtf(dist);
+      }
+    }
+    typedef uint32_t u32u __attribute__((aligned(1)));
+    typedef uint16_t u16u __attribute__((aligned(1)));
+    if (real) {
+      if (Q == 4) *reinterpret_cast<u32u*>(codes + at) = word;
+      else *reinterpret_cast<u16u*>(codes + at) = (uint16_t)word;
+    }
   }
 }
 
@@ -1264,15 +1420,19 @@ int spt_mha_pq_assign(const spt_mha_shape_t* shape, const void* X, const float* 
   if (rc != SPT_OK) return rc;
   if (!aligned16(X) || !aligned4(C) || !codes || (err && !aligned4(err))) return SPT_ERR_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const dim3 grid((shape->n + 255) / 256, shape->S);
+  // 512 vectors per workgroup, for what it prepares once; fewer where that would be less than two workgroups per CU.
+  int groups = (shape->n + 511) / 512;
+  while ((int64_t)groups * shape->S < 512 && groups * kPqVectors < shape->n) ++groups;
+  const int per = ((shape->n + groups - 1) / groups + kPqVectors - 1) / kPqVectors * kPqVectors;
+  const dim3 grid((shape->n + per - 1) / per, shape->S);
   {
     ScopedKernelTimer tm(kSlotMhaPq, st);
     if (shape->M == 8)
-      hipLaunchKernelGGL(pq_assign_kernel<8>, grid, dim3(256), 0, st, static_cast<const uint16_t*>(X), C, codes,
-                         err, shape->n, shape->H, shape->E);
+      hipLaunchKernelGGL(pq_assign_kernel<8>, grid, dim3(kPqWaves * 64), 0, st, static_cast<const uint16_t*>(X), C, codes,
+                         err, shape->n, shape->H, shape->E, per);
     else
-      hipLaunchKernelGGL(pq_assign_kernel<16>, grid, dim3(256), 0, st, static_cast<const uint16_t*>(X), C, codes,
-                         err, shape->n, shape->H, shape->E);
+      hipLaunchKernelGGL(pq_assign_kernel<16>, grid, dim3(kPqWaves * 64), 0, st, static_cast<const uint16_t*>(X), C, codes,
+                         err, shape->n, shape->H, shape->E, per);
   }
   return hipGetLastError() == hipSuccess ? SPT_OK : SPT_ERR_HIP;
 }

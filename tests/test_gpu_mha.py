@@ -135,6 +135,46 @@ def test_attention_tile_edges(n, dh, L):
     test_whole_path_matches_oracle(custom_mha_shape(1, 2, n, dh, L, seed=n + L))
 
 
+def nearest_in_order(X, C):
+    """Algorithm 2, line 3 as a loop: the first codeword whose distance is less than all before it (and than infinity)."""
+    best = np.full(X.shape[:-1], np.inf, dtype=np.float32); arg = np.zeros(X.shape[:-1], dtype=np.uint8)
+    with np.errstate(all="ignore"):
+        for e in range(C.shape[2]):
+            d = ((X - C[:, None, :, e, :].repeat(X.shape[0] // C.shape[0], 0)) ** 2).sum(-1, dtype=np.float32)
+            less = d < best
+            best[less] = d[less]; arg[less] = e
+    return arg
+
+
+# Ties (small integers: every distance is exact, in any order), codewords twice, all alike, huge, tiny, infinite and NaN;
+# vector counts around the 16 of a wavefront and the 128 of a workgroup.
+@pytest.mark.parametrize("kind", ("ties", "twice", "large", "small", "not_finite"))
+@pytest.mark.parametrize("S,n,dh,E", ((1, 1, 64, 16), (2, 15, 128, 16), (1, 17, 64, 3), (3, 127, 128, 1), (2, 129, 64, 16), (1, 513, 128, 7)))
+def test_assignment_where_codewords_are_equally_near(S, n, dh, E, kind):
+    rng = np.random.default_rng(n + E)
+    M = dh // 8
+    X = rng.integers(-2, 3, (S, n, M, 8)).astype(np.float32)
+    C = rng.integers(-2, 3, (1, M, E, 8)).astype(np.float32)
+    if kind == "twice":
+        C[:, :, E // 2:] = C[:, :, :E - E // 2]
+        X[:, :, ::2] = C[0, ::2, E - 1]
+    scale = {"large": 2.0 ** 62, "small": 2.0 ** -66}.get(kind, 1.0)      # squares up to 2^127; and below the smallest normal number
+    X *= scale; C *= scale
+    if kind == "not_finite":
+        X[:, ::3, 0, 5] = np.inf; X[:, 1::3, M - 1, 0] = np.nan
+        C[0, 1, 0, 2] = np.inf; C[0, 2, E - 1, 0] = np.nan; C[0, 3, :, 1] = -np.inf
+    s = mha.make_shape(S, 1, n, dh, min(n, 4), E=E)
+    err = torch.empty(S, n, M, device="cuda")
+    got = mha.pq_assign(s, torch.from_numpy(X.reshape(S, n, dh)).cuda().to(torch.bfloat16), torch.from_numpy(C).cuda(),
+                        torch.full((S, n, M), 255, dtype=torch.uint8, device="cuda"), err)
+    want = nearest_in_order(X, C)
+    if kind == "small":                       # (squares lose bits there: whatever is taken is as near, in squares of 2^-132 and less)
+        d = lambda code: ((X / scale - np.take_along_axis(C[0][None, None].repeat(n, 1).repeat(S, 0) / scale, code[..., None, None].astype(np.int64), 3)[..., 0, :]) ** 2).sum(-1)
+        assert np.abs(d(got.cpu().numpy()) - d(want)).max() <= 8 * 2.0 ** -149 / scale ** 2
+    else:
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
 # Selection: key counts around the 64-key pairs of mask words and the parts a query's keys are split into, row lengths
 # from 1 to n, one and all codes alike (every key in the top bucket), sequences of one to many workgroups.
 @pytest.mark.parametrize("E", (1, 3, 16))
