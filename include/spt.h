@@ -85,7 +85,8 @@ size_t spt_workspace_bytes(const spt_shape_t* shape, int which);
  *   idx    out  int32 [T,k]
  *   logits out  fp32 [T,N] or NULL (diagnostic copy of the fp32 logits)
  *   ws: spt_workspace_bytes(shape, SPT_WS_ROUTER) bytes (holds the logits or parts of their
- *       sums between the two kernels; not touched when `logits` is given).                               */
+ *       sums between the two kernels; not touched when `logits` is given).
+ * Without `logits` and for many tokens only what decides the ids is summed in fp64: the ids are the same.  */
 int spt_router_topk(const spt_shape_t* shape, const void* X, const float* W_r,
                     const float* b_r, int32_t* idx, float* logits, void* ws, size_t ws_bytes,
                     void* stream);

@@ -96,4 +96,29 @@ __device__ __forceinline__ bf16x8 tr_read_frag(const char* lds_lo, const char* l
   return __builtin_bit_cast(bf16x8, t);
 }
 
+__device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) { return __builtin_bit_cast(bf16x8, v); }
+
+// Halves of eight words -> an MFMA fragment.
+__device__ __forceinline__ bf16x8 pick_halves(const u32x4& a, const u32x4& b, uint32_t which) {
+  return as_bf16x8(u32x4{__builtin_amdgcn_perm(a[1], a[0], which), __builtin_amdgcn_perm(a[3], a[2], which),
+                         __builtin_amdgcn_perm(b[1], b[0], which), __builtin_amdgcn_perm(b[3], b[2], which)});
+}
+__device__ __forceinline__ bf16x8 upper_halves(const u32x4& a, const u32x4& b) { return pick_halves(a, b, 0x07060302u); }
+__device__ __forceinline__ bf16x8 lower_halves(const u32x4& a, const u32x4& b) { return pick_halves(a, b, 0x05040100u); }
+
+// fp32 as three bf16 whose sum it is: its upper half, that of what it leaves, and that of what is left then
+// (truncations, so exact down to bf16's denormals).  Eight words at once.
+__device__ __forceinline__ float less_upper_half(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
+__device__ __forceinline__ void split_bf16x3(u32x4 a, u32x4 b, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
+  auto step = [](u32x4& x) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(less_upper_half(__uint_as_float(x[e])));
+  };
+  hi = upper_halves(a, b);
+  step(a); step(b);
+  mid = upper_halves(a, b);
+  step(a); step(b);
+  lo = upper_halves(a, b);
+}
+
 }  // namespace spt

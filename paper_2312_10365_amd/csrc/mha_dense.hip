@@ -52,8 +52,6 @@ __device__ __forceinline__ void store_at(void* base, uint32_t bytes, const T& v)
   *reinterpret_cast<T*>(static_cast<char*>(base) + bytes) = v;
 }
 
-__device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) { return __builtin_bit_cast(bf16x8, v); }
-
 // Workgroup -> (sequence, part): the parts of a sequence run side by side on one XCD (sequence mod 8).
 __device__ __forceinline__ bool seq_part(int parts, int S, int& s, int& part) {
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -78,30 +76,8 @@ __device__ __forceinline__ float max_mag(float m, float x, float y) {
   return m;
 }
 
-// Halves of eight words -> an MFMA fragment.
-__device__ __forceinline__ bf16x8 pick_halves(const u32x4& a, const u32x4& b, uint32_t which) {
-  return as_bf16x8(u32x4{__builtin_amdgcn_perm(a[1], a[0], which), __builtin_amdgcn_perm(a[3], a[2], which),
-                         __builtin_amdgcn_perm(b[1], b[0], which), __builtin_amdgcn_perm(b[3], b[2], which)});
-}
-__device__ __forceinline__ bf16x8 upper_halves(const u32x4& a, const u32x4& b) { return pick_halves(a, b, 0x07060302u); }
-__device__ __forceinline__ bf16x8 lower_halves(const u32x4& a, const u32x4& b) { return pick_halves(a, b, 0x05040100u); }
-
-// fp32 as three bf16 whose sum it is: its upper half, that of what it leaves, and that of what is left then
-// (truncations: exact, see above).  Eight words in registers at once, or one on its way to the tile: the first two parts
-// in a word, the third for itself.
-__device__ __forceinline__ float less_upper_half(float x) { return x - __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
-__device__ __forceinline__ void split_bf16x3(u32x4 a, u32x4 b, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
-  auto step = [](u32x4& x) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(less_upper_half(__uint_as_float(x[e])));
-  };
-  hi = upper_halves(a, b);
-  step(a); step(b);
-  mid = upper_halves(a, b);
-  step(a); step(b);
-  lo = upper_halves(a, b);
-}
-__device__ __forceinline__ float split_bf16x3(float w, uint16_t& third) {
+// One weight on its way to the tile: the first two parts in a word, the third for itself.
+__device__ __forceinline__ float split_weight(float w, uint16_t& third) {
   const float r = less_upper_half(w);
   third = (uint16_t)(__float_as_uint(less_upper_half(r)) >> 16);
   return __uint_as_float(__builtin_amdgcn_perm(__float_as_uint(w), __float_as_uint(r), 0x07060302u));
@@ -502,8 +478,8 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL, STAT>())) voi
 #pragma unroll
         for (int e = 0; e < 4; e += 2) {
           uint16_t t0, t1;
-          w[v][e] = split_bf16x3(w[v][e], t0);
-          w[v][e + 1] = split_bf16x3(w[v][e + 1], t1);
+          w[v][e] = split_weight(w[v][e], t0);
+          w[v][e + 1] = split_weight(w[v][e + 1], t1);
           third[v][e / 2] = t0 | (uint32_t)t1 << 16;
         }
     }

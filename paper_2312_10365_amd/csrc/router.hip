@@ -5,6 +5,8 @@
 // additions can move the fp64 sum, by parts in 1e-16 -- far below the fp32 rounding step.
 // The k largest keys win; equal keys go to the lower block id; ids are emitted ascending.
 //
+// Many tokens without the caller's logits: the ids come from bf16 products and fp32 sums, from fp64 ones where those
+// leave a doubt (router_near_kernel, topk_near_kernel).  Otherwise:
 // Kernel 1 (logits): fp64 matrix cores, v_mfma_f64_16x16x4_f64.  A workgroup owns 16 MT tokens x 16 NT
 // blocks and its KS wavefronts split d; their sums are added through LDS in wavefront order.
 // Operands go straight from global memory to registers: a lane reads 8
@@ -16,7 +18,7 @@
 // ties at it go to the lowest block ids: block b is selected iff fewer than k blocks b' have
 // key[b'] > key[b] or (key[b'] == key[b] and b' < b).  With at most 32 blocks one workgroup holds all
 // logits of its tokens and selects in the same launch.
-#include "spt_device.hpp"
+#include "ffn_common.hpp"
 #include "spt_host.hpp"
 #include "profile.hpp"
 
@@ -35,13 +37,9 @@ __device__ __forceinline__ uint32_t key_image(float logit, int flags) {   // lar
   const uint32_t u = (bits & 0x80000000u) ? ~bits : (bits | 0x80000000u);
   return u ? u : 1u;                       // (only a NaN with all mantissa bits set maps to 0)
 }
+// The k-th largest of the images u (block lane + 64 n; 0, below every real one, past the last block).
 template <int NPL>
-__device__ __forceinline__ void select_topk(const float (&logit)[NPL], int lane, int N, int k, int flags,
-                                            int32_t* __restrict__ out) {
-  uint32_t u[NPL];                         // 0 for lanes past N: below every real key
-#pragma unroll
-  for (int n = 0; n < NPL; ++n)
-    u[n] = lane + 64 * n < N ? key_image(logit[n], flags) : 0u;
+__device__ __forceinline__ uint32_t kth_image(const uint32_t (&u)[NPL], int k) {
   uint32_t thr = 0u;
 #pragma unroll 1
   for (int bit = 31; bit >= 0; --bit) {
@@ -51,6 +49,11 @@ __device__ __forceinline__ void select_topk(const float (&logit)[NPL], int lane,
     for (int n = 0; n < NPL; ++n) c += __popcll(__ballot(u[n] >= cand));
     if (c >= k) thr = cand;                // uniform
   }
+  return thr;
+}
+template <int NPL>
+__device__ __forceinline__ void emit_topk(const uint32_t (&u)[NPL], uint32_t thr, int lane, int k,
+                                          int32_t* __restrict__ out) {
   int above = 0;
 #pragma unroll
   for (int n = 0; n < NPL; ++n) above += __popcll(__ballot(u[n] > thr));
@@ -61,7 +64,7 @@ __device__ __forceinline__ void select_topk(const float (&logit)[NPL], int lane,
     const unsigned long long below = (1ull << lane) - 1ull;
     const unsigned long long eq = __ballot(u[n] == thr);
     const bool sel = (u[n] > thr) || (u[n] == thr && __popcll(eq & below) < need);
-    need -= min(need, __popcll(eq));
+    need -= min(need, (int)__popcll(eq));
     const unsigned long long m = __ballot(sel);
     const int pos = base + __popcll(m & below);
     if (sel) out[pos] = lane + 64 * n;
@@ -247,7 +250,383 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ log
       }
     }
   }
-  select_topk<NPL>(l, lane, N, k, flags, idx + (size_t)t * k);
+  uint32_t u[NPL];
+#pragma unroll
+  for (int n = 0; n < NPL; ++n) u[n] = lane + 64 * n < N ? key_image(l[n], flags) : 0u;
+  emit_topk<NPL>(u, kth_image<NPL>(u, k), lane, k, idx + (size_t)t * k);
+}
+
+// Many tokens, 33 to 128 blocks, only the ids wanted: the order of a token's logits rarely hangs on their last bits.  Sums
+// good to a few parts in 10^6 of |x| |w_b| settle it for 97 to 99 % of the tokens; for the rest the blocks around
+// the k-th are summed again, in fp64 as above (topk_near_kernel).  The ids are those of the fp64 logits.
+//
+// router_near_kernel: bf16 matrix cores at 29 times the fp64 rate.  X is bf16, W_r is split into three bf16 whose sum it is, so
+// the products are exact and the sums are fp32: over one stage of the d axis in the MFMA chain, the stages added outside
+// of it.  A workgroup has 128 tokens, all blocks and a part of d (gridDim = tiles x parts); its wavefronts are CTW column tiles of
+// 32 blocks x KP interleaved shares of the K-steps, so each value of W_r is loaded and split once per workgroup.  Stages
+// of 128 columns of X go through LDS, requested a stage ahead, as is W_r.
+// What a sum can be off by: every MFMA by two units in the last place of the magnitudes so far (a bound on its inner
+// additions, in whatever order), every fp32 addition by half a unit; sum |x w| <= |x| |w| over the part (x and w with
+// the squares that underflow added: `tiny`); exactly 0 where the tokens or the weights are zeros.  `reach` holds it per token
+// and part, with the largest |w| of the blocks.  Measured over d 64 to 8192: at most 0.014 of it, 0.0025 at d = 4096.
+//
+// us, both launches, fp64 -> this: T 8192, d 4096, N 128 167 -> 55; T 3001 77 -> 41; T 16384, d 1024, N 64 55 -> 33.  The fp64
+// units were busy 70 % of the time; here no unit is (T 3001: MFMA 23 %, vector units 39 % of the cycles): a workgroup's first
+// loads, its last sums and three to eight stages one after the other.  Registers (235) hold it at one workgroup per CU: the
+// next step's split among the MFMAs spilled and took 50 us where 38 is, a fixed stage without branches 45.
+constexpr int kNearTokens = 128, kNearWaves = 8, kNearStage = 8;   // tokens; wavefronts; K-steps of 16 of a stage
+template <int CTW>
+__global__ __launch_bounds__(64 * kNearWaves, 2) void router_near_kernel(
+    const uint16_t* __restrict__ X, const float* __restrict__ Wr, int T, int d, int N, int splits, float tie,
+    float* __restrict__ near, float* __restrict__ reach, float* __restrict__ Wt) {
+  constexpr int MT = kNearTokens / 32, KP = kNearWaves / CTW, JS = kNearStage / KP, NTH = 64 * kNearWaves;
+  __shared__ uint4 smem[2 * kNearTokens * 16];             // two stages: rows of 128 columns, 16-byte pieces permuted by row
+  const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), ct = wave % CTW, kp = wave / CTW;
+  const int z = blockIdx.x % splits, tile = blockIdx.x / splits, tiles = gridDim.x / splits, tok0 = tile * kNearTokens;
+  const int units = (d + 63) / 64;                         // (parts begin at whole cache lines of a token)
+  const int sbeg = 4 * (int)((int64_t)z * units / splits), send = min(4 * (int)((int64_t)(z + 1) * units / splits), d / 16);
+  const bool active = ct * 32 < N;
+  const int share = min(tiles, send - sbeg);
+
+  // pieces of a stage: row tid / 16 + 32 u, piece tid % 16
+  const int prow = tid >> 4, pcol = tid & 15;
+  const uint16_t* xbase = X + (size_t)tok0 * d;            // (one base for the workgroup, 32-bit offsets)
+  uint32_t xrow[MT];
+#pragma unroll
+  for (int u = 0; u < MT; ++u) xrow[u] = (uint32_t)min(prow + 32 * u, T - 1 - tok0) * (uint32_t)d;
+  u32x4 xn[MT];
+  float x2[MT] = {};
+  uint32_t xany[MT] = {};
+  auto request_x = [&](int s) {
+    const int c = min((sbeg + s * kNearStage) * 16 + pcol * 8, d - 8);   // (past the end: a piece nobody multiplies)
+#pragma unroll
+    for (int u = 0; u < MT; ++u) xn[u] = *reinterpret_cast<const u32x4*>(xbase + (xrow[u] + c));
+  };
+  auto store_x = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < MT; ++u) {
+      const int r = prow + 32 * u;
+      *reinterpret_cast<u32x4*>(smem + buf * (kNearTokens * 16) + r * 16 + (pcol ^ (r & 15))) = xn[u];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bf16x2 v = __builtin_bit_cast(bf16x2, (uint32_t)xn[u][e]);
+        x2[u] = __builtin_amdgcn_fdot2_f32_bf16(v, v, x2[u], false);
+        xany[u] |= xn[u][e];
+      }
+    }
+  };
+  const uint32_t wcol = 8 * h * N + min(ct * 32 + i, N - 1);
+  float wq[JS][8], w2 = 0.f;
+  uint32_t wany = 0u;
+  auto request_w = [&](int j, int step) {
+    const float* p = Wr + (size_t)min(step, send - 1) * 16 * N;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) wq[j][e] = (p + (size_t)e * N)[wcol];
+  };
+
+  f32x16 sum[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[m][v] = 0.f;
+  request_x(0);
+#pragma unroll
+  for (int j = 0; j < JS; ++j) request_w(j, sbeg + kp + KP * j);
+  store_x(0);
+  __syncthreads();
+  const int stages = (send - sbeg + kNearStage - 1) / kNearStage;
+  for (int s = 0; s < stages; ++s) {
+    const bool more = s + 1 < stages;                      // uniform
+    if (more) request_x(s + 1);
+    const int s0 = sbeg + s * kNearStage + kp;
+    if (active && s0 < send) {                             // uniform over the wavefront
+      const uint4* rows = smem + (s & 1) * (kNearTokens * 16);
+      f32x16 acc[MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[m][v] = 0.f;
+#pragma unroll
+      for (int j = 0; j < JS; ++j) {
+        const int step = s0 + KP * j;
+        if (step >= send) break;                           // uniform
+        bf16x8 part[3], xf[MT];
+        u32x4 wa, wb;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { wa[e] = __float_as_uint(wq[j][e]); wb[e] = __float_as_uint(wq[j][e + 4]); }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          w2 = fmaf(wq[j][e], wq[j][e], w2);
+          wany |= __float_as_uint(wq[j][e]);
+        }
+        // (the copy of W_r with the blocks as rows, by each tile of tokens a share of it)
+        if ((step - sbeg) % share == tile && ct * 32 + i < N) {
+          u32x4* to = reinterpret_cast<u32x4*>(Wt + (size_t)(ct * 32 + i) * d + step * 16 + 8 * h);
+          to[0] = wa;
+          to[1] = wb;
+        }
+        split_bf16x3(wa, wb, part[0], part[1], part[2]);
+        request_w(j, step + kNearStage);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const int r = 32 * m + i;
+          xf[m] = __builtin_bit_cast(bf16x8, rows[r * 16 + ((2 * (kp + KP * j) + h) ^ (r & 15))]);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+            acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[m], part[c], acc[m], 0, 0, 0);
+      }
+#pragma unroll
+      for (int m = 0; m < MT; ++m) sum[m] += acc[m];
+    }
+    if (more) store_x((s + 1) & 1);
+    __syncthreads();
+  }
+
+  // How far a token's sums over this part of d can be off (see above).
+  float* xnorm = reinterpret_cast<float*>(smem);           // [128] of the tokens
+  float* wnorm = xnorm + kNearTokens;                      // [KP][32 CTW] of the blocks
+  uint32_t* wmax = reinterpret_cast<uint32_t*>(wnorm + KP * 32 * CTW);
+  const float tiny = (float)d * 0x1p-100f;
+#pragma unroll
+  for (int u = 0; u < MT; ++u) {
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      x2[u] += __shfl_xor(x2[u], o);
+      xany[u] |= (uint32_t)__shfl_xor((int)xany[u], o);
+    }
+    if (pcol == 0) xnorm[prow + 32 * u] = xany[u] & 0x7FFF7FFFu ? x2[u] + tiny : 0.f;
+  }
+  w2 += __shfl_xor(w2, 32);
+  wany |= (uint32_t)__shfl_xor((int)wany, 32);
+  if (h == 0) wnorm[kp * (32 * CTW) + ct * 32 + i] = wany << 1 ? w2 + tiny : 0.f;
+  __syncthreads();
+  if (tid < 32 * CTW) {
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < KP; ++q) v += wnorm[q * (32 * CTW) + tid];
+    int bits = __float_as_int(v) & 0x7FFFFFFF;             // (as whole numbers: a NaN is the largest)
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) bits = max(bits, __shfl_xor(bits, o));
+    if (lane == 0) wmax[wave] = (uint32_t)bits;
+  }
+  __syncthreads();
+  if (tid < kNearTokens && tok0 + tid < T) {
+    uint32_t bits = wmax[0];
+    if (CTW > 2) bits = max(bits, wmax[1]);
+    reach[(size_t)z * T + tok0 + tid] = tie * sqrtf(xnorm[tid]) * sqrtf(__uint_as_float(bits));
+  }
+
+  // The wavefronts of a column tile add their sums up in pairs, each keeping half of the token tiles: a fixed order.
+  f32x4* red = reinterpret_cast<f32x4*>(smem);             // [wavefront][8][64], then [4]
+  int mine = 0;                                            // the first token tile kept
+#pragma unroll
+  for (int half = KP / 2, cnt = MT / 2; half >= 1; half >>= 1, cnt >>= 1) {
+    if (kp & half) {                                       // uniform: what is kept comes first
+      mine += cnt;
+#pragma unroll
+      for (int m = 0; m < cnt; ++m) {
+        const f32x16 x = sum[m];
+        sum[m] = sum[m + cnt];
+        sum[m + cnt] = x;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < cnt; ++m)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        red[(wave * 8 + m * 4 + v) * 64 + lane] =
+            f32x4{sum[m + cnt][4 * v], sum[m + cnt][4 * v + 1], sum[m + cnt][4 * v + 2], sum[m + cnt][4 * v + 3]};
+    __syncthreads();
+    const f32x4* from = red + (size_t)((kp ^ half) * CTW + ct) * (8 * 64) + lane;
+#pragma unroll
+    for (int m = 0; m < cnt; ++m)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const f32x4 x = from[(m * 4 + v) * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[m][4 * v + e] += x[e];
+      }
+  }
+  // (accumulator: column = block, rows v % 4 + 8 (v / 4) + 4 h = tokens)
+  const int b = ct * 32 + i;
+  if (b < N) {
+    float* out = near + ((size_t)z * T + tok0) * N + b;
+#pragma unroll
+    for (int m = 0; m < MT / KP; ++m)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int t = 32 * (mine + m) + (v & 3) + 8 * (v >> 2) + 4 * h;
+        if (tok0 + t < T) out[t * N] = sum[m][v];
+      }
+  }
+}
+
+// Selection from those sums, a wavefront per token.  kth - after, the distance between the k-th key and the one after, beyond
+// what both can be off by (twice `reach` and the rounding to fp32): the k largest are the right ones.  Otherwise every key
+// more than that above `after` is in, every key more than that below kth is out, and those between are summed in fp64 (x times a
+// row of the copy of W_r that the kernel above leaves: its columns are a cache line per value) and compete for the places
+// left.  Sums that are not finite leave all blocks open.  (One chain of loads and sums, 6 us for the few wavefronts that go through
+// it; all four of a workgroup on one token's blocks: 15.8 where 17.3 is at T 3001, 17.3 where 14.6 is at T 16384.)
+// Weights with a part common to all blocks leave more open: both launches at T 8192, d 4096 58 us where it is three times what
+// tells the blocks apart, 68 where 30, 91 where 100.
+template <int NPL>
+__global__ __launch_bounds__(256) void topk_near_kernel(const float* __restrict__ near, const float* __restrict__ reach,
+                                                        const float* __restrict__ Wt, const uint16_t* __restrict__ X,
+                                                        const float* __restrict__ br, int splits, int T, int d, int N,
+                                                        int k, int flags, int32_t* __restrict__ idx) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = blockIdx.x * 4 + wave;
+  if (t >= T) return;                      // whole wavefront; the kernel has no barrier
+  double sum[NPL] = {};
+  float off = 0.f;
+  for (int z0 = 0; z0 < splits; z0 += 8) {   // eight parts in flight
+    float p[8][NPL], r[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const size_t row = (size_t)min(z0 + q, splits - 1) * T + t;
+      r[q] = z0 + q < splits ? reach[row] : 0.f;
+#pragma unroll
+      for (int n = 0; n < NPL; ++n) p[q][n] = z0 + q < splits && lane + 64 * n < N ? near[row * N + lane + 64 * n] : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      off += r[q];
+#pragma unroll
+      for (int n = 0; n < NPL; ++n) sum[n] += (double)p[q][n];
+    }
+  }
+  float key[NPL];
+  uint32_t u[NPL];
+  bool finite = true;
+#pragma unroll
+  for (int n = 0; n < NPL; ++n) {
+    const int b = lane + 64 * n;
+    const float l = b < N ? (float)(sum[n] + (br ? (double)br[b] : 0.0)) : 0.f;
+    key[n] = (flags & 1) ? fabsf(l) : l;
+    u[n] = b < N ? key_image(l, flags) : 0u;
+    finite = finite && fabsf(l) < INFINITY;
+  }
+  uint32_t thr = kth_image<NPL>(u, k);
+  off = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(off)));
+  if (off != 0.f) {                        // (no error: the sums are zeros; NaN != 0)
+    auto value = [](uint32_t image) { return __uint_as_float((image & 0x80000000u) ? image & 0x7FFFFFFFu : ~image); };
+    int at_least = 0;
+    uint32_t next = 0u;                    // the largest image not selected
+#pragma unroll
+    for (int n = 0; n < NPL; ++n) {
+      at_least += (int)__popcll(__ballot(u[n] >= thr));
+      next = max(next, u[n] < thr ? u[n] : 0u);
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) next = max(next, (uint32_t)__shfl_xor((int)next, o));
+    if (at_least > k) next = thr;
+    const float kth = value(thr), after = value(next);
+    float margin = 2.f * off + 0x1p-22f * fmaxf(fabsf(kth), fabsf(after));
+    if (!__all(finite)) margin = INFINITY;
+    if (next != 0u && !(kth - after > margin)) {
+      unsigned long long open[2] = {0ull, 0ull};
+#pragma unroll
+      for (int n = 0; n < NPL; ++n) {
+        const int b = lane + 64 * n;
+        const bool in = key[n] - margin > after, out = key[n] + margin < kth;
+        open[n] = __ballot(b < N && !in && !out);
+        u[n] = b < N && in ? 0xFFFFFFFFu : 0u;
+      }
+      auto take = [&]() -> int {           // the lowest open block
+        const int n = open[0] ? 0 : 1, b = (int)__builtin_ctzll(open[n]) + 64 * n;
+        open[n] &= open[n] - 1;
+        return b;
+      };
+      const uint16_t* x = X + (size_t)t * d;
+      while (open[0] | open[1]) {          // two blocks a turn
+        const int b0 = take(), b1 = open[0] | open[1] ? take() : b0;
+        const float *w0 = Wt + (size_t)b0 * d, *w1 = Wt + (size_t)b1 * d;
+        double s0 = 0.0, s1 = 0.0;
+        for (int k0 = 8 * lane; k0 < d; k0 += 512 * 2) {
+          u32x4 xv[2];
+          f32x4 wv[2][4];
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int c = min(k0 + 512 * q, d - 8);
+            xv[q] = *reinterpret_cast<const u32x4*>(x + c);
+            wv[q][0] = *reinterpret_cast<const f32x4*>(w0 + c);
+            wv[q][1] = *reinterpret_cast<const f32x4*>(w0 + c + 4);
+            wv[q][2] = *reinterpret_cast<const f32x4*>(w1 + c);
+            wv[q][3] = *reinterpret_cast<const f32x4*>(w1 + c + 4);
+          }
+          // (all of them requested before the first is used)
+          asm volatile("" : "+v"(xv[0]), "+v"(xv[1]), "+v"(wv[0][0]), "+v"(wv[0][1]), "+v"(wv[0][2]), "+v"(wv[0][3]),
+                       "+v"(wv[1][0]), "+v"(wv[1][1]), "+v"(wv[1][2]), "+v"(wv[1][3]));
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            if (k0 + 512 * q >= d) break;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const double xe = (double)(e & 1 ? hi_bf16(xv[q][e / 2]) : lo_bf16(xv[q][e / 2]));
+              s0 = fma(xe, (double)wv[q][e / 4][e % 4], s0);
+              s1 = fma(xe, (double)wv[q][2 + e / 4][e % 4], s1);
+            }
+          }
+        }
+        // (lanes below 32 go on with the first sum, the others with the second)
+        double both = (lane < 32 ? s0 : s1) + __shfl_xor(lane < 32 ? s1 : s0, 32);
+#pragma unroll
+        for (int o = 16; o >= 1; o >>= 1) both += __shfl_xor(both, o);
+        s0 = __shfl(both, 0);
+        s1 = __shfl(both, 32);
+#pragma unroll
+        for (int n = 0; n < NPL; ++n) {
+          const int b = lane + 64 * n;
+          if (b == b0 || b == b1) u[n] = key_image((float)((b == b0 ? s0 : s1) + (br ? (double)br[b] : 0.0)), flags);
+        }
+      }
+      thr = kth_image<NPL>(u, k);
+    }
+  }
+  emit_topk<NPL>(u, thr, lane, k, idx + (size_t)t * k);
+}
+
+// Parts of d for that path, 0 for none: it costs 13 to 40 us, the more the longer a row, however few the tokens, against fp64
+// units that take 30 x 10^6 products a us.  us, fp64 / this: d 4096, N 128 T 1024 26 / 31, 2048 46 / 35; d 2048, N 64 T 2048
+// 17 / 19, 4096 28 / 23; d 1024, N 64 T 4096 18 / 18, 8192 29 / 24; d 512, N 64 T 8192 20 / 20, 16384 34 / 28; d 256, N 128
+// T 8192 25 / 26, 16384 44 / 36; d 8192, N 128 T 1024 46 / 42.  (Up to 32 blocks the fp64 kernel selects as well.)
+static int near_splits(const spt_shape_t& s) {
+  if (s.N <= 32 || s.N > 128 || (int64_t)s.T * s.N * s.d < (1ll << 28) + (1ll << 17) * s.d) return 0;
+  const int tiles = (s.T + kNearTokens - 1) / kNearTokens, units = (s.d + 63) / 64;
+  // the fewest rounds of workgroups times units of 64 columns, and about three units' time before and after them
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int p = 1; p <= 16 && (p == 1 || units / p >= 4); ++p) {
+    const int64_t rounds = ((int64_t)tiles * p + 255) / 256, cost = rounds * ((units + p - 1) / p + 3);
+    if (cost < least) { least = cost; best = p; }
+  }
+  return best;
+}
+// What a sum can be off by, as a multiple of |x| |w|: three MFMAs for each of a stage's K-steps of a wavefront, each by two units
+// in the last place of the magnitudes so far, a half for each addition of a stage, of the wavefronts and of the parts.
+static float near_tie(const spt_shape_t& s, int splits) {
+  const int steps = 4 * ((((s.d + 63) / 64) + splits - 1) / splits);
+  return (float)(48 + (steps + kNearStage - 1) / kNearStage + kNearWaves + splits) * 0x1p-24f;
+}
+// Workspace: W_r with the blocks as rows, the sums of the parts, what they can be off by.
+static size_t near_copy_floats(const spt_shape_t& s) { return (size_t)s.N * s.d; }
+static void launch_near(const spt_shape_t& s, const uint16_t* X, const float* Wr, float* ws, int splits, hipStream_t st) {
+  const int grid = (s.T + kNearTokens - 1) / kNearTokens * splits;
+  float *near = ws + near_copy_floats(s), *reach = near + (size_t)splits * s.T * s.N;
+  const float tie = near_tie(s, splits);
+  if (s.N <= 64) router_near_kernel<2><<<grid, 64 * kNearWaves, 0, st>>>(X, Wr, s.T, s.d, s.N, splits, tie, near, reach, ws);
+  else router_near_kernel<4><<<grid, 64 * kNearWaves, 0, st>>>(X, Wr, s.T, s.d, s.N, splits, tie, near, reach, ws);
+}
+template <int NPL>
+static void launch_topk_near(const spt_shape_t& s, const uint16_t* X, const float* br, const float* ws, int splits,
+                             int32_t* idx, hipStream_t st) {
+  const float *near = ws + near_copy_floats(s), *reach = near + (size_t)splits * s.T * s.N;
+  topk_near_kernel<NPL><<<(s.T + 3) / 4, 256, 0, st>>>(near, reach, ws, X, br, splits, s.T, s.d, s.N, s.k, s.flags, idx);
 }
 
 template <int NPL>
@@ -268,6 +647,7 @@ static int router_splits(const spt_shape_t& s) {
 
 size_t router_ws_bytes(const spt_shape_t& s) {
   const size_t n = (size_t)s.T * s.N;
+  if (const int near = near_splits(s)) return align256((near_copy_floats(s) + (n + s.T) * near) * sizeof(float));
   const int splits = router_splits(s);
   return align256(splits > 1 ? n * splits * sizeof(double) : n * sizeof(float));
 }
@@ -283,6 +663,18 @@ static void launch_logits(const spt_shape_t& s, const uint16_t* X, const float* 
 hipError_t run_router_topk(const spt_shape_t& s, const void* X, const float* Wr, const float* br,
                            int32_t* idx, float* logits, float* ws, hipStream_t st) {
   const uint16_t* x = static_cast<const uint16_t*>(X);
+  if (const int near = logits ? 0 : near_splits(s)) {
+    {
+      ScopedKernelTimer tm(kSlotRouter, st);
+      launch_near(s, x, Wr, ws, near, st);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    ScopedKernelTimer tm(kSlotTopk, st);
+    if (s.N <= 64) launch_topk_near<1>(s, x, br, ws, near, idx, st);
+    else launch_topk_near<2>(s, x, br, ws, near, idx, st);
+    return hipGetLastError();
+  }
   // (the caller's logits leave no workspace to split over)
   const int splits = logits ? 1 : router_splits(s);
   const bool fused = s.N <= 32 && splits == 1;
@@ -294,7 +686,7 @@ hipError_t run_router_topk(const spt_shape_t& s, const void* X, const float* Wr,
       return (int64_t)((s.T + 16 * mt - 1) / (16 * mt)) * ((s.N + 16 * nt - 1) / (16 * nt));
     };
     // The largest tile of which there are two for every CU (a wider one shares the conversions of a
-    // token's values between its blocks; measured at N = 128, d = 4096, us: T 8192 164 with 32 x 32 against
+    // token's values between its blocks; measured at N = 128, d = 4096, with logits, us: T 8192 164 with 32 x 32 against
     // 186 with 16 x 16, T 3001 87 against 75 with 16 x 32, T 24 46 against 21 with 16 x 16).
     if (fused && s.N <= 16) launch_logits<1, 1, 8, 3, true>(s, x, Wr, br, idx, l, partial, splits, st);
     else if (fused) launch_logits<1, 2, 8, 3, true>(s, x, Wr, br, idx, l, partial, splits, st);

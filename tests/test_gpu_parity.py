@@ -243,6 +243,36 @@ def test_router_many_blocks_and_ties():
     assert np.array_equal(g_idx, np.tile(np.arange(s.k, dtype=np.int32), (s.T, 1)))
 
 
+# Many tokens, ids only: fp32 sums decide where they can, fp64 ones the rest.  The ids are those of the fp64 logits, whatever is
+# close: edges of the token tiles (128), of the column tiles (32), of d's parts and stages (64, 128), first, last and
+# every block selected; blocks with the same weights, tokens of zeros, tokens and weights whose squares underflow.
+@pytest.mark.parametrize("T,d,N,k", [(16385, 320, 64, 16), (17000, 640, 33, 33), (40001, 64, 120, 7), (1537, 4096, 128, 127),
+                                     (12500, 832, 65, 1), (4096, 2048, 96, 48)])
+@pytest.mark.parametrize("kind", ["plain", "bias, magnitude", "twins", "zeros", "tiny"])
+def test_router_ids_of_many_tokens(T, d, N, k, kind):
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    X = torch.randn(T, d, generator=g, device="cuda")
+    W = 0.02 * torch.randn(d, N, generator=g, device="cuda")
+    b = 3.0 * torch.randn(N, generator=g, device="cuda") if kind == "bias, magnitude" else None
+    if kind == "twins":
+        W[:, 1::2] = W[:, 0:N - 1:2]
+    if kind in ("zeros", "tiny"):
+        X[::3] = 0.0
+    if kind == "tiny":
+        X[1::3] *= 1e-22
+        W *= 1e-10
+    X = X.bfloat16()
+    s = spt.make_shape(T, d, N, 32, k, spt.ACT_GELU, spt.FLAG_ABS_LOGIT if b is not None else 0)
+    assert spt.alloc_workspace(s, spt.WS_ROUTER).nbytes >= 4 * (N * d + T * N)     # (the sums and the weights' copy)
+    logits = torch.empty(T, N, device="cuda")
+    want = spt.router_topk(s, X, W, b, logits=logits)            # (the fp64 kernels)
+    got = spt.router_topk(s, X, W, b)
+    exact = X[:2048].double() @ W.double() + (0.0 if b is None else b.double())
+    torch.cuda.synchronize()
+    assert torch.allclose(logits[:2048].double(), exact, rtol=1e-7, atol=1e-30)
+    assert torch.equal(got, want), int((got != want).any(1).sum())
+
+
 def test_values_with_oracle_bucketing_and_determinism():
     # Feed the oracle's offsets/perm/inv to the GPU (value parity decoupled from routing),
     # and require bit-identical outputs on a second run.
