@@ -55,6 +55,10 @@ __device__ __forceinline__ float pin_vgpr(float x) {
   return x;
 }
 
+__device__ __forceinline__ uint4 pack_bf16x8(const float (&v)[8]) {
+  return make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+}
+
 // One A_EDGE x B_EDGE output tile.  b: block; a0 / n0: first A-side / B-side index; [qb, qe): the K
 // range (OP_DW: the bucket's rows) -- for the other GEMMs qe bounds the B-side rows.
 template <int OP, int ACT, int MA, int NB>
@@ -325,67 +329,104 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
       }
     return;
   }
-  uint4 zsave[(OP == OP_DH) ? NB : 1][(OP == OP_DH) ? MA : 1][2];
-  if (OP == OP_DH) {
+  if (OP == OP_DH || (OP == OP_UP && !(ACT & 2))) {
+    // Two outputs per value: likewise, two A-side tiles at a time (64 bf16 outputs of a row are a line), through rows of
+    // 256 bytes whose 16-byte pieces are permuted by row, so that no pass of an access meets a bank twice.  (The partial
+    // rows and the inference forward write half as much and gain nothing: 135 us either way, 53 -> 56.)
+    // us, low-rank pass of T 8192, d 2048, 4 blocks of 2048, k 2: up-projection 171 -> 157, dH 183 -> 171; d 4096, blocks of 2752:
+    // 363 -> 363, 396 -> 383.
+    constexpr int MP = MA / 2;                               // pairs of A-side tiles
+    const int c8 = (lane & 7) * 8, r0 = lane >> 3;           // lane's piece: rows r0 + 8 r, 8 columns from c8 on
+    uint4 zsave[(OP == OP_DH) ? NB : 1][(OP == OP_DH) ? MP : 1][4];
+    if (OP == OP_DH) {
+#pragma unroll
+      for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+        for (int mp = 0; mp < MP; ++mp)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int nidx = n0 + wn * B_HALF + ni * 32 + r0 + 8 * r, aidx = a0 + wm * A_HALF + mp * 64 + c8;
+            if (nidx < qe && aidx < a_lim)
+              zsave[ni][mp][r] = *reinterpret_cast<const uint4*>(p.Hsave + (size_t)nidx * Bs + aidx);
+          }
+    }
+    __builtin_amdgcn_s_barrier();                            // (the ring is free, as above)
+    f32x4* tbuf = reinterpret_cast<f32x4*>(smem) + wave * (32 * 16);
+    auto put = [&](int ni, int mp) {
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const f32x16& c = acc[2 * mp + m][ni];
+          tbuf[i * 16 + ((8 * m + 4 * h + e) ^ (i & 15))] = f32x4{c[4 * e], c[4 * e + 1], c[4 * e + 2], c[4 * e + 3]};
+        }
+    };
+    put(0, 0);
 #pragma unroll
     for (int ni = 0; ni < NB; ++ni) {
-      const int nidx = n0 + wn * B_HALF + ni * 32 + i;
 #pragma unroll
-      for (int mi = 0; mi < MA; ++mi) {
-        const int aidx = a0 + wm * A_HALF + mi * 32 + 16 * h;
-        if (nidx < qe && aidx < a_lim) {
-          const uint4* src = reinterpret_cast<const uint4*>(p.Hsave + (size_t)nidx * Bs + aidx);
-          zsave[ni][mi][0] = src[0];
-          zsave[ni][mi][1] = src[1];
+      for (int mp = 0; mp < MP; ++mp) {
+        wave_lds_fence();
+        f32x4 o[4][2];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) o[r][e] = tbuf[(r0 + 8 * r) * 16 + ((2 * (lane & 7) + e) ^ ((r0 + 8 * r) & 15))];
+        wave_lds_fence();
+        // (the next pair goes in behind these reads)
+        if (mp + 1 < MP) put(ni, mp + 1);
+        else if (ni + 1 < NB) put(ni + 1, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int nidx = n0 + wn * B_HALF + ni * 32 + r0 + 8 * r, aidx = a0 + wm * A_HALF + mp * 64 + c8;
+          if (nidx < qe && aidx < a_lim) {
+            const size_t at = (size_t)nidx * Bs + aidx;
+            float cv[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) cv[e] = o[r][e / 4][e % 4];
+            if (OP == OP_UP) {
+              *reinterpret_cast<uint4*>(p.Hsave + at) = pack_bf16x8(cv);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) cv[e] = act_fn<(ACT & 1)>(cv[e]);
+              *reinterpret_cast<uint4*>(p.Hact + at) = pack_bf16x8(cv);
+            } else {
+              const uint4 z = zsave[(OP == OP_DH) ? ni : 0][(OP == OP_DH) ? mp : 0][r];
+              const uint32_t zw[4] = {z.x, z.y, z.z, z.w};
+              float av[8];
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                const float x = e & 1 ? hi_bf16(zw[e / 2]) : lo_bf16(zw[e / 2]);
+                cv[e] *= act_grad<(ACT & 1)>(x);
+                av[e] = act_fn<(ACT & 1)>(x);
+              }
+              *reinterpret_cast<uint4*>(p.dHpre + at) = pack_bf16x8(cv);
+              *reinterpret_cast<uint4*>(p.Hact + at) = pack_bf16x8(av);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);  // 8 values at a time keeps the register need low
         }
       }
     }
+    return;
   }
 #pragma unroll
   for (int ni = 0; ni < NB; ++ni) {
     const int nidx = n0 + wn * B_HALF + ni * 32 + i;
-    const bool n_ok = (OP == OP_DW) ? nidx < Bs : nidx < qe;
 #pragma unroll
     for (int mi = 0; mi < MA; ++mi) {
       const int aidx = a0 + wm * A_HALF + mi * 32 + 16 * h;
       const f32x16& c = acc[mi][ni];
-      if (n_ok && aidx < a_lim) {
-        if (OP == OP_UP) {
+      if (nidx < qe && aidx < a_lim) {
+        if (OP == OP_UP) {                 // bit 1 of ACT: inference forward, nothing saved for a backward pass
           const size_t o = (size_t)nidx * Bs + aidx;
 #pragma unroll
           for (int hf = 0; hf < 2; ++hf) {  // 8 values at a time keeps the register need low
             float cv[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) cv[e] = pin_vgpr(c[8 * hf + e]);
-            if (!(ACT & 2))  // bit 1 of ACT: inference forward, nothing saved for a backward pass
-              reinterpret_cast<uint4*>(p.Hsave + o)[hf] =
-                  make_uint4(pack_bf16x2(cv[0], cv[1]), pack_bf16x2(cv[2], cv[3]),
-                             pack_bf16x2(cv[4], cv[5]), pack_bf16x2(cv[6], cv[7]));
-            reinterpret_cast<uint4*>(p.Hact + o)[hf] =
-                make_uint4(pack_bf16x2(act_fn<(ACT & 1)>(cv[0]), act_fn<(ACT & 1)>(cv[1])),
-                           pack_bf16x2(act_fn<(ACT & 1)>(cv[2]), act_fn<(ACT & 1)>(cv[3])),
-                           pack_bf16x2(act_fn<(ACT & 1)>(cv[4]), act_fn<(ACT & 1)>(cv[5])),
-                           pack_bf16x2(act_fn<(ACT & 1)>(cv[6]), act_fn<(ACT & 1)>(cv[7])));
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        } else if (OP == OP_DH) {
-          const size_t o = (size_t)nidx * Bs + aidx;
 #pragma unroll
-          for (int hf = 0; hf < 2; ++hf) {
-            float cv[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) cv[e] = pin_vgpr(c[8 * hf + e]);
-            const uint4 z = zsave[(OP == OP_DH) ? ni : 0][(OP == OP_DH) ? mi : 0][hf];
-            const uint32_t zw[4] = {z.x, z.y, z.z, z.w};
-            uint32_t gv[4], av[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float zl = lo_bf16(zw[e]), zh = hi_bf16(zw[e]);
-              gv[e] = pack_bf16x2(cv[2 * e] * act_grad<(ACT & 1)>(zl), cv[2 * e + 1] * act_grad<(ACT & 1)>(zh));
-              av[e] = pack_bf16x2(act_fn<(ACT & 1)>(zl), act_fn<(ACT & 1)>(zh));
-            }
-            reinterpret_cast<uint4*>(p.dHpre + o)[hf] = make_uint4(gv[0], gv[1], gv[2], gv[3]);
-            reinterpret_cast<uint4*>(p.Hact + o)[hf] = make_uint4(av[0], av[1], av[2], av[3]);
+            for (int e = 0; e < 8; ++e) cv[e] = act_fn<(ACT & 1)>(cv[e]);
+            reinterpret_cast<uint4*>(p.Hact + o)[hf] = pack_bf16x8(cv);
             __builtin_amdgcn_sched_barrier(0);
           }
         } else if (OP == OP_PART) {
