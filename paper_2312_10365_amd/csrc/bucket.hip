@@ -174,21 +174,24 @@ __global__ __launch_bounds__(1024) void bucket_small_kernel(const int32_t* __res
     }
   }
   __syncthreads();
-  for (int b = wave; b < N; b += 16) {                     // a wavefront per block, lanes over words
+  // 2^seg lanes over the words of a block (all 64 from 33 words on), as many blocks side by side as a wavefront then holds: few
+  // tokens are few steps, and one turn for 64 blocks where it was one each (24 tokens, 128 blocks: 7.4 -> 4.0 us).
+  const int seg = nw > 32 ? 6 : (nw > 1 ? 32 - __clz(nw - 1) : 0), width = 1 << seg, lw = lane & (width - 1);
+  for (int b0 = wave << (6 - seg); b0 < N; b0 += 16 << (6 - seg)) {
+    const int b = b0 + (lane >> seg);
     int sum = 0;
     for (int w0 = 0; w0 < nw; w0 += 64) {
-      const int w = w0 + lane;
-      const int c = w < nw ? __popc(mask[b * nwp + w]) : 0;
+      const int w = w0 + lw;
+      const int c = b < N && w < nw ? __popc(mask[b * nwp + w]) : 0;
       int incl = c;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
+      for (int o = 1; o < width; o <<= 1) {
         const int up = __shfl_up(incl, o);
-        if (lane >= o) incl += up;
+        if (lw >= o) incl += up;
       }
-      if (w < nw) pre[b * nwp + w] = (uint16_t)(sum + incl - c);
-      sum += __shfl(incl, 63);
+      if (b < N && w < nw) pre[b * nwp + w] = (uint16_t)(sum + incl - c);
+      sum += __shfl(incl, lane | (width - 1));
     }
-    if (lane == 0) tot[b] = sum;
+    if (b < N && lw == 0) tot[b] = sum;
   }
   __syncthreads();
   const int mine = tid < N ? tot[tid] : 0;

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
   }
   __shared__ int32_t wtot[16];
   if (threadIdx.x < 64) p.zero_row[threadIdx.x] = 0u;  // 256 bytes of zeros for padded K rows
-  __shared__ int32_t sm_m[1024];
+  __shared__ __align__(16) int32_t sm_m[1024];
   __shared__ int32_t sm_ntq_by_rank[1024];
   const int b = threadIdx.x;
   const int off = (b < N) ? off_sh[b] : 0;
@@ -118,18 +118,31 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
 
   sm_m[b] = m;
   __syncthreads();
-  int rank = 0;
-  if (b < N)
-    for (int o = 0; o < N; ++o) rank += (sm_m[o] > m) || (sm_m[o] == m && o < b);
+  // rank by size: as many threads per bucket as there are, at most a wavefront's, each with a share of the others, four at a time
+  // (a thread per bucket: 8.2 -> 7.0 us for the whole kernel with 24 tokens and 128 buckets, 14.6 -> 10.6 with 131072 pairs in 64)
+  const int tlog = 10 - (32 - __clz(N - 1)), tpb = 1 << tlog, tb = b >> tlog;
+  __shared__ int16_t sm_rank[1024];
+  {
+    const int share = b & (tpb - 1), step = min(tpb, 64), tm = sm_m[min(tb, 1023)];
+    int r = 0;
+    if (share < step)
+      for (int o = 4 * share; o < N; o += 4 * step) {            // (sizes past the last bucket are 0, their ids above every bucket's)
+        const int4 q = *reinterpret_cast<const int4*>(sm_m + o);
+        r += (q.x > tm || (q.x == tm && o < tb)) + (q.y > tm || (q.y == tm && o + 1 < tb)) +
+             (q.z > tm || (q.z == tm && o + 2 < tb)) + (q.w > tm || (q.w == tm && o + 3 < tb));
+      }
+    for (int o = 1; o < step; o <<= 1) r += __shfl_xor(r, o);
+    if (share == 0 && tb < N) sm_rank[tb] = (int16_t)r;
+  }
+  __syncthreads();
+  const int rank = b < N ? sm_rank[b] : 0;
   // Tiles of p.QT rows; with 256 a bucket's last rows, if they are at most 128, are listed apart (1: up to 64, 2: up to 128).
   __shared__ uint8_t sm_short_by_rank[1024];
-  __shared__ int16_t sm_rank[1024];
   const bool parts = p.QT == FU_ROWS && N >= 16 && !p.wide;
   const int end_rows = m & (p.QT - 1), mine_short = !parts || end_rows == 0 || end_rows > 128 ? 0 : end_rows > 64 ? 2 : 1;
   const int ntq = (m >> (31 - __clz(p.QT))) + (end_rows > 0 && !mine_short);   // (64 or 256: a power of two)
   if (b < N) {
     p.border[rank] = b;
-    sm_rank[b] = (int16_t)rank;
     sm_ntq_by_rank[rank] = ntq;
     sm_short_by_rank[rank] = (uint8_t)mine_short;
   }
@@ -235,7 +248,6 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
       __syncthreads();
     }
     // the tiles: as many threads per bucket as there are, a level each
-    const int tlog = 10 - (32 - __clz(N - 1)), tpb = 1 << tlog, tb = b >> tlog;
     if (tb < N) {
       const int trank = sm_rank[tb], g = group_of(trank), pg = trank >> 3, tm = sm_m[tb], toff = off_sh[tb];
       const int members = (N + 7) / 8, tn = sm_ntq_by_rank[trank];

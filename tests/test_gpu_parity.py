@@ -461,6 +461,17 @@ def test_routing_and_bucketing_launch_edges(T, d, N, k, flags):
     check_bucket(dv, idx, g_idx, tag)
 
 
+# One workgroup's bucketing: words of 32 tokens, one to a block's lanes up to more than a wavefront has (1, 2, 3, 32, 33, 65
+# words), blocks that fill a turn and one more.
+@pytest.mark.parametrize("T,N,k", [(1, 65, 65), (32, 129, 9), (33, 1024, 40), (96, 33, 5), (1000, 16, 8), (1024, 17, 7),
+                                   (1056, 8, 7), (2080, 5, 3), (4096, 2, 2)])
+def test_bucketing_by_one_workgroup(T, N, k):
+    s = gen.custom_shape(T, 64, N, 32, k, seed=T + k, zipf_bias=True, wr_std=0.2)
+    dv = Dev(gen.make_inputs(s))
+    idx, g_idx, _ = check_routing(dv, f"one workgroup T{T} N{N}")
+    check_bucket(dv, idx, g_idx, f"one workgroup T{T} N{N}")
+
+
 # Feed-forward kernels at the edges of their launch rules.
 @pytest.mark.parametrize("dims", [
     # (T, d, N, Bs, k).  Up-projection of decoding batches: one row tile up to 24 rows a bucket, two beyond, 40 and 64
