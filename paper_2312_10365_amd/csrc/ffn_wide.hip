@@ -329,12 +329,12 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
       }
     return;
   }
-  if (OP == OP_DH || (OP == OP_UP && !(ACT & 2))) {
+  if (OP == OP_DH || (OP == OP_UP && (ACT & 3) == 1)) {
     // Two outputs per value: likewise, two A-side tiles at a time (64 bf16 outputs of a row are a line), through rows of
-    // 256 bytes whose 16-byte pieces are permuted by row, so that no pass of an access meets a bank twice.  (The partial
-    // rows and the inference forward write half as much and gain nothing: 135 us either way, 53 -> 56.)
-    // us, low-rank pass of T 8192, d 2048, 4 blocks of 2048, k 2: up-projection 171 -> 157, dH 183 -> 171; d 4096, blocks of 2752:
-    // 363 -> 363, 396 -> 383.
+    // 256 bytes whose 16-byte pieces are permuted by row, so that no pass of an access meets a bank twice.
+    // us, low-rank pass of T 8192, d 2048, 4 blocks of 2048, k 2, ReLU: up-projection 171 -> 157, dH 183 -> 171; d 4096, blocks of
+    // 2752, GELU: dH 396 -> 383.  Nothing gained, so stored as they lie: the up-projection with GELU (363 -> 363, 760 tokens of
+    // d 3392 35 -> 36: the stores go out behind its arithmetic), the inference forward (53 -> 56), the partial rows (135).
     constexpr int MP = MA / 2;                               // pairs of A-side tiles
     const int c8 = (lane & 7) * 8, r0 = lane >> 3;           // lane's piece: rows r0 + 8 r, 8 columns from c8 on
     uint4 zsave[(OP == OP_DH) ? NB : 1][(OP == OP_DH) ? MP : 1][4];
@@ -417,13 +417,15 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
       const int aidx = a0 + wm * A_HALF + mi * 32 + 16 * h;
       const f32x16& c = acc[mi][ni];
       if (nidx < qe && aidx < a_lim) {
-        if (OP == OP_UP) {                 // bit 1 of ACT: inference forward, nothing saved for a backward pass
+        if (OP == OP_UP) {
           const size_t o = (size_t)nidx * Bs + aidx;
 #pragma unroll
           for (int hf = 0; hf < 2; ++hf) {  // 8 values at a time keeps the register need low
             float cv[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) cv[e] = pin_vgpr(c[8 * hf + e]);
+            if (!(ACT & 2))  // bit 1 of ACT: inference forward, nothing saved for a backward pass
+              reinterpret_cast<uint4*>(p.Hsave + o)[hf] = pack_bf16x8(cv);
 #pragma unroll
             for (int e = 0; e < 8; ++e) cv[e] = act_fn<(ACT & 1)>(cv[e]);
             reinterpret_cast<uint4*>(p.Hact + o)[hf] = pack_bf16x8(cv);

@@ -490,6 +490,15 @@ def test_ffn_launch_edges(dims):
     full_parity(gen.custom_shape(T, d, N, Bs, k, seed=T + N, w_std=0.05, wr_std=0.05), f"edges {dims}")
 
 
+# Wide blocks with ReLU, whose up-projection and dH write whole lines: whole tiles, halves and quarters of them; blocks
+# that end in the middle of a line, one and two A-side tiles before the edge.
+@pytest.mark.parametrize("dims", [(1300, 192, 2, 288, 2), (5000, 320, 2, 288, 2), (5000, 64, 2, 1056, 2), (700, 128, 3, 160, 2),
+                                  (900, 64, 2, 608, 1)], ids=str)
+def test_wide_blocks_write_whole_lines(dims):
+    T, d, N, Bs, k = dims
+    full_parity(gen.custom_shape(T, d, N, Bs, k, seed=T + N, act=spt.ACT_RELU, w_std=0.05, wr_std=0.05), f"lines {dims}")
+
+
 @pytest.mark.parametrize("dims", [
     # (T, d, N, Bs, k, rows of a tile): few rows a bucket on average, most of them in one bucket of several row tiles; one
     # and two 32-row tiles at a time
