@@ -116,14 +116,21 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     return block_inclusive_sum(v, wtot, total);
   };
 
+  __shared__ int32_t own[8], shorts[8][2];                      // per XCD: its group's tiles, and bucket ends listed apart (parts)
+  if (b < 8) { own[b] = 0; shorts[b][0] = 0; shorts[b][1] = 0; }
   sm_m[b] = m;
   __syncthreads();
   // rank by size: as many threads per bucket as there are, at most a wavefront's, each with a share of the others, four at a time
   // (a thread per bucket: 8.2 -> 7.0 us for the whole kernel with 24 tokens and 128 buckets, 14.6 -> 10.6 with 131072 pairs in 64)
   const int tlog = 10 - (32 - __clz(N - 1)), tpb = 1 << tlog, tb = b >> tlog;
   __shared__ int16_t sm_rank[1024];
-  {
-    const int share = b & (tpb - 1), step = min(tpb, 64), tm = sm_m[min(tb, 1023)];
+  int rank = 0;
+  if (N < 16) {                 // (not worth the barrier: 4.8 -> 4.5 us with 6 buckets)
+    if (b < N)
+      for (int o = 0; o < N; ++o) rank += (sm_m[o] > m) || (sm_m[o] == m && o < b);
+  } else {
+    const int need = (N + 3) >> 2, step = min(min(tpb, 64), need > 1 ? 1 << (32 - __clz(need - 1)) : 1);
+    const int share = b & (tpb - 1), tm = sm_m[min(tb, 1023)];
     int r = 0;
     if (share < step)
       for (int o = 4 * share; o < N; o += 4 * step) {            // (sizes past the last bucket are 0, their ids above every bucket's)
@@ -133,15 +140,22 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
       }
     for (int o = 1; o < step; o <<= 1) r += __shfl_xor(r, o);
     if (share == 0 && tb < N) sm_rank[tb] = (int16_t)r;
+    __syncthreads();
+    rank = b < N ? sm_rank[b] : 0;
   }
-  __syncthreads();
-  const int rank = b < N ? sm_rank[b] : 0;
   // Tiles of p.QT rows; with 256 a bucket's last rows, if they are at most 128, are listed apart (1: up to 64, 2: up to 128).
   __shared__ uint8_t sm_short_by_rank[1024];
   const bool parts = p.QT == FU_ROWS && N >= 16 && !p.wide;
   const int end_rows = m & (p.QT - 1), mine_short = !parts || end_rows == 0 || end_rows > 128 ? 0 : end_rows > 64 ? 2 : 1;
   const int ntq = (m >> (31 - __clz(p.QT))) + (end_rows > 0 && !mine_short);   // (64 or 256: a power of two)
+  // rank r goes to group r%16 (<8) or 15 - r%16: position pg = r/8 inside the group; the
+  // member at position p of group g has rank 8p + (p even ? g : 7 - g); sizes fall with p.
+  auto group_of = [&](int r) { return (r >> 3 & 1) ? 7 - (r & 7) : (r & 7); };
   if (b < N) {
+    if (parts) {
+      atomicAdd(&own[group_of(rank)], ntq);
+      if (mine_short) atomicAdd(&shorts[group_of(rank)][mine_short - 1], 1);
+    }
     p.border[rank] = b;
     sm_ntq_by_rank[rank] = ntq;
     sm_short_by_rank[rank] = (uint8_t)mine_short;
@@ -190,13 +204,10 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
       for (int lvl = 0; lvl < ntq; ++lvl) p.kd_list[inc - ntq + lvl] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + lvl * p.QT};
     if (b == N - 1) p.kd_count[0] = inc;
   } else if (N >= 16) {
-    // rank r goes to group r%16 (<8) or 15 - r%16: position pg = r/8 inside the group; the
-    // member at position p of group g has rank 8p + (p even ? g : 7 - g); sizes fall with p.
-    auto group_of = [&](int r) { return (r >> 3 & 1) ? 7 - (r & 7) : (r & 7); };
     auto member_rank = [&](int grp, int pos) { return 8 * pos + ((pos & 1) ? 7 - grp : grp); };
-    // Per XCD: its group's tiles and the bucket ends listed apart; then, for lists that one workgroup per CU walks in rounds
-    // (parts), the same number of tiles for every XCD, and how those of a last, unfilled round are cut.
-    __shared__ int32_t own[8], surplus0[8], gap0[9], have[8], cut[8], shorts[8][2];
+    // For lists that one workgroup per CU walks in rounds (parts): the same number of tiles for every XCD, and how those of a
+    // last, unfilled round are cut.
+    __shared__ int32_t surplus0[8], gap0[9], have[8], cut[8];
     int most = 0;                 // tiles of an XCD
     if (!parts) {
       if (b < 8) {
@@ -208,13 +219,6 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
         p.kd_count[b] = total;
       }
     } else {
-      if (b < 8) { own[b] = 0; shorts[b][0] = 0; shorts[b][1] = 0; }
-      __syncthreads();
-      if (b < N) {
-        atomicAdd(&own[group_of(rank)], ntq);
-        if (mine_short) atomicAdd(&shorts[group_of(rank)][mine_short - 1], 1);
-      }
-      __syncthreads();
 #pragma unroll
       for (int x = 0; x < 8; ++x) most += own[x];
       most = (most + 7) / 8;

@@ -453,7 +453,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
 // operand bytes per product; a second and third round of quarters gains nothing over a full one).
 // Whole row tiles dealt to the XCDs before: 9 of 66 to some, 4 rounds of 11 A-side tiles each, where 2.84
 // rounds' worth of items is there.  us, before and now: T 8192, d 4096, 4 blocks of 2752, k 2: up-projection 450,
-// 373, its backward 499, 403, partial rows 376, 345; 3001 tokens of that 215, 168; 24 tokens 85, 46.
+// 373, its backward 499, 403 (385 since its outputs go out as whole lines), partial rows 376, 345; 3001 tokens of that 215, 168; 24 tokens 85, 46.
 template <int OP, int ACT>
 __global__ __launch_bounds__(256, 1) void wide_rows_kernel(WideArgs p) {
   extern __shared__ uint4 w_smem[];
