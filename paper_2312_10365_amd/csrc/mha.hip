@@ -58,14 +58,17 @@ __device__ __forceinline__ float wave_sum(float v) {
 // A score's last four bits give way to the codeword's index, so a maximum carries it along.  What is lost with them, the
 // rounding of the scores and that of the distances they stand for are below kPqTie (|x|^2 + max |c|^2): 32 additions of
 // 2^-23 of at most (|x|^2 + 2 |c|^2) / 2 on either side, 2^-19 of that for the index, 10 of 2^-24 of a distance of at most
-// 2 (|x|^2 + |c|^2): together 2^-16.3 of |x|^2 + |c|^2.  A vector whose second best is nearer than that -- or with anything
-// infinite or NaN about it, which makes the test fail -- is measured again as Algorithm 2 has it: the distances in fp32, the
-// lower index on a tie.  So the codes are those of the distances, bit for bit.
+// 2 (|x|^2 + |c|^2): together 2^-16.3 of |x|^2 + |c|^2.  The products, sums, squares and parts of a codeword that fall below the
+// smallest normal number may be lost whole: 56 of up to 2^-126, eight of them times max(1, |x|, |c|).  kPqFloor, added to the bound,
+// is 2^20 times that for |x|, |c| up to 1, and beyond 1 the bound grows faster.  A vector whose second best is nearer than the
+// two -- or with anything infinite or NaN about it, which makes the test fail -- is measured again as Algorithm 2 has it: the
+// distances in fp32, the lower index on a tie.  So the codes are those of the distances, bit for bit.
 // us, distances measured one by one (256 instructions of the vector units per wavefront of them) -> this: S 512, n 512, E 16:
 // 20.1 -> 15.9 (8 codebooks), 37.5 -> 28.4 (16); S 96, n 1100 25.0 -> 17.6; S 8, n 130 7.6 -> 5.6; S 64, n 777, E 8 7.7 -> 7.9.  What
 // is left is reading X (15 us of the 28), preparing the codebooks, and the wait for both.  (One MFMA per codebook, its sub-vector in
 // all lane groups: 71, bound by 20 loads of 16 lines each per 16 vectors.)
 constexpr float kPqTie = 1.52587890625e-5f;   // 2^-16
+constexpr float kPqFloor = 0x1p-100f;
 constexpr int kPqWaves = 8, kPqVectors = 16 * kPqWaves;   // vectors of a workgroup at a time
 
 __device__ __forceinline__ float hw_max(float a, float b) {   // (fmaxf would quiet its operands first)
@@ -110,7 +113,7 @@ __global__ __launch_bounds__(kPqWaves * 64) void pq_assign_kernel(const uint16_t
   __shared__ uint16_t none[kDp];                 // zeros
   __shared__ float cb[M][kMaxE][kDp];
   __shared__ float norm[M][kMaxE];               // -|c|^2 / 2
-  __shared__ float tie[M];                       // kPqTie max |c|^2
+  __shared__ float tie[M];                       // kPqTie max |c|^2 + kPqFloor
   const int s = blockIdx.y, head = s % H, tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4;
   const int first = blockIdx.x * per, end = min(n, first + per);
   const size_t base = (size_t)s * n;
@@ -157,7 +160,7 @@ __global__ __launch_bounds__(kPqWaves * 64) void pq_assign_kernel(const uint16_t
     }(std::make_integer_sequence<int, kMaxE - 1>{});
     norm[m][e] = e < E && !again ? -0.5f * sq : -3e38f;   // (no codeword: never near the best)
     // (non-negative: their order is that of the bits; infinite, NaN, or too large to tell: everything is near)
-    atomicMax(reinterpret_cast<uint32_t*>(&tie[m]), __float_as_uint(sq < 1e38f ? kPqTie * sq : INFINITY));
+    atomicMax(reinterpret_cast<uint32_t*>(&tie[m]), __float_as_uint(sq < 1e38f ? kPqTie * sq + kPqFloor : INFINITY));
   }
   __syncthreads();
 
