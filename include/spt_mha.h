@@ -36,7 +36,9 @@ typedef struct {
  * distance is evaluated in fp32.  Lines 4-5: err (fp32 [S][n][M], or NULL on the mini-batches that
  * skip them -- the paper adjusts the codebooks every 20th) receives the quantisation error, the
  * Euclidean distance between the sub-vector and the codeword it was given; the codebook
- * adjustment that consumes it is an optimiser step outside this library. */
+ * adjustment that consumes it is an optimiser step outside this library.  A codeword at no
+ * finite distance (infinities, NaN) is never the nearest; a sub-vector with no other gets code 0
+ * and the error infinity. */
 int spt_mha_pq_assign(const spt_mha_shape_t* shape, const void* X, const float* C, uint8_t* codes,
                       float* err, void* stream);
 

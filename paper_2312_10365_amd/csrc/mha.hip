@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kPqWaves * 64) void pq_assign_kernel(const uint16_t
           const float df = (j % 2 ? hi_bf16(xm[j / 2]) : lo_bf16(xm[j / 2])) - c[j];
           dist = fmaf(df, df, dist);
         }
-        err[at + p] = sqrtf(dist);
+        err[at + p] = sqrtf(dist < INFINITY ? dist : INFINITY);   // (NaN is no distance: none was found)
       }
     }
     typedef uint32_t u32u __attribute__((aligned(1)));

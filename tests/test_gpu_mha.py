@@ -177,8 +177,10 @@ def test_assignment_where_codewords_are_equally_near(S, n, dh, E, kind):
     err = torch.full((S, n, M), -1.0, device="cuda")
     got = mha.pq_assign(s, torch.from_numpy(X.reshape(S, n, dh)).cuda().to(torch.bfloat16), torch.from_numpy(C).cuda(),
                         torch.full((S, n, M), 255, dtype=torch.uint8, device="cuda"), err)
-    want, _ = nearest_in_order(X, C)
+    want, dist = nearest_in_order(X, C)
     np.testing.assert_array_equal(got.cpu().numpy(), want)
+    # (the error of a sub-vector that is no distance from any codeword -- NaN, or infinitely far -- is infinity)
+    np.testing.assert_allclose(err.cpu().numpy(), np.sqrt(dist), rtol=2.0 ** -22)
 
 
 # Selection: key counts around the 64-key pairs of mask words and the parts a query's keys are split into, row lengths
