@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ log
 // the squares that underflow added: `tiny`); exactly 0 where the tokens or the weights are zeros.  `reach` holds it per token
 // and part, with the largest |w| of the blocks.  Measured over d 64 to 8192: at most 0.014 of it, 0.0025 at d = 4096.
 //
-// us, both launches, fp64 -> this: T 8192, d 4096, N 128 167 -> 55; T 3001 77 -> 41; T 16384, d 1024, N 64 55 -> 33.  The fp64
+// us, both launches, fp64 -> this: T 8192, d 4096, N 128 151 -> 54; T 3001 65 -> 38; T 16384, d 1024, N 64 50 -> 34.  The fp64
 // units were busy 70 % of the time; here no unit is (T 3001: MFMA 23 %, vector units 39 % of the cycles): a workgroup's first
 // loads, its last sums and three to eight stages one after the other.  Registers (235) hold it at one workgroup per CU: the
 // next step's split among the MFMAs spilled and took 50 us where 38 is, a fixed stage without branches 45.
@@ -470,131 +470,205 @@ __global__ __launch_bounds__(64 * kNearWaves, 2) void router_near_kernel(
 // what both can be off by (twice `reach` and the rounding to fp32): the k largest are the right ones.  Otherwise every key
 // more than that above `after` is in, every key more than that below kth is out, and those between are summed in fp64 (x times a
 // row of the copy of W_r that the kernel above leaves: its columns are a cache line per value) and compete for the places
-// left.  Sums that are not finite leave all blocks open.  (One chain of loads and sums, 6 us for the few wavefronts that go through
-// it; all four of a workgroup on one token's blocks: 15.8 where 17.3 is at T 3001, 17.3 where 14.6 is at T 16384.)
-// Weights with a part common to all blocks leave more open: both launches at T 8192, d 4096 58 us where it is three times what
-// tells the blocks apart, 68 where 30, 91 where 100.
+// left.  Sums that are not finite leave all blocks open.
+// How many are open hangs on the data (weights with a large part common to all blocks, blocks alike, tokens that are
+// not finite: all of them), so the 16 tokens of a workgroup share that work.  Up to kNearTurns turns of two blocks are dealt to the
+// wavefronts whatever token they are of; beyond that the fp64 matrix cores sum all blocks of the 16 tokens, which costs the
+// same for any data.  The line lies where the two meet: T 8192, d 4096, N 128 with a common part of 300 times what tells the
+// blocks apart (14 open a token) 136 us dealt, 222 summed; with half the turns it would go to the second.
+// us, both launches, a wavefront per token with all its open blocks -> this: T 8192, d 4096, N 128: ordinary weights 57 -> 58,
+// common part x 30 67 -> 65, x 1000 345 -> 222, all alike 850 -> 222 (fp64 throughout: 150), one token of NaN 204 -> 75; T 3001
+// 37 -> 38, 290 -> 121 (65); T 16384, d 1024, N 64 32 -> 34, 210 -> 74 (50); T 40000, d 256, N 128 67 -> 70, 750 -> 137 (100).
+// Workgroups of 16 wavefronts wait for 16 places, which is what ordinary weights pay: at most 64 registers, so that a CU has two
+// (with 72 and one: 63, 40 and 92 us).
+constexpr int kOpenTokens = 16, kNearTurns = 8 * kOpenTokens;
 template <int NPL>
-__global__ __launch_bounds__(256) void topk_near_kernel(const float* __restrict__ near, const float* __restrict__ reach,
-                                                        const float* __restrict__ Wt, const uint16_t* __restrict__ X,
-                                                        const float* __restrict__ br, int splits, int T, int d, int N,
-                                                        int k, int flags, int32_t* __restrict__ idx) {
+__global__ __launch_bounds__(64 * kOpenTokens, 8) void topk_near_kernel(
+    const float* __restrict__ near, const float* __restrict__ reach, const float* __restrict__ Wt,
+    const uint16_t* __restrict__ X, const float* __restrict__ br, int splits, int T, int d, int N, int k, int flags,
+    int32_t* __restrict__ idx) {
+  constexpr int CT = 4 * NPL, KP = kOpenTokens / CT;       // column tiles of 16 blocks, shares of d (matrix cores)
+  __shared__ uint8_t list[kOpenTokens][64 * NPL];          // the open blocks of a token
+  __shared__ int turns[kOpenTokens];
+  __shared__ uint32_t keys[kOpenTokens][64 * NPL];         // images of their fp64 logits
+  __shared__ double red[KP - 1][CT][4][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int t = blockIdx.x * 4 + wave;
-  if (t >= T) return;                      // whole wavefront; the kernel has no barrier
-  double sum[NPL] = {};
-  float off = 0.f;
-  for (int z0 = 0; z0 < splits; z0 += 8) {   // eight parts in flight
-    float p[8][NPL], r[8];
+  const int tok0 = blockIdx.x * kOpenTokens, t = tok0 + wave;
+  const bool live = t < T;                 // (a wavefront without a token still shares the work)
+  uint32_t u[NPL], thr = 0u;
+  unsigned long long open[NPL] = {};
+  if (live) {
+    double sum[NPL] = {};
+    float off = 0.f;
+    for (int z0 = 0; z0 < splits; z0 += 8) {   // eight parts in flight
+      float p[8][NPL], r[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const size_t row = (size_t)min(z0 + q, splits - 1) * T + t;
-      r[q] = z0 + q < splits ? reach[row] : 0.f;
+      for (int q = 0; q < 8; ++q) {
+        const size_t row = (size_t)min(z0 + q, splits - 1) * T + t;
+        r[q] = z0 + q < splits ? reach[row] : 0.f;
 #pragma unroll
-      for (int n = 0; n < NPL; ++n) p[q][n] = z0 + q < splits && lane + 64 * n < N ? near[row * N + lane + 64 * n] : 0.f;
+        for (int n = 0; n < NPL; ++n) p[q][n] = z0 + q < splits && lane + 64 * n < N ? near[row * N + lane + 64 * n] : 0.f;
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        off += r[q];
+#pragma unroll
+        for (int n = 0; n < NPL; ++n) sum[n] += (double)p[q][n];
+      }
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      off += r[q];
-#pragma unroll
-      for (int n = 0; n < NPL; ++n) sum[n] += (double)p[q][n];
-    }
-  }
-  float key[NPL];
-  uint32_t u[NPL];
-  bool finite = true;
-#pragma unroll
-  for (int n = 0; n < NPL; ++n) {
-    const int b = lane + 64 * n;
-    const float l = b < N ? (float)(sum[n] + (br ? (double)br[b] : 0.0)) : 0.f;
-    key[n] = (flags & 1) ? fabsf(l) : l;
-    u[n] = b < N ? key_image(l, flags) : 0u;
-    finite = finite && fabsf(l) < INFINITY;
-  }
-  uint32_t thr = kth_image<NPL>(u, k);
-  off = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(off)));
-  if (off != 0.f) {                        // (no error: the sums are zeros; NaN != 0)
-    auto value = [](uint32_t image) { return __uint_as_float((image & 0x80000000u) ? image & 0x7FFFFFFFu : ~image); };
-    int at_least = 0;
-    uint32_t next = 0u;                    // the largest image not selected
+    float key[NPL];
+    bool finite = true;
 #pragma unroll
     for (int n = 0; n < NPL; ++n) {
-      at_least += (int)__popcll(__ballot(u[n] >= thr));
-      next = max(next, u[n] < thr ? u[n] : 0u);
+      const int b = lane + 64 * n;
+      const float l = b < N ? (float)(sum[n] + (br ? (double)br[b] : 0.0)) : 0.f;
+      key[n] = (flags & 1) ? fabsf(l) : l;
+      u[n] = b < N ? key_image(l, flags) : 0u;
+      finite = finite && fabsf(l) < INFINITY;
     }
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) next = max(next, (uint32_t)__shfl_xor((int)next, o));
-    if (at_least > k) next = thr;
-    const float kth = value(thr), after = value(next);
-    float margin = 2.f * off + 0x1p-22f * fmaxf(fabsf(kth), fabsf(after));
-    if (!__all(finite)) margin = INFINITY;
-    if (next != 0u && !(kth - after > margin)) {
-      unsigned long long open[2] = {0ull, 0ull};
+    thr = kth_image<NPL>(u, k);
+    off = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(off)));
+    if (off != 0.f) {                      // (no error: the sums are zeros; NaN != 0)
+      auto value = [](uint32_t image) { return __uint_as_float((image & 0x80000000u) ? image & 0x7FFFFFFFu : ~image); };
+      int at_least = 0;
+      uint32_t next = 0u;                  // the largest image not selected
 #pragma unroll
       for (int n = 0; n < NPL; ++n) {
-        const int b = lane + 64 * n;
-        const bool in = key[n] - margin > after, out = key[n] + margin < kth;
-        open[n] = __ballot(b < N && !in && !out);
-        u[n] = b < N && in ? 0xFFFFFFFFu : 0u;
+        at_least += (int)__popcll(__ballot(u[n] >= thr));
+        next = max(next, u[n] < thr ? u[n] : 0u);
       }
-      auto take = [&]() -> int {           // the lowest open block
-        const int n = open[0] ? 0 : 1, b = (int)__builtin_ctzll(open[n]) + 64 * n;
-        open[n] &= open[n] - 1;
-        return b;
-      };
-      const uint16_t* x = X + (size_t)t * d;
-      while (open[0] | open[1]) {          // two blocks a turn
-        const int b0 = take(), b1 = open[0] | open[1] ? take() : b0;
-        const float *w0 = Wt + (size_t)b0 * d, *w1 = Wt + (size_t)b1 * d;
-        double s0 = 0.0, s1 = 0.0;
-        for (int k0 = 8 * lane; k0 < d; k0 += 512 * 2) {
-          u32x4 xv[2];
-          f32x4 wv[2][4];
 #pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int c = min(k0 + 512 * q, d - 8);
-            xv[q] = *reinterpret_cast<const u32x4*>(x + c);
-            wv[q][0] = *reinterpret_cast<const f32x4*>(w0 + c);
-            wv[q][1] = *reinterpret_cast<const f32x4*>(w0 + c + 4);
-            wv[q][2] = *reinterpret_cast<const f32x4*>(w1 + c);
-            wv[q][3] = *reinterpret_cast<const f32x4*>(w1 + c + 4);
-          }
-          // (all of them requested before the first is used)
-          asm volatile("" : "+v"(xv[0]), "+v"(xv[1]), "+v"(wv[0][0]), "+v"(wv[0][1]), "+v"(wv[0][2]), "+v"(wv[0][3]),
-                       "+v"(wv[1][0]), "+v"(wv[1][1]), "+v"(wv[1][2]), "+v"(wv[1][3]));
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            if (k0 + 512 * q >= d) break;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const double xe = (double)(e & 1 ? hi_bf16(xv[q][e / 2]) : lo_bf16(xv[q][e / 2]));
-              s0 = fma(xe, (double)wv[q][e / 4][e % 4], s0);
-              s1 = fma(xe, (double)wv[q][2 + e / 4][e % 4], s1);
-            }
-          }
-        }
-        // (lanes below 32 go on with the first sum, the others with the second)
-        double both = (lane < 32 ? s0 : s1) + __shfl_xor(lane < 32 ? s1 : s0, 32);
-#pragma unroll
-        for (int o = 16; o >= 1; o >>= 1) both += __shfl_xor(both, o);
-        s0 = __shfl(both, 0);
-        s1 = __shfl(both, 32);
+      for (int o = 1; o < 64; o <<= 1) next = max(next, (uint32_t)__shfl_xor((int)next, o));
+      if (at_least > k) next = thr;
+      const float kth = value(thr), after = value(next);
+      float margin = 2.f * off + 0x1p-22f * fmaxf(fabsf(kth), fabsf(after));
+      if (!__all(finite)) margin = INFINITY;
+      if (next != 0u && !(kth - after > margin)) {
 #pragma unroll
         for (int n = 0; n < NPL; ++n) {
           const int b = lane + 64 * n;
-          if (b == b0 || b == b1) u[n] = key_image((float)((b == b0 ? s0 : s1) + (br ? (double)br[b] : 0.0)), flags);
+          const bool in = key[n] - margin > after, out = key[n] + margin < kth;
+          open[n] = __ballot(b < N && !in && !out);
+          u[n] = b < N && in ? 0xFFFFFFFFu : 0u;
         }
       }
-      thr = kth_image<NPL>(u, k);
     }
+  }
+  int count = 0;
+#pragma unroll
+  for (int n = 0; n < NPL; ++n) {
+    if (open[n] >> lane & 1) list[wave][count + __popcll(open[n] & ((1ull << lane) - 1ull))] = (uint8_t)(lane + 64 * n);
+    count += (int)__popcll(open[n]);
+  }
+  if (lane == 0) turns[wave] = (count + 1) >> 1 | count << 16;
+  __syncthreads();
+  // Lane i: the turns of token i and of those before it.
+  const int mine = lane < kOpenTokens ? turns[lane] : 0;
+  int upto = mine & 0xFFFF;
+#pragma unroll
+  for (int o = 1; o < kOpenTokens; o <<= 1) {
+    const int below = __shfl_up(upto, o);
+    if (lane >= o) upto += below;
+  }
+  const int total = __builtin_amdgcn_readlane(upto, kOpenTokens - 1);
+  if (total > kNearTurns) {
+    // All blocks of the 16 tokens, as router_logits_kernel has it: a wavefront takes a column tile and a share of d's chunks of 32.
+    const int r16 = lane & 15, slot = lane >> 4, ct = wave % CT, kp = wave / CT, b = 16 * ct + r16;
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    if (16 * ct < N) {                     // uniform
+      const uint16_t* x = X + (size_t)min(tok0 + r16, T - 1) * d + 8 * slot;
+      const float* w = Wt + (size_t)min(b, N - 1) * d + 8 * slot;
+      const int last = d / 32 - 1;
+      u32x4 xn;
+      f32x4 wn[2];
+      auto request = [&](int c) {          // (past the last chunk: repeated, not used)
+        xn = *reinterpret_cast<const u32x4*>(x + 32 * min(c, last));
+        wn[0] = *reinterpret_cast<const f32x4*>(w + 32 * min(c, last));
+        wn[1] = *reinterpret_cast<const f32x4*>(w + 32 * min(c, last) + 4);
+      };
+      request(kp);
+      for (int c = kp; c <= last; c += KP) {
+        const u32x4 xv = xn;
+        const f32x4 wv[2] = {wn[0], wn[1]};
+        request(c + KP);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(e & 1 ? hi_bf16(xv[e / 2]) : lo_bf16(xv[e / 2])),
+                                                     (double)wv[e / 4][e % 4], acc, 0, 0, 0);
+      }
+      if (kp > 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[kp - 1][ct][v][lane] = acc[v];
+      }
+    }
+    __syncthreads();
+    if (kp == 0 && b < N) {                // (the shares in order; rows 4 v + slot are the tokens)
+      const double bias = br ? (double)br[b] : 0.0;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+#pragma unroll
+        for (int q = 0; q < KP - 1; ++q) acc[v] += red[q][ct][v][lane];
+        keys[4 * v + slot][b] = key_image((float)(acc[v] + bias), flags);
+      }
+    }
+  } else {
+    for (int turn = wave; turn < total; turn += kOpenTokens) {   // two blocks of a token
+      const int i = (int)__popcll(__ballot(lane < kOpenTokens && upto <= turn));
+      const int first = 2 * (turn - (i ? __builtin_amdgcn_readlane(upto, i - 1) : 0));
+      const int second = min(first + 1, (__builtin_amdgcn_readlane(mine, i) >> 16) - 1);
+      const int b0 = __builtin_amdgcn_readfirstlane(list[i][first]), b1 = __builtin_amdgcn_readfirstlane(list[i][second]);
+      const uint16_t* x = X + (size_t)(tok0 + i) * d;
+      const float *w0 = Wt + (size_t)b0 * d, *w1 = Wt + (size_t)b1 * d;
+      double s0 = 0.0, s1 = 0.0;
+      for (int k0 = 8 * lane; k0 < d; k0 += 512 * 2) {
+        u32x4 xv[2];
+        f32x4 wv[2][4];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int c = min(k0 + 512 * q, d - 8);
+          xv[q] = *reinterpret_cast<const u32x4*>(x + c);
+          wv[q][0] = *reinterpret_cast<const f32x4*>(w0 + c);
+          wv[q][1] = *reinterpret_cast<const f32x4*>(w0 + c + 4);
+          wv[q][2] = *reinterpret_cast<const f32x4*>(w1 + c);
+          wv[q][3] = *reinterpret_cast<const f32x4*>(w1 + c + 4);
+        }
+        // (all of them requested before the first is used)
+        asm volatile("" : "+v"(xv[0]), "+v"(xv[1]), "+v"(wv[0][0]), "+v"(wv[0][1]), "+v"(wv[0][2]), "+v"(wv[0][3]),
+                     "+v"(wv[1][0]), "+v"(wv[1][1]), "+v"(wv[1][2]), "+v"(wv[1][3]));
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          if (k0 + 512 * q >= d) break;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const double xe = (double)(e & 1 ? hi_bf16(xv[q][e / 2]) : lo_bf16(xv[q][e / 2]));
+            s0 = fma(xe, (double)wv[q][e / 4][e % 4], s0);
+            s1 = fma(xe, (double)wv[q][2 + e / 4][e % 4], s1);
+          }
+        }
+      }
+      // (lanes below 32 go on with the first sum, the others with the second)
+      double both = (lane < 32 ? s0 : s1) + __shfl_xor(lane < 32 ? s1 : s0, 32);
+#pragma unroll
+      for (int o = 16; o >= 1; o >>= 1) both += __shfl_xor(both, o);
+      const int b = lane < 32 ? b0 : b1;
+      if ((lane & 31) == 0) keys[i][b] = key_image((float)(both + (br ? (double)br[b] : 0.0)), flags);
+    }
+  }
+  if (total > 0) __syncthreads();          // uniform
+  if (!live) return;
+  if (count > 0) {                         // uniform
+#pragma unroll
+    for (int n = 0; n < NPL; ++n)
+      if (open[n] >> lane & 1) u[n] = keys[wave][lane + 64 * n];
+    thr = kth_image<NPL>(u, k);
   }
   emit_topk<NPL>(u, thr, lane, k, idx + (size_t)t * k);
 }
 
 // Parts of d for that path, 0 for none: it costs 13 to 40 us, the more the longer a row, however few the tokens, against fp64
-// units that take 30 x 10^6 products a us.  us, fp64 / this: d 4096, N 128 T 1024 26 / 31, 2048 46 / 35; d 2048, N 64 T 2048
-// 17 / 19, 4096 28 / 23; d 1024, N 64 T 4096 18 / 18, 8192 29 / 24; d 512, N 64 T 8192 20 / 20, 16384 34 / 28; d 256, N 128
-// T 8192 25 / 26, 16384 44 / 36; d 8192, N 128 T 1024 46 / 42.  (Up to 32 blocks the fp64 kernel selects as well.)
+// units that take 30 x 10^6 products a us.  us, fp64 / this: d 4096, N 128 T 1024 28 / 33, 2048 46 / 37; d 2048, N 64 T 2048
+// 16 / 20, 4096 27 / 23; d 1024, N 64 T 4096 18 / 19, 8192 29 / 24; d 512, N 64 T 8192 20 / 21, 16384 34 / 30; d 256, N 128
+// T 8192 25 / 26, 16384 45 / 37; d 8192, N 128 T 1024 46 / 41.  (Up to 32 blocks the fp64 kernel selects as well.)
 static int near_splits(const spt_shape_t& s) {
   if (s.N <= 32 || s.N > 128 || (int64_t)s.T * s.N * s.d < (1ll << 28) + (1ll << 17) * s.d) return 0;
   const int tiles = (s.T + kNearTokens - 1) / kNearTokens, units = (s.d + 63) / 64;
@@ -626,7 +700,8 @@ template <int NPL>
 static void launch_topk_near(const spt_shape_t& s, const uint16_t* X, const float* br, const float* ws, int splits,
                              int32_t* idx, hipStream_t st) {
   const float *near = ws + near_copy_floats(s), *reach = near + (size_t)splits * s.T * s.N;
-  topk_near_kernel<NPL><<<(s.T + 3) / 4, 256, 0, st>>>(near, reach, ws, X, br, splits, s.T, s.d, s.N, s.k, s.flags, idx);
+  topk_near_kernel<NPL><<<(s.T + kOpenTokens - 1) / kOpenTokens, 64 * kOpenTokens, 0, st>>>(
+      near, reach, ws, X, br, splits, s.T, s.d, s.N, s.k, s.flags, idx);
 }
 
 template <int NPL>

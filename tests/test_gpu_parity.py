@@ -273,6 +273,56 @@ def test_router_ids_of_many_tokens(T, d, N, k, kind):
     assert torch.equal(got, want), int((got != want).any(1).sum())
 
 
+# Data that leaves many blocks open to fp64 sums, up to all of them: a large part common to all weights (few tokens of a
+# workgroup's sixteen over its limit to all of them), blocks alike, infinite values in half of the tokens or one in 37.
+@pytest.mark.parametrize("T,d,N,k", [(16385, 320, 64, 16), (131107, 64, 33, 5), (12500, 832, 65, 1), (4099, 2048, 128, 40)])
+@pytest.mark.parametrize("kind", ["common 30", "common 300", "common 3000", "alike", "half infinite", "few infinite"])
+def test_router_ids_where_many_blocks_are_close(T, d, N, k, kind):
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    X = torch.randn(T, d, generator=g, device="cuda")
+    W = 0.02 * torch.randn(d, N, generator=g, device="cuda")
+    b = 0.1 * torch.randn(N, generator=g, device="cuda") if kind == "few infinite" else None
+    if kind.startswith("common"):
+        W += float(kind.split()[1]) * 0.02 * torch.randn(d, 1, generator=g, device="cuda")
+    if kind == "alike":
+        W[:] = W[:, :1].clone()
+    if kind.endswith("infinite"):
+        X[::2 if kind == "half infinite" else 37, 5] = float("inf")
+    X = X.bfloat16()
+    s = spt.make_shape(T, d, N, 32, k, spt.ACT_GELU, 0)
+    assert spt.alloc_workspace(s, spt.WS_ROUTER).nbytes >= 4 * (N * d + T * N)     # (the sums and the weights' copy)
+    want = spt.router_topk(s, X, W, b, logits=torch.empty(T, N, device="cuda"))      # (the fp64 kernels)
+    got = spt.router_topk(s, X, W, b)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want), int((got != want).any(1).sum())
+
+
+# ... and ids alone take no more than two and a half times as long as all sums in fp64 do (1.4 to 1.9 measured).
+@pytest.mark.parametrize("T,d,N,k", [(8192, 4096, 128, 32), (40000, 256, 128, 32), (16384, 1024, 64, 16)])
+def test_router_time_does_not_hang_on_the_data(T, d, N, k):
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    X = torch.randn(T, d, generator=g, device="cuda").bfloat16()
+    W = (0.02 * torch.randn(d, 1, generator=g, device="cuda")).repeat(1, N)
+    s = spt.make_shape(T, d, N, 32, k, spt.ACT_GELU, 0)
+    ws, idx, logits = spt.alloc_workspace(s, spt.WS_ROUTER), torch.empty(T, k, dtype=torch.int32, device="cuda"), torch.empty(T, N, device="cuda")
+
+    def us(**out):
+        best = float("inf")
+        for _ in range(5):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            for _ in range(5):
+                spt.router_topk(s, X, W, idx=idx, ws=ws, **out)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, 200.0 * start.elapsed_time(end))
+        return best
+
+    fp64, ids = us(logits=logits), us()
+    print(f"[router, all blocks alike] {(T, d, N)}: fp64 {fp64:.1f} us, ids only {ids:.1f} us")
+    assert ids <= 2.5 * fp64
+
+
 def test_values_with_oracle_bucketing_and_determinism():
     # Feed the oracle's offsets/perm/inv to the GPU (value parity decoupled from routing),
     # and require bit-identical outputs on a second run.
