@@ -102,6 +102,11 @@ __device__ __forceinline__ Top2 fold(const Top2& a, const Top2& b) {
   return merge(Top2{__uint_as_float(p[0]), __uint_as_float(q[0])}, Top2{__uint_as_float(p[1]), __uint_as_float(q[1])});
 }
 __device__ __forceinline__ float upper_half(float x) { return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
+// f of the constants 1, 2, ...
+template <class F, int... O>
+__device__ __forceinline__ void each_from_one(F f, std::integer_sequence<int, O...>) {
+  (f(std::integral_constant<int, O + 1>{}), ...);
+}
 
 template <int M>
 __global__ __launch_bounds__(kPqWaves * 64) void pq_assign_kernel(const uint16_t* __restrict__ X,
@@ -155,9 +160,7 @@ __global__ __launch_bounds__(kPqWaves * 64) void pq_assign_kernel(const uint16_t
         again |= same;
       }
     };
-    [&]<int... O>(std::integer_sequence<int, O...>) {
-      (compare(std::integral_constant<int, O + 1>{}), ...);
-    }(std::make_integer_sequence<int, kMaxE - 1>{});
+    each_from_one(compare, std::make_integer_sequence<int, kMaxE - 1>{});
     norm[m][e] = e < E && !again ? -0.5f * sq : -3e38f;   // (no codeword: never near the best)
     // (non-negative: their order is that of the bits; infinite, NaN, or too large to tell: everything is near)
     atomicMax(reinterpret_cast<uint32_t*>(&tie[m]), __float_as_uint(sq < 1e38f ? kPqTie * sq + kPqFloor : INFINITY));
