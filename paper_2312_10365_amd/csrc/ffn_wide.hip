@@ -454,6 +454,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
 // Whole row tiles dealt to the XCDs before: 9 of 66 to some, 4 rounds of 11 A-side tiles each, where 2.84
 // rounds' worth of items is there.  us, before and now: T 8192, d 4096, 4 blocks of 2752, k 2: up-projection 450,
 // 373, its backward 499, 403 (385 since its outputs go out as whole lines), partial rows 376, 345; 3001 tokens of that 215, 168; 24 tokens 85, 46.
+// (Registers: all 256 and 256 of accumulators; dH with GELU and the adapters' stages keeps one in scratch, read back once an item.)
 template <int OP, int ACT>
 __global__ __launch_bounds__(256, 1) void wide_rows_kernel(WideArgs p) {
   extern __shared__ uint4 w_smem[];

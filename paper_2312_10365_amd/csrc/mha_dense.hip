@@ -150,9 +150,10 @@ __device__ __forceinline__ u32x4 tr_frag(const char* p) {
 constexpr int NW = 8, BQ = 32, NT = NW * 64;
 template <int DH, int KT>
 constexpr bool rows_planes() { return DH == 128 || KT == 1; }
-// Registers: 128 per lane (two workgroups on a CU) where that holds the fragments and the lists, 256 otherwise.  Two
-// variants of 65 to 128 entries (64-wide heads beyond 256 keys and 128-wide up to 256, backward) keep one K fragment in
-// scratch, reloaded once per block; no other variant spills.
+// Registers: 128 per lane (two workgroups on a CU) where that holds the fragments and the lists, 256 otherwise.  Where it
+// does not quite: 64-wide heads, 257 to 512 keys, 65 to 128 entries, backward keep one K fragment in scratch, read back once per
+// block; 128-wide heads beyond 512 keys with more than 192 entries keep 12 (backward 13) registers of the lists there, stored
+// once per block and read back once per chunk of the second product.  No other variant spills.
 template <int DH, int KT, int LPL, bool STAT>
 constexpr int rows_waves_per_simd() { return !STAT || (KT * DH <= 128 && LPL <= 2) ? 4 : 2; }
 // Keys of a chunk of the second product where a sequence takes several: what two workgroups of a CU have LDS for.
