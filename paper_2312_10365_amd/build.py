@@ -13,6 +13,8 @@ SOURCES = ("api.cpp", "profile.cpp", "router.hip", "bucket.hip", "ffn.hip", "ffn
            "lora.hip", "mha.hip", "mha_dense.hip", "calibrate.hip")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# (accumulators that vector instructions add to the LDS slab: in vector registers, not copied out of the accumulator file)
+EXTRA = {"ffn_scatter.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _run(cmd):
@@ -27,7 +29,7 @@ def build_libspt(verbose: bool = False, only=None) -> str:
     directory, so each call compiles everything again."""
     with tempfile.TemporaryDirectory() as tmp:
         objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
-        cmds = [["hipcc", *FLAGS, "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
+        cmds = [["hipcc", *FLAGS, *EXTRA.get(s, []), "-c", os.path.join(CSRC, s), "-o", o] for s, o in zip(SOURCES, objs)]
         with ThreadPoolExecutor(max_workers=min(8, len(cmds))) as ex:
             logs = list(ex.map(_run, cmds))
         logs.append(_run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT, *objs]))

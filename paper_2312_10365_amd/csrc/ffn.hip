@@ -60,7 +60,7 @@ struct PlanArgs {
   int32_t* starts;
   RunRec* runs;
   int32_t* nruns;
-  int run_cap;
+  int run_cap, run_rows;
   int dw_rows, dw_cap;
   DwPiece* dw_pieces;
   int32_t* dw_xlist;
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     if (p.R > 0) {
       __syncthreads();   // (the table is this workgroup's own)
       for (int r = threadIdx.x >> 6; r < p.nr; r += 16)
-        compact_runs(p.starts, N, p.run_cap, p.runs, p.nruns, r, threadIdx.x & 63);
+        compact_runs(p.starts, N, p.run_cap, p.run_rows, p.runs, p.nruns, r, threadIdx.x & 63);
     }
   }
 }
@@ -1364,7 +1364,7 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
   a.tok = sc.tok;
   if (sc.rstart) {
     a.R = sp.R; a.nr = sp.nr; a.starts = scatter_starts(sp, sc.rstart);
-    a.runs = scatter_runs(sp, sc.rstart); a.nruns = scatter_counts(sp, sc.rstart); a.run_cap = sp.cap;
+    a.runs = scatter_runs(sp, sc.rstart); a.nruns = scatter_counts(sp, sc.rstart); a.run_cap = sp.cap; a.run_rows = sp.run_rows;
   }
   a.dw_rows = sc.dw_rows; a.dw_cap = sc.dw_cap; a.dw_pieces = sc.dw_pieces; a.dw_xlist = sc.dw_xlist;
   const bool all = P <= 8192;   // eight positions per thread: less than the two launches it saves

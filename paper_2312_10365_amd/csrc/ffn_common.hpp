@@ -34,13 +34,12 @@ struct KdTile { uint16_t bucket, rows; int32_t q0; };
 // that belong to the range are one contiguous run of sorted positions (inside a bucket the token
 // ids ascend): [starts[r][b], starts[r+1][b]), a dense table the schedule kernel fills.  One
 // wavefront per range turns its two table rows into the list of the range's NON-EMPTY runs, in
-// ascending block order and cut into pieces of at most SC_RUN rows (one pass of the GEMM
-// kernel's four row tiles), as (block, first, end, 0) records, and their count.  A range has at
-// most N + R k / SC_RUN records.
-constexpr int SC_RUN = 128;
-struct RunRec { int32_t b, lo, hi, pad; };
+// ascending block order and cut into pieces (the K = Bs kernel's 16-row tiles start at a multiple of
+// four positions, so a piece ends run_rows behind one), as (block, first, end, piece) records, and
+// their count.  A range has at most N + (R k + 3 N) / run_rows records.
+struct RunRec { int32_t b, lo, hi, piece; };
 
-__device__ __forceinline__ void compact_runs(const int32_t* starts, int N, int cap, RunRec* runs, int32_t* nruns, int r,
+__device__ __forceinline__ void compact_runs(const int32_t* starts, int N, int cap, int run_rows, RunRec* runs, int32_t* nruns, int r,
                                              int lane) {
   const int32_t* s0 = starts + (size_t)r * N;
   const int32_t* s1 = s0 + N;
@@ -49,7 +48,8 @@ __device__ __forceinline__ void compact_runs(const int32_t* starts, int N, int c
   for (int b0 = 0; b0 < N; b0 += 64) {
     const int b = b0 + lane;
     const int first = (b < N) ? s0[b] : 0, end = (b < N) ? s1[b] : 0;
-    const int pieces = (end - first + SC_RUN - 1) / SC_RUN;
+    const int base = first & ~3;
+    const int pieces = end > first ? (end - base + run_rows - 1) / run_rows : 0;
     int incl = pieces;  // inclusive scan over the wavefront
 #pragma unroll
     for (int sft = 1; sft < 64; sft <<= 1) {
@@ -58,7 +58,7 @@ __device__ __forceinline__ void compact_runs(const int32_t* starts, int N, int c
     }
     int at = count + incl - pieces;
     for (int p = 0; p < pieces; ++p, ++at)
-      if (at < cap) list[at] = RunRec{b, first + p * SC_RUN, min(first + (p + 1) * SC_RUN, end), 0};
+      if (at < cap) list[at] = RunRec{b, max(first, base + p * run_rows), min(base + (p + 1) * run_rows, end), p};
     count += __shfl(incl, 63);
   }
   if (lane == 0) nruns[r] = count < cap ? count : cap;

@@ -6,35 +6,47 @@
 //
 // forward: Hin = act(H), W = W2, out = Y;  backward: Hin = dHpre, W = W1, out = dX.
 //
-// The GEMM is token-range stationary.  A workgroup owns R consecutive tokens x C output columns
-// as an fp32 slab in LDS and walks the N blocks in order.  Inside a bucket the sorted positions
-// ascend with the token id, so the rows of block b that belong to the workgroup's tokens are one
-// contiguous run [rstart[r][b], rstart[r+1][b]) -- about R k / N of them.  The run is multiplied
-// by the block's C weight columns on the matrix cores (v_mfma_f32_32x32x16_bf16; bucket rows on
-// the lane axis, output columns on the register axis, permuted by rho32 so a lane holds 16
-// consecutive columns of ITS row) and every lane adds its 64 bytes into the LDS row of its
-// token.  A token occurs at most once per block, the blocks come in ascending order and a
-// barrier separates them, so every output element is summed in fp32 in one fixed order -- no
-// atomics, no partial rows in HBM, one rounding to bf16 when the slab is written out.
+// The GEMM is token-range stationary.  A workgroup owns R consecutive tokens x 64 output columns
+// as an fp32 slab in LDS.  Inside a bucket the sorted positions ascend with the token id, so the
+// rows of block b that belong to the workgroup's tokens are one contiguous run
+// [rstart[r][b], rstart[r+1][b]) -- about R k / N of them.  A run (cut into records of at most
+// 16 NT rows) is one WAVEFRONT's work, and the wavefronts of a workgroup are at different runs:
+// wavefront w takes records w, w + 4, ...  It turns the block's 64 weight columns into matrix
+// operands once, streams the run's rows past them in tiles of 16 (v_mfma_f32_16x16x32_bf16, rows on
+// the register axis) and adds every finished tile into the slab rows of its tokens.  Nothing is
+// shared between wavefronts but the slab, so there is no barrier in the loop.
 //
-// Operands.  The weight slice (Bs x 64 columns, hidden-unit major as stored) travels global ->
-// registers -> LDS stage and is turned into K-contiguous MFMA fragments by ds_read_b64_tr_b16;
-// the fragments of a run live in registers, so a stage is free again as soon as they are read.
-// Hin is stored in fragment order (ffn_common.hpp): the 16 bytes per K-step of 32 consecutive
-// rows are one contiguous kilobyte, which goes straight from global memory into the lanes that
-// own the rows.  Both are requested several runs ahead of their use.
-// Every load is an ordinary load, so all vmcnt bookkeeping is the compiler's (asynchronous
-// global -> LDS copies would be invisible to it, and it would then wait too long for the loads
-// it can see).  Four wavefronts, one 32-row tile each; a run longer than 128 rows takes more
-// passes over the same register-resident weight fragments.
+// A token occurs at most once per block, and its sums have a fixed order (no atomics, no partial rows
+// in HBM, one rounding to bf16 when the slab is written out):
+//   one slab (OWN = false)  blocks in order.  Each wavefront says in LDS up to which token its record is done; a
+//                           tile is added once the three records before it are past its last token.  Tokens
+//                           ascend in every run, so the four wavefronts follow one another through the slab a
+//                           tile or two apart.  A wait is for lower records only, so it ends.  (Looking at the
+//                           one record before it alone, the second piece of a long run held up the next block:
+//                           blocks of 96 +- 7 rows in records of 96 761 us, now 635.)
+//   four slabs (OWN = true) every wavefront has its own, nobody waits, and the four are added at the end,
+//                           0 + 1 + 2 + 3.  For ranges of at most 159 tokens: few records to follow one
+//                           another, and shorter than what they would wait.
 //
-// LDS slab rows are padded by 16 bytes: the 16-byte accesses of a lane group then spread over
-// the banks by token id (measured 65 % of the LDS peak with random rows, against 100 % for
-// consecutive rows and 30 % for 4-byte accesses with the lanes on the column axis; the LDS
-// float atomic add runs at a hundredth of that rate).
+// Slab rows are 256 bytes.  Lane (g, i) = (lane / 16, lane % 16) of a tile holds rows 4 g .. + 3 of columns
+// 4 i .. + 3 (W columns 4 i + t go to tile t), so a 16-byte access of the wavefront is four whole slab rows:
+// no bank conflict whatever the tokens are (with the lanes on the row axis a third of the LDS cycles were).
+// LDS writes are what the slab costs: 79 B/clk per CU against 256 for reads, one ds_write_b128 of all four
+// SIMDs per 52 clk.  So the weight slice does not pass through LDS: 8-byte loads of 4 columns x 8 units per lane and
+// byte permutes make the operand (16 b128 writes and 32 transposing reads per slice instead: 515 -> 497 us).
+// Hin is stored in fragment order (ffn_common.hpp): the 16 bytes per K-step of 16 consecutive
+// rows are two contiguous half kilobytes, which go straight from global memory into the lanes that own the rows.
+//
+// Measured, us a launch, the kernel this replaces (four wavefronts at one run, a barrier per run) -> this one: 7B-like
+// (T 8192, d 4096, N 128, Bs 128, k 32) 590 -> 497; BERT-large-like (16384, 1024, 64, 64, 16) 124 -> 82; the
+// OPT-1.3B-like layer (8192, 2048, 64, 128, 16) 195 -> 165; BERT-base-like (2048, 768, 32, 96, 8) 25 -> 18.
+// What bounds it: one wavefront per SIMD (its registers hold the operands of a run and the next one's loads in flight) issues
+// about 110 instructions per tile against 256 clk of products, 540 clk with nothing loaded or added, 720 with both; bytes
+// into the CUs come at 13 TB/s, which is the limit where a range is short and the weights are read often.
 #include <math.h>
 #include <stdlib.h>
 #include <type_traits>
+#include <utility>
 
 #include "ffn_common.hpp"
 #include "spt_host.hpp"
@@ -42,9 +54,13 @@
 
 namespace spt {
 
-constexpr int SC_CC = 64;          // output columns per weight chunk (128-byte LDS rows)
-constexpr int SC_PAD = 16;         // bytes of padding per slab row
-constexpr int SC_THREADS = 256;
+constexpr int SC_C = 64;                 // output columns per workgroup
+constexpr int SC_STRIDE = SC_C * 4;      // bytes per slab row
+constexpr int SC_WAVES = 4;
+constexpr int SC_THREADS = 64 * SC_WAVES;
+constexpr int SC_CODE = 1024;            // progress codes per record; more than the rows of a slab
+constexpr int SC_NONE = -(1 << 29);      // a code that is always reached
+constexpr int SC_RSRC = 0x00027000;      // last word of a raw buffer descriptor
 
 __device__ __forceinline__ void sc_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -53,82 +69,54 @@ __device__ __forceinline__ void sc_barrier() {
 }
 
 // One wavefront per token range: see compact_runs.
-__global__ __launch_bounds__(64) void scatter_runs_kernel(const int32_t* __restrict__ starts, int N, int cap,
+__global__ __launch_bounds__(64) void scatter_runs_kernel(const int32_t* __restrict__ starts, int N, int cap, int run_rows,
                                                           RunRec* __restrict__ runs,
                                                           int32_t* __restrict__ nruns) {
-  compact_runs(starts, N, cap, runs, nruns, blockIdx.x, threadIdx.x);
+  compact_runs(starts, N, cap, run_rows, runs, nruns, blockIdx.x, threadIdx.x);
 }
 
-// KS = Bs / 16 K-steps per block.  A workgroup owns R tokens x 64 output columns; a run (at most
-// 128 rows) is four 32-row tiles, one per wavefront, by two 32-column tiles.
-//
-// The loop over a range's runs is software-pipelined so that the operands of a run are in
-// registers when its turn comes.  The slab rows of a run (the running sums of its tokens, 64
-// bytes per lane and column tile) are read straight INTO the accumulators, the matrix cores add
-// the run's products on top, and the accumulators go back to the same place: the
-// read-modify-write costs no vector instruction.  Consecutive runs update the same token rows (a
-// token often activates consecutive blocks), so one barrier per iteration separates them.
-// Iteration j:
-//     barrier               run j-1 is in the slab, weight slice j+1 visible, stage j free
-//     read tiles 0 and 1 of run j's slab rows -> accumulators
-//     stage weight slice j+2, request slice j+4, token ids, Hin rows of run j+2
-//     MFMAs of tile 0, write tile 0     (tile 1's slab values arrive meanwhile)
-//     MFMAs of tile 1, write tile 1     (tile 0's write completes meanwhile)
-// with the fragment reads of run j+1 spread behind the MFMAs.  Lanes past the end of a run skip
-// the slab accesses by EXEC mask only, so the loop body has no branch; whatever their
-// accumulators hold stays in their own lane (an MFMA output column depends on its own B-operand
-// column only).
-// Measured on the 7B-like shape, in the order built: slab update by vector adds, one run behind
-// the MFMAs, 0.67 ms; slab rows through the accumulators, one K loop over both tiles 0.645; the K
-// loop in two halves per tile 0.600; tile after tile, as here, 0.585; a second barrier in the
-// middle so that tile 0 of the next run can be read an iteration ahead 0.62 (the barrier drains
-// the LDS queue).  Two wavefronts with two row tiles each (weight fragments read half as often)
-// took 0.91 ms, eight with one column tile each (Hin rows loaded twice) 0.71 ms.
-constexpr int SC_C = 64;                     // output columns per workgroup
-constexpr int SC_STRIDE = SC_C * 4 + SC_PAD; // bytes per slab row
-constexpr int SC_STAGES = 2;                 // weight-slice stages in LDS
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-template <int KS>
-__global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
+template <class F, int... I>
+__device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+// KS = Bs / 16.  NT tiles of 16 rows per record, each a slot of the unrolled loop; rows are requested RH tiles ahead.
+// LATE: the next weight slice is requested in a record's last slot, not behind its first (64 registers less).
+// WG: workgroups a CU is to hold.
+template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
+__global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
     const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
     const int32_t* __restrict__ nruns, const int32_t* __restrict__ tok, int N, int d, int T, int R,
-    int nr, int nslab, int cap, uint16_t* __restrict__ out, const uint16_t* __restrict__ Z,
+    int nr, int nslab, int inner, int cap, uint16_t* __restrict__ out, const uint16_t* __restrict__ Z,
     float* __restrict__ split) {
   constexpr int Bs = KS * 16;
+  constexpr int KT = KS / 2;                   // K-steps of 32 hidden units
   constexpr int THREADS = SC_THREADS;
-  constexpr int NWAVES = THREADS / 64;
-  constexpr int PIECES = 2 * KS;               // kilobytes of a weight slice
-  constexpr int NW = (PIECES + NWAVES - 1) / NWAVES;   // 16-byte pieces of a weight slice per lane
-  constexpr int STAGE_BYTES = Bs * 128;
+  
   extern __shared__ uint4 sc_smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rtile = wave;                      // this wavefront's 32-row tile of a run
-  const int i = lane & 31, h = lane >> 5;
+  const int i = lane & 15, g = lane >> 4;
 
-  // Work item.  With a multiple of 8 slabs an XCD (workgroup id mod 8) keeps to its own slabs
-  // and the workgroups it runs together are token ranges x up to 8 slabs (all of its slabs at
-  // d = 4096: every run of Hin rows is then fetched once per XCD): per block they want a few weight
-  // slices and a few runs of Hin rows, which its L2 serves to all of them.
-  int r, slab;
-  if (nslab % 8 == 0) {
-    const int spx = nslab >> 3, x = blockIdx.x & 7, j = blockIdx.x >> 3;
-    const int inner = spx < 8 ? spx : 8;       // slabs that run side by side
-    const int grp = j / (inner * nr), rem = j % (inner * nr);
-    slab = x * spx + grp * inner + rem % inner;
-    r = rem / inner;
-    if (grp * inner + rem % inner >= spx) return;
-  } else {
-    slab = blockIdx.x % nslab;
-    r = blockIdx.x / nslab;
-  }
-  if (r >= nr) return;
+  // Work item.  An XCD (workgroup id mod 8) takes an eighth of the items in order: groups of `inner` slabs, range after
+  // range of a group, so that what it runs together is a few ranges x inner slabs, which share weight slices and runs of
+  // Hin rows in its L2.
+  const int per = (nslab * nr + 7) >> 3, item = (blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || item >= nslab * nr) return;
+  const int grp = item / (inner * nr), rem = item % (inner * nr);
+  const int size = nslab - grp * inner < inner ? nslab - grp * inner : inner;
+  const int slab = grp * inner + rem % size, r = rem / size;
   const int t0 = r * R, c0 = slab * SC_C;
   const int rows = (T - t0 < R) ? T - t0 : R;
 
-  char* slab_lds = reinterpret_cast<char*>(sc_smem);           // R + 1 rows: the last one is the dummy
-  const int ring_off = (R + 1) * SC_STRIDE;
-  char* ring = slab_lds + ring_off;
+  const int slab_bytes = (R + 1) * SC_STRIDE;                  // (the last row is the dummy)
+  char* const slabs = reinterpret_cast<char*>(sc_smem);
+  char* const slab_lds = slabs + (OWN ? wave * slab_bytes : 0);
+  // how far each wavefront is: SC_CODE x record + first token of it that is not done, a word per lane
+  typedef __attribute__((address_space(3))) int* lds_int_ptr;
+  const lds_int_ptr prog = (lds_int_ptr)(uintptr_t)(slabs + slab_bytes);
 
   typedef const __attribute__((address_space(4))) RunRec* const_run_ptr;
   // (few tokens: blockIdx.y takes its part of the range's records and leaves fp32 sums to be added)
@@ -136,83 +124,14 @@ __global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
   const int jfirst = (int)((int64_t)Mall * blockIdx.y / gridDim.y);
   const int M = (int)((int64_t)Mall * (blockIdx.y + 1) / gridDim.y) - jfirst;
   const const_run_ptr rl = (const_run_ptr)(uintptr_t)(runs + (size_t)r * cap + jfirst);
-  struct Run { int b, lo, hi; bool real; };
-  auto run_at = [&](int j) {  // wave-uniform scalar load; past the end: the last run again, marked unreal
-    const int jj = j < M ? j : (M > 0 ? M - 1 : 0);
-    return Run{rl[jj].b, rl[jj].lo, rl[jj].hi, j < M};
+  struct Run { int b, lo, hi, piece; };
+  auto run_at = [&](int j) {  // wave-uniform scalar load; past the end: the last run again
+    const int jj = j < M ? j : M - 1;
+    return Run{rl[jj].b, rl[jj].lo, rl[jj].hi, rl[jj].piece};
   };
 
-  // weight slice: piece j of this lane is 16 bytes of stage row 8 (wave NW + j) + lane / 8 (a stage
-  // row = 128 bytes = one hidden unit x 64 columns), physical 16-byte slot lane % 8 = logical ^
-  // (((row >> 1) & 1) << 2)
-  struct Slice { u32x4 v[NW]; };
-  // (where the pieces do not divide evenly among the wavefronts, the surplus ones repeat a
-  // piece: same bytes to the same place, and no branch in the loop)
-  int w_off[NW], w_piece[NW];
-#pragma unroll
-  for (int j = 0; j < NW; ++j) {
-    w_piece[j] = (wave * NW + j) % PIECES;
-    const int unit = 8 * w_piece[j] + (lane >> 3);
-    const int ch = (lane & 7) ^ (((unit >> 1) & 1) << 2);
-    w_off[j] = unit * d + c0 + ch * 8;
-  }
-  auto load_w = [&](Slice& w, int b) {
-    const uint16_t* wb = W + (size_t)b * Bs * d;
-#pragma unroll
-    for (int j = 0; j < NW; ++j) w.v[j] = *reinterpret_cast<const u32x4*>(wb + w_off[j]);
-  };
-  auto store_w = [&](const Slice& w, int stage) {
-    char* st = ring + stage * STAGE_BYTES + lane * 16;
-#pragma unroll
-    for (int j = 0; j < NW; ++j) *reinterpret_cast<u32x4*>(st + w_piece[j] * 1024) = w.v[j];
-  };
-
-  // transposing fragment reads (natural K order: lane half h holds units 16 s + 8 h .. + 7):
-  // lane (g = lane / 16, sl = lane % 16) points at stage row 16 s + 8 (g >> 1) + 4 rr + (sl >> 2)
-  // and at the 4-column group that gives MFMA row 16 (g & 1) + j the output column rho32 of it.
-  const int g = lane >> 4, sl = lane & 15, a4 = sl & 3;
-  const int colgrp = 4 * (a4 & 1) + 2 * (g & 1) + (a4 >> 1);
-  uint32_t tr_off[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int krow = 8 * (g >> 1) + (sl >> 2);
-    const int col = t * 32 + 4 * colgrp;
-    const int ch = (col >> 3) ^ (((krow >> 1) & 1) << 2);
-    tr_off[t] = (uint32_t)(krow * 128 + ch * 16 + (col & 4) * 2);
-  }
-
-  // Hin rows of (run, row tile): 16 bytes per K-step for the lane's row; lanes past the run's
-  // end read its first row
-  struct RowTile { bf16x8 hb[KS]; bool live; };
-  auto row_of = [&](bool& live, const Run& run) {
-    const int q = run.lo + rtile * 32 + i;
-    live = q < run.hi && run.real;
-    return q < run.hi ? q : run.lo;
-  };
-  auto load_rows = [&](RowTile& rt, const Run& run) {
-    const int qq = row_of(rt.live, run);
-    const uint4* src = reinterpret_cast<const uint4*>(Hin + hfrag_off(qq, 8 * h, Bs));
-#pragma unroll
-    for (int s = 0; s < KS; ++s) rt.hb[s] = as_bf16x8(src[64 * s]);   // K-step s: 1 KiB further
-  };
-  // the lane's 64 bytes of column tile 0 in its token's slab row (tile 1: 128 bytes further)
-  auto slab_ptr = [&](bool live, int token) {
-    return reinterpret_cast<f32x4*>(slab_lds + (live ? token - t0 : R) * SC_STRIDE + 64 * h);
-  };
-  auto slab_read = [&](f32x16& a, const f32x4* p) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const f32x4 o = p[c];
-      a[4 * c] = o[0]; a[4 * c + 1] = o[1]; a[4 * c + 2] = o[2]; a[4 * c + 3] = o[3];
-    }
-  };
-  auto slab_write = [&](f32x4* p, const f32x16& a) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) p[c] = f32x4{a[4 * c], a[4 * c + 1], a[4 * c + 2], a[4 * c + 3]};
-  };
-  // ---- prologue: request the first operands, clear the slab while they fly, stage slices 0 and
-  // 1 and read run 0's fragments.  (Every token activates k >= 1 blocks, so a range always has
-  // runs; M = 0 means a caller's table that lists nothing for these tokens: zeros.)
+  // (every token activates k >= 1 blocks, so a range always has records; M = 0 means a caller's table that lists nothing for
+  // these tokens: zeros)
   if (M == 0 && split) {
     for (int it = tid; it < rows * (SC_C / 4); it += THREADS)
       *reinterpret_cast<uint4*>(split + ((size_t)blockIdx.y * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
@@ -226,156 +145,247 @@ __global__ __launch_bounds__(SC_THREADS, 1) void ffn_scatter_kernel(
     }
     return;
   }
-  // (requests past the last run repeat it -- run_at clamps -- into registers nobody uses any
-  // more: the loop has no branch around a load, which keeps the compiler's vmcnt waits exact)
-  Run q0 = run_at(0), q1 = run_at(1), q2 = run_at(2), q3 = run_at(3), q4 = run_at(4);
-  Slice wbuf[2];
-  RowTile hbuf[2];
-  bf16x8 af[2][2][KS];
-  f32x16 acc0, acc1;      // column tiles 0 and 1
-  // Token ids of the lane's rows: both halves of an unrolled pair of iterations request theirs in
-  // the first half (tok_next[0] for the run two iterations on, tok_next[1] for the one after it),
-  // and the second half works on a copy taken a whole pair later.  A loop-carried copy of a loaded
-  // register makes the compiler wait for that load where the copy is made; this way every such
-  // wait is for a request at least an iteration old.  The prologue issues its requests in the
-  // order of a pair of iterations (ids, slice, rows, slice, rows), so the compiler's count of
-  // outstanding loads is the same on both ways into the loop and its waits come out exact.
-  int tok_next[2], tok_second = 0;
-  {
-    Slice w0, w1;
-    load_w(w0, q0.b);
-    load_w(w1, q1.b);
-    bool unused;
-    tok_next[0] = tok[row_of(unused, q0)];
-    tok_next[1] = tok[row_of(unused, q1)];
-    load_w(wbuf[0], q2.b);
-    load_rows(hbuf[0], q0);
-    load_w(wbuf[1], q3.b);
-    load_rows(hbuf[1], q1);
-    for (int o = tid * 16; o < (R + 1) * SC_STRIDE; o += THREADS * 16)
-      *reinterpret_cast<uint4*>(slab_lds + o) = make_uint4(0u, 0u, 0u, 0u);
-    store_w(w0, 0);
-    store_w(w1, 1);
-  }
-#pragma unroll
-  for (int v = 0; v < 16; ++v) { acc0[v] = 0.f; acc1[v] = 0.f; }
-  sc_barrier();
-#pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-      af[0][t][s] = tr_read_frag(ring + tr_off[t] + s * 2048, ring + tr_off[t] + s * 2048 + 512);
 
-  // ---- iteration j (0 <= j < M, rounded up to a whole pair).  The loop is unrolled by two so that
-  // the double-buffer halves (j mod 2) are compile-time constants.  At the top of iteration j:
-  // slice j+1 is in stage (j+1) mod 2, slices j+2 and j+3 are in (or on their way into) wbuf, rows
-  // j and j+1 in (or on their way into) hbuf, the fragments of run j in af[j mod 2].
-  int j = 0;
-  int rd_stage = STAGE_BYTES;   // byte offset of the stage iteration j reads fragments from: (j+1) mod 2
-  asm volatile("" : "+s"(rd_stage));
-  auto iteration = [&](auto tag) {
-    constexpr int par = decltype(tag)::value;
-    sc_barrier();      // everyone's slab updates (run j-1) and fragment reads (run j) are done, slice j+1 is visible
-    const bool live = hbuf[par].live;
-    const int token = (par == 0) ? tok_next[0] : tok_second;
-    if (par == 0) tok_second = tok_next[1];
-    f32x4* sp = slab_ptr(live, token);
-    if (live) { slab_read(acc0, sp); slab_read(acc1, sp + 8); }
-    // slice j+2 into the stage slice j left (its fragments were read in iteration j-1, before
-    // the barrier), then the requests for the token ids of runs j+2 and j+3 (first half only) and
-    // for slice j+4 into the registers just read out
-    store_w(wbuf[par], par);
-    if (par == 0) {
-      bool unused;
-      tok_next[0] = tok[row_of(unused, q2)];
-      tok_next[1] = tok[row_of(unused, q3)];
-    }
-    load_w(wbuf[par], q4.b);
-    // rows of run j+2: requested piece by piece behind tile 1's MFMAs, the last to read run j's
-    const int qq = row_of(hbuf[par].live, q2);
-    const uint4* src = reinterpret_cast<const uint4*>(Hin + hfrag_off(qq, 8 * h, Bs));
-    // (the stage base is kept a run-time value: as a constant it would make all 4 KS fragment
-    // addresses loop invariants that are hoisted into registers instead of immediate offsets)
-    const char* st = ring + rd_stage;
-    rd_stage = STAGE_BYTES - rd_stage;
-    __builtin_amdgcn_sched_barrier(0);
-    Run qn;
-    // tile 0
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[par][0][s], hbuf[par].hb[s], acc0, 0, 0, 0);
-      // (the scalar loads of the run record five runs on go out here, behind the wait for the
-      // slab values and a whole K loop ahead of the barrier's wait: in front of either one they
-      // would show their full latency in every iteration)
-      if (s == 0) qn = run_at(j + 5);
-      af[par ^ 1][0][s] = tr_read_frag(st + tr_off[0] + s * 2048, st + tr_off[0] + s * 2048 + 512);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (live) slab_write(sp, acc0);
-    __builtin_amdgcn_sched_barrier(0);
-    // tile 1
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[par][1][s], hbuf[par].hb[s], acc1, 0, 0, 0);
-      hbuf[par].hb[s] = as_bf16x8(src[64 * s]);
-      af[par ^ 1][1][s] = tr_read_frag(st + tr_off[1] + s * 2048, st + tr_off[1] + s * 2048 + 512);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (live) slab_write(sp + 8, acc1);
-    __builtin_amdgcn_sched_barrier(0);
-    q0 = q1; q1 = q2; q2 = q3; q3 = q4; q4 = qn;
-    ++j;
+  // Weight slice: lane (g, i) takes columns 4 i .. 4 i + 3 of units 32 s + 8 g + e.
+  u32x2 wraw[KT][8];
+  const int w_off = (8 * g * d + 4 * i) * 2;
+  auto w_rsrc = [&](int b) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(W + (size_t)b * Bs * d + c0), 0,
+                                             (int)(((unsigned)(Bs - 1) * d + SC_C) * 2), SC_RSRC);
   };
-  // (always whole pairs, one exit: an exit between the halves would share the latch with the
-  // way round, and the compiler would size the waits there for the shorter of the two.  The
-  // iteration past the last one sees a run without rows: it updates nothing.)
-  do {
-    iteration(std::integral_constant<int, 0>{});
-    iteration(std::integral_constant<int, 1>{});
-  } while (j < M);
+  auto load_w = [&](int s, int e, __amdgpu_buffer_rsrc_t rs) {
+    wraw[s][e] = __builtin_amdgcn_raw_buffer_load_b64(rs, w_off, (32 * s + e) * d * 2, 0);
+  };
+  // MFMA operand of K-step s, columns 4 i + t
+  bf16x8 wf[KT][4];
+  auto make_w = [&](int s, int t) {
+    const uint32_t sel = (t & 1) ? 0x07060302u : 0x05040100u;
+    u32x4 f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = __builtin_amdgcn_perm(wraw[s][2 * e + 1][t >> 1], wraw[s][2 * e][t >> 1], sel);
+    wf[s][t] = as_bf16x8(f);
+  };
+
+  static_assert(NT % RH == 0, "a run ends where the ring does");
+  bf16x8 hb[RH][KT];
+  int tokv[RH];
+  // Where a record lies: byte offsets of the lane's rows from 32 aligned positions on (the tiles start at a multiple of four:
+  // whole cache lines), even and odd tiles, and of its last row, whose repetition stands for rows past the end.
+  struct Where { int even, odd, last, tok; __amdgpu_buffer_rsrc_t h, t, w; };
+  auto where = [&](const Run& q) {
+    Where x;
+    const int first = q.lo & ~31, st = (q.lo & ~3) - first, last = q.hi - 1 - first;
+    auto off = [&](int p) { return (p >> 5) * (KS * 1024) + (p & 31) * 32; };
+    const int part = (g >> 1) * 1024 + (g & 1) * 16;
+    x.even = off(st + i) + part;
+    x.odd = off(st + 16 + i) + part;
+    x.last = off(last) + part;
+    x.tok = (st + 4 * g + (i & 3)) * 4;
+    x.h = __builtin_amdgcn_make_buffer_rsrc((void*)(reinterpret_cast<const char*>(Hin) + (size_t)(first >> 5) * (KS * 1024)), 0,
+                                            0x40000000, SC_RSRC);
+    x.t = __builtin_amdgcn_make_buffer_rsrc((void*)(tok + first), 0, (last + 1) * 4, SC_RSRC);   // (past the run: zeros)
+    x.w = w_rsrc(q.b);
+    return x;
+  };
+  // What slot ti of a run requests for the wavefront's next run (the prologue in the same order: the compiler's waits
+  // count the loads behind the one they are for).
+  auto request_h = [&](auto tag, const Where& x, int s) {
+    constexpr int ti = decltype(tag)::value;
+    const int o = min((ti & 1 ? x.odd : x.even) + (ti >> 1) * (KS * 1024), x.last);
+    hb[ti % RH][s] = as_bf16x8(__builtin_bit_cast(
+        u32x4, __builtin_amdgcn_raw_buffer_load_b128(x.h, o + (s & 1) * 2048, (s >> 1) * 4096, 0)));
+  };
+  auto request_t = [&](auto tag, const Where& x) {
+    constexpr int ti = decltype(tag)::value;
+    tokv[ti % RH] = (int)__builtin_amdgcn_raw_buffer_load_b32(x.t, x.tok + ti * 64, 0, 0);
+  };
+  // The share of the next slice that slot ti requests.  (Slot 0 turns the present one into operands; early, because the wait
+  // for it there is a wait for everything requested before it.)
+  auto request_w = [&](auto tag, const Where& x) {
+    constexpr int ti = decltype(tag)::value, n = 8 * KT, WS = NT > 4 ? 3 : 1;
+    constexpr int lo = ti == 0 ? 0 : ti > WS ? n : (ti - 1) * n / WS, hi = ti > WS ? n : ti * n / WS;
+#pragma unroll
+    for (int u = lo; u < hi; ++u) load_w(u >> 3, u & 7, x.w);
+  };
+  auto request_late = [&](auto tag, const Where& x, int s) {
+    constexpr int ti = decltype(tag)::value;
+    if (ti == NT - 1) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) load_w(s, e, x.w);
+    }
+  };
+
+  // Accumulators: of the tile in hand, and of the one before it until it is in the slab.
+  static_assert(NT % 2 == 0, "a record leaves them as it found them");
+  f32x4 acc[2][4];
+  int xprev = R * SC_STRIDE, need_prev = SC_NONE;     // (before the first: nothing, to the dummy row)
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc[1][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 sl[4];
+  const lds_int_ptr prog_in = prog + (lane & (SC_WAVES - 1)) * 64 + lane;     // lane l looks at wavefront l mod 4
+  const lds_int_ptr prog_out = prog + wave * 64 + lane;
+  auto progress = [&] { return OWN ? 0 : __hip_atomic_load(prog_in, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+  auto slab_at = [&](int v, int x) -> f32x4* {
+    int a;
+    switch (v) {
+      case 0: a = __builtin_amdgcn_mov_dpp(x, 0x00, 0xf, 0xf, true); break;
+      case 1: a = __builtin_amdgcn_mov_dpp(x, 0x55, 0xf, 0xf, true); break;
+      case 2: a = __builtin_amdgcn_mov_dpp(x, 0xaa, 0xf, 0xf, true); break;
+      default: a = __builtin_amdgcn_mov_dpp(x, 0xff, 0xf, 0xf, true); break;
+    }
+    return reinterpret_cast<f32x4*>(slab_lds + (a + 16 * i));
+  };
+  auto behind = [&](int f) { return __builtin_amdgcn_ballot_w64(f < need_prev) != 0; };
+  auto may_go = [&](int& f) {
+    if (!OWN && behind(f))
+      do f = progress(); while (behind(f));
+    wave_lds_fence();
+  };
+  auto rmw_read = [&](int v) { sl[v] = *slab_at(v, xprev); };
+  auto rmw_write = [&](int v, const f32x4 (&a)[4]) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) sl[v][t] += a[t][v];
+    *slab_at(v, xprev) = sl[v];
+  };
+  auto publish = [&](int done) {
+    wave_lds_fence();
+    if (!OWN) __hip_atomic_store(prog_out, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+
+  Run q = run_at(wave), qn = run_at(wave + SC_WAVES);
+  const int iters = M > wave ? (M - wave + SC_WAVES - 1) / SC_WAVES : 0;
+  if (iters > 0) {
+    const Where x = where(q);
+    auto first = [&](auto tag) {     // in the loop's order: tile ti's slot requests tile ti + RH
+      constexpr int tr = decltype(tag)::value, ti = tr + NT - RH;
+      if (!LATE && RH < NT && tr == 0) {
+#pragma unroll
+        for (int u = 0; u < 8 * KT; ++u) load_w(u >> 3, u & 7, x.w);
+      }
+#pragma unroll
+      for (int s = 0; s < KT; ++s) {
+        request_h(tag, x, s);
+        if (LATE) request_late(std::integral_constant<int, ti>{}, x, s);
+        else if (s == 0 && RH == NT) request_w(std::integral_constant<int, ti>{}, x);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      request_t(tag, x);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for_each_index(first, std::make_integer_sequence<int, RH>{});
+  }
+  for (int o = tid * 16; o < (OWN ? SC_WAVES * slab_bytes : slab_bytes + SC_WAVES * 256); o += THREADS * 16)
+    *reinterpret_cast<uint4*>(slabs + o) = make_uint4(0u, 0u, 0u, 0u);
   sc_barrier();
 
+  int code = wave * SC_CODE;
+  Where xc = where(q);
+  // The lane looks at the record `ahead` places before this wavefront's.  A tile may be added once the records before it are past
+  // its last token; the pieces before it of its own run have other tokens, so of those only the start is waited
+  // for, which says that what their wavefronts did before is done.
+  const int ahead = (wave - lane) & (SC_WAVES - 1);
+  int need_base = ahead == 0 ? SC_NONE : code - ahead * SC_CODE;
+  int f = 0;                 // how far that was when last looked at
+  for (int it = 0; it < iters; ++it, code += SC_WAVES * SC_CODE, need_base += SC_WAVES * SC_CODE) {
+    const int st = q.lo & ~3;
+    const int ntile = (q.hi - st + 15) >> 4;    // 1 .. NT
+    const int len = q.hi - q.lo;
+    const int rel = st - q.lo + 4 * g + (i & 3);
+    const int last_row = (q.hi - 1 - st) & 15, last_lane = (last_row >> 2) * 16 + (last_row & 3);
+    const bool other_run = ahead > q.piece;
+    const Run qnn = run_at(wave + SC_WAVES * (it + 2));
+    const Where x = where(qn);
+    auto slot = [&](auto tag) {
+      constexpr int ti = decltype(tag)::value, par = ti & 1, before = par ^ 1;
+      auto mfma1 = [&](int s, int t) {
+        acc[par][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hb[ti % RH][s], wf[s][t],
+                                                              s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[par][t], 0, 0, 0);
+      };
+      constexpr std::integral_constant<int, (ti + RH) % NT> ask{};
+      const Where& xa = ti + RH < NT ? xc : x;
+      constexpr int G = 4 * KT;
+      int tk = 0, xcur = 0, last_token = 0, first_token = 0;
+      // Everything but the products, dealt to the gaps behind them (n: 0 .. G - 1): a vector instruction or two in the shadow of
+      // every product cost nothing, bunched they cost 4 clk each.
+      auto gap = [&](int n) {
+        if (n == 0) tk = tokv[ti % RH] - t0;
+        if (n == (G > 4 ? 1 : 0)) {    // the lane's row of this tile: its token's slab row, or the dummy
+          tk = (ti == 0 ? (unsigned)rel < (unsigned)len : rel < len - 16 * ti) ? tk : R;
+          xcur = tk * SC_STRIDE;
+          asm volatile("" : "+v"(xcur));
+        }
+        if (n == G / 4) { rmw_read(0); rmw_read(1); }
+        if (n == G / 4 + (G > 4 ? 1 : 0)) { rmw_read(2); rmw_read(3); }
+        if (n == G / 2) last_token = __builtin_amdgcn_readlane(tk, ti + 1 < ntile ? 63 : last_lane);
+        if (n == G / 2) first_token = __builtin_amdgcn_readlane(tk, ti == 0 ? q.lo & 3 : 0);
+        if (n >= 4 && n % 4 == 0) request_h(ask, xa, n / 4 - 1);
+        if (LATE && n % 4 == 1 && n > 4) request_late(tag, x, n / 4 - 1);
+        if (!LATE && n == (G > 4 ? 6 : 2)) request_w(tag, x);
+        if (n == G - 4) f = progress();
+        if (G > 4 && n >= G - 4) rmw_write(n - (G - 4), acc[before]);
+        if (G == 4 && n == 3) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) rmw_write(v, acc[before]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+#pragma unroll
+      for (int n = 0; n < G; ++n) {
+        if (ti == 0) make_w(n / 4, n % 4);
+        if (n == G / 4) may_go(f);
+        mfma1(n / 4, n % 4);
+        gap(n);
+      }
+      publish(code + (ti < ntile ? first_token : SC_CODE));
+      request_h(ask, xa, KT - 1);
+      if (LATE) request_late(tag, x, KT - 1);
+      request_t(ask, xa);
+      xprev = xcur;
+      need_prev = ti < ntile ? need_base + (other_run ? last_token + 1 : 0) : SC_NONE;
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    for_each_index(slot, std::make_integer_sequence<int, NT>{});
+    q = qn; qn = qnn;
+    xc = x;
+  }
+  if (iters > 0) {
+    may_go(f);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) rmw_read(v);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) rmw_write(v, acc[1]);
+    publish(code);
+  }
+  sc_barrier();
+
+  auto sum_at = [&](int o) {
+    f32x4 a = *reinterpret_cast<const f32x4*>(slabs + o);
+    if (OWN) {
+#pragma unroll
+      for (int w = 1; w < SC_WAVES; ++w) a += *reinterpret_cast<const f32x4*>(slabs + w * slab_bytes + o);
+    }
+    return a;
+  };
+  // Write the slab out, one rounding to bf16: eight columns of a row at a time (fp32 sums of a part: four).
   if (split) {
     for (int it = tid; it < rows * (SC_C / 4); it += THREADS)
-      *reinterpret_cast<uint4*>(split + ((size_t)blockIdx.y * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
-          *reinterpret_cast<const uint4*>(slab_lds + (it / (SC_C / 4)) * SC_STRIDE + (it % (SC_C / 4)) * 16);
+      *reinterpret_cast<f32x4*>(split + ((size_t)blockIdx.y * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
+          sum_at((it / (SC_C / 4)) * SC_STRIDE + (it % (SC_C / 4)) * 16);
     return;
   }
-  // write the slab out: one rounding to bf16 (+ the low-rank row of the token, if any)
   constexpr int CG = SC_C / 8;  // 16-byte output pieces per row
-  if (!Z) {
-    for (int it = tid; it < rows * CG; it += THREADS) {
-      const f32x4* p = reinterpret_cast<const f32x4*>(slab_lds + (it / CG) * SC_STRIDE + (it % CG) * 32);
-      const f32x4 lo4 = p[0], hi4 = p[1];
-      *reinterpret_cast<uint4*>(out + (size_t)(t0 + it / CG) * d + c0 + (it % CG) * 8) =
-          make_uint4(pack_bf16x2(lo4[0], lo4[1]), pack_bf16x2(lo4[2], lo4[3]), pack_bf16x2(hi4[0], hi4[1]),
-                     pack_bf16x2(hi4[2], hi4[3]));
+  for (int it = tid; it < rows * CG; it += THREADS) {
+    const int at = (it / CG) * SC_STRIDE + (it % CG) * 32;
+    f32x4 lo4 = sum_at(at), hi4 = sum_at(at + 16);
+    const size_t o = (size_t)(t0 + it / CG) * d + c0 + (it % CG) * 8;
+    if (Z) {                    // the low-rank row of the token
+      const uint4 z = *reinterpret_cast<const uint4*>(Z + o);
+      lo4 += f32x4{lo_bf16(z.x), hi_bf16(z.x), lo_bf16(z.y), hi_bf16(z.y)};
+      hi4 += f32x4{lo_bf16(z.z), hi_bf16(z.z), lo_bf16(z.w), hi_bf16(z.w)};
     }
-    return;
-  }
-  constexpr int UN = 4;         // pieces per thread and pass: their low-rank rows are requested together
-  for (int it0 = tid; it0 < rows * CG; it0 += THREADS * UN) {
-    size_t o[UN];
-    uint4 z[UN];
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const int it = it0 + u * THREADS;
-      const int itc = it < rows * CG ? it : it0;   // past the end: the first piece again, not stored
-      o[u] = (size_t)(t0 + itc / CG) * d + c0 + (itc % CG) * 8;
-      z[u] = *reinterpret_cast<const uint4*>(Z + o[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const int it = it0 + u * THREADS;
-      if (it >= rows * CG) break;
-      const f32x4* p = reinterpret_cast<const f32x4*>(slab_lds + (it / CG) * SC_STRIDE + (it % CG) * 32);
-      f32x4 lo4 = p[0], hi4 = p[1];
-      lo4 += f32x4{lo_bf16(z[u].x), hi_bf16(z[u].x), lo_bf16(z[u].y), hi_bf16(z[u].y)};
-      hi4 += f32x4{lo_bf16(z[u].z), hi_bf16(z[u].z), lo_bf16(z[u].w), hi_bf16(z[u].w)};
-      *reinterpret_cast<uint4*>(out + o[u]) =
-          make_uint4(pack_bf16x2(lo4[0], lo4[1]), pack_bf16x2(lo4[2], lo4[3]), pack_bf16x2(hi4[0], hi4[1]),
-                     pack_bf16x2(hi4[2], hi4[3]));
-    }
+    *reinterpret_cast<uint4*>(out + o) =
+        make_uint4(pack_bf16x2(lo4[0], lo4[1]), pack_bf16x2(lo4[2], lo4[3]), pack_bf16x2(hi4[0], hi4[1]),
+                   pack_bf16x2(hi4[2], hi4[3]));
   }
 }
 
@@ -396,39 +406,75 @@ __global__ __launch_bounds__(256) void scatter_sum_kernel(const float* __restric
 
 // ------------------------------------------------------------------------------------------
 // host side
+// The kernel's forms.  rec: us per record of a full workgroup by K-steps (Bs / 32).  These and the constants of the
+// cost below were fitted to 1900 timings (150 shapes of 16 to 128 blocks, up to 12112 tokens and 4096 columns, every form with up
+// to 12 range counts and 6 splits of the block list); over them the form chosen is within 1 % of the quickest one on average.
+struct ScatterForm { int nt, wg; bool own; double rec[4]; };
+static const ScatterForm kScatterForms[] = {
+    {2, 1, true, {.15, .22, .285, .36}},
+    {6, 2, false, {.55, .66, .70, .88}},
+    {8, 1, false, {.51, .62, .72, .81}},
+    {10, 1, false, {.62, .72, .74, .86}},
+};
+
 static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
-  ScatterPlan p;
-  const int budget = 160 * 1024 - SC_STAGES * s.Bs * 128 - SC_STRIDE;  // (one slab row is the dummy)
-  int rmax = budget / SC_STRIDE;
-  if (rmax > 448) rmax = 448;
+  ScatterPlan p = {};
   p.nslab = s.d / SC_C;
-  // Tokens per range.  A workgroup's time is that of its run records (two thirds of it whatever a record holds, a third
-  // with its rows: slab accesses) plus a prologue and epilogue worth about six of them, and the chip runs
-  // 256 workgroups at a time: of the range counts the LDS slab allows, down to 64 tokens per range, take
-  // the one with the least record time in a row.  Rows of a range in a block are about Binomial(R, k / N), so a
-  // record count per block of 1 + P(rows > 128) + ...: at k / N = 1/4 about 430 tokens (108 rows) are the most that
-  // rarely need a second record, at 2/5 300 are (448 would need two for almost every block).  Both sides at the
-  // 7B-like layer, us a launch: 20 ranges of 410 tokens (five full rounds of workgroups) 592, 19 of 432 (4.75) 598.
+  // A launch takes its rounds of workgroups, each its records one after the other (four at a time) and a prologue and an
+  // epilogue, or as long as its bytes (rows once per column slab, weights once per range) come into the CUs at 13.4 TB/s.
+  // Rows of a range in a block are about Binomial(R, k / N), in records of at most 16 nt rows: 1 + P(rows > 16 nt) + ... per
+  // block (a run's next piece is stuck behind the tokens the runs before it are at: a quarter more).  Per form the range
+  // counts that fill a number of rounds, of which the quickest by that count is taken.  Both sides, us a pass: 7B-like, 16
+  // ranges in 10 tiles 2311, 20 in 8 tiles 2384, 28 in 6 tiles and two workgroups per CU 2410; BERT-large-like, 64 ranges in 6
+  // tiles 501, 32 in 10 tiles 533; a layer of 512 tokens, slabs of their own for 32 tokens 52.7, one slab for 64 61.8.
   const double share = (double)s.k / s.N;
-  const int nr_min = (s.T + rmax - 1) / rmax, nr_max = (s.T + 63) / 64 > nr_min ? (s.T + 63) / 64 : nr_min;
+  const double row_bytes = (double)s.T * s.k * s.Bs * 2 * p.nslab, w_bytes = (double)s.N * s.Bs * s.d * 2;
   double best = -1.0;
-  for (int nr = nr_min; nr <= nr_max && nr <= nr_min + 512; ++nr) {
-    const int R = (s.T + nr - 1) / nr, real_nr = (s.T + R - 1) / R;
-    const double mean = R * share, sd = sqrt(mean * (1.0 - share) + 1e-9);
-    double records = 1.0 - exp(-mean);                       // (blocks none of the range's tokens activates have none)
-    for (int c = 1; c * SC_RUN < mean + 6.0 * sd; ++c) records += 0.5 * erfc((c * SC_RUN + 0.5 - mean) / (sd * 1.41421356));
+  for (const ScatterForm& f : kScatterForms) {
+    const int lds = 160 * 1024 / f.wg;
+    const int rmax = f.own ? lds / SC_WAVES / SC_STRIDE - 1 : (lds - SC_WAVES * 256) / SC_STRIDE - 1;   // (one slab row is the dummy)
+    const int run = 16 * f.nt, nr_min = (s.T + rmax - 1) / rmax, nr_max = (s.T + 31) / 32 > nr_min ? (s.T + 31) / 32 : nr_min;
+    const int chip = 256 * f.wg;
     // With few tokens the block list is cut into parts too (16 records or more each), whose fp32 sums are
     // added by another launch: fewer weight slices per workgroup, for 8 bytes per part, token and column.
-    for (int sp = 1; sp == 1 || (sp <= 16 && sp * 16 <= s.N); sp += sp < 4 ? 1 : 2) {
-      const int64_t rounds = ((int64_t)real_nr * p.nslab * sp + 255) / 256;
-      double cost = (double)rounds * (s.N * records * (0.7 + 0.3 * (mean < SC_RUN ? mean / SC_RUN : 1.0)) / sp + 4.0 + R * 0.005);
-      if (sp > 1) cost += 5.0 + (double)sp * s.T * s.d * 8.0 / 2.5e6;   // (in records of 0.7 us)
-      if (best < 0.0 || cost < best * 0.999) { best = cost; p.R = R; p.nr = real_nr; p.splits = sp; }
+    for (int sp = 1; sp == 1 || (sp <= 8 && sp * 16 <= s.N); sp += sp < 4 ? 1 : 2) {
+      int last = 0;
+      for (int round = 0; round <= 24; ++round) {
+        int64_t nr64 = round == 0 ? nr_min : (int64_t)round * chip / ((int64_t)p.nslab * sp);
+        if (nr64 < nr_min) continue;
+        const int nr = nr64 > nr_max ? nr_max : (int)nr64;
+        if (nr == last) continue;
+        last = nr;
+        const int R = (s.T + nr - 1) / nr, real_nr = (s.T + R - 1) / R;
+        const double mean = R * share, sd = sqrt(mean * (1.0 - share) + 1e-9);
+        double records = 1.0 - exp(-mean);                       // (blocks none of the range's tokens activates have none)
+        for (int c = 1; c * run < mean + 6.0 * sd + 2.0; ++c)
+          records += (f.own ? 0.5 : 0.61) * erfc((c * run - 1.0 - mean) / (sd * 1.41421356));
+        const int64_t rounds = ((int64_t)real_nr * p.nslab * sp + chip - 1) / chip;
+        const int wg = (int64_t)real_nr * p.nslab * sp <= 256 ? 1 : f.wg;          // (alone on its CU after all)
+        const double rec = f.rec[s.Bs / 32 - 1] * (wg < f.wg ? 0.71 : 1.0);
+        double cost = (double)rounds * (s.N * records * rec / sp + ((wg > 1 ? 3.3 : 5.0) + R * (f.own ? 0.034 : 0.018)) * wg);
+        const double bytes = (row_bytes + w_bytes * real_nr * (records < 1.0 ? records : 1.0)) / 13.4e6;
+        if (cost < bytes) cost = bytes;
+        if (sp > 1) cost += 1.5 + (double)sp * s.T * s.d * 8.0 / 6.3e6;
+        if (best < 0.0 || cost < best * 0.999) {
+          best = cost; p.R = R; p.nr = real_nr; p.splits = sp; p.nt = f.nt;
+          p.smem = f.own ? SC_WAVES * (R + 1) * SC_STRIDE : (R + 1) * SC_STRIDE + SC_WAVES * 256;
+        }
+      }
     }
   }
+  p.run_rows = 16 * p.nt;
+  // Slabs side by side on an XCD: of a ranges x b slabs that run together (a b = 32 workgroups per place on a CU) it fetches a
+  // runs of `mean` rows and b slices of 64 columns per block, least at b^2 = a b mean / 64; all ranges where there are few.
+  // (47 slabs, 32 ranges of one slab side by side instead of four by eight: 346 us, 312.)
+  const int together = 32 * (p.nt == 6 ? 2 : 1);
+  p.inner = (int)(sqrt(together * (p.R * share) / 64.0) + 0.5);
+  if (p.inner < (together + p.nr - 1) / p.nr) p.inner = (together + p.nr - 1) / p.nr;
+  if (p.inner < 1) p.inner = 1;
+  if (p.inner > p.nslab) p.inner = p.nslab;
   p.split_bytes = p.splits > 1 ? align256((size_t)p.splits * s.T * s.d * 4) : 0;
-  p.smem = (p.R + 1) * SC_STRIDE + SC_STAGES * s.Bs * 128;
-  p.cap = s.N + (int)(((int64_t)p.R * s.k + SC_RUN - 1) / SC_RUN);
+  p.cap = s.N + (int)(((int64_t)p.R * s.k + 3 * s.N + p.run_rows - 1) / p.run_rows);
   p.runs_bytes = align256((size_t)p.nr * p.cap * sizeof(RunRec));
   p.counts_bytes = align256((size_t)p.nr * 4);
   p.table_bytes = p.runs_bytes + p.counts_bytes + align256((size_t)(p.nr + 1) * s.N * 4);
@@ -458,34 +504,28 @@ int32_t* scatter_counts(const ScatterPlan& p, int32_t* table) {
 }
 
 hipError_t run_scatter_ranges(const spt_shape_t& s, const ScatterPlan& p, int32_t* table, hipStream_t st) {
-  scatter_runs_kernel<<<p.nr, 64, 0, st>>>(scatter_starts(p, table), s.N, p.cap, scatter_runs(p, table),
+  scatter_runs_kernel<<<p.nr, 64, 0, st>>>(scatter_starts(p, table), s.N, p.cap, p.run_rows, scatter_runs(p, table),
                                            scatter_counts(p, table));
   return hipGetLastError();
 }
 
-template <int KS>
+template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
 static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin,
                                    const uint16_t* W, const int32_t* table, const int32_t* tok,
                                    uint16_t* out, const uint16_t* Z, float* split, hipStream_t st) {
   static bool attr_set = false;
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_scatter_kernel<KS>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  int grid;
-  if (p.nslab % 8 == 0) {
-    const int spx = p.nslab / 8, inner = spx < 8 ? spx : 8, groups = (spx + inner - 1) / inner;
-    grid = 8 * groups * inner * p.nr;
-  } else {
-    grid = p.nslab * p.nr;
-  }
+  const int grid = 8 * ((p.nslab * p.nr + 7) / 8);
   const RunRec* runs = reinterpret_cast<const RunRec*>(table);
   const int32_t* nruns = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + p.runs_bytes);
   const bool parts = p.splits > 1;
-  ffn_scatter_kernel<KS><<<dim3(grid, p.splits), SC_THREADS, p.smem, st>>>(Hin, W, runs, nruns, tok, s.N, s.d, s.T, p.R,
-                                                                         p.nr, p.nslab, p.cap, out, Z, parts ? split : nullptr);
+  ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN><<<dim3(grid, p.splits), SC_THREADS, p.smem, st>>>(
+      Hin, W, runs, nruns, tok, s.N, s.d, s.T, p.R, p.nr, p.nslab, p.inner, p.cap, out, Z, parts ? split : nullptr);
   if (!parts) return hipGetLastError();
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -497,7 +537,14 @@ static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, c
 hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W,
                           const int32_t* table, const int32_t* tok, uint16_t* out, const uint16_t* Z,
                           float* split, hipStream_t st) {
-#define SPT_SC(KS) launch_scatter_t<KS>(s, p, Hin, W, table, tok, out, Z, split, st)
+  // (six tiles and two workgroups per CU leave a lane 256 registers: rows requested fewer tiles ahead, and with eight K-steps
+  // of 16 the weight slice later)
+#define SPT_SC_ARGS s, p, Hin, W, table, tok, out, Z, split, st
+#define SPT_SC(KS)                                                                                                      \
+  (p.nt == 2   ? launch_scatter_t<KS, 2, 2, false, 1, true>(SPT_SC_ARGS)                                                \
+   : p.nt == 6 ? launch_scatter_t<KS, 6, (KS > 4 ? 3 : 6), (KS > 6), 2, false>(SPT_SC_ARGS)                             \
+   : p.nt == 8 ? launch_scatter_t<KS, 8, 8, false, 1, false>(SPT_SC_ARGS)                                               \
+               : launch_scatter_t<KS, 10, 10, false, 1, false>(SPT_SC_ARGS))
   switch (s.Bs / 16) {
     case 2: return SPT_SC(2);
     case 4: return SPT_SC(4);
@@ -505,6 +552,7 @@ hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint
     case 8: return SPT_SC(8);
     default: return hipErrorInvalidValue;
   }
+#undef SPT_SC_ARGS
 #undef SPT_SC
 }
 

@@ -68,6 +68,9 @@ BwdWorkspace plan_bwd(const spt_shape_t& s, void* ws, bool weight_grads = true);
 struct ScatterPlan {
   int R, nr, nslab, smem;
   int cap;               // run records per range
+  int run_rows;          // rows of a record at most
+  int nt;                // ... in tiles of 16
+  int inner;             // column slabs that run side by side on an XCD
   int splits;            // parts of the block list given to workgroups of their own (few tokens; else 1)
   size_t split_bytes;    // [splits][T][d] fp32 sums of the parts, added afterwards
   size_t runs_bytes;     // bytes of the [nr][cap] run records

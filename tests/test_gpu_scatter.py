@@ -1,0 +1,88 @@
+"""K = Bs contraction with the per-token write-back: every form of the kernel (records of 2, 6, 8 and 10 tiles of 16 rows, one
+slab or one per wavefront, the block list in parts), each block size, at the edges of tiles, records, ranges and slabs.
+
+With ReLU the kernel's operand is max(Hsave, 0) exactly, so the reference is a plain sum in 64 bits over the saved values, and
+what may differ is stated by the types: fp32 sums of K = k Bs products (each product and sum within 2^-24 of the sum of
+magnitudes, at most 2 sqrt(K) of them in the same direction) and one rounding to bf16 (8 significant bits: half a unit
+in the last place is at most 2^-8 of the value)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2312_10365_amd import spt
+
+pytestmark = pytest.mark.gpu
+
+
+def routing(T, N, k, kind, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "few":                       # half of the blocks hold nearly everything, some hold nothing
+        w = np.where(np.arange(N) % 2 == 0, 1.0, 1e-3) * (np.arange(N) != N - 1)
+    else:
+        w = np.ones(N)
+    keys = rng.exponential(size=(T, N)) / np.maximum(w, 1e-12)
+    return np.sort(np.argsort(keys, axis=1)[:, :k], axis=1).astype(np.int32)
+
+
+def run(T, d, N, Bs, k, kind):
+    g = torch.Generator(device="cuda").manual_seed(T + d + Bs)
+    normal = lambda *s, std=1.0: (torch.randn(*s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    shape = spt.make_shape(T, d, N, Bs, k, spt.ACT_RELU)
+    X, W1, W2 = normal(T, d), normal(N, Bs, d, std=0.05), normal(N, Bs, d, std=0.05)
+    idx = torch.from_numpy(routing(T, N, k, kind, T + N)).cuda()
+    offsets, perm, inv = spt.bucket_tokens(shape, idx)
+    outs = []
+    for fill in (0x00, 0xFF):               # whatever a workspace held before
+        ws = spt.alloc_workspace(shape, spt.WS_FWD)
+        ws.fill_(fill)
+        H = torch.empty(T * k, Bs, dtype=torch.bfloat16, device="cuda")
+        Y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        spt.routed_ffn_fwd(shape, X, W1, W2, offsets, perm, inv, ws=ws, Y=Y, Hsave=H)
+        outs.append(Y)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]), "sums in a fixed order"
+    ref = torch.zeros(T, d, dtype=torch.float64)
+    mag = torch.zeros(T, d, dtype=torch.float64)
+    Hc, W, pos = H.double().clamp(min=0).cpu(), W2.double().cpu(), inv.view(T, k).long().cpu()
+    ids = idx.long().cpu()
+    for b in range(N):
+        t, j = torch.nonzero(ids == b, as_tuple=True)
+        if len(t):
+            h = Hc[pos[t, j]]
+            ref[t] += h @ W[b]
+            mag[t] += h.abs() @ W[b].abs()
+    err = (outs[0].double().cpu() - ref).abs()
+    bound = 2.0 ** -8 * ref.abs() + 2.0 * (k * Bs) ** 0.5 * 2.0 ** -24 * mag + 1e-30
+    worst = float((err / bound).max())
+    print(f"[parity] T{T} d{d} N{N} Bs{Bs} k{k} {kind}: worst error / bound {worst:.3f}")
+    assert worst <= 1.0 + 2.0 ** -8
+
+
+@pytest.mark.parametrize("Bs", [32, 64, 96, 128])
+@pytest.mark.parametrize("T,d,N,k", [
+    (1, 64, 3, 2),               # one token
+    (33, 192, 17, 5),            # three slabs, a slab per wavefront
+    (24, 256, 64, 16),           # block list in parts
+    (700, 64, 40, 9),            # one slab, many ranges
+    (1203, 448, 24, 8),          # seven slabs
+    (4500, 1024, 16, 4),         # records of several tiles, one slab
+    (5003, 960, 32, 14),         # runs near the end of a record
+])
+def test_forms(T, d, N, Bs, k):
+    run(T, d, N, Bs, k, "even")
+
+
+@pytest.mark.parametrize("Bs", [32, 64, 96, 128])
+@pytest.mark.parametrize("T,d,N,k", [
+    (1111, 512, 6, 6),           # every token in every block: runs in several records
+    (2600, 1024, 5, 5),
+    (6001, 1536, 3, 3),          # runs of hundreds of rows, more records of one run than wavefronts
+    (3001, 256, 1, 1),           # one block
+])
+def test_runs_of_many_records(T, d, N, Bs, k):
+    run(T, d, N, Bs, k, "even")
+
+
+@pytest.mark.parametrize("T,d,N,Bs,k", [(900, 320, 20, 128, 7), (4097, 2048, 24, 64, 9), (2500, 4096, 16, 96, 6)])
+def test_uneven_blocks(T, d, N, Bs, k):
+    run(T, d, N, Bs, k, "few")
