@@ -910,8 +910,7 @@ __global__ __launch_bounds__(256) void ffn_up_few_rows_kernel(
 // K = bucket rows GEMMs for Bs <= 128: dW1 (Act = X, Hin = dHpre) and dW2 (Act = dY, Hin = act(H)).
 //   dW[b][u][c] = sum_{q in bucket b} Hin[q][u] * Act[tok[q]][c]    MFMA rows c, columns u
 // K runs over the bucket's rows in sorted order, so the sum order is fixed (no split-K, no
-// atomics).  A workgroup owns CT output columns x UT hidden units of one block (CT = 256 here; 512
-// further down).  UT = 128: wavefront (wm, wn) owns 128 columns x 64 units (4 x 2 MFMA tiles);
+// atomics).  A workgroup owns 256 output columns x UT hidden units of one block.  UT = 128: wavefront (wm, wn) owns 128 columns x 64 units (4 x 2 MFMA tiles);
 // UT = 64, for blocks of at most 64 units (a 128-unit tile would be half padding): wavefront wm
 // owns 64 columns x 64 units (2 x 2 tiles).  Two workgroups share a CU.
 // Both operands are token-major in memory, i.e. K is the strided dimension for both.  They
@@ -925,22 +924,24 @@ __global__ __launch_bounds__(256) void ffn_up_few_rows_kernel(
 // constant).  Issues 0..4 go out up front, iteration kt sends issue kt+5 (LA = 5 below).  At the top of
 // iteration kt the stages kt and kt+1 are visible and the fragments of stage kt are in
 // registers; the iteration multiplies them (8 MFMAs per wavefront) with, behind each MFMA, one
-// piece of the other work: first the 3 DMA instructions (the copies are what the kernel waits
-// for, so the slot the barrier has just freed is refilled at once: sending them last cost 4 %) and
-// the scalar loads of the token ids for the next iteration's DMA (wave-uniform addresses in the
-// constant address space; they leave the vmcnt bookkeeping alone), then the 6 fragment reads of
-// stage kt+1.
+// piece of the other work: first the 3 DMA instructions, one behind each MFMA (two behind the first one: 2 % slower),
+// then the 6 fragment reads of stage kt+1.
 // Rows past the bucket's end read a zero line for Hin (so they add nothing) and any valid row
 // for the activations.
-//
-// CT = 512: eight wavefronts share one workgroup's hidden-unit tiles for two 256-column halves (one
-// workgroup per CU; the same wavefronts per CU, tiles per wavefront and registers as two workgroups
-// of four).  The hidden-unit side is then copied once for 512 columns instead of once per 256: a
-// sixth fewer bytes into the CU, which is what the kernel waits for.  Wavefronts 4-7 copy the second
-// half's columns of the same token rows and no hidden-unit rows.
+// The token ids of the gathered rows are copied to LDS as well, 16 stages at a time and 16 to 32 stages ahead, each
+// wavefront those of its own rows.  (As scalar loads, one cache line per stage fetched an iteration ahead, they shared a
+// counter with the fragment reads: the matrix instructions of every stage waited for a load from L2, and no depth of the ring helped.
+// us, both sides on one box: T 8192, d 4096, 128 blocks of 128, 32 active, one product 303 -> 283; T 16384, d 1024, 64 blocks of 64, 16
+// active, both products 114 -> 89; T 8192, d 2048, 64 blocks of 128, 16 active and skewed 181 -> 157.)
+// What bounds it now: for the first of these MFMAs and fragment reads without copies take 229, copies alone (L2 delivers
+// them at twice that rate to loads that nothing else accompanies) less; the clock falls with the matrix units' load.  512 columns
+// per workgroup, for a sixth fewer copied bytes, gains nothing any more: 296 against 294; nor do 4, 5 or 7 slots, nor four workgroups of 64-unit
+// tiles per CU.
 constexpr int DW_KT = 16;                          // tokens per stage
-constexpr int DW_HALF_BYTES = DW_KT * 256 * 2;     // 8 KiB: 16 token rows x 256 columns
-constexpr int DW_SLOTS = 6;   // 72 KiB per workgroup with 256 x 128 tiles, 120 with 512 x 128 (a 7th slot gained nothing)
+constexpr int DW_CT = 256;                         // columns of a workgroup
+constexpr int DW_A_BYTES = DW_KT * DW_CT * 2;      // 8 KiB: 16 token rows x 256 columns
+constexpr int DW_SLOTS = 6;                        // 72 KiB per workgroup with 256 x 128 tiles
+constexpr int DW_ID_BYTES = 256;                   // token ids of a wavefront's rows of 16 stages
 
 // One product of the weight-gradient GEMM: its operands, the gradient, and the staging slots of pieces.
 struct DwOperands {
@@ -948,8 +949,8 @@ struct DwOperands {
   float *dW, *stage;
 };
 
-template <int UT, int CT>
-__global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
+template <int UT>
+__global__ __launch_bounds__(256, 2) void kq_gemm_kernel(
     DwOperands ops0, DwOperands ops1,
     const int32_t* __restrict__ tok, const uint16_t* __restrict__ zero_row, int npieces, int Bs,
     int d, const DwPiece* __restrict__ pieces, int nblocks) {
@@ -960,8 +961,6 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
   float* __restrict__ dW = ops.dW;
   float* __restrict__ stage = ops.stage;
   constexpr int MI = UT == 128 ? 4 : 2;               // 32-column tiles per wavefront
-  constexpr int DW_CT = CT;
-  constexpr int DW_A_BYTES = (CT / 256) * DW_HALF_BYTES;   // 8 or 16 KiB
   constexpr int DW_B_BYTES = DW_KT * UT * 2;          // 4 or 2 KiB
   constexpr int DW_STAGE_BYTES = DW_A_BYTES + DW_B_BYTES;
   constexpr int CPW = UT == 128 ? 128 : 64;           // columns per wavefront
@@ -995,9 +994,6 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = UT == 128 ? wave >> 1 : wave, wn = UT == 128 ? wave & 1 : 0;
-  const int wq = wave & 3, chalf = wave >> 2;          // copy role: quarter of the token rows, column half
-  const int fhalf = (wm * CPW) >> 8, fwm = wm & (256 / CPW - 1);  // fragment role: column half, place in it
-  const bool copies_b = wave < 4;
   const int i = lane & 31, h = lane >> 5;
   const uint32_t lds0 = (uint32_t)(uintptr_t)dw_smem;
   const int nk = (qe - qb + DW_KT - 1) / DW_KT;
@@ -1014,35 +1010,35 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
   int a_coloff[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int row = 4 * wq + 2 * j + lane_half;
-    const int col = c0 + 256 * chalf + (((lane & 31) ^ ((row & 3) << 2)) << 3);
+    const int row = 4 * wave + 2 * j + lane_half;
+    const int col = c0 + (((lane & 31) ^ ((row & 3) << 2)) << 3);
     a_coloff[j] = (col < d) ? col : c0;  // ragged last column tile: harmless duplicate, never stored
   }
-  const int b_row = UT == 128 ? 4 * wq + (lane >> 4) : 8 * (wave & 1) + (lane >> 3);
+  const int b_row = UT == 128 ? 4 * wave + (lane >> 4) : 8 * (wave & 1) + (lane >> 3);
   int b_coloff = UT == 128 ? u0 + (((lane & 15) ^ ((b_row & 3) << 2)) << 3)
                            : u0 + (((lane & 7) ^ (((b_row >> 1) & 1) << 2)) << 3);
   if (b_coloff >= Bs) b_coloff = u0;
-  typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-  const const_i32_ptr tok_c = (const_i32_ptr)(uintptr_t)tok;
-  auto load_ids = [&](int kt, int (&ids)[4]) {  // token ids of this wavefront's 4 rows of stage kt
-    const int r0 = qb + kt * DW_KT + 4 * wq;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) ids[e] = tok_c[min(r0 + e, qe - 1)];
+  // Token ids of this wavefront's four rows of 16 stages, 256 bytes; two such groups per wavefront.
+  const uint32_t ids0 = DW_SLOTS * DW_STAGE_BYTES + wave * 2 * DW_ID_BYTES;
+  auto fetch_ids = [&](int group) {
+    const int q = qb + (group * 16 + (lane >> 2)) * DW_KT + 4 * wave + (lane & 3);
+    dma4(tok + min(q, qe - 1), __builtin_amdgcn_readfirstlane(lds0 + ids0 + (group & 1) * DW_ID_BYTES));
   };
-  auto issue_a = [&](int j, int slot, const int (&ids)[4]) {
-    // (arithmetic select: a select between two array elements would become an indexed load
-    // from a private-memory copy of the array)
-    const int t = ids[2 * j] + lane_half * (ids[2 * j + 1] - ids[2 * j]);
-    dma16(Act + (size_t)t * d + a_coloff[j],
+  auto load_ids = [&](int kt, int (&ids)[2]) {  // of the lane's row of either copy of stage kt
+    const int* p = reinterpret_cast<const int*>(reinterpret_cast<const char*>(dw_smem) + ids0 + (kt & 31) * 16 + lane_half * 4);
+    ids[0] = p[0];
+    ids[1] = p[2];
+  };
+  auto issue_a = [&](int j, int slot, const int (&ids)[2]) {
+    dma16(Act + (size_t)ids[j] * d + a_coloff[j],
           __builtin_amdgcn_readfirstlane(
-              lds0 + (uint32_t)(slot * DW_STAGE_BYTES + chalf * DW_HALF_BYTES + (wq * 2 + j) * 1024)));
+              lds0 + (uint32_t)(slot * DW_STAGE_BYTES + (wave * 2 + j) * 1024)));
   };
   auto issue_b = [&](int slot, int kt) {
-    if (CT == 512 && !copies_b) return;  // (wave-uniform)
     const int q = qb + kt * DW_KT + b_row;
     const uint16_t* src = (q < qe) ? Hin + hfrag_off(q, b_coloff, Bs) : zero_row + ((lane & 15) << 3);
     dma16(src, __builtin_amdgcn_readfirstlane(
-                   lds0 + (uint32_t)(slot * DW_STAGE_BYTES + DW_A_BYTES + (UT == 128 ? wq : wave & 1) * 1024)));
+                   lds0 + (uint32_t)(slot * DW_STAGE_BYTES + DW_A_BYTES + (UT == 128 ? wave : wave & 1) * 1024)));
   };
 
   // Transposing fragment reads, lane (group g = lane/16, s = lane%16): token row
@@ -1058,7 +1054,7 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
   uint32_t a_off[MI], b_off[2];  // byte offsets of the r = 0 read inside a stage
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi)
-    a_off[mi] = (uint32_t)(fhalf * DW_HALF_BYTES + krow0 * 512 + ((((fwm * MI + mi) * 4 + (acol >> 3)) ^ sw) * 16) +
+    a_off[mi] = (uint32_t)(krow0 * 512 + ((((wm * MI + mi) * 4 + (acol >> 3)) ^ sw) * 16) +
                            (acol & 4) * 2);
 #pragma unroll
   for (int ni = 0; ni < 2; ++ni)
@@ -1078,8 +1074,11 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
       for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
 
   bf16x8 fa[2][MI], fb[2][2];
-  int ids[4] = {0, 0, 0, 0};
+  int ids[2] = {0, 0};
   if (nk > 0) {
+    fetch_ids(0);
+    fetch_ids(1);
+    wait_vmcnt<0>();
 #pragma unroll
     for (int st = 0; st < LA; ++st) {
       const int ks = st < klast ? st : klast;
@@ -1089,8 +1088,8 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
       issue_b(st, ks);
     }
     load_ids(LA < klast ? LA : klast, ids);
-    // issues 0 and 1 have landed (the LA - 2 later ones may be out: 3 instructions each, 2 without hidden rows)
-    if (CT == 512 && !copies_b) wait_vmcnt<2 * (LA - 2)>(); else wait_vmcnt<3 * (LA - 2)>();
+    // issues 0 and 1 have landed (the LA - 2 later ones may be out: 3 instructions each)
+    wait_vmcnt<3 * (LA - 2)>();
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int f = 0; f < MI; ++f) fa[0][f] = load_frag(ring, f);
@@ -1106,13 +1105,18 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
     // after the last stage the look-ahead reads the current one again: harmless
     const char* st1 = ring + ((kt + 1 < nk) ? next_slot : slot) * DW_STAGE_BYTES;
     const int kfill = kt + LA < klast ? kt + LA : klast;
-    int ids_next[4] = {0, 0, 0, 0};
+    const int kids = kt + LA + 1 < klast ? kt + LA + 1 : klast;
+    int ids_next[2] = {0, 0};
 #pragma unroll
     for (int m = 0; m < 2 * MI; ++m) {
       const int mi = m >> 1, ni = m & 1;
       acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][mi], fb[cur][ni], acc[mi][ni], 0, 0, 0);
-      if (m == 0) { issue_a(0, fill, ids); issue_a(1, fill, ids); }
-      else if (m == 1) { issue_b(fill, kfill); load_ids(kt + LA + 1 < klast ? kt + LA + 1 : klast, ids_next); }
+      if (m == 2) {
+        issue_b(fill, kfill);
+        if (((kt + LA + 1) & 15) == 0 && kt + LA + 1 < klast) fetch_ids((kt + LA + 1) / 16 + 1);  // (over the group that has been read to its end)
+        load_ids(kids, ids_next);
+      }
+      if (m < 2) issue_a(m, fill, ids);
       else if (m < MI + 2) fa[cur ^ 1][m - 2] = load_frag(st1, m - 2);
       else fb[cur ^ 1][m - MI - 2] = load_frag(st1, m - 2);
       __builtin_amdgcn_sched_barrier(0);
@@ -1122,11 +1126,11 @@ __global__ __launch_bounds__(CT, CT == 512 ? 1 : 2) void kq_gemm_kernel(
       fb[cur ^ 1][1] = load_frag(st1, MI + 1);
       __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) ids[e] = ids_next[e];
+    ids[0] = ids_next[0];
+    ids[1] = ids_next[1];
     // own copies of stage kt+2 have landed: only issues kt+3 .. kt+LA (3 instructions each) may
     // be outstanding; the barrier makes everyone's visible and ends all reads of stage kt
-    if (CT == 512 && !copies_b) wait_vmcnt<2 * (LA - 2)>(); else wait_vmcnt<3 * (LA - 2)>();
+    wait_vmcnt<3 * (LA - 2)>();
     __builtin_amdgcn_s_barrier();
   };
   int slot = 0;
@@ -1454,30 +1458,21 @@ static hipError_t launch_up(const spt_shape_t& s, const uint16_t* Wa, const uint
 }
 
 // One instantiation of the weight-gradient GEMM (UT = hidden units per workgroup tile).
-template <int UT, int CT>
-static hipError_t launch_dw_ct(const DwOperands* ops, int nops, const Schedule& sc, int N, int Bs, int d, hipStream_t st) {
-  const int nct = (d + CT - 1) / CT, np = sc.dw_cap;
+template <int UT>
+static hipError_t launch_dw_ut(const DwOperands* ops, int nops, const Schedule& sc, int N, int Bs, int d, hipStream_t st) {
+  const int nct = (d + DW_CT - 1) / DW_CT, np = sc.dw_cap;
   const int gx = nct % 8 != 0 && 8 % nct == 0 ? 8 * ((np + 8 / nct - 1) / (8 / nct)) : nct * np;
-  const int dw_smem = DW_SLOTS * ((CT / 256) * DW_HALF_BYTES + DW_KT * UT * 2);
+  const int dw_smem = DW_SLOTS * (DW_A_BYTES + DW_KT * UT * 2) + 4 * 2 * DW_ID_BYTES;
   static bool attr_set = false;
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kq_gemm_kernel<UT, CT>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kq_gemm_kernel<UT>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, dw_smem);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  kq_gemm_kernel<UT, CT><<<dim3(gx, (Bs + UT - 1) / UT, nops), CT, dw_smem, st>>>(
+  kq_gemm_kernel<UT><<<dim3(gx, (Bs + UT - 1) / UT, nops), 256, dw_smem, st>>>(
       ops[0], ops[nops - 1], sc.tok, sc.zero_row, np, Bs, d, sc.dw_pieces, N);
   return hipGetLastError();
-}
-
-// 512-column workgroups where each CU still gets at least four of them one after the other (with
-// fewer, the uneven last round costs more than the shared hidden-unit copies save: measured on the
-// skewed OPT-1.3B-like shape), 256-column ones otherwise.
-template <int UT>
-static hipError_t launch_dw_ut(const DwOperands* ops, int nops, const Schedule& sc, int N, int Bs, int d, hipStream_t st) {
-  if (d % 512 == 0 && (int64_t)(d / 512) * sc.dw_cap >= 1024) return launch_dw_ct<UT, 512>(ops, nops, sc, N, Bs, d, st);
-  return launch_dw_ct<UT, 256>(ops, nops, sc, N, Bs, d, st);
 }
 
 // dW[b][u][c] = sum_{q in bucket b} Hin[q][u] * Act[tok[q]][c], the narrow-block weight-gradient GEMM over the

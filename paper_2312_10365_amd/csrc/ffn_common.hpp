@@ -71,6 +71,10 @@ __device__ __forceinline__ int kd_slot(int row, int chunk) { return row * 4 + (c
 __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
 }
+// The same with 4 bytes per lane.
+__device__ __forceinline__ void dma4(const void* gptr, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(lds_base), "v"(gptr) : "memory");
+}
 // s_waitcnt vmcnt(N) alone (N <= 63): the other counters are left at their maxima.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

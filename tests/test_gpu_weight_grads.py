@@ -1,0 +1,48 @@
+"""Weight gradients with the gathered rows' token ids staged a group of stages ahead: bucket sizes around the 16- and
+32-row stages, the groups (256 rows) and two of them, every tile width, narrow and wide blocks.
+
+One block per token, so a block's bucket has exactly the rows asked for, its tokens scattered over the batch.  With ReLU the
+operands of dW2 are max(Hsave, 0) and dY as they are: what may differ from a sum in 64 bits is the fp32 sum of K rows (each
+product exact, each addition within 2^-24 of the sum of magnitudes, at most 2 sqrt(K) of them in the same direction).  dW1's
+operand dHpre is rounded to bf16 first (within 2^-8 of each value, of which K independent ones add up to at most their sum)
+after an fp32 sum of d products."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2312_10365_amd import spt
+
+pytestmark = pytest.mark.gpu
+
+SIZES = (0, 1, 15, 16, 17, 33, 96, 111, 255, 256, 257, 271, 287, 300, 511, 512, 513, 529, 545, 800)
+
+
+@pytest.mark.parametrize("d,Bs", [(64, 64), (192, 32), (320, 96), (512, 128), (256, 160), (576, 288)])
+def test_bucket_sizes_around_the_groups(d, Bs):
+    sizes = np.array(SIZES)
+    N, T = len(sizes), int(sizes.sum())
+    rng = np.random.default_rng(d + Bs)
+    block = rng.permutation(np.repeat(np.arange(N), sizes)).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(d + Bs)
+    normal = lambda *s, std=1.0: (torch.randn(*s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    shape = spt.make_shape(T, d, N, Bs, 1, spt.ACT_RELU)
+    X, dY, W1, W2 = normal(T, d), normal(T, d), normal(N, Bs, d, std=0.05), normal(N, Bs, d, std=0.05)
+    print(f"d {d} Bs {Bs} T {T}", flush=True)
+    offsets, perm, inv = spt.bucket_tokens(shape, torch.from_numpy(block[:, None]).cuda())
+    _, H = spt.routed_ffn_fwd(shape, X, W1, W2, offsets, perm, inv)
+    _, dW1, dW2 = spt.routed_ffn_bwd(shape, X, W1, W2, dY, offsets, perm, inv, H)
+    torch.cuda.synchronize()
+    x, dy, w2, h, pos = X.double().cpu(), dY.double().cpu(), W2.double().cpu(), H.double().cpu(), inv.view(-1).long().cpu()
+    for b in range(N):
+        t = torch.from_numpy(np.nonzero(block == b)[0])
+        K = max(len(t), 1)
+        hb = h[pos[t]]
+        act, dh = hb.clamp(min=0), (dy[t] @ w2[b].T) * (hb > 0)
+        dh_mag = (dy[t].abs() @ w2[b].abs().T) * (hb > 0)
+        for name, got, left, right, extra in (
+                ("dW2", dW2[b], act, dy[t], 0.0),
+                ("dW1", dW1[b], dh, x[t], (2.0 ** -8 * dh.abs() + 2.0 * d ** 0.5 * 2.0 ** -24 * dh_mag).T @ x[t].abs())):
+            ref, mag = left.T @ right, left.abs().T @ right.abs()
+            bound = extra + 2.0 * K ** 0.5 * 2.0 ** -24 * mag + 2.0 ** -23 * ref.abs() + 1e-30
+            worst = float(((got.double().cpu() - ref).abs() / bound).max())
+            assert worst <= 1.0 + 2.0 ** -8, (name, b, K, worst)
