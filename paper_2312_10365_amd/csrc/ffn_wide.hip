@@ -68,7 +68,8 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   constexpr bool B_TR = (OP == OP_DW);
   static_assert((MA == 4 && NB == 4) || OP != OP_DW, "the weight gradients have full tiles only");
   using Tile = WideTile<MA, NB>;
-  constexpr int W_STAGE = Tile::STAGE, W_STAGES = Tile::STAGES;
+  // (weight gradients: a slot less, for the token ids)
+  constexpr int W_STAGE = Tile::STAGE, W_STAGES = OP == OP_DW ? Tile::STAGES - 1 : Tile::STAGES;
   constexpr int A_CH = 8 * MA, B_CH = 8 * NB;      // 16-byte chunks of a K-row of a K-major operand
   constexpr int A_HALF = 32 * MA, B_HALF = 32 * NB;  // A-side / B-side indices of a wavefront
   const int Bs = p.Bs, d = p.d;
@@ -132,23 +133,22 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
     }
   }
   const int lane_half = lane >> 5;
-  typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-  const const_i32_ptr tok_c = (const_i32_ptr)(uintptr_t)p.tok;
-  // Token ids of the 8 gathered K-rows this wavefront copies per stage (dW only): wave-uniform
-  // addresses in the constant address space, so they are scalar loads, which leave the vmcnt
-  // bookkeeping of the DMA alone (the ids were written by an earlier launch).  They are
-  // fetched one iteration before the copy that needs them is issued.
-  auto load_ids = [&](int kt, int (&ids)[8]) {
+  // Token ids of the gathered K-rows (dW only), copied to LDS as well: the eight rows of this wavefront of 8 stages
+  // are a group of 256 bytes, two groups per wavefront.  (As scalar loads they shared a counter with the fragment
+  // reads, and every stage waited for a load from L2: us, T 8192, d 4096, 4 blocks of 2752, 2 active, a gradient: 395 -> 345.)
+  const uint32_t ids0 = W_STAGES * W_STAGE + wave * 512;
+  auto fetch_ids = [&](int group) {
+    const int q = qb + (group * 8 + (lane >> 3)) * WK + 8 * wave + (lane & 7);
+    dma4(p.tok + min(q, qe - 1), __builtin_amdgcn_readfirstlane(lds0 + ids0 + (group & 1) * 256));
+  };
+  auto load_ids = [&](int kt, int (&ids)[4]) {   // of the lane's row of each copy of stage kt
+    const int* at = reinterpret_cast<const int*>(reinterpret_cast<const char*>(smem) + ids0 + (kt & 15) * 32 + lane_half * 4);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r0 = qb + kt * WK + 2 * (wave * 4 + j);
-      ids[2 * j] = tok_c[min(r0, qe - 1)];
-      ids[2 * j + 1] = tok_c[min(r0 + 1, qe - 1)];
-    }
+    for (int j = 0; j < 4; ++j) ids[j] = at[2 * j];
   };
   // One DMA instruction: j-th of this wavefront for operand A (which = 0) or B (which = 1),
   // K-stage kt into ring slot `stage`.
-  auto issue_one = [&](int which, int j, int stage, int kt, const int (&ids)[8]) {
+  auto issue_one = [&](int which, int j, int stage, int kt, const int (&ids)[4]) {
     const uint32_t dst = __builtin_amdgcn_readfirstlane(
         lds0 + (uint32_t)(stage * W_STAGE + (which ? Tile::A_REGION : 0) + (wave * (which ? NB : MA) + j) * 1024));
     if (which == 0) {
@@ -161,9 +161,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
       } else if (OP == OP_PART) {
         dma16(a_ptr[j] + (size_t)kt * WK * d, dst);
       } else {
-        // (arithmetic select: a select between two array elements would be turned into an
-        // indexed load from a private-memory copy of the array)
-        dma16(Aop + (size_t)(ids[2 * j] + lane_half * (ids[2 * j + 1] - ids[2 * j])) * d + a_coloff[j], dst);
+        dma16(Aop + (size_t)ids[j] * d + a_coloff[j], dst);
       }
     } else {
       if (!B_TR) {
@@ -229,14 +227,19 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   // other instruction of the iteration is therefore placed right behind an MFMA (each keeps the
   // matrix pipe busy for 32 cycles): after MFMA 0..7 of a K-step one fragment read for the next
   // K-step (issued half an iteration before its data are used), after MFMA 8..11 one DMA
-  // instruction, after MFMA 12 the scalar loads of the token ids for the next iteration's DMA.
+  // instruction, after MFMA 12 the reads of the token ids for the next iteration's DMA.
   // (The smaller tiles: a fragment read behind each of the first MFMAs, the copies behind the last ones.)
   const int klast = nk - 1;
   auto kclamp = [&](int j) { return j < klast ? j : klast; };
-  int ids[8] = {0, 0, 0, 0, 0, 0, 0, 0}, ids_next[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  int ids[4] = {0, 0, 0, 0}, ids_next[4] = {0, 0, 0, 0};
   bf16x8 fa[2][MA], fb[2][NB];
   const char* ring = reinterpret_cast<const char*>(smem);
   if (nk > 0) {
+    if (OP == OP_DW) {
+      fetch_ids(0);
+      fetch_ids(1);
+      wait_vmcnt<0>();
+    }
 #pragma unroll
     for (int st = 0; st < W_STAGES - 1; ++st) {
       if (OP == OP_DW) load_ids(kclamp(st), ids);
@@ -278,13 +281,14 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
         if (m >= c0 && m < c0 + copies) {
           issue_one(half, m - c0, fill, kfill, ids);
         } else if (m == 12 && half == 1 && OP == OP_DW) {
+          if (((kt + W_STAGES) & 7) == 0 && kt + W_STAGES < klast) fetch_ids((kt + W_STAGES) / 8 + 1);   // (over the group read to its end)
           load_ids(kclamp(kt + W_STAGES), ids_next);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ids[e] = ids_next[e];
+    for (int e = 0; e < 4; ++e) ids[e] = ids_next[e];
     // own copies of stage kt+2 have landed: only issues kt+3 .. kt+S-1 (MA + NB instructions each) may
     // be outstanding; the barrier makes everyone's visible and ends all reads of stage kt
     wait_vmcnt<(W_STAGES - 3) * (MA + NB)>();
