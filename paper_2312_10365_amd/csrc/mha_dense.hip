@@ -147,6 +147,10 @@ __device__ __forceinline__ u32x4 tr_frag(const char* p) {
 // n 1024, L 200 92 / 132 -> 92 / 91; S 32, n 2048, L 256 174 / 234 -> 149 / 147.  (128-wide with 512 keys per chunk of scores and
 // the fragments of one tile fetched behind the other's products: 262 / 265 where 242 / 244 is; a barrier more, to start the
 // copies before the scatter: 266 / 266; 64-wide with 256 keys per chunk of scores 184 / 182 where 149 / 147 is.)
+// 64-wide heads of several chunks: eight key groups, each wavefront both column tiles, so a weight is split once and not by two
+// column groups (the vector units' largest part); forward, four groups -> eight: S 32, n 2048, L 256 139 -> 129; S 64, n 1024, L 200
+// 81 -> 77; S 256, n 600, L 90 131 -> 127.  With one chunk the second accumulator spills and nothing is gained (121 / 122); 128-wide
+// heads with four groups and chunks of 128 keys spill: 241 -> 314 at S 96, n 1100, L 137.
 constexpr int NW = 8, BQ = 32, NT = NW * 64;
 template <int DH, int KT>
 constexpr bool rows_planes() { return DH == 128 || KT == 1; }
@@ -889,7 +893,7 @@ hipError_t rows_by_shape(const spt_mha_shape_t& s, const uint16_t* R, const uint
   if (s.dh == 64) {
     if (s.n <= 256) SPT_ROWS(64, 1, 4, true);
     if (s.n <= 512) SPT_ROWS(64, 2, 4, true);
-    SPT_ROWS(64, 2, 4, false);
+    SPT_ROWS(64, 2, 8, false);
   }
   if (s.n <= 256) SPT_ROWS(128, 1, 2, true);
   if (s.n <= 512) SPT_ROWS(128, 2, 4, true);
