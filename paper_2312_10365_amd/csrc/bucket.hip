@@ -16,35 +16,48 @@ namespace spt {
 
 constexpr int kWordsPerChunk = kBucketChunkTokens / 32;
 
-__device__ __forceinline__ void build_chunk_mask(const int32_t* __restrict__ idx, int T, int N,
-                                                 int k, int chunk, uint32_t* mask) {
-  for (int e = threadIdx.x; e < N * kWordsPerChunk; e += blockDim.x) mask[e] = 0u;
-  __syncthreads();
-  const int t0 = chunk * kBucketChunkTokens;
-  const int nt = min(kBucketChunkTokens, T - t0);
-  const int64_t p0 = (int64_t)t0 * k;
-  // (eight loads in flight per thread: one at a time, each waits out its own latency)
-  for (int e0 = threadIdx.x; e0 < nt * k; e0 += 8 * blockDim.x) {
-    int bv[8];
+// A thread's pairs of a chunk of `count`: the first eight, tid, tid + threads, .., are held in registers (requested together, and once
+// for all passes over them), what is beyond -- more than eight times the threads -- is loaded in every pass.
+struct ChunkPairs {
+  const int32_t* idx;
+  int count, held[8];
+  __device__ __forceinline__ ChunkPairs(const int32_t* from, int n) : idx(from), count(n) {
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int e = e0 + u * blockDim.x;
-      bv[u] = (e < nt * k) ? idx[p0 + e] : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int tl = (e0 + u * blockDim.x) / k;
-      if (bv[u] >= 0 && bv[u] < N) atomicOr(&mask[bv[u] * kWordsPerChunk + (tl >> 5)], 1u << (tl & 31));
+      const int e = threadIdx.x + u * blockDim.x;
+      held[u] = e < count ? idx[e] : -1;
     }
   }
+  // f(pair, its block), for blocks below N
+  template <class F>
+  __device__ __forceinline__ void each(int N, F f) const {
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (held[u] >= 0 && held[u] < N) f((int)(threadIdx.x + u * blockDim.x), held[u]);
+    for (int e = threadIdx.x + 8 * blockDim.x; e < count; e += blockDim.x) {
+      const int b = idx[e];
+      if (b >= 0 && b < N) f(e, b);
+    }
+  }
+};
+
+__device__ __forceinline__ void build_chunk_mask(const ChunkPairs& pairs, int N, int k, uint32_t* mask) {
+  for (int e = threadIdx.x; e < N * kWordsPerChunk; e += blockDim.x) mask[e] = 0u;
+  __syncthreads();
+  pairs.each(N, [&](int e, int b) {
+    const int tl = e / k;
+    atomicOr(&mask[b * kWordsPerChunk + (tl >> 5)], 1u << (tl & 31));
+  });
   __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void bucket_hist_kernel(const int32_t* __restrict__ idx, int T,
+__global__ __launch_bounds__(1024) void bucket_hist_kernel(const int32_t* __restrict__ idx, int T,
                                                           int N, int k,
                                                           int32_t* __restrict__ chunk_hist) {
   extern __shared__ uint32_t mask[];
-  build_chunk_mask(idx, T, N, k, blockIdx.x, mask);
+  const int t0 = blockIdx.x * kBucketChunkTokens;
+  const ChunkPairs pairs(idx + (int64_t)t0 * k, min(kBucketChunkTokens, T - t0) * k);
+  build_chunk_mask(pairs, N, k, mask);
   for (int b = threadIdx.x; b < N; b += blockDim.x) {
     int c = 0;
 #pragma unroll
@@ -98,20 +111,36 @@ __global__ __launch_bounds__(1024) void bucket_scatter_kernel(
   extern __shared__ uint32_t mask[];                       // [N][4] bits, then [N] first position per bucket
   int32_t* first = reinterpret_cast<int32_t*>(mask + N * kWordsPerChunk);
   __shared__ int32_t wtot[16];
-  const int chunk = blockIdx.x;
+  const int chunk = blockIdx.x, t0 = chunk * kBucketChunkTokens;
+  const int64_t p0 = (int64_t)t0 * k;
+  const ChunkPairs pairs(idx + p0, min(kBucketChunkTokens, T - t0) * k);
   if (kScan) {
-    const int b = threadIdx.x;
+    // thread = bucket and a share of the chunks (sixteen or more, if the threads are not enough), sixteen loads in flight
+    __shared__ int2 share[1024];
+    const int blog = N > 1 ? 32 - __clz(N - 1) : 0, shares = min((int)blockDim.x >> blog, (nchunks + 15) / 16);
+    const int b = threadIdx.x, sb = b & ((1 << blog) - 1), sh = b >> blog;
+    const int per = (nchunks + shares - 1) / shares, cend = sh < shares ? min(nchunks, (sh + 1) * per) : 0;
     int before = 0, all = 0;
-    if (b < N) {
-      for (int c0 = 0; c0 < nchunks; c0 += 16) {           // sixteen loads in flight
+    if (sb < N) {
+      for (int c0 = sh * per; c0 < cend; c0 += 16) {
         int v[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = (c0 + u < nchunks) ? chunk_hist[(size_t)(c0 + u) * N + b] : 0;
+        for (int u = 0; u < 16; ++u) v[u] = (c0 + u < cend) ? chunk_hist[(size_t)(c0 + u) * N + sb] : 0;
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
           before += c0 + u < chunk ? v[u] : 0;
           all += v[u];
         }
+      }
+    }
+    share[b] = make_int2(before, all);
+    __syncthreads();
+    before = all = 0;
+    if (b < N) {
+      for (int x = 0; x < shares; ++x) {
+        const int2 y = share[(x << blog) + b];
+        before += y.x;
+        all += y.y;
       }
     }
     int total;
@@ -124,30 +153,16 @@ __global__ __launch_bounds__(1024) void bucket_scatter_kernel(
   } else {
     for (int b = threadIdx.x; b < N; b += blockDim.x) first[b] = offsets[b] + chunk_hist[(size_t)chunk * N + b];
   }
-  build_chunk_mask(idx, T, N, k, chunk, mask);
-  const int t0 = chunk * kBucketChunkTokens;
-  const int nt = min(kBucketChunkTokens, T - t0);
-  const int64_t p0 = (int64_t)t0 * k;
-  for (int e0 = threadIdx.x; e0 < nt * k; e0 += 4 * blockDim.x) {   // four pairs at a time per thread
-    int bv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = e0 + u * blockDim.x;
-      bv[u] = (e < nt * k) ? idx[p0 + e] : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = e0 + u * blockDim.x, b = bv[u];
-      if (b < 0 || b >= N) continue;
-      const int tl = e / k;
-      const uint32_t* m = mask + b * kWordsPerChunk;
-      int r = __popc(m[tl >> 5] & ((1u << (tl & 31)) - 1u));
-      for (int w = 0; w < (tl >> 5); ++w) r += __popc(m[w]);
-      const int q = first[b] + r;
-      perm[q] = (int32_t)(p0 + e);
-      inv[p0 + e] = q;
-    }
-  }
+  build_chunk_mask(pairs, N, k, mask);
+  pairs.each(N, [&](int e, int b) {
+    const int tl = e / k;
+    const uint32_t* m = mask + b * kWordsPerChunk;
+    int r = __popc(m[tl >> 5] & ((1u << (tl & 31)) - 1u));
+    for (int w = 0; w < (tl >> 5); ++w) r += __popc(m[w]);
+    const int q = first[b] + r;
+    perm[q] = (int32_t)(p0 + e);
+    inv[p0 + e] = q;
+  });
 }
 
 // All pairs by one workgroup: the (block x token) bitmask of the whole batch, bits before each of its words, and
@@ -251,9 +266,16 @@ hipError_t run_bucket(const spt_shape_t& s, const int32_t* idx, int32_t* offsets
   }
   const int nchunks = (s.T + kBucketChunkTokens - 1) / kBucketChunkTokens;
   const size_t smem = (size_t)s.N * kWordsPerChunk * sizeof(uint32_t);
+  // Two pairs of a chunk per thread, a thread per bucket at least.  A chunk's work is a chain of loads, LDS atomics and
+  // stores whose length is the number of pairs a thread has, behind that of the histograms it adds up.  us, 256 threads with
+  // the pairs loaded anew for every pass and all histograms per thread -> this: 8192 tokens, 128 blocks, 32 each 13.8 -> 9.4;
+  // 16384, 64, 16 11.3 -> 7.3; 3001, 128, 32 11.8 -> 8.2.  512 threads there: 10.9, 7.6, 9.8; 1024 threads for 2 of 4 blocks, 8192
+  // tokens, 8.5 where 256 take 6.0.
+  int threads = 256;
+  while (threads < 1024 && (threads < s.N || threads < kBucketChunkTokens / 2 * s.k)) threads *= 2;
   {
     ScopedKernelTimer tm(kSlotBucketHist, st);
-    bucket_hist_kernel<<<nchunks, 256, smem, st>>>(idx, s.T, s.N, s.k, chunk_hist);
+    bucket_hist_kernel<<<nchunks, threads, smem, st>>>(idx, s.T, s.N, s.k, chunk_hist);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -266,7 +288,6 @@ hipError_t run_bucket(const spt_shape_t& s, const int32_t* idx, int32_t* offsets
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   ScopedKernelTimer tm(kSlotBucketScatter, st);
-  const int threads = s.N <= 256 ? 256 : 1024;
   const size_t sm = smem + (size_t)s.N * sizeof(int32_t);
   if (scan)
     bucket_scatter_kernel<false><<<nchunks, threads, sm, st>>>(idx, s.T, s.N, s.k, chunk_hist, nchunks, offsets, perm, inv);
