@@ -87,28 +87,31 @@ __device__ __forceinline__ void plan_position(const PlanArgs& p, const int32_t* 
     for (int r = rq + 1; r <= p.nr; ++r) p.starts[(size_t)r * p.N + b] = q + 1;
 }
 
-// Workgroup 0 builds the tables over buckets, the others take 1024 sorted positions each; kAll: one
-// workgroup does everything, the run lists of the K = Bs kernel included (few pairs: a launch of the
-// path then costs more than the work in it).
+// Workgroup 0 builds the row tiles' lists over the buckets, workgroup 1 the pieces of the weight gradients (one after the
+// other in one workgroup they were the length of the launch; us: 8192 tokens, 128 blocks, 32 each 10.8 -> 8.8; 16384, 64, 16
+// 9.6 -> 7.7; 2048, 32, 8 6.1 -> 5.1), the others take 1024 sorted positions each; kAll: one workgroup does everything, the
+// run lists of the K = Bs kernel included (few pairs: a launch of the path then costs more than the work in it).
 template <bool kAll>
 __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
   __shared__ int32_t off_sh[1025];
   const int N = p.N;
   for (int e = threadIdx.x; e <= N; e += 1024) off_sh[e] = p.offsets[e];
   __syncthreads();
-  if (!kAll && blockIdx.x > 0) {
-    const int q = (blockIdx.x - 1) * 1024 + threadIdx.x;
+  if (!kAll && blockIdx.x > 1) {
+    const int q = (blockIdx.x - 2) * 1024 + threadIdx.x;
     if (q < p.P) plan_position(p, off_sh, q);
     return;
   }
+  const bool lists = kAll || blockIdx.x == 0, cuts = p.dw_pieces && (kAll || blockIdx.x == 1);
+  if (!lists && !cuts) return;
   __shared__ int32_t wtot[16];
-  if (threadIdx.x < 64) p.zero_row[threadIdx.x] = 0u;  // 256 bytes of zeros for padded K rows
+  if (lists && threadIdx.x < 64) p.zero_row[threadIdx.x] = 0u;  // 256 bytes of zeros for padded K rows
   __shared__ __align__(16) int32_t sm_m[1024];
   __shared__ int32_t sm_ntq_by_rank[1024];
   const int b = threadIdx.x;
   const int off = (b < N) ? off_sh[b] : 0;
   const int m = (b < N) ? off_sh[b + 1] - off : 0;
-  if (p.R > 0 && b < N && m == 0)   // an empty bucket has no row to write its table column
+  if (lists && p.R > 0 && b < N && m == 0)   // an empty bucket has no row to write its table column
     for (int r = 0; r <= p.nr; ++r) p.starts[(size_t)r * N + b] = off;
 
   auto inclusive_scan = [&](int v) {
@@ -156,7 +159,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
       atomicAdd(&own[group_of(rank)], ntq);
       if (mine_short) atomicAdd(&shorts[group_of(rank)][mine_short - 1], 1);
     }
-    p.border[rank] = b;
+    if (lists) p.border[rank] = b;
     sm_ntq_by_rank[rank] = ntq;
     sm_short_by_rank[rank] = (uint8_t)mine_short;
   }
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
   // ceil(m / p.dw_rows) pieces of equal size (an empty bucket one empty piece: its gradient block
   // is written as zeros), listed largest bucket first.  A bucket's first piece goes straight
   // into its gradient block, the others into staging slots that are added afterwards in order.
-  if (p.dw_pieces) {
+  if (cuts) {
     __shared__ int32_t sm_np_rank[1024];
     __shared__ int32_t sm_wstart[1024];
     const int np = (b < N) ? (m > p.dw_rows ? (m + p.dw_rows - 1) / p.dw_rows : 1) : 0;
@@ -197,6 +200,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     }
     for (int e = total_pieces + b; e < p.dw_cap; e += 1024) p.dw_pieces[e] = DwPiece{0, 0, -1, 0};
   }
+  if (!lists) return;
 
   if (p.wide) {
     const int inc = inclusive_scan(ntq);
@@ -1375,7 +1379,7 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
   {
     ScopedKernelTimer tm(kSlotPlan, st);
     if (all) plan_kernel<true><<<1, 1024, 0, st>>>(a);
-    else plan_kernel<false><<<1 + (P + 1023) / 1024, 1024, 0, st>>>(a);
+    else plan_kernel<false><<<2 + (P + 1023) / 1024, 1024, 0, st>>>(a);
   }
   SPT_LAUNCH_CHECK();
   if (sc.rstart && !all) {
