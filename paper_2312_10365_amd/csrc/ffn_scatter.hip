@@ -21,7 +21,8 @@
 //   one slab (OWN = false)  blocks in order.  Each wavefront says in LDS up to which token its record is done; a
 //                           tile is added once the three records before it are past its last token.  Tokens
 //                           ascend in every run, so the four wavefronts follow one another through the slab a
-//                           tile or two apart.  A wait is for lower records only, so it ends.  (Looking at the
+//                           tile or two apart.  A wait is for lower records only and for no more than their end (tokens
+//                           are clamped to the range), so it ends, also with a table that is not sorted.  (Looking at the
 //                           one record before it alone, the second piece of a long run held up the next block:
 //                           blocks of 96 +- 7 rows in records of 96 761 us, now 635.)
 //   four slabs (OWN = true) every wavefront has its own, nobody waits, and the four are added at the end,
@@ -308,7 +309,9 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
       // Everything but the products, dealt to the gaps behind them (n: 0 .. G - 1): a vector instruction or two in the shadow of
       // every product cost nothing, bunched they cost 4 clk each.
       auto gap = [&](int n) {
-        if (n == 0) tk = tokv[ti % RH] - t0;
+        // (the table's tokens are the caller's: one outside the range, where a bucket's are not ascending, is the dummy's too.  What
+        // a wait needs is then at most R + 1 into a record, which its wavefront reaches whatever the table says.)
+        if (n == 0) tk = (int)min((unsigned)(tokv[ti % RH] - t0), (unsigned)R);
         if (n == (G > 4 ? 1 : 0)) {    // the lane's row of this tile: its token's slab row, or the dummy
           tk = (ti == 0 ? (unsigned)rel < (unsigned)len : rel < len - 16 * ti) ? tk : R;
           xcur = tk * SC_STRIDE;

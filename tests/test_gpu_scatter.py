@@ -86,3 +86,31 @@ def test_runs_of_many_records(T, d, N, Bs, k):
 @pytest.mark.parametrize("T,d,N,Bs,k", [(900, 320, 20, 128, 7), (4097, 2048, 24, 64, 9), (2500, 4096, 16, 96, 6)])
 def test_uneven_blocks(T, d, N, Bs, k):
     run(T, d, N, Bs, k, "few")
+
+
+# Sorted by block as offsets say, but not stable (tokens descend, or are shuffled, inside a bucket): not what the header asks for
+# and not refused.  The sums are then not defined, but the call ends, leaves the next one alone and writes numbers: the records'
+# order in the slab waits for tokens read from the caller's table, which are clamped to the range.
+@pytest.mark.parametrize("T,d,N,Bs,k", [(9001, 1024, 12, 128, 3), (12001, 256, 24, 64, 6), (3001, 4096, 32, 32, 8),
+                                        (8192, 2048, 16, 96, 4), (2070, 1280, 76, 128, 29)])
+@pytest.mark.parametrize("kind", ["descending", "shuffled"])
+def test_tokens_out_of_order_end(T, d, N, Bs, k, kind):
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    normal = lambda *s, std=1.0: (torch.randn(*s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    shape = spt.make_shape(T, d, N, Bs, k, spt.ACT_RELU)
+    X, W1, W2 = normal(T, d), normal(N, Bs, d, std=0.05), normal(N, Bs, d, std=0.05)
+    offsets, perm, inv = spt.bucket_tokens(shape, torch.from_numpy(routing(T, N, k, "even", T + N)).cuda())
+    right, _ = spt.routed_ffn_fwd(shape, X, W1, W2, offsets, perm, inv)
+    rng = np.random.default_rng(T)
+    p, off = perm.cpu().numpy().copy(), offsets.cpu().numpy()
+    for b in range(N):
+        part = p[off[b]:off[b + 1]]
+        part[:] = part[::-1].copy() if kind == "descending" else rng.permutation(part)
+    back = np.empty_like(p)
+    back[p] = np.arange(T * k, dtype=np.int32)
+    print(f"T {T} d {d} N {N} Bs {Bs} k {k} {kind}", flush=True)
+    Y, _ = spt.routed_ffn_fwd(shape, X, W1, W2, offsets, torch.from_numpy(p).cuda(), torch.from_numpy(back).cuda())
+    torch.cuda.synchronize()
+    assert torch.isfinite(Y.float()).all()
+    again, _ = spt.routed_ffn_fwd(shape, X, W1, W2, offsets, perm, inv)
+    assert torch.equal(again, right)
