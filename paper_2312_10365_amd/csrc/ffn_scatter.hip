@@ -78,6 +78,22 @@ __global__ __launch_bounds__(64) void scatter_runs_kernel(const int32_t* __restr
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
+// Work item of workgroup `wg`: a part of the range's records, a token range and a slab; slab < 0: none.  An XCD (workgroup id mod
+// 8) takes an eighth of all items in order, parts included: part after part, in it groups of `inner` slabs, range after
+// range of a group, so that what it runs together is a few ranges x inner slabs, which share weight slices and runs of Hin
+// rows in its L2.  (With an eighth of the ranges and slabs and all parts of each, 85 of them in three parts were 33 workgroups
+// for the 32 CUs of seven XCDs, and a second round: 2100 tokens, d 320, 60 blocks of 128, 24 each 49 us a launch, now 30.)
+struct ScatterItem { int part, r, slab; };
+__host__ __device__ __forceinline__ ScatterItem scatter_item(int wg, int nslab, int nr, int parts, int inner) {
+  const int each = nslab * nr, per = (each * parts + 7) >> 3, item = (wg & 7) * per + (wg >> 3);
+  if ((wg >> 3) >= per || item >= each * parts) return ScatterItem{0, 0, -1};
+  const int part = parts > 1 ? item / each : 0, in_part = item - part * each;
+  const int grp = in_part / (inner * nr), rem = in_part % (inner * nr);
+  const int size = nslab - grp * inner < inner ? nslab - grp * inner : inner;
+  return ScatterItem{part, rem / size, grp * inner + rem % size};
+}
+inline int scatter_grid(const ScatterPlan& p) { return 8 * ((p.nslab * p.nr * p.splits + 7) / 8); }
+
 template <class F, int... I>
 __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
@@ -90,7 +106,7 @@ template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
 __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
     const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
     const int32_t* __restrict__ nruns, const int32_t* __restrict__ tok, int N, int d, int T, int R,
-    int nr, int nslab, int inner, int cap, uint16_t* __restrict__ out, const uint16_t* __restrict__ Z,
+    int nr, int nslab, int parts, int inner, int cap, uint16_t* __restrict__ out, const uint16_t* __restrict__ Z,
     float* __restrict__ split) {
   constexpr int Bs = KS * 16;
   constexpr int KT = KS / 2;                   // K-steps of 32 hidden units
@@ -101,14 +117,9 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
 
-  // Work item.  An XCD (workgroup id mod 8) takes an eighth of the items in order: groups of `inner` slabs, range after
-  // range of a group, so that what it runs together is a few ranges x inner slabs, which share weight slices and runs of
-  // Hin rows in its L2.
-  const int per = (nslab * nr + 7) >> 3, item = (blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per || item >= nslab * nr) return;
-  const int grp = item / (inner * nr), rem = item % (inner * nr);
-  const int size = nslab - grp * inner < inner ? nslab - grp * inner : inner;
-  const int slab = grp * inner + rem % size, r = rem / size;
+  const ScatterItem item = scatter_item(blockIdx.x, nslab, nr, parts, inner);
+  if (item.slab < 0) return;
+  const int slab = item.slab, r = item.r;
   const int t0 = r * R, c0 = slab * SC_C;
   const int rows = (T - t0 < R) ? T - t0 : R;
 
@@ -120,10 +131,10 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
   const lds_int_ptr prog = (lds_int_ptr)(uintptr_t)(slabs + slab_bytes);
 
   typedef const __attribute__((address_space(4))) RunRec* const_run_ptr;
-  // (few tokens: blockIdx.y takes its part of the range's records and leaves fp32 sums to be added)
+  // (few tokens: a workgroup takes a part of the range's records and leaves fp32 sums to be added)
   const int Mall = __builtin_amdgcn_readfirstlane(nruns[r]);
-  const int jfirst = (int)((int64_t)Mall * blockIdx.y / gridDim.y);
-  const int M = (int)((int64_t)Mall * (blockIdx.y + 1) / gridDim.y) - jfirst;
+  const int jfirst = (int)((int64_t)Mall * item.part / parts);
+  const int M = (int)((int64_t)Mall * (item.part + 1) / parts) - jfirst;
   const const_run_ptr rl = (const_run_ptr)(uintptr_t)(runs + (size_t)r * cap + jfirst);
   struct Run { int b, lo, hi, piece; };
   auto run_at = [&](int j) {  // wave-uniform scalar load; past the end: the last run again
@@ -135,7 +146,7 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
   // these tokens: zeros)
   if (M == 0 && split) {
     for (int it = tid; it < rows * (SC_C / 4); it += THREADS)
-      *reinterpret_cast<uint4*>(split + ((size_t)blockIdx.y * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
+      *reinterpret_cast<uint4*>(split + ((size_t)item.part * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
           make_uint4(0u, 0u, 0u, 0u);
     return;
   }
@@ -372,7 +383,7 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
   // Write the slab out, one rounding to bf16: eight columns of a row at a time (fp32 sums of a part: four).
   if (split) {
     for (int it = tid; it < rows * (SC_C / 4); it += THREADS)
-      *reinterpret_cast<f32x4*>(split + ((size_t)blockIdx.y * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
+      *reinterpret_cast<f32x4*>(split + ((size_t)item.part * T + t0 + it / (SC_C / 4)) * d + c0 + (it % (SC_C / 4)) * 4) =
           sum_at((it / (SC_C / 4)) * SC_STRIDE + (it % (SC_C / 4)) * 16);
     return;
   }
@@ -523,12 +534,11 @@ static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, c
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  const int grid = 8 * ((p.nslab * p.nr + 7) / 8);
   const RunRec* runs = reinterpret_cast<const RunRec*>(table);
   const int32_t* nruns = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + p.runs_bytes);
   const bool parts = p.splits > 1;
-  ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN><<<dim3(grid, p.splits), SC_THREADS, p.smem, st>>>(
-      Hin, W, runs, nruns, tok, s.N, s.d, s.T, p.R, p.nr, p.nslab, p.inner, p.cap, out, Z, parts ? split : nullptr);
+  ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN><<<scatter_grid(p), SC_THREADS, p.smem, st>>>(
+      Hin, W, runs, nruns, tok, s.N, s.d, s.T, p.R, p.nr, p.nslab, p.splits, p.inner, p.cap, out, Z, parts ? split : nullptr);
   if (!parts) return hipGetLastError();
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -560,3 +570,18 @@ hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint
 }
 
 }  // namespace spt
+
+// For tests, not declared in the header: the plan of a shape (tiles of 16 rows per record, tokens per range, ranges, parts, column
+// slabs, grid) and what the grid's first `count` workgroups do (part, range, slab each).  0 if the shape has no such launch.
+extern "C" int spt_internal_scatter_layout(const spt_shape_t* s, int32_t* plan, int32_t* items, int count) {
+  using namespace spt;
+  if (!s || !plan || s->T < 1 || s->N < 1 || s->k < 1 || s->k > s->N || s->d < SC_C || s->d % SC_C || s->Bs % 32 || s->Bs < 32 || s->Bs > 128) return 0;
+  const ScatterPlan p = plan_scatter(*s);
+  const int out[6] = {p.nt, p.R, p.nr, p.splits, p.nslab, scatter_grid(p)};
+  for (int e = 0; e < 6; ++e) plan[e] = out[e];
+  for (int wg = 0; wg < count && wg < out[5]; ++wg) {
+    const ScatterItem x = scatter_item(wg, p.nslab, p.nr, p.splits, p.inner);
+    items[3 * wg] = x.part; items[3 * wg + 1] = x.r; items[3 * wg + 2] = x.slab;
+  }
+  return 1;
+}

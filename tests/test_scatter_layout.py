@@ -1,0 +1,49 @@
+"""Host side of the K = Bs contraction: which workgroup takes which part of the records, token range and column slab.  No GPU."""
+import ctypes
+import random
+
+import numpy as np
+import pytest
+
+from paper_2312_10365_amd import spt
+
+
+def layout(T, d, N, Bs, k):
+    """(tiles per record, tokens per range, ranges, parts, slabs, grid), and the (part, range, slab) of each workgroup."""
+    shape = spt.make_shape(T, d, N, Bs, k)
+    plan = (ctypes.c_int32 * 6)()
+    f = spt.lib().spt_internal_scatter_layout
+    assert f(ctypes.byref(shape), plan, None, 0) == 1
+    items = np.zeros((plan[5], 3), np.int32)
+    assert f(ctypes.byref(shape), plan, items.ctypes.data_as(ctypes.c_void_p), int(plan[5])) == 1
+    return tuple(plan), items
+
+
+def shapes(seed, count):
+    rng = random.Random(seed)
+    log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    for _ in range(count):
+        N = log(1, 1024)
+        yield log(1, 40000), 64 * log(1, 64), N, 32 * rng.randint(1, 4), max(1, round(N * rng.uniform(0.02, 1.0)))
+
+
+def check(shape):
+    (_, R, nr, parts, nslab, grid), items = layout(*shape)
+    assert (nr - 1) * R < shape[0] <= nr * R and nslab == shape[1] // 64
+    real = items[:, 2] >= 0
+    want = {(p, r, c) for p in range(parts) for r in range(nr) for c in range(nslab)}
+    got = [tuple(x) for x in items[real].tolist()]
+    assert len(got) == len(want) and set(got) == want            # each item once
+    per_xcd = [int(real[x::8].sum()) for x in range(8)]          # workgroups go to the eight XCDs in turn
+    assert max(per_xcd) == -(-len(want) // 8), (shape, per_xcd)
+
+
+# 85 items in three parts, 84 in three, 63 in two: 33 workgroups for an XCD's 32 CUs where each XCD has all parts of its own items
+@pytest.mark.parametrize("shape", [(2100, 320, 60, 128, 24), (7000, 256, 90, 128, 30), (1, 64, 1, 32, 1), (24, 4096, 128, 128, 32)])
+def test_every_item_once_and_no_xcd_more_than_an_eighth(shape):
+    check(shape)
+
+
+def test_drawn_shapes():
+    for shape in shapes(1, 600):
+        check(shape)
