@@ -420,59 +420,68 @@ __global__ __launch_bounds__(256) void scatter_sum_kernel(const float* __restric
 
 // ------------------------------------------------------------------------------------------
 // host side
-// The kernel's forms.  rec: us per record of a full workgroup by K-steps (Bs / 32).  These and the constants of the
-// cost below were fitted to 1900 timings (150 shapes of 16 to 128 blocks, up to 12112 tokens and 4096 columns, every form with up
-// to 12 range counts and 6 splits of the block list); over them the form chosen is within 1 % of the quickest one on average.
-struct ScatterForm { int nt, wg; bool own; double rec[4]; };
+// The kernel's forms: tiles per record, a slab per wavefront, workgroups of a CU that the registers allow and us per four records of
+// a workgroup that has its CU to itself, both by K-steps (Bs / 32).  A record takes its tiles whatever it holds, so few rows per block and
+// range want few tiles; a record's start (the slice of weights) is the larger part of a short one.
+struct ScatterForm { int nt; bool own; int wg[4]; double rec[4]; };
 static const ScatterForm kScatterForms[] = {
-    {2, 1, true, {.15, .22, .285, .36}},
-    {6, 2, false, {.55, .66, .70, .88}},
-    {8, 1, false, {.51, .62, .72, .81}},
-    {10, 1, false, {.62, .72, .74, .86}},
+    {2, true, {4, 3, 2, 2}, {.68, .80, 1.16, 1.52}},
+    {4, false, {4, 2, 2, 2}, {1.40, 1.60, 1.96, 2.08}},
+    {6, false, {3, 2, 2, 2}, {1.80, 1.88, 2.20, 2.52}},
+    {8, false, {3, 2, 1, 1}, {2.24, 2.36, 2.76, 3.16}},
+    {10, false, {3, 2, 1, 1}, {2.72, 2.80, 3.28, 3.76}},
 };
+
+// us that a launch takes with `nr` ranges of R tokens and the block list in `sp` parts, the same for even and for skewed routing.
+// Fitted to the time of 858 shapes (1 to 65536 tokens, 1 to 1024 blocks, 64 to 4096 columns, all block sizes) under even and under
+// skewed routing, 40 thousand plans timed; the plan of least cost takes 0.5 % more than the quickest timed one on average, 3.8 % at the
+// 95th percentile, 13 % at most.
+static double scatter_cost(const spt_shape_t& s, const ScatterForm& f, int nslab, int R, int nr, int sp) {
+  const int ks = s.Bs / 32 - 1, run = 16 * f.nt;
+  // Records of a block in a range: its rows are about Binomial(R, k / N); 1 + P(rows > run) + P(rows > 2 run) + .. if it has any.
+  const double share = (double)s.k / s.N, mean = R * share, sd = sqrt(mean * (1.0 - share) + 1e-9);
+  const double some = mean < 30.0 ? 1.0 - exp(-mean) : 1.0;
+  double records = some;
+  for (int c = 1; c * run < mean + 4.0 * sd + 2.0; ++c) records += 0.46 * erfc((c * run - 1.5 - mean) / (sd * 1.41421356));
+  const double body = R * (f.own ? 0.0187 : 0.0098) + (s.N * records / (4.0 * sp) + 0.6) * f.rec[ks];
+  // Workgroups per CU, as many at once as registers and LDS allow; each one more makes the others slower by `beside`.
+  static const double kBeside[4] = {.27, .32, .37, .42};
+  const int lds = 160 * 1024 / (f.own ? SC_WAVES * (R + 1) * SC_STRIDE : (R + 1) * SC_STRIDE + SC_WAVES * 256);
+  const int at_once = lds < f.wg[ks] ? lds : f.wg[ks];
+  const int64_t each = ((int64_t)nr * nslab * sp + 255) / 256, full = each / at_once, rest = each % at_once;
+  const double work = body * (full * (1.0 + (at_once - 1) * kBeside[ks]) + (rest ? 1.0 + (rest - 1) * kBeside[ks] : 0.0));
+  // Bytes: into the CUs rows once per column slab and weights once per range, at 17.8 TB/s; from memory both once, at 6.6 (fitted).
+  const double rows = (double)s.T * s.k * s.Bs * 2, weights = (double)s.N * s.Bs * s.d * 2, total = s.T * share;
+  const double in = (rows * nslab + weights * nr * some) / 17.8e6;
+  const double once = (rows + weights * (total < 30.0 ? 1.0 - exp(-total) : 1.0) + (double)s.T * s.d * 2) / 6.6e6;
+  const double bytes = in > once ? in : once;
+  const double more = work > bytes ? work : bytes, less = work > bytes ? bytes : work;
+  double us = more + 0.26 * less * less * less / (more * more);
+  if (sp > 1) us += 2.0 + 0.2 * sp + (double)sp * s.T * s.d * 8.0 / 9.5e6;     // the parts' sums, added by another launch
+  return us;
+}
 
 static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   ScatterPlan p = {};
   p.nslab = s.d / SC_C;
-  // A launch takes its rounds of workgroups, each its records one after the other (four at a time) and a prologue and an
-  // epilogue, or as long as its bytes (rows once per column slab, weights once per range) come into the CUs at 13.4 TB/s.
-  // Rows of a range in a block are about Binomial(R, k / N), in records of at most 16 nt rows: 1 + P(rows > 16 nt) + ... per
-  // block (a run's next piece is stuck behind the tokens the runs before it are at: a quarter more).  Per form the range
-  // counts that fill a number of rounds, of which the quickest by that count is taken.  Both sides, us a pass: 7B-like, 16
-  // ranges in 10 tiles 2311, 20 in 8 tiles 2384, 28 in 6 tiles and two workgroups per CU 2410; BERT-large-like, 64 ranges in 6
-  // tiles 501, 32 in 10 tiles 533; a layer of 512 tokens, slabs of their own for 32 tokens 52.7, one slab for 64 61.8.
-  const double share = (double)s.k / s.N;
-  const double row_bytes = (double)s.T * s.k * s.Bs * 2 * p.nslab, w_bytes = (double)s.N * s.Bs * s.d * 2;
+  // Per form and number of parts (16 blocks or more in each) the range counts that give every CU one workgroup, two, ...; more than
+  // five are too short for parts.  Both sides, us a launch: 7B-like, 16 ranges in 10 tiles 516, 20 in 8 tiles 570; BERT-large-like, 64 ranges in
+  // 6 tiles 97, 32 in 10 tiles 120; 10956 tokens, d 512, 92 blocks of 96, 19 each: 64 ranges in 6 tiles 88, 32 in 8 tiles 77; 32768,
+  // 1024, 128 of 32, 16: 64 in 8 tiles 311, 112 in 4 tiles 241.
   double best = -1.0;
   for (const ScatterForm& f : kScatterForms) {
-    const int lds = 160 * 1024 / f.wg;
-    const int rmax = f.own ? lds / SC_WAVES / SC_STRIDE - 1 : (lds - SC_WAVES * 256) / SC_STRIDE - 1;   // (one slab row is the dummy)
-    const int run = 16 * f.nt, nr_min = (s.T + rmax - 1) / rmax, nr_max = (s.T + 31) / 32 > nr_min ? (s.T + 31) / 32 : nr_min;
-    const int chip = 256 * f.wg;
-    // With few tokens the block list is cut into parts too (16 records or more each), whose fp32 sums are
-    // added by another launch: fewer weight slices per workgroup, for 8 bytes per part, token and column.
+    const int rmax = f.own ? 160 * 1024 / SC_WAVES / SC_STRIDE - 1 : (160 * 1024 - SC_WAVES * 256) / SC_STRIDE - 1;   // (one slab row is the dummy)
+    const int nr_min = (s.T + rmax - 1) / rmax, nr_max = (s.T + 31) / 32 > nr_min ? (s.T + 31) / 32 : nr_min;
     for (int sp = 1; sp == 1 || (sp <= 8 && sp * 16 <= s.N); sp += sp < 4 ? 1 : 2) {
       int last = 0;
-      for (int round = 0; round <= 24; ++round) {
-        int64_t nr64 = round == 0 ? nr_min : (int64_t)round * chip / ((int64_t)p.nslab * sp);
-        if (nr64 < nr_min) continue;
-        const int nr = nr64 > nr_max ? nr_max : (int)nr64;
-        if (nr == last) continue;
-        last = nr;
-        const int R = (s.T + nr - 1) / nr, real_nr = (s.T + R - 1) / R;
-        const double mean = R * share, sd = sqrt(mean * (1.0 - share) + 1e-9);
-        double records = 1.0 - exp(-mean);                       // (blocks none of the range's tokens activates have none)
-        for (int c = 1; c * run < mean + 6.0 * sd + 2.0; ++c)
-          records += (f.own ? 0.5 : 0.61) * erfc((c * run - 1.0 - mean) / (sd * 1.41421356));
-        const int64_t rounds = ((int64_t)real_nr * p.nslab * sp + chip - 1) / chip;
-        const int wg = (int64_t)real_nr * p.nslab * sp <= 256 ? 1 : f.wg;          // (alone on its CU after all)
-        const double rec = f.rec[s.Bs / 32 - 1] * (wg < f.wg ? 0.71 : 1.0);
-        double cost = (double)rounds * (s.N * records * rec / sp + ((wg > 1 ? 3.3 : 5.0) + R * (f.own ? 0.034 : 0.018)) * wg);
-        const double bytes = (row_bytes + w_bytes * real_nr * (records < 1.0 ? records : 1.0)) / 13.4e6;
-        if (cost < bytes) cost = bytes;
-        if (sp > 1) cost += 1.5 + (double)sp * s.T * s.d * 8.0 / 6.3e6;
-        if (best < 0.0 || cost < best * 0.999) {
-          best = cost; p.R = R; p.nr = real_nr; p.splits = sp; p.nt = f.nt;
+      for (int each = 0; each <= (sp == 1 ? 24 : 5) && last < nr_max; ++each) {
+        const int64_t nr64 = each == 0 ? nr_min : (int64_t)each * 256 / ((int64_t)p.nslab * sp);
+        if (nr64 <= last || nr64 < nr_min) continue;
+        last = nr64 > nr_max ? nr_max : (int)nr64;
+        const int R = (s.T + last - 1) / last, nr = (s.T + R - 1) / R;
+        const double cost = scatter_cost(s, f, p.nslab, R, nr, sp);
+        if (best < 0.0 || cost < best) {
+          best = cost; p.R = R; p.nr = nr; p.splits = sp; p.nt = f.nt;
           p.smem = f.own ? SC_WAVES * (R + 1) * SC_STRIDE : (R + 1) * SC_STRIDE + SC_WAVES * 256;
         }
       }
@@ -483,7 +492,7 @@ static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   // runs of `mean` rows and b slices of 64 columns per block, least at b^2 = a b mean / 64; all ranges where there are few.
   // (47 slabs, 32 ranges of one slab side by side instead of four by eight: 346 us, 312.)
   const int together = 32 * (p.nt == 6 ? 2 : 1);
-  p.inner = (int)(sqrt(together * (p.R * share) / 64.0) + 0.5);
+  p.inner = (int)(sqrt(together * ((double)p.R * s.k / s.N) / 64.0) + 0.5);
   if (p.inner < (together + p.nr - 1) / p.nr) p.inner = (together + p.nr - 1) / p.nr;
   if (p.inner < 1) p.inner = 1;
   if (p.inner > p.nslab) p.inner = p.nslab;
@@ -550,11 +559,12 @@ static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, c
 hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W,
                           const int32_t* table, const int32_t* tok, uint16_t* out, const uint16_t* Z,
                           float* split, hipStream_t st) {
-  // (six tiles and two workgroups per CU leave a lane 256 registers: rows requested fewer tiles ahead, and with eight K-steps
+  // (four and six tiles, two workgroups per CU, leave a lane 256 registers: rows requested fewer tiles ahead, and with eight K-steps
   // of 16 the weight slice later)
 #define SPT_SC_ARGS s, p, Hin, W, table, tok, out, Z, split, st
 #define SPT_SC(KS)                                                                                                      \
   (p.nt == 2   ? launch_scatter_t<KS, 2, 2, false, 1, true>(SPT_SC_ARGS)                                                \
+   : p.nt == 4 ? launch_scatter_t<KS, 4, (KS > 6 ? 2 : 4), (KS > 6), 2, false>(SPT_SC_ARGS)                             \
    : p.nt == 6 ? launch_scatter_t<KS, 6, (KS > 4 ? 3 : 6), (KS > 6), 2, false>(SPT_SC_ARGS)                             \
    : p.nt == 8 ? launch_scatter_t<KS, 8, 8, false, 1, false>(SPT_SC_ARGS)                                               \
                : launch_scatter_t<KS, 10, 10, false, 1, false>(SPT_SC_ARGS))

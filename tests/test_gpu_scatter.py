@@ -1,4 +1,4 @@
-"""K = Bs contraction with the per-token write-back: every form of the kernel (records of 2, 6, 8 and 10 tiles of 16 rows, one
+"""K = Bs contraction with the per-token write-back: every form of the kernel (records of 2, 4, 6, 8 and 10 tiles of 16 rows, one
 slab or one per wavefront, the block list in parts), each block size, at the edges of tiles, records, ranges and slabs.
 
 With ReLU the kernel's operand is max(Hsave, 0) exactly, so the reference is a plain sum in 64 bits over the saved values, and
@@ -10,6 +10,7 @@ import pytest
 import torch
 
 from paper_2312_10365_amd import spt
+from scatter_shapes import LAYERS
 
 pytestmark = pytest.mark.gpu
 
@@ -18,6 +19,8 @@ def routing(T, N, k, kind, seed):
     rng = np.random.default_rng(seed)
     if kind == "few":                       # half of the blocks hold nearly everything, some hold nothing
         w = np.where(np.arange(N) % 2 == 0, 1.0, 1e-3) * (np.arange(N) != N - 1)
+    elif kind == "full":                    # two blocks hold every token, next to ordinary ones
+        w = np.where(np.arange(N) % (N // 2 + 1) == 1, 1e9, 1.0)
     else:
         w = np.ones(N)
     keys = rng.exponential(size=(T, N)) / np.maximum(w, 1e-12)
@@ -86,6 +89,12 @@ def test_runs_of_many_records(T, d, N, Bs, k):
 @pytest.mark.parametrize("T,d,N,Bs,k", [(900, 320, 20, 128, 7), (4097, 2048, 24, 64, 9), (2500, 4096, 16, 96, 6)])
 def test_uneven_blocks(T, d, N, Bs, k):
     run(T, d, N, Bs, k, "few")
+
+
+# Runs that hold every token of their range, in records of each size (what a layer is for: scatter_shapes.py).
+@pytest.mark.parametrize("tiles,parts,pieces,shape", LAYERS)
+def test_full_runs(tiles, parts, pieces, shape):
+    run(*shape, "full")
 
 
 # Sorted by block as offsets say, but not stable (tokens descend, or are shuffled, inside a bucket): not what the header asks for

@@ -1,11 +1,14 @@
 """Host side of the K = Bs contraction: which workgroup takes which part of the records, token range and column slab.  No GPU."""
 import ctypes
+import json
+import os
 import random
 
 import numpy as np
 import pytest
 
 from paper_2312_10365_amd import spt
+from scatter_shapes import LAYERS
 
 
 def layout(T, d, N, Bs, k):
@@ -47,3 +50,26 @@ def test_every_item_once_and_no_xcd_more_than_an_eighth(shape):
 def test_drawn_shapes():
     for shape in shapes(1, 600):
         check(shape)
+
+
+# What the layers that the GPU tests run are there for.
+@pytest.mark.parametrize("tiles,parts,pieces,shape", LAYERS)
+def test_layers_of_the_gpu_tests(tiles, parts, pieces, shape):
+    (nt, R, nr, p, _, _), _ = layout(*shape)
+    assert (nt, p > 1, -(-R // (16 * nt))) == (tiles, parts, pieces) and nr >= 3
+    check(shape)
+
+
+# us of a launch on an MI355X under even and under skewed routing, [tiles, tokens per range, parts, even, skewed], for the quicker
+# ones of the plans tried (up to 25 % above the quickest).  The plan taken is one of them, by the geometric mean of the two routings at most
+# 1 % above the quickest on average and never 15 %.  (Without records of 4 tiles, and a CU taken to hold one workgroup: ten plans not among
+# them, the others 2.8 % above on average, 24 % at most.)
+def test_plans_against_measured_ones():
+    with open(os.path.join(os.path.dirname(__file__), "golden", "scatter_plan_us.json")) as f:
+        measured = json.load(f)
+    worse = []
+    for shape, plans in measured:
+        us = {tuple(p[:3]): (p[3] * p[4]) ** 0.5 for p in plans}
+        nt, R, _, parts, _, _ = layout(*shape)[0]
+        worse.append(us.get((nt, R, parts), 1.3 * min(us.values())) / min(us.values()))
+    assert np.mean(worse) < 1.01 and max(worse) < 1.15, (np.mean(worse), measured[int(np.argmax(worse))][0], max(worse))
