@@ -436,51 +436,74 @@ static const ScatterForm kScatterForms[] = {
 // Fitted to the time of 858 shapes (1 to 65536 tokens, 1 to 1024 blocks, 64 to 4096 columns, all block sizes) under even and under
 // skewed routing, 40 thousand plans timed; the plan of least cost takes 0.5 % more than the quickest timed one on average, 3.8 % at the
 // 95th percentile, 13 % at most.
-static double scatter_cost(const spt_shape_t& s, const ScatterForm& f, int nslab, int R, int nr, int sp) {
-  const int ks = s.Bs / 32 - 1, run = 16 * f.nt;
-  // Records of a block in a range: its rows are about Binomial(R, k / N); 1 + P(rows > run) + P(rows > 2 run) + .. if it has any.
-  const double share = (double)s.k / s.N, mean = R * share, sd = sqrt(mean * (1.0 - share) + 1e-9);
-  const double some = mean < 30.0 ? 1.0 - exp(-mean) : 1.0;
-  double records = some;
-  for (int c = 1; c * run < mean + 4.0 * sd + 2.0; ++c) records += 0.46 * erfc((c * run - 1.5 - mean) / (sd * 1.41421356));
-  const double body = R * (f.own ? 0.0187 : 0.0098) + (s.N * records / (4.0 * sp) + 0.6) * f.rec[ks];
+// (What does not depend on the plan is in ScatterWork.  `best`: the least so far; a plan whose workgroups or bytes alone take longer, by what
+// they take at least, is not looked at further, and the records' error functions, two thirds of the search, are left out.)
+struct ScatterWork {
+  double share, rows, weights, once, sums;
+  int ks, nslab;
+  explicit ScatterWork(const spt_shape_t& s)
+      : share((double)s.k / s.N), rows((double)s.T * s.k * s.Bs * 2), weights((double)s.N * s.Bs * s.d * 2),
+        sums((double)s.T * s.d * 8.0 / 9.5e6), ks(s.Bs / 32 - 1), nslab(s.d / SC_C) {
+    // from memory: rows and weights once, at 6.6 TB/s (fitted)
+    const double total = s.T * share;
+    once = (rows + weights * (total < 30.0 ? 1.0 - exp(-total) : 1.0) + (double)s.T * s.d * 2) / 6.6e6;
+  }
+};
+static double scatter_cost(const spt_shape_t& s, const ScatterWork& w, const ScatterForm& f, int R, int nr, int sp, double best) {
+  const int run = 16 * f.nt;
   // Workgroups per CU, as many at once as registers and LDS allow; each one more makes the others slower by `beside`.
   static const double kBeside[4] = {.27, .32, .37, .42};
+  const double beside = kBeside[w.ks];
   const int lds = 160 * 1024 / (f.own ? SC_WAVES * (R + 1) * SC_STRIDE : (R + 1) * SC_STRIDE + SC_WAVES * 256);
-  const int at_once = lds < f.wg[ks] ? lds : f.wg[ks];
-  const int64_t each = ((int64_t)nr * nslab * sp + 255) / 256, full = each / at_once, rest = each % at_once;
-  const double work = body * (full * (1.0 + (at_once - 1) * kBeside[ks]) + (rest ? 1.0 + (rest - 1) * kBeside[ks] : 0.0));
-  // Bytes: into the CUs rows once per column slab and weights once per range, at 17.8 TB/s; from memory both once, at 6.6 (fitted).
-  const double rows = (double)s.T * s.k * s.Bs * 2, weights = (double)s.N * s.Bs * s.d * 2, total = s.T * share;
-  const double in = (rows * nslab + weights * nr * some) / 17.8e6;
-  const double once = (rows + weights * (total < 30.0 ? 1.0 - exp(-total) : 1.0) + (double)s.T * s.d * 2) / 6.6e6;
-  const double bytes = in > once ? in : once;
+  const int at_once = lds < f.wg[w.ks] ? lds : f.wg[w.ks];
+  const int each = (int)(((int64_t)nr * w.nslab * sp + 255) / 256), full = each / at_once, rest = each % at_once;
+  const double times = full * (1.0 + (at_once - 1) * beside) + (rest ? 1.0 + (rest - 1) * beside : 0.0);
+  const double rec = f.rec[w.ks] / (4.0 * sp) * s.N, fixed = R * (f.own ? 0.0187 : 0.0098) + 0.6 * f.rec[w.ks];
+  const double added = sp > 1 ? 2.0 + 0.2 * sp + sp * w.sums : 0.0;             // the parts' sums, added by another launch
+  const double mean = R * w.share, some_least = mean / (1.0 + mean), full_least = 0.9 * mean / run;
+  const double rec_least = rec * (some_least > full_least ? some_least : full_least);
+  // (more ranges are more records and more bytes: -1)
+  const double shared = (1.0 + (f.wg[w.ks] - 1) * beside) / f.wg[w.ks];
+  if ((double)nr * w.nslab * (sp / 256.0) * shared * rec * some_least + added >= best) return -1.0;
+  if (times * (fixed + rec_least) + added >= best || w.once + added >= best) return best;
+  // Bytes into the CUs: rows once per column slab and weights once per range, at 17.8 TB/s (fitted).
+  const double some = mean < 30.0 ? 1.0 - exp(-mean) : 1.0;
+  const double in = (w.rows * w.nslab + w.weights * nr * some) / 17.8e6;
+  if (in + added >= best) return -1.0;
+  // Records of a block in a range: its rows are about Binomial(R, k / N); 1 + P(rows > run) + P(rows > 2 run) + .. if it has any.
+  const double sd = sqrt(mean * (1.0 - w.share) + 1e-9), by = 1.0 / (sd * 1.41421356);
+  double records = some;
+  for (int c = 1; c * run < mean + 4.0 * sd + 2.0; ++c) records += 0.46 * erfc((c * run - 1.5 - mean) * by);
+  const double work = times * (fixed + rec * records), bytes = in > w.once ? in : w.once;
   const double more = work > bytes ? work : bytes, less = work > bytes ? bytes : work;
-  double us = more + 0.26 * less * less * less / (more * more);
-  if (sp > 1) us += 2.0 + 0.2 * sp + (double)sp * s.T * s.d * 8.0 / 9.5e6;     // the parts' sums, added by another launch
-  return us;
+  return more + 0.26 * less * less * less / (more * more) + added;
 }
 
 static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   ScatterPlan p = {};
-  p.nslab = s.d / SC_C;
+  const ScatterWork w(s);
+  p.nslab = w.nslab;
   // Per form and number of parts (16 blocks or more in each) the range counts that give every CU one workgroup, two, ...; more than
-  // five are too short for parts.  Both sides, us a launch: 7B-like, 16 ranges in 10 tiles 516, 20 in 8 tiles 570; BERT-large-like, 64 ranges in
-  // 6 tiles 97, 32 in 10 tiles 120; 10956 tokens, d 512, 92 blocks of 96, 19 each: 64 ranges in 6 tiles 88, 32 in 8 tiles 77; 32768,
-  // 1024, 128 of 32, 16: 64 in 8 tiles 311, 112 in 4 tiles 241.
-  double best = -1.0;
+  // five are too short for parts.  Both sides, us a launch: 7B-like, 16 ranges in 10 tiles 526, 28 in 6 tiles 534, 20 in 8 tiles 556; BERT-large-like,
+  // 64 ranges in 6 tiles 97, 32 in 10 tiles 107; 10956 tokens, d 512, 92 blocks of 96, 19 each: 32 ranges in 6 tiles 68, 64 in 6 tiles 88; 32768,
+  // 1024, 128 of 32, 16: 112 ranges in 4 tiles 241, 64 in 6 tiles 260, in 8 tiles 311.
+  double best = 1e300;
+  int fits = 0;
   for (const ScatterForm& f : kScatterForms) {
     const int rmax = f.own ? 160 * 1024 / SC_WAVES / SC_STRIDE - 1 : (160 * 1024 - SC_WAVES * 256) / SC_STRIDE - 1;   // (one slab row is the dummy)
+    if (s.T <= fits) break;      // (no run is longer than the records of the form before)
+    fits = 16 * f.nt - 4;        // (a run may start in the last place of four)
     const int nr_min = (s.T + rmax - 1) / rmax, nr_max = (s.T + 31) / 32 > nr_min ? (s.T + 31) / 32 : nr_min;
     for (int sp = 1; sp == 1 || (sp <= 8 && sp * 16 <= s.N); sp += sp < 4 ? 1 : 2) {
       int last = 0;
       for (int each = 0; each <= (sp == 1 ? 24 : 5) && last < nr_max; ++each) {
-        const int64_t nr64 = each == 0 ? nr_min : (int64_t)each * 256 / ((int64_t)p.nslab * sp);
-        if (nr64 <= last || nr64 < nr_min) continue;
-        last = nr64 > nr_max ? nr_max : (int)nr64;
+        const int count = each == 0 ? nr_min : each * 256 / (p.nslab * sp);
+        if (count <= last || count < nr_min) continue;
+        last = count > nr_max ? nr_max : count;
         const int R = (s.T + last - 1) / last, nr = (s.T + R - 1) / R;
-        const double cost = scatter_cost(s, f, p.nslab, R, nr, sp);
-        if (best < 0.0 || cost < best) {
+        const double cost = scatter_cost(s, w, f, R, nr, sp, best);
+        if (cost < 0.0) break;
+        if (cost < best) {
           best = cost; p.R = R; p.nr = nr; p.splits = sp; p.nt = f.nt;
           p.smem = f.own ? SC_WAVES * (R + 1) * SC_STRIDE : (R + 1) * SC_STRIDE + SC_WAVES * 256;
         }
@@ -490,7 +513,8 @@ static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   p.run_rows = 16 * p.nt;
   // Slabs side by side on an XCD: of a ranges x b slabs that run together (a b = 32 workgroups per place on a CU) it fetches a
   // runs of `mean` rows and b slices of 64 columns per block, least at b^2 = a b mean / 64; all ranges where there are few.
-  // (47 slabs, 32 ranges of one slab side by side instead of four by eight: 346 us, 312.)
+  // (47 slabs, 32 ranges of one slab side by side instead of four by eight: 346 us, 312.  Two places also for the other forms that have them:
+  // within 0.3 % over 270 layers.)
   const int together = 32 * (p.nt == 6 ? 2 : 1);
   p.inner = (int)(sqrt(together * ((double)p.R * s.k / s.N) / 64.0) + 0.5);
   if (p.inner < (together + p.nr - 1) / p.nr) p.inner = (together + p.nr - 1) / p.nr;
@@ -504,8 +528,8 @@ static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   return p;
 }
 
-// (The search over range counts takes 0.1 to 16 microseconds and every call of the path asks several times:
-// each thread keeps the plans of the last few shapes, which are functions of the shape alone.)
+// (The search takes 0.4 microseconds for 24 tokens, 2.5 for 3001 or 8192 of the 7B-like layer, and every call of the path asks several
+// times: each thread keeps the plans of the last few shapes, which are functions of the shape alone.)
 ScatterPlan plan_scatter(const spt_shape_t& s) {
   struct Kept { int32_t T, d, N, Bs, k; ScatterPlan plan; };
   static thread_local Kept kept[8] = {};

@@ -3,6 +3,7 @@ import ctypes
 import json
 import os
 import random
+import time
 
 import numpy as np
 import pytest
@@ -73,3 +74,25 @@ def test_plans_against_measured_ones():
         nt, R, _, parts, _, _ = layout(*shape)[0]
         worse.append(us.get((nt, R, parts), 1.3 * min(us.values())) / min(us.values()))
     assert np.mean(worse) < 1.01 and max(worse) < 1.15, (np.mean(worse), measured[int(np.argmax(worse))][0], max(worse))
+
+
+def test_search_is_short():
+    """A plan that is not among the last few: what a token count that changes from pass to pass adds to every pass, in calls of the same
+    function that find theirs (0.24 us).  24 tokens 1.8 such calls and 3001 tokens 11; with every plan looked at in full 5.9 and 24, and 7.9 and 48
+    with range counts beyond what the tokens allow tried as well."""
+    plan = (ctypes.c_int32 * 6)()
+    f = spt.lib().spt_internal_scatter_layout
+
+    def per_call(shapes):
+        refs, best = [ctypes.byref(s) for s in shapes], 1e9
+        for _ in range(60):
+            t = time.perf_counter()
+            for r in refs:
+                f(r, plan, None, 0)
+            best = min(best, (time.perf_counter() - t) / len(refs))
+        return best
+
+    for T, calls in ((24, 4.0), (3001, 18.0)):
+        shapes = [spt.make_shape(T + i, 4096, 128, 128, 32) for i in range(16)]     # (eight are kept)
+        found = per_call(shapes[:1] * 16)
+        assert per_call(shapes) - found < calls * found, (T, per_call(shapes) / found)
