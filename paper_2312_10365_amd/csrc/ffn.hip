@@ -1375,7 +1375,11 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
     a.runs = scatter_runs(sp, sc.rstart); a.nruns = scatter_counts(sp, sc.rstart); a.run_cap = sp.cap; a.run_rows = sp.run_rows;
   }
   a.dw_rows = sc.dw_rows; a.dw_cap = sc.dw_cap; a.dw_pieces = sc.dw_pieces; a.dw_xlist = sc.dw_xlist;
-  const bool all = P <= 8192;   // eight positions per thread: less than the two launches it saves
+  // One workgroup for everything where its chain of phases, whose length grows with the positions and the runs, is at most a launch longer: a
+  // pass that is waited for takes 5 to 7 us more with the second launch, one among others nothing.  us in a graph, one workgroup /
+  // several: tables with the weight gradients' pieces, 1024 pairs 7.7 / 6.8, 2048 8.9 / 6.9, 4096 11.3 / 6.9, 6144 13.7 / 7.0, 8192 16.9 / 7.1 (32
+  // blocks; 128 blocks 12.9 / 8.0 for 4096, 18.8 / 8.2 for 8192); a forward pass 23.7 / 23.7, 26.2 / 24.9, 32.3 / 28.6, 36.6 / 30.5, 41.4 / 31.7.
+  const bool all = P <= 4096;
   {
     ScopedKernelTimer tm(kSlotPlan, st);
     if (all) plan_kernel<true><<<1, 1024, 0, st>>>(a);

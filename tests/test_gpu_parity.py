@@ -530,8 +530,8 @@ def test_bucketing_by_one_workgroup(T, N, k):
     (24, 1024, 64, 128, 16), (33, 320, 128, 32, 40),
     # 64-row tiles at 127 buckets, 256-row ones from 128; one, two, three stages of 64 values in rings of three and four
     (700, 64, 127, 32, 16), (700, 64, 128, 32, 16), (700, 128, 128, 96, 16), (700, 192, 130, 64, 16), (1100, 320, 64, 128, 24),
-    # schedule by one workgroup up to 8192 pairs
-    (1024, 64, 40, 32, 8), (2731, 64, 40, 32, 3),
+    # schedule by one workgroup up to 4096 pairs
+    (1024, 64, 40, 32, 4), (4097, 64, 40, 32, 1), (1024, 64, 40, 32, 8), (2731, 64, 40, 32, 3),
     # wide blocks, items left over per XCD: as quarters, as halves, as whole tiles, after a full round
     (1300, 192, 2, 288, 2), (5000, 320, 2, 288, 2), (5000, 64, 2, 1056, 2), (5000, 64, 2, 1696, 2),
 ], ids=str)
