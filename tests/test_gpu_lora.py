@@ -11,6 +11,7 @@ from paper_2312_10365_amd import inputs as gen
 from paper_2312_10365_amd import spt
 
 from parity_util import TOL, check, rel_err
+from scatter_shapes import LORA_LAYERS
 
 pytestmark = pytest.mark.gpu
 
@@ -160,3 +161,10 @@ def test_lora_full_size_7b_like_parity():
 def test_lora_launch_edges(dims):
     T, d, N, Bs, k, r = dims
     check_full(gen.custom_shape(T, d, N, Bs, k, seed=T + N + r, w_std=0.05, wr_std=0.05), r, std=0.1)
+
+
+# The outer term added when one slab of all wavefronts is written out, and with the sums of the block list's parts.
+@pytest.mark.parametrize("tiles,parts,pieces,shape", LORA_LAYERS)
+def test_lora_one_slab_and_parts(tiles, parts, pieces, shape):
+    T, d, N, Bs, k = shape
+    check_full(gen.custom_shape(T, d, N, Bs, k, seed=T + N, w_std=0.05, wr_std=0.05), 5, std=0.1)

@@ -146,23 +146,23 @@ def test_ragged_shapes_full_parity(dims, act):
 
 
 @pytest.mark.parametrize("dims", [
-    # (T, d, N, Bs, k): d a multiple of 512 and at least 1024 (column tile, block) work items, where the
-    # weight-gradient GEMM runs its 512-column workgroups (eight wavefronts); 64- and 128-unit tiles
+    # (T, d, N, Bs, k): two thousand (column tile, block) work items of the weight-gradient GEMM, a dozen rows each; 64- and
+    # 128-unit tiles
     (600, 512, 1024, 32, 20),
     (500, 512, 1024, 96, 24),
 ])
-def test_many_blocks_wide_column_tiles(dims):
+def test_many_blocks(dims):
     T, d, N, Bs, k = dims
     s = gen.custom_shape(T, d, N, Bs, k, seed=T + N, w_std=0.05, wr_std=0.05)
     full_parity(s)
 
 
-def test_many_blocks_wide_column_tiles_with_a_split_bucket():
-    # the same kernel variant with one block drawn by every token: its bucket (900 rows) is cut into
-    # pieces that go through the staging slots and the fixed-order sum
+def test_many_blocks_with_a_split_bucket():
+    # as many with one block drawn by every token: its bucket (900 rows) is cut into pieces that go through the staging slots and
+    # the fixed-order sum
     T, d, N, Bs, k = 900, 512, 1024, 32, 12
     s = gen.custom_shape(T, d, N, Bs, k, seed=T + N, zipf_bias=True, w_std=0.05, wr_std=0.01)
-    dv, (offsets, _, _), _ = full_parity(s, f"skewed, 512-column tiles T={T} N={N} k={k}")
+    dv, (offsets, _, _), _ = full_parity(s, f"skewed, many blocks T={T} N={N} k={k}")
     sizes = np.diff(offsets.cpu().numpy())
     assert sizes.max() > 2 * 256, "the case is meant to have a bucket of more than two pieces"
 

@@ -1,5 +1,6 @@
 """K = Bs contraction with the per-token write-back: every form of the kernel (records of 2, 4, 6, 8 and 10 tiles of 16 rows, one
-slab or one per wavefront, the block list in parts), each block size, at the edges of tiles, records, ranges and slabs.
+slab or one per wavefront, the block list in parts) at each block size, with several records per wavefront and runs of several records
+(test_full_runs, by the layers of scatter_shapes.py), and the edges of tiles, records, ranges and slabs.
 
 With ReLU the kernel's operand is max(Hsave, 0) exactly, so the reference is a plain sum in 64 bits over the saved values, and
 what may differ is stated by the types: fp32 sums of K = k Bs products (each product and sum within 2^-24 of the sum of
@@ -66,10 +67,10 @@ def run(T, d, N, Bs, k, kind):
     (1, 64, 3, 2),               # one token
     (33, 192, 17, 5),            # three slabs, a slab per wavefront
     (24, 256, 64, 16),           # block list in parts
-    (700, 64, 40, 9),            # one slab, many ranges
-    (1203, 448, 24, 8),          # seven slabs
-    (4500, 1024, 16, 4),         # records of several tiles, one slab
-    (5003, 960, 32, 14),         # runs near the end of a record
+    (700, 64, 40, 9),            # ... and many ranges of 32 tokens
+    (1203, 448, 24, 8),          # seven column slabs, a slab per wavefront
+    (4500, 1024, 16, 4),         # records of 4 and 6 tiles, one slab
+    (5003, 960, 32, 14),         # records of 4, 6 and 10 tiles, runs near the end of a record
 ])
 def test_forms(T, d, N, Bs, k):
     run(T, d, N, Bs, k, "even")
@@ -77,12 +78,12 @@ def test_forms(T, d, N, Bs, k):
 
 @pytest.mark.parametrize("Bs", [32, 64, 96, 128])
 @pytest.mark.parametrize("T,d,N,k", [
-    (1111, 512, 6, 6),           # every token in every block: runs in several records
-    (2600, 1024, 5, 5),
-    (6001, 1536, 3, 3),          # runs of hundreds of rows, more records of one run than wavefronts
-    (3001, 256, 1, 1),           # one block
+    (1111, 512, 6, 6),           # every token in every block: 35 rows a run, two records of 32 or one of 64
+    (2600, 1024, 5, 5),          # one record of 55 or 82 rows a run
+    (6001, 1536, 3, 3),          # 188 or 286 rows a run, two or three records: six or nine in all for four wavefronts
+    (3001, 256, 1, 1),           # one block: a run is all there is, wavefronts without a record
 ])
-def test_runs_of_many_records(T, d, N, Bs, k):
+def test_every_token_in_every_block(T, d, N, Bs, k):
     run(T, d, N, Bs, k, "even")
 
 

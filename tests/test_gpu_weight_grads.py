@@ -17,9 +17,15 @@ pytestmark = pytest.mark.gpu
 SIZES = (0, 1, 15, 16, 17, 33, 96, 111, 255, 256, 257, 271, 287, 300, 511, 512, 513, 529, 545, 800)
 
 
-@pytest.mark.parametrize("d,Bs", [(64, 64), (192, 32), (320, 96), (512, 128), (256, 160), (576, 288)])
-def test_bucket_sizes_around_the_groups(d, Bs):
-    sizes = np.array(SIZES)
+# Narrow blocks cut a bucket of more than 1.5 times the mean (1120 rows here) into pieces of equal size: 2101 rows into two, 2777 into three of
+# 926 and 925, which begin anywhere and have more stages (58 to 66 of 16 rows) than the ids of two groups hold.
+PIECES = (37, 2101, 5, 700, 301, 2777, 0, 1)
+
+
+@pytest.mark.parametrize("sizes,d,Bs", [(SIZES, 64, 64), (SIZES, 192, 32), (SIZES, 320, 96), (SIZES, 512, 128), (SIZES, 256, 160),
+                                        (SIZES, 576, 288), (PIECES, 192, 32), (PIECES, 320, 96), (PIECES, 256, 160)], ids=str)
+def test_bucket_sizes_around_the_groups(sizes, d, Bs):
+    sizes = np.array(sizes)
     N, T = len(sizes), int(sizes.sum())
     rng = np.random.default_rng(d + Bs)
     block = rng.permutation(np.repeat(np.arange(N), sizes)).astype(np.int32)

@@ -1,5 +1,6 @@
 """Host side of the K = Bs contraction: which workgroup takes which part of the records, token range and column slab.  No GPU."""
 import ctypes
+import itertools
 import json
 import os
 import random
@@ -9,7 +10,7 @@ import numpy as np
 import pytest
 
 from paper_2312_10365_amd import spt
-from scatter_shapes import LAYERS
+from scatter_shapes import LAYERS, LORA_LAYERS
 
 
 def layout(T, d, N, Bs, k):
@@ -54,11 +55,16 @@ def test_drawn_shapes():
 
 
 # What the layers that the GPU tests run are there for.
-@pytest.mark.parametrize("tiles,parts,pieces,shape", LAYERS)
+@pytest.mark.parametrize("tiles,parts,pieces,shape", LAYERS + LORA_LAYERS)
 def test_layers_of_the_gpu_tests(tiles, parts, pieces, shape):
     (nt, R, nr, p, _, _), _ = layout(*shape)
     assert (nt, p > 1, -(-R // (16 * nt))) == (tiles, parts, pieces) and nr >= 3
     check(shape)
+
+
+def test_layers_of_the_gpu_tests_are_all_forms():
+    assert {(tiles, shape[3], parts) for tiles, parts, _, shape in LAYERS} == set(
+        itertools.product((2, 4, 6, 8, 10), (32, 64, 96, 128), (False, True)))
 
 
 # us of a launch on an MI355X under even and under skewed routing, [tiles, tokens per range, parts, even, skewed], for the quicker
