@@ -256,7 +256,9 @@ hipError_t bucket_static_scratch(int32_t** out) {
 
 hipError_t run_bucket(const spt_shape_t& s, const int32_t* idx, int32_t* offsets, int32_t* perm,
                       int32_t* inv, int32_t* chunk_hist, hipStream_t st) {
-  // One workgroup sorts 8 thousand pairs in 5-7 us, two launches over many CUs take 9 (16 thousand: 14 us).
+  // One workgroup up to where it takes as long as the two launches and what the second one costs a pass that is waited for, 5 to 7 us.
+  // us in a graph, one workgroup / two launches: 2048 pairs 4.8 / 7.0, 4096 5.8 / 7.1, 6144 7.0 / 7.2, 8192 8.0 / 7.4, 12288 10.9 / 7.3,
+  // 16384 13.0 / 7.5 (16 blocks, 4 each); 4096 6.5 / 9.8, 8192 9.5 / 9.9, 12288 13.8 / 10.2 (128, 32); 8192 11.0 / 7.6, 12288 17.0 / 7.8 (128, 8).
   const size_t nwp = ((s.T + 31) / 32) | 1;
   const size_t small = (size_t)s.N * nwp * 4 + ((size_t)s.N * nwp + 1) / 2 * 4 + (size_t)s.N * 4;
   if ((int64_t)s.T * s.k <= 8192 && small <= 60 * 1024) {
@@ -266,7 +268,8 @@ hipError_t run_bucket(const spt_shape_t& s, const int32_t* idx, int32_t* offsets
   }
   const int nchunks = (s.T + kBucketChunkTokens - 1) / kBucketChunkTokens;
   const size_t smem = (size_t)s.N * kWordsPerChunk * sizeof(uint32_t);
-  // Two pairs of a chunk per thread, a thread per bucket at least.  A chunk's work is a chain of loads, LDS atomics and
+  // Two pairs of a chunk per thread up to 16 of a token's blocks, k / 8 beyond (1024 threads at most; the first eight held in registers), a thread
+  // per bucket and 256 at least.  A chunk's work is a chain of loads, LDS atomics and
   // stores whose length is the number of pairs a thread has, behind that of the histograms it adds up.  us, 256 threads with
   // the pairs loaded anew for every pass and all histograms per thread -> this: 8192 tokens, 128 blocks, 32 each 13.8 -> 9.4;
   // 16384, 64, 16 11.3 -> 7.3; 3001, 128, 32 11.8 -> 8.2.  512 threads there: 10.9, 7.6, 9.8; 1024 threads for 2 of 4 blocks, 8192

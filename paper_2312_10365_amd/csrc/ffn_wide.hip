@@ -7,6 +7,8 @@
 //   128 x 128 per wavefront (4 x 4 tiles of v_mfma_f32_32x32x16_bf16, 256 accumulator
 //   registers), K in stages of 32 through a 5-slot LDS ring (32 KiB per stage, three stages
 //   in flight, two resident) filled by global_load_lds_dwordx4 with hand-placed vmcnt waits.
+//   The weight gradients have four slots, two stages in flight, and the token ids of their gathered
+//   rows in the last one's place (global_load_lds_dword, 2 KiB).
 //
 //   GEMM                       | A side (MFMA rows)           | B side (MFMA columns)        | K
 //   up  (Alg. 4 inner proj.)   | hidden units: rows of W1_b   | bucket rows: gathered X rows | d
@@ -70,6 +72,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   using Tile = WideTile<MA, NB>;
   // (weight gradients: a slot less, for the token ids)
   constexpr int W_STAGE = Tile::STAGE, W_STAGES = OP == OP_DW ? Tile::STAGES - 1 : Tile::STAGES;
+  static_assert(OP != OP_DW || W_STAGES * W_STAGE + 4 * 512 <= W_SMEM, "the token ids lie behind the ring");
   constexpr int A_CH = 8 * MA, B_CH = 8 * NB;      // 16-byte chunks of a K-row of a K-major operand
   constexpr int A_HALF = 32 * MA, B_HALF = 32 * NB;  // A-side / B-side indices of a wavefront
   const int Bs = p.Bs, d = p.d;

@@ -149,7 +149,8 @@ __device__ __forceinline__ u32x4 tr_frag(const char* p) {
 // copies before the scatter: 266 / 266; 64-wide with 256 keys per chunk of scores 184 / 182 where 149 / 147 is.)
 // 64-wide heads of several chunks: eight key groups, each wavefront both column tiles, so a weight is split once and not by two
 // column groups (the vector units' largest part); forward, four groups -> eight: S 32, n 2048, L 256 139 -> 129; S 64, n 1024, L 200
-// 81 -> 77; S 256, n 600, L 90 131 -> 127.  With one chunk the second accumulator spills and nothing is gained (121 / 122); 128-wide
+// 81 -> 77; S 256, n 600, L 90 131 -> 127; backward 138 -> 130, 82 -> 79, 135 -> 132; few entries gain nothing: n 768, L 48 49 / 47 both, n 700, L 8 50
+// both, 47 -> 48 backward.  With one chunk the second accumulator spills and nothing is gained (121 / 122); 128-wide
 // heads with four groups and chunks of 128 keys spill: 241 -> 314 at S 96, n 1100, L 137.
 constexpr int NW = 8, BQ = 32, NT = NW * 64;
 template <int DH, int KT>
