@@ -498,6 +498,7 @@ static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
       int last = 0;
       for (int each = 0; each <= (sp == 1 ? 24 : 5) && last < nr_max; ++each) {
         const int count = each == 0 ? nr_min : each * 256 / (p.nslab * sp);
+        if (sp > 1 && (int64_t)count * p.nslab * sp > 5 * 256) break;   // (also the fewest there can be: 84857 tokens, 3.3 GB of sums)
         if (count <= last || count < nr_min) continue;
         last = count > nr_max ? nr_max : count;
         const int R = (s.T + last - 1) / last, nr = (s.T + R - 1) / R;

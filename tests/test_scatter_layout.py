@@ -39,6 +39,7 @@ def check(shape):
     want = {(p, r, c) for p in range(parts) for r in range(nr) for c in range(nslab)}
     got = [tuple(x) for x in items[real].tolist()]
     assert len(got) == len(want) and set(got) == want            # each item once
+    assert parts == 1 or len(want) <= 5 * 256                    # parts, and their sums' memory, for few tokens
     per_xcd = [int(real[x::8].sum()) for x in range(8)]          # workgroups go to the eight XCDs in turn
     assert max(per_xcd) == -(-len(want) // 8), (shape, per_xcd)
 
