@@ -45,7 +45,8 @@ def check(shape):
 
 
 # 85 items in three parts, 84 in three, 63 in two: 33 workgroups for an XCD's 32 CUs where each XCD has all parts of its own items
-@pytest.mark.parametrize("shape", [(2100, 320, 60, 128, 24), (7000, 256, 90, 128, 30), (1, 64, 1, 32, 1), (24, 4096, 128, 128, 32)])
+@pytest.mark.parametrize("shape", [(2100, 320, 60, 128, 24), (7000, 256, 90, 128, 30), (1, 64, 1, 32, 1), (24, 4096, 128, 128, 32),
+                                   (84857, 5184, 951, 128, 579)])
 def test_every_item_once_and_no_xcd_more_than_an_eighth(shape):
     check(shape)
 
