@@ -41,9 +41,13 @@
 // Measured, us a launch, the kernel this replaces (four wavefronts at one run, a barrier per run) -> this one: 7B-like
 // (T 8192, d 4096, N 128, Bs 128, k 32) 590 -> 497; BERT-large-like (16384, 1024, 64, 64, 16) 124 -> 82; the
 // OPT-1.3B-like layer (8192, 2048, 64, 128, 16) 195 -> 165; BERT-base-like (2048, 768, 32, 96, 8) 25 -> 18.
-// What bounds it: one wavefront per SIMD (its registers hold the operands of a run and the next one's loads in flight) issues
-// about 110 instructions per tile against 256 clk of products, 540 clk with nothing loaded or added, 720 with both; bytes
-// into the CUs come at 13 TB/s, which is the limit where a range is short and the weights are read often.
+// Then tiles that a record does not hold left out, and the slab's new values written and published earlier (`ALL`, `WRITE` below), us of a
+// launch in turn on one box: 7B-like 513 -> 484; the OPT-1.3B-like layer, skewed routing, 162 -> 147; 3001 tokens of the 7B-like layer
+// 236 -> 223; 16384 tokens, d 4096, 64 blocks of 96, 12 each 396 -> 378; BERT-large-like as it was.
+// What bounds it (8 K-steps): one wavefront per SIMD, because its registers hold the operands of a run and the next one's loads in flight.  It issues
+// in 54 % of the cycles, waits for loads, LDS or its turn in 28 % and for a unit in 18 %; the matrix cores are busy in 27 %.  Without the order
+// of the records a launch takes 7 % less (7B-like), 19 % (3001 tokens) and 22 % less (BERT-large-like, 4.6 tiles a run: four wavefronts
+// that stay nearly two tiles apart do not fit in it), without the slab 15, 19 and 32 %, with all rows in one line of L1 4, 11 and 4 %.
 #include <math.h>
 #include <stdlib.h>
 #include <type_traits>
@@ -102,7 +106,12 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
 // KS = Bs / 16.  NT tiles of 16 rows per record, each a slot of the unrolled loop; rows are requested RH tiles ahead.
 // LATE: the next weight slice is requested in a record's last slot, not behind its first (64 registers less).
 // WG: workgroups a CU is to hold.
-template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
+// ALL: slots that are gone through whatever the record holds; of the others those without a tile only request the rows and weights that
+// fall to them.  (All loads stay in common code, in one order: the compiler's waits count them.)  Records of 8 and 10 tiles, and of 6 with at least
+// 6 K-steps: rows requested behind the products and not between them cost less than empty slots.  Where a slot is
+// short they cost as much or more, us with and without: 32768 tokens, d 1024, 128 blocks of 32, 16 each (4 tiles) 287 / 246; 65536, 512, 32
+// of 64, 4 each (4 tiles) 95 / 87; BERT-large-like (6 tiles) 92 / 90.
+template <int KS, int NT, int RH, bool LATE, int WG, bool OWN, int ALL>
 __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
     const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
     const int32_t* __restrict__ nruns, const int32_t* __restrict__ tok, int N, int d, int T, int R,
@@ -309,6 +318,7 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
     const Where x = where(qn);
     auto slot = [&](auto tag) {
       constexpr int ti = decltype(tag)::value, par = ti & 1, before = par ^ 1;
+      constexpr bool may_skip = ti >= ALL;
       auto mfma1 = [&](int s, int t) {
         acc[par][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hb[ti % RH][s], wf[s][t],
                                                               s == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[par][t], 0, 0, 0);
@@ -316,6 +326,10 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
       constexpr std::integral_constant<int, (ti + RH) % NT> ask{};
       const Where& xa = ti + RH < NT ? xc : x;
       constexpr int G = 4 * KT;
+      // Where the slab's rows are read and written behind the products, and where the others' progress is looked at again.  What lies between
+      // reading and publishing is time that the records behind this one wait: reading earlier makes this one wait for its own turn
+      // (READ 1, 2, 4: 507, 495, 484 us 7B-like), writing in the last four gaps and publishing behind them 3001 tokens 231, from the middle on 223.
+      constexpr int READ = G / 4, WRITE = G > 8 ? G / 2 : G - 4, LOOK = G - 4;
       int tk = 0, xcur = 0, last_token = 0, first_token = 0;
       // Everything but the products, dealt to the gaps behind them (n: 0 .. G - 1): a vector instruction or two in the shadow of
       // every product cost nothing, bunched they cost 4 clk each.
@@ -328,34 +342,56 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
           xcur = tk * SC_STRIDE;
           asm volatile("" : "+v"(xcur));
         }
-        if (n == G / 4) { rmw_read(0); rmw_read(1); }
-        if (n == G / 4 + (G > 4 ? 1 : 0)) { rmw_read(2); rmw_read(3); }
-        if (n == G / 2) last_token = __builtin_amdgcn_readlane(tk, ti + 1 < ntile ? 63 : last_lane);
-        if (n == G / 2) first_token = __builtin_amdgcn_readlane(tk, ti == 0 ? q.lo & 3 : 0);
-        if (n >= 4 && n % 4 == 0) request_h(ask, xa, n / 4 - 1);
-        if (LATE && n % 4 == 1 && n > 4) request_late(tag, x, n / 4 - 1);
-        if (!LATE && n == (G > 4 ? 6 : 2)) request_w(tag, x);
-        if (n == G - 4) f = progress();
-        if (G > 4 && n >= G - 4) rmw_write(n - (G - 4), acc[before]);
+        if (n == READ) { rmw_read(0); rmw_read(1); }
+        if (n == READ + (G > 4 ? 1 : 0)) { rmw_read(2); rmw_read(3); }
+        if (n == READ + 2) last_token = __builtin_amdgcn_readlane(tk, ti + 1 < ntile ? 63 : last_lane);
+        if (n == READ + 2) first_token = __builtin_amdgcn_readlane(tk, ti == 0 ? q.lo & 3 : 0);
+        if (!may_skip) {
+          if (n >= 4 && n % 4 == 0) request_h(ask, xa, n / 4 - 1);
+          if (LATE && n % 4 == 1 && n > 4) request_late(tag, x, n / 4 - 1);
+          if (!LATE && n == (G > 4 ? 6 : 2)) request_w(tag, x);
+        }
+        if (n == LOOK) f = progress();
+        if (G > 4 && n >= WRITE && n < WRITE + 4) rmw_write(n - WRITE, acc[before]);
+        if (G > 8 && n == WRITE + 3) publish(code + (may_skip || ti < ntile ? first_token : SC_CODE));
         if (G == 4 && n == 3) {
 #pragma unroll
           for (int v = 0; v < 4; ++v) rmw_write(v, acc[before]);
         }
         __builtin_amdgcn_sched_barrier(0);
       };
+      auto products = [&] {
 #pragma unroll
-      for (int n = 0; n < G; ++n) {
-        if (ti == 0) make_w(n / 4, n % 4);
-        if (n == G / 4) may_go(f);
-        mfma1(n / 4, n % 4);
-        gap(n);
+        for (int n = 0; n < G; ++n) {
+          if (ti == 0) make_w(n / 4, n % 4);
+          if (n == READ) may_go(f);
+          mfma1(n / 4, n % 4);
+          gap(n);
+        }
+        if (G <= 8) publish(code + (may_skip || ti < ntile ? first_token : SC_CODE));
+        xprev = xcur;
+        need_prev = may_skip || ti < ntile ? need_base + (other_run ? last_token + 1 : 0) : SC_NONE;
+      };
+      if (!may_skip) {
+        products();
+        request_h(ask, xa, KT - 1);
+        if (LATE) request_late(tag, x, KT - 1);
+      } else {
+        if (ti < ntile) {
+          products();
+        } else if (par == 1 && ti == ntile) {     // (the last tile waits where the next record's first slot adds it from)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) acc[1][t] = acc[0][t];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < KT; ++s) {
+          request_h(ask, xa, s);
+          if (LATE) request_late(tag, x, s);
+          else if (s == 0) request_w(tag, x);
+        }
       }
-      publish(code + (ti < ntile ? first_token : SC_CODE));
-      request_h(ask, xa, KT - 1);
-      if (LATE) request_late(tag, x, KT - 1);
       request_t(ask, xa);
-      xprev = xcur;
-      need_prev = ti < ntile ? need_base + (other_run ? last_token + 1 : 0) : SC_NONE;
       __builtin_amdgcn_sched_barrier(0);
     };
     for_each_index(slot, std::make_integer_sequence<int, NT>{});
@@ -557,13 +593,13 @@ hipError_t run_scatter_ranges(const spt_shape_t& s, const ScatterPlan& p, int32_
   return hipGetLastError();
 }
 
-template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
+template <int KS, int NT, int RH, bool LATE, int WG, bool OWN, int ALL>
 static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin,
                                    const uint16_t* W, const int32_t* table, const int32_t* tok,
                                    uint16_t* out, const uint16_t* Z, float* split, hipStream_t st) {
   static bool attr_set = false;
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN, ALL>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
@@ -571,7 +607,7 @@ static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, c
   const RunRec* runs = reinterpret_cast<const RunRec*>(table);
   const int32_t* nruns = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + p.runs_bytes);
   const bool parts = p.splits > 1;
-  ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN><<<scatter_grid(p), SC_THREADS, p.smem, st>>>(
+  ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN, ALL><<<scatter_grid(p), SC_THREADS, p.smem, st>>>(
       Hin, W, runs, nruns, tok, s.N, s.d, s.T, p.R, p.nr, p.nslab, p.splits, p.inner, p.cap, out, Z, parts ? split : nullptr);
   if (!parts) return hipGetLastError();
   const hipError_t e = hipGetLastError();
@@ -588,11 +624,11 @@ hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint
   // of 16 the weight slice later)
 #define SPT_SC_ARGS s, p, Hin, W, table, tok, out, Z, split, st
 #define SPT_SC(KS)                                                                                                      \
-  (p.nt == 2   ? launch_scatter_t<KS, 2, 2, false, 1, true>(SPT_SC_ARGS)                                                \
-   : p.nt == 4 ? launch_scatter_t<KS, 4, (KS > 6 ? 2 : 4), (KS > 6), 2, false>(SPT_SC_ARGS)                             \
-   : p.nt == 6 ? launch_scatter_t<KS, 6, (KS > 4 ? 3 : 6), (KS > 6), 2, false>(SPT_SC_ARGS)                             \
-   : p.nt == 8 ? launch_scatter_t<KS, 8, 8, false, 1, false>(SPT_SC_ARGS)                                               \
-               : launch_scatter_t<KS, 10, 10, false, 1, false>(SPT_SC_ARGS))
+  (p.nt == 2   ? launch_scatter_t<KS, 2, 2, false, 1, true, 2>(SPT_SC_ARGS)                                             \
+   : p.nt == 4 ? launch_scatter_t<KS, 4, (KS > 6 ? 2 : 4), (KS > 6), 2, false, 4>(SPT_SC_ARGS)                          \
+   : p.nt == 6 ? launch_scatter_t<KS, 6, (KS > 4 ? 3 : 6), (KS > 6), 2, false, (KS > 4 ? 4 : 6)>(SPT_SC_ARGS)           \
+   : p.nt == 8 ? launch_scatter_t<KS, 8, 8, false, 1, false, 4>(SPT_SC_ARGS)                                            \
+               : launch_scatter_t<KS, 10, 10, false, 1, false, 4>(SPT_SC_ARGS))
   switch (s.Bs / 16) {
     case 2: return SPT_SC(2);
     case 4: return SPT_SC(4);

@@ -22,6 +22,8 @@ def routing(T, N, k, kind, seed):
         w = np.where(np.arange(N) % 2 == 0, 1.0, 1e-3) * (np.arange(N) != N - 1)
     elif kind == "full":                    # two blocks hold every token, next to ordinary ones
         w = np.where(np.arange(N) % (N // 2 + 1) == 1, 1e9, 1.0)
+    elif kind == "steps":                   # a block holds more than the one before it: runs of one row up to most of a range
+        w = 4.0 ** (np.arange(N) * 6.0 / N - 3.0)
     else:
         w = np.ones(N)
     keys = rng.exponential(size=(T, N)) / np.maximum(w, 1e-12)
@@ -96,6 +98,12 @@ def test_uneven_blocks(T, d, N, Bs, k):
 @pytest.mark.parametrize("tiles,parts,pieces,shape", LAYERS)
 def test_full_runs(tiles, parts, pieces, shape):
     run(*shape, "full")
+
+
+# Runs of every length, so that a record holds any number of its tiles: the slots past its last one are left out.
+@pytest.mark.parametrize("tiles,parts,pieces,shape", [x for x in LAYERS if x[0] >= 6])
+def test_records_of_any_length(tiles, parts, pieces, shape):
+    run(*shape, "steps")
 
 
 # Sorted by block as offsets say, but not stable (tokens descend, or are shuffled, inside a bucket): not what the header asks for
