@@ -106,12 +106,7 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
 // KS = Bs / 16.  NT tiles of 16 rows per record, each a slot of the unrolled loop; rows are requested RH tiles ahead.
 // LATE: the next weight slice is requested in a record's last slot, not behind its first (64 registers less).
 // WG: workgroups a CU is to hold.
-// ALL: slots that are gone through whatever the record holds; of the others those without a tile only request the rows and weights that
-// fall to them.  (All loads stay in common code, in one order: the compiler's waits count them.)  Records of 8 and 10 tiles, and of 6 with at least
-// 6 K-steps: rows requested behind the products and not between them cost less than empty slots.  Where a slot is
-// short they cost as much or more, us with and without: 32768 tokens, d 1024, 128 blocks of 32, 16 each (4 tiles) 287 / 246; 65536, 512, 32
-// of 64, 4 each (4 tiles) 95 / 87; BERT-large-like (6 tiles) 92 / 90.
-template <int KS, int NT, int RH, bool LATE, int WG, bool OWN, int ALL>
+template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
 __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
     const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
     const int32_t* __restrict__ nruns, const int32_t* __restrict__ tok, int N, int d, int T, int R,
@@ -119,6 +114,13 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
     float* __restrict__ split) {
   constexpr int Bs = KS * 16;
   constexpr int KT = KS / 2;                   // K-steps of 32 hidden units
+  // Slots that are gone through whatever the record holds; of the others those without a tile only request the rows that
+  // fall to them.  (All loads stay in common code, in one order: the compiler's waits count them.)  Rows requested behind the products and not
+  // between them cost less than the empty slots of records of 8 and 10 tiles, but where two workgroups share a CU, and fill each other's gaps, as much or
+  // more, us with and without: 4 tiles, 32768 tokens, d 1024, 128 blocks of 32, 16 each 287 / 246; 65536, 512, 32 of 64, 4 95 / 87; 6 tiles,
+  // 4000, 1024, 100 of 128, 30 70 / 64; 3000, 256, 100 of 96, 30 24.3 / 22.7; BERT-large-like 92 / 90.
+  constexpr int ALL = NT > 6 ? 4 : NT;
+  static_assert(ALL == NT || !LATE, "weights are requested in slots that are gone through");
   constexpr int THREADS = SC_THREADS;
   
   extern __shared__ uint4 sc_smem[];
@@ -385,11 +387,7 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < KT; ++s) {
-          request_h(ask, xa, s);
-          if (LATE) request_late(tag, x, s);
-          else if (s == 0) request_w(tag, x);
-        }
+        for (int s = 0; s < KT; ++s) request_h(ask, xa, s);
       }
       request_t(ask, xa);
       __builtin_amdgcn_sched_barrier(0);
@@ -593,13 +591,13 @@ hipError_t run_scatter_ranges(const spt_shape_t& s, const ScatterPlan& p, int32_
   return hipGetLastError();
 }
 
-template <int KS, int NT, int RH, bool LATE, int WG, bool OWN, int ALL>
+template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
 static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin,
                                    const uint16_t* W, const int32_t* table, const int32_t* tok,
                                    uint16_t* out, const uint16_t* Z, float* split, hipStream_t st) {
   static bool attr_set = false;
   if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN, ALL>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
     attr_set = true;
@@ -607,7 +605,7 @@ static hipError_t launch_scatter_t(const spt_shape_t& s, const ScatterPlan& p, c
   const RunRec* runs = reinterpret_cast<const RunRec*>(table);
   const int32_t* nruns = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(table) + p.runs_bytes);
   const bool parts = p.splits > 1;
-  ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN, ALL><<<scatter_grid(p), SC_THREADS, p.smem, st>>>(
+  ffn_scatter_kernel<KS, NT, RH, LATE, WG, OWN><<<scatter_grid(p), SC_THREADS, p.smem, st>>>(
       Hin, W, runs, nruns, tok, s.N, s.d, s.T, p.R, p.nr, p.nslab, p.splits, p.inner, p.cap, out, Z, parts ? split : nullptr);
   if (!parts) return hipGetLastError();
   const hipError_t e = hipGetLastError();
@@ -624,11 +622,11 @@ hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint
   // of 16 the weight slice later)
 #define SPT_SC_ARGS s, p, Hin, W, table, tok, out, Z, split, st
 #define SPT_SC(KS)                                                                                                      \
-  (p.nt == 2   ? launch_scatter_t<KS, 2, 2, false, 1, true, 2>(SPT_SC_ARGS)                                             \
-   : p.nt == 4 ? launch_scatter_t<KS, 4, (KS > 6 ? 2 : 4), (KS > 6), 2, false, 4>(SPT_SC_ARGS)                          \
-   : p.nt == 6 ? launch_scatter_t<KS, 6, (KS > 4 ? 3 : 6), (KS > 6), 2, false, (KS > 4 ? 4 : 6)>(SPT_SC_ARGS)           \
-   : p.nt == 8 ? launch_scatter_t<KS, 8, 8, false, 1, false, 4>(SPT_SC_ARGS)                                            \
-               : launch_scatter_t<KS, 10, 10, false, 1, false, 4>(SPT_SC_ARGS))
+  (p.nt == 2   ? launch_scatter_t<KS, 2, 2, false, 1, true>(SPT_SC_ARGS)                                                \
+   : p.nt == 4 ? launch_scatter_t<KS, 4, (KS > 6 ? 2 : 4), (KS > 6), 2, false>(SPT_SC_ARGS)                             \
+   : p.nt == 6 ? launch_scatter_t<KS, 6, (KS > 4 ? 3 : 6), (KS > 6), 2, false>(SPT_SC_ARGS)                             \
+   : p.nt == 8 ? launch_scatter_t<KS, 8, 8, false, 1, false>(SPT_SC_ARGS)                                               \
+               : launch_scatter_t<KS, 10, 10, false, 1, false>(SPT_SC_ARGS))
   switch (s.Bs / 16) {
     case 2: return SPT_SC(2);
     case 4: return SPT_SC(4);

@@ -101,7 +101,7 @@ def test_full_runs(tiles, parts, pieces, shape):
 
 
 # Runs of every length, so that a record holds any number of its tiles: the slots past its last one are left out.
-@pytest.mark.parametrize("tiles,parts,pieces,shape", [x for x in LAYERS if x[0] >= 6])
+@pytest.mark.parametrize("tiles,parts,pieces,shape", [x for x in LAYERS if x[0] >= 8])
 def test_records_of_any_length(tiles, parts, pieces, shape):
     run(*shape, "steps")
 
