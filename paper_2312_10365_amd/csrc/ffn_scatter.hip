@@ -54,6 +54,7 @@
 #include <utility>
 
 #include "ffn_common.hpp"
+#include "ffn_dw.hpp"
 #include "spt_host.hpp"
 #include "profile.hpp"
 
@@ -106,9 +107,9 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
 // KS = Bs / 16.  NT tiles of 16 rows per record, each a slot of the unrolled loop; rows are requested RH tiles ahead.
 // LATE: the next weight slice is requested in a record's last slot, not behind its first (64 registers less).
 // WG: workgroups a CU is to hold.
-template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
-__global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
-    const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
+template <int KS, int NT, int RH, bool LATE, bool OWN>
+__device__ __forceinline__ void scatter_tile(
+    int wg, const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
     const int32_t* __restrict__ nruns, const int32_t* __restrict__ tok, int N, int d, int T, int R,
     int nr, int nslab, int parts, int inner, int cap, uint16_t* __restrict__ out, const uint16_t* __restrict__ Z,
     float* __restrict__ split) {
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
 
-  const ScatterItem item = scatter_item(blockIdx.x, nslab, nr, parts, inner);
+  const ScatterItem item = scatter_item(wg, nslab, nr, parts, inner);
   if (item.slab < 0) return;
   const int slab = item.slab, r = item.r;
   const int t0 = r * R, c0 = slab * SC_C;
@@ -437,6 +438,34 @@ __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
   }
 }
 
+template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
+__global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
+    const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
+    const int32_t* __restrict__ nruns, const int32_t* __restrict__ tok, int N, int d, int T, int R,
+    int nr, int nslab, int parts, int inner, int cap, uint16_t* __restrict__ out, const uint16_t* __restrict__ Z,
+    float* __restrict__ split) {
+  scatter_tile<KS, NT, RH, LATE, OWN>(blockIdx.x, Hin, W, runs, nruns, tok, N, d, T, R, nr, nslab, parts, inner, cap, out, Z, split);
+}
+
+// dX and both weight gradients of a backward pass, which need nothing of one another, in one launch: the first `mine` workgroups are
+// those of the contraction (two tiles a record), the others those of the weight gradients' kernel.  For the layers whose launches leave CUs empty or are not much
+// longer than their own latency.
+template <int KS, int UT>
+__global__ __launch_bounds__(SC_THREADS, 2) void ffn_scatter_dw_kernel(
+    const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
+    const int32_t* __restrict__ nruns, const int32_t* __restrict__ tok, int N, int d, int T, int R,
+    int nr, int nslab, int inner, int cap, uint16_t* __restrict__ out, int mine, DwOperands ops0, DwOperands ops1, int each,
+    const uint16_t* __restrict__ zero_row, int npieces, const DwPiece* __restrict__ pieces) {
+  static_assert(SC_THREADS == 256, "both kernels' workgroups");
+  const int wg = blockIdx.x;
+  if (wg < mine) {
+    scatter_tile<KS, 2, 2, false, true>(wg, Hin, W, runs, nruns, tok, N, d, T, R, nr, nslab, 1, inner, cap, out, nullptr, nullptr);
+    return;
+  }
+  const int rest = wg - mine;
+  dw_tile<UT>(rest < each ? ops0 : ops1, rest < each ? rest : rest - each, 0, tok, zero_row, npieces, KS * 16, d, pieces, N);
+}
+
 // out = the parts' sums added in order (+ the low-rank row), rounded once.
 __global__ __launch_bounds__(256) void scatter_sum_kernel(const float* __restrict__ split, int splits, int64_t total,
                                                           uint16_t* __restrict__ out, const uint16_t* __restrict__ Z) {
@@ -636,6 +665,42 @@ hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint
   }
 #undef SPT_SC_ARGS
 #undef SPT_SC
+}
+
+// Where two workgroups share a CU, so that the launch holds as much at once as the two it replaces.  us a pass, two launches and one: 512 tokens, d 256, 16
+// blocks of 64, 4 each (34 KB of slabs) 52 / 49; 1024, 1024, 32 of 128, 8 (67 KB) 110 / 101; 4096, 512, 32 of 64, 8 (67 KB) 100 / 98; with one
+// workgroup per CU 2048, 768, 32 of 96, 8 (101 KB) 105 / 107; 1500, 1024, 64 of 32, 16 (97 KB) 101 / 104.
+bool scatter_takes_dw(const ScatterPlan& p) { return p.nt == 2 && p.splits == 1 && p.smem <= 80 * 1024; }
+
+template <int KS>
+static hipError_t launch_scatter_dw_t(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W,
+                                      const Schedule& sc, uint16_t* out, const DwOperands* ops, hipStream_t st) {
+  constexpr int UT = KS > 4 ? 128 : 64;
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_scatter_dw_kernel<KS, UT>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  const RunRec* runs = reinterpret_cast<const RunRec*>(sc.rstart);
+  const int32_t* nruns = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(sc.rstart) + p.runs_bytes);
+  const int mine = scatter_grid(p), each = dw_grid(sc.dw_cap, s.d), lds = p.smem > dw_smem_bytes<UT>() ? p.smem : dw_smem_bytes<UT>();
+  ffn_scatter_dw_kernel<KS, UT><<<mine + 2 * each, SC_THREADS, lds, st>>>(
+      Hin, W, runs, nruns, sc.tok, s.N, s.d, s.T, p.R, p.nr, p.nslab, p.inner, p.cap, out, mine, ops[0], ops[1], each, sc.zero_row,
+      sc.dw_cap, sc.dw_pieces);
+  return hipGetLastError();
+}
+
+hipError_t launch_scatter_dw(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W, const Schedule& sc,
+                             uint16_t* out, const DwOperands* ops, hipStream_t st) {
+  switch (s.Bs / 16) {
+    case 2: return launch_scatter_dw_t<2>(s, p, Hin, W, sc, out, ops, st);
+    case 4: return launch_scatter_dw_t<4>(s, p, Hin, W, sc, out, ops, st);
+    case 6: return launch_scatter_dw_t<6>(s, p, Hin, W, sc, out, ops, st);
+    case 8: return launch_scatter_dw_t<8>(s, p, Hin, W, sc, out, ops, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace spt

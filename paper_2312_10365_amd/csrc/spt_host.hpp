@@ -89,6 +89,15 @@ hipError_t run_scatter_ranges(const spt_shape_t& s, const ScatterPlan& p, int32_
 hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W,
                           const int32_t* rstart, const int32_t* tok, uint16_t* out, const uint16_t* Z,
                           float* split, hipStream_t st);
+// One product of the narrow-block weight-gradient GEMM: its operands, the gradient, and the staging slots of pieces.
+struct DwOperands {
+  const uint16_t *Act, *Hin;
+  float *dW, *stage;
+};
+// The same contraction and both weight-gradient GEMMs in one launch (their pieces still to be summed): short token ranges only.
+bool scatter_takes_dw(const ScatterPlan& p);
+hipError_t launch_scatter_dw(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W, const Schedule& sc,
+                             uint16_t* out, const DwOperands* ops, hipStream_t st);
 
 // Arguments of the wide-block GEMM kernels (blocks of more than 128 hidden units).
 struct WideArgs {

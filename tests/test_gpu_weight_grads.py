@@ -52,3 +52,48 @@ def test_bucket_sizes_around_the_groups(sizes, d, Bs):
             bound = extra + 2.0 * K ** 0.5 * 2.0 ** -24 * mag + 2.0 ** -23 * ref.abs() + 1e-30
             worst = float(((got.double().cpu() - ref).abs() / bound).max())
             assert worst <= 1.0 + 2.0 ** -8, (name, b, K, worst)
+
+
+# dX and both weight gradients in one launch (short token ranges whose slabs leave a CU room for a second workgroup): every block size, one and
+# several column tiles, ragged ones, few and many pieces, and slabs of 80 KB and the next larger ones, which are launches of their own.  dX is the sum of
+# k Bs products of dHpre, rounded to bf16 like above, and rounded once more.
+@pytest.mark.parametrize("T,d,N,Bs,k,uneven", [(33, 192, 17, 128, 5, False), (512, 256, 16, 64, 4, True), (300, 320, 24, 32, 5, True),
+                                               (777, 192, 9, 96, 3, False), (1900, 448, 12, 128, 3, True), (1300, 512, 12, 96, 6, True),
+                                               (1024, 1024, 32, 128, 8, False), (5000, 64, 7, 32, 2, False), (1250, 1024, 20, 64, 5, False),
+                                               (1270, 1024, 20, 64, 5, False)])
+def test_beside_dx(T, d, N, Bs, k, uneven):
+    rng = np.random.default_rng(T)
+    weight = np.where(np.arange(N) % 4 == 1, 1e3, 1.0) if uneven else np.ones(N)
+    ids = np.sort(np.argsort(rng.exponential(size=(T, N)) / weight, axis=1)[:, :k], axis=1).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s, std=1.0: (torch.randn(*s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    shape = spt.make_shape(T, d, N, Bs, k, spt.ACT_RELU)
+    X, dY, W1, W2 = normal(T, d), normal(T, d), normal(N, Bs, d, std=0.05), normal(N, Bs, d, std=0.05)
+    print(f"T {T} d {d} N {N} Bs {Bs} k {k}", flush=True)
+    offsets, perm, inv = spt.bucket_tokens(shape, torch.from_numpy(ids).cuda())
+    _, H = spt.routed_ffn_fwd(shape, X, W1, W2, offsets, perm, inv)
+    outs = []
+    for fill in (0x00, 0xFF):               # whatever a workspace held before
+        ws = spt.alloc_workspace(shape, spt.WS_BWD)
+        ws.fill_(fill)
+        outs.append([x.clone() for x in spt.routed_ffn_bwd(shape, X, W1, W2, dY, offsets, perm, inv, H, ws=ws)])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*outs)), "sums in a fixed order"
+    dX, dW1, dW2 = (o.double().cpu() for o in outs[0])
+    x, dy, w1, w2, h, pos = (t.double().cpu() for t in (X, dY, W1, W2, H, inv.view(T, k)))
+    ref, rounded, mag = (torch.zeros(T, d, dtype=torch.float64) for _ in range(3))
+    for b in range(N):
+        t, j = (torch.from_numpy(y) for y in np.nonzero(ids == b))
+        hb, K = h[pos[t, j].long()], max(len(t), 1)
+        act, dh = hb.clamp(min=0), (dy[t] @ w2[b].T) * (hb > 0)
+        off = 2.0 ** -8 * dh.abs() + 2.0 * d ** 0.5 * 2.0 ** -24 * (dy[t].abs() @ w2[b].abs().T) * (hb > 0)
+        for name, got, left, right, extra in (("dW2", dW2[b], act, dy[t], 0.0), ("dW1", dW1[b], dh, x[t], off.T @ x[t].abs())):
+            want, most = left.T @ right, left.abs().T @ right.abs()
+            bound = extra + 2.0 * K ** 0.5 * 2.0 ** -24 * most + 2.0 ** -23 * want.abs() + 1e-30
+            worst = float(((got - want).abs() / bound).max())
+            assert worst <= 1.0 + 2.0 ** -8, (name, b, K, worst)
+        ref[t] += dh @ w1[b]
+        rounded[t] += off @ w1[b].abs()
+        mag[t] += dh.abs() @ w1[b].abs()
+    bound = 2.0 ** -8 * ref.abs() + (1 + 2.0 ** -8) * rounded + 2.0 * (k * Bs) ** 0.5 * 2.0 ** -24 * mag + 1e-30
+    assert float(((dX - ref).abs() / bound).max()) <= 1.0 + 2.0 ** -8
