@@ -352,7 +352,7 @@ __global__ __launch_bounds__(1024) void topl_lane_kernel(const uint8_t* __restri
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       const uint32_t e = (cw[m >> 2] >> (8 * (m & 3))) & 15u;
-      atomicOr(table + (m * 16 + e) * nwp + (j >> 5), 1u << (j & 31));
+      atomicOr(table + __umul24(m * 16 + e, nwp) + (j >> 5), 1u << (j & 31));
     }
   }
   const int wave = tid >> 6, lane = tid & 63, part = lane % P;
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(1024) void topl_lane_kernel(const uint8_t* __restri
     for (int w = 0; w < M / 4; ++w) cw[w] = qsrc[w];
 #pragma unroll
     for (int m = 0; m < M; ++m)
-      off[m] = (m * 16 + (int)(cw[m >> 2] >> (8 * (m & 3)) & 15u)) * nwp + part * (2 * pairs);
+      off[m] = (int)__umul24(m * 16 + (cw[m >> 2] >> (8 * (m & 3)) & 15u), nwp) + part * (2 * pairs);
   }
   __syncthreads();
 
@@ -467,21 +467,42 @@ __global__ __launch_bounds__(1024) void topl_lane_kernel(const uint8_t* __restri
   // stage -> idx: the wavefront's rows are one contiguous run of the output, written 64 neighbouring words at a time
   const int rows = min(QW, n - q0);
   if (rows <= 0) return;
-  const uint32_t items = rows * L;
-  const uint32_t magic = 0xFFFFFFFFu / (uint32_t)L + 1u;   // it / L = mulhi(it, magic): it < 2^14, L <= 2^8 (L = 1: it)
-  const uint16_t* from = reinterpret_cast<const uint16_t*>(mystage);
-  int32_t* dst = idx + ((size_t)s * n + q0) * L;
-  for (uint32_t it0 = lane; it0 < items; it0 += 64 * 8) {
-    uint32_t key[8];
+  // (keys are below 2^12, none is 0xFFFF: sign extension makes it -1.  Pieces of one key, or of two where a row holds a whole number of them.  A step is 64
+  // pieces on: `down` rows and `right` pieces, and a row more where that leaves the row.  Division by L, three products of 32 bits for every key: 50 us where
+  // this takes TOPL_A, S 512, n 512, 8 codebooks, L 64.)
+  auto write_out = [&](auto keys) {
+    constexpr int K = decltype(keys)::value;
+    typedef std::conditional_t<K == 2, uint32_t, uint16_t> Staged;
+    const int per = L / K, items = rows * per, down = 64 / per, right = 64 - down * per;
+    const Staged* from = reinterpret_cast<const Staged*>(mystage);
+    const int stride = lw * 2 / K, step = down * stride + right, wrap = stride - per;
+    int col = lane % per, at = lane / per * stride + col;
+    int32_t* dst = idx + ((size_t)s * n + q0) * L;
+    for (int it0 = lane; it0 < items; it0 += 64 * 8) {
+      uint32_t key[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const uint32_t it = min(it0 + u * 64, items - 1), r = L == 1 ? it : __umulhi(it, magic);
-      key[u] = from[r * (2 * lw) + (it - r * L)];
+      for (int u = 0; u < 8; ++u) {
+        key[u] = from[it0 + u * 64 < items ? at : 0];
+        col += right;
+        at += step;
+        const bool over = col >= per;
+        at += over ? wrap : 0;
+        col -= over ? per : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (it0 + u * 64 < items) {
+          if constexpr (K == 2) {
+            typedef int i32x2u __attribute__((ext_vector_type(2), aligned(4)));
+            reinterpret_cast<i32x2u*>(dst)[it0 + u * 64] = i32x2u{(int)(key[u] << 16) >> 16, (int)key[u] >> 16};
+          } else {
+            dst[it0 + u * 64] = (int16_t)key[u];
+          }
+        }
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (it0 + u * 64 < items) dst[it0 + u * 64] = key[u] == 0xFFFFu ? -1 : (int32_t)key[u];
-  }
+  };
+  if (L & 1) write_out(std::integral_constant<int, 1>{});
+  else       write_out(std::integral_constant<int, 2>{});
 }
 
 // ---------------------------------------------------------------- Algorithm 1, lines 4-5 and their backward
