@@ -469,7 +469,7 @@ __global__ __launch_bounds__(1024) void topl_lane_kernel(const uint8_t* __restri
   if (rows <= 0) return;
   // (keys are below 2^12, none is 0xFFFF: sign extension makes it -1.  Pieces of one key, or of two where a row holds a whole number of them.  A step is 64
   // pieces on: `down` rows and `right` pieces, and a row more where that leaves the row.  Division by L, three products of 32 bits for every key: 50 us where
-  // this takes TOPL_A, S 512, n 512, 8 codebooks, L 64.)
+  // this takes 48, S 512, n 512, 8 codebooks, L 64.)
   auto write_out = [&](auto keys) {
     constexpr int K = decltype(keys)::value;
     typedef std::conditional_t<K == 2, uint32_t, uint16_t> Staged;

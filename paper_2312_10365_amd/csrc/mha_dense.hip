@@ -76,6 +76,27 @@ __device__ __forceinline__ float max_mag(float m, float x, float y) {
   return m;
 }
 
+// 4 x 4 transpose of 16-byte pieces over four lanes in a row: piece j of lane q becomes piece q of lane j.
+template <int CTRL>
+__device__ __forceinline__ void quad_exchange(bf16x8& pa, bf16x8& pb, bool second) {   // a of the second lane of a pair for b of the first
+  u32x4 a = __builtin_bit_cast(u32x4, pa), b = __builtin_bit_cast(u32x4, pb);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t from_b = (uint32_t)__builtin_amdgcn_mov_dpp((int)b[e], CTRL, 0xF, 0xF, true);
+    const uint32_t from_a = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[e], CTRL, 0xF, 0xF, true);
+    a[e] = second ? from_b : a[e];
+    b[e] = second ? b[e] : from_a;
+  }
+  pa = as_bf16x8(a);
+  pb = as_bf16x8(b);
+}
+__device__ __forceinline__ void quad_transpose(bf16x8* x, uint32_t lane) {
+  quad_exchange<0xB1>(x[0], x[1], lane & 1);
+  quad_exchange<0xB1>(x[2], x[3], lane & 1);
+  quad_exchange<0x4E>(x[0], x[2], lane & 2);
+  quad_exchange<0x4E>(x[1], x[3], lane & 2);
+}
+
 // One weight on its way to the tile: the first two parts in a word, the third for itself.
 __device__ __forceinline__ float split_weight(float w, uint16_t& third) {
   const float r = less_upper_half(w);
@@ -216,14 +237,27 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL, STAT>())) voi
   for (int ct = 0; ct < CT; ++ct) vtr[ct] = tr_offset<DH>(lane, cg * CT + ct);
 
   bf16x8 kf[KT][KS];
+  // (!STAT: four lanes in a row, which want four rows, request 64 adjacent bytes of each of them in turn and exchange the 16-byte pieces
+  // afterwards: pieces of one line that four such lanes ask for cost a quarter of pieces of four lines.  us, forward / backward, before and now: S 96,
+  // n 1100, L 137, 128-wide 251 / 255, 234 / 238; S 64, n 1024, L 200, 64-wide 85 / 84, 81 / 79.  128-wide heads exchange in front of the products, 64-wide
+  // ones at once: the other way round 239 / 242 and 84 / 84.)
+  auto order_k = [&](int from, int to) {
+#pragma unroll
+    for (int t = from; t < to; ++t)
+#pragma unroll
+      for (int k = 0; k < KS; k += 4) quad_transpose(&kf[t][k], lane);
+  };
   auto load_k = [&](uint32_t c0) {
 #pragma unroll
-    for (int t = 0; t < KT; ++t) {
-      // (padding keys: any row, their words are never read)
-      const uint32_t key = min(c0 + (wave * KT + t) * 32 + rho32(i), (uint32_t)n - 1);
+    for (int t = 0; t < KT; ++t)
 #pragma unroll
-      for (int k = 0; k < KS; ++k) kf[t][k] = as_bf16x8(load_at<u32x4>(g1, key * (DH * 2) + h * DH + k * 16));
-    }
+      for (int k = 0; k < KS; ++k) {
+        // (padding keys: any row, their words are never read)
+        const uint32_t row = STAT ? i : (i & ~3u) + k % 4, piece = STAT ? (uint32_t)k : k / 4 * 4 + (lane & 3);
+        const uint32_t key = min(c0 + (wave * KT + t) * 32 + rho32(row), (uint32_t)n - 1);
+        kf[t][k] = as_bf16x8(load_at<u32x4>(g1, key * (DH * 2) + h * DH + piece * 16));
+      }
+    if (!STAT && DH == 64) order_k(0, KT);
   };
   // G2 rows c0 .. c0 + kc of the sequence into the tile's space; `mag`: largest magnitude so far.
   u16x2 mag = {0, 0};
@@ -381,6 +415,7 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL, STAT>())) voi
         f32x16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        if (!STAT && DH == 128) order_k(t, t + 1);
 #pragma unroll
         for (int k = 0; k < KS; ++k) {
           const bf16x8 rf = as_bf16x8(*reinterpret_cast<const u32x4*>(rlds + i * RSTRIDE + h * DH + k * 16));
