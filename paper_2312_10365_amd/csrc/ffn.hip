@@ -333,63 +333,15 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
 //   MODE 0 (forward, Alg. 4 line 4):  Hsave = Xg W1_b^T,  Hact = act(Hsave)
 //   MODE 1 (backward):  dHpre = (dYg W2_b^T) * act'(Hsave),  Hact = act(Hsave)
 // Hsave is row-major [P, Bs] (it crosses the ABI); Hact and dHpre are in fragment order (hfrag_off).
-// C[u][q] is computed with hidden units as MFMA rows, so a lane holds hidden units of ITS bucket row q.  The
-// gathered rows and the weight block go through an LDS ring (global_load_lds_dwordx4, the gather folded into the copy
-// addresses).  The kernel is bound by bytes entering the CU.  The K = Bs contraction that follows
-// (down-projection, dX) is the token-range-stationary kernel of ffn_scatter.hip.
-// Two tilings: 256 rows, eight wavefronts, one workgroup per CU (ffn_up_pair_kernel); and, where that would leave CUs
-// without a tile, 64 rows, two wavefronts of 32 rows each, three workgroups per CU (ffn_up_kernel).
-constexpr int KD_KT = 32;         // K values per stage of the 64-row tiles
-constexpr int FU_ROWS_FEW = 64;   // ... where 256-row tiles would leave CUs without one
+// C[u][q] is computed with hidden units as MFMA rows, so a lane holds hidden units of ITS bucket row q.  The K = Bs contraction that
+// follows (down-projection, dX) is the token-range-stationary kernel of ffn_scatter.hip.
+// Two kernels: tiles of 256 rows, eight wavefronts, one workgroup per CU, the gathered rows and the weight block through an LDS ring
+// (global_load_lds_dwordx4, the gather folded into the copy addresses), bound by bytes entering the CU
+// (ffn_up_pair_kernel); and, where those would leave CUs without a tile, 32 hidden units x 64 rows a workgroup, operands straight into
+// registers (ffn_up_few_rows_kernel).
+constexpr int FU_ROWS_FEW = 64;   // rows of a tile where 256-row tiles would leave CUs without one
 
-template <int KS>
-struct UpTile {
-  static constexpr int SLOTS = 4;
-  static constexpr int UNITS = KS * 16;                           // weight rows of a stage
-  static constexpr int STAGE_SLOTS = (UNITS + FU_ROWS_FEW) * 4;   // 16-byte slots of a stage (12 KiB at 128 units)
-  static constexpr int SMEM = SLOTS * STAGE_SLOTS * 16;
-};
-
-// Epilogue of a 32-row tile: lane (i, h) holds, for row q, units 32 mi + 8 g + 4 h + e in c[mi][4 g + e].
-template <int MODE, int ACT, int MI>
-__device__ __forceinline__ void up_store(const f32x16 (&c)[MI], int q, int q0, int qend, int h, int Bs,
-                                         uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact,
-                                         uint16_t* __restrict__ dHpre) {
-  const bool live = q < qend;
-  const int ql = live ? q : q0;
-#pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int u = mi * 32 + 8 * g + 4 * h;
-      const size_t off = (size_t)ql * Bs + u;           // Hsave: row-major
-      const size_t foff = hfrag_off(ql, u, Bs);         // Hact, dHpre
-      const float c0 = c[mi][4 * g], c1 = c[mi][4 * g + 1], c2 = c[mi][4 * g + 2], c3 = c[mi][4 * g + 3];
-      if (MODE == 0) {
-        if (live) {
-          if (Hsave) *reinterpret_cast<uint2*>(Hsave + off) = make_uint2(pack_bf16x2(c0, c1), pack_bf16x2(c2, c3));
-          *reinterpret_cast<uint2*>(Hact + foff) =
-              make_uint2(pack_bf16x2(act_fn<ACT>(c0), act_fn<ACT>(c1)), pack_bf16x2(act_fn<ACT>(c2), act_fn<ACT>(c3)));
-        }
-      } else {
-        const uint2 hp = *reinterpret_cast<const uint2*>(Hsave + off);
-        const float z0 = lo_bf16(hp.x), z1 = hi_bf16(hp.x), z2 = lo_bf16(hp.y), z3 = hi_bf16(hp.y);
-        if (live) {
-          *reinterpret_cast<uint2*>(dHpre + foff) =
-              make_uint2(pack_bf16x2(c0 * act_grad<ACT>(z0), c1 * act_grad<ACT>(z1)),
-                         pack_bf16x2(c2 * act_grad<ACT>(z2), c3 * act_grad<ACT>(z3)));
-          *reinterpret_cast<uint2*>(Hact + foff) =
-              make_uint2(pack_bf16x2(act_fn<ACT>(z0), act_fn<ACT>(z1)), pack_bf16x2(act_fn<ACT>(z2), act_fn<ACT>(z3)));
-        }
-      }
-    }
-    // keep the scheduler from interleaving the 16-value groups: their erf evaluations
-    // would otherwise all be in flight at once and spill
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// The same where the hidden units went through rho32: units 32 (first + mi) + 16 h + (0..15) in c[mi], stored as 32-byte
+// Epilogue of a 32-row tile whose hidden units went through rho32: units 32 (first + mi) + 16 h + (0..15) in c[mi], stored as 32-byte
 // runs; only the first `many` of the tiles are (all of them where that is a constant, which costs nothing).
 template <int MODE, int ACT, int MI>
 __device__ __forceinline__ void up_store_runs(const f32x16 (&c)[MI], int q, int q0, int qend, int first, int many, int h,
@@ -442,128 +394,6 @@ __device__ __forceinline__ void up_store_runs(const f32x16 (&c)[MI], int q, int 
       // flight at once and spill
       __builtin_amdgcn_sched_barrier(0);
     }
-  }
-}
-
-template <int MODE, int ACT, int KS>
-__global__ __launch_bounds__(128, 2) void ffn_up_kernel(
-    const uint16_t* __restrict__ Wa, const uint16_t* __restrict__ Act,
-    const int32_t* __restrict__ offsets, const int32_t* __restrict__ kd_count,
-    const KdTile* __restrict__ kd_list, int cap, const int32_t* __restrict__ tok, int Bs, int d,
-    uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact, uint16_t* __restrict__ dHpre,
-    const uint16_t* __restrict__ Xe, const uint16_t* __restrict__ We) {
-  constexpr int MI = KS / 2;   // 32-unit tiles of the block
-  typedef UpTile<KS> Tile;
-  constexpr int SLOTS = Tile::SLOTS, STAGE = Tile::STAGE_SLOTS;
-  constexpr int NA = MI, NB = 2, NP = NA + NB;   // a wavefront's copies per stage: weights, rows, all
-  extern __shared__ uint4 fu_smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)fu_smem;
-  // Low-rank adapters (section 2.2) enter as two more K-stages: 64 extra K-values per
-  // gathered row (Xe[token][64]) and per hidden unit (We[unit][64]).
-  const int nkd = d / KD_KT;
-  const int nk = nkd + (Xe ? 2 : 0);
-  const int xcd = blockIdx.x & 7, wg_per_xcd = gridDim.x >> 3;
-  const int count = kd_count[xcd];
-  const int i = lane & 31, h = lane >> 5;
-  for (int slot_id = blockIdx.x >> 3; slot_id < count; slot_id += wg_per_xcd) {
-    const KdTile tile = kd_list[(size_t)xcd * cap + slot_id];
-    const int b = tile.bucket, q0 = tile.q0;
-    const int qend = offsets[b + 1];
-    __builtin_amdgcn_s_barrier();  // LDS of the previous tile is free
-
-    // DMA: a stage is the block's weight rows + the tile's gathered rows of 64 bytes (32 K-values);
-    // an instruction moves 16 rows; this wavefront issues NA + NB of them per stage.
-    // Lane L of instruction j fills row 16 j + L / 4, physical chunk L % 4 = logical ^ swizzle.
-    // (the swizzle term (row >> 2) & 3 is (lane >> 4) & 3 for every instruction: the rows an
-    // instruction covers start at a multiple of 16)
-    const int ch8 = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;
-    int urow[NA], apiece[NA], tq[NB];  // hidden unit / token id of this lane's row in each instruction
-#pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      apiece[j] = wave * NA + j;
-      urow[j] = b * Bs + apiece[j] * 16 + (lane >> 2);
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int row = (wave * NB + j) * 16 + (lane >> 2);
-      tq[j] = tok[(q0 + row < qend) ? q0 + row : q0];
-    }
-    // (row addresses are formed once per tile: a 64-bit multiply per copy in the K loop sits on
-    // the path between the barrier and the fragment reads)
-    const uint16_t* arow[NA];
-    const uint16_t* brow[NB];
-#pragma unroll
-    for (int j = 0; j < NA; ++j) arow[j] = Wa + (size_t)urow[j] * d + ch8;
-#pragma unroll
-    for (int j = 0; j < NB; ++j) brow[j] = Act + (size_t)tq[j] * d + ch8;
-    // copy `piece` (0 .. NA-1: weight rows; then gathered rows) of K-stage kt into ring slot `stage`
-    auto issue_piece = [&](int stage, int kt, int piece) {
-      const uint32_t base = lds0 + (uint32_t)(stage * STAGE) * 16u;
-      const bool ext = kt >= nkd;  // wave-uniform
-      if (piece < NA) {
-        const int j = piece;
-        dma16(ext ? We + (size_t)urow[j] * (2 * KD_KT) + ch8 + (kt - nkd) * KD_KT : arow[j] + kt * KD_KT,
-              __builtin_amdgcn_readfirstlane(base + (uint32_t)(apiece[j] * 64) * 16u));
-      } else {
-        const int j = piece - NA;
-        dma16(ext ? Xe + (size_t)tq[j] * (2 * KD_KT) + ch8 + (kt - nkd) * KD_KT : brow[j] + kt * KD_KT,
-              __builtin_amdgcn_readfirstlane(base + (uint32_t)(Tile::UNITS * 4 + (wave * NB + j) * 64) * 16u));
-      }
-    };
-
-    f32x16 acc[MI];
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[mi][v] = 0.f;
-    // Ring schedule: "issue j" copies K-stage min(j, nk-1) into slot j % SLOTS; past the last stage it
-    // repeats it into a slot nobody reads any more, so the loop body has no branch and every
-    // vmcnt wait is a constant.  Issues 0 .. SLOTS-2 go out up front, iteration kt sends issue kt+SLOTS-1
-    // piece by piece behind its first MFMAs (the slot stage kt-1 left at the barrier).
-    const int klast = nk - 1;
-#pragma unroll
-    for (int st = 0; st < SLOTS - 1; ++st)
-#pragma unroll
-      for (int p = 0; p < NP; ++p) issue_piece(st, klast < st ? klast : st, p);
-    int stage = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-      // own copies of stage kt have landed (those of the SLOTS-2 stages after it may still be in flight) ...
-      wait_vmcnt<NP * (SLOTS - 2)>();
-      __builtin_amdgcn_s_barrier();  // ... and everyone's; all are done reading stage kt-1
-      const int fill = stage >= 1 ? stage - 1 : SLOTS - 1;
-      const int kfill = kt + SLOTS - 1 < klast ? kt + SLOTS - 1 : klast;
-      const uint4* As = fu_smem + stage * STAGE;
-      const uint4* Bt = As + Tile::UNITS * 4;
-      // all fragment reads of the stage go out first, so the MFMAs of the first K-step run
-      // while the second K-step's fragments are still arriving (the compiler left to itself
-      // sinks each read next to its use and exposes the LDS latency every few MFMAs)
-      bf16x8 a[KD_KT / 16][MI], bb[KD_KT / 16];
-#pragma unroll
-      for (int s = 0; s < KD_KT / 16; ++s) {
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) a[s][mi] = as_bf16x8(As[kd_slot(mi * 32 + i, 2 * s + h)]);
-        bb[s] = as_bf16x8(Bt[kd_slot(wave * 32 + i, 2 * s + h)]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int s = 0; s < KD_KT / 16; ++s)
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) {
-          acc[mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][mi], bb[s], acc[mi], 0, 0, 0);
-          const int m = s * MI + mi;
-          if (m < NP) {
-            issue_piece(fill, kfill, m);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-#pragma unroll
-      for (int m = (KD_KT / 16) * MI; m < NP; ++m) issue_piece(fill, kfill, m);  // (small blocks: fewer MFMAs than copies)
-      __builtin_amdgcn_sched_barrier(0);
-      stage = (stage == SLOTS - 1) ? 0 : stage + 1;
-    }
-    wait_vmcnt<0>();  // the trailing copies (repeats of the last stage) are done too
-    up_store<MODE, ACT, MI>(acc, q0 + wave * 32 + i, q0, qend, h, Bs, Hsave, Hact, dHpre);
   }
 }
 
@@ -817,59 +647,74 @@ __global__ __launch_bounds__(512, 2) void ffn_up_pair_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// The same forward GEMM where a bucket holds a handful of rows (decoding batches): every weight is read
-// for few multiply-adds, so the launch is bound by streaming W1 and wants bytes in flight on all CUs, not
-// tiles.  A workgroup owns 32 hidden units of one block and one row tile of its bucket, 32 RT rows at a time; its four
-// wavefronts split d in chunks of 32 and load both operands straight into registers, chunks ahead
-// (a lane reads 32 contiguous bytes of a row; which K-values share an MFMA slot is the same for both
-// operands, which is all a contraction needs).  The wavefronts' sums are added through LDS in order.
-// 7B-like layer, 24 tokens (6 rows a bucket): 32 us, with 256-row tiles 69 (128 of 256 CUs, one K-stage per
-// memory latency).
-// The row tiles come from the schedule's lists, as those of the tile kernels do: the mean says little about a single
+// The same GEMMs where 256-row tiles would leave CUs without one: decoding batches, where every weight is read for few
+// multiply-adds, and small layers, where a tile's K loop is a chain of memory latencies.  Both want bytes in flight on all
+// CUs.  A workgroup owns 32 hidden units of one block and one row tile of at most 64 rows of its bucket, 32 RT rows at a time; its four
+// wavefronts split d in chunks of 64 values and load both operands straight into registers, a chunk ahead.  The
+// wavefronts' sums are added through LDS in order.
+// A lane multiplies values of one row, but four lanes in a row, which want four rows, request 64 adjacent bytes of each of them
+// in turn and exchange the 16-byte pieces afterwards (quad_transpose): four pieces of one line cost what one piece of each of four lines
+// costs four times.  us, 24 and 100 tokens of the 7B-like layer (6 and 25 rows a bucket): each lane its own row 25, 51; this 17, 28.
+// (Which layers take it, and both sides of the line: few_rows.)
+// The row tiles come from the schedule's lists, as those of the tile kernel do: the mean says little about a single
 // bucket.  8192 tokens, 256 blocks of 128 units, d 2048, k 1, half of the tokens in one block: 220 us, with a
 // workgroup per bucket and 32 units 2834.
-template <int ACT, int RT>
+template <int MODE, int ACT, int RT, bool EXT>
 __global__ __launch_bounds__(256) void ffn_up_few_rows_kernel(
-    const uint16_t* __restrict__ W1, const uint16_t* __restrict__ X, const int32_t* __restrict__ offsets,
+    const uint16_t* __restrict__ Wa, const uint16_t* __restrict__ Act, const int32_t* __restrict__ offsets,
     const int32_t* __restrict__ kd_count, const KdTile* __restrict__ kd_list, int cap,
-    const int32_t* __restrict__ tok, int Bs, int d, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact) {
-  constexpr int DEPTH = 4;                       // chunks in registers, DEPTH - 1 of them in flight (8: no faster)
+    const int32_t* __restrict__ tok, int Bs, int d, uint16_t* __restrict__ Hsave, uint16_t* __restrict__ Hact,
+    uint16_t* __restrict__ dHpre, const uint16_t* __restrict__ Xe, const uint16_t* __restrict__ We) {
+  constexpr int DEPTH = 2;                       // chunks in registers, one of them in flight (3 or 4, less of them on a CU: 17 -> 18, 28 -> 31)
   __shared__ float red[4][RT][16][64];
   // (the unit slices of a tile side by side; workgroups that find the list at its end are the last ones handed out)
   const int slices = Bs / 32, xcd = blockIdx.x & 7, per_xcd = (int)(gridDim.x >> 3) / slices, count = kd_count[xcd];
   const int u0 = (int)(blockIdx.x >> 3) % slices * 32;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int i = lane & 31, h = lane >> 5;
-  const int chunks = d / 32, cbeg = wave * chunks / 4, cend = (wave + 1) * chunks / 4, clast = cend - 1;
+  const int i = lane & 31, h = lane >> 5, at = 32 * h + 8 * (lane & 3);   // the lane's piece of a chunk
+  const int chunks = d / 64, cbeg = wave * chunks / 4, cend = (wave + 1) * chunks / 4, clast = cend - 1;
   for (int slot = (int)(blockIdx.x >> 3) / slices; slot < count; slot += per_xcd) {
     const KdTile tile = kd_list[(size_t)xcd * cap + slot];
     const int qe = min(tile.q0 + tile.rows, offsets[tile.bucket + 1]);
-    const uint16_t* wrow = W1 + ((size_t)tile.bucket * Bs + u0 + rho32(i)) * d + 16 * h;
-    for (int q0 = tile.q0; q0 < qe; q0 += 32 * RT) {
-      const uint16_t* xrow[RT];
+    const size_t unit0 = (size_t)tile.bucket * Bs + u0;
+    const uint16_t* wrow[4];                     // rows of the lane's group of four
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) xrow[rt] = X + (size_t)tok[min(q0 + rt * 32 + i, qe - 1)] * d + 16 * h;
+    for (int j = 0; j < 4; ++j) wrow[j] = Wa + (unit0 + rho32((i & ~3) + j)) * d + at;
+    for (int q0 = tile.q0; q0 < qe; q0 += 32 * RT) {
+      int tokens[RT][4];
+      const uint16_t* xrow[RT][4];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) tokens[rt][j] = tok[min(q0 + rt * 32 + (i & ~3) + j, qe - 1)];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) xrow[rt][j] = Act + (size_t)tokens[rt][j] * d + at;
       f32x16 acc[RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[rt][v] = 0.f;
-      uint4 wq[DEPTH][2], xq[DEPTH][RT][2];
+      bf16x8 wq[DEPTH][4], xq[DEPTH][RT][4];
       auto fetch = [&](int st, int c) {
-        const int k0 = min(c, clast) * 32;       // (requests past the last chunk repeat it: no branch around a load)
+        const int k0 = min(c, clast) * 64;       // (requests past the last chunk repeat it: no branch around a load)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          wq[st][s] = *reinterpret_cast<const uint4*>(wrow + k0 + 8 * s);
+        for (int s = 0; s < 4; ++s) {
+          wq[st][s] = as_bf16x8(*reinterpret_cast<const uint4*>(wrow[s] + k0));
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) xq[st][rt][s] = *reinterpret_cast<const uint4*>(xrow[rt] + k0 + 8 * s);
+          for (int rt = 0; rt < RT; ++rt) xq[st][rt][s] = as_bf16x8(*reinterpret_cast<const uint4*>(xrow[rt][s] + k0));
         }
       };
       auto consume = [&](int st) {
+        quad_transpose(wq[st], lane);
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int rt = 0; rt < RT; ++rt) quad_transpose(xq[st][rt], lane);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt)
-            acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(wq[st][s]), as_bf16x8(xq[st][rt][s]), acc[rt], 0, 0, 0);
+            acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wq[st][s], xq[st][rt][s], acc[rt], 0, 0, 0);
       };
       if (cbeg < cend) {
 #pragma unroll
@@ -886,22 +731,44 @@ __global__ __launch_bounds__(256) void ffn_up_few_rows_kernel(
         for (int s = 0; s < DEPTH - 1; ++s)
           if (c + s < cend) consume(s);
       }
+      if (EXT && wave == 3) {                    // low-rank adapters: 64 more values of every row, and one chunk more
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          wq[0][s] = as_bf16x8(*reinterpret_cast<const uint4*>(We + (unit0 + rho32((i & ~3) + s)) * 64 + at));
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) xq[0][rt][s] = as_bf16x8(*reinterpret_cast<const uint4*>(Xe + (size_t)tokens[rt][s] * 64 + at));
+        }
+        consume(0);
+      }
+      // wavefront w finishes accumulators 4 w .. 4 w + 3: hidden units u0 + 16 h + 4 w .. + 3 of the lane's row
+      const int u = u0 + 16 * h + 4 * wave;
+      uint2 zsave[RT];
+      if (MODE)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) zsave[rt] = *reinterpret_cast<const uint2*>(Hsave + (size_t)min(q0 + rt * 32 + i, qe - 1) * Bs + u);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) red[wave][rt][v][lane] = acc[rt][v];
       __syncthreads();
-      // wavefront w finishes accumulators 4 w .. 4 w + 3: hidden units u0 + 16 h + 4 w .. + 3 of the lane's row
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        const int q = q0 + rt * 32 + i, u = u0 + 16 * h + 4 * wave;
+        const int q = q0 + rt * 32 + i;
         float z[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           z[e] = ((red[0][rt][4 * wave + e][lane] + red[1][rt][4 * wave + e][lane]) + red[2][rt][4 * wave + e][lane]) +
                  red[3][rt][4 * wave + e][lane];
         if (q < qe) {
-          if (Hsave) *reinterpret_cast<uint2*>(Hsave + (size_t)q * Bs + u) = make_uint2(pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3]));
+          if (MODE) {
+            const float h0 = lo_bf16(zsave[rt].x), h1 = hi_bf16(zsave[rt].x), h2 = lo_bf16(zsave[rt].y), h3 = hi_bf16(zsave[rt].y);
+            *reinterpret_cast<uint2*>(dHpre + hfrag_off(q, u, Bs)) =
+                make_uint2(pack_bf16x2(z[0] * act_grad<ACT>(h0), z[1] * act_grad<ACT>(h1)),
+                           pack_bf16x2(z[2] * act_grad<ACT>(h2), z[3] * act_grad<ACT>(h3)));
+            z[0] = h0; z[1] = h1; z[2] = h2; z[3] = h3;
+          } else if (Hsave) {
+            *reinterpret_cast<uint2*>(Hsave + (size_t)q * Bs + u) = make_uint2(pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3]));
+          }
           *reinterpret_cast<uint2*>(Hact + hfrag_off(q, u, Bs)) =
               make_uint2(pack_bf16x2(act_fn<ACT>(z[0]), act_fn<ACT>(z[1])), pack_bf16x2(act_fn<ACT>(z[2]), act_fn<ACT>(z[3])));
         }
@@ -991,21 +858,18 @@ static int max_row_tiles(const spt_shape_t& s, int rows) {
 
 static bool use_narrow(const spt_shape_t& s) { return s.Bs <= TILE; }
 
-// Rows of a K = d tile: 256, or 64 (narrow blocks) where 256-row tiles of mean buckets would occupy fewer than half
-// the CUs.  us, 256 against 64 rows: 64 tiles (T 3053, d 1088, N 16) 30, 21; 128 tiles 55, 54 (T 2000, d 2048,
-// N 64) and 85, 95 (T 1000, d 4096, N 128); 213 tiles 26, 32.
-static int kd_rows(const spt_shape_t& s) {
-  const int64_t mean = ((int64_t)s.T * s.k + s.N - 1) / s.N;
-  return use_narrow(s) && (mean + FU_ROWS - 1) / FU_ROWS * s.N < 128 ? FU_ROWS_FEW : FU_ROWS;
-}
-
-// Few rows per bucket on average: a decoding batch.  Measured up-projection, us, 256-row tiles against this: 7B-like
-// layer, 16 rows 70, 47; 32 rows 75, 66; 64 rows 76, 112; layers with no more than one workgroup per CU gain up
-// to 64 rows (d 2048, N 64: 40, 30; 128 rows: 40, 46).
+// Narrow blocks: tiles of 64 rows, and the kernel that loads its operands straight into registers, where those are at most a workgroup (32 hidden
+// units each) per CU for mean buckets, or a bucket has few rows and the weights are what is read.  us, up-projection and dH
+// together, 256-row tiles (and their parts) against this: d 4096, 16 blocks of 128, 128 rows 41.2, 30.6; 256 rows 41.7, 42.3; 512 rows 44, 63;
+// d 768, 32 of 96, 48 rows 17.7, 13.3; 180 rows 19.7, 18.7; 512 rows 24.1, 29.9; d 1024, 32 of 128, 80 rows 20.1, 14.7; 256 rows 21.6, 28.5; d 256, 16
+// of 64, 128 rows 11.5, 10.1; d 4096, 128 of 128, 6 rows 68, 59; 48 rows 73, 71; 64 rows 79, 92; d 320, 128 of 128, 23 rows 14.3, 11.4; 47 rows 16.5, 20.2.
+// (Until both were measured with whole lines requested, a third kernel had the layers between: 64-row tiles through LDS, 81, 81, 82; 21, 25, 31; 30, 32;
+// 12.4.)
 static bool few_rows(const spt_shape_t& s) {
-  const int64_t P = (int64_t)s.T * s.k;
-  return P <= 40 * (int64_t)s.N || (P <= 64 * (int64_t)s.N && s.N * (s.Bs / 32) <= 256);
+  const int64_t P = (int64_t)s.T * s.k, mean = (P + s.N - 1) / s.N;
+  return use_narrow(s) && (P <= 32 * (int64_t)s.N || (mean + FU_ROWS_FEW - 1) / FU_ROWS_FEW * s.N * (s.Bs / 32) <= 256);
 }
+static int kd_rows(const spt_shape_t& s) { return few_rows(s) ? FU_ROWS_FEW : FU_ROWS; }
 
 static size_t carve_schedule(const spt_shape_t& s, char* p, size_t o0, Schedule& sc, bool weight_grads = false) {
   const size_t P = (size_t)s.T * s.k;
@@ -1157,36 +1021,36 @@ template <int MODE, int ACT, int KS>
 static hipError_t launch_up_t(const spt_shape_t& s, const uint16_t* Wa, const uint16_t* Act,
                               const int32_t* offsets, const Schedule& sc, uint16_t* Hsave, uint16_t* Hact,
                               uint16_t* dHpre, hipStream_t st, const uint16_t* Xe, const uint16_t* We) {
-  static const hipError_t attr[3] = {
-      hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_kernel<MODE, ACT, KS>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, UpTile<KS>::SMEM),
+  static const hipError_t attr[2] = {
       hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_pair_kernel<MODE, ACT, KS, false>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, UpPair<KS>::SMEM),
       hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_up_pair_kernel<MODE, ACT, KS, true>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, UpPair<KS>::SMEM)};
-  const bool few = kd_rows(s) == FU_ROWS_FEW;
-  const hipError_t e = attr[few ? 0 : Xe ? 2 : 1];
+  const hipError_t e = attr[Xe ? 1 : 0];
   if (e != hipSuccess) return e;
-  const int most = few ? 96 : 32;     // three workgroups per CU, or one
-  const int grid = 8 * (sc.kd_cap < most ? sc.kd_cap : most);
+  const int grid = 8 * (sc.kd_cap < 32 ? sc.kd_cap : 32);
   const KdTile* list = static_cast<const KdTile*>(sc.kd_list);
 #define SPT_UP_ARGS Wa, Act, offsets, sc.kd_count, list, sc.kd_cap, sc.tok, s.Bs, s.d, Hsave, Hact, dHpre, Xe, We
-  if (few) ffn_up_kernel<MODE, ACT, KS><<<grid, 128, UpTile<KS>::SMEM, st>>>(SPT_UP_ARGS);
-  else if (Xe) ffn_up_pair_kernel<MODE, ACT, KS, true><<<grid, 512, UpPair<KS>::SMEM, st>>>(SPT_UP_ARGS);
-  else ffn_up_pair_kernel<MODE, ACT, KS, false><<<grid, 512, UpPair<KS>::SMEM, st>>>(SPT_UP_ARGS);
-#undef SPT_UP_ARGS
+  if (Xe) ffn_up_pair_kernel<MODE, ACT, KS, true><<<grid, 512, UpPair<KS>::SMEM, st>>>(SPT_UP_ARGS);
+  else    ffn_up_pair_kernel<MODE, ACT, KS, false><<<grid, 512, UpPair<KS>::SMEM, st>>>(SPT_UP_ARGS);
   return hipGetLastError();
 }
 
-// The forward GEMM of a batch with few rows per bucket (see ffn_up_few_rows_kernel).
-static hipError_t launch_up_few_rows(const spt_shape_t& s, const uint16_t* W1, const uint16_t* X, const int32_t* offsets,
-                                     const Schedule& sc, uint16_t* Hsave, uint16_t* Hact, hipStream_t st) {
-  const int grid = (max_row_tiles(s, kd_rows(s)) + 7) / 8 * 8 * (s.Bs / 32);   // (an XCD with more tiles than its share takes more rounds)
+template <int MODE, int ACT>
+static hipError_t launch_up_few_rows(const spt_shape_t& s, const uint16_t* Wa, const uint16_t* Act, const int32_t* offsets,
+                                     const Schedule& sc, uint16_t* Hsave, uint16_t* Hact, uint16_t* dHpre, hipStream_t st,
+                                     const uint16_t* Xe, const uint16_t* We) {
+  const int grid = (sc.kd_cap + 7) / 8 * 8 * (s.Bs / 32);   // (an XCD with more tiles than its share takes more rounds)
+  const KdTile* list = static_cast<const KdTile*>(sc.kd_list);
   const bool one = (int64_t)s.T * s.k <= (int64_t)24 * s.N;
-#define SPT_FEW(ACT, RT) ffn_up_few_rows_kernel<ACT, RT><<<grid, 256, 0, st>>>(W1, X, offsets, sc.kd_count, static_cast<const KdTile*>(sc.kd_list), sc.kd_cap, sc.tok, s.Bs, s.d, Hsave, Hact)
-  if (s.act == SPT_ACT_GELU) { if (one) SPT_FEW(0, 1); else SPT_FEW(0, 2); }
-  else                       { if (one) SPT_FEW(1, 1); else SPT_FEW(1, 2); }
-#undef SPT_FEW
+  if (one) {
+    if (Xe) ffn_up_few_rows_kernel<MODE, ACT, 1, true><<<grid, 256, 0, st>>>(SPT_UP_ARGS);
+    else    ffn_up_few_rows_kernel<MODE, ACT, 1, false><<<grid, 256, 0, st>>>(SPT_UP_ARGS);
+  } else {
+    if (Xe) ffn_up_few_rows_kernel<MODE, ACT, 2, true><<<grid, 256, 0, st>>>(SPT_UP_ARGS);
+    else    ffn_up_few_rows_kernel<MODE, ACT, 2, false><<<grid, 256, 0, st>>>(SPT_UP_ARGS);
+  }
+#undef SPT_UP_ARGS
   return hipGetLastError();
 }
 
@@ -1197,6 +1061,9 @@ static hipError_t launch_up(const spt_shape_t& s, const uint16_t* Wa, const uint
                             const int32_t* offsets, const Schedule& sc, uint16_t* Hsave, uint16_t* Hact,
                             uint16_t* dHpre, hipStream_t st, const uint16_t* Xe = nullptr,
                             const uint16_t* We = nullptr) {
+  if (few_rows(s))
+    return s.act == SPT_ACT_GELU ? launch_up_few_rows<MODE, 0>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We)
+                                 : launch_up_few_rows<MODE, 1>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We);
 #define SPT_UP(ACT, KS)                                                                                                \
   return launch_up_t<MODE, ACT, KS>(s, Wa, Act, offsets, sc, Hsave, Hact, dHpre, st, Xe, We)
 #define SPT_UP_KS(ACT)                    \
@@ -1270,8 +1137,7 @@ hipError_t run_fwd(const spt_shape_t& s, const void* X, const void* W1, const vo
   if (use_narrow(s)) {
     {
       ScopedKernelTimer tm(kSlotUp, st);
-      e = few_rows(s) ? launch_up_few_rows(s, w1, x, offsets, sc, hs, w.Hact, st)
-                      : launch_up<0>(s, w1, x, offsets, sc, hs, w.Hact, nullptr, st);
+      e = launch_up<0>(s, w1, x, offsets, sc, hs, w.Hact, nullptr, st);
     }
     if (e != hipSuccess) return e;
     ScopedKernelTimer tm(kSlotDown, st);

@@ -102,6 +102,27 @@ __device__ __forceinline__ bf16x8 tr_read_frag(const char* lds_lo, const char* l
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const u32x4& v) { return __builtin_bit_cast(bf16x8, v); }
 
+// 4 x 4 transpose of 16-byte pieces over four lanes in a row: piece j of lane q becomes piece q of lane j.
+template <int CTRL>
+__device__ __forceinline__ void quad_exchange(bf16x8& pa, bf16x8& pb, bool second) {   // a of the second lane of a pair for b of the first
+  u32x4 a = __builtin_bit_cast(u32x4, pa), b = __builtin_bit_cast(u32x4, pb);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint32_t from_b = (uint32_t)__builtin_amdgcn_mov_dpp((int)b[e], CTRL, 0xF, 0xF, true);
+    const uint32_t from_a = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[e], CTRL, 0xF, 0xF, true);
+    a[e] = second ? from_b : a[e];
+    b[e] = second ? b[e] : from_a;
+  }
+  pa = as_bf16x8(a);
+  pb = as_bf16x8(b);
+}
+__device__ __forceinline__ void quad_transpose(bf16x8* x, uint32_t lane) {
+  quad_exchange<0xB1>(x[0], x[1], lane & 1);
+  quad_exchange<0xB1>(x[2], x[3], lane & 1);
+  quad_exchange<0x4E>(x[0], x[2], lane & 2);
+  quad_exchange<0x4E>(x[1], x[3], lane & 2);
+}
+
 // Halves of eight words -> an MFMA fragment.
 __device__ __forceinline__ bf16x8 pick_halves(const u32x4& a, const u32x4& b, uint32_t which) {
   return as_bf16x8(u32x4{__builtin_amdgcn_perm(a[1], a[0], which), __builtin_amdgcn_perm(a[3], a[2], which),

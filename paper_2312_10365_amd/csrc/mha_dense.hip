@@ -76,27 +76,6 @@ __device__ __forceinline__ float max_mag(float m, float x, float y) {
   return m;
 }
 
-// 4 x 4 transpose of 16-byte pieces over four lanes in a row: piece j of lane q becomes piece q of lane j.
-template <int CTRL>
-__device__ __forceinline__ void quad_exchange(bf16x8& pa, bf16x8& pb, bool second) {   // a of the second lane of a pair for b of the first
-  u32x4 a = __builtin_bit_cast(u32x4, pa), b = __builtin_bit_cast(u32x4, pb);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t from_b = (uint32_t)__builtin_amdgcn_mov_dpp((int)b[e], CTRL, 0xF, 0xF, true);
-    const uint32_t from_a = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[e], CTRL, 0xF, 0xF, true);
-    a[e] = second ? from_b : a[e];
-    b[e] = second ? b[e] : from_a;
-  }
-  pa = as_bf16x8(a);
-  pb = as_bf16x8(b);
-}
-__device__ __forceinline__ void quad_transpose(bf16x8* x, uint32_t lane) {
-  quad_exchange<0xB1>(x[0], x[1], lane & 1);
-  quad_exchange<0xB1>(x[2], x[3], lane & 1);
-  quad_exchange<0x4E>(x[0], x[2], lane & 2);
-  quad_exchange<0x4E>(x[1], x[3], lane & 2);
-}
-
 // One weight on its way to the tile: the first two parts in a word, the third for itself.
 __device__ __forceinline__ float split_weight(float w, uint16_t& third) {
   const float r = less_upper_half(w);
