@@ -858,16 +858,15 @@ static int max_row_tiles(const spt_shape_t& s, int rows) {
 
 static bool use_narrow(const spt_shape_t& s) { return s.Bs <= TILE; }
 
-// Narrow blocks: tiles of 64 rows, and the kernel that loads its operands straight into registers, where those are at most a workgroup (32 hidden
-// units each) per CU for mean buckets, or a bucket has few rows and the weights are what is read.  us, up-projection and dH
-// together, 256-row tiles (and their parts) against this: d 4096, 16 blocks of 128, 128 rows 41.2, 30.6; 256 rows 41.7, 42.3; 512 rows 44, 63;
-// d 768, 32 of 96, 48 rows 17.7, 13.3; 180 rows 19.7, 18.7; 512 rows 24.1, 29.9; d 1024, 32 of 128, 80 rows 20.1, 14.7; 256 rows 21.6, 28.5; d 256, 16
-// of 64, 128 rows 11.5, 10.1; d 4096, 128 of 128, 6 rows 68, 59; 48 rows 73, 71; 64 rows 79, 92; d 320, 128 of 128, 23 rows 14.3, 11.4; 47 rows 16.5, 20.2.
-// (Until both were measured with whole lines requested, a third kernel had the layers between: 64-row tiles through LDS, 81, 81, 82; 21, 25, 31; 30, 32;
-// 12.4.)
+// Narrow blocks: tiles of 64 rows, and the kernel that loads its operands straight into registers, where those are about two workgroups (32 hidden
+// units each) per CU at most, or a bucket has few rows and the weights are what is read.  us a pass on inputs that change, 256-row tiles (and their
+// parts) / this: training 1024 tokens, d 2048, 16 blocks of 128, 4 each (288 workgroups) 99.3 / 96.8; 300, 4096, 64 of 128, 16 (428) 211 / 202; 1000,
+// 3008, 24 of 96, 8 (411) 150 / 146; 2048, 4096, 16 of 128, 4 (544) 182 / 189; 1500, 768, 32 of 96, 8 (611) 84 / 86; 2048 of those (816) 96 / 102;
+// prefill of the 7B-like layer, 192 tokens (48 rows a bucket) 117 / 115, 256 tokens 126 / 131.
+// (Until both requested whole lines a third kernel had the layers between, 64-row tiles through LDS: 1024 tokens, d 1024, 32 of 128, 8: 109, now 87.)
 static bool few_rows(const spt_shape_t& s) {
-  const int64_t P = (int64_t)s.T * s.k, mean = (P + s.N - 1) / s.N;
-  return use_narrow(s) && (P <= 32 * (int64_t)s.N || (mean + FU_ROWS_FEW - 1) / FU_ROWS_FEW * s.N * (s.Bs / 32) <= 256);
+  const int64_t P = (int64_t)s.T * s.k;
+  return use_narrow(s) && (P <= 48 * (int64_t)s.N || (P + FU_ROWS_FEW / 2 * (int64_t)s.N) / FU_ROWS_FEW * (s.Bs / 32) <= 512);
 }
 static int kd_rows(const spt_shape_t& s) { return few_rows(s) ? FU_ROWS_FEW : FU_ROWS; }
 
