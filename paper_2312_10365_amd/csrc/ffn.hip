@@ -52,7 +52,7 @@ constexpr int kPartAlone[3] = {12 * 32, 7 * 32, 5 * 32}, kPartShare[3] = {20, 13
 struct PlanArgs {
   const int32_t* offsets;
   const int32_t* perm;
-  int N, QT, cap, P, k, wide;
+  int N, QT, cap, P, k, wide, tails;
   int32_t *border, *kd_count;
   KdTile* kd_list;
   uint32_t* zero_row;
@@ -204,10 +204,20 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
   if (!lists) return;
 
   if (p.wide) {
-    const int inc = inclusive_scan(ntq);
-    if (b < N)
-      for (int lvl = 0; lvl < ntq; ++lvl) p.kd_list[inc - ntq + lvl] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + lvl * p.QT};
-    if (b == N - 1) p.kd_count[0] = inc;
+    // (p.tails: a bucket's last rows, if they are at most 64, behind everything else.  P is small then: one sum for both)
+    const int small = p.tails && end_rows > 0 && end_rows <= 64, big = ntq - small;
+    const int both = inclusive_scan(small << 20 | big), inc = p.tails ? both & 0xFFFFF : both, tails = p.tails ? both >> 20 : 0;
+    __shared__ int32_t bigs;
+    if (b == N - 1) {
+      bigs = inc;
+      p.kd_count[0] = inc + tails;
+      p.kd_count[1] = inc;
+    }
+    if (p.tails) __syncthreads();
+    if (b < N) {
+      for (int lvl = 0; lvl < big; ++lvl) p.kd_list[inc - big + lvl] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + lvl * p.QT};
+      if (small) p.kd_list[bigs + tails - 1] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + big * p.QT};
+    }
   } else if (N >= 16) {
     auto member_rank = [&](int grp, int pos) { return 8 * pos + ((pos & 1) ? 7 - grp : grp); };
     // For lists that one workgroup per CU walks in rounds (parts): the same number of tiles for every XCD, and how those of a
@@ -975,6 +985,7 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
   PlanArgs a = {};
   a.offsets = offsets; a.perm = perm;
   a.wide = !use_narrow(s);
+  a.tails = a.wide && wide_tails(s);
   a.N = s.N; a.QT = kd_rows(s); a.cap = sc.kd_cap; a.P = P; a.k = s.k;
   a.border = sc.border; a.kd_count = sc.kd_count; a.kd_list = static_cast<KdTile*>(sc.kd_list);
   a.zero_row = reinterpret_cast<uint32_t*>(sc.zero_row);

@@ -36,14 +36,14 @@ constexpr int WK = 32;                       // K values per stage
 constexpr int W_RT = 4;                      // row tiles per scheduling group
 
 // A tile of MA x NB MFMA tiles per wavefront: 4 x 4 is the 256 x 256 one, 4 x 2 has half the B-side rows, 2 x 2 is
-// a quarter (both for what is left after the last full round of the CUs).  Fewer products per stage hide less of a
-// copy's latency, so the smaller ones keep more stages in flight, in rings of the same 160 KiB or less.
+// a quarter (both for what is left after the last full round of the CUs), 1 x 1 for a bucket's last rows (at most 64).  Fewer products
+// per stage hide less of a copy's latency, so the smaller ones keep more stages in flight, in rings of the same 160 KiB or less.
 template <int MA, int NB>
 struct WideTile {
   static constexpr int A_EDGE = 64 * MA, B_EDGE = 64 * NB;
   static constexpr int A_REGION = A_EDGE * WK * 2, B_REGION = B_EDGE * WK * 2;  // bytes of an operand in a stage
   static constexpr int STAGE = A_REGION + B_REGION;                            // 32, 24, 16 KiB
-  static constexpr int STAGES = 160 * 1024 / STAGE;                            // 5, 6, 10
+  static constexpr int STAGES = 160 * 1024 / STAGE;                            // 5, 6, 10, 20
 };
 constexpr int W_SMEM = WideTile<4, 4>::STAGES * WideTile<4, 4>::STAGE;   // 160 KiB, the whole LDS of a CU
 
@@ -73,6 +73,9 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   // (weight gradients: a slot less, for the token ids)
   constexpr int W_STAGE = Tile::STAGE, W_STAGES = OP == OP_DW ? Tile::STAGES - 1 : Tile::STAGES;
   static_assert(OP != OP_DW || W_STAGES * W_STAGE + 4 * 512 <= W_SMEM, "the token ids lie behind the ring");
+  constexpr bool SMALL = MA * NB == 1;
+  constexpr int GROUP = 4;                         // SMALL: stages between barriers
+  static_assert(!SMALL || W_STAGES % GROUP == 0, "whole groups");
   constexpr int A_CH = 8 * MA, B_CH = 8 * NB;      // 16-byte chunks of a K-row of a K-major operand
   constexpr int A_HALF = 32 * MA, B_HALF = 32 * NB;  // A-side / B-side indices of a wavefront
   const int Bs = p.Bs, d = p.d;
@@ -96,6 +99,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   // chunk lane % 4 (logical chunk = physical ^ swizzle(row)); for a K-major operand (MA = 4) K-rows
   // 2 (4 wave + j) + lane / 32, physical chunk lane % 32 (logical = physical ^ ((krow & 3) << 2)); MA = 2: K-rows
   // 4 (2 wave + j) + lane / 16, chunk lane % 16.
+  auto k_swizzle = [](int krow) { return A_CH == 8 ? (krow >> 1 & 1) << 2 : (krow & 3) << 2; };   // (MA = 1: 8 chunks)
   const uint16_t* a_ptr[MA];
   const uint16_t* b_ptr[NB];
   int a_coloff[MA], b_coloff[NB];
@@ -105,7 +109,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
     const int row = (wave * MA + j) * 16 + (lane >> 2);
     const int ch = (lane & 3) ^ ((row >> 2) & 3);
     const int krow = (64 / A_CH) * (wave * MA + j) + lane / A_CH;
-    const int kcol = ((lane & (A_CH - 1)) ^ ((krow & 3) << 2)) << 3;
+    const int kcol = ((lane & (A_CH - 1)) ^ k_swizzle(krow)) << 3;
     if (!A_TR) {
       const int u = (a0 + row < Bs) ? a0 + row : a0;
       a_ptr[j] = Aop + ((size_t)b * Bs + u) * d + ch * 8;
@@ -184,7 +188,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   // K-row 8 (g >> 1) + 4 r + (s >> 2) of the 16-row K-step; column group: natural order
   // 16 (g & 1) + 4 (s & 3) on the B side, the rho32-permuted one on the A side.
   const int g = lane >> 4, sl = lane & 15;
-  const int sw = ((sl >> 2) & 3) << 2;
+  const int sw = ((sl >> 2) & 3) << 2, sw_a = k_swizzle(sl >> 2);
   const int ag = sl & 3;
   const int acol = 4 * (4 * (ag & 1) + 2 * (g & 1) + (ag >> 1));
   const int bcol = 16 * (g & 1) + 4 * (sl & 3);
@@ -195,7 +199,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
   auto load_frag = [&](const char* st, int s, int f) -> bf16x8 {
     if (f < MA) {
       if (!A_TR) return as_bf16x8(reinterpret_cast<const uint4*>(st)[kd_slot(wm * A_HALF + f * 32 + arow, 2 * s + h)]);
-      const uint32_t ch = (uint32_t)((((wm * MA + f) * 4 + (acol >> 3)) ^ sw) * 16 + (acol & 4) * 2);
+      const uint32_t ch = (uint32_t)((((wm * MA + f) * 4 + (acol >> 3)) ^ sw_a) * 16 + (acol & 4) * 2);
       const char* base = st + s * 16 * A_CH * 16 + tr_row0 * A_CH + ch;
       return tr_read_frag(base, base + 4 * A_CH * 16);
     }
@@ -244,7 +248,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
       wait_vmcnt<0>();
     }
 #pragma unroll
-    for (int st = 0; st < W_STAGES - 1; ++st) {
+    for (int st = 0; st < (SMALL ? W_STAGES - GROUP : W_STAGES - 1); ++st) {
       if (OP == OP_DW) load_ids(kclamp(st), ids);
 #pragma unroll
       for (int j = 0; j < MA; ++j) issue_one(0, j, st, kclamp(st), ids);
@@ -252,51 +256,77 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
       for (int j = 0; j < NB; ++j) issue_one(1, j, st, kclamp(st), ids);
     }
     if (OP == OP_DW) load_ids(kclamp(W_STAGES - 1), ids);
-    wait_vmcnt<(W_STAGES - 3) * (MA + NB)>();  // issues 0 and 1 have landed (2 .. S-2 may be out)
-    __builtin_amdgcn_s_barrier();
+    if (!SMALL) {
+      wait_vmcnt<(W_STAGES - 3) * (MA + NB)>();  // issues 0 and 1 have landed (2 .. S-2 may be out)
+      __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int f = 0; f < MA; ++f) fa[0][f] = load_frag(ring, 0, f);
+      for (int f = 0; f < MA; ++f) fa[0][f] = load_frag(ring, 0, f);
 #pragma unroll
-    for (int f = 0; f < NB; ++f) fb[0][f] = load_frag(ring, 0, f + MA);
+      for (int f = 0; f < NB; ++f) fb[0][f] = load_frag(ring, 0, f + MA);
+    }
   }
-  int stage = 0;
-  for (int kt = 0; kt < nk; ++kt) {
-    const int next = (stage + 1 == W_STAGES) ? 0 : stage + 1;
-    const int fill = (stage == 0) ? W_STAGES - 1 : stage - 1;  // slot of stage kt-1 = (kt+S-1) % S
-    const char* st0 = ring + stage * W_STAGE;
-    // after the last stage the look-ahead reads the current one again: harmless
-    const char* st1 = ring + ((kt + 1 < nk) ? next : stage) * W_STAGE;
-    const int kfill = kclamp(kt + W_STAGES - 1);
+  if constexpr (SMALL) {
+    // Two products a stage: four stages between barriers, four groups of them in flight, and the copies of a group go out in front of
+    // the products of the one that has landed.
+    for (int kt = 0; kt < nk; kt += GROUP) {
+      wait_vmcnt<(W_STAGES / GROUP - 2) * GROUP * (MA + NB)>();
+      __builtin_amdgcn_s_barrier();                        // (everyone's copies, and everyone has read the group before)
+      const int at = kt % W_STAGES, into = (at == 0 ? W_STAGES : at) - GROUP;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      // half 0: multiply K-step 0, read (stage kt, K-step 1), copy the A part of issue kt+S-1;
-      // half 1: multiply K-step 1, read (stage kt+1, K-step 0), copy the B part.
-      constexpr int M = MA * NB;
-      const int copies = half ? NB : MA, c0 = M == 16 ? 8 : M - copies;   // c0: first MFMA with a copy behind it
+      for (int u = 0; u < GROUP; ++u) {
+        const int kfill = kclamp(kt + W_STAGES - GROUP + u);
+        issue_one(0, 0, into + u, kfill, ids);
+        issue_one(1, 0, into + u, kfill, ids);
+      }
 #pragma unroll
-      for (int m = 0; m < M; ++m) {
-        const int mi = m / NB, ni = m % NB;
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[half][mi], fb[half][ni], acc[mi][ni], 0, 0, 0);
-        if (m < MA + NB) {
-          const bf16x8 fr = load_frag(half ? st1 : st0, half ? 0 : 1, m);
-          if (m < MA) fa[half ^ 1][m] = fr; else fb[half ^ 1][m - MA] = fr;
-        }
-        if (m >= c0 && m < c0 + copies) {
-          issue_one(half, m - c0, fill, kfill, ids);
-        } else if (m == 12 && half == 1 && OP == OP_DW) {
-          if (((kt + W_STAGES) & 7) == 0 && kt + W_STAGES < klast) fetch_ids((kt + W_STAGES) / 8 + 1);   // (over the group read to its end)
-          load_ids(kclamp(kt + W_STAGES), ids_next);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+      for (int u = 0; u < GROUP; ++u) {
+        if (kt + u >= nk) break;                           // uniform
+        const char* st0 = ring + (at + u) * W_STAGE;
+#pragma unroll
+        for (int sx = 0; sx < 2; ++sx)
+          acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_frag(st0, sx, 0), load_frag(st0, sx, 1), acc[0][0], 0, 0, 0);
       }
     }
+  } else {
+    int stage = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+      const int next = (stage + 1 == W_STAGES) ? 0 : stage + 1;
+      const int fill = (stage == 0) ? W_STAGES - 1 : stage - 1;  // slot of stage kt-1 = (kt+S-1) % S
+      const char* st0 = ring + stage * W_STAGE;
+      // after the last stage the look-ahead reads the current one again: harmless
+      const char* st1 = ring + ((kt + 1 < nk) ? next : stage) * W_STAGE;
+      const int kfill = kclamp(kt + W_STAGES - 1);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) ids[e] = ids_next[e];
-    // own copies of stage kt+2 have landed: only issues kt+3 .. kt+S-1 (MA + NB instructions each) may
-    // be outstanding; the barrier makes everyone's visible and ends all reads of stage kt
-    wait_vmcnt<(W_STAGES - 3) * (MA + NB)>();
-    __builtin_amdgcn_s_barrier();
-    stage = next;
+      for (int half = 0; half < 2; ++half) {
+        // half 0: multiply K-step 0, read (stage kt, K-step 1), copy the A part of issue kt+S-1;
+        // half 1: multiply K-step 1, read (stage kt+1, K-step 0), copy the B part.
+        constexpr int M = MA * NB;
+        const int copies = half ? NB : MA, c0 = M == 16 ? 8 : M - copies;   // c0: first MFMA with a copy behind it
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+          const int mi = m / NB, ni = m % NB;
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[half][mi], fb[half][ni], acc[mi][ni], 0, 0, 0);
+          if (m < MA + NB) {
+            const bf16x8 fr = load_frag(half ? st1 : st0, half ? 0 : 1, m);
+            if (m < MA) fa[half ^ 1][m] = fr; else fb[half ^ 1][m - MA] = fr;
+          }
+          if (m >= c0 && m < c0 + copies) {
+            issue_one(half, m - c0, fill, kfill, ids);
+          } else if (m == 12 && half == 1 && OP == OP_DW) {
+            if (((kt + W_STAGES) & 7) == 0 && kt + W_STAGES < klast) fetch_ids((kt + W_STAGES) / 8 + 1);   // (over the group read to its end)
+            load_ids(kclamp(kt + W_STAGES), ids_next);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ids[e] = ids_next[e];
+      // own copies of stage kt+2 have landed: only issues kt+3 .. kt+S-1 (MA + NB instructions each) may
+      // be outstanding; the barrier makes everyone's visible and ends all reads of stage kt
+      wait_vmcnt<(W_STAGES - 3) * (MA + NB)>();
+      __builtin_amdgcn_s_barrier();
+      stage = next;
+    }
   }
   wait_vmcnt<0>();  // the trailing copies (repeats of the last stage) are done too
 
@@ -336,7 +366,7 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
       }
     return;
   }
-  if (OP == OP_DH || (OP == OP_UP && (ACT & 3) == 1)) {
+  if constexpr (MA > 1 && (OP == OP_DH || (OP == OP_UP && (ACT & 3) == 1))) {
     // Two outputs per value: likewise, two A-side tiles at a time (64 bf16 outputs of a row are a line), through rows of
     // 256 bytes whose 16-byte pieces are permuted by row, so that no pass of an access meets a bank twice.
     // us, low-rank pass of T 8192, d 2048, 4 blocks of 2048, k 2, ReLU: up-projection 171 -> 157, dH 183 -> 171; d 4096, blocks of
@@ -438,6 +468,22 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
             reinterpret_cast<uint4*>(p.Hact + o)[hf] = pack_bf16x8(cv);
             __builtin_amdgcn_sched_barrier(0);
           }
+        } else if (OP == OP_DH) {                          // (a bucket's last rows)
+          const size_t o = (size_t)nidx * Bs + aidx;
+#pragma unroll
+          for (int hf = 0; hf < 2; ++hf) {
+            const uint4 z = reinterpret_cast<const uint4*>(p.Hsave + o)[hf];
+            const uint32_t zw[4] = {z.x, z.y, z.z, z.w};
+            float cv[8], av[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float x = e & 1 ? hi_bf16(zw[e / 2]) : lo_bf16(zw[e / 2]);
+              cv[e] = c[8 * hf + e] * act_grad<(ACT & 1)>(x);
+              av[e] = act_fn<(ACT & 1)>(x);
+            }
+            reinterpret_cast<uint4*>(p.dHpre + o)[hf] = pack_bf16x8(cv);
+            reinterpret_cast<uint4*>(p.Hact + o)[hf] = pack_bf16x8(av);
+          }
         } else if (OP == OP_PART) {
           uint4* dst = reinterpret_cast<uint4*>(p.part + (size_t)nidx * d + aidx);
           dst[0] = make_uint4(pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3]), pack_bf16x2(c[4], c[5]),
@@ -462,14 +508,33 @@ __device__ __forceinline__ void wide_tile(const WideArgs& p, uint4* smem, int b,
 // rounds' worth of items is there.  us, before and now: T 8192, d 4096, 4 blocks of 2752, k 2: up-projection 450,
 // 373, its backward 499, 403 (385 since its outputs go out as whole lines), partial rows 376, 345; 3001 tokens of that 215, 168; 24 tokens 85, 46.
 // (Registers: all 256 and 256 of accumulators; dH with GELU and the adapters' stages keeps one in scratch, read back once an item.)
-template <int OP, int ACT>
+// TAILS: buckets' last rows, where they are at most 64, are listed behind the full tiles (kd_count[1] of those) and can go out as pieces of 64 rows x
+// 64 A-side indices, at about 0.12 of a round, instead of as tiles like the others: whichever is less.  For layers whose mean bucket is that small: us
+// a pass, 24 tokens of d 4096, 4 blocks of 2752, 2 active 87 -> 65; 100 tokens of d 2048, 4 of 2048 54 -> 44.  Larger buckets, whose tails
+// are a few of many tiles, gain nothing (8192 tokens of d 2048, 4 of 2048: 66 items on 32 CUs an XCD, or 64 and the tails, 134.5 / 134.3 -- what the chip
+// saves in a last round it has spent on its clock) and pay for the longer kernel: 700 tokens of that layer 151.9 -> 152.8.
+template <int OP, int ACT, bool TAILS>
 __global__ __launch_bounds__(256, 1) void wide_rows_kernel(WideArgs p) {
   extern __shared__ uint4 w_smem[];
   const int xcd = blockIdx.x & 7, wg = blockIdx.x >> 3, wgs = gridDim.x >> 3;
-  const int count = p.kd_count[0];
   const int a_lim = (OP == OP_PART) ? p.d : p.Bs;
   const int n_at = (a_lim + WD - 1) / WD;
   const KdTile* list = static_cast<const KdTile*>(p.kd_list);
+  int count = p.kd_count[0], first_tail = 0, pieces = 0;
+  constexpr int PIECE = 64;
+  const int n_pt = (a_lim + PIECE - 1) / PIECE;
+  if (TAILS) {
+    const int big = p.kd_count[1], grid = gridDim.x, all = (count - big) * n_pt;
+    auto rounds = [&](int tiles) {                         // in hundredths, of the fullest slice
+      const int64_t n = ((int64_t)tiles * n_at + 7) >> 3;
+      const int left = (int)(n % wgs);
+      return n / wgs * 100 + (left == 0 ? 0 : left <= wgs / 4 ? 35 : left <= wgs / 2 ? 60 : 100);
+    };
+    if (rounds(big) + 12 * ((all + grid - 1) / grid) < rounds(count)) {
+      count = first_tail = big;
+      pieces = all;
+    }
+  }
   const int64_t items = (int64_t)count * n_at;
   const int lo = (int)(items * xcd / 8), n = (int)(items * (xcd + 1) / 8) - lo;
   const int left = n % wgs, split = left > wgs / 2 ? 1 : (left > wgs / 4 ? 2 : 4), full = split > 1 ? n - left : n;
@@ -485,14 +550,20 @@ __global__ __launch_bounds__(256, 1) void wide_rows_kernel(WideArgs p) {
     locate(lo + e, t, a0);
     wide_tile<OP, ACT, 4, 4>(p, w_smem, t.bucket, a0, t.q0, 0, p.offsets[t.bucket + 1]);
   }
-  // (at most one piece per workgroup)
-  if (wg >= split * (n - full)) return;
-  locate(lo + full + wg / split, t, a0);
-  const int part = wg % split, n0 = t.q0 + (part & 1) * (WD / 2), qe = p.offsets[t.bucket + 1];
-  a0 += (part >> 1) * (WD / 2);
-  if (n0 >= qe || a0 >= a_lim) return;
-  if (split == 2) wide_tile<OP, ACT, 4, 2>(p, w_smem, t.bucket, a0, n0, 0, qe);
-  else            wide_tile<OP, ACT, 2, 2>(p, w_smem, t.bucket, a0, n0, 0, qe);
+  if (wg < split * (n - full)) {                           // (at most one piece per workgroup)
+    locate(lo + full + wg / split, t, a0);
+    const int part = wg % split, n0 = t.q0 + (part & 1) * (WD / 2), qe = p.offsets[t.bucket + 1];
+    a0 += (part >> 1) * (WD / 2);
+    if (n0 < qe && a0 < a_lim) {
+      if (split == 2) wide_tile<OP, ACT, 4, 2>(p, w_smem, t.bucket, a0, n0, 0, qe);
+      else            wide_tile<OP, ACT, 2, 2>(p, w_smem, t.bucket, a0, n0, 0, qe);
+    }
+  }
+  if (TAILS)
+    for (int e = blockIdx.x; e < pieces; e += gridDim.x) {
+      t = list[first_tail + e / n_pt];
+      wide_tile<OP, ACT, 1, 1>(p, w_smem, t.bucket, e % n_pt * PIECE, t.q0, 0, p.offsets[t.bucket + 1]);
+    }
 }
 
 // dW GEMMs: one work item (column tile, unit tile, bucket) per workgroup.  With a multiple of
@@ -521,28 +592,31 @@ __global__ __launch_bounds__(256, 1) void wide_dw_kernel(WideArgs p) {
 }
 
 template <int OP, int ACT>
-static void launch_rows(const WideArgs& a, hipStream_t st) {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(wide_rows_kernel<OP, ACT>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, W_SMEM);
+static void launch_rows(const WideArgs& a, bool tails, hipStream_t st) {
+  static const hipError_t attr[2] = {hipFuncSetAttribute(reinterpret_cast<const void*>(wide_rows_kernel<OP, ACT, false>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, W_SMEM),
+                                     hipFuncSetAttribute(reinterpret_cast<const void*>(wide_rows_kernel<OP, ACT, true>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, W_SMEM)};
   (void)attr;
-  wide_rows_kernel<OP, ACT><<<8 * 32, 256, W_SMEM, st>>>(a);
+  if (tails) wide_rows_kernel<OP, ACT, true><<<8 * 32, 256, W_SMEM, st>>>(a);
+  else       wide_rows_kernel<OP, ACT, false><<<8 * 32, 256, W_SMEM, st>>>(a);
 }
 
 hipError_t launch_wide(int op, const spt_shape_t& s, const WideArgs& a, hipStream_t st) {
-  const bool gelu = s.act == SPT_ACT_GELU;
+  const bool gelu = s.act == SPT_ACT_GELU, tails = wide_tails(s);
   switch (op) {
     case OP_UP:  // the activation code's bit 1 marks the inference forward (no Hsave), bit 2
                  // the low-rank extension of the K loop
-      if (a.Xe)         { if (gelu) launch_rows<OP_UP, 4>(a, st); else launch_rows<OP_UP, 5>(a, st); }
-      else if (a.Hsave) { if (gelu) launch_rows<OP_UP, 0>(a, st); else launch_rows<OP_UP, 1>(a, st); }
-      else              { if (gelu) launch_rows<OP_UP, 2>(a, st); else launch_rows<OP_UP, 3>(a, st); }
+      if (a.Xe)         { if (gelu) launch_rows<OP_UP, 4>(a, tails, st); else launch_rows<OP_UP, 5>(a, tails, st); }
+      else if (a.Hsave) { if (gelu) launch_rows<OP_UP, 0>(a, tails, st); else launch_rows<OP_UP, 1>(a, tails, st); }
+      else              { if (gelu) launch_rows<OP_UP, 2>(a, tails, st); else launch_rows<OP_UP, 3>(a, tails, st); }
       break;
     case OP_DH:
-      if (a.Xe) { if (gelu) launch_rows<OP_DH, 4>(a, st); else launch_rows<OP_DH, 5>(a, st); }
-      else      { if (gelu) launch_rows<OP_DH, 0>(a, st); else launch_rows<OP_DH, 1>(a, st); }
+      if (a.Xe) { if (gelu) launch_rows<OP_DH, 4>(a, tails, st); else launch_rows<OP_DH, 5>(a, tails, st); }
+      else      { if (gelu) launch_rows<OP_DH, 0>(a, tails, st); else launch_rows<OP_DH, 1>(a, tails, st); }
       break;
     case OP_PART:
-      launch_rows<OP_PART, 0>(a, st);
+      launch_rows<OP_PART, 0>(a, tails, st);
       break;
     default: {
       const int n_ct = (s.d + WD - 1) / WD, n_ut = (s.Bs + WD - 1) / WD;

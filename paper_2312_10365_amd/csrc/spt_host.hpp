@@ -119,6 +119,8 @@ struct WideArgs {
   const uint16_t* We;        //                                        [N*Bs][64] per hidden unit
 };
 enum WideOp { kWideUp = 0, kWideDH = 1, kWidePart = 2, kWideDW = 3 };
+// Buckets so small that their last rows are listed apart (wide_rows_kernel).
+inline bool wide_tails(const spt_shape_t& s) { return (int64_t)s.T * s.k <= 64 * (int64_t)s.N; }
 hipError_t launch_wide(int op, const spt_shape_t& s, const WideArgs& a, hipStream_t st);
 
 // The schedule in a buffer of its own (the layout plan_bwd carves, weight-gradient tables included),

@@ -168,3 +168,12 @@ def test_lora_launch_edges(dims):
 def test_lora_one_slab_and_parts(tiles, parts, pieces, shape):
     T, d, N, Bs, k = shape
     check_full(gen.custom_shape(T, d, N, Bs, k, seed=T + N, w_std=0.05, wr_std=0.05), 5, std=0.1)
+
+
+# Buckets of few rows: the adapters' stage of the kernel without LDS tiles (32 and 64 rows at a time), the 64-row pieces of wide blocks.
+@pytest.mark.parametrize("dims", [(60, 448, 3, 288, 2, 16), (100, 576, 4, 1056, 2, 32), (7, 256, 5, 160, 5, 3), (20, 192, 5, 96, 2, 8),
+                                  (150, 320, 4, 128, 2, 16)], ids=str)
+@pytest.mark.parametrize("act", [spt.ACT_GELU, spt.ACT_RELU])
+def test_lora_small_buckets(dims, act):
+    T, d, N, Bs, k, r = dims
+    check_full(gen.custom_shape(T, d, N, Bs, k, seed=T + N + r, act=act, w_std=0.05, wr_std=0.05), r, std=0.1)
