@@ -622,17 +622,25 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL, STAT>())) voi
 // owns 64 keys and all columns of one of the two gradients in accumulators (64-wide heads: two workgroups per CU,
 // up to 128 entries; one otherwise).  The A and dS words of a step are scattered
 // into two LDS tiles [key][query] and taken out again afterwards (only the words that were set), by
-// the wavefront that owns the query: two barriers per step.  Entries whose key is another
-// workgroup's go to dummy words behind the tile.
+// the wavefront that owns the query.  Entries whose key is another workgroup's go to dummy words behind the tile.
+// One pair of tiles: scatter, barrier, products, barrier; the matrix cores stand still while the lists are scattered, unless
+// another workgroup of the CU has products to do.  Where there is one workgroup per CU and the lists have more than 64 entries, so that
+// the scatter is a good part of a step, there are two pairs (keys_two_tiles): the lists of the next step go out among the products of
+// this one.  us, one pair and two: 128-wide heads, S 96, n 1100, L 137 267 -> 241; S 128, n 384, L 100 48 -> 44; 64-wide, S 64, n 700, L 170
+// 68 -> 61; not where a list is one vector: 128-wide, S 512, n 512, L 64 228 -> 238 (twice the tiles to clear before 16 steps).
 // 16-byte chunk c of tile row r sits at c ^ ((r >> 1) & 7): the 16 rows of a pass hit all banks.
 // What the products read is split into its three parts here: split in front of the tile (one gradient per workgroup, or the
 // tiles would not fit) the scatter, which is what a step waits for, has half as much again to do: 129 -> 166 us at 64-wide
 // heads, S 512, n 512, L 64, 259 -> 575 at 128-wide, n 1100, L 137.  128-wide heads on 16 wavefronts of 64 columns
-// split every word twice: 255 us against 227 (n 512), 270 against 259 (n 1100).
+// split every word twice: 255 us against 227 (n 512), 270 against 259 (n 1100).  The words of the next quarter are read in front
+// of the products of this one where registers allow, and a part of the weights goes through all column tiles before the next part
+// does: no product waits for the one in front of it (128-wide heads, L 64: 706 -> 697 us a training pass; L 240 572 -> 556).
 constexpr int KV_KEYS = 256, KV_Q = 32;
 constexpr int KV_TILE = KV_KEYS * KV_Q;                    // words
 constexpr int KV_TS = KV_TILE + 64;                        // ... and the 64 dummy words behind them
 constexpr int KV_FLAGS = 16;                               // bytes
+template <int DH, int LPL>
+constexpr bool keys_two_tiles() { return LPL > 2 || (DH == 128 && LPL == 2); }
 template <int DH, int LPL>
 __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ dY, const int32_t* __restrict__ idx,
@@ -641,9 +649,11 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
   constexpr int NC = DH / 8, CT = DH / 32;                 // 16-byte pieces and 32-column tiles of a row
   constexpr int QW = KV_Q / NW, EL = QW;                   // queries per wavefront; 64 / QW lanes x EL entries cover 64
   constexpr int ROWS = KV_Q * DH * 2;                      // bytes of a step's dY (then Q) rows
+  constexpr int TILES = keys_two_tiles<DH, LPL>() ? 2 : 1;
+  constexpr bool AHEAD = DH == 128 || TILES == 2;          // (registers)
   extern __shared__ uint4 kv_smem[];
-  char* smem = reinterpret_cast<char*>(kv_smem);           // A tile, dS tile, dY rows, Q rows
-  char* rows = smem + 2 * KV_TS * 4;
+  char* smem = reinterpret_cast<char*>(kv_smem);           // A tile, dS tile (of even steps, of odd ones), dY rows, Q rows
+  char* rows = smem + TILES * 2 * KV_TS * 4;
   uint32_t* steps = reinterpret_cast<uint32_t*>(rows + 2 * ROWS);   // [4] a bit for every step (n <= 4096: at most 128) that meets an infinity or a NaN
   float* words = reinterpret_cast<float*>(smem);
   // (lane roles are formed again for every step from a value the compiler cannot follow, see the rows kernel)
@@ -663,7 +673,7 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
   A += base * L;
   dS += base * L;
 
-  for (uint32_t e = tid; e < 2 * KV_TS / 4; e += NT) reinterpret_cast<uint4*>(smem)[e] = make_uint4(0u, 0u, 0u, 0u);
+  for (uint32_t e = tid; e < TILES * 2 * KV_TS / 4; e += NT) reinterpret_cast<uint4*>(smem)[e] = make_uint4(0u, 0u, 0u, 0u);
   if (tid < 4) steps[tid] = 0u;
   __syncthreads();
   const uint32_t last = min(KV_KEYS, n - key0);
@@ -705,30 +715,36 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
       }
     }
   };
-  uint32_t old[LPL][EL / 2];                               // the words this lane has set, two to a register
+  uint32_t old[TILES][LPL][EL / 2];                        // the words this lane has set, two to a register
 #pragma unroll
-  for (int v = 0; v < LPL; ++v)
-#pragma unroll
-    for (int e = 0; e < EL / 2; ++e) old[v][e] = (KV_TILE + lane) * 0x10001u;
-  auto set = [&](int v, int e) -> uint32_t { return e % 2 ? old[v][e / 2] >> 16 : old[v][e / 2] & 0xFFFFu; };
-  auto scatter = [&](int b) {
+  for (int x = 0; x < TILES; ++x)
 #pragma unroll
     for (int v = 0; v < LPL; ++v)
 #pragma unroll
-      for (int e = 0; e < EL; ++e) { words[set(v, e)] = 0.f; words[set(v, e) + KV_TS] = 0.f; }
-    const uint32_t ql = query(), lim = b * KV_Q + ql < (uint32_t)n ? last : 0;   // queries past the end have no entries
+      for (int e = 0; e < EL / 2; ++e) old[x][v][e] = (KV_TILE + lane) * 0x10001u;
+  auto clear = [&](float* words, uint32_t (&old)[LPL][EL / 2]) {
 #pragma unroll
     for (int v = 0; v < LPL; ++v)
 #pragma unroll
       for (int e = 0; e < EL; ++e) {
-        const uint32_t j = (uint32_t)(jn[v][e] - key0);
-        const uint32_t at = j * KV_Q + (((ql >> 2) ^ ((j >> 1) & 7)) << 2) + (ql & 3);
-        uint32_t to = KV_TILE + lane;
-        to = j < lim ? at : to;
-        words[to] = an[v][e];
-        words[to + KV_TS] = dn[v][e];
-        old[v][e / 2] = e % 2 ? old[v][e / 2] | to << 16 : to;
+        const uint32_t at = e % 2 ? old[v][e / 2] >> 16 : old[v][e / 2] & 0xFFFFu;
+        words[at] = 0.f;
+        words[at + KV_TS] = 0.f;
       }
+  };
+  auto scatter = [&](int b, float* words, uint32_t (&old)[LPL][EL / 2], auto from, auto to) {   // entries from .. to - 1
+    const uint32_t ql = query(), lim = b * KV_Q + ql < (uint32_t)n ? last : 0;   // queries past the end have no entries
+#pragma unroll
+    for (int x = from; x < to; ++x) {
+      const int v = x / EL, e = x % EL;
+      const uint32_t j = (uint32_t)(jn[v][e] - key0);
+      const uint32_t at = j * KV_Q + (((ql >> 2) ^ ((j >> 1) & 7)) << 2) + (ql & 3);
+      uint32_t to = KV_TILE + lane;
+      to = j < lim ? at : to;
+      words[to] = an[v][e];
+      words[to + KV_TS] = dn[v][e];
+      old[v][e / 2] = e % 2 ? old[v][e / 2] | to << 16 : to;
+    }
   };
   // What is infinite or NaN in the rows of a step, or infinite among its weights, in the registers it has arrived in: zeros
   // are multiplied in its place, and the step is marked.  (A NaN weight reaches its own key only.)
@@ -768,51 +784,103 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
       for (int v = 0; v < 16; ++v) acc[kt][ct][v] = 0.f;
 
   const int nblk = (n + KV_Q - 1) / KV_Q;
-  // vectors requested ahead of the products; the others, where registers for them are lacking, behind
   const std::integral_constant<int, 0> zero;
-  const std::integral_constant<int, DH == 64 && LPL == 2 ? 1 : LPL> early;
   const std::integral_constant<int, LPL> all;
-  request_rows(0);
-  request_lists(0, zero, all);
-  for (int b = 0; b < nblk; ++b) {
-    fresh_roles();
-    drop_not_finite(b);
-    scatter(b);
+  const std::integral_constant<int, LPL * EL> entries;
+  auto store_rows = [&]() {
 #pragma unroll
     for (int u = 0; u < RP; ++u) *reinterpret_cast<u32x4*>(rows + row_dst() + u * RQ * DH * 2) = rnext[u];
-    request_rows(b + 1);
-    request_lists(b + 1, zero, early);
-    __syncthreads();
-    if (kg * 64 < last) {                                   // uniform
-      fresh_roles();
-      uint32_t vtr[CT], wrow[2];                           // fragments of the rows; this lane's key rows in its tensor's tile
+  };
+  // The products of a step with this wavefront's 64 keys, `behind` what goes out behind each quarter of them.
+  auto products = [&](const float* words, auto behind) {
+    if (kg * 64 >= last) {                                 // uniform
+      behind(0); behind(1); behind(2); behind(3);
+      return;
+    }
+    fresh_roles();
+    uint32_t vtr[CT], wrow[2];                             // fragments of the rows; this lane's key rows in its tensor's tile
 #pragma unroll
-      for (int x = 0; x < CT; ++x) vtr[x] = t * ROWS + tr_offset<DH>(lane, x);
+    for (int x = 0; x < CT; ++x) vtr[x] = t * ROWS + tr_offset<DH>(lane, x);
 #pragma unroll
-      for (int x = 0; x < 2; ++x) wrow[x] = t * KV_TS + (kg * 64 + x * 32 + i) * KV_Q;
-      const uint32_t wsw = (i >> 1) & 7;                   // (32 and 64 rows on: the same swizzle)
+    for (int x = 0; x < 2; ++x) wrow[x] = t * KV_TS + (kg * 64 + x * 32 + i) * KV_Q;
+    const uint32_t wsw = (i >> 1) & 7;                     // (32 and 64 rows on: the same swizzle)
+    u32x4 w[2];
+    auto read_words = [&](int x) {                         // quarter x: keys 32 (x % 2) .., queries 16 (x / 2) ..
+      const u32x4* trow = reinterpret_cast<const u32x4*>(words + wrow[x % 2]);
+      w[0] = trow[(4 * (x / 2) + 2 * h) ^ wsw];
+      w[1] = trow[(4 * (x / 2) + 2 * h + 1) ^ wsw];
+    };
+    if (AHEAD) read_words(0);
 #pragma unroll
-      for (int k = 0; k < KV_Q / 16; ++k) {
-        bf16x8 rf[CT];
+    for (int k = 0; k < KV_Q / 16; ++k) {
+      bf16x8 rf[CT];
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) rf[ct] = as_bf16x8(tr_frag<DH>(rows + 16 * k * (DH * 2) + vtr[ct]));
+      for (int ct = 0; ct < CT; ++ct) rf[ct] = as_bf16x8(tr_frag<DH>(rows + 16 * k * (DH * 2) + vtr[ct]));
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-          const u32x4* trow = reinterpret_cast<const u32x4*>(words + wrow[kt]);
-          bf16x8 hi, mid, lo;
-          split_bf16x3(trow[(4 * k + 2 * h) ^ wsw], trow[(4 * k + 2 * h + 1) ^ wsw], hi, mid, lo);
+      for (int kt = 0; kt < 2; ++kt) {
+        bf16x8 hi, mid, lo;
+        if (!AHEAD) read_words(2 * k + kt);
+        split_bf16x3(w[0], w[1], hi, mid, lo);
+        if (AHEAD && k + kt < 2) read_words(2 * k + kt + 1);
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) {
-            acc[kt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf[ct], hi, acc[kt][ct], 0, 0, 0);
-            acc[kt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf[ct], mid, acc[kt][ct], 0, 0, 0);
-            acc[kt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf[ct], lo, acc[kt][ct], 0, 0, 0);
-          }
-          __builtin_amdgcn_sched_barrier(0);               // (one key tile's fragments at a time: registers)
-        }
+        for (int ct = 0; ct < CT; ++ct) acc[kt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf[ct], hi, acc[kt][ct], 0, 0, 0);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[kt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf[ct], mid, acc[kt][ct], 0, 0, 0);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[kt][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rf[ct], lo, acc[kt][ct], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);                 // (one key tile's fragments at a time: registers)
+        behind(2 * k + kt);
       }
     }
-    request_lists(b + 1, early, all);
+  };
+  request_rows(0);
+  request_lists(0, zero, all);
+  if constexpr (TILES == 2) {
+    // The lists of the next step go into the other pair of tiles among the products of this one; its rows, into the one place
+    // for them, between two barriers.
+    const std::integral_constant<int, LPL * EL / 2> half;
+    drop_not_finite(0);
+    scatter(0, words, old[0], zero, entries);
+    store_rows();
+    request_rows(1);
+    request_lists(1, zero, all);
     __syncthreads();
+    auto step = [&](int b, const float* from, float* into, uint32_t (&old)[LPL][EL / 2]) {
+      fresh_roles();
+      if (b + 1 < nblk) drop_not_finite(b + 1);
+      products(from, [&](int quarter) {
+        if (quarter == 0) clear(into, old);
+        if (quarter == 1) scatter(b + 1, into, old, zero, half);
+        if (quarter == 2) {
+          scatter(b + 1, into, old, half, entries);
+          request_lists(b + 2, zero, all);
+        }
+      });
+      __syncthreads();
+      store_rows();
+      request_rows(b + 2);
+      __syncthreads();
+    };
+    for (int b = 0; b < nblk; b += 2) {
+      step(b, words, words + 2 * KV_TS, old[1]);
+      if (b + 1 < nblk) step(b + 1, words + 2 * KV_TS, words, old[0]);
+    }
+  } else {
+    // vectors requested ahead of the products; the others, where registers for them are lacking, behind
+    const std::integral_constant<int, LPL == 2 ? 1 : LPL> early;
+    for (int b = 0; b < nblk; ++b) {
+      fresh_roles();
+      drop_not_finite(b);
+      clear(words, old[0]);
+      scatter(b, words, old[0], zero, entries);
+      store_rows();
+      request_rows(b + 1);
+      request_lists(b + 1, zero, early);
+      __syncthreads();
+      products(words, [](int) {});
+      request_lists(b + 1, early, all);
+      __syncthreads();
+    }
   }
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt) {
@@ -932,7 +1000,7 @@ hipError_t rows_by_length(const spt_mha_shape_t& s, const void* R, const void* G
 template <int DH, int LPL>
 hipError_t launch_keys_t(const spt_mha_shape_t& s, const uint16_t* Q, const uint16_t* dY, const int32_t* idx,
                          const float* A, const float* dS, uint16_t* dK, uint16_t* dV, hipStream_t st) {
-  const size_t lds = 2 * KV_TS * 4 + 2 * KV_Q * DH * 2 + KV_FLAGS;
+  const size_t lds = (keys_two_tiles<DH, LPL>() ? 4 : 2) * KV_TS * 4 + 2 * KV_Q * DH * 2 + KV_FLAGS;
   static bool attr_set = false;
   if (!attr_set) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(mha_keys_kernel<DH, LPL>),

@@ -215,6 +215,14 @@ def test_attention_several_chunks(n, dh, L):
     test_whole_path_matches_oracle(custom_mha_shape(1, 1, n, dh, L, seed=n + L))
 
 
+# The keys kernel's two pairs of tiles (lists of more than 64 entries at 128 columns, of more than 128 at 64): an odd and an even number of steps
+# of 32 queries, a last one of one query, wavefronts and whole parts with few keys or none.
+@pytest.mark.parametrize("n,dh,L", [(66, 128, 65), (97, 128, 66), (128, 128, 128), (257, 128, 129), (289, 128, 193), (130, 64, 129),
+                                    (160, 64, 160), (257, 64, 193), (577, 64, 255)])
+def test_key_gradients_by_steps(n, dh, L):
+    test_whole_path_matches_oracle(custom_mha_shape(1, 2, n, dh, L, seed=n + L))
+
+
 def test_backward_is_deterministic_and_workspace_reusable():
     sh = custom_mha_shape(2, 2, 200, 64, 40, seed=21)
     inp = make_mha_inputs(sh)

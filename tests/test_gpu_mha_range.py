@@ -117,3 +117,14 @@ def test_outliers_stay_where_they_are_kept(n, dh, L, value):
         t = {y: v.copy() for y, v in base.items()}
         t[x][0, row, 5], t[x][1, row, 5] = value, -value
         check_all(*(run(base, idx, dh ** -0.5, t) if x in "QK" else run(t, idx, dh ** -0.5)))
+
+
+# In the keys kernel's first, odd, even and last steps, where the next one's operands are looked at among the products of the one before.
+@pytest.mark.parametrize("n,dh,L", [(97, 128, 66), (225, 64, 140)])
+@pytest.mark.parametrize("row", [0, 31, 32, 64, 95, 96])
+def test_outliers_of_any_step(n, dh, L, row):
+    rng, base, idx = make(n, dh, L, 53)
+    for x in ("dY", "Q"):
+        t = {y: v.copy() for y, v in base.items()}
+        t[x][0, row, 5], t[x][1, row, 6] = np.inf, np.nan
+        check_all(*(run(base, idx, dh ** -0.5, t) if x == "Q" else run(t, idx, dh ** -0.5)))
