@@ -88,22 +88,85 @@ __device__ __forceinline__ void plan_position(const PlanArgs& p, const int32_t* 
     for (int r = rq + 1; r <= p.nr; ++r) p.starts[(size_t)r * p.N + b] = q + 1;
 }
 
+// The same for all positions of a batch of few pairs by one workgroup, Q per thread (products below 2^31: quotients by a multiplication
+// are exact), and the run records of the K = Bs kernel, for which the table stays in LDS if it fits.
+constexpr int kAllPairs = 4096, kAllTable = 10240;
+template <int Q>
+__device__ __forceinline__ void plan_positions(const PlanArgs& p, int32_t* off_sh) {
+  __shared__ int32_t sm_table[kAllTable];
+  auto over = [](uint32_t x, uint32_t y_inv) { return (int)((uint64_t)x * y_inv >> 31); };
+  const uint32_t k_inv = (0x80000000u + p.k - 1) / p.k, r_inv = p.R > 0 ? (0x80000000u + p.R - 1) / p.R : 0u;
+  const int N = p.N, q0 = threadIdx.x;
+  int at[Q], before[Q], lo[Q];
+#pragma unroll
+  for (int x = 0; x < Q; ++x) {
+    const int q = min(q0 + x * 1024, p.P - 1);
+    at[x] = p.perm[q];
+    before[x] = p.perm[max(q - 1, 0)];
+    lo[x] = 0;
+  }
+  for (int e = q0; e <= N; e += 1024) off_sh[e] = p.offsets[e];
+#pragma unroll
+  for (int x = 0; x < Q; ++x) {
+    at[x] = over(at[x], k_inv);
+    before[x] = over(before[x], k_inv);
+    if (q0 + x * 1024 < p.P) p.tok[q0 + x * 1024] = at[x];
+  }
+  if (p.R <= 0) return;
+  __syncthreads();
+  for (int step = 1 << (31 - __clz(N)); step; step >>= 1)   // bucket of q: the largest b with offsets[b] <= q
+#pragma unroll
+    for (int x = 0; x < Q; ++x) {
+      const int mid = lo[x] + step;
+      if (off_sh[min(mid, N)] <= q0 + x * 1024 && mid < N) lo[x] = mid;
+    }
+  auto runs = [&](int32_t* table) {
+    for (int e = q0; e < N; e += 1024)        // an empty bucket has no row to write its table column
+      if (off_sh[e] == off_sh[e + 1])
+        for (int r = 0; r <= p.nr; ++r) table[r * N + e] = off_sh[e];
+#pragma unroll
+    for (int x = 0; x < Q; ++x) {
+      const int q = q0 + x * 1024, b = lo[x];
+      if (q >= p.P) break;
+      const int rq = over(at[x], r_inv), rprev = q > off_sh[b] ? over(before[x], r_inv) : -1;
+      for (int r = rprev + 1; r <= rq; ++r) table[r * N + b] = q;
+      if (q + 1 == off_sh[b + 1])
+        for (int r = rq + 1; r <= p.nr; ++r) table[r * N + b] = q + 1;
+    }
+    __syncthreads();
+    for (int r = q0 >> 6; r < p.nr; r += 16) compact_runs(table, N, p.run_cap, p.run_rows, p.runs, p.nruns, r, q0 & 63);
+  };
+  if ((p.nr + 1) * N <= kAllTable) runs(sm_table);
+  else runs(p.starts);
+}
+
 // Workgroup 0 builds the row tiles' lists over the buckets, workgroup 1 the pieces of the weight gradients (one after the
 // other in one workgroup they were the length of the launch; us: 8192 tokens, 128 blocks, 32 each 10.8 -> 8.8; 16384, 64, 16
-// 9.6 -> 7.7; 2048, 32, 8 6.1 -> 5.1), the others take 1024 sorted positions each; kAll: one workgroup does everything, the
-// run lists of the K = Bs kernel included (few pairs: a launch of the path then costs more than the work in it).
-template <bool kAll>
+// 9.6 -> 7.7; 2048, 32, 8 6.1 -> 5.1), the others take 1024 sorted positions each; kAll: one workgroup takes them all, and the
+// run lists of the K = Bs kernel after them (few pairs: a launch of the path then costs more than the work in it).
+template <int Q>
 __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
+  constexpr bool kAll = Q > 0;
   __shared__ int32_t off_sh[1025];
   const int N = p.N;
+  if constexpr (kAll) {
+    if (blockIdx.x == 2) {
+      plan_positions<Q>(p, off_sh);
+      return;
+    }
+  }
   for (int e = threadIdx.x; e <= N; e += 1024) off_sh[e] = p.offsets[e];
   __syncthreads();
+  if (!kAll && blockIdx.x == 0 && p.R > 0)     // an empty bucket has no row to write its table column
+    for (int e = threadIdx.x; e < N; e += 1024)
+      if (off_sh[e] == off_sh[e + 1])
+        for (int r = 0; r <= p.nr; ++r) p.starts[(size_t)r * N + e] = off_sh[e];
   if (!kAll && blockIdx.x > 1) {
     const int q = (blockIdx.x - 2) * 1024 + threadIdx.x;
     if (q < p.P) plan_position(p, off_sh, q);
     return;
   }
-  const bool lists = kAll || blockIdx.x == 0, cuts = p.dw_pieces && (kAll || blockIdx.x == 1);
+  const bool lists = blockIdx.x == 0, cuts = p.dw_pieces && blockIdx.x == 1;
   if (!lists && !cuts) return;
   __shared__ int32_t wtot[16];
   if (lists && threadIdx.x < 64) p.zero_row[threadIdx.x] = 0u;  // 256 bytes of zeros for padded K rows
@@ -112,8 +175,6 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
   const int b = threadIdx.x;
   const int off = (b < N) ? off_sh[b] : 0;
   const int m = (b < N) ? off_sh[b + 1] - off : 0;
-  if (lists && p.R > 0 && b < N && m == 0)   // an empty bucket has no row to write its table column
-    for (int r = 0; r <= p.nr; ++r) p.starts[(size_t)r * N + b] = off;
 
   auto inclusive_scan = [&](int v) {
     int total;
@@ -326,14 +387,6 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     if (b < 8) {
       const int left = total - b * per;
       p.kd_count[b] = left < 0 ? 0 : (left < per ? left : per);
-    }
-  }
-  if (kAll) {
-    for (int q = threadIdx.x; q < p.P; q += 1024) plan_position(p, off_sh, q);
-    if (p.R > 0) {
-      __syncthreads();   // (the table is this workgroup's own)
-      for (int r = threadIdx.x >> 6; r < p.nr; r += 16)
-        compact_runs(p.starts, N, p.run_cap, p.run_rows, p.runs, p.nruns, r, threadIdx.x & 63);
     }
   }
 }
@@ -995,15 +1048,17 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
     a.runs = scatter_runs(sp, sc.rstart); a.nruns = scatter_counts(sp, sc.rstart); a.run_cap = sp.cap; a.run_rows = sp.run_rows;
   }
   a.dw_rows = sc.dw_rows; a.dw_cap = sc.dw_cap; a.dw_pieces = sc.dw_pieces; a.dw_xlist = sc.dw_xlist;
-  // One workgroup for everything where its chain of phases, whose length grows with the positions and the runs, is at most a launch longer: a
-  // pass that is waited for takes 5 to 7 us more with the second launch, one among others nothing.  us in a graph, one workgroup /
-  // several: tables with the weight gradients' pieces, 1024 pairs 7.7 / 6.8, 2048 8.9 / 6.9, 4096 11.3 / 6.9, 6144 13.7 / 7.0, 8192 16.9 / 7.1 (32
-  // blocks; 128 blocks 12.9 / 8.0 for 4096, 18.8 / 8.2 for 8192); a forward pass 23.7 / 23.7, 26.2 / 24.9, 32.3 / 28.6, 36.6 / 30.5, 41.4 / 31.7.
-  const bool all = P <= 4096;
+  // One launch, three workgroups side by side (lists; pieces; positions, then run records), where the one that takes all positions is
+  // less than a second launch.  us a pass, one launch / two: 6144 pairs in 32 blocks 60.1 / 58.2; 8000 in 16 57 / 55; 16384 in 32 103 / 97; 4096 in 32 34.2 / 36.
+  // (The three one after the other in one workgroup, quotients by division, the run starts in memory: the launch 8.6 against 4.8; passes of 512 tokens,
+  // d 256, 16 blocks of 64, 4 each 41.3 -> 37.0; 24 tokens, d 4096, 128 of 128, 32 each 79.7 -> 76.6; 100 tokens, d 1024, 128 of 128, 40 each
+  // 52.2 -> 45.7; 512 tokens, d 512, 32 of 64, 8 each, forward 39.0 -> 34.2.  Two positions a thread where four are not needed: 0.8 %.)
+  const bool all = P <= kAllPairs;
   {
     ScopedKernelTimer tm(kSlotPlan, st);
-    if (all) plan_kernel<true><<<1, 1024, 0, st>>>(a);
-    else plan_kernel<false><<<2 + (P + 1023) / 1024, 1024, 0, st>>>(a);
+    if (P <= 2048) plan_kernel<2><<<3, 1024, 0, st>>>(a);
+    else if (all) plan_kernel<kAllPairs / 1024><<<3, 1024, 0, st>>>(a);
+    else plan_kernel<0><<<2 + (P + 1023) / 1024, 1024, 0, st>>>(a);
   }
   SPT_LAUNCH_CHECK();
   if (sc.rstart && !all) {

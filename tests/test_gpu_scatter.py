@@ -132,3 +132,13 @@ def test_tokens_out_of_order_end(T, d, N, Bs, k, kind):
     assert torch.isfinite(Y.float()).all()
     again, _ = spt.routed_ffn_fwd(shape, X, W1, W2, offsets, perm, inv)
     assert torch.equal(again, right)
+
+
+# The tables of a batch of few pairs by three workgroups: two and four positions per thread, their ends, the run starts in LDS and (many
+# blocks times ranges) in memory, empty buckets, one block.
+@pytest.mark.parametrize("T,d,N,Bs,k,kind", [(1, 64, 1, 32, 1, "even"), (37, 64, 3, 64, 3, "even"), (2047, 64, 5, 32, 1, "few"),
+                                             (683, 128, 16, 32, 3, "few"), (1024, 64, 17, 64, 2, "full"), (293, 64, 64, 32, 7, "steps"),
+                                             (4095, 64, 700, 32, 1, "few"), (4096, 128, 33, 32, 1, "steps"), (1365, 64, 1000, 32, 3, "even"),
+                                             (4097, 64, 700, 32, 1, "few"), (4, 256, 1024, 32, 1024, "even")])
+def test_tables_of_few_pairs(T, d, N, Bs, k, kind):
+    run(T, d, N, Bs, k, kind)
