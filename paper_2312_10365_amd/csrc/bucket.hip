@@ -166,7 +166,10 @@ __global__ __launch_bounds__(1024) void bucket_scatter_kernel(
 }
 
 // All pairs by one workgroup: the (block x token) bitmask of the whole batch, bits before each of its words, and
-// the block totals' prefix all sit in LDS.
+// the block totals' prefix all sit in LDS.  A thread has Q pairs, loaded before the masks are cleared; P k < 2^31, so that a pair's token is
+// exact as a product.  (Loaded twice, divisions, eight of them whatever P: us a pass of 512 tokens in 32 blocks, 8 each 34.2, now 33.5; of 24 tokens in 128, 32
+// each 76.7, 76.1.)
+template <int Q>
 __global__ __launch_bounds__(1024) void bucket_small_kernel(const int32_t* __restrict__ idx, int T, int N, int k,
                                                             int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
                                                             int32_t* __restrict__ inv) {
@@ -176,17 +179,16 @@ __global__ __launch_bounds__(1024) void bucket_small_kernel(const int32_t* __res
   uint16_t* pre = reinterpret_cast<uint16_t*>(mask + N * nwp);
   int32_t* tot = reinterpret_cast<int32_t*>(pre + ((N * nwp + 1) & ~1));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint32_t k_inv = (0x80000000u + k - 1) / k;
+  int held[Q], tok[Q];
+#pragma unroll
+  for (int u = 0; u < Q; ++u) held[u] = tid + u * 1024 < P ? idx[tid + u * 1024] : -1;
   for (int e = tid; e < N * nwp; e += 1024) mask[e] = 0u;
   __syncthreads();
-  for (int p0 = tid; p0 < P; p0 += 8 * 1024) {
-    int bv[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) bv[u] = p0 + u * 1024 < P ? idx[p0 + u * 1024] : -1;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = (p0 + u * 1024) / k;
-      if (bv[u] >= 0 && bv[u] < N) atomicOr(&mask[bv[u] * nwp + (t >> 5)], 1u << (t & 31));
-    }
+  for (int u = 0; u < Q; ++u) {
+    tok[u] = (int)((uint64_t)(uint32_t)(tid + u * 1024) * k_inv >> 31);
+    if (held[u] >= 0 && held[u] < N) atomicOr(&mask[held[u] * nwp + (tok[u] >> 5)], 1u << (tok[u] & 31));
   }
   __syncthreads();
   // 2^seg lanes over the words of a block (all 64 from 33 words on), as many blocks side by side as a wavefront then holds: few
@@ -215,19 +217,14 @@ __global__ __launch_bounds__(1024) void bucket_small_kernel(const int32_t* __res
   if (tid < N) { tot[tid] = off; offsets[tid] = off; }
   if (tid == 0) offsets[N] = total;
   __syncthreads();
-  for (int p0 = tid; p0 < P; p0 += 4 * 1024) {
-    int bv[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) bv[u] = p0 + u * 1024 < P ? idx[p0 + u * 1024] : -1;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int p = p0 + u * 1024, b = bv[u];
-      if (b < 0 || b >= N) continue;
-      const int t = p / k, w = b * nwp + (t >> 5);
-      const int q = tot[b] + pre[w] + __popc(mask[w] & ((1u << (t & 31)) - 1u));
-      perm[q] = p;
-      inv[p] = q;
-    }
+  for (int u = 0; u < Q; ++u) {
+    const int b = held[u], t = tok[u];
+    if (b < 0 || b >= N) continue;
+    const int w = b * nwp + (t >> 5);
+    const int q = tot[b] + pre[w] + __popc(mask[w] & ((1u << (t & 31)) - 1u));
+    perm[q] = tid + u * 1024;
+    inv[tid + u * 1024] = q;
   }
 }
 
@@ -261,9 +258,12 @@ hipError_t run_bucket(const spt_shape_t& s, const int32_t* idx, int32_t* offsets
   // 16384 13.0 / 7.5 (16 blocks, 4 each); 4096 6.5 / 9.8, 8192 9.5 / 9.9, 12288 13.8 / 10.2 (128, 32); 8192 11.0 / 7.6, 12288 17.0 / 7.8 (128, 8).
   const size_t nwp = ((s.T + 31) / 32) | 1;
   const size_t small = (size_t)s.N * nwp * 4 + ((size_t)s.N * nwp + 1) / 2 * 4 + (size_t)s.N * 4;
-  if ((int64_t)s.T * s.k <= 8192 && small <= 60 * 1024) {
+  const int64_t P = (int64_t)s.T * s.k;
+  if (P <= 8192 && small <= 60 * 1024) {
     ScopedKernelTimer tm(kSlotBucketScatter, st);
-    bucket_small_kernel<<<1, 1024, small, st>>>(idx, s.T, s.N, s.k, offsets, perm, inv);
+    if (P <= 2048) bucket_small_kernel<2><<<1, 1024, small, st>>>(idx, s.T, s.N, s.k, offsets, perm, inv);
+    else if (P <= 4096) bucket_small_kernel<4><<<1, 1024, small, st>>>(idx, s.T, s.N, s.k, offsets, perm, inv);
+    else bucket_small_kernel<8><<<1, 1024, small, st>>>(idx, s.T, s.N, s.k, offsets, perm, inv);
     return hipGetLastError();
   }
   const int nchunks = (s.T + kBucketChunkTokens - 1) / kBucketChunkTokens;

@@ -522,6 +522,12 @@ def test_bucketing_by_one_workgroup(T, N, k):
     check_bucket(dv, idx, g_idx, f"one workgroup T{T} N{N}")
 
 
+# ... with two, four and eight pairs a thread.
+@pytest.mark.parametrize("T,N,k", [(2047, 3, 1), (2048, 3, 1), (683, 9, 3), (2048, 12, 2), (241, 40, 17), (8191, 2, 1)])
+def test_bucketing_by_one_workgroup_pairs(T, N, k):
+    test_bucketing_by_one_workgroup(T, N, k)
+
+
 # Feed-forward kernels at the edges of their launch rules.
 @pytest.mark.parametrize("dims", [
     # (T, d, N, Bs, k).  Up-projection of decoding batches: one row tile up to 24 rows a bucket, two beyond, 40 and 64
