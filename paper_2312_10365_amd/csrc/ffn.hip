@@ -36,7 +36,7 @@ namespace spt {
 //                     tiles that run together then share both the activation rows (each
 //                     token sits in k of the N buckets) and, level after level, the same few
 //                     weight blocks.  With fewer buckets the bucket-major tile sequence is
-//                     cut into 8 contiguous runs (weight reuse only).
+//                     cut into 8 contiguous runs of equal length (weight reuse only).
 //                     Wide blocks have one list, bucket-major, and its length in kd_count[0]: there
 //                     the kernel itself cuts the (row tile, A-side tile) items into 8 equal slices.
 
@@ -279,7 +279,24 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
       for (int lvl = 0; lvl < big; ++lvl) p.kd_list[inc - big + lvl] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + lvl * p.QT};
       if (small) p.kd_list[bigs + tails - 1] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + big * p.QT};
     }
-  } else if (N >= 16) {
+    return;
+  }
+  // Into how many parts (1 << c) the `left` tiles of an unfilled last round go: what takes least, with s2 ends of up to 128 rows and s1 of
+  // up to 64 behind them.
+  auto cheapest_cut = [](int left, int s1, int s2) {
+    int best = 0, least = 0;
+    for (int c = 0; (left || s2) && c < 3; ++c) {
+      const int big = left << c, mid = c == 2 ? 0 : s2, n = big + (c == 2 ? 2 * s2 : s2) + s1;
+      int cost = 0;
+      for (int at = 0; at < n; at += 32) {
+        const int cls = at < big ? c : at < big + mid ? 1 : 2;
+        cost += max(kPartAlone[cls], kPartShare[cls] * min(32, n - at));
+      }
+      if (c == 0 || cost < least) { least = cost; best = c; }
+    }
+    return best;
+  };
+  if (N >= 16) {
     auto member_rank = [&](int grp, int pos) { return 8 * pos + ((pos & 1) ? 7 - grp : grp); };
     // For lists that one workgroup per CU walks in rounds (parts): the same number of tiles for every XCD, and how those of a
     // last, unfilled round are cut.
@@ -310,17 +327,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
         surplus0[b] = sur; gap0[b] = gap;
         if (b == 7) gap0[8] = 0x7FFFFFFF;
         const int hv = mine >= most ? most : mine + max(0, min(all - gap, most - mine));
-        int best = 0, least = 0;
-        const int left = hv % 32, s1 = shorts[b][0], s2 = shorts[b][1];
-        for (int c = 0; (left || s2) && c < 3; ++c) {
-          const int big = left << c, mid = c == 2 ? 0 : s2, n = big + (c == 2 ? 2 * s2 : s2) + s1;
-          int cost = 0;
-          for (int at = 0; at < n; at += 32) {
-            const int cls = at < big ? c : at < big + mid ? 1 : 2;
-            cost += max(kPartAlone[cls], kPartShare[cls] * min(32, n - at));
-          }
-          if (c == 0 || cost < least) { least = cost; best = c; }
-        }
+        const int left = hv % 32, s1 = shorts[b][0], s2 = shorts[b][1], best = cheapest_cut(left, s1, s2);
         have[b] = hv;
         cut[b] = best;
         p.kd_count[b] = hv - left + (left << best) + (best == 2 ? 2 * s2 : s2) + s1;
@@ -374,19 +381,34 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     }
   } else {
     const int inc = inclusive_scan(ntq);
-    __shared__ int32_t total_sh;
-    if (b == N - 1) total_sh = inc;
+    __shared__ int32_t tiles_to[16], part_cut[8];   // tiles up to and with those of bucket b
+    if (b < 16) tiles_to[b] = inc;
     __syncthreads();
-    const int total = total_sh;
-    const int per = (total + 7) / 8 > 0 ? (total + 7) / 8 : 1;
-    if (b < N)
-      for (int lvl = 0; lvl < ntq; ++lvl) {
-        const int t = inc - ntq + lvl;
-        p.kd_list[(size_t)(t / per) * p.cap + (t % per)] = KdTile{(uint16_t)b, (uint16_t)p.QT, off + lvl * p.QT};
-      }
+    const int total = tiles_to[N - 1];
+    // XCD x has tiles total x / 8 .. total (x + 1) / 8 - 1; of 256-row tiles, those of its last, unfilled round in parts (above; a bucket's end counts
+    // as a whole tile).  us a training pass, whole tiles dealt by one thread per bucket -> this: 8832 tokens, d 2048, 4 blocks of 128, 1 each 180 -> 151;
+    // 4352, 1024, 8 of 128, 2 113 -> 94; 2491, 2048, 15 of 64, 7 130 -> 118; 51168, 2048, 1 of 32 980 -> 963.
+    const bool in_parts = p.QT == FU_ROWS;
     if (b < 8) {
-      const int left = total - b * per;
-      p.kd_count[b] = left < 0 ? 0 : (left < per ? left : per);
+      const int n = (int)((int64_t)total * (b + 1) / 8) - (int)((int64_t)total * b / 8), left = in_parts ? n % 32 : 0;
+      const int c = cheapest_cut(left, 0, 0);
+      part_cut[b] = c;
+      p.kd_count[b] = n - left + (left << c);
+    }
+    __syncthreads();
+    for (int t = b; t < total; t += 1024) {
+      int o = 0;                                    // the tile's bucket
+      while (tiles_to[o] <= t) ++o;
+      const int x = (int)((8 * (int64_t)t + 7) / total), first = (int)((int64_t)total * x / 8);
+      const int n = (int)((int64_t)total * (x + 1) / 8) - first, at = t - first, full = in_parts ? n / 32 * 32 : n;
+      const int c = part_cut[x], rows = p.QT >> c, end = off_sh[o + 1], q = off_sh[o] + (t - (o ? tiles_to[o - 1] : 0)) * p.QT;
+      KdTile* list = p.kd_list + (size_t)x * p.cap;
+      if (at < full) {
+        list[at] = KdTile{(uint16_t)o, (uint16_t)p.QT, q};
+      } else {
+        for (int e = 0; e < 1 << c; ++e)
+          list[full + ((at - full) << c) + e] = KdTile{(uint16_t)o, (uint16_t)(q + e * rows < end ? rows : 0), q + e * rows};
+      }
     }
   }
 }
@@ -925,7 +947,8 @@ static bool use_narrow(const spt_shape_t& s) { return s.Bs <= TILE; }
 // units each) per CU at most, or a bucket has few rows and the weights are what is read.  us a pass on inputs that change, 256-row tiles (and their
 // parts) / this: training 1024 tokens, d 2048, 16 blocks of 128, 4 each (288 workgroups) 99.3 / 96.8; 300, 4096, 64 of 128, 16 (428) 211 / 202; 1000,
 // 3008, 24 of 96, 8 (411) 150 / 146; 2048, 4096, 16 of 128, 4 (544) 182 / 189; 1500, 768, 32 of 96, 8 (611) 84 / 86; 2048 of those (816) 96 / 102;
-// prefill of the 7B-like layer, 192 tokens (48 rows a bucket) 117 / 115, 256 tokens 126 / 131.
+// prefill of the 7B-like layer, 192 tokens (48 rows a bucket) 117 / 115, 256 tokens 126 / 131.  Fewer than 16 blocks: 2240 tokens, d 2048, 4 of 128, 1 each
+// (148) 84 / 79; 3712, 2048, 8 of 128, 2 (480) 111 / 111; 7648, 1024, 1 of 128 (480) 187 / 187; 4384, 512, 12 of 64, 4 (560) 80 / 85; 8832, 2048, 4 of 128, 1 (560) 151 / 160.
 // (Until both requested whole lines a third kernel had the layers between, 64-row tiles through LDS: 1024 tokens, d 1024, 32 of 128, 8: 109, now 87.)
 static bool few_rows(const spt_shape_t& s) {
   const int64_t P = (int64_t)s.T * s.k;

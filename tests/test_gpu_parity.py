@@ -588,10 +588,14 @@ TILE_EDGES = [2048, 1700, 1500, 1025, 1024, 900, 769, 768, 640, 513, 512, 511, 4
 @pytest.mark.parametrize("sizes", [TILE_EDGES + [0] * 80 + [25] * 8, [300] * 128, [256] * 80 + [90] * 48, [256] * 32 + [40] * 96],
                          ids=["edges", "ends", "halves", "quarters"])
 def test_row_tiles_of_a_last_round(sizes, Bs):
-    k, N = 8, len(sizes)
+    k = 8
     sizes = list(sizes)
     sizes[-1] += -sum(sizes) % k
-    T = sum(sizes) // k
+    check_sizes(sizes, k, Bs)
+
+
+def check_sizes(sizes, k, Bs):
+    N, T = len(sizes), sum(sizes) // k
     s = gen.custom_shape(T, 64, N, Bs, k, seed=N + Bs, act=spt.ACT_RELU if Bs == 64 else spt.ACT_GELU, w_std=0.1)
     inp = gen.make_inputs(s)
     dv = Dev(inp)
@@ -605,3 +609,20 @@ def test_row_tiles_of_a_last_round(sizes, Bs):
     for name, got, ref in (("Hsave", Hsave, oracle.to_bucket_order(oH, o_perm)), ("Y", Y, oY), ("dX", dX, odX),
                            ("dW1", dW1, odW1), ("dW2", dW2, odW2)):
         check(s.name, name, got.float().cpu().numpy(), ref)
+    return dv, offsets, perm
+
+
+# The same with fewer than 16 blocks, whose tiles are one sequence over all buckets: no last round shorter than the CUs in whole tiles
+# where parts take less.  Quarters and halves of 4, 5, 10 and 11 tiles an XCD, parts of a bucket's end without rows, an empty bucket, one bucket; 25
+# tiles, which stay whole; a round of whole tiles, and one with a tile or two of the next.
+@pytest.mark.parametrize("sizes,k,Bs,entries", [
+    ([1537, 1700, 0, 2048, 1, 1100, 900, 1026], 2, 128, 4 * 37), ([2304] * 4, 1, 128, 4 * 36), ([9001], 1, 128, 4 * 36),
+    ([1200, 1500, 1, 1700, 1264, 1280, 1345, 1300, 1290, 1400, 1320, 1408, 1000, 1409, 1413], 7, 96, 2 * 81),
+    ([5001, 4000, 2047, 3000, 4096, 4200], 3, 64, 2 * 89), ([17000, 16641, 17001], 1, 32, 200), ([32768, 32768], 1, 32, 256),
+    ([12000, 11000, 10001, 9999, 12001, 12801], 2, 32, 256 + 4 * 12)],
+                         ids=["quarters", "even", "one", "halves", "ragged", "whole", "round", "after"])
+def test_row_tiles_of_few_blocks(sizes, k, Bs, entries):
+    dv, offsets, perm = check_sizes(sizes, k, Bs)
+    at = (len(sizes) * 4 + 255) // 256 * 256                # the schedule: buckets by size, then each XCD's count of tiles
+    counts = spt.build_schedule(dv.shape, offsets, perm).view(torch.uint8)[at:at + 32].view(torch.int32).cpu().numpy()
+    assert counts.sum() == entries and counts.max() - counts.min() <= 4, counts
