@@ -54,3 +54,31 @@ def test_bucket_sizes(sizes, d, Bs):
         dh = (dy[t] @ w2[b].T) * (hb > 0)
         off = 2.0 ** -8 * dh.abs() + 2.0 * d ** 0.5 * 2.0 ** -24 * (dy[t].abs() @ w2[b].abs().T) * (hb > 0)
         near(f"dX {b}", dX[t.cuda()], dh @ w1[b], dh.abs() @ w1[b].abs(), Bs, (1 + 2.0 ** -8) * (off @ w1[b].abs()))
+
+
+# Row lists of uneven buckets, many levels deep: every row in one tile, as many tiles for one XCD as for another where that matters (64-row tiles; 256-row
+# ones with parts of a last round behind them), by threads per bucket and, from a level on, by threads per tile.
+@pytest.mark.parametrize("sizes,Bs,rows", [((3000,) + (14,) * 129, 64, 64), ((0, 3) * 64 + (1025, 1024, 700), 96, 64), ((2000, 8000) + (14,) * 600, 32, 64),
+                                           ((300,) * 20 + (1200,), 128, 64), ((1500,) + (1,) * 200, 32, 64), ((30000,) + (3,) * 519, 128, 256), ((9000, 8193, 8192) + (1,) * 20, 128, 256)],
+                         ids=lambda x: f"{len(x)}x{max(x)}" if isinstance(x, tuple) else str(x))
+def test_row_lists(sizes, Bs, rows):
+    N, T = len(sizes), sum(sizes)
+    test_bucket_sizes(sizes, 64, Bs)
+    block = np.repeat(np.arange(N), sizes).astype(np.int32)
+    shape = spt.make_shape(T, 64, N, Bs, 1, spt.ACT_RELU)
+    offsets, perm, _ = spt.bucket_tokens(shape, torch.from_numpy(block[:, None]).cuda())
+    sched = spt.build_schedule(shape, offsets, perm).view(torch.uint8).cpu().numpy()
+    # buckets by size, each XCD's count, its list of (bucket, rows, first row)
+    cap = -(-T // rows) + N + (4 * 32 + -(-N // 8) * 2 if rows == 256 else 0)
+    at = -(-N * 4 // 256) * 256
+    counts = sched[at:at + 32].view(np.int32)
+    lists = sched[at + 256:at + 256 + 64 * cap].view([("bucket", "<u2"), ("rows", "<u2"), ("q0", "<i4")]).reshape(8, cap)
+    seen = np.zeros(T, np.int32)
+    ends = offsets.cpu().numpy()
+    for x in range(8):
+        for b, m, q0 in lists[x, :counts[x]]:
+            assert m in (0, 64, 128, 256) and m <= rows and (m == 0 or ends[b] <= q0 < ends[b + 1]), (x, b, m, q0)
+            seen[q0:min(int(q0) + int(m), ends[b + 1])] += 1
+    assert (seen == 1).all()
+    if rows == 64 and -(-T // 64) * (Bs // 32) > 32:
+        assert counts.max() - counts.min() <= max(8 * -(-counts.sum() // 8) - counts.sum(), 1), counts
