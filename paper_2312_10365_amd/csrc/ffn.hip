@@ -961,13 +961,18 @@ static bool use_narrow(const spt_shape_t& s) { return s.Bs <= TILE; }
 // Narrow blocks: tiles of 64 rows, and the kernel that loads its operands straight into registers, where those are about two workgroups (32 hidden
 // units each) per CU at most, or a bucket has few rows and the weights are what is read.  us a pass on inputs that change, 256-row tiles (and their
 // parts) / this: training 1024 tokens, d 2048, 16 blocks of 128, 4 each (288 workgroups) 99.3 / 96.8; 300, 4096, 64 of 128, 16 (428) 211 / 202; 1000,
-// 3008, 24 of 96, 8 (411) 150 / 146; 2048, 4096, 16 of 128, 4 (544) 182 / 189; 1500, 768, 32 of 96, 8 (611) 84 / 86; 2048 of those (816) 96 / 102;
-// prefill of the 7B-like layer, 192 tokens (48 rows a bucket) 117 / 115, 256 tokens 126 / 131.  Fewer than 16 blocks: 2240 tokens, d 2048, 4 of 128, 1 each
-// (148) 84 / 79; 3712, 2048, 8 of 128, 2 (480) 111 / 111; 7648, 1024, 1 of 128 (480) 187 / 187; 4384, 512, 12 of 64, 4 (560) 80 / 85; 8832, 2048, 4 of 128, 1 (560) 151 / 160.
-// (Until both requested whole lines a third kernel had the layers between, 64-row tiles through LDS: 1024 tokens, d 1024, 32 of 128, 8: 109, now 87.)
+// 3008, 24 of 96, 8 (411) 150 / 146; 2048, 4096, 16 of 128, 4 (544) 182 / 189; 1500, 768, 32 of 96, 8 (611) 84 / 86; 2048 of those (816) 96 / 102.
+// Fewer than 16 blocks: 2240 tokens, d 2048, 4 of 128, 1 each (148) 84 / 79; 3712, 2048, 8 of 128, 2 (480) 111 / 111; 7648, 1024, 1 of 128 (480)
+// 187 / 187; 4384, 512, 12 of 64, 4 (560) 80 / 85; 8832, 2048, 4 of 128, 1 (560) 151 / 160.
+// From 128 blocks on, of more than 32 units, their 256-row tiles fill half the CUs themselves: up to 40 rows a bucket.  Even routing: 3840 tokens, d 4096,
+// 128 of 128, 1 each (30 rows) 537 / 532; 640, 4096, 128 of 128, 8 (40) 354 / 346; 768 of those (48) 364 / 369; 768, 1024, 128 of 64, 8 (48) 100 / 103; 7686,
+// 1024, 183 of 96, 1 (42) 326 / 334; 32 units: 897, 1664, 129, 22 161 / 155.  Skewed: 1920, 2048, 128 of 128, 2 (30) 259 / 265; 1536, 1024, 256 of 64, 8 (48)
+// 200 / 200; 790, 1600, 129 of 64, 8 (48) 143 / 148.  Prefill of the 7B-like layer, 192 tokens (48) 117 / 115, 256 tokens 126 / 131.
 static bool few_rows(const spt_shape_t& s) {
   const int64_t P = (int64_t)s.T * s.k;
-  return use_narrow(s) && (P <= 48 * (int64_t)s.N || (P + FU_ROWS_FEW / 2 * (int64_t)s.N) / FU_ROWS_FEW * (s.Bs / 32) <= 512);
+  if (!use_narrow(s)) return false;
+  return P <= 40 * (int64_t)s.N ||
+         ((s.N < 128 || s.Bs == 32) && (P + FU_ROWS_FEW / 2 * (int64_t)s.N) / FU_ROWS_FEW * (s.Bs / 32) <= 512);
 }
 static int kd_rows(const spt_shape_t& s) { return few_rows(s) ? FU_ROWS_FEW : FU_ROWS; }
 
@@ -1077,9 +1082,10 @@ static hipError_t run_plan(const spt_shape_t& s, const int32_t* offsets, const i
   a.offsets = offsets; a.perm = perm;
   a.wide = !use_narrow(s);
   a.tails = a.wide && wide_tails(s);
-  // Dealt by size rank, an XCD has of each level (the i-th tiles of all buckets) at most one tile more than another: left so where those are no more
-  // workgroups than it has CUs, which costs a small pass 0.7 us less.
-  a.spread = !a.wide && (!few_rows(s) || (s.T + FU_ROWS_FEW - 1) / FU_ROWS_FEW * (s.Bs / 32) > 32);
+  // Dealt by size rank, an XCD has of each level (the i-th tiles of all buckets) at most one tile more than another: left so where even then each
+  // workgroup has a CU, which costs a small pass 0.7 us less.  (Up to 32 workgroups more whatever there are: 993 tokens, d 2496, 66 blocks of 32, 19 each, skewed 151; spread 142.)
+  const int levels = (s.T + FU_ROWS_FEW - 1) / FU_ROWS_FEW, slices = s.Bs / 32;
+  a.spread = !a.wide && (!few_rows(s) || (levels > 1 && (max_row_tiles(s, FU_ROWS_FEW) / 8 + levels) * slices > 32));
   a.N = s.N; a.QT = kd_rows(s); a.cap = sc.kd_cap; a.P = P; a.k = s.k;
   a.border = sc.border; a.kd_count = sc.kd_count; a.kd_list = static_cast<KdTile*>(sc.kd_list);
   a.zero_row = reinterpret_cast<uint32_t*>(sc.zero_row);
