@@ -1272,6 +1272,11 @@ hipError_t run_fwd(const spt_shape_t& s, const void* X, const void* W1, const vo
   return run_combine(s, w.part, inv, Y, kSlotCombineY, st);
 }
 
+// dX and both weight gradients in one launch.
+static bool joined_backward(const spt_shape_t& s, const BwdWorkspace& w, const ScatterPlan& sp) {
+  return w.dw_stage2 && scatter_takes_dw(s, sp);
+}
+
 hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const void* W2,
                    const void* dY, const int32_t* offsets, const int32_t* perm,
                    const int32_t* inv, const void* Hsave, void* dX, float* dW1, float* dW2,
@@ -1319,7 +1324,7 @@ hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const vo
   if (e != hipSuccess) return e;
   const DwOperands ops[2] = {{dy, w.Hact, dW2, w.dw_stage}, {x, w.dHpre, dW1, w.dw_stage2}};
   const ScatterPlan sp = plan_scatter(s);
-  if (w.dw_stage2 && scatter_takes_dw(sp)) {
+  if (joined_backward(s, w, sp)) {
     ScopedKernelTimer tm(kSlotDXPart, st);   // (dX and both weight gradients)
     e = launch_scatter_dw(s, sp, w.dHpre, w1, sc, static_cast<uint16_t*>(dX), ops, st);
     return e != hipSuccess ? e : launch_dw_sum(ops, 2, sc, s.N, s.Bs, s.d, st);
@@ -1521,3 +1526,9 @@ hipError_t run_lora_bwd(const spt_shape_t& s, int r, const void* X, const void* 
 }
 
 }  // namespace spt
+
+// For tests, not declared in the header: whether a backward pass of the shape has dX and both weight gradients in one launch.
+extern "C" int spt_internal_joined_backward(const spt_shape_t* s) {
+  using namespace spt;
+  return s && use_narrow(*s) && joined_backward(*s, plan_bwd(*s, nullptr, true), plan_scatter(*s));
+}

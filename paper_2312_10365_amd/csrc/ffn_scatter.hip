@@ -667,10 +667,18 @@ hipError_t launch_scatter(const spt_shape_t& s, const ScatterPlan& p, const uint
 #undef SPT_SC
 }
 
-// Where two workgroups share a CU, so that the launch holds as much at once as the two it replaces.  us a pass, two launches and one: 512 tokens, d 256, 16
-// blocks of 64, 4 each (34 KB of slabs) 52 / 49; 1024, 1024, 32 of 128, 8 (67 KB) 110 / 101; 4096, 512, 32 of 64, 8 (67 KB) 100 / 98; with one
-// workgroup per CU 2048, 768, 32 of 96, 8 (101 KB) 105 / 107; 1500, 1024, 64 of 32, 16 (97 KB) 101 / 104.
-bool scatter_takes_dw(const ScatterPlan& p) { return p.nt == 2 && p.splits == 1 && p.smem <= 80 * 1024; }
+// Where two workgroups share a CU, so that the launch holds as much at once as the two it replaces.  us a pass, two launches and one, unless said otherwise 4 to 8
+// less over 60 layers: 512 tokens, d 256, 16 blocks of 64, 4 each (34 KB of slabs) 42 / 37; 2287, 512, 28 of 96, 12 (74 KB) 106 / 98; with one
+// workgroup per CU 573, 2752, 151 of 32, 17 (119 KB) 186 / 193; 829, 2304, 35 of 32, 6 (123 KB) 86.0 / 87.3; 1304, 1024, 40 of 32, 4 (85 KB) 73 / 73.
+// The gradients' 62 or 72 KB of LDS leave room for two of the contraction's workgroups where short ranges and narrow blocks would put three or four on a CU.  With
+// more than two for each, up to 20000 rows: 4670 tokens, d 512, 3 of 32, 1 69 / 66; 5202 rows of 1734, 1024, 6 of 32, 3 69 / 67; but 4589,
+// 448, 19 of 32, 10 103 / 108; 9775, 192, 14 of 32, 8 138 / 144; 4369, 576, 16 of 32, 9 102 / 106; and in six rounds and more the contraction is nearly all there
+// is: 10472, 512, 99 of 32, 1 141 / 145; 13494, 960, 197 of 32, 2 461 / 490.
+bool scatter_takes_dw(const spt_shape_t& s, const ScatterPlan& p) {
+  if (p.nt != 2 || p.splits != 1 || p.smem > 80 * 1024) return false;
+  const int grid = p.nr * p.nslab, regs = kScatterForms[0].wg[s.Bs / 32 - 1], lds = 160 * 1024 / p.smem;
+  return grid <= 2 * 256 || (regs < lds ? regs : lds) <= 2 || (grid <= 6 * 256 && (int64_t)s.T * s.k <= 20000);
+}
 
 template <int KS>
 static hipError_t launch_scatter_dw_t(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W,

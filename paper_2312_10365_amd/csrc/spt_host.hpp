@@ -95,7 +95,7 @@ struct DwOperands {
   float *dW, *stage;
 };
 // The same contraction and both weight-gradient GEMMs in one launch (their pieces still to be summed): short token ranges only.
-bool scatter_takes_dw(const ScatterPlan& p);
+bool scatter_takes_dw(const spt_shape_t& s, const ScatterPlan& p);
 hipError_t launch_scatter_dw(const spt_shape_t& s, const ScatterPlan& p, const uint16_t* Hin, const uint16_t* W, const Schedule& sc,
                              uint16_t* out, const DwOperands* ops, hipStream_t st);
 

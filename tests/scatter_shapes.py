@@ -32,3 +32,14 @@ LAYERS = [
 LORA_LAYERS = [
     (4, True, 6, (1306, 640, 102, 96, 3)), (6, False, 3, (974, 2944, 12, 64, 4)),
 ]
+
+# (dX and both weight gradients in one launch, tokens, columns, blocks, units, blocks per token, uneven routing): every block size, one and
+# several column tiles, ragged ones, few and many pieces; slabs of 80 KB and the next larger ones, more than two workgroups a CU and up to
+# 20000 rows, and more of either, which are launches of their own.
+JOINED = [
+    (True, 33, 192, 17, 128, 5, False), (True, 512, 256, 16, 64, 4, True), (True, 300, 320, 24, 32, 5, True),
+    (True, 777, 192, 9, 96, 3, False), (True, 1900, 448, 12, 128, 3, True), (True, 1300, 512, 12, 96, 6, True),
+    (True, 1024, 1024, 32, 128, 8, False), (True, 5000, 64, 7, 32, 2, False), (True, 1250, 1024, 20, 64, 5, False),
+    (False, 1270, 1024, 20, 64, 5, False),
+    (True, 1024, 1856, 7, 32, 3, False), (False, 1892, 1024, 57, 32, 29, False), (False, 10472, 512, 99, 32, 1, False),
+]

@@ -11,6 +11,7 @@ import pytest
 import torch
 
 from paper_2312_10365_amd import spt
+from scatter_shapes import JOINED
 
 pytestmark = pytest.mark.gpu
 
@@ -54,14 +55,10 @@ def test_bucket_sizes_around_the_groups(sizes, d, Bs):
             assert worst <= 1.0 + 2.0 ** -8, (name, b, K, worst)
 
 
-# dX and both weight gradients in one launch (short token ranges whose slabs leave a CU room for a second workgroup): every block size, one and
-# several column tiles, ragged ones, few and many pieces, and slabs of 80 KB and the next larger ones, which are launches of their own.  dX is the sum of
-# k Bs products of dHpre, rounded to bf16 like above, and rounded once more.
-@pytest.mark.parametrize("T,d,N,Bs,k,uneven", [(33, 192, 17, 128, 5, False), (512, 256, 16, 64, 4, True), (300, 320, 24, 32, 5, True),
-                                               (777, 192, 9, 96, 3, False), (1900, 448, 12, 128, 3, True), (1300, 512, 12, 96, 6, True),
-                                               (1024, 1024, 32, 128, 8, False), (5000, 64, 7, 32, 2, False), (1250, 1024, 20, 64, 5, False),
-                                               (1270, 1024, 20, 64, 5, False)])
-def test_beside_dx(T, d, N, Bs, k, uneven):
+# dX and both weight gradients in one launch (short token ranges whose slabs leave a CU room for a second workgroup), and in launches of their own;
+# tests/test_scatter_layout.py pins which layer has which.  dX is the sum of k Bs products of dHpre, rounded to bf16 like above, and rounded once more.
+@pytest.mark.parametrize("joined,T,d,N,Bs,k,uneven", JOINED)
+def test_beside_dx(joined, T, d, N, Bs, k, uneven):
     rng = np.random.default_rng(T)
     weight = np.where(np.arange(N) % 4 == 1, 1e3, 1.0) if uneven else np.ones(N)
     ids = np.sort(np.argsort(rng.exponential(size=(T, N)) / weight, axis=1)[:, :k], axis=1).astype(np.int32)

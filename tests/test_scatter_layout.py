@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 from paper_2312_10365_amd import spt
-from scatter_shapes import LAYERS, LORA_LAYERS
+from scatter_shapes import JOINED, LAYERS, LORA_LAYERS
 
 
 def layout(T, d, N, Bs, k):
@@ -67,6 +67,29 @@ def test_layers_of_the_gpu_tests(tiles, parts, pieces, shape):
 def test_layers_of_the_gpu_tests_are_all_forms():
     assert {(tiles, shape[3], parts) for tiles, parts, _, shape in LAYERS} == set(
         itertools.product((2, 4, 6, 8, 10), (32, 64, 96, 128), (False, True)))
+
+
+def joined(*layer):
+    return bool(spt.lib().spt_internal_joined_backward(ctypes.byref(spt.make_shape(*layer))))
+
+
+@pytest.mark.parametrize("one,T,d,N,Bs,k,uneven", JOINED)
+def test_layers_with_gradients_beside_dx(one, T, d, N, Bs, k, uneven):
+    assert joined(T, d, N, Bs, k) == one
+    (nt, R, nr, parts, nslab, _), _ = layout(T, d, N, Bs, k)
+    slabs = 4 * (R + 1) * 256
+    if one:
+        assert nt == 2 and parts == 1 and slabs <= 80 * 1024
+    if not one and slabs <= 80 * 1024:                           # more than two a CU: too many rows, or too many workgroups
+        assert nt == 2 and Bs <= 64 and 160 * 1024 // slabs > 2 and nr * nslab > 2 * 256 and (T * k > 20000 or nr * nslab > 6 * 256)
+
+
+def test_layers_with_gradients_beside_dx_are_all_kinds():
+    assert {x[4] for x in JOINED if x[0]} == {32, 64, 96, 128}
+    plans = [layout(*x[1:6])[0] for x in JOINED]
+    edges = [4 * (p[1] + 1) * 256 - 80 * 1024 for p in plans]
+    assert 0 in edges and 1024 in edges                          # both sides of the slabs' limit
+    assert any(x[0] and p[2] * p[4] > 2 * 256 for x, p in zip(JOINED, plans))
 
 
 # us of a launch on an MI355X under even and under skewed routing, [tiles, tokens per range, parts, even, skewed], for the quicker
