@@ -396,31 +396,38 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     }
   } else {
     const int inc = inclusive_scan(ntq);
-    __shared__ int32_t tiles_to[16], part_cut[8];   // tiles up to and with those of bucket b
+    __shared__ __align__(16) int32_t tiles_to[16];   // tiles up to and with those of bucket b (past the last bucket: all)
+    __shared__ int32_t part_cut[8];
     if (b < 16) tiles_to[b] = inc;
     __syncthreads();
     const int total = tiles_to[N - 1];
     // XCD x has tiles total x / 8 .. total (x + 1) / 8 - 1; of 256-row tiles, those of its last, unfilled round in parts (above; a bucket's end counts
     // as a whole tile).  us a training pass, whole tiles dealt by one thread per bucket -> this: 8832 tokens, d 2048, 4 blocks of 128, 1 each 180 -> 151;
     // 4352, 1024, 8 of 128, 2 113 -> 94; 2491, 2048, 15 of 64, 7 130 -> 118; 51168, 2048, 1 of 32 980 -> 963.
+    // (Products of 32 bits: below 2^25 + 16 tiles.)
     const bool in_parts = p.QT == FU_ROWS;
     if (b < 8) {
-      const int n = (int)((int64_t)total * (b + 1) / 8) - (int)((int64_t)total * b / 8), left = in_parts ? n % 32 : 0;
-      const int c = cheapest_cut(left, 0, 0);
+      const int n = total * (b + 1) / 8 - total * b / 8, left = in_parts ? n % 32 : 0, c = in_parts ? cheapest_cut(left, 0, 0) : 0;
       part_cut[b] = c;
       p.kd_count[b] = n - left + (left << c);
     }
-    __syncthreads();
+    if (in_parts) __syncthreads();
     for (int t = b; t < total; t += 1024) {
-      int o = 0;                                    // the tile's bucket
-      while (tiles_to[o] <= t) ++o;
-      const int x = (int)((8 * (int64_t)t + 7) / total), first = (int)((int64_t)total * x / 8);
-      const int n = (int)((int64_t)total * (x + 1) / 8) - first, at = t - first, full = in_parts ? n / 32 * 32 : n;
-      const int c = part_cut[x], rows = p.QT >> c, end = off_sh[o + 1], q = off_sh[o] + (t - (o ? tiles_to[o - 1] : 0)) * p.QT;
+      int o = 0, before = 0;                        // the tile's bucket, and the tiles in front of it
+#pragma unroll
+      for (int y = 0; y < 15; ++y) {
+        const int to = tiles_to[y];
+        o += to <= t;
+        before = to <= t ? to : before;
+      }
+      const int x = (int)((8u * t + 7u) / (uint32_t)total), first = total * x / 8, at = t - first;
+      const int q = off_sh[o] + (t - before) * p.QT;
+      const int full = in_parts ? (total * (x + 1) / 8 - first) / 32 * 32 : total;
       KdTile* list = p.kd_list + (size_t)x * p.cap;
       if (at < full) {
         list[at] = KdTile{(uint16_t)o, (uint16_t)p.QT, q};
       } else {
+        const int c = part_cut[x], rows = p.QT >> c, end = off_sh[o + 1];
         for (int e = 0; e < 1 << c; ++e)
           list[full + ((at - full) << c) + e] = KdTile{(uint16_t)o, (uint16_t)(q + e * rows < end ? rows : 0), q + e * rows};
       }
