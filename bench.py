@@ -40,6 +40,7 @@ def kernel_models(s, kernels=()):
         "dx_gemm": dict(bound="mfma", flops=gemm, bytes=h + w + (0 if part else act), extra=part),
         "dw2_gemm": dict(bound="mfma", flops=gemm, bytes=act + h + 2 * w),      # fp32 dW = 2 w
         "dw1_gemm": dict(bound="mfma", flops=gemm, bytes=act + h + 2 * w),
+        "dx_dw_gemm": dict(bound="mfma", flops=3 * gemm, bytes=(h + w + act) + 2 * (act + h + 2 * w)),   # small layers: one launch
         "combine_y": dict(bound="hbm", flops=0.0, bytes=act + P * 4, extra=part),
         "combine_dx": dict(bound="hbm", flops=0.0, bytes=act + P * 4, extra=part),
     }

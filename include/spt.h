@@ -225,7 +225,8 @@ const char* spt_strerror(int code);
  * inside a timed region), spt_profile_enable(0) stops (events are created on the host, lazily,
  * and recycled); spt_profile_read waits for the recorded events, adds up milliseconds and launch
  * counts per kernel slot into ms_sum[spt_profile_slots()] / launches[...] (host arrays), and
- * clears the records.  Not thread-safe; leave disabled in production. */
+ * clears the records.  A launch that does the work of several slots has one of its own or counts in the first of them: "dw2_gemm"
+ * is both weight gradients where "dw1_gemm" has no launches, "dx_dw_gemm" dX and both.  Not thread-safe; leave disabled in production. */
 int spt_profile_enable(int on);
 int spt_profile_slots(void);
 const char* spt_profile_slot_name(int slot);

@@ -1332,7 +1332,7 @@ hipError_t run_bwd(const spt_shape_t& s, const void* X, const void* W1, const vo
   const DwOperands ops[2] = {{dy, w.Hact, dW2, w.dw_stage}, {x, w.dHpre, dW1, w.dw_stage2}};
   const ScatterPlan sp = plan_scatter(s);
   if (joined_backward(s, w, sp)) {
-    ScopedKernelTimer tm(kSlotDXPart, st);   // (dX and both weight gradients)
+    ScopedKernelTimer tm(kSlotDXDW, st);
     e = launch_scatter_dw(s, sp, w.dHpre, w1, sc, static_cast<uint16_t*>(dX), ops, st);
     return e != hipSuccess ? e : launch_dw_sum(ops, 2, sc, s.N, s.Bs, s.d, st);
   }

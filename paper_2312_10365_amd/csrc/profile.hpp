@@ -10,6 +10,7 @@ enum KernelSlot {
   kSlotUp, kSlotDown, kSlotCombineY, kSlotDH, kSlotDW2, kSlotDW1, kSlotDXPart,
   kSlotCombineDX, kSlotLoraSmall, kSlotLoraGrad, kSlotBalance,
   kSlotMhaPq, kSlotMhaTopl, kSlotMhaFwd, kSlotMhaBwdQ, kSlotMhaTranspose, kSlotMhaBwdKV,
+  kSlotDXDW,   // dX and both weight gradients in one launch, and the sum of the gradients' pieces
   kNumSlots
 };
 

@@ -6,6 +6,10 @@ operands of dW2 are max(Hsave, 0) and dY as they are: what may differ from a sum
 product exact, each addition within 2^-24 of the sum of magnitudes, at most 2 sqrt(K) of them in the same direction).  dW1's
 operand dHpre is rounded to bf16 first (within 2^-8 of each value, of which K independent ones add up to at most their sum)
 after an fp32 sum of d products."""
+import importlib.util
+import os
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 import torch
@@ -94,3 +98,28 @@ def test_beside_dx(joined, T, d, N, Bs, k, uneven):
         mag[t] += dh.abs() @ w1[b].abs()
     bound = 2.0 ** -8 * ref.abs() + (1 + 2.0 ** -8) * rounded + 2.0 * (k * Bs) ** 0.5 * 2.0 ** -24 * mag + 1e-30
     assert float(((dX - ref).abs() / bound).max()) <= 1.0 + 2.0 ** -8
+
+
+# Each GEMM of a training pass is in one slot, whichever launches make them, and the benchmark's model of the slots counts all six.
+@pytest.mark.parametrize("layer", [JOINED[1][1:6], JOINED[9][1:6], (300, 64, 4, 160, 2)], ids=str)
+def test_every_gemm_in_a_slot(layer):
+    T, d, N, Bs, k = layer
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(root, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    shape = spt.make_shape(T, d, N, Bs, k, spt.ACT_RELU)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    X, dY, W1, W2 = normal(T, d), normal(T, d), normal(N, Bs, d), normal(N, Bs, d)
+    ids = torch.rand(T, N, generator=g, device="cuda").argsort(1)[:, :k].sort(1).values.int().contiguous()
+    offsets, perm, inv = spt.bucket_tokens(shape, ids)
+    spt.profile_read()
+    spt.profile_enable(True)
+    _, H = spt.routed_ffn_fwd(shape, X, W1, W2, offsets, perm, inv)
+    spt.routed_ffn_bwd(shape, X, W1, W2, dY, offsets, perm, inv, H)
+    spt.profile_enable(False)
+    timed = {n: c for n, (_, c) in spt.profile_read().items() if c}
+    models = bench.kernel_models(SimpleNamespace(P=T * k, d=d, Bs=Bs, T=T, N=N, k=k), timed)
+    assert ("dx_dw_gemm" in timed) == (layer == JOINED[1][1:6]), timed
+    assert sum(models[n]["flops"] * c for n, c in timed.items() if n in models) == 6 * 2.0 * T * k * d * Bs, timed
