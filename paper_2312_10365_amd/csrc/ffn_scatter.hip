@@ -106,7 +106,7 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
 
 // KS = Bs / 16.  NT tiles of 16 rows per record, each a slot of the unrolled loop; rows are requested RH tiles ahead.
 // LATE: the next weight slice is requested in a record's last slot, not behind its first (64 registers less).
-// WG: workgroups a CU is to hold.
+// OWN: a slab per wavefront.
 template <int KS, int NT, int RH, bool LATE, bool OWN>
 __device__ __forceinline__ void scatter_tile(
     int wg, const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
@@ -438,6 +438,7 @@ __device__ __forceinline__ void scatter_tile(
   }
 }
 
+// WG: workgroups a CU is to hold.
 template <int KS, int NT, int RH, bool LATE, int WG, bool OWN>
 __global__ __launch_bounds__(SC_THREADS, WG) void ffn_scatter_kernel(
     const uint16_t* __restrict__ Hin, const uint16_t* __restrict__ W, const RunRec* __restrict__ runs,
@@ -484,8 +485,9 @@ __global__ __launch_bounds__(256) void scatter_sum_kernel(const float* __restric
 // ------------------------------------------------------------------------------------------
 // host side
 // The kernel's forms: tiles per record, a slab per wavefront, workgroups of a CU that the registers allow and us per four records of
-// a workgroup that has its CU to itself, both by K-steps (Bs / 32).  A record takes its tiles whatever it holds, so few rows per block and
-// range want few tiles; a record's start (the slice of weights) is the larger part of a short one.
+// a workgroup that has its CU to itself, both by K-steps (Bs / 32).  A record of up to 6 tiles takes them whatever it holds, so few rows per block
+// and range want few tiles; a record's start (the slice of weights) is the larger part of a short one.  Records of 8 and 10 tiles stop behind their
+// last one; `rec` is of full ones (below).
 struct ScatterForm { int nt; bool own; int wg[4]; double rec[4]; };
 static const ScatterForm kScatterForms[] = {
     {2, true, {4, 3, 2, 2}, {.68, .80, 1.16, 1.52}},
@@ -497,8 +499,11 @@ static const ScatterForm kScatterForms[] = {
 
 // us that a launch takes with `nr` ranges of R tokens and the block list in `sp` parts, the same for even and for skewed routing.
 // Fitted to the time of 858 shapes (1 to 65536 tokens, 1 to 1024 blocks, 64 to 4096 columns, all block sizes) under even and under
-// skewed routing, 40 thousand plans timed; the plan of least cost takes 0.5 % more than the quickest timed one on average, 3.8 % at the
-// 95th percentile, 13 % at most.
+// skewed routing, 40 thousand plans timed, when records of 8 and 10 tiles still went through all their slots: the plan of least cost took 0.5 % more
+// than the quickest timed one on average, 3.8 % at the 95th percentile, 13 % at most.  With the present kernel it is 1.0, 7 and 12 % over 248 of those
+// shapes and 1.3, 7 and 38 % over 700 others (5668 plans; at most: 5.6 against 7.8 us, one block).  Constants fitted anew to half of these 948 shapes do little
+// better on the other half: 1.2 % as it is, 1.0 with a price of 8- and 10-tile records that falls with the tiles they hold, 0.9 with all constants free,
+// a launch above 40 us 2.0, 1.7 and 1.7 %: left as they are.
 // (What does not depend on the plan is in ScatterWork.  `best`: the least so far; a plan whose workgroups or bytes alone take longer, by what
 // they take at least, is not looked at further, and the records' error functions, two thirds of the search, are left out.)
 struct ScatterWork {
@@ -547,9 +552,10 @@ static ScatterPlan plan_scatter_once(const spt_shape_t& s) {
   const ScatterWork w(s);
   p.nslab = w.nslab;
   // Per form and number of parts (16 blocks or more in each) the range counts that give every CU one workgroup, two, ...; more than
-  // five are too short for parts.  Both sides, us a launch: 7B-like, 16 ranges in 10 tiles 526, 28 in 6 tiles 534, 20 in 8 tiles 556; BERT-large-like,
-  // 64 ranges in 6 tiles 97, 32 in 10 tiles 107; 10956 tokens, d 512, 92 blocks of 96, 19 each: 32 ranges in 6 tiles 68, 64 in 6 tiles 88; 32768,
-  // 1024, 128 of 32, 16: 112 ranges in 4 tiles 241, 64 in 6 tiles 260, in 8 tiles 311.
+  // five are too short for parts.  Both sides, us a launch, again and again on the same rows: 7B-like, 16 ranges in 10 tiles 457, 28 in 6 tiles 484, 20 in 8 tiles
+  // 497; 3001 tokens of it, 8 in 8 tiles 198, 12 in 6 tiles 203, 8 in 10 tiles 209; BERT-large-like, 64 ranges in 6 tiles 98, 32 in 10 tiles 101, 64 in 8 tiles
+  // 103; 10956 tokens, d 512, 92 blocks of 96, 19 each: 32 ranges in 6 tiles 59, in 8 tiles 67, in 10 tiles 70; 32768, 1024, 128 of 32, 16: 112 ranges in 4 tiles
+  // 234, 64 in 6 tiles 250, 52 in 8 tiles 297.
   double best = 1e300;
   int fits = 0;
   for (const ScatterForm& f : kScatterForms) {
