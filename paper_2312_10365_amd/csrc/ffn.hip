@@ -22,7 +22,7 @@
 namespace spt {
 
 // ------------------------------------------------------------------------------------------
-// Schedule tables, built on the device from `offsets` by one workgroup (thread b = bucket b).
+// Schedule tables, built on the device from `offsets` (plan_kernel: the row lists by one workgroup, thread b = bucket b).
 //
 // The chip has 8 XCDs with a private L2 each, and workgroups are handed to XCDs round-robin
 // by workgroup id, so "which XCD runs which tile, and when" decides what is served from L2
@@ -39,6 +39,8 @@ namespace spt {
 //                     cut into 8 contiguous runs of equal length (weight reuse only).
 //                     Wide blocks have one list, bucket-major, and its length in kd_count[0]: there
 //                     the kernel itself cuts the (row tile, A-side tile) items into 8 equal slices.
+//                     Where the mean bucket is small (wide_tails) the buckets' last tiles, if they are of
+//                     at most 64 rows, are behind all others, and kd_count[1] is how many are in front of them.
 
 constexpr int FU_ROWS = 256;      // rows of a K = d tile of narrow blocks
 // A round of K = d tiles of 256, 128 or 64 rows, one per CU of an XCD, takes as long as a tile that has the memory path for itself,

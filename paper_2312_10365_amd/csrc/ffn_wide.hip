@@ -42,7 +42,7 @@ template <int MA, int NB>
 struct WideTile {
   static constexpr int A_EDGE = 64 * MA, B_EDGE = 64 * NB;
   static constexpr int A_REGION = A_EDGE * WK * 2, B_REGION = B_EDGE * WK * 2;  // bytes of an operand in a stage
-  static constexpr int STAGE = A_REGION + B_REGION;                            // 32, 24, 16 KiB
+  static constexpr int STAGE = A_REGION + B_REGION;                            // 32, 24, 16, 8 KiB
   static constexpr int STAGES = 160 * 1024 / STAGE;                            // 5, 6, 10, 20
 };
 constexpr int W_SMEM = WideTile<4, 4>::STAGES * WideTile<4, 4>::STAGE;   // 160 KiB, the whole LDS of a CU

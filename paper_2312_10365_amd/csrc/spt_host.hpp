@@ -31,8 +31,8 @@ hipError_t bucket_static_scratch(int32_t** out);
 struct DwPiece { int32_t lo, hi, dst, pad; };
 struct Schedule {
   int32_t* border;       // [N] buckets by size, largest first
-  int32_t* kd_count;     // [8] row tiles of the K = d GEMMs per XCD
-  void* kd_list;         // [8][kd_cap] (bucket, first row) in per-XCD run order
+  int32_t* kd_count;     // [8] row tiles of the K = d GEMMs per XCD; wide blocks: [0] all, [1] those in front of the tails
+  void* kd_list;         // [8][kd_cap] (bucket, rows, first row) in per-XCD run order; wide blocks: one list
   int32_t* tok;          // [P] token id of every sorted position
   uint16_t* zero_row;    // 256 bytes of zeros (padding rows of the dW GEMMs' K dimension)
   int32_t* rstart;       // narrow blocks: per token range, the non-empty runs of bucket rows (ffn_scatter.hip)
@@ -104,8 +104,8 @@ struct WideArgs {
   const void* A;             // A-side operand (MFMA rows): W block, or the gathered activations
   const void* B;             // B-side operand: gathered activation rows, or H / dHpre
   const int32_t* offsets;
-  const int32_t* kd_count;   // number of row tiles
-  const void* kd_list;       // row tiles, bucket-major
+  const int32_t* kd_count;   // number of row tiles, and of those in front of the tails (wide_tails)
+  const void* kd_list;       // row tiles, bucket-major, the tails behind them
   const int32_t* tok;
   const int32_t* border;
   const uint16_t* zero_row;
