@@ -368,20 +368,25 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs p) {
     // As many threads per bucket as there are, a level each.  Where that would be many levels for the threads of the largest, a tile each, its bucket
     // searched for: every level is a walk through the members, one after the other.  us a training pass, threads per bucket and 64-row tiles on their bucket's
     // XCD -> this, skewed routing: 8416 tokens, d 640, 526 blocks of 64, 1 each 729 -> 367; 3692, 576, 568 of 64, 2 469 -> 274; 12288, 1024, 256 of 64, 1
-    // 490 -> 401; 6981, 448, 107 of 32, 4 184 -> 154; 256-row tiles in their place, listed so, 377, 283, 398, 158.
-    if (sm_ntq_by_rank[0] <= 4 * tpb) {
-      if (tb < N)
-        for (int lvl = b & (tpb - 1), tn = sm_ntq_by_rank[sm_rank[tb]]; lvl < tn; lvl += tpb) place(tb, lvl);
-    } else {
-      __shared__ int32_t tiles_to[1024];                   // tiles up to and with those of bucket b
+    // 490 -> 401; 6981, 448, 107 of 32, 4 184 -> 154; 256-row tiles in their place, listed so, 377, 283, 398, 158.  (One loop for both: written twice, a pass of the
+    // BERT-base-like layer took 96.8 where this takes 96.6.)
+    const bool by_tile = sm_ntq_by_rank[0] > 4 * tpb;
+    __shared__ int32_t tiles_to[1024];                     // tiles up to and with those of bucket b
+    int first = b & (tpb - 1), step = tpb, end = tb < N ? (int)sm_ntq_by_rank[sm_rank[tb]] : 0;
+    if (by_tile) {
       tiles_to[b] = inclusive_scan(ntq);
       __syncthreads();
-      for (int t = b; t < tiles_to[N - 1]; t += 1024) {
-        int o = 0;                                         // the first bucket with more
-        for (int step = 512; step; step >>= 1)
-          if (o + step <= N - 1 && tiles_to[o + step - 1] <= t) o += step;
-        place(o, t - (o ? tiles_to[o - 1] : 0));
+      first = b; step = 1024; end = tiles_to[N - 1];
+    }
+    for (int t = first; t < end; t += step) {
+      int o = tb, before = 0;
+      if (by_tile) {
+        o = 0;                                             // the first bucket with more
+        for (int by = 512; by; by >>= 1)
+          if (o + by <= N - 1 && tiles_to[o + by - 1] <= t) o += by;
+        before = o ? tiles_to[o - 1] : 0;
       }
+      place(o, t - before);
     }
     if (b < N && mine_short) {      // a bucket's end, behind the tiles: those of up to 128 rows, then of up to 64
       const int g = group_of(rank), pg = rank >> 3;
