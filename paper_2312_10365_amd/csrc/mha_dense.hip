@@ -626,8 +626,8 @@ __global__ __launch_bounds__(NT, (rows_waves_per_simd<DH, KT, LPL, STAT>())) voi
 // One pair of tiles: scatter, barrier, products, barrier; the matrix cores stand still while the lists are scattered, unless
 // another workgroup of the CU has products to do.  Where there is one workgroup per CU and the lists have more than 64 entries, so that
 // the scatter is a good part of a step, there are two pairs (keys_two_tiles): the lists of the next step go out among the products of
-// this one.  us, one pair and two: 128-wide heads, S 96, n 1100, L 137 267 -> 241; S 128, n 384, L 100 48 -> 44; 64-wide, S 64, n 700, L 170
-// 68 -> 61; not where a list is one vector: 128-wide, S 512, n 512, L 64 228 -> 238 (twice the tiles to clear before 16 steps).
+// this one.  us, one pair and two: 128-wide heads, S 96, n 1100, L 137 267 -> 241; S 128, n 384, L 100 48 -> 44; 64-wide, S 192, n 700, L 170
+// 219 -> 198; not where a list is one vector: 128-wide, S 512, n 512, L 64 228 -> 238 (twice the tiles to clear before 16 steps).
 // 16-byte chunk c of tile row r sits at c ^ ((r >> 1) & 7): the 16 rows of a pass hit all banks.
 // What the products read is split into its three parts here: split in front of the tile (one gradient per workgroup, or the
 // tiles would not fit) the scatter, which is what a step waits for, has half as much again to do: 129 -> 166 us at 64-wide
@@ -837,7 +837,10 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
   request_lists(0, zero, all);
   if constexpr (TILES == 2) {
     // The lists of the next step go into the other pair of tiles among the products of this one; its rows, into the one place
-    // for them, between two barriers.
+    // for them, between two barriers.  64-wide heads, with half of the products, look at the lists behind the first half of them and ask for those of the step after
+    // as soon as all words are out: looked at in front and asked for behind the third quarter, as 128-wide heads do, they are waited for where long
+    // lists come from memory.  us, one pair / so / this: S 156, n 1500, L 140 527 / 550 / 502; S 120, n 2048, L 130 703 / 735 / 670; S 192, n 700, L 170
+    // 219 / 217 / 198; 128-wide, S 96, n 1100, L 137 256 / 230, looked at later 238.
     const std::integral_constant<int, LPL * EL / 2> half;
     drop_not_finite(0);
     scatter(0, words, old[0], zero, entries);
@@ -847,11 +850,14 @@ __global__ __launch_bounds__(NT, DH == 64 && LPL <= 2 ? 4 : 2) void mha_keys_ker
     __syncthreads();
     auto step = [&](int b, const float* from, float* into, uint32_t (&old)[LPL][EL / 2]) {
       fresh_roles();
-      if (b + 1 < nblk) drop_not_finite(b + 1);
+      if (DH == 128 && b + 1 < nblk) drop_not_finite(b + 1);
       products(from, [&](int quarter) {
         if (quarter == 0) clear(into, old);
-        if (quarter == 1) scatter(b + 1, into, old, zero, half);
-        if (quarter == 2) {
+        if (quarter == 1) {
+          if (DH == 64 && b + 1 < nblk) drop_not_finite(b + 1);
+          scatter(b + 1, into, old, zero, half);
+        }
+        if (quarter == (DH == 64 ? 1 : 2)) {
           scatter(b + 1, into, old, half, entries);
           request_lists(b + 2, zero, all);
         }
