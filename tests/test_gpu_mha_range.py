@@ -128,3 +128,10 @@ def test_outliers_of_any_step(n, dh, L, row):
         t = {y: v.copy() for y, v in base.items()}
         t[x][0, row, 5], t[x][1, row, 6] = np.inf, np.nan
         check_all(*(run(base, idx, dh ** -0.5, t) if x == "Q" else run(t, idx, dh ** -0.5)))
+
+
+# The last steps of 64-wide heads (more than 128 entries: two pairs of tiles), of one query and of whole ones; keys of more than one workgroup.
+@pytest.mark.parametrize("n,dh,L,row", [(225, 64, 140, 191), (225, 64, 140, 192), (225, 64, 140, 224), (256, 64, 200, 223), (256, 64, 200, 255),
+                                        (289, 64, 193, 288)])
+def test_outliers_of_last_steps(n, dh, L, row):
+    test_outliers_of_any_step(n, dh, L, row)
